@@ -649,19 +649,20 @@ qrm_status qrm_create(const qrm_extractor_desc *ext, const qrm_rs_desc *rs, int 
     if (rs) {
         c->has_rs = true;
         const int q = 1 << rs->m;
-        e = hipMalloc(&c->d_tables, 1024);
+        // alpha has order q - 1: only fcr mod (q - 1) matters, and the kernels multiply it by positions in 32 bits
+        c->rs = RsParams{rs->m, q, rs->n, rs->k, rs->n - rs->k, rs->fcr % (q - 1), nullptr, 0};
+        const std::vector<uint8_t> image = rs_table_image(c->rs, exp2, lg);
+        e = hipMalloc(&c->d_tables, kKeyBytes + image.size());
         if (e != hipSuccess) { if (c->d_weights) (void)hipFree(c->d_weights); delete c; return hip_fail(nullptr, e, "hipMalloc(tables)"); }
-        e = hipMemcpy(c->d_tables, exp2.data(), exp2.size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy((uint8_t *)c->d_tables + 512, lg.data(), lg.size(), hipMemcpyHostToDevice);
+        e = hipMemcpy((uint8_t *)c->d_tables + kKeyBytes, image.data(), image.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             (void)hipFree(c->d_tables);
             if (c->d_weights) (void)hipFree(c->d_weights);
             delete c;
             return hip_fail(nullptr, e, "hipMemcpy(tables)");
         }
-        // alpha has order q - 1: only fcr mod (q - 1) matters, and the kernels multiply it by positions in 32 bits
-        c->rs = RsParams{rs->m, q, rs->n, rs->k, rs->n - rs->k, rs->fcr % (q - 1), (const uint8_t *)c->d_tables,
-                         (const uint8_t *)c->d_tables + 512};
+        c->rs.tab = (const uint8_t *)c->d_tables + kKeyBytes;
+        c->rs.tab_bytes = (int)image.size();
     }
     *out = c;
     return QRM_OK;
@@ -929,9 +930,9 @@ qrm_status qrm_set_key(qrm_ctx *c, const uint8_t *h_key, int32_t tau)
     if (tau < 0 || tau > c->rs.k * c->rs.m + 1) return fail(c, QRM_E_INVALID, "tau outside 0 .. k*m+1");
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
-    uint8_t masked[256] = {0};
+    uint8_t masked[kKeyBytes] = {0};
     for (int i = 0; i < c->rs.k; ++i) masked[i] = (uint8_t)(h_key[i] & (c->rs.q - 1));
-    e = hipMemcpy((uint8_t *)c->d_tables + 768, masked, 256, hipMemcpyHostToDevice);
+    e = hipMemcpy(c->d_tables, masked, kKeyBytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(c, e, "hipMemcpy(key)");
     c->has_key = true;
     c->key_tau = tau;
@@ -948,7 +949,7 @@ qrm_status qrm_verify_key(qrm_ctx *c, const uint8_t *d_msg, int64_t N, int32_t *
     if (!d_msg || !d_matches) return fail(c, QRM_E_INVALID, "d_msg / d_matches is NULL");
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
-    const KeyArgs key{(const uint8_t *)c->d_tables + 768, c->key_tau, d_matches, d_detected};
+    const KeyArgs key{(const uint8_t *)c->d_tables, c->key_tau, d_matches, d_detected};
     e = launch_verify(c->rs, d_msg, N, key, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "verify launch");
     return QRM_OK;
@@ -997,7 +998,7 @@ static qrm_status detect_common(qrm_ctx *c, const uint8_t *d_images, int64_t N, 
     st = run_extractor(c, (uint8_t *)slot->ws, L, src, N, tile, tile, -1, d_logits, d_bits, d_sym, c->rs.m, nullptr, true, s);
     if (st == QRM_OK) {
         KeyArgs key{};
-        if (verify) key = KeyArgs{(const uint8_t *)c->d_tables + 768, c->key_tau, d_matches, d_detected};
+        if (verify) key = KeyArgs{(const uint8_t *)c->d_tables, c->key_tau, d_matches, d_detected};
         qrm_ctx::Timed *t = time_begin(c, true, QRM_PROFILE_RS_DECODE, 0.0, s);
         e = launch_rs_decode(c->rs, d_sym, N, d_msg, d_codeword, d_nerr, key, s);
         if (e != hipSuccess) st = hip_fail(c, e, "rs_decode launch");

@@ -7,6 +7,8 @@
 
 #include "qrm_internal.h"
 
+constexpr size_t kKeyBytes = 256; // one byte per message symbol
+
 // A workspace of the context: the device memory the kernels of one caller stream work in.
 struct QrmSlot {
     bool used = false;
@@ -37,7 +39,7 @@ struct qrm_ctx {
     bool pairable = false;                // weights are prepared for the fused schedule (see qrm_create)
     // code
     qrm::RsParams rs{};
-    void *d_tables = nullptr;             // 1 KiB: antilog table, log table at 512, key symbols at 768
+    void *d_tables = nullptr;             // key symbols [kKeyBytes], then the code's table image (rs_table_image)
     bool has_key = false;
     int key_tau = 0;
     // workspaces: one per caller stream in use, plus the kernel stream of qrm_detect_host

@@ -143,6 +143,30 @@ def test_rs_decode_full_size_sets(qrm):
         ctx.close()
 
 
+@pytest.mark.parametrize("m,n,t", [(4, 12, 2), (4, 13, 2), (4, 15, 1), (8, 16, 2), (5, 17, 2), (5, 31, 1), (4, 15, 5), (6, 32, 3),
+                                   (6, 33, 5), (7, 64, 4), (7, 65, 8), (8, 128, 6), (8, 129, 1), (8, 255, 4)])
+def test_rs_decode_edges_of_the_word_layouts(qrm, m, n, t):
+    """Word counts around the runs a workgroup takes, word lengths around what a lane holds, buffers at odd and
+    at aligned addresses; bit-exact against the oracle."""
+    code = dict(m=m, prim_poly={4: 0x13, 5: 0x25, 6: 0x43, 7: 0x89, 8: 0x11D}[m], n=n, k=n - 2 * t, fcr=n % 3)
+    count = 515
+    msgs, err, _ = synth.rs_cases(60 + n, count, n, n - 2 * t, m, max_err=t + 1)
+    words = oracle.rs_encode(msgs, **code) ^ err
+    words[200:240] = synth.random_words(60 + n, 40, n, m)
+    om, oc, oe = oracle.rs_decode(words, **code)
+    ctx = qrm.Context(rs=code)
+    for N, shift in ((1, 0), (7, 1), (16, 0), (255, 2), (256, 0), (257, 3), (515, 0), (515, 1)):
+        sym = empty((N * n + shift,), torch.uint8)[shift:]
+        sym.copy_(torch.from_numpy(words[:N].reshape(-1)))
+        d_msg, d_cw = empty((N * (n - 2 * t) + shift,), torch.uint8)[shift:], empty((N * n + shift,), torch.uint8)[shift:]
+        d_ne = empty((N,), torch.int8)
+        ctx.qrm_rs_decode(sym, N, d_msg, d_cw, d_ne)
+        torch.cuda.synchronize()
+        assert np.array_equal(d_ne.cpu().numpy(), oe[:N]), (N, shift)
+        assert np.array_equal(d_msg.cpu().numpy().reshape(N, -1), om[:N]) and np.array_equal(d_cw.cpu().numpy().reshape(N, -1), oc[:N])
+    ctx.close()
+
+
 def test_rs_symbols_above_field_are_masked(qrm):
     code = dict(m=4, prim_poly=0x13, n=12, k=8, fcr=1)
     msgs, err, _ = synth.rs_cases(1, 100, 12, 8, 4)
