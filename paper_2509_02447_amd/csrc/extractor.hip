@@ -26,6 +26,7 @@
 //    average pool are linear, so nine border-aware channel sums per image are all head_kernel needs to
 //    apply the final convolution (fp32 weights), the linear layer, the threshold and the symbol packing.
 //    With a final ReLU, conv_final_kernel sums the final convolution's output in its accumulators.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -307,14 +308,50 @@ __device__ __forceinline__ void load_weight_frags(bf16x8 (&Wr)[9][C / 16], const
 //  (1) weights are bf16 on the matrix cores; the rounding residual W - bf16(W) acts on the mean
 //      activation as a constant per output channel, the only part of the rounding error that global
 //      average pooling does not wash out.  The consumer adds sum_c rsum[o][c] * mean[c] to its bias
-//      (rsum = residual summed over the 9 taps), with mean estimated from every eighth strip.
+//      (rsum = residual summed over the 9 taps), with mean estimated from every eighth strip of four
+//      rows: strips p, p + 8, .. with p = sampled_strip(strips).  A record of C sums is written per sampled
+//      piece of the image (sample_records), by whichever wavefront computes that piece; the number of pixels
+//      behind an image's records is known beforehand (MeanIn::inv_cnt).  Records exist for sampled rows
+//      only: a record per workgroup and wavefront, as many as 128 per image in a small launch and most of them
+//      zero, took a consumer longer to read (30 of a block's 42 us for 7 tiles of 128 x 128) than its matrix work.
 //  (2) the last conv (C -> n_bits, no ReLU) followed by the global average pool is linear, so it only
 //      needs, per channel of the last block's output, the sums over the whole tile, its first / last
-//      row, first / last column and four corners (9 numbers): the last block writes no activations.
-// A record is written per (image, workgroup that touched it): rec[q*C + c] sums, rec[NQ*C] = pixel count.
+//      row, first / last column and four corners (9 numbers): the last block writes no activations but a
+//      record of nine sums per (image, workgroup that touched it, wavefront): rec[q*C + c].
 // Accumulation order is fixed, so results do not depend on scheduling.
-constexpr int kStatPad = 16;
-__host__ __device__ constexpr int stat_rec(int C, int nq) { return nq * C + kStatPad; }
+__host__ __device__ constexpr int stat_rec(int C) { return 9 * C; }
+__host__ __device__ constexpr int sampled_strip(int strips) { return strips < 4 ? strips - 1 : 3; }
+
+// The sampled channel means of image n, from its mi.recs records, into dst[0 .. C) (LDS) by one wavefront: 16 bytes
+// per lane, four loads in flight, i.e. 16 (C = 64) or 32 (C = 32) records per round trip to memory.
+template <int C>
+__device__ __forceinline__ void image_means(const MeanIn &mi, int n, float *dst, int lane)
+{
+    constexpr int LPR = C / 4, RPL = 64 / LPR; // lanes per record, records per wavefront-wide load
+    const f32x4 *p = (const f32x4 *)(mi.rec + (int64_t)n * mi.recs * C) + lane % LPR;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int r0 = 0; r0 < mi.recs; r0 += 4 * RPL) {
+        f32x4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = p[min(r0 + u * RPL + lane / LPR, mi.recs - 1) * LPR];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool ok = r0 + u * RPL + lane / LPR < mi.recs;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += ok ? v[u][e] : 0.f;
+        }
+    }
+#pragma unroll
+    for (int sh = LPR; sh < 64; sh <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] += __shfl_xor(sum[e], sh);
+    if (lane < LPR) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] *= mi.inv_cnt;
+        *(f32x4 *)(dst + 4 * lane) = sum;
+    }
+}
 
 // Sum over the 32 pixel lanes of one half-wavefront with DPP lane permutes (no LDS traffic, no waits).
 // After the four butterfly steps every lane holds the sum of its row of 16 lanes; the last step adds the
@@ -371,19 +408,6 @@ __device__ __forceinline__ float reduce16_over_half(const float (&t)[16], int px
     return y;
 }
 
-// lanes with `pred` add their 16 values into this wavefront's private LDS accumulators
-__device__ __forceinline__ void lds_accumulate(float *slot16, const float (&tv)[16], bool pred)
-{
-    if (pred) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            f32x4 cur = *(f32x4 *)(slot16 + 4 * q);
-            cur[0] += tv[4 * q]; cur[1] += tv[4 * q + 1]; cur[2] += tv[4 * q + 2]; cur[3] += tv[4 * q + 3];
-            *(f32x4 *)(slot16 + 4 * q) = cur;
-        }
-    }
-}
-
 // Four values of one lane into the wavefront's accumulators with LDS add instructions that return nothing:
 // no round trip to wait for (a read-modify-write costs one per call, a dozen per step in the last block).
 // Every accumulator has one writer (one lane of one wavefront), LDS executes a wavefront's instructions in
@@ -402,13 +426,13 @@ __device__ __forceinline__ void lds_accumulate4(float *slot4, const float (&tv)[
 }
 
 // Channel sums of the RW output rows (first row yw, column x) held in `acc`, after bias `si` (this lane's
-// 16 channels) and ReLU, added to this wavefront's accumulators `my_stat` ([sum index][32 channels] floats,
-// already offset to the lane's 16 channels).  LAST = false: sum index 0 only (the whole strip).  LAST = true:
-// the nine border-aware sums of the last block: 0 all, 1 / 2 first / last row, 3 / 4 first / last column,
-// 5 .. 8 the corners (top-left, top-right, bottom-left, bottom-right).  Four channels at a time: registers
+// 16 channels) and ReLU.  LAST = false: written to the record at `dst` (global memory, already offset to the lane's
+// 16 channels).  LAST = true: the nine border-aware sums of the last block, added to this wavefront's accumulators
+// `dst` ([sum index][32 channels] floats in LDS, offset likewise): 0 all, 1 / 2 first / last row, 3 / 4 first / last
+// column, 5 .. 8 the corners (top-left, top-right, bottom-left, bottom-right).  Four channels at a time: registers
 // are scarce next to weights and accumulators.
 template <int RW, bool LAST>
-__device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const float *si, float *my_stat, int x, int yw,
+__device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const float *si, float *dst, int x, int yw,
                                                  int h, int w, int px)
 {
     const bool colok = (uint32_t)x < (uint32_t)w; // (x = -1: the column left of a wide tile's first block)
@@ -428,22 +452,24 @@ __device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const 
             for (int e = 0; e < 4; ++e) tv[e] = 0.f;
         }
         if (LAST) {
-            lds_accumulate4(my_stat + 3 * 32 + 4 * q, tv, x == 0);       // first column
-            lds_accumulate4(my_stat + 4 * 32 + 4 * q, tv, x == w - 1);   // last column
+            lds_accumulate4(dst + 3 * 32 + 4 * q, tv, x == 0);       // first column
+            lds_accumulate4(dst + 4 * 32 + 4 * q, tv, x == w - 1);   // last column
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) tv[e] = half_sum(tv[e]);
-        lds_accumulate4(my_stat + 4 * q, tv, px == kSumLane);            // whole tile (or its sampled strips)
-        if (LAST) {
+        if (!LAST) {
+            if (px == kSumLane) *(f32x4 *)(dst + 4 * q) = (f32x4){tv[0], tv[1], tv[2], tv[3]};
+        } else {
+            lds_accumulate4(dst + 4 * q, tv, px == kSumLane);        // whole tile
             if (yw == 0) { // image row 0 is this wavefront's first row
                 float rv[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) rv[e] = colok ? fmaxf(acc[0][4 * q + e] + bq[e], 0.f) : 0.f;
-                lds_accumulate4(my_stat + 5 * 32 + 4 * q, rv, x == 0);
-                lds_accumulate4(my_stat + 6 * 32 + 4 * q, rv, x == w - 1);
+                lds_accumulate4(dst + 5 * 32 + 4 * q, rv, x == 0);
+                lds_accumulate4(dst + 6 * 32 + 4 * q, rv, x == w - 1);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) rv[e] = half_sum(rv[e]);
-                lds_accumulate4(my_stat + 1 * 32 + 4 * q, rv, px == kSumLane);
+                lds_accumulate4(dst + 1 * 32 + 4 * q, rv, px == kSumLane);
             }
             if (rl >= 0 && rl < RW) {
                 float rv[4];
@@ -454,11 +480,11 @@ __device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const 
                     for (int r = 1; r < RW; ++r) a = rl == r ? acc[r][4 * q + e] : a;
                     rv[e] = colok ? fmaxf(a + bq[e], 0.f) : 0.f;
                 }
-                lds_accumulate4(my_stat + 7 * 32 + 4 * q, rv, x == 0);
-                lds_accumulate4(my_stat + 8 * 32 + 4 * q, rv, x == w - 1);
+                lds_accumulate4(dst + 7 * 32 + 4 * q, rv, x == 0);
+                lds_accumulate4(dst + 8 * 32 + 4 * q, rv, x == w - 1);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) rv[e] = half_sum(rv[e]);
-                lds_accumulate4(my_stat + 2 * 32 + 4 * q, rv, px == kSumLane);
+                lds_accumulate4(dst + 2 * 32 + 4 * q, rv, px == kSumLane);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -466,11 +492,10 @@ __device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const 
 }
 
 struct StatArgs {
-    const float *tin;   // records of the input's channel sums [n_img][in_slots][stat_rec(C,1)], or nullptr
-    int in_slots;
-    const float *rsum;  // [c_in][c_out] residual-weight sums of this layer (fp32), or nullptr
-    float *tout;        // records written by this launch [n_img][out_slots][stat_rec(C,NQ)], or nullptr
-    int out_slots;
+    MeanIn tin;         // channel sums of the input (rec null: no correction)
+    const float *rsum;  // [c_in][c_out] residual-weight sums of this layer (fp32)
+    float *tout;        // records written by this launch: MODE_MID [n_img][out_recs][C], MODE_LAST [n_img][out_recs][9 C]
+    int out_recs;       // records per image
     int per;            // tiles per workgroup: divides, or is a multiple of, the tiles of one image
 };
 
@@ -481,9 +506,8 @@ constexpr int kMidWaves = 8; // wavefronts of a conv_mid workgroup: two groups o
 
 template <int C, int MODE>
 struct MidRing {
-    static constexpr int NQ = MODE == MODE_LAST ? 9 : 1;      // sums per channel in a statistics record
     static constexpr int NSLOT = MODE == MODE_LAST ? 14 : 15; // row slots of the LDS ring (>= 12)
-    static constexpr int NSUB = kMidWaves / MidCfg<C>::NCB;   // statistics records a workgroup writes per image
+    static constexpr int NSUB = kMidWaves / MidCfg<C>::NCB;   // MODE_LAST: records a workgroup writes per image
 };
 
 // C -> C (+bias, ReLU), bf16 NHWC in / out.  One persistent workgroup of eight wavefronts per CU, two
@@ -510,16 +534,16 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
     typedef MidRing<C, MODE> R;
     constexpr int RG = 2 / K::NCB;     // row groups among the 4 wavefronts of a group
     constexpr int RW = kRows / RG;     // output rows per wavefront
-    constexpr int NQ = R::NQ, NSLOT = R::NSLOT;
+    constexpr int NSLOT = R::NSLOT;
+    constexpr int NQ = MODE == MODE_LAST ? 9 : 0; // sums per channel gathered in LDS
     constexpr int WIN = kRows + 2;     // staged rows one strip reads
     __shared__ __attribute__((aligned(1024))) uint8_t lds[NSLOT * K::ROWB];
-    __shared__ __attribute__((aligned(16))) float s_stat[kMidWaves][NQ][32]; // per wavefront, 32 channels of its block
+    __shared__ __attribute__((aligned(16))) float s_stat[kMidWaves][NQ ? NQ : 1][32]; // MODE_LAST: per wavefront, 32 channels of its block
     // bias + rounding-residual correction per image, indexed by image mod 4: it is written two phases
     // before the image's first strip is multiplied and read until one phase after its last, and an
     // image may be a single strip
     __shared__ __attribute__((aligned(16))) float s_init[4][C];
     __shared__ __attribute__((aligned(16))) float s_mean[kMidWaves][C];
-    __shared__ float s_cnt[kMidWaves];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -583,17 +607,9 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
         const int lane = pin_in_loop(tid & 63);
         const int o = w4 * OPW + lane % OPW, part = lane / OPW;
         float d = 0.f;
-        const float *tin = st.tin, *rsum = st.rsum;
-        if (tin && rsum) {
-            if (lane < C) {
-                float sum = 0.f, cnt = 0.f;
-                for (int s2 = 0; s2 < st.in_slots; ++s2) {
-                    const float *rec = tin + ((int64_t)n * st.in_slots + s2) * stat_rec(C, 1);
-                    sum += rec[lane];
-                    cnt += rec[C];
-                }
-                s_mean[wave][lane] = cnt > 0.f ? sum / cnt : 0.f;
-            }
+        const float *rsum = st.rsum;
+        if (st.tin.rec && rsum) {
+            image_means<C>(st.tin, n, s_mean[wave], lane);
 #pragma unroll 4
             for (int k = 0; k < CP; ++k) { // (little unrolling: registers are scarce here)
                 const int c = part * CP + k;
@@ -604,11 +620,11 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
         }
         if (part == 0) s_init[n & 3][o] = bias[o] + d;
     };
-    // this wavefront's statistics of image n -> its record; accumulators cleared
+    // MODE_LAST: this wavefront's statistics of image n -> its record; accumulators cleared
     auto flush = [&](int n) {
-        if (st.tout) {
+        if (MODE == MODE_LAST && st.tout) {
             const int lane = pin_in_loop(tid & 63);
-            float *rec = st.tout + (((int64_t)n * st.out_slots + out_slot) * R::NSUB + wave / K::NCB) * stat_rec(C, NQ);
+            float *rec = st.tout + ((int64_t)n * st.out_recs + out_slot * R::NSUB + wave / K::NCB) * stat_rec(C);
             if (lane < 32) {
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
@@ -616,19 +632,14 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                     s_stat[wave][q][lane] = 0.f;
                 }
             }
-            if (cb == 0 && lane == 0) {
-                rec[NQ * C] = s_cnt[wave];
-                s_cnt[wave] = 0.f;
-            }
         }
     };
     f32x16 acc[RW];
-    const int sample_phase = min(3, g.strips - 1); // strips 3, 11, 19, .. are sampled (the last one of a short tile)
+    const int sample_phase = sampled_strip(g.strips); // strips 3, 11, 19, .. are sampled (the last one of a short tile)
     // bias, ReLU, bf16, stores and statistics of strip i (accumulated by this wavefront)
     auto epilogue = [&](const Geo &q) {
         const int lane = pin_in_loop(tid & 63);
         const int px = lane & 31, half = lane >> 5;
-        float *my_stat = &s_stat[wave][0][half * 16];
         const int strip = q.strip, n = q.n, x0 = q.colblk * kTileW;
         const int y0 = strip * kRows;
         const int x = x0 + xb * 32 + px;
@@ -661,11 +672,13 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                 }
             }
         }
-        if (st.tout && (MODE == MODE_LAST || (strip & 7) == sample_phase)) {
-            strip_statistics<RW, MODE == MODE_LAST>(acc, si, my_stat, x, yw, g.h, g.w, px);
-            if (cb == 0 && lane == 0) {
-                const int rows = max(0, min(RW, g.h - yw)), cols = max(0, min(32, g.w - (x0 + xb * 32)));
-                s_cnt[wave] += (float)(rows * cols);
+        if (st.tout) {
+            if (MODE == MODE_LAST) {
+                strip_statistics<RW, true>(acc, si, &s_stat[wave][0][half * 16], x, yw, g.h, g.w, px);
+            } else if ((strip & 7) == sample_phase) { // records of a sampled strip: column block, row group, pixel block
+                const int ri = (((strip >> 3) * g.colblks + q.colblk) * RG + rg) * 2 + xb;
+                strip_statistics<RW, false>(acc, si, st.tout + ((int64_t)n * st.out_recs + ri) * C + cb * 32 + half * 16, x, yw,
+                                            g.h, g.w, px);
             }
         }
     };
@@ -675,7 +688,6 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 #pragma unroll
         for (int q = 0; q < NQ; ++q) s_stat[wave][q][lane] = 0.f;
     }
-    if (lane == 0) s_cnt[wave] = 0.f;
     if (grp == 0) prepare_init(gc.n);
     else if (ns > 1 && g1.n != gc.n) prepare_init(g1.n);
     if (grp == 1) {
@@ -772,16 +784,15 @@ constexpr int kPairRing = 8;
 constexpr int kSeamRowBytes = 2 * 64 * 2; // two pixels of 64 bf16 channels: what one row hands over
 
 struct PairArgs {
-    const float *tin;   // records of the input's channel sums [n_img][in_slots][stat_rec(C,1)], or nullptr
-    int in_slots;
-    const float *rsum;  // [c_in][c_out] residual-weight sums of the first block (fp32), or nullptr
-    float *tout;        // records of the output's channel sums [n_img][out_slots][stat_rec(C, 1 or 9)], or nullptr
-    int out_slots;      // records per image (the first kPairSub of them are written here)
+    MeanIn tin;         // channel sums of the input (rec null: no correction)
+    const float *rsum;  // [c_in][c_out] residual-weight sums of the first block (fp32)
+    float *tout;        // channel sums of the output, or nullptr: [n_img][out_recs][C], LASTB [n_img][out_recs][9 C]
+    int out_recs;       // records per image (LASTB: the first kPairSub of them are written here)
     int ipw;            // images per workgroup
     uint8_t *seam;      // WIDE: [workgroup][2][2 S rows][2 pixels][C] bf16, columns handed to the next column block
     uint8_t *seam_last; // WIDE, width a multiple of 64: [image][2 S rows][2 pixels][C], intermediate columns w-2, w-1
 };
-constexpr int kPairSub = 2; // statistics records per image: one per pixel-block pair of wavefronts of group B
+constexpr int kPairSub = 2; // LASTB: records per image: one per pixel-block pair of wavefronts of group B
 
 // FIRST: the first of the two blocks is the network's first block (3 -> C on the raw u8 tile: crop and
 //        normalisation fused, weights as bf16 high part + residual, see conv_first_kernel) instead of a
@@ -802,7 +813,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     typedef MidCfg<C> K;
     static_assert(K::NCB == 2, "the pair kernel is written for 64 channels");
     constexpr int RW = 2;
-    constexpr int NQ = LASTB ? 9 : 1;
+    constexpr int NQ = LASTB ? 9 : 0;             // sums per channel gathered in LDS
     constexpr int ROWB = kHaloW * K::PS;          // staged rows are packed: 66 pixels x 144 bytes
     constexpr int SLOTS = ROWB / 16;              // 16-byte slots per row
     constexpr int PIECES = (SLOTS + 63) / 64;     // wavefront-wide loads per row, the last one partial
@@ -811,9 +822,8 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     __shared__ __attribute__((aligned(16))) uint16_t s_pix[FIRST ? kPairRing : 1][kHaloW][4]; // raw pixels as bf16; channel 3 = 1 inside the tile
     __shared__ __attribute__((aligned(16))) float s_initA[C]; // first block: bias (+ rounding-residual correction of the image)
     __shared__ __attribute__((aligned(16))) float s_biasB[C];
-    __shared__ __attribute__((aligned(16))) float s_stat[4][NQ][32];
+    __shared__ __attribute__((aligned(16))) float s_stat[4][NQ ? NQ : 1][32];
     __shared__ __attribute__((aligned(16))) float s_mean[4][C];
-    __shared__ float s_cnt[4];
     // FIRST: group B hands its fp32 accumulators to group A, which has time to spare, for the epilogue:
     // [buffer = row pair parity][wavefront][row * 4 + channel quad][lane] x 4 floats
     __shared__ __attribute__((aligned(16))) float s_accx[FIRST ? 2 * 4 * 8 * 256 : 4];
@@ -847,7 +857,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     const uint32_t row_bytes = (uint32_t)(g.w * C * 2);
     const lrow_t in_base = lds_address(ring_in) + (xb * 32 + px) * K::PS + half * 16;
     const lrow_t mid_base = lds_address(ring_mid) + (xb * 32 + px) * K::PS + half * 16;
-    const int sample_phase = min(3, g.strips - 1);
+    const int sample_phase = sampled_strip(g.strips);
     auto slot_of = [](int y) { return (y + 2) & (kPairRing - 1); };
 
     // Loads of input row y of image n into its ring slot by the four wavefronts of one group: piece q of
@@ -888,16 +898,8 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         const int ln = pin_in_loop(tid & 63);
         const int o = w4 * OPW + ln % OPW, part = ln / OPW;
         float d = 0.f;
-        if (st.tin && st.rsum) {
-            if (ln < C) {
-                float sum = 0.f, cnt = 0.f;
-                for (int s2 = 0; s2 < st.in_slots; ++s2) {
-                    const float *rec = st.tin + ((int64_t)n * st.in_slots + s2) * stat_rec(C, 1);
-                    sum += rec[ln];
-                    cnt += rec[C];
-                }
-                s_mean[w4][ln] = cnt > 0.f ? sum / cnt : 0.f;
-            }
+        if (st.tin.rec && st.rsum) {
+            image_means<C>(st.tin, n, s_mean[w4], ln);
 #pragma unroll 4
             for (int k = 0; k < CP; ++k) {
                 const int c = part * CP + k;
@@ -941,12 +943,9 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     };
 
     // ---- once per workgroup: biases, the halo columns of the intermediate ring, statistics
-    if (grp == kFinishGroup) {
-        if (lane < 32) {
+    if (LASTB && grp == kFinishGroup && lane < 32) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) s_stat[w4][q][lane] = 0.f;
-        }
-        if (lane == 0) s_cnt[w4] = 0.f;
+        for (int q = 0; q < NQ; ++q) s_stat[w4][q][lane] = 0.f;
     }
     if (grp == 1) {
         if (tid - 256 < C) s_biasB[tid - 256] = biasB[tid - 256];
@@ -1138,31 +1137,21 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         if (LASTB) {
             if (st.tout) last_block_statistics(a, si, x, x_lo + xb * 32, j, pxl, hf);
         } else if (st.tout && ((j >> 1) & 7) == sample_phase) { // (the rows conv_mid would sample)
-            strip_statistics<RW, false>(a, si, &s_stat[w4][0][hf * 16], x, 2 * j, g.h, g.w, pxl);
+            const int ri = (((j >> 4) * 2 + (j & 1)) * J + blk) * 2 + xb; // sampled row pair, column block, pixel block
+            strip_statistics<RW, false>(a, si, st.tout + ((int64_t)n * st.out_recs + ri) * C + cb * 32 + hf * 16, x, 2 * j, g.h,
+                                        g.w, pxl);
         }
-        if (st.tout && (LASTB || ((j >> 1) & 7) == sample_phase)) {
-            if (cb == 0 && ln == 0) {
-                const int rows = max(0, min(RW, g.h - 2 * j));
-                const int cols = max(0, min(x_lo + xb * 32 + 32, g.w) - max(x_lo + xb * 32, 0));
-                s_cnt[w4] += (float)(rows * cols);
-            }
-        }
-        if (st.tout && j == S - 1 && blk == J - 1) { // what this wavefront gathered for the image (its own part of s_stat)
-            if (LASTB) { // the whole-tile sums lived in a register: one channel per lane
-                if ((pxl & 1) == 0) s_stat[w4][0][hf * 16 + reduce16_index(pxl)] = run_sum;
-                run_sum = 0.f;
-            }
-            float *rec = st.tout + ((int64_t)n * st.out_slots + xb) * stat_rec(C, NQ);
+        if (LASTB && st.tout && j == S - 1 && blk == J - 1) { // what this wavefront gathered for the image (its own part of s_stat)
+            // the whole-tile sums lived in a register: one channel per lane
+            if ((pxl & 1) == 0) s_stat[w4][0][hf * 16 + reduce16_index(pxl)] = run_sum;
+            run_sum = 0.f;
+            float *rec = st.tout + ((int64_t)n * st.out_recs + xb) * stat_rec(C);
             if (ln < 32) {
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
                     rec[q * C + cb * 32 + ln] = s_stat[w4][q][ln];
                     s_stat[w4][q][ln] = 0.f;
                 }
-            }
-            if (cb == 0 && ln == 0) {
-                rec[NQ * C] = s_cnt[w4];
-                s_cnt[w4] = 0.f;
             }
         }
     };
@@ -1398,11 +1387,11 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
 template <int C, bool LASTB>
 __global__ __launch_bounds__(128) void conv_seam_kernel(const uint8_t *__restrict__ seam_last, ConvGeom g,
                                                         const bf16_t *__restrict__ wfragB, const float *__restrict__ biasB,
-                                                        float *__restrict__ tout, int out_slots, int rec_first,
+                                                        float *__restrict__ tout, int out_recs, int rec_first,
                                                         bf16_t *__restrict__ out)
 {
     typedef MidCfg<C> K;
-    __shared__ float s_rec[LASTB ? stat_rec(C, 9) : 1];
+    __shared__ float s_rec[LASTB ? stat_rec(C) : 1];
     const int lane = threadIdx.x & 63;
     const int cb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int px = lane & 31, half = lane >> 5;
@@ -1412,7 +1401,7 @@ __global__ __launch_bounds__(128) void conv_seam_kernel(const uint8_t *__restric
     const uint8_t *sl = seam_last + (size_t)n * (2 * ((g.h + 1) / 2)) * kSeamRowBytes;
     const bf16x8 *wp = (const bf16x8 *)wfragB + (size_t)cb * 9 * K::KC * 64 + lane;
     if (LASTB) {
-        for (int i = threadIdx.x; i < stat_rec(C, 9); i += 128) s_rec[i] = 0.f;
+        for (int i = threadIdx.x; i < stat_rec(C); i += 128) s_rec[i] = 0.f;
         __syncthreads();
     }
     // all operands are asked for before the first is used (unconditional loads from a clamped row; what lies
@@ -1480,10 +1469,9 @@ __global__ __launch_bounds__(128) void conv_seam_kernel(const uint8_t *__restric
                 s_rec[8 * C + ch + v] = a;
             }
         }
-        if (threadIdx.x == 0) s_rec[9 * C] = (float)max(0, min(32, g.h - t * 32));
         __syncthreads();
-        float *rec = tout + ((int64_t)n * out_slots + rec_first + t) * stat_rec(C, 9);
-        for (int i = threadIdx.x; i < stat_rec(C, 9); i += 128) rec[i] = s_rec[i];
+        float *rec = tout + ((int64_t)n * out_recs + rec_first + t) * stat_rec(C);
+        for (int i = threadIdx.x; i < stat_rec(C); i += 128) rec[i] = s_rec[i];
     }
 }
 
@@ -1597,12 +1585,10 @@ constexpr int kFirstPix = (kRows + 2) * kHaloW;
 template <int C>
 __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeom g, const bf16_t *__restrict__ wfrag,
                                                          const float *__restrict__ bias, float *__restrict__ tout,
-                                                         int out_slots, int per, bf16_t *__restrict__ out)
+                                                         int out_recs, int per, bf16_t *__restrict__ out)
 {
     constexpr int NCB = C / 32;
     __shared__ __attribute__((aligned(16))) uint16_t lds[kFirstPix * 4];
-    __shared__ __attribute__((aligned(16))) float s_stat[4][32]; // per wavefront, the 32 channels of its block
-    __shared__ float s_cnt[4];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int px = lane & 31, half = lane >> 5;
@@ -1637,8 +1623,6 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
             tap = tap > 8 ? 8 : tap;
             toff[q][j] = ((tap / 3) * kHaloW + tap % 3) * 8;
         }
-    for (int i = tid; i < 4 * 32; i += 256) (&s_stat[0][0])[i] = 0.f;
-    if (tid < 4) s_cnt[tid] = 0.f;
 
     const int plane = src.H * src.W;
 
@@ -1646,35 +1630,12 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
     const int total = g.n_img * tpi;
     const int t_begin = blockIdx.x * per;
     const int t_end = min(total, t_begin + per);
-    const int out_slot = per >= tpi ? 0 : (t_begin % tpi) / per;
 
-    auto flush = [&](int n) {
-        __syncthreads();
-        float *rec = tout + ((int64_t)n * out_slots + out_slot) * stat_rec(C, 1);
-        if (tid < C) {
-            float v = 0.f;
-#pragma unroll
-            for (int w2 = 0; w2 < 4; ++w2)
-                if (w2 % NCB == tid / 32) v += s_stat[w2][tid & 31];
-            rec[tid] = v;
-        }
-        if (tid == 0) rec[C] = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
-        __syncthreads();
-        for (int i = tid; i < 4 * 32; i += 256) (&s_stat[0][0])[i] = 0.f;
-        if (tid < 4) s_cnt[tid] = 0.f;
-        __syncthreads();
-    };
-
-    int cur_n = -1;
     for (int t = t_begin; t < t_end; ++t) {
         const int colblk = t % g.colblks;
         const int strip = (t / g.colblks) % g.strips;
         const int n = t / tpi;
         const int y0 = strip * kRows, x0 = colblk * kTileW;
-        if (n != cur_n) {
-            if (cur_n >= 0 && tout) flush(cur_n);
-            cur_n = n;
-        }
         int oy = 0, ox = 0;
         if (src.off) {
             oy = clampi(src.off[2 * n], 0, src.H - g.h);
@@ -1699,7 +1660,8 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
         }
         __syncthreads();
 
-        const bool sample = tout && (strip & 7) == min(3, g.strips - 1);
+        const bool sample = tout && (strip & 7) == sampled_strip(g.strips);
+        float tv[16] = {}; // sampled strip: channel sums over this wavefront's rows, this lane's columns
 #pragma unroll
         for (int rr = 0; rr < NCB; ++rr) {
             const int row = rbase + rr;
@@ -1730,16 +1692,22 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
                 if (x < g.w)
                     store_tile_bf16(out + (((int64_t)n * g.h + y) * g.w + x) * C + cb * 32 + half * 16, acc, dither16(x, y), true);
                 if (sample) {
-                    float tv[16];
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) tv[v] = half_sum(x < g.w ? fmaxf(acc[v], 0.f) : 0.f);
-                    lds_accumulate(&s_stat[wave][half * 16], tv, px == kSumLane);
-                    if (cb == 0 && lane == 0) s_cnt[wave] += (float)max(0, min(32, g.w - (x0 + xb * 32)));
+                    for (int v = 0; v < 16; ++v) tv[v] += x < g.w ? fmaxf(acc[v], 0.f) : 0.f;
                 }
             }
         }
+        if (sample) { // a record per sampled strip, column block and wavefront of the same channels
+            const int ri = ((strip >> 3) * g.colblks + colblk) * (4 / NCB) + wave / NCB;
+            float *rec = tout + ((int64_t)n * out_recs + ri) * C + cb * 32 + half * 16;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) tv[v] = half_sum(tv[v]);
+            if (px == kSumLane) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) *(f32x4 *)(rec + 4 * q) = (f32x4){tv[4 * q], tv[4 * q + 1], tv[4 * q + 2], tv[4 * q + 3]};
+            }
+        }
     }
-    if (cur_n >= 0 && tout) flush(cur_n);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1762,26 +1730,48 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
                                                    const float *__restrict__ lin_b, float *__restrict__ logits,
                                                    uint8_t *__restrict__ bits, uint8_t *__restrict__ symbols, int m)
 {
-    __shared__ float Q[kHeadIpb][9][64];
+    __shared__ __attribute__((aligned(16))) float Q[kHeadIpb][9 * 64];       // the image's sums, [q*C + c]
+    __shared__ __attribute__((aligned(16))) float Qp[kHeadThreads * 4];      // partial sums over the records
     __shared__ float S[kHeadIpb][9 * 64]; // [c*9 + tap]
     __shared__ float part[kHeadKParts][kHeadIpb][128];
     __shared__ float pooled[kHeadIpb][128];
     __shared__ uint8_t sbit[kHeadIpb][128];
     const int tid = threadIdx.x;
     const int64_t n0 = (int64_t)blockIdx.x * kHeadIpb;
-    const int rec = stat_rec(C, 9);
-    for (int idx = tid; idx < kHeadIpb * 9 * C; idx += kHeadThreads) {
-        const int i = idx / (9 * C), r = idx - i * 9 * C; // r = q*C + c
-        float v = 0.f;
-        if (n0 + i < n_img)
-            for (int s2 = 0; s2 < slots; ++s2) v += recs[((n0 + i) * slots + s2) * rec + r];
-        Q[i][r / C][r % C] = v;
+    // records -> Q: groups of 9 C / 4 threads (16 bytes each) take every `groups`-th record, four loads in flight;
+    // a launch of few images has a record per workgroup and wavefront that worked on one, 128 of them for a 128 x 128
+    // tile, which cost 71 us when every thread added up its entries one load after the other
+    const int lpr = 9 * C / 4, groups = kHeadThreads / lpr;
+    for (int i = 0; i < kHeadIpb; ++i) {
+        const int grp = tid / lpr, l = tid - grp * lpr;
+        if (grp < groups) {
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+            if (n0 + i < n_img) {
+                const f32x4 *p = (const f32x4 *)recs + (n0 + i) * slots * lpr + l;
+                for (int r0 = grp; r0 < slots; r0 += 4 * groups) {
+                    f32x4 v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = p[(int64_t)min(r0 + u * groups, slots - 1) * lpr];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[e] += r0 + u * groups < slots ? v[u][e] : 0.f;
+                }
+            }
+            *(f32x4 *)&Qp[(grp * lpr + l) * 4] = sum;
+        }
+        __syncthreads();
+        for (int r = tid; r < 9 * C; r += kHeadThreads) {
+            float v = 0.f;
+            for (int g2 = 0; g2 < groups; ++g2) v += Qp[g2 * 9 * C + r];
+            Q[i][r] = v;
+        }
+        __syncthreads();
     }
-    __syncthreads();
     for (int idx = tid; idx < kHeadIpb * C; idx += kHeadThreads) {
         const int i = idx / C, c = idx - i * C;
-        const float T = Q[i][0][c], R0 = Q[i][1][c], Rl = Q[i][2][c], C0 = Q[i][3][c], Cl = Q[i][4][c];
-        const float c00 = Q[i][5][c], c0l = Q[i][6][c], cl0 = Q[i][7][c], cll = Q[i][8][c];
+        const float T = Q[i][0 * C + c], R0 = Q[i][1 * C + c], Rl = Q[i][2 * C + c], C0 = Q[i][3 * C + c], Cl = Q[i][4 * C + c];
+        const float c00 = Q[i][5 * C + c], c0l = Q[i][6 * C + c], cl0 = Q[i][7 * C + c], cll = Q[i][8 * C + c];
 #pragma unroll
         for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
@@ -1907,23 +1897,47 @@ int persistent_blocks(int num_cu, int per_cu, int64_t work)
 
 } // namespace
 
+// What the consumer of a launch's sampled channel sums has to know: records per image and pixels behind them.
+// `cols`: output columns the launch covers; `pieces`: records per sampled strip and column block.
+static MeanIn sampled_strips(const ConvGeom &g, int cols, int pieces)
+{
+    const int first = sampled_strip(g.strips), count = (g.strips - 1 - first) / 8 + 1, last = first + 8 * (count - 1);
+    const int rows = (count - 1) * kRows + std::min(kRows, g.h - last * kRows);
+    return MeanIn{nullptr, count * g.colblks * pieces, 1.0f / ((float)rows * (float)cols)};
+}
+
+MeanIn conv_first_samples(const ConvGeom &g, int C) { return sampled_strips(g, g.w, 4 / (C / 32)); }
+
+MeanIn conv_mid_samples(const ConvGeom &g, int C) { return sampled_strips(g, g.w, 2 * (2 / (C / 32))); }
+
+MeanIn conv_pair_samples(const ConvGeom &g)
+{
+    // two row pairs per strip, unless the last sampled strip is the tile's last one and has one row pair only; a wide
+    // tile's last column belongs to conv_seam_kernel, which takes no samples
+    const bool seam_column = g.colblks > 1 && g.w % kTileW == 0;
+    MeanIn m = sampled_strips(g, g.w - (seam_column ? 1 : 0), 4);
+    const int pairs = (g.h + 1) / 2;
+    const bool last_sampled = ((g.strips - 1) & 7) == sampled_strip(g.strips);
+    if (last_sampled && (pairs & 1)) m.recs -= 2 * g.colblks;
+    return m;
+}
+
 hipError_t launch_conv_first(const TileSrc &src, const ConvGeom &g, int C, const bf16_t *wfrag, const float *bias,
                              float *tout, const Partition &part, bf16_t *out, hipStream_t s)
 {
+    const int recs = conv_first_samples(g, C).recs;
     if (C == 64)
-        hipLaunchKernelGGL(conv_first_kernel<64>, dim3(part.blocks), dim3(256), 0, s, src, g, wfrag, bias, tout,
-                           part.slots, part.per, out);
+        hipLaunchKernelGGL(conv_first_kernel<64>, dim3(part.blocks), dim3(256), 0, s, src, g, wfrag, bias, tout, recs, part.per, out);
     else
-        hipLaunchKernelGGL(conv_first_kernel<32>, dim3(part.blocks), dim3(256), 0, s, src, g, wfrag, bias, tout,
-                           part.slots, part.per, out);
+        hipLaunchKernelGGL(conv_first_kernel<32>, dim3(part.blocks), dim3(256), 0, s, src, g, wfrag, bias, tout, recs, part.per, out);
     return hipGetLastError();
 }
 
 hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, const bf16_t *wfrag,
-                           const float *bias, const float *tin, int in_slots, const float *rsum, float *tout,
+                           const float *bias, const MeanIn &tin, const float *rsum, float *tout,
                            const Partition &part, bool last, bf16_t *out, hipStream_t s)
 {
-    StatArgs st{tin, in_slots, rsum, tout, part.slots, part.per};
+    StatArgs st{tin, rsum, tout, last ? part.slots * part.sub : conv_mid_samples(g, C).recs, part.per};
     const dim3 grid(part.blocks), block(64 * kMidWaves);
     if (C == 64) {
         if (last) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_LAST>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, out);
@@ -1937,10 +1951,10 @@ hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, 
 
 bool conv_pair_supported(int C, const ConvGeom &g) { return C == 64 && g.colblks >= 1; }
 
-int conv_pair_records_per_image(const ConvGeom &g, bool last)
+int conv_pair_last_records(const ConvGeom &g)
 {
     const bool seam_column = g.colblks > 1 && g.w % kTileW == 0; // conv_seam_kernel adds records of its own
-    return kPairSub + ((last && seam_column) ? (g.h + 31) / 32 : 0);
+    return kPairSub + (seam_column ? (g.h + 31) / 32 : 0);
 }
 
 size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu)
@@ -1961,7 +1975,7 @@ static void launch_pair_variant(bool wide, dim3 grid, hipStream_t s, const uint8
 
 hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
                             const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a, const float *bias_b,
-                            const float *tin, int in_slots, const float *rsum_a, float *tout, bool last, int num_cu,
+                            const MeanIn &tin, const float *rsum_a, float *tout, bool last, int num_cu,
                             uint8_t *seam, bf16_t *out, hipStream_t s)
 {
     if (!conv_pair_supported(C, g)) return hipErrorInvalidValue;
@@ -1973,8 +1987,8 @@ hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileS
     if ((int)grid.x > num_cu) return hipErrorInvalidValue; // the seam buffer holds num_cu workgroups
     const size_t half = (size_t)(2 * ((g.h + 1) / 2)) * kSeamRowBytes;
     uint8_t *seam_last = seam_column ? seam + 2 * (size_t)num_cu * half : nullptr;
-    const int out_slots = conv_pair_records_per_image(g, last);
-    PairArgs st{tin, in_slots, rsum_a, tout, out_slots, ipw, seam, seam_last};
+    const int out_recs = last ? conv_pair_last_records(g) : conv_pair_samples(g).recs;
+    PairArgs st{tin, rsum_a, tout, out_recs, ipw, seam, seam_last};
     const TileSrc src = first ? *first : TileSrc{};
     if (first) {
         if (last) launch_pair_variant<true, true>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
@@ -1986,8 +2000,8 @@ hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileS
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !seam_column) return e;
     const dim3 sgrid((unsigned)g.n_img * (unsigned)((g.h + 31) / 32));
-    if (last) hipLaunchKernelGGL((conv_seam_kernel<64, true>), sgrid, dim3(128), 0, s, seam_last, g, wfrag_b, bias_b, tout, out_slots, kPairSub, out);
-    else hipLaunchKernelGGL((conv_seam_kernel<64, false>), sgrid, dim3(128), 0, s, seam_last, g, wfrag_b, bias_b, tout, out_slots, kPairSub, out);
+    if (last) hipLaunchKernelGGL((conv_seam_kernel<64, true>), sgrid, dim3(128), 0, s, seam_last, g, wfrag_b, bias_b, tout, out_recs, kPairSub, out);
+    else hipLaunchKernelGGL((conv_seam_kernel<64, false>), sgrid, dim3(128), 0, s, seam_last, g, wfrag_b, bias_b, tout, out_recs, kPairSub, out);
     return hipGetLastError();
 }
 
@@ -2025,7 +2039,7 @@ Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks, 
     return p;
 }
 
-size_t stat_record_floats(int C, int nq) { return (size_t)stat_rec(C, nq); }
+size_t last_record_floats(int C) { return (size_t)stat_rec(C); }
 
 int conv_mid_records_per_workgroup(int C) { return kMidWaves / (C / 32); }
 

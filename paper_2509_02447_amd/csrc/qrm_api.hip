@@ -281,20 +281,20 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
         L.partial = align_up((size_t)L.mb * L.n_part * c->nbp * 4);
         // statistics records: sized for the fullest micro-batch and for the ragged last one
         const int tpi = tiles_per_image(h, w);
-        size_t recs = 0;
+        size_t recs = 0; // floats
         const int64_t counts[2] = {L.mb, L.mb ? N % L.mb : 0};
         for (int64_t cnt : counts) {
             if (cnt <= 0) continue;
-            const Partition pf = make_partition(cnt, tpi, first_blocks(c));
             const Partition pm = make_partition(cnt, tpi, mid_blocks(c), conv_mid_records_per_workgroup(c->C));
             const ConvGeom g{(int)cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
-            const int rp = c->pairable ? conv_pair_records_per_image(g, true) : 0;
-            const int rf = pf.slots * pf.sub, rm = pm.slots * pm.sub;
-            const size_t r = (size_t)cnt * std::max(rp, std::max(rf, rm));
-            if (r > recs) recs = r;
+            // floats per image: records of the last block, or sampled channel sums of any other
+            const size_t last = std::max(c->pairable ? conv_pair_last_records(g) : 0, pm.slots * pm.sub) * last_record_floats(c->C);
+            const int samples = std::max(c->pairable ? conv_pair_samples(g).recs : 0,
+                                         std::max(conv_first_samples(g, c->C).recs, conv_mid_samples(g, c->C).recs));
+            recs = std::max(recs, (size_t)cnt * std::max(last, (size_t)samples * c->C));
             if (c->pairable) L.seam = std::max(L.seam, align_up(conv_pair_seam_bytes(g, c->num_cu)));
         }
-        L.stats = align_up(recs * stat_record_floats(c->C, 9) * 4);
+        L.stats = align_up(recs * 4);
     }
     L.symbols = (want_symbols && c->has_rs) ? align_up((size_t)N * c->rs.n) : 0;
     L.total = kZeroBytes + 2 * L.act + L.partial + 2 * L.stats + L.seam + L.symbols;
@@ -424,7 +424,8 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         const Partition pm = make_partition(cnt, tpi, mid_blocks(c), conv_mid_records_per_workgroup(c->C));
         src.img = img0 + n0 * 3 * (int64_t)src.H * src.W;
         src.off = off0 ? off0 + 2 * n0 : nullptr;
-        int cur = 0, tcur = 0, in_slots = pf.slots * pf.sub;
+        int cur = 0, tcur = 0, last_recs = 0; // records of nine sums per image, once the last block has run
+        MeanIn means{};                       // channel sums the next block reads
         const int blocks = n_run > 0 ? n_run : c->n_blocks; // blocks to run: the first one and C -> C layers m = b - 1
         // Fused schedule (64 channels; see use_fused): [first + layer 0], (1,2), (3,4), ..; what is left over
         // runs alone.
@@ -434,39 +435,44 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         if (fused) {
             qrm_ctx::Timed *t = time_begin(c, may_time, is_last(1) ? QRM_PROFILE_PAIR_LAST : QRM_PROFILE_PAIR_FIRST,
                                            (first_flops + block_flops) * cnt, s);
-            e = launch_conv_pair(base, nullptr, &src, g, c->C, c->d_w_first, c->d_w_mid[0], c->d_bias, c->d_bias + (size_t)c->C, nullptr,
-                                 0, nullptr, tb[tcur], is_last(1), c->num_cu, seam, buf[cur], s);
+            e = launch_conv_pair(base, nullptr, &src, g, c->C, c->d_w_first, c->d_w_mid[0], c->d_bias, c->d_bias + (size_t)c->C, MeanIn{},
+                                 nullptr, tb[tcur], is_last(1), c->num_cu, seam, buf[cur], s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_pair (first) launch");
             time_end(t, s);
-            in_slots = conv_pair_records_per_image(g, is_last(1));
+            if (is_last(1)) last_recs = conv_pair_last_records(g);
+            else means = conv_pair_samples(g);
             b = 2;
         } else {
             qrm_ctx::Timed *t = time_begin(c, may_time, QRM_PROFILE_BLOCK_FIRST, first_flops * cnt, s);
             e = launch_conv_first(src, g, c->C, c->d_w_first, c->d_bias, tb[tcur], pf, buf[cur], s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_first launch");
             time_end(t, s);
+            means = conv_first_samples(g, c->C);
         }
         while (b < blocks) {
             const int m = b - 1;
             const bool pair = fused && (m & 1) == 1 && b + 1 < blocks;
             const float *rsum = c->d_rsum + (size_t)m * c->C * c->C;
+            means.rec = tb[tcur];
             if (pair) {
                 qrm_ctx::Timed *t = time_begin(c, may_time, is_last(b + 1) ? QRM_PROFILE_PAIR_LAST : QRM_PROFILE_PAIR_MID,
                                                2.0 * block_flops * cnt, s);
                 e = launch_conv_pair(base, base + buf_off[cur], nullptr, g, c->C, c->d_w_mid[m], c->d_w_mid[m + 1],
-                                     c->d_bias + (size_t)b * c->C, c->d_bias + (size_t)(b + 1) * c->C, tb[tcur], in_slots, rsum,
+                                     c->d_bias + (size_t)b * c->C, c->d_bias + (size_t)(b + 1) * c->C, means, rsum,
                                      tb[tcur ^ 1], is_last(b + 1), c->num_cu, seam, buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_pair launch");
                 time_end(t, s);
-                in_slots = conv_pair_records_per_image(g, is_last(b + 1));
+                if (is_last(b + 1)) last_recs = conv_pair_last_records(g);
+                else means = conv_pair_samples(g);
             } else {
                 qrm_ctx::Timed *t = time_begin(c, may_time, is_last(b) ? QRM_PROFILE_BLOCK_LAST : QRM_PROFILE_BLOCK_MID,
                                                block_flops * cnt, s);
-                e = launch_conv_mid(base, buf_off[cur], g, c->C, c->d_w_mid[m], c->d_bias + (size_t)b * c->C, tb[tcur], in_slots,
+                e = launch_conv_mid(base, buf_off[cur], g, c->C, c->d_w_mid[m], c->d_bias + (size_t)b * c->C, means,
                                     rsum, tb[tcur ^ 1], pm, is_last(b), buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_mid launch");
                 time_end(t, s);
-                in_slots = pm.slots * pm.sub;
+                if (is_last(b)) last_recs = pm.slots * pm.sub;
+                else means = conv_mid_samples(g, c->C);
             }
             cur ^= 1;
             tcur ^= 1;
@@ -482,7 +488,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         uint8_t *sy = nsym ? d_symbols + n0 * nsym : nullptr;
         qrm_ctx::Timed *t = time_begin(c, may_time, QRM_PROFILE_HEAD, 0.0, s);
         if (c->collapse) {
-            e = launch_head(tb[tcur], in_slots, c->C, cnt, c->n_bits, c->nbp, inv_hw, c->d_wft, c->d_bias_final,
+            e = launch_head(tb[tcur], last_recs, c->C, cnt, c->n_bits, c->nbp, inv_hw, c->d_wft, c->d_bias_final,
                             c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {

@@ -47,43 +47,52 @@ hipError_t launch_extract_tiles(const uint8_t *img, int64_t N, int H, int W, con
 struct Partition {
     int per;    // tiles per workgroup
     int slots;  // workgroups that touch one image
-    int sub;    // statistics records a workgroup writes per image; records per image = slots * sub
+    int sub;    // records of nine sums a workgroup writes per image (last block); records per image = slots * sub
     int blocks; // grid size
 };
 Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks, int sub = 1);
 int conv_mid_records_per_workgroup(int C);
-size_t stat_record_floats(int C, int nq); // floats per statistics record holding nq sums per channel
+size_t last_record_floats(int C); // floats per record of the last block (nine sums per channel)
+
+// Sampled per-image channel sums of a launch's output, as its consumer reads them.
+struct MeanIn {
+    const float *rec; // [n_img][recs][C], or null: none
+    int recs;         // records per image
+    float inv_cnt;    // 1 / pixels of an image behind its records
+};
+MeanIn conv_first_samples(const ConvGeom &g, int C); // (rec null)
+MeanIn conv_mid_samples(const ConvGeom &g, int C);
+MeanIn conv_pair_samples(const ConvGeom &g);
 
 // conv1: crop + normalise + conv3x3 (3 -> C, bf16 high + residual weights) + bias + ReLU -> bf16 NHWC;
-// tout (optional): sampled channel sums of the output, [n_img][part.slots][stat_record_floats(C,1)]
+// tout (optional): sampled channel sums of the output, conv_first_samples() says how many
 hipError_t launch_conv_first(const TileSrc &src, const ConvGeom &g, int C, const bf16_t *wfrag, const float *bias,
                              float *tout, const Partition &part, bf16_t *out, hipStream_t s);
 
 // conv3x3 C -> C + bias + ReLU, bf16 NHWC in/out.  The input is addressed as ws + in_off + image * its bytes
 // (+ 32-bit offsets inside an image); the first kZeroBytes of ws must be zero: the source of the zero padding.
-// tin / in_slots / rsum: channel sums of the input (in_slots records per image) and the summed weight-rounding
-// residual [c_in][c_out] used
-// to correct the bias (either may be null).  tout: statistics of the output.  last: no activations are
-// written, tout receives the nine border-aware sums per channel (stat_record_floats(C,9) per record).
+// tin / rsum: channel sums of the input and the summed weight-rounding residual [c_in][c_out] used to correct the
+// bias (tin.rec and rsum may be null).  tout: channel sums of the output (conv_mid_samples()).  last: no activations
+// are written, tout receives the nine border-aware sums per channel, part.slots * part.sub records per image.
 constexpr size_t kZeroBytes = 256;
 hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, const bf16_t *wfrag,
-                           const float *bias, const float *tin, int in_slots, const float *rsum, float *tout,
+                           const float *bias, const MeanIn &tin, const float *rsum, float *tout,
                            const Partition &part, bool last, bf16_t *out, hipStream_t s);
 
 // Two consecutive blocks in one launch, the activations between them staying in LDS (C = 64:
 // conv_pair_supported; tiles wider than 64 columns are walked through in column blocks and need `seam`,
 // conv_pair_seam_bytes() bytes of scratch).  zeros: kZeroBytes of zeros; in: the input activations.
 // first != nullptr: the first of the two is the network's first block (raw u8 tiles, wfrag_a / bias_a of that
-// block; in / tin / rsum_a unused); otherwise both are C -> C blocks and tin / in_slots / rsum_a are as for
+// block; in / tin / rsum_a unused); otherwise both are C -> C blocks and tin / rsum_a are as for
 // launch_conv_mid (first block only: the second block's weights are rounded so that it needs no correction).
-// last: the second block is the network's last one (no activations written, nine sums per channel in the
-// records).  tout: channel sums of the output, conv_pair_records_per_image() records per image.
+// tout: channel sums of the output (conv_pair_samples()).  last: the second block is the network's last one: no
+// activations are written, tout receives conv_pair_last_records() records of nine sums per channel and image.
 bool conv_pair_supported(int C, const ConvGeom &g);
-int conv_pair_records_per_image(const ConvGeom &g, bool last);
+int conv_pair_last_records(const ConvGeom &g);
 size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu);
 hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
                             const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a, const float *bias_b,
-                            const float *tin, int in_slots, const float *rsum_a, float *tout, bool last, int num_cu,
+                            const MeanIn &tin, const float *rsum_a, float *tout, bool last, int num_cu,
                             uint8_t *seam, bf16_t *out, hipStream_t s);
 
 // nine channel sums of the last block -> final conv + average pool in closed form -> linear -> logits,

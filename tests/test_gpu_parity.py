@@ -234,6 +234,46 @@ def test_extractor_blocks_match_oracle_layer_by_layer(qrm, C, nb, h, w):
     ctx.close()
 
 
+# heights around the strips whose channel sums are sampled (strips of four rows, one in eight; row pairs in the fused
+# schedule): one strip, an odd number of row pairs in the sampled strip, a second sampled strip begun
+SAMPLE_CASES = [(64, 4, 1, 20, 0), (64, 4, 5, 64, 0), (64, 5, 13, 33, 0), (64, 4, 46, 64, 0), (64, 4, 13, 70, 0),
+                (64, 4, 13, 70, 4), (64, 5, 46, 128, 4), (64, 3, 14, 64, 1), (32, 3, 13, 64, 0), (32, 4, 46, 30, 0)]
+
+
+@pytest.mark.parametrize("C,nb,h,w,flags", SAMPLE_CASES)
+def test_results_do_not_depend_on_the_batch_around_a_tile(qrm, C, nb, h, w, flags):
+    """A tile alone, in a batch of a few and in one of more tiles than compute units: how the rows are dealt to
+    workgroups differs, the sampled channel sums and with them every activation do not (bit-equal); the last block's
+    sums are added up in another order (fp32 sums of non-negative values over a few partial sums, a few 1e-7 relative,
+    times the cancellation of the head's weighted sums).  Workspaces are filled with NaN first."""
+    wts = small_weights(C, nb, 16, C + nb + h)
+    rng = np.random.default_rng(h * w + C)
+    tile = rng.integers(0, 256, size=(1, 3, h, w), dtype=np.uint8)
+    acts, logits = [], []
+    for N, at in ((1, 0), (7, 5), (300, 299)):
+        ctx = qrm.Context(weights=wts)
+        ctx.qrm_diag_set_flags(flags | qrm.binding.QRM_DIAG_POISON_WORKSPACE)
+        tiles = rng.integers(0, 256, size=(N, 3, h, w), dtype=np.uint8)
+        tiles[at] = tile[0]
+        d_tiles, d_act, d_log = dev(tiles), empty((N, C, h, w), torch.float32), empty((N, 16), torch.float32)
+        ctx.qrm_extractor_blocks(d_tiles, N, h, w, nb, d_act)
+        ctx.qrm_extractor_forward(d_tiles, N, h, w, d_log, None)
+        torch.cuda.synchronize()
+        acts.append(d_act[at].cpu().numpy())
+        logits.append(d_log[at].cpu().numpy().astype(np.float64))
+        ctx.close()
+    # schedules are the same in all three batches only where the number of tiles does not choose one
+    same = w <= 64 or flags != 0
+    for a, lg in zip(acts[1:], logits[1:]):
+        assert np.isfinite(lg).all()
+        if same:
+            assert np.array_equal(a, acts[0])
+            assert np.max(np.abs(lg - logits[0]) / np.maximum(1.0, np.abs(logits[0]))) <= 2e-5
+    ref = oracle.extractor_forward(wts, tile)[0]
+    for lg in logits:
+        check_logits(lg[None], ref, what=f"C={C} {h}x{w} flags {flags}")
+
+
 EXT_CASES = [
     ("C1 shape 32x32 c32 b4 60bit", 32, 4, 60, 32, 32, 16),
     ("C2 shape 64x64 c64 b8 48bit", 64, 8, 48, 64, 64, 6),
