@@ -316,8 +316,10 @@ __device__ __forceinline__ void load_weight_frags(bf16x8 (&Wr)[9][C / 16], const
 //      zero, took a consumer longer to read (30 of a block's 42 us for 7 tiles of 128 x 128) than its matrix work.
 //  (2) the last conv (C -> n_bits, no ReLU) followed by the global average pool is linear, so it only
 //      needs, per channel of the last block's output, the sums over the whole tile, its first / last
-//      row, first / last column and four corners (9 numbers): the last block writes no activations but a
-//      record of nine sums per (image, workgroup that touched it, wavefront): rec[q*C + c].
+//      row, first / last column and four corners (9 numbers): the last block writes no activations.  The
+//      single-block kernel writes a record of nine sums per (image, workgroup that touched it, wavefront),
+//      rec[q*C + c]; the fused kernel writes lines of C sums, each over a part of the image that does not depend on
+//      how the rows were dealt to workgroups (LastSums), so that its results do not either.
 // Accumulation order is fixed, so results do not depend on scheduling.
 __host__ __device__ constexpr int stat_rec(int C) { return 9 * C; }
 __host__ __device__ constexpr int sampled_strip(int strips) { return strips < 4 ? strips - 1 : 3; }
@@ -786,13 +788,17 @@ constexpr int kSeamRowBytes = 2 * 64 * 2; // two pixels of 64 bf16 channels: wha
 struct PairArgs {
     MeanIn tin;         // channel sums of the input (rec null: no correction)
     const float *rsum;  // [c_in][c_out] residual-weight sums of the first block (fp32)
-    float *tout;        // channel sums of the output, or nullptr: [n_img][out_recs][C], LASTB [n_img][out_recs][9 C]
-    int out_recs;       // records per image (LASTB: the first kPairSub of them are written here)
-    int ipw;            // images per workgroup
+    float *tout;        // channel sums of the output, or nullptr: [n_img][out_recs][C]
+    int out_recs;       // records (LASTB: lines) per image
+    int per;            // pieces (of kChunk row pairs with LASTB, of one row pair otherwise) per workgroup
+    int sum_rows;       // LASTB: LastSums::rows, the other places follow from the tile's size
     uint8_t *seam;      // WIDE: [workgroup][2][2 S rows][2 pixels][C] bf16, columns handed to the next column block
     uint8_t *seam_last; // WIDE, width a multiple of 64: [image][2 S rows][2 pixels][C], intermediate columns w-2, w-1
 };
-constexpr int kPairSub = 2; // LASTB: records per image: one per pixel-block pair of wavefronts of group B
+// Row pairs behind one line of the last block's sums, and the granularity at which its images are cut between
+// workgroups: 1 would store four times as much (35 KB instead of 10 for a 64 x 64 tile), 8 would make the last launch of
+// a single tile twice as long.
+constexpr int kChunk = 4;
 
 // FIRST: the first of the two blocks is the network's first block (3 -> C on the raw u8 tile: crop and
 //        normalisation fused, weights as bf16 high part + residual, see conv_first_kernel) instead of a
@@ -801,8 +807,10 @@ constexpr int kPairSub = 2; // LASTB: records per image: one per pixel-block pai
 //        nine border-aware channel sums (see strip_statistics).
 // WIDE : tiles of more than one column block (see above); the other instantiations keep the straight-line code
 //        of the one-block case.
+// PART : workgroups take runs of row pairs that begin and end inside images; otherwise every workgroup takes whole
+//        images (st.per is a multiple of an image's pieces), which costs fewer scalar instructions per step.
 // zeros: kZeroBytes of zeros (the source of the padding); in: the input activations of the launch.
-template <int C, bool FIRST, bool LASTB, bool WIDE>
+template <int C, bool FIRST, bool LASTB, bool WIDE, bool PART>
 __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__restrict__ zeros, const uint8_t *__restrict__ in, TileSrc src,
                                                            ConvGeom g, const bf16_t *__restrict__ wfragA,
                                                            const bf16_t *__restrict__ wfragB,
@@ -813,7 +821,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     typedef MidCfg<C> K;
     static_assert(K::NCB == 2, "the pair kernel is written for 64 channels");
     constexpr int RW = 2;
-    constexpr int NQ = LASTB ? 9 : 0;             // sums per channel gathered in LDS
+    constexpr int QUANT = LASTB ? kChunk : 1;     // row pairs per piece dealt to workgroups
     constexpr int ROWB = kHaloW * K::PS;          // staged rows are packed: 66 pixels x 144 bytes
     constexpr int SLOTS = ROWB / 16;              // 16-byte slots per row
     constexpr int PIECES = (SLOTS + 63) / 64;     // wavefront-wide loads per row, the last one partial
@@ -822,7 +830,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     __shared__ __attribute__((aligned(16))) uint16_t s_pix[FIRST ? kPairRing : 1][kHaloW][4]; // raw pixels as bf16; channel 3 = 1 inside the tile
     __shared__ __attribute__((aligned(16))) float s_initA[C]; // first block: bias (+ rounding-residual correction of the image)
     __shared__ __attribute__((aligned(16))) float s_biasB[C];
-    __shared__ __attribute__((aligned(16))) float s_stat[4][NQ ? NQ : 1][32];
+    __shared__ __attribute__((aligned(16))) float s_stat[LASTB ? 4 : 1][2][32]; // LASTB: sums of the first / last column
     __shared__ __attribute__((aligned(16))) float s_mean[4][C];
     // FIRST: group B hands its fp32 accumulators to group A, which has time to spare, for the epilogue:
     // [buffer = row pair parity][wavefront][row * 4 + channel quad][lane] x 4 floats
@@ -849,10 +857,16 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     }
 
     const int vb = xcd_virtual_block(blockIdx.x, gridDim.x);
-    const int n_begin = vb * st.ipw, n_end = min(g.n_img, n_begin + st.ipw);
-    if (n_begin >= n_end) return;
     const int S = (g.h + 1) / 2;
     const int J = WIDE ? g.colblks : 1;           // column blocks of a tile
+    // The launch's row pairs, image after image, are cut into runs of st.per pieces, one run per workgroup: row pairs ja
+    // of image n_begin up to (not including) jb of image n_begin + n_cnt - 1.  Whole images per workgroup left 35 % of
+    // the compute units idle at 333 images (two each for 166 of them, none for the others) and all but one at 1.
+    const int ppi = (S + QUANT - 1) / QUANT;      // pieces per image
+    const int q0 = vb * st.per, q1 = min(g.n_img * ppi, q0 + st.per);
+    if (q0 >= q1) return;
+    const int n_begin = q0 / ppi, ja = PART ? (q0 - n_begin * ppi) * QUANT : 0;
+    const int n_cnt = (q1 - 1) / ppi - n_begin + 1, jb = PART ? min(S, (q1 - (n_begin + n_cnt - 1) * ppi) * QUANT) : S;
     const size_t img_bytes = (size_t)g.h * g.w * C * 2;
     const uint32_t row_bytes = (uint32_t)(g.w * C * 2);
     const lrow_t in_base = lds_address(ring_in) + (xb * 32 + px) * K::PS + half * 16;
@@ -943,10 +957,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     };
 
     // ---- once per workgroup: biases, the halo columns of the intermediate ring, statistics
-    if (LASTB && grp == kFinishGroup && lane < 32) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) s_stat[w4][q][lane] = 0.f;
-    }
+    if (LASTB && grp == kFinishGroup) (&s_stat[w4][0][0])[lane] = 0.f;
     if (grp == 1) {
         if (tid - 256 < C) s_biasB[tid - 256] = biasB[tid - 256];
     } else if (FIRST) {
@@ -959,32 +970,50 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         *(u32x4 *)(ring_mid + row * ROWB + (side ? (kHaloW - 1) : 0) * K::PS + sl * 16) = (u32x4){0u, 0u, 0u, 0u};
     }
 
-    // The units (image, column block) of a workgroup form one stream of row pairs: unit u takes P = S + 1 steps
-    // (S row pairs and the pair of padding rows below the tile, which is also the padding row above the next
-    // unit), and virtual row 2 P u + y stands for row y of unit u in both rings.  In step sigma group A is at
-    // position sigma of the stream, group B at sigma - 2, the epilogue of B's rows at sigma - 3, the loads at
-    // sigma + 2: nothing drains between units.
+    // The units (image, column block) of a workgroup form one stream of positions, one per step.  A unit's output row
+    // pairs are lo .. hi-1 (all S of them but for the workgroup's first and last image); its positions s are
+    //   an opening position: -1, or lo - 2 if the unit begins inside the image.  Nothing is computed (zeros go to
+    //       the intermediate ring: the padding below the unit before and above this one), only loads are issued;
+    //   lo - 1, if the unit begins inside the image: the pair whose second row is the halo row above the unit;
+    //   lo .. hi - 1;
+    //   hi, if the unit ends inside the image: the pair whose first row is the halo row below.
+    // (The halo pairs are computed by both neighbours, to the same bits.)  The workgroup's first unit skips its opening
+    // position; one more opening position follows the last unit.  At position number sg of the stream group A
+    // computes intermediate rows 2s, 2s + 1 of the unit, which live in the rings as virtual rows 2 sg, 2 sg + 1;
+    // group B is at position sg - 2, the epilogue of B's rows at sg - 3, the loads at sg + 2 (pixels: sg + 1):
+    // nothing drains between units.
     struct Pos {
-        int i, b, s; // image within the workgroup, column block within the image, step within the unit
+        int i, b, s; // image within the workgroup (n_cnt: none), column block within the image, position in the unit
     };
-    const int P = S + 1;
-    const int n_cnt = n_end - n_begin;
-    auto pos_of = [P, J](int sigma) {
-        const int u = sigma >= 0 ? sigma / P : -((P - 1 - sigma) / P);
-        const int i = u >= 0 ? u / J : -((J - 1 - u) / J);
-        return Pos{i, u - i * J, sigma - u * P};
-    };
-    auto advance = [P, J](Pos &p) {
-        if (__builtin_expect(++p.s == P, 0)) { // once per unit: kept out of the way of the other steps
-            p.s = 0;
+    auto lo = [ja](int i) { return PART && i == 0 ? ja : 0; };
+    auto hi = [n_cnt, jb, S](int i) { return PART && i == n_cnt - 1 ? jb : S; };
+    auto opening = [ja](int i) { return PART && i == 0 && ja > 0 ? ja - 2 : -1; };
+    auto closing = [hi, S](int i) { return min(hi(i), S - 1); };
+    auto computes = [lo](const Pos &p) { return p.s >= max(lo(p.i) - 1, 0); }; // not an opening position
+    auto owns = [lo, hi](const Pos &p) { return p.s >= lo(p.i) && (!PART || p.s < hi(p.i)); };
+    auto advance = [J, closing, opening](Pos &p) {
+        if (__builtin_expect(++p.s > closing(p.i), 0)) { // once per unit: kept out of the way of the other steps
             if (++p.b == J) {
                 p.b = 0;
                 ++p.i;
             }
+            p.s = opening(p.i);
         }
     };
-    auto next_unit = [J](const Pos &p) { return p.b + 1 == J ? Pos{p.i + 1, 0, 0} : Pos{p.i, p.b + 1, 0}; };
-    Pos pa = pos_of(0), pb = pos_of(-2), pf = pos_of(-3), pl = pos_of(2), p1 = pos_of(1);
+    int n_pos = n_cnt > 2 ? (n_cnt - 2) * J * (S + 1) : 0; // positions, opening position behind the last unit included
+    n_pos += J * (closing(0) - opening(0) + 1);
+    if (n_cnt > 1) n_pos += J * (closing(n_cnt - 1) + 2);
+    // A wavefront keeps the positions its group needs, no others: the loop is short of scalar registers (six positions
+    // in every wavefront spilled 16 to 35 of them and cost 1 .. 5 % of a launch).
+    Pos pw{0, 0, max(ja - 1, 0)}; // group A: position sg; group B: position sg - 2
+    Pos p1 = pw;                  // FIRST: group A's pixel loads, position sg + 1; group B's seam loads, position sg
+    if (!FIRST || grp == 0) advance(p1);
+    Pos pe = pw;                  // epilogue, position sg - 3 (group B; FIRST: group A); otherwise group A's loads, sg + 2
+    if (!FIRST && grp == 0) {
+        pe = p1;
+        advance(pe);
+    }
+    const int w_start = grp == 0 ? 0 : 2, e_start = !FIRST && grp == 0 ? 0 : 3; // the steps the positions move from
     auto tile_origin = [&](int n) {
         int oy = 0, ox = 0;
         if (src.off) {
@@ -1006,16 +1035,15 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                 for (int k = 0; k < 2; ++k) {
                     bool inside;
                     uint32_t shift;
-                    const uint32_t v = pixel_fetch(tile0, 0, y0, tid + 256 * k, inside, shift);
+                    const uint32_t v = pixel_fetch(tile0, 0, 2 * pw.s + y0, tid + 256 * k, inside, shift);
                     pixel_store(y0, tid + 256 * k, v, shift, inside);
                 }
         }
     } else {
 #pragma unroll 1
         for (int v = -1 + grp; v <= 4; v += 2) { // first, so that they travel while the correction is computed
-            const int u = (v + 1) / (2 * P);     // a tile of one or two rows: rows 3, 4 of the stream are the next unit's
-            const int i = u / J;
-            if (i < n_cnt) issue_row(n_begin + i, u - i * J, v - 2 * P * u, v);
+            if (v <= 2) issue_row(n_begin, 0, 2 * pw.s + v, v);
+            else if (p1.i < n_cnt) issue_row(n_begin + p1.i, p1.b, 2 * p1.s + v - 2, v);
         }
         if (grp == 0) prepare_init(n_begin);
     }
@@ -1025,15 +1053,17 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     __syncthreads();
 
     // LASTB: the nine border-aware channel sums of the last block's output (see strip_statistics) from the two
-    // rows in `a`.  The sum over the whole tile, the only one every pixel goes into, is kept in a register per
-    // lane: the 16 channel values of a lane (both rows added) go through one butterfly over the 32 pixel lanes,
-    // after which every lane holds the sum of one channel and adds it to its running total (run_sum; written to
-    // the record when the image is done).  First / last column: the one lane that holds it adds its 16 values
-    // to the LDS accumulators, in the wavefronts that contain such a column only.  First / last row and the four
-    // corners: the same for that row alone, in the (two) steps that contain those rows.
+    // rows in `a`, written as lines of C sums (LastSums).  The sum over the whole tile, the only one every pixel goes
+    // into, is kept in a register per lane: the 16 channel values of a lane (both rows added) go through one butterfly
+    // over the 32 pixel lanes, after which every lane holds the sum of one channel and adds it to its running total
+    // (run_sum), which becomes a line at the end of a chunk.  First / last column: the one lane that holds it adds its
+    // 16 values to the LDS accumulators, in the wavefronts that contain such a column only; a line per chunk.  First /
+    // last row and the four corners: lines of their own, in the (two) steps that contain those rows.
     float run_sum = 0.f;
-    auto last_block_statistics = [&](const f32x16 (&a)[RW], const float *si, int x, int x0w, int j, int pxl, int hf) {
-        float *stat = &s_stat[w4][0][hf * 16]; // + sum index * 32 + channel
+    auto last_block_statistics = [&](const f32x16 (&a)[RW], const float *si, const Pos &p, int x, int x0w, int pxl, int hf) {
+        const int j = p.s;
+        float *stat = &s_stat[w4][0][hf * 16];
+        float *lines = st.tout + (int64_t)(n_begin + p.i) * st.out_recs * C + cb * 32 + hf * 16;
         const bool colok = (uint32_t)x < (uint32_t)g.w;
         const bool allcols = x0w >= 0 && x0w + 32 <= g.w; // same for the whole wavefront
         const bool row1 = 2 * j + 1 < g.h;                // (row 2j always lies in the tile)
@@ -1060,9 +1090,30 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                 lds_accumulate4(dst + 4 * q, four, pred);
             }
         };
-        if (has_first) column(stat + 3 * 32, t, x == 0);
-        if (has_last) column(stat + 4 * 32, t, x == g.w - 1);
+        auto corner = [&](float *dst, const float (&val)[16], bool pred) { // the same into global memory, once
+            if (pred) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) *(f32x4 *)(dst + 4 * q) = (f32x4){val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
+            }
+        };
+        if (has_first) column(stat, t, x == 0);
+        if (has_last) column(stat + 32, t, x == g.w - 1);
         run_sum += reduce16_over_half(t, pxl);
+        if (j % kChunk == kChunk - 1 || j == S - 1) { // the chunk's lines
+            const int ch = j / kChunk, blk2 = p.b * 2 + xb, chunks = (S + kChunk - 1) / kChunk;
+            if ((pxl & 1) == 0) lines[(ch * 2 * J + blk2) * C + reduce16_index(pxl)] = run_sum;
+            run_sum = 0.f;
+            if (pxl < 16) {
+                if (has_first) {
+                    lines[(2 * J * chunks + ch) * C + pxl] = stat[pxl];
+                    stat[pxl] = 0.f;
+                }
+                if (has_last) {
+                    lines[((2 * J + 1) * chunks + ch) * C + pxl] = stat[32 + pxl];
+                    stat[32 + pxl] = 0.f;
+                }
+            }
+        }
         const int rl = g.h - 1 - 2 * j; // the tile's last row, counted from this pair's first
         if (j == 0 || rl < RW) { // the tile's first and / or last row is one of the two
 #pragma unroll 1
@@ -1076,20 +1127,17 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                     rv[v] = colok ? fmaxf(av + bias[v], 0.f) : 0.f;
                 }
                 const float y = reduce16_over_half(rv, pxl);
-                if ((pxl & 1) == 0) { // (an LDS add, as in lds_accumulate4)
-                    const lrow_t ad = lds_address(stat + (1 + which) * 32 + reduce16_index(pxl));
-                    asm volatile("ds_add_f32 %0, %1" : : "v"(ad), "v"(y) : "memory");
-                }
-                if (has_first) column(stat + (5 + 2 * which) * 32, rv, x == 0);
-                if (has_last) column(stat + (6 + 2 * which) * 32, rv, x == g.w - 1);
+                if ((pxl & 1) == 0) lines[(st.sum_rows + (which * J + p.b) * 2 + xb) * C + reduce16_index(pxl)] = y;
+                if (has_first) corner(lines + (st.sum_rows + 4 * J + 2 * which) * C, rv, x == 0);
+                if (has_last) corner(lines + (st.sum_rows + 4 * J + 2 * which + 1) * C, rv, x == g.w - 1);
             }
         }
     };
 
     // bias, ReLU, bf16, stores (or nothing: LASTB) and statistics of output rows 2j, 2j+1 of column block blk of
-    // image n held in `a`; after the last row pair of an image its channel sums go to its records and the
-    // accumulators are cleared
-    auto finish = [&](const f32x16 (&a)[RW], int n, int blk, int j) {
+    // image n held in `a`
+    auto finish = [&](const f32x16 (&a)[RW], const Pos &p) {
+        const int n = n_begin + p.i, blk = p.b, j = p.s;
         const int ln = pin_in_loop(tid & 63);
         const int pxl = ln & 31, hf = ln >> 5;
         const int x_lo = blk * kTileW - kSkew;     // first of the workgroup's 64 output columns (-1 in block 0 of a wide tile)
@@ -1135,24 +1183,11 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
             }
         }
         if (LASTB) {
-            if (st.tout) last_block_statistics(a, si, x, x_lo + xb * 32, j, pxl, hf);
+            if (st.tout) last_block_statistics(a, si, p, x, x_lo + xb * 32, pxl, hf);
         } else if (st.tout && ((j >> 1) & 7) == sample_phase) { // (the rows conv_mid would sample)
             const int ri = (((j >> 4) * 2 + (j & 1)) * J + blk) * 2 + xb; // sampled row pair, column block, pixel block
             strip_statistics<RW, false>(a, si, st.tout + ((int64_t)n * st.out_recs + ri) * C + cb * 32 + hf * 16, x, 2 * j, g.h,
                                         g.w, pxl);
-        }
-        if (LASTB && st.tout && j == S - 1 && blk == J - 1) { // what this wavefront gathered for the image (its own part of s_stat)
-            // the whole-tile sums lived in a register: one channel per lane
-            if ((pxl & 1) == 0) s_stat[w4][0][hf * 16 + reduce16_index(pxl)] = run_sum;
-            run_sum = 0.f;
-            float *rec = st.tout + ((int64_t)n * st.out_recs + xb) * stat_rec(C);
-            if (ln < 32) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    rec[q * C + cb * 32 + ln] = s_stat[w4][q][ln];
-                    s_stat[w4][q][ln] = 0.f;
-                }
-            }
         }
     };
 
@@ -1188,75 +1223,60 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     };
     // !FIRST, group A, in the middle of its step (between its matrix work and its epilogue): what the wavefront
     // issued a step ago - the two input rows of the step after this one, the seam columns - is waited for, then the
-    // two rows needed two steps from now are put on their way: rows 2s+1, 2s+2 of the unit of step sg + 2, or rows
-    // -1, 0 of the unit after it when that step is the one of the padding rows.  Their ring slots were last read in
-    // the step before this one.  In the middle of the step, not at its end: the vector-memory instructions of a
+    // two rows needed two steps from now are put on their way: rows 2s+1, 2s+2 of the position of step sg + 2.  Their
+    // ring slots were last read in the step before this one.  In the middle of the step, not at its end: the vector-memory instructions of a
     // compute unit queue up behind each other, and group B's stores at the start of the next step - the critical
     // path - would otherwise wait behind these twenty loads.
     auto input_loads = [&](int sg) {
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        if (pl.i < n_cnt) {
-            const bool nxt = pl.s == S;
-            const Pos lu = nxt ? next_unit(pl) : pl;
-            if (lu.i < n_cnt) {
-                issue_row(n_begin + lu.i, lu.b, (nxt ? -1 : 2 * pl.s + 1), 2 * sg + 5);
-                issue_row(n_begin + lu.i, lu.b, (nxt ? -1 : 2 * pl.s + 1) + 1, 2 * sg + 6);
-            }
+        if (pe.i < n_cnt) {
+            issue_row(n_begin + pe.i, pe.b, 2 * pe.s + 1, 2 * sg + 5);
+            issue_row(n_begin + pe.i, pe.b, 2 * pe.s + 2, 2 * sg + 6);
         }
     };
     // WIDE: ring pixels 0 and 1 of the intermediate rows group A writes in this step: the two columns left of its
-    // block, from the seam of the block before (zeros in block 0 and in the padding rows); 2 x 9 slots per row,
+    // block, from the seam of the block before (zeros in block 0 and at opening positions); 2 x 9 slots per row,
     // straight into LDS.  One wavefront issues them at the start of the step - a wavefront of the group that is
     // not the step's critical path: vector-memory instructions of a compute unit queue up behind each other, and
     // right after the barrier the queue still holds what was issued at the end of the previous step - and waits
     // for them before the step's barrier.
     const size_t seam_half = (size_t)(2 * S) * kSeamRowBytes; // one of a workgroup's two seam buffers
-    auto seam_loads = [&](int sg) {
-        if (w4 != 0 || pa.i >= n_cnt) return;
+    auto seam_loads = [&](int sg, const Pos &p) {
+        if (w4 != 0) return;
         const int ln = pin_in_loop(tid & 63);
-        const bool have = pa.b > 0 && pa.s < S;
-        const uint8_t *sp = st.seam + ((size_t)blockIdx.x * 2 + ((pa.b & 1) ^ 1)) * seam_half + (size_t)(2 * pa.s) * kSeamRowBytes;
+        const bool have = p.b > 0 && computes(p);
+        const uint8_t *sp = st.seam + ((size_t)blockIdx.x * 2 + ((p.b & 1) ^ 1)) * seam_half + (size_t)(2 * p.s) * kSeamRowBytes;
         const int spx = ln / K::SPP, sslot = ln - spx * K::SPP;
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
-            const uint8_t *p = (have && sslot < C / 8) ? sp + r * kSeamRowBytes + spx * (C * 2) + sslot * 16 : zeros;
+            const uint8_t *src16 = (have && sslot < C / 8) ? sp + r * kSeamRowBytes + spx * (C * 2) + sslot * 16 : zeros;
             if (ln < 2 * K::SPP)
-                __builtin_amdgcn_global_load_lds((gptr_t)p, (lptr_t)(ring_mid + slot_of(2 * sg + r) * ROWB), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((gptr_t)src16, (lptr_t)(ring_mid + slot_of(2 * sg + r) * ROWB), 16, 0, 0);
         }
     };
     f32x16 acc[RW];
-    const int n_steps = n_cnt * J * P + 2;
+    const int n_steps = n_pos + 2;
 #pragma unroll 1
     for (int sg = 0; sg < n_steps; ++sg) {
-        const bool fin = pf.i >= 0 && pf.i < n_cnt && pf.s < S; // rows accumulated in the previous step wait for their epilogue
+        const bool fin = (FIRST || grp == 1) && sg >= 3 && pe.i < n_cnt && owns(pe); // rows accumulated in the previous step wait for their epilogue
         uint8_t *seam_rows_step = nullptr;
         if (grp == 0) {
             const int ln = pin_in_loop(tid & 63);
             const int pxl = ln & 31, hf = ln >> 5;
             const int xl = xb * 32 + pxl;          // this lane's column within the block
-            const int x = pa.b * kTileW + xl;      // and within the tile
+            const int x = pw.b * kTileW + xl;      // and within the tile
             uint8_t *seam_rows = nullptr;          // WIDE: where the seam columns of this step's rows go, if anywhere
-            if (WIDE && !FIRST) seam_loads(sg);    // (waited for at the end of the step, with this group's other loads)
+            if (WIDE && !FIRST) seam_loads(sg, pw); // (waited for at the end of the step, with this group's other loads)
             // FIRST: the raw pixels of virtual rows 2sg+3, 2sg+4 (window of step sg+1) start their way into registers
             uint32_t pv[2] = {0, 0}, psh[2] = {0, 0};
             bool pin[2] = {false, false};
-            bool fetch = false;
-            if (FIRST && p1.i < n_cnt) {
-                int y0 = 2 * p1.s + 1, fb = p1.b;
-                fetch = true;
-                if (p1.s == S) { // rows -1, 0 of the next unit
-                    const Pos nu = next_unit(p1);
-                    fetch = nu.i < n_cnt;
-                    y0 = -1;
-                    fb = nu.b;
-                    if (fetch && nu.b == 0) tile0 = tile_origin(n_begin + nu.i);
-                }
-                if (fetch) {
+            const bool fetch = FIRST && p1.i < n_cnt;
+            if (fetch) {
+                if (p1.s == -1 && p1.b == 0) tile0 = tile_origin(n_begin + p1.i); // the next image opens
 #pragma unroll
-                    for (int k = 0; k < 2; ++k) pv[k] = pixel_fetch(tile0, fb * kTileW, y0, tid + 256 * k, pin[k], psh[k]);
-                }
+                for (int k = 0; k < 2; ++k) pv[k] = pixel_fetch(tile0, p1.b * kTileW, 2 * p1.s + 1, tid + 256 * k, pin[k], psh[k]);
             }
-            if (pa.i < n_cnt && pa.s < S) {
+            if (pw.i < n_cnt && computes(pw)) {
                 if (FIRST) {
                     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1290,20 +1310,20 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                 }
                 // epilogue: + bias and correction, ReLU, bf16 -> intermediate ring (zeros outside the tile)
                 const float *si = &s_initA[cb * 32 + hf * 16];
-                const uint32_t dbase = dither16(x, 2 * pa.s);
+                const uint32_t dbase = dither16(x, 2 * pw.s);
                 // WIDE: the last two columns of the block also go to the seam (seam_flush below): the workgroup's
                 // own (for its next column block) or the image's (the tile's last two columns, for conv_seam_kernel)
                 if (WIDE) {
-                    if (pa.b + 1 < J) seam_rows = st.seam + ((size_t)blockIdx.x * 2 + (pa.b & 1)) * seam_half;
-                    else if (st.seam_last) seam_rows = st.seam_last + (size_t)(n_begin + pa.i) * seam_half;
-                    if (seam_rows) seam_rows += (size_t)(2 * pa.s) * kSeamRowBytes;
+                    if (pw.b + 1 < J) seam_rows = st.seam + ((size_t)blockIdx.x * 2 + (pw.b & 1)) * seam_half;
+                    else if (st.seam_last && owns(pw)) seam_rows = st.seam_last + (size_t)(n_begin + pw.i) * seam_half;
+                    if (seam_rows) seam_rows += (size_t)(2 * pw.s) * kSeamRowBytes;
                 }
 #pragma unroll
                 for (int hq = 0; hq < 2; ++hq) {
                     const f32x4 b0 = *(const f32x4 *)(si + 8 * hq), b1 = *(const f32x4 *)(si + 8 * hq + 4);
 #pragma unroll
                     for (int r = 0; r < RW; ++r) {
-                        const int y = 2 * pa.s + r;
+                        const int y = 2 * pw.s + r;
                         const uint32_t dth = dbase ^ ((uint32_t)r << 15);
                         u32x4 pk;
                         pk[0] = pack_bf16_relu(acc[r][8 * hq + 0] + b0[0], acc[r][8 * hq + 1] + b0[1], dth, true);
@@ -1314,7 +1334,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                         *(u32x4 *)(ring_mid + slot_of(2 * sg + r) * ROWB + (1 + kSkew + xl) * K::PS + (cb * 32 + hf * 16 + 8 * hq) * 2) = pk;
                     }
                 }
-            } else if (pa.i < n_cnt) { // the rows below the tile: zero padding of the second block (and above the next image)
+            } else { // opening position: zero padding of the second block, below the unit before and above this one
                 if (!FIRST) input_loads(sg);
 #pragma unroll
                 for (int r = 0; r < RW; ++r)
@@ -1322,7 +1342,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                     for (int hq = 0; hq < 2; ++hq)
                         *(u32x4 *)(ring_mid + slot_of(2 * sg + r) * ROWB + (1 + kSkew + xl) * K::PS + (cb * 32 + hf * 16 + 8 * hq) * 2) =
                             (u32x4){0u, 0u, 0u, 0u};
-                if (!FIRST && pa.b == J - 1 && pa.i + 1 < n_cnt) prepare_init(n_begin + pa.i + 1); // nobody reads s_initA in this step
+                if (!FIRST && pw.b == 0 && pw.i < n_cnt) prepare_init(n_begin + pw.i); // nobody reads s_initA in this step
             }
             // WIDE: once per step this group waits for all of its global memory traffic, at a point where it has
             // to wait for its loads anyway; the stores of the previous step are then known to be done, among them
@@ -1344,13 +1364,13 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                         const f32x4 v = *(const f32x4 *)(srcx + (r * 4 + q) * 256);
                         a[r][4 * q] = v[0]; a[r][4 * q + 1] = v[1]; a[r][4 * q + 2] = v[2]; a[r][4 * q + 3] = v[3];
                     }
-                finish(a, n_begin + pf.i, pf.b, pf.s);
+                finish(a, pe);
             }
         } else {
             const int ln = pin_in_loop(tid & 63);
-            if (WIDE && FIRST) seam_loads(sg); // (group A is the critical path of this variant)
-            if (!FIRST && fin) finish(acc, n_begin + pf.i, pf.b, pf.s); // the rows accumulated in the previous step
-            if (pb.i >= 0 && pb.i < n_cnt && pb.s < S) {
+            if (WIDE && FIRST) seam_loads(sg, p1); // (group A is the critical path of this variant)
+            if (!FIRST && fin) finish(acc, pe); // the rows accumulated in the previous step
+            if (sg >= 2 && pw.i < n_cnt && owns(pw)) {
                 lrow_t rowp[RW + 2];
 #pragma unroll
                 for (int r = 0; r < RW + 2; ++r) rowp[r] = mid_base + (uint32_t)slot_of(2 * (sg - 2) - 1 + r) * ROWB;
@@ -1369,11 +1389,9 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         if (!FIRST && WIDE && grp == 0) seam_flush(seam_rows_step, sg);
         if (WIDE && FIRST && grp == 1 && w4 == 0) __builtin_amdgcn_s_waitcnt(kWaitVm0); // the seam columns have landed
         lds_barrier();
-        advance(pa);
-        advance(pb);
-        advance(pf);
-        advance(pl);
-        advance(p1);
+        if (sg >= w_start) advance(pw);
+        if (sg >= e_start) advance(pe);
+        if (FIRST) advance(p1);
     }
 }
 
@@ -1382,16 +1400,14 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
 // column right of them is the zero padding, so only the taps dx = 0, 1 count.  One workgroup of two wavefronts
 // (one per 32 output channels) per 32 rows of an image; a lane's pixel is a row.  Operands come straight from
 // global memory: the launch is a fraction of a percent of the fused one's work.
-// LASTB: instead of activations the column's share of the nine border-aware channel sums, one record per
-// workgroup (record rec_first + its index within the image).
+// LASTB: instead of activations the column's lines of the nine border-aware channel sums (LastSums).
 template <int C, bool LASTB>
 __global__ __launch_bounds__(128) void conv_seam_kernel(const uint8_t *__restrict__ seam_last, ConvGeom g,
                                                         const bf16_t *__restrict__ wfragB, const float *__restrict__ biasB,
-                                                        float *__restrict__ tout, int out_recs, int rec_first,
+                                                        float *__restrict__ tout, int out_recs, LastSums sums,
                                                         bf16_t *__restrict__ out)
 {
     typedef MidCfg<C> K;
-    __shared__ float s_rec[LASTB ? stat_rec(C) : 1];
     const int lane = threadIdx.x & 63;
     const int cb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int px = lane & 31, half = lane >> 5;
@@ -1400,10 +1416,6 @@ __global__ __launch_bounds__(128) void conv_seam_kernel(const uint8_t *__restric
     const int r = t * 32 + px; // this lane's output row
     const uint8_t *sl = seam_last + (size_t)n * (2 * ((g.h + 1) / 2)) * kSeamRowBytes;
     const bf16x8 *wp = (const bf16x8 *)wfragB + (size_t)cb * 9 * K::KC * 64 + lane;
-    if (LASTB) {
-        for (int i = threadIdx.x; i < stat_rec(C); i += 128) s_rec[i] = 0.f;
-        __syncthreads();
-    }
     // all operands are asked for before the first is used (unconditional loads from a clamped row; what lies
     // outside the tile is dropped afterwards): the launch is bound by memory latency, not by its 24 matrix instructions
     u32x4 bv[3][2][K::KC];
@@ -1449,29 +1461,21 @@ __global__ __launch_bounds__(128) void conv_seam_kernel(const uint8_t *__restric
             *(u32x4 *)(dst + 8) = hi;
         }
     } else if (tout) {
-        // sums 0 (everything) and 4 (last column): all rows; 1 and 6 (first row, its right corner): row 0;
-        // 2 and 8 (last row, its right corner): row h-1.  Every entry has one writer.
-        const int ch = cb * 32 + half * 16;
+        // a line for these rows of the last column, and the column's first / last row: the right corners
+        float *lines = tout + (int64_t)n * out_recs * C + cb * 32 + half * 16;
+        float col[16], tot[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const float a = r < g.h ? fmaxf(val[v], 0.f) : 0.f;
-            const float tot = half_sum(a);
-            if (px == kSumLane) {
-                s_rec[0 * C + ch + v] = tot;
-                s_rec[4 * C + ch + v] = tot;
-            }
-            if (r == 0) {
-                s_rec[1 * C + ch + v] = a;
-                s_rec[6 * C + ch + v] = a;
-            }
-            if (r == g.h - 1) {
-                s_rec[2 * C + ch + v] = a;
-                s_rec[8 * C + ch + v] = a;
-            }
+            col[v] = r < g.h ? fmaxf(val[v], 0.f) : 0.f;
+            tot[v] = half_sum(col[v]);
         }
-        __syncthreads();
-        float *rec = tout + ((int64_t)n * out_recs + rec_first + t) * stat_rec(C);
-        for (int i = threadIdx.x; i < stat_rec(C); i += 128) rec[i] = s_rec[i];
+        auto put = [](float *dst, const float (&src)[16]) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *(f32x4 *)(dst + 4 * q) = (f32x4){src[4 * q], src[4 * q + 1], src[4 * q + 2], src[4 * q + 3]};
+        };
+        if (px == kSumLane) put(lines + (sums.last_col + t) * C, tot);
+        if (r == 0) put(lines + (sums.corners + 1) * C, col);
+        if (r == g.h - 1) put(lines + (sums.corners + 3) * C, col);
     }
 }
 
@@ -1719,11 +1723,28 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
 //   (dy = 0 never reaches the last row, dy = 2 never the first; same for dx and columns).
 // IPB images per block share every weight read.
 // ------------------------------------------------------------------------------------------------
+// Sum of the 16-byte pieces p[r * stride], r = start, start + step, .. < count, four loads in flight.
+__device__ __forceinline__ f32x4 sum_lines(const f32x4 *p, int stride, int start, int step, int count)
+{
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int r0 = start; r0 < count; r0 += 4 * step) {
+        f32x4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = p[(int64_t)min(r0 + u * step, count - 1) * stride];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += r0 + u * step < count ? v[u][e] : 0.f;
+    }
+    return sum;
+}
+
 constexpr int kHeadIpb = 1;   // images per block (a launch of a few hundred images should reach every compute unit)
 constexpr int kHeadKParts = 8; // the k = (channel, tap) range is cut in eight, one part per 64 threads
 constexpr int kHeadThreads = 64 * kHeadKParts;
 
-__global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restrict__ recs, int slots, int C, int n_img,
+__global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restrict__ recs, LastSums sums, int C, int n_img,
                                                    int n_bits, int nbp, float inv_hw,
                                                    const float *__restrict__ wft /*[C*9][nbp]*/,
                                                    const float *__restrict__ fbias, const float *__restrict__ lin_w,
@@ -1738,33 +1759,58 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
     __shared__ uint8_t sbit[kHeadIpb][128];
     const int tid = threadIdx.x;
     const int64_t n0 = (int64_t)blockIdx.x * kHeadIpb;
-    // records -> Q: groups of 9 C / 4 threads (16 bytes each) take every `groups`-th record, four loads in flight;
-    // a launch of few images has a record per workgroup and wavefront that worked on one, 128 of them for a 128 x 128
-    // tile, which cost 71 us when every thread added up its entries one load after the other
-    const int lpr = 9 * C / 4, groups = kHeadThreads / lpr;
     for (int i = 0; i < kHeadIpb; ++i) {
-        const int grp = tid / lpr, l = tid - grp * lpr;
-        if (grp < groups) {
-            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-            if (n0 + i < n_img) {
-                const f32x4 *p = (const f32x4 *)recs + (n0 + i) * slots * lpr + l;
-                for (int r0 = grp; r0 < slots; r0 += 4 * groups) {
-                    f32x4 v[4];
+        const bool have = n0 + i < n_img;
+        if (sums.records) {
+            // records -> Q: groups of 9 C / 4 threads (16 bytes each) take every `groups`-th record, four loads in
+            // flight; a launch of few images has a record per workgroup and wavefront that worked on one, 128 of them for
+            // a 128 x 128 tile, which cost 71 us when every thread added up its entries one load after the other
+            const int lpr = 9 * C / 4, groups = kHeadThreads / lpr;
+            const int grp = tid / lpr, l = tid - grp * lpr;
+            if (grp < groups) {
+                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+                if (have) sum = sum_lines((const f32x4 *)recs + (n0 + i) * sums.records * lpr + l, lpr, grp, groups, sums.records);
+                *(f32x4 *)&Qp[(grp * lpr + l) * 4] = sum;
+            }
+            __syncthreads();
+            for (int r = tid; r < 9 * C; r += kHeadThreads) {
+                float v = 0.f;
+                for (int g2 = 0; g2 < groups; ++g2) v += Qp[g2 * 9 * C + r];
+                Q[i][r] = v;
+            }
+        } else {
+            // lines (C = 64) -> Q: wavefronts 0 .. 3 the whole-tile lines, 4 and 5 the columns, 6 the rows, 7 the
+            // corners; 16 bytes per lane, i.e. four lines per load and four loads in flight
+            const int wave = tid >> 6, lane = tid & 63, l = lane & 15, sub = lane >> 4;
+            const f32x4 *p = (const f32x4 *)recs + (n0 + i) * sums.lines * 16 + l;
+            auto total = [&](int first, int count, int start, int step, float *dst) {
+                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                if (have) v = sum_lines(p + first * 16, 16, start, step, count);
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) v[u] = p[(int64_t)min(r0 + u * groups, slots - 1) * lpr];
+                for (int sh = 16; sh < 64; sh <<= 1)
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) sum[e] += r0 + u * groups < slots ? v[u][e] : 0.f;
+                    for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], sh);
+                if (sub == 0) *(f32x4 *)(dst + 4 * l) = v;
+            };
+            if (wave < 4) total(0, sums.first_col, wave * 4 + sub, 16, &Qp[wave * 64]);
+            else if (wave == 4) total(sums.first_col, sums.last_col - sums.first_col, sub, 4, &Q[i][3 * 64]);
+            else if (wave == 5) total(sums.last_col, sums.rows - sums.last_col, sub, 4, &Q[i][4 * 64]);
+            else if (wave == 6) {
+                const int half = (sums.corners - sums.rows) / 2;
+                total(sums.rows, half, sub, 4, &Q[i][1 * 64]);
+                total(sums.rows + half, half, sub, 4, &Q[i][2 * 64]);
+            } else {
+                *(f32x4 *)&Q[i][(5 + sub) * 64 + 4 * l] = have ? p[(sums.corners + sub) * 16] : (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
+            __syncthreads();
+            if (tid < 64) {
+                Q[i][tid] = (Qp[tid] + Qp[64 + tid]) + (Qp[128 + tid] + Qp[192 + tid]);
+                if (sums.seam) { // the last column was computed apart: it is not in the whole-tile and row lines yet
+                    Q[i][tid] += Q[i][4 * 64 + tid];
+                    Q[i][1 * 64 + tid] += Q[i][6 * 64 + tid];
+                    Q[i][2 * 64 + tid] += Q[i][8 * 64 + tid];
                 }
             }
-            *(f32x4 *)&Qp[(grp * lpr + l) * 4] = sum;
-        }
-        __syncthreads();
-        for (int r = tid; r < 9 * C; r += kHeadThreads) {
-            float v = 0.f;
-            for (int g2 = 0; g2 < groups; ++g2) v += Qp[g2 * 9 * C + r];
-            Q[i][r] = v;
         }
         __syncthreads();
     }
@@ -1951,10 +1997,17 @@ hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, 
 
 bool conv_pair_supported(int C, const ConvGeom &g) { return C == 64 && g.colblks >= 1; }
 
-int conv_pair_last_records(const ConvGeom &g)
+LastSums conv_pair_last_sums(const ConvGeom &g)
 {
-    const bool seam_column = g.colblks > 1 && g.w % kTileW == 0; // conv_seam_kernel adds records of its own
-    return kPairSub + (seam_column ? (g.h + 31) / 32 : 0);
+    const int chunks = ((g.h + 1) / 2 + kChunk - 1) / kChunk;
+    LastSums l{};
+    l.seam = g.colblks > 1 && g.w % kTileW == 0;
+    l.first_col = chunks * 2 * g.colblks;
+    l.last_col = l.first_col + chunks;
+    l.rows = l.last_col + (l.seam ? (g.h + 31) / 32 : chunks); // (conv_seam_kernel: a line per 32 rows)
+    l.corners = l.rows + 4 * g.colblks;
+    l.lines = l.corners + 4;
+    return l;
 }
 
 size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu)
@@ -1964,13 +2017,13 @@ size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu)
     return half * (2 * (size_t)num_cu + (g.w % kTileW == 0 ? (size_t)g.n_img : 0));
 }
 
-template <bool FIRST, bool LASTB>
+template <bool FIRST, bool LASTB, bool PART>
 static void launch_pair_variant(bool wide, dim3 grid, hipStream_t s, const uint8_t *zeros, const uint8_t *in, const TileSrc &src,
                                 const ConvGeom &g, const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a,
                                 const float *bias_b, const PairArgs &st, bf16_t *out)
 {
-    if (wide) hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, true>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-    else hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, false>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+    if (wide) hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, true, PART>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+    else hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, false, PART>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
 }
 
 hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
@@ -1982,36 +2035,49 @@ hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileS
     const bool wide = g.colblks > 1;
     const bool seam_column = wide && g.w % kTileW == 0;
     if (wide && !seam) return hipErrorInvalidValue;
-    const int ipw = (g.n_img + num_cu - 1) / num_cu;
-    const dim3 grid((g.n_img + ipw - 1) / ipw);
+    // Whole images per workgroup if that keeps all but 4 % of the compute units busy, else every compute unit one run of
+    // the launch's row pairs.
+    const int quant = last ? kChunk : 1;
+    const int ppi = ((g.h + 1) / 2 + quant - 1) / quant;
+    const int64_t pieces = (int64_t)g.n_img * ppi;
+    const int whole = (g.n_img + num_cu - 1) / num_cu;
+    const bool part = (int64_t)g.n_img * 100 < (int64_t)whole * num_cu * 96;
+    const int per = part ? (int)((pieces + num_cu - 1) / num_cu) : whole * ppi;
+    const dim3 grid((unsigned)((pieces + per - 1) / per));
     if ((int)grid.x > num_cu) return hipErrorInvalidValue; // the seam buffer holds num_cu workgroups
     const size_t half = (size_t)(2 * ((g.h + 1) / 2)) * kSeamRowBytes;
     uint8_t *seam_last = seam_column ? seam + 2 * (size_t)num_cu * half : nullptr;
-    const int out_recs = last ? conv_pair_last_records(g) : conv_pair_samples(g).recs;
-    PairArgs st{tin, rsum_a, tout, out_recs, ipw, seam, seam_last};
+    const LastSums sums = conv_pair_last_sums(g);
+    const int out_recs = last ? sums.lines : conv_pair_samples(g).recs;
+    PairArgs st{tin, rsum_a, tout, out_recs, per, sums.rows, seam, seam_last};
     const TileSrc src = first ? *first : TileSrc{};
-    if (first) {
-        if (last) launch_pair_variant<true, true>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-        else launch_pair_variant<true, false>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-    } else {
-        if (last) launch_pair_variant<false, true>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-        else launch_pair_variant<false, false>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-    }
+    auto launch = [&](auto part) {
+        constexpr bool PART = decltype(part)::value;
+        if (first) {
+            if (last) launch_pair_variant<true, true, PART>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            else launch_pair_variant<true, false, PART>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+        } else {
+            if (last) launch_pair_variant<false, true, PART>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            else launch_pair_variant<false, false, PART>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+        }
+    };
+    if (part) launch(std::true_type{});
+    else launch(std::false_type{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !seam_column) return e;
     const dim3 sgrid((unsigned)g.n_img * (unsigned)((g.h + 31) / 32));
-    if (last) hipLaunchKernelGGL((conv_seam_kernel<64, true>), sgrid, dim3(128), 0, s, seam_last, g, wfrag_b, bias_b, tout, out_recs, kPairSub, out);
-    else hipLaunchKernelGGL((conv_seam_kernel<64, false>), sgrid, dim3(128), 0, s, seam_last, g, wfrag_b, bias_b, tout, out_recs, kPairSub, out);
+    if (last) hipLaunchKernelGGL((conv_seam_kernel<64, true>), sgrid, dim3(128), 0, s, seam_last, g, wfrag_b, bias_b, tout, out_recs, sums, out);
+    else hipLaunchKernelGGL((conv_seam_kernel<64, false>), sgrid, dim3(128), 0, s, seam_last, g, wfrag_b, bias_b, tout, out_recs, sums, out);
     return hipGetLastError();
 }
 
-hipError_t launch_head(const float *recs, int slots, int C, int64_t n_img, int n_bits, int nbp, float inv_hw,
+hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n_img, int n_bits, int nbp, float inv_hw,
                        const float *wft, const float *fbias, const float *lin_w, const float *lin_b, float *logits,
                        uint8_t *bits, uint8_t *symbols, int m, hipStream_t s)
 {
     if (n_img <= 0) return hipSuccess;
     const unsigned blocks = (unsigned)((n_img + kHeadIpb - 1) / kHeadIpb);
-    hipLaunchKernelGGL(head_kernel, dim3(blocks), dim3(kHeadThreads), 0, s, recs, slots, C, (int)n_img, n_bits, nbp, inv_hw, wft,
+    hipLaunchKernelGGL(head_kernel, dim3(blocks), dim3(kHeadThreads), 0, s, recs, sums, C, (int)n_img, n_bits, nbp, inv_hw, wft,
                        fbias, lin_w, lin_b, logits, bits, symbols, m);
     return hipGetLastError();
 }

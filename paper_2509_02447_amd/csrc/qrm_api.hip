@@ -287,8 +287,8 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
             if (cnt <= 0) continue;
             const Partition pm = make_partition(cnt, tpi, mid_blocks(c), conv_mid_records_per_workgroup(c->C));
             const ConvGeom g{(int)cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
-            // floats per image: records of the last block, or sampled channel sums of any other
-            const size_t last = std::max(c->pairable ? conv_pair_last_records(g) : 0, pm.slots * pm.sub) * last_record_floats(c->C);
+            // floats per image: what the last block leaves for the head, or sampled channel sums of any other
+            const size_t last = std::max(c->pairable ? (size_t)conv_pair_last_sums(g).lines * c->C : 0, pm.slots * pm.sub * last_record_floats(c->C));
             const int samples = std::max(c->pairable ? conv_pair_samples(g).recs : 0,
                                          std::max(conv_first_samples(g, c->C).recs, conv_mid_samples(g, c->C).recs));
             recs = std::max(recs, (size_t)cnt * std::max(last, (size_t)samples * c->C));
@@ -424,8 +424,9 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         const Partition pm = make_partition(cnt, tpi, mid_blocks(c), conv_mid_records_per_workgroup(c->C));
         src.img = img0 + n0 * 3 * (int64_t)src.H * src.W;
         src.off = off0 ? off0 + 2 * n0 : nullptr;
-        int cur = 0, tcur = 0, last_recs = 0; // records of nine sums per image, once the last block has run
-        MeanIn means{};                       // channel sums the next block reads
+        int cur = 0, tcur = 0;
+        MeanIn means{};         // channel sums the next block reads
+        LastSums last_sums{};   // what the last block has left
         const int blocks = n_run > 0 ? n_run : c->n_blocks; // blocks to run: the first one and C -> C layers m = b - 1
         // Fused schedule (64 channels; see use_fused): [first + layer 0], (1,2), (3,4), ..; what is left over
         // runs alone.
@@ -439,7 +440,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                                  nullptr, tb[tcur], is_last(1), c->num_cu, seam, buf[cur], s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_pair (first) launch");
             time_end(t, s);
-            if (is_last(1)) last_recs = conv_pair_last_records(g);
+            if (is_last(1)) last_sums = conv_pair_last_sums(g);
             else means = conv_pair_samples(g);
             b = 2;
         } else {
@@ -462,7 +463,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                                      tb[tcur ^ 1], is_last(b + 1), c->num_cu, seam, buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_pair launch");
                 time_end(t, s);
-                if (is_last(b + 1)) last_recs = conv_pair_last_records(g);
+                if (is_last(b + 1)) last_sums = conv_pair_last_sums(g);
                 else means = conv_pair_samples(g);
             } else {
                 qrm_ctx::Timed *t = time_begin(c, may_time, is_last(b) ? QRM_PROFILE_BLOCK_LAST : QRM_PROFILE_BLOCK_MID,
@@ -471,7 +472,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                                     rsum, tb[tcur ^ 1], pm, is_last(b), buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_mid launch");
                 time_end(t, s);
-                if (is_last(b)) last_recs = pm.slots * pm.sub;
+                if (is_last(b)) last_sums = LastSums{pm.slots * pm.sub, 0, 0, 0, 0, 0, 0};
                 else means = conv_mid_samples(g, c->C);
             }
             cur ^= 1;
@@ -488,7 +489,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         uint8_t *sy = nsym ? d_symbols + n0 * nsym : nullptr;
         qrm_ctx::Timed *t = time_begin(c, may_time, QRM_PROFILE_HEAD, 0.0, s);
         if (c->collapse) {
-            e = launch_head(tb[tcur], last_recs, c->C, cnt, c->n_bits, c->nbp, inv_hw, c->d_wft, c->d_bias_final,
+            e = launch_head(tb[tcur], last_sums, c->C, cnt, c->n_bits, c->nbp, inv_hw, c->d_wft, c->d_bias_final,
                             c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {

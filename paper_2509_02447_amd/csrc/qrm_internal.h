@@ -60,6 +60,15 @@ struct MeanIn {
     int recs;         // records per image
     float inv_cnt;    // 1 / pixels of an image behind its records
 };
+// What the last block leaves of an image for the head: `records` records of nine sums per channel, or (records = 0)
+// `lines` lines of C sums.  Lines 0 .. first_col-1: the whole tile, a line per chunk of row pairs, column block and block
+// of 32 columns; from first_col / last_col on: the first / last column, a line per chunk; from rows on: the first, then
+// the last row, a line per column block and block of 32 columns; from corners on: top left, top right, bottom left,
+// bottom right.  seam: the last column was computed apart and is missing from the whole-tile and the row lines.
+struct LastSums {
+    int records;
+    int lines, first_col, last_col, rows, corners, seam;
+};
 MeanIn conv_first_samples(const ConvGeom &g, int C); // (rec null)
 MeanIn conv_mid_samples(const ConvGeom &g, int C);
 MeanIn conv_pair_samples(const ConvGeom &g);
@@ -86,18 +95,18 @@ hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, 
 // block; in / tin / rsum_a unused); otherwise both are C -> C blocks and tin / rsum_a are as for
 // launch_conv_mid (first block only: the second block's weights are rounded so that it needs no correction).
 // tout: channel sums of the output (conv_pair_samples()).  last: the second block is the network's last one: no
-// activations are written, tout receives conv_pair_last_records() records of nine sums per channel and image.
+// activations are written, tout receives lines of channel sums (conv_pair_last_sums()).
 bool conv_pair_supported(int C, const ConvGeom &g);
-int conv_pair_last_records(const ConvGeom &g);
+LastSums conv_pair_last_sums(const ConvGeom &g);
 size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu);
 hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
                             const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a, const float *bias_b,
                             const MeanIn &tin, const float *rsum_a, float *tout, bool last, int num_cu,
                             uint8_t *seam, bf16_t *out, hipStream_t s);
 
-// nine channel sums of the last block -> final conv + average pool in closed form -> linear -> logits,
+// recs / sums: channel sums of the last block -> final conv + average pool in closed form -> linear -> logits,
 // bits, symbols.  wft: final conv weights fp32, [C*9][nbp] (k = c*9 + tap major)
-hipError_t launch_head(const float *recs, int slots, int C, int64_t n_img, int n_bits, int nbp, float inv_hw,
+hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n_img, int n_bits, int nbp, float inv_hw,
                        const float *wft, const float *fbias, const float *lin_w, const float *lin_b, float *logits,
                        uint8_t *bits, uint8_t *symbols, int m, hipStream_t s);
 
