@@ -498,7 +498,7 @@ struct StatArgs {
     const float *rsum;  // [c_in][c_out] residual-weight sums of this layer (fp32)
     float *tout;        // records written by this launch: MODE_MID [n_img][out_recs][C], MODE_LAST [n_img][out_recs][9 C]
     int out_recs;       // records per image
-    int per;            // tiles per workgroup: divides, or is a multiple of, the tiles of one image
+    int per;            // strips per workgroup
 };
 
 constexpr int MODE_MID = 0;  // write activations, sample channel sums from every eighth strip
@@ -564,7 +564,6 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
     const int t_begin = vb * st.per;
     const int ns = min(total, t_begin + st.per) - t_begin; // strips of this workgroup's run
     if (ns <= 0) return;
-    const int out_slot = st.per >= tpi ? 0 : (t_begin % tpi) / st.per;
     const lrow_t lbase = lds_address(lds) + (xb * 32 + px) * K::PS + half * 16;
     const size_t img_bytes = (size_t)g.h * g.w * C * 2;
 
@@ -626,7 +625,8 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
     auto flush = [&](int n) {
         if (MODE == MODE_LAST && st.tout) {
             const int lane = pin_in_loop(tid & 63);
-            float *rec = st.tout + ((int64_t)n * st.out_recs + out_slot * R::NSUB + wave / K::NCB) * stat_rec(C);
+            const int slot = vb - (n * tpi) / st.per; // which of the workgroups that touch the image this is
+            float *rec = st.tout + ((int64_t)n * st.out_recs + slot * R::NSUB + wave / K::NCB) * stat_rec(C);
             if (lane < 32) {
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
@@ -1769,7 +1769,9 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
             const int grp = tid / lpr, l = tid - grp * lpr;
             if (grp < groups) {
                 f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-                if (have) sum = sum_lines((const f32x4 *)recs + (n0 + i) * sums.records * lpr + l, lpr, grp, groups, sums.records);
+                const int first = (int)((n0 + i) * sums.strips) / sums.per, last = (int)((n0 + i) * sums.strips + sums.strips - 1) / sums.per;
+                const int count = (last - first + 1) * sums.sub; // of the workgroups that touched the image
+                if (have) sum = sum_lines((const f32x4 *)recs + (n0 + i) * sums.records * lpr + l, lpr, grp, groups, count);
                 *(f32x4 *)&Qp[(grp * lpr + l) * 4] = sum;
             }
             __syncthreads();
@@ -2082,25 +2084,18 @@ hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n
     return hipGetLastError();
 }
 
-// Tiles are dealt to workgroups in contiguous runs of `per`; `per` divides the tiles of one image or is
-// a multiple of them, so a workgroup never holds two partial images and an image is touched by exactly
-// `slots` workgroups.
+// Strips are dealt to workgroups in contiguous runs of `per` that begin and end anywhere; an image is touched by at most
+// `slots` workgroups.  (Runs that divide an image, or are whole images, left workgroups without work: 16 tiles of
+// 75 x 100, 38 strips each, went to 32 of 256 compute units.)
 Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks, int sub)
 {
     Partition p{};
     p.sub = sub;
     const int64_t total = n_img * tiles_per_image;
-    int64_t want = (total + target_blocks - 1) / target_blocks;
-    if (want < 1) want = 1;
-    if (want >= tiles_per_image) {
-        p.per = (int)((want + tiles_per_image - 1) / tiles_per_image) * tiles_per_image;
-        p.slots = 1;
-    } else {
-        int d = (int)want;
-        while (tiles_per_image % d) ++d;
-        p.per = d;
-        p.slots = tiles_per_image / d;
-    }
+    p.per = (int)std::max<int64_t>(1, (total + target_blocks - 1) / target_blocks);
+    if (p.per % tiles_per_image == 0) p.slots = 1;
+    else if (tiles_per_image % p.per == 0) p.slots = tiles_per_image / p.per;
+    else p.slots = (tiles_per_image + p.per - 2) / p.per + 1;
     p.blocks = (int)((total + p.per - 1) / p.per);
     return p;
 }

@@ -244,13 +244,15 @@ int default_micro_batch(const qrm_ctx *c, int h, int w)
 }
 
 // Whether a launch of cnt images of h x w runs the fused schedule (two blocks per launch).  Narrow tiles always
-// do; wide ones only when the launch has images for at least half of the compute units (a workgroup of the fused
-// kernel takes whole images; the single-block kernel deals strips).
-bool use_fused(const qrm_ctx *c, int cnt, int w, int blocks)
+// do (1.04 .. 1.3 times as fast at 1 .. 400 tiles of 16 x 64 .. 64 x 64).  On wide tiles a workgroup's run of row pairs costs three
+// steps more per column block than it has row pairs, the single-block kernel's run of strips costs none: fused is 0.45 ..
+// 0.85 times as fast below two row pairs per compute unit, 0.92 .. 1.03 at four to ten, 0.97 .. 1.08 at 12 to 16 and 1.06 ..
+// 1.10 from 25 on (75 x 100, 96 x 96, 128 x 128, 256 x 256, 32 x 200, 200 x 66; eight blocks).
+bool use_fused(const qrm_ctx *c, int cnt, int h, int w, int blocks)
 {
     if ((c->diag_flags & QRM_DIAG_NO_FUSED_PAIRS) || !c->pairable || blocks < 2) return false;
     if (w <= kTileW || (c->diag_flags & QRM_DIAG_FUSE_ALWAYS)) return true;
-    return 2 * cnt >= c->num_cu;
+    return (int64_t)cnt * ((h + 1) / 2) >= 12 * (int64_t)c->num_cu;
 }
 
 int effective_micro_batch(const qrm_ctx *c, int64_t N, int h, int w, size_t act_budget)
@@ -430,7 +432,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         const int blocks = n_run > 0 ? n_run : c->n_blocks; // blocks to run: the first one and C -> C layers m = b - 1
         // Fused schedule (64 channels; see use_fused): [first + layer 0], (1,2), (3,4), ..; what is left over
         // runs alone.
-        const bool fused = use_fused(c, cnt, w, blocks) && conv_pair_supported(c->C, g);
+        const bool fused = use_fused(c, cnt, h, w, blocks) && conv_pair_supported(c->C, g);
         auto is_last = [&](int b) { return n_run < 0 && c->collapse && b == c->n_blocks - 1; };
         int b = 1;
         if (fused) {
@@ -472,7 +474,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                                     rsum, tb[tcur ^ 1], pm, is_last(b), buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_mid launch");
                 time_end(t, s);
-                if (is_last(b)) last_sums = LastSums{pm.slots * pm.sub, 0, 0, 0, 0, 0, 0};
+                if (is_last(b)) last_sums = LastSums{pm.slots * pm.sub, pm.sub, pm.per, tpi, 0, 0, 0, 0, 0, 0};
                 else means = conv_mid_samples(g, c->C);
             }
             cur ^= 1;

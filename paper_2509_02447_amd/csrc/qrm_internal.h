@@ -46,8 +46,8 @@ hipError_t launch_extract_tiles(const uint8_t *img, int64_t N, int H, int W, con
 // How the tiles of a launch are dealt to workgroups (see make_partition).
 struct Partition {
     int per;    // tiles per workgroup
-    int slots;  // workgroups that touch one image
-    int sub;    // records of nine sums a workgroup writes per image (last block); records per image = slots * sub
+    int slots;  // workgroups that touch one image, at most
+    int sub;    // records of nine sums a workgroup writes per image (last block); room per image: slots * sub
     int blocks; // grid size
 };
 Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks, int sub = 1);
@@ -60,13 +60,14 @@ struct MeanIn {
     int recs;         // records per image
     float inv_cnt;    // 1 / pixels of an image behind its records
 };
-// What the last block leaves of an image for the head: `records` records of nine sums per channel, or (records = 0)
-// `lines` lines of C sums.  Lines 0 .. first_col-1: the whole tile, a line per chunk of row pairs, column block and block
+// What the last block leaves of an image for the head: room for `records` records of nine sums per channel, `sub` for
+// each workgroup that touched it (workgroups take runs of `per` of the launch's strips, `strips` an image), or (records
+// = 0) `lines` lines of C sums.  Lines 0 .. first_col-1: the whole tile, a line per chunk of row pairs, column block and block
 // of 32 columns; from first_col / last_col on: the first / last column, a line per chunk; from rows on: the first, then
 // the last row, a line per column block and block of 32 columns; from corners on: top left, top right, bottom left,
 // bottom right.  seam: the last column was computed apart and is missing from the whole-tile and the row lines.
 struct LastSums {
-    int records;
+    int records, sub, per, strips;
     int lines, first_col, last_col, rows, corners, seam;
 };
 MeanIn conv_first_samples(const ConvGeom &g, int C); // (rec null)
@@ -82,7 +83,7 @@ hipError_t launch_conv_first(const TileSrc &src, const ConvGeom &g, int C, const
 // (+ 32-bit offsets inside an image); the first kZeroBytes of ws must be zero: the source of the zero padding.
 // tin / rsum: channel sums of the input and the summed weight-rounding residual [c_in][c_out] used to correct the
 // bias (tin.rec and rsum may be null).  tout: channel sums of the output (conv_mid_samples()).  last: no activations
-// are written, tout receives the nine border-aware sums per channel, part.slots * part.sub records per image.
+// are written, tout receives the nine border-aware sums per channel (LastSums::records).
 constexpr size_t kZeroBytes = 256;
 hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, const bf16_t *wfrag,
                            const float *bias, const MeanIn &tin, const float *rsum, float *tout,
