@@ -268,8 +268,9 @@ int effective_micro_batch(const qrm_ctx *c, int64_t N, int h, int w, size_t act_
 }
 
 int tiles_per_image(int h, int w) { return ((h + kRows - 1) / kRows) * ((w + kTileW - 1) / kTileW); }
-int first_blocks(const qrm_ctx *c) { return 8 * c->num_cu; }
-int mid_blocks(const qrm_ctx *c) { return c->num_cu; } // one persistent workgroup per CU
+int launch_cu(const qrm_ctx *c) { return c->num_cu - c->lent_cu; }
+int first_blocks(const qrm_ctx *c) { return 8 * launch_cu(c); }
+int mid_blocks(const qrm_ctx *c) { return launch_cu(c); } // one persistent workgroup per CU
 
 } // namespace
 
@@ -296,7 +297,7 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
             const int samples = std::max(c->pairable ? conv_pair_samples(g).recs : 0,
                                          std::max(conv_first_samples(g, c->C).recs, conv_mid_samples(g, c->C).recs));
             recs = std::max(recs, (size_t)cnt * std::max(last, (size_t)samples * c->C));
-            if (c->pairable) L.seam = std::max(L.seam, align_up(conv_pair_seam_bytes(g, c->num_cu)));
+            if (c->pairable) L.seam = std::max(L.seam, align_up(conv_pair_seam_bytes(g, launch_cu(c))));
         }
         L.stats = align_up(recs * 4);
     }
@@ -441,7 +442,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             qrm_ctx::Timed *t = time_begin(c, may_time, is_last(1) ? QRM_PROFILE_PAIR_LAST : QRM_PROFILE_PAIR_FIRST,
                                            (first_flops + block_flops) * cnt, s);
             e = launch_conv_pair(base, nullptr, &src, g, c->C, c->d_w_first, c->d_w_mid[0], c->d_bias, c->d_bias + (size_t)c->C, MeanIn{},
-                                 nullptr, tb[tcur], is_last(1), c->num_cu, seam, buf[cur], s);
+                                 nullptr, tb[tcur], is_last(1), launch_cu(c), seam, buf[cur], s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_pair (first) launch");
             time_end(t, s);
             if (is_last(1)) last_sums = conv_pair_last_sums(g);
@@ -464,7 +465,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                                                2.0 * block_flops * cnt, s);
                 e = launch_conv_pair(base, base + buf_off[cur], nullptr, g, c->C, c->d_w_mid[m], c->d_w_mid[m + 1],
                                      c->d_bias + (size_t)b * c->C, c->d_bias + (size_t)(b + 1) * c->C, means, rsum,
-                                     tb[tcur ^ 1], is_last(b + 1), c->num_cu, seam, buf[cur ^ 1], s);
+                                     tb[tcur ^ 1], is_last(b + 1), launch_cu(c), seam, buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_pair launch");
                 time_end(t, s);
                 if (is_last(b + 1)) last_sums = conv_pair_last_sums(g);
@@ -498,7 +499,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {
             e = launch_conv_final(base, buf_off[cur], g, c->C, c->nbp, c->d_w_final, c->d_bias_final, c->final_relu,
-                                  partial, c->num_cu, s);
+                                  partial, launch_cu(c), s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_final launch");
             e = launch_linear_pack(partial, L.n_part, c->nbp, cnt, c->n_bits, inv_hw,
                                    c->final_relu ? nullptr : c->d_bias_final, c->d_lin_w, c->d_lin_b, lg, bt, sy,
@@ -1058,6 +1059,26 @@ static qrm_status grow(qrm_ctx *c, void **p, size_t *have, size_t need, hipStrea
     return QRM_OK;
 }
 
+// The device's address of `bytes` bytes of host memory if a kernel may read all of them, else null: one page-locked,
+// coherent allocation that covers them (pageable, registered piecemeal, managed or device memory is copied instead).
+static const uint8_t *host_chunk_on_device(const uint8_t *p, size_t bytes)
+{
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError(); // memory the runtime does not know
+        return nullptr;
+    }
+    if (a.type != hipMemoryTypeHost || !a.devicePointer || (a.allocationFlags & hipHostMallocNonCoherent)) return nullptr;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)a.devicePointer) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    const uintptr_t lo = (uintptr_t)base, at = (uintptr_t)a.devicePointer;
+    return at >= lo && at - lo <= size && size - (at - lo) >= bytes ? (const uint8_t *)a.devicePointer : nullptr;
+}
+
 qrm_status qrm_detect_host(qrm_ctx *c, const uint8_t *const *h_chunks, int32_t n_chunks, int32_t chunk_images, int32_t H,
                            int32_t W, const int32_t *const *h_off_chunks, int32_t tile, int32_t depth, uint8_t *h_msg,
                            uint8_t *h_codeword, int8_t *h_nerr)
@@ -1076,11 +1097,31 @@ qrm_status qrm_detect_host(qrm_ctx *c, const uint8_t *const *h_chunks, int32_t n
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
 
-    const size_t img_bytes = (size_t)chunk_images * 3 * H * W, off_bytes = (size_t)chunk_images * 2 * sizeof(int32_t);
+    // Chunks whose tiles are a small part of the images come as tiles (see launch_gather_host_tiles), when every chunk
+    // lies in memory a kernel can read.
+    const size_t chunk_bytes = (size_t)chunk_images * 3 * H * W;
+    std::vector<const uint8_t *> d_chunks;
+    bool gather = gather_host_tiles_pays(H, W, tile);
+    for (int i = 0; gather && i < n_chunks; ++i) {
+        const uint8_t *p = host_chunk_on_device(h_chunks[i], chunk_bytes);
+        if (p) d_chunks.push_back(p);
+        else gather = false;
+    }
+    // The gather of a chunk runs beside the kernels of the chunk before (with one staging buffer, or one chunk, beside
+    // nothing), which then leave it its compute units: a persistent workgroup that found none free would double the
+    // time of its launch.
+    const int used = depth < n_chunks ? depth : n_chunks;
+    const bool beside = gather && used > 1 && c->num_cu >= 64;
+    const int gather_wgs = beside ? gather_host_tiles_workgroups(tile, 18.0 * c->C * c->C * (c->n_blocks - 1) * tile * tile) : 32;
+    struct Lend {
+        qrm_ctx *c;
+        ~Lend() { c->lent_cu = 0; }
+    } lend{c};
+    if (beside) c->lent_cu = gather_wgs;
+    const size_t img_bytes = gather ? (size_t)chunk_images * 3 * tile * tile : chunk_bytes, off_bytes = (size_t)chunk_images * 2 * sizeof(int32_t);
     const int k = c->rs.k, n = c->rs.n;
     const size_t msg_bytes = (size_t)chunk_images * k, cw_bytes = (size_t)chunk_images * n;
     const size_t out_bytes = msg_bytes + cw_bytes + (size_t)chunk_images;
-    const int used = depth < n_chunks ? depth : n_chunks;
     for (hipStream_t *s : {&c->s_up, &c->s_run, &c->s_down})
         if (!*s) {
             e = hipStreamCreateWithFlags(s, hipStreamNonBlocking); // default priority
@@ -1143,17 +1184,23 @@ qrm_status qrm_detect_host(qrm_ctx *c, const uint8_t *const *h_chunks, int32_t n
         e = hipSuccess;
         if (i >= used) e = hipStreamWaitEvent(c->s_up, sg.computed, 0); // the kernels of chunk i - depth have read d_img
         mark(i, 0, c->s_up);
-        if (e == hipSuccess) e = hipMemcpyAsync(sg.d_img, h_chunks[i], img_bytes, hipMemcpyHostToDevice, c->s_up);
         if (e == hipSuccess && h_off_chunks)
             e = hipMemcpyAsync(sg.d_off, h_off_chunks[i], off_bytes, hipMemcpyHostToDevice, c->s_up);
+        if (e == hipSuccess && gather)
+            e = launch_gather_host_tiles(d_chunks[i], chunk_images, H, W, h_off_chunks ? sg.d_off : nullptr, tile, sg.d_img,
+                                         i == 0 ? 32 : gather_wgs, c->s_up);
+        else if (e == hipSuccess)
+            e = hipMemcpyAsync(sg.d_img, h_chunks[i], img_bytes, hipMemcpyHostToDevice, c->s_up);
         if (e == hipSuccess) e = hipEventRecord(sg.uploaded, c->s_up);
         mark(i, 1, c->s_up);
         if (e == hipSuccess) e = hipStreamWaitEvent(c->s_run, sg.uploaded, 0);
         if (e == hipSuccess && i >= used) e = hipStreamWaitEvent(c->s_run, sg.downloaded, 0); // d_out is free again
         mark(i, 2, c->s_run);
         if (e != hipSuccess) { st = hip_fail(c, e, "upload of a chunk"); break; }
-        st = qrm_detect(c, sg.d_img, chunk_images, H, W, h_off_chunks ? sg.d_off : nullptr, tile, nullptr, nullptr, d_msg,
-                        h_codeword ? d_cw : nullptr, d_ne, c->s_run);
+        st = gather ? qrm_detect(c, sg.d_img, chunk_images, tile, tile, nullptr, tile, nullptr, nullptr, d_msg,
+                                 h_codeword ? d_cw : nullptr, d_ne, c->s_run)
+                    : qrm_detect(c, sg.d_img, chunk_images, H, W, h_off_chunks ? sg.d_off : nullptr, tile, nullptr, nullptr, d_msg,
+                                 h_codeword ? d_cw : nullptr, d_ne, c->s_run);
         if (st != QRM_OK) break;
         e = hipEventRecord(sg.computed, c->s_run);
         if (e != hipSuccess) { st = hip_fail(c, e, "hipEventRecord"); break; }

@@ -22,6 +22,7 @@ struct QrmSlot {
 struct qrm_ctx {
     int device = 0;
     int num_cu = 256;
+    int lent_cu = 0; // compute units qrm_detect_host's gather has, while that call runs
     bool has_ext = false, has_rs = false;
     // extractor
     int n_blocks = 0, C = 0, n_bits = 0, nbp = 0, final_relu = 0, final_affine = 0;

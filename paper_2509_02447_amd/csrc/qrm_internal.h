@@ -43,6 +43,14 @@ struct TileSrc {
 hipError_t launch_extract_tiles(const uint8_t *img, int64_t N, int H, int W, const int32_t *off, int tile,
                                 uint8_t *out, hipStream_t s);
 
+// The same crops out of images in page-locked host memory the device can read (img: its device address), and whether
+// that beats copying the images.  workgroups: compute units it takes; gather_host_tiles_workgroups(): how many of them
+// when tiles that take `flops` of work each are being worked on at the same time.
+bool gather_host_tiles_pays(int H, int W, int tile);
+int gather_host_tiles_workgroups(int tile, double flops);
+hipError_t launch_gather_host_tiles(const uint8_t *img, int64_t N, int H, int W, const int32_t *off, int tile, uint8_t *out,
+                                    int workgroups, hipStream_t s);
+
 // How the tiles of a launch are dealt to workgroups (see make_partition).
 struct Partition {
     int per;    // tiles per workgroup

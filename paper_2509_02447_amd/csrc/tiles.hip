@@ -52,6 +52,55 @@ __global__ __launch_bounds__(256) void extract_tiles_kernel(const uint8_t *__res
     }
 }
 
+// Tile crops out of images in page-locked HOST memory, read over the link by the kernel itself: a tile's rows are all
+// that crosses it, not the image (1/16 of it for 64 x 64 tiles of 256 x 256 images).  What bounds it: the link, which
+// carries whole lines, a row of 64 bytes touching up to two of them: 1024 such tiles take 0.63 ms, the copy of
+// the images 3.52 ms (57 GB/s).  It runs beside the convolutions of the chunk before, whose workgroups fill a compute
+// unit each, so it is a few large workgroups (kGatherLds of LDS: one to a compute unit) on compute units those
+// leave free, a dword per lane, every lane of the workgroup with a request on its way: 8 workgroups take 0.59 / 0.93 / 2.5
+// ms for 1024 tiles of 32 / 64 / 128, 16 of them 0.32 / 0.65 / 1.78, 256 no less than that.
+constexpr int kGatherThreads = 1024;
+constexpr int kGatherLds = 84 * 1024; // more than half of a compute unit's
+template <bool WORDS>
+__global__ __launch_bounds__(kGatherThreads) void gather_host_tiles_kernel(const uint8_t *__restrict__ img, int planes, int H, int W,
+                                                                const int32_t *__restrict__ off, int tile,
+                                                                uint8_t *__restrict__ out)
+{
+    typedef const uint32_t __attribute__((address_space(1))) *host_word_t;
+    const uint32_t wpr = WORDS ? tile >> 2 : tile; // dwords / bytes per output row
+    const uint32_t row0 = threadIdx.x / wpr, col0 = threadIdx.x - row0 * wpr;
+    const uint32_t drow = kGatherThreads / wpr, dcol = kGatherThreads - drow * wpr; // what that many more dwords are
+    for (int p = blockIdx.x; p < planes; p += gridDim.x) {
+        int oy = 0, ox = 0;
+        if (off) {
+            oy = clampi(off[2 * (p / 3)], 0, H - tile);
+            ox = clampi(off[2 * (p / 3) + 1], 0, W - tile);
+        }
+        // the tile's first byte as an aligned dword (the same for the whole workgroup) + byte offset
+        const uintptr_t first = (uintptr_t)(img + p * (int64_t)H * W + (int64_t)oy * W + ox);
+        const uintptr_t base = first & ~(uintptr_t)3;
+        const uint32_t skew = (uint32_t)first & 3u;
+        uint8_t *dst = out + p * (int64_t)tile * tile;
+        uint32_t row = row0, col = col0;
+        for (uint32_t idx = threadIdx.x; idx < wpr * tile; idx += kGatherThreads) {
+            const uint32_t o = row * W + (WORDS ? col * 4 : col) + skew;
+            const uint32_t lo = *(host_word_t)(base + (o & ~3u));
+            if (WORDS) { // the second dword is another one only where the first does not hold all four bytes
+                const uint32_t hi = *(host_word_t)(base + ((o + 3) & ~3u));
+                *(uint32_t *)(dst + idx * 4) = __builtin_amdgcn_alignbyte(hi, lo, o & 3u);
+            } else {
+                dst[idx] = (uint8_t)(lo >> (8 * (o & 3u)));
+            }
+            col += dcol;
+            row += drow;
+            if (col >= wpr) {
+                col -= wpr;
+                ++row;
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 // Variance-based tile selection (Listing 1 of the paper, `select_patch`): windows of win x win pixels at
 // a stride that divides win; score of a window = sum over channels of w_c * (n S2_c - S1_c^2), i.e. the
@@ -416,6 +465,35 @@ hipError_t launch_select_tiles_variance(const uint8_t *img, int64_t N, int H, in
         else
             hipLaunchKernelGGL(tile_variance_kernel<1>, dim3((unsigned)cnt), dim3(256), 0, s, img0, a, off_yx + 2 * n0, sc0);
     }
+    return hipGetLastError();
+}
+
+bool gather_host_tiles_pays(int H, int W, int tile)
+{
+    // bytes a tile's rows touch on average, in pieces of 64, against the image's: 64 x 64 tiles of 256 x 256 images 0.12 (0.63 ms
+    // for 1024 against 3.52 for the copy), 128: 0.37 (1.75), 192: 0.75 (2.66), 256: 1.2 (3.50).  The copy needs no compute units:
+    // the gather has to halve the bytes.
+    return 2 * (int64_t)tile * (tile + 63) <= (int64_t)H * W;
+}
+
+int gather_host_tiles_workgroups(int tile, double flops)
+{
+    // 8 or 16 (figures above): 8 where the tile's own work on the rest of the chip takes longer than they do
+    return flops / 1.2e15 > 3.0 * tile * 5.5e-9 ? 8 : 16;
+}
+
+hipError_t launch_gather_host_tiles(const uint8_t *img, int64_t N, int H, int W, const int32_t *off, int tile, uint8_t *out,
+                                    int workgroups, hipStream_t s)
+{
+    if (N <= 0) return hipSuccess;
+    if (N > (1 << 29)) return hipErrorInvalidValue;
+    const int planes = (int)N * 3;
+    const dim3 grid((unsigned)std::min(planes, workgroups));
+    // (dwords: the output is dword aligned; an aligned dword that holds a byte of the images never leaves its page)
+    if (tile % 4 == 0 && ((uintptr_t)out & 3u) == 0)
+        hipLaunchKernelGGL(gather_host_tiles_kernel<true>, grid, dim3(kGatherThreads), kGatherLds, s, img, planes, H, W, off, tile, out);
+    else
+        hipLaunchKernelGGL(gather_host_tiles_kernel<false>, grid, dim3(kGatherThreads), kGatherLds, s, img, planes, H, W, off, tile, out);
     return hipGetLastError();
 }
 

@@ -822,6 +822,41 @@ def test_detect_host_chunked_pipeline_equals_resident_detect(qrm):
     ctx.close()
 
 
+@pytest.mark.parametrize("H,W,tile", [(256, 256, 64), (100, 117, 30), (91, 75, 23), (128, 100, 32), (64, 64, 40)])
+def test_detect_host_tiles_read_from_host_memory(qrm, H, W, tile):
+    """Chunks whose tiles are read out of page-locked memory by a kernel (whole dwords or bytes, rows at every alignment,
+    a chunk that begins inside an allocation, origins beyond the border), chunks in pageable memory and tiles large
+    enough to copy the images instead: all as qrm_detect on the same images in device memory."""
+    chunk, n_chunks = 5, 4
+    wts = small_weights(32, 2, 60, tile)
+    rng = np.random.default_rng(tile)
+    n = chunk * n_chunks
+    imgs = synth.field_images(synth.CONFIGS["C1"], tile, n)[:, :, :H, :W].copy()
+    imgs[::2] = rng.integers(0, 256, size=imgs[::2].shape, dtype=np.uint8)
+    off = rng.integers(-9, max(H, W) + 9, size=(n, 2), dtype=np.int32)
+    ctx = qrm.Context(weights=wts, rs=dict(m=4, prim_poly=0x13, n=15, k=11, fcr=1))
+    step = chunk * 3 * H * W
+    pinned = torch.empty((n_chunks * step + 1,), dtype=torch.uint8, pin_memory=True)[1:]     # chunks at odd addresses
+    pinned.copy_(torch.from_numpy(imgs.reshape(-1)))
+    pageable = torch.from_numpy(imgs.reshape(-1))
+    offs = torch.empty((n, 2), dtype=torch.int32, pin_memory=True).copy_(torch.from_numpy(off))
+    for with_off in (True, False):
+        msg, cw, ne = empty((n, 11), torch.uint8), empty((n, 15), torch.uint8), empty((n,), torch.int8)
+        ctx.qrm_detect(dev(imgs), n, H, W, dev(off) if with_off else None, tile, None, None, msg, cw, ne)
+        torch.cuda.synchronize()
+        for src in (pinned, pageable):
+            for depth in (1, 2, 3):
+                h_msg = torch.zeros((n, 11), dtype=torch.uint8, pin_memory=True)
+                h_cw = torch.zeros((n, 15), dtype=torch.uint8, pin_memory=True)
+                h_ne = torch.zeros((n,), dtype=torch.int8, pin_memory=True)
+                ctx.qrm_detect_host([src[i * step:(i + 1) * step] for i in range(n_chunks)], chunk, H, W,
+                                    [offs[i * chunk:(i + 1) * chunk] for i in range(n_chunks)] if with_off else None, tile,
+                                    depth, h_msg, h_cw, h_ne)
+                assert np.array_equal(h_msg.numpy(), msg.cpu().numpy()) and np.array_equal(h_cw.numpy(), cw.cpu().numpy())
+                assert np.array_equal(h_ne.numpy(), ne.cpu().numpy())
+    ctx.close()
+
+
 @pytest.mark.timeout(900)
 def test_detect_host_full_streamed_configuration(qrm):
     """The streamed configuration at its real size: 128 chunks of 8192 images (1 048 576 images, 206 GB over the
