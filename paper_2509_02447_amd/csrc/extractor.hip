@@ -25,7 +25,7 @@
 //  * The last block writes no activations when the final convolution has no ReLU: final conv + global
 //    average pool are linear, so nine border-aware channel sums per image are all head_kernel needs to
 //    apply the final convolution (fp32 weights), the linear layer, the threshold and the symbol packing.
-//    With a final ReLU, conv_final_kernel sums the final convolution's output in its accumulators.
+//    With a final ReLU, conv_mid_kernel<C, MODE_FINAL> sums the final convolution's output over the pixels.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -139,7 +139,6 @@ struct MidCfg {
     static constexpr int ROW_SLOTS = kHaloW * SPP;    // slots of one staged row (halo columns included)
     static constexpr int PIECES = (ROW_SLOTS + 63) / 64; // wavefront-wide direct-to-LDS loads per row
     static constexpr int ROWB = PIECES * 1024;        // LDS bytes per staged row
-    static constexpr int LDS_BYTES = (kRows + 2) * ROWB;
     static constexpr int QPW = (PIECES + 3) / 4;      // pieces of a row one wavefront is responsible for
 };
 
@@ -235,12 +234,10 @@ __device__ __forceinline__ void frag_wait(bf16x8 &frag)
 // their waits are written as assembly: the compiler, not knowing which direct-to-LDS load fills which
 // bytes, would otherwise drain the whole vector-memory queue (stores included) before the first read.
 // `rowp` holds the LDS byte address of each staged row for this lane.
-// POOL: all rows are summed into acc[0] / acc[1] (global average pool of the last layer); rows at or
-// beyond `rows_valid` are skipped (RAGGED: the last strip of a tile whose height is not a multiple of kRows).
-// INIT: the accumulators are not read; the first matrix instruction of every output row starts from zero.
-template <int C, int RW, bool POOL, bool RAGGED = false, bool INIT = false>
+// The accumulators are not read; the first matrix instruction of every output row starts from zero.
+template <int C, int RW>
 __device__ __forceinline__ void strip_mma(const lrow_t (&rowp)[RW + 2], const bf16x8 (&Wr)[9][C / 16],
-                                          f32x16 *acc, int rows_valid)
+                                          f32x16 (&acc)[RW])
 {
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     bool started[RW] = {};
@@ -272,9 +269,7 @@ __device__ __forceinline__ void strip_mma(const lrow_t (&rowp)[RW + 2], const bf
         for (int dy = 0; dy < 3; ++dy) {
             const int orow = r - dy;
             if (orow >= 0 && orow < RW) {
-                if (POOL) {
-                    if (!RAGGED || orow < rows_valid) acc[orow & 1] = mfma32(Wr[dy * 3 + dx][kc], fr, acc[orow & 1]);
-                } else if (INIT && !started[orow]) {
+                if (!started[orow]) {
                     acc[orow] = mfma32(Wr[dy * 3 + dx][kc], fr, zero);
                     started[orow] = true;
                 } else {
@@ -496,20 +491,23 @@ __device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const 
 struct StatArgs {
     MeanIn tin;         // channel sums of the input (rec null: no correction)
     const float *rsum;  // [c_in][c_out] residual-weight sums of this layer (fp32)
-    float *tout;        // records written by this launch: MODE_MID [n_img][out_recs][C], MODE_LAST [n_img][out_recs][9 C]
+    float *tout;        // records written by this launch: MODE_MID [n_img][out_recs][C], MODE_LAST [n_img][out_recs][9 C],
+                        // MODE_FINAL [n_img][out_recs][C * slices]
     int out_recs;       // records per image
     int per;            // strips per workgroup
+    float low;          // MODE_FINAL: lower bound of an output (0: ReLU, -inf: none)
 };
 
 constexpr int MODE_MID = 0;  // write activations, sample channel sums from every eighth strip
 constexpr int MODE_LAST = 1; // last block: no activations, the nine border-aware channel sums
+constexpr int MODE_FINAL = 2; // final convolution (C output channels per grid.y slice), summed over the pixels: no activations
 
 constexpr int kMidWaves = 8; // wavefronts of a conv_mid workgroup: two groups of four
 
 template <int C, int MODE>
 struct MidRing {
     static constexpr int NSLOT = MODE == MODE_LAST ? 14 : 15; // row slots of the LDS ring (>= 12)
-    static constexpr int NSUB = kMidWaves / MidCfg<C>::NCB;   // MODE_LAST: records a workgroup writes per image
+    static constexpr int NSUB = kMidWaves / MidCfg<C>::NCB;   // MODE_LAST, MODE_FINAL: records a workgroup writes per image
 };
 
 // C -> C (+bias, ReLU), bf16 NHWC in / out.  One persistent workgroup of eight wavefronts per CU, two
@@ -556,7 +554,8 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
     const int rg = w4 / (K::NCB * 2);
 
     bf16x8 Wr[9][K::KC];
-    load_weight_frags<C>(Wr, wfrag, cb, lane);
+    const int slice = MODE == MODE_FINAL ? blockIdx.y : 0; // C output channels of the launch
+    load_weight_frags<C>(Wr, wfrag, slice * K::NCB + cb, lane);
 
     const int tpi = g.strips * g.colblks; // tiles per image
     const int total = g.n_img * tpi;
@@ -619,10 +618,19 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 #pragma unroll
             for (int sh = OPW; sh < 64; sh <<= 1) d += __shfl_xor(d, sh);
         }
-        if (part == 0) s_init[n & 3][o] = bias[o] + d;
+        if (part == 0) s_init[n & 3][o] = (MODE != MODE_FINAL || bias ? bias[slice * C + o] : 0.f) + d;
     };
-    // MODE_LAST: this wavefront's statistics of image n -> its record; accumulators cleared
+    // MODE_LAST, MODE_FINAL: this wavefront's sums of image n -> its record; accumulators cleared
+    float run_sum = 0.f; // MODE_FINAL: one channel per lane (reduce16_over_half)
     auto flush = [&](int n) {
+        if (MODE == MODE_FINAL) {
+            const int lane = pin_in_loop(tid & 63);
+            const int px = lane & 31, half = lane >> 5;
+            const int slot = vb - (n * tpi) / st.per;
+            float *rec = st.tout + (((int64_t)n * st.out_recs + slot * R::NSUB + wave / K::NCB) * gridDim.y + slice) * C;
+            if ((px & 1) == 0) rec[cb * 32 + half * 16 + reduce16_index(px)] = run_sum;
+            run_sum = 0.f;
+        }
         if (MODE == MODE_LAST && st.tout) {
             const int lane = pin_in_loop(tid & 63);
             const int slot = vb - (n * tpi) / st.per; // which of the workgroups that touch the image this is
@@ -674,7 +682,23 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                 }
             }
         }
-        if (st.tout) {
+        if (MODE == MODE_FINAL) {
+            const bool colok = x < g.w;
+            float t[16];
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4 b = *(const f32x4 *)(si + 4 * q4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float v = 0.f;
+#pragma unroll
+                    for (int r = 0; r < RW; ++r)
+                        if (yw + r < g.h) v += fmaxf(acc[r][4 * q4 + e] + b[e], st.low); // (the same for the whole wavefront)
+                    t[4 * q4 + e] = colok ? v : 0.f;
+                }
+            }
+            run_sum += reduce16_over_half(t, px);
+        } else if (st.tout) {
             if (MODE == MODE_LAST) {
                 strip_statistics<RW, true>(acc, si, &s_stat[wave][0][half * 16], x, yw, g.h, g.w, px);
             } else if ((strip & 7) == sample_phase) { // records of a sampled strip: column block, row group, pixel block
@@ -709,7 +733,7 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 #pragma unroll
                 for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((start + r) % NSLOT) * K::ROWB;
                 __builtin_amdgcn_s_setprio(3); // the matrix stream goes first whenever both wavefronts of a SIMD are ready
-                strip_mma<C, RW, false, false, true>(rowp, Wr, acc, RW);
+                strip_mma<C, RW>(rowp, Wr, acc);
                 __builtin_amdgcn_s_setprio(0);
             }
         } else {
@@ -1305,7 +1329,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                     lrow_t rowp[RW + 2];
 #pragma unroll
                     for (int r = 0; r < RW + 2; ++r) rowp[r] = in_base + (uint32_t)slot_of(2 * sg - 1 + r) * ROWB;
-                    strip_mma<C, RW, false, false, true>(rowp, Wr, acc, RW);
+                    strip_mma<C, RW>(rowp, Wr, acc);
                     input_loads(sg);
                 }
                 // epilogue: + bias and correction, ReLU, bf16 -> intermediate ring (zeros outside the tile)
@@ -1374,7 +1398,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                 lrow_t rowp[RW + 2];
 #pragma unroll
                 for (int r = 0; r < RW + 2; ++r) rowp[r] = mid_base + (uint32_t)slot_of(2 * (sg - 2) - 1 + r) * ROWB;
-                strip_mma<C, RW, false, false, true>(rowp, Wr, acc, RW);
+                strip_mma<C, RW>(rowp, Wr, acc);
                 if (FIRST) { // group A finishes these rows in the next step
                     float *dst = &s_accx[((((sg - 2) & 1) * 4 + w4) * 8) * 256 + ln * 4];
 #pragma unroll
@@ -1476,99 +1500,6 @@ __global__ __launch_bounds__(128) void conv_seam_kernel(const uint8_t *__restric
         if (px == kSumLane) put(lines + (sums.last_col + t) * C, tot);
         if (r == 0) put(lines + (sums.corners + 1) * C, col);
         if (r == g.h - 1) put(lines + (sums.corners + 3) * C, col);
-    }
-}
-
-// Final conv C -> 64 output channels per grid.y slice, summed over the pixels of one (image, column
-// block).  partial[n][colblk*2 + xb][slice*64 + cb*32 + half*16 + v]
-template <int C, bool RELU>
-__global__ __launch_bounds__(256, 2) void conv_final_kernel(const uint8_t *__restrict__ ws, size_t in_off,
-                                                            ConvGeom g, int nbp,
-                                                            const bf16_t *__restrict__ wfrag,
-                                                            const float *__restrict__ bias,
-                                                            float *__restrict__ partial)
-{
-    typedef MidCfg<C> K;
-    constexpr int RW = kRows;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[K::LDS_BYTES];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int px = lane & 31, half = lane >> 5;
-    const int cb = wave & 1, xb = wave >> 1;
-    const int slice = blockIdx.y;
-    const int cout0 = slice * 64 + cb * 32; // first output channel of this wavefront
-
-    bf16x8 Wr[9][K::KC];
-    load_weight_frags<C>(Wr, wfrag, cout0 / 32, lane);
-    float bias16[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) bias16[v] = (RELU && bias) ? bias[cout0 + half * 16 + v] : 0.f;
-
-    const int total = g.n_img * g.colblks;
-    const int nb = gridDim.x;
-    const int vb = xcd_virtual_block(blockIdx.x, nb);
-    const int per = (total + nb - 1) / nb;
-    const int t_begin = vb * per;
-    const int t_end = min(total, t_begin + per);
-    lrow_t rowp[RW + 2];
-#pragma unroll
-    for (int r = 0; r < RW + 2; ++r) rowp[r] = lds_address(lds) + r * K::ROWB + (xb * 32 + px) * K::PS + half * 16;
-    const size_t img_bytes = (size_t)g.h * g.w * C * 2;
-
-    for (int t = t_begin; t < t_end; ++t) {
-        const int colblk = t % g.colblks;
-        const int n = t / g.colblks;
-        const int x0 = colblk * kTileW;
-        const int x = x0 + xb * 32 + px;
-
-        f32x16 sum[2];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { sum[0][v] = 0.f; sum[1][v] = 0.f; }
-
-        __syncthreads();
-        issue_strip_loads<C>(lds, ws, ws + in_off + (size_t)n * img_bytes, g.h, g.w, 0, x0, wave, lane);
-        for (int strip = 0; strip < g.strips; ++strip) {
-            const int y0 = strip * kRows;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            if (!RELU) {
-                if (g.h - y0 >= RW) strip_mma<C, RW, true, false>(rowp, Wr, sum, RW);
-                else strip_mma<C, RW, true, true>(rowp, Wr, sum, g.h - y0);
-                __syncthreads();
-                if (strip + 1 < g.strips)
-                    issue_strip_loads<C>(lds, ws, ws + in_off + (size_t)n * img_bytes, g.h, g.w, y0 + kRows, x0, wave, lane);
-            } else {
-                f32x16 acc[RW];
-#pragma unroll
-                for (int r = 0; r < RW; ++r)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[r][v] = bias16[v];
-                strip_mma<C, RW, false>(rowp, Wr, acc, RW);
-                __syncthreads();
-                if (strip + 1 < g.strips)
-                    issue_strip_loads<C>(lds, ws, ws + in_off + (size_t)n * img_bytes, g.h, g.w, y0 + kRows, x0, wave, lane);
-#pragma unroll
-                for (int r = 0; r < RW; ++r)
-                    if (y0 + r < g.h)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) sum[0][v] += fmaxf(acc[r][v], 0.f);
-            }
-        }
-
-        // mask columns beyond the tile, reduce over the 32 pixel lanes of each half
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            float s = (x < g.w) ? (sum[0][v] + sum[1][v]) : 0.f;
-#pragma unroll
-            for (int off = 16; off >= 1; off >>= 1) s += __shfl_xor(s, off, 32);
-            sum[0][v] = s;
-        }
-        if (px == 0) {
-            float *dst = partial + ((int64_t)n * (g.colblks * 2) + colblk * 2 + xb) * nbp + cout0 + half * 16;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) dst[v] = sum[0][v];
-        }
     }
 }
 
@@ -1740,6 +1671,13 @@ __device__ __forceinline__ f32x4 sum_lines(const f32x4 *p, int stride, int start
     return sum;
 }
 
+// Records of image n: those of the workgroups that touched it.
+__device__ __forceinline__ int sums_of_image(const LastSums &sums, int64_t n)
+{
+    const int first = (int)(n * sums.strips) / sums.per, last = (int)(n * sums.strips + sums.strips - 1) / sums.per;
+    return (last - first + 1) * sums.sub;
+}
+
 constexpr int kHeadIpb = 1;   // images per block (a launch of a few hundred images should reach every compute unit)
 constexpr int kHeadKParts = 8; // the k = (channel, tap) range is cut in eight, one part per 64 threads
 constexpr int kHeadThreads = 64 * kHeadKParts;
@@ -1769,9 +1707,7 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
             const int grp = tid / lpr, l = tid - grp * lpr;
             if (grp < groups) {
                 f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-                const int first = (int)((n0 + i) * sums.strips) / sums.per, last = (int)((n0 + i) * sums.strips + sums.strips - 1) / sums.per;
-                const int count = (last - first + 1) * sums.sub; // of the workgroups that touched the image
-                if (have) sum = sum_lines((const f32x4 *)recs + (n0 + i) * sums.records * lpr + l, lpr, grp, groups, count);
+                if (have) sum = sum_lines((const f32x4 *)recs + (n0 + i) * sums.records * lpr + l, lpr, grp, groups, sums_of_image(sums, n0 + i));
                 *(f32x4 *)&Qp[(grp * lpr + l) * 4] = sum;
             }
             __syncthreads();
@@ -1888,22 +1824,28 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
 }
 
 // ------------------------------------------------------------------------------------------------
-// pooled -> linear -> logits -> bits -> symbols.  One block of 128 threads per image.
+// pooled -> linear -> logits -> bits -> symbols.  One block per image; its threads share the records of the image
+// (16 bytes each, four loads in flight), which a launch of few images has hundreds of.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(128) void linear_pack_kernel(const float *__restrict__ partial, int n_part, int nbp,
-                                                          int n_bits, float inv_hw, const float *__restrict__ fbias,
-                                                          const float *__restrict__ lin_w,
-                                                          const float *__restrict__ lin_b, float *__restrict__ logits,
-                                                          uint8_t *__restrict__ bits, uint8_t *__restrict__ symbols,
-                                                          int m)
+__global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *__restrict__ partial, LastSums sums, int nbp,
+                                                                   int n_bits, float inv_hw, const float *__restrict__ fbias,
+                                                                   const float *__restrict__ lin_w,
+                                                                   const float *__restrict__ lin_b, float *__restrict__ logits,
+                                                                   uint8_t *__restrict__ bits, uint8_t *__restrict__ symbols,
+                                                                   int m)
 {
+    __shared__ __attribute__((aligned(16))) float part[kHeadThreads * 4];
     __shared__ float pooled[128];
     __shared__ uint8_t sbit[128];
     const int64_t n = blockIdx.x;
-    const int o = threadIdx.x;
+    const int tid = threadIdx.x, o = tid;
+    const int lpr = nbp / 4, groups = kHeadThreads / lpr; // lanes per record
+    *(f32x4 *)&part[tid * 4] = sum_lines((const f32x4 *)partial + n * sums.records * lpr + tid % lpr, lpr, tid / lpr, groups,
+                                         sums_of_image(sums, n));
+    __syncthreads();
     if (o < n_bits) {
         float s = 0.f;
-        for (int p = 0; p < n_part; ++p) s += partial[(n * n_part + p) * nbp + o];
+        for (int g2 = 0; g2 < groups; ++g2) s += part[g2 * nbp + o];
         pooled[o] = s * inv_hw + (fbias ? fbias[o] : 0.f);
     }
     __syncthreads();
@@ -1933,14 +1875,6 @@ __global__ __launch_bounds__(256) void nhwc_to_nchw_kernel(const bf16_t *__restr
         const int pix = (int)(p % hw);
         out[(n * C + c) * hw + pix] = (float)in[i];
     }
-}
-
-int persistent_blocks(int num_cu, int per_cu, int64_t work)
-{
-    int64_t b = (int64_t)num_cu * per_cu;
-    if (b > work) b = work;
-    if (b < 1) b = 1;
-    return (int)b;
 }
 
 } // namespace
@@ -1985,7 +1919,7 @@ hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, 
                            const float *bias, const MeanIn &tin, const float *rsum, float *tout,
                            const Partition &part, bool last, bf16_t *out, hipStream_t s)
 {
-    StatArgs st{tin, rsum, tout, last ? part.slots * part.sub : conv_mid_samples(g, C).recs, part.per};
+    StatArgs st{tin, rsum, tout, last ? part.slots * part.sub : conv_mid_samples(g, C).recs, part.per, 0.f};
     const dim3 grid(part.blocks), block(64 * kMidWaves);
     if (C == 64) {
         if (last) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_LAST>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, out);
@@ -2104,30 +2038,27 @@ size_t last_record_floats(int C) { return (size_t)stat_rec(C); }
 
 int conv_mid_records_per_workgroup(int C) { return kMidWaves / (C / 32); }
 
-hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp,
-                             const bf16_t *wfrag, const float *bias, int relu, float *partial, int num_cu,
-                             hipStream_t s)
+Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int C, int nbp)
 {
-    const int64_t units = (int64_t)g.n_img * g.colblks;
-    const int slices = nbp / 64;
-    int blocks = persistent_blocks(num_cu, 2, units);
-    dim3 grid(blocks, slices);
-    if (C == 64) {
-        if (relu) hipLaunchKernelGGL((conv_final_kernel<64, true>), grid, dim3(256), 0, s, ws, in_off, g, nbp, wfrag, bias, partial);
-        else hipLaunchKernelGGL((conv_final_kernel<64, false>), grid, dim3(256), 0, s, ws, in_off, g, nbp, wfrag, bias, partial);
-    } else {
-        if (relu) hipLaunchKernelGGL((conv_final_kernel<32, true>), grid, dim3(256), 0, s, ws, in_off, g, nbp, wfrag, bias, partial);
-        else hipLaunchKernelGGL((conv_final_kernel<32, false>), grid, dim3(256), 0, s, ws, in_off, g, nbp, wfrag, bias, partial);
-    }
+    return make_partition(n_img, tiles_per_image, std::max(1, num_cu / (nbp / C)), conv_mid_records_per_workgroup(C));
+}
+
+hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
+                             const float *bias, int relu, float *partial, const Partition &part, hipStream_t s)
+{
+    StatArgs st{MeanIn{}, nullptr, partial, part.slots * part.sub, part.per, relu ? 0.f : -__builtin_inff()};
+    const dim3 grid(part.blocks, nbp / C), block(64 * kMidWaves);
+    if (C == 64) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
+    else hipLaunchKernelGGL((conv_mid_kernel<32, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
     return hipGetLastError();
 }
 
-hipError_t launch_linear_pack(const float *partial, int n_part, int nbp, int64_t n_img, int n_bits, float inv_hw,
+hipError_t launch_linear_pack(const float *partial, const LastSums &sums, int nbp, int64_t n_img, int n_bits, float inv_hw,
                               const float *fbias, const float *lin_w, const float *lin_b, float *logits,
                               uint8_t *bits, uint8_t *symbols, int m, hipStream_t s)
 {
     if (n_img <= 0) return hipSuccess;
-    hipLaunchKernelGGL(linear_pack_kernel, dim3((unsigned)n_img), dim3(128), 0, s, partial, n_part, nbp, n_bits, inv_hw,
+    hipLaunchKernelGGL(linear_pack_kernel, dim3((unsigned)n_img), dim3(kHeadThreads), 0, s, partial, sums, nbp, n_bits, inv_hw,
                        fbias, lin_w, lin_b, logits, bits, symbols, m);
     return hipGetLastError();
 }

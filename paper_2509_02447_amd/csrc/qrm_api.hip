@@ -281,9 +281,7 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
     WsLayout L{};
     if (c->has_ext) {
         L.mb = effective_micro_batch(c, N, h, w, act_budget);
-        L.n_part = ((w + kTileW - 1) / kTileW) * 2;
         L.act = align_up((size_t)L.mb * h * w * c->C * 2);
-        L.partial = align_up((size_t)L.mb * L.n_part * c->nbp * 4);
         // statistics records: sized for the fullest micro-batch and for the ragged last one
         const int tpi = tiles_per_image(h, w);
         size_t recs = 0; // floats
@@ -292,8 +290,12 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
             if (cnt <= 0) continue;
             const Partition pm = make_partition(cnt, tpi, mid_blocks(c), conv_mid_records_per_workgroup(c->C));
             const ConvGeom g{(int)cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
+            if (!c->collapse) {
+                const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
+                L.partial = std::max(L.partial, align_up((size_t)cnt * pl.slots * pl.sub * c->nbp * 4));
+            }
             // floats per image: what the last block leaves for the head, or sampled channel sums of any other
-            const size_t last = std::max(c->pairable ? (size_t)conv_pair_last_sums(g).lines * c->C : 0, pm.slots * pm.sub * last_record_floats(c->C));
+            const size_t last = !c->collapse ? 0 : std::max(c->pairable ? (size_t)conv_pair_last_sums(g).lines * c->C : 0, pm.slots * pm.sub * last_record_floats(c->C));
             const int samples = std::max(c->pairable ? conv_pair_samples(g).recs : 0,
                                          std::max(conv_first_samples(g, c->C).recs, conv_mid_samples(g, c->C).recs));
             recs = std::max(recs, (size_t)cnt * std::max(last, (size_t)samples * c->C));
@@ -498,10 +500,11 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                             c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {
-            e = launch_conv_final(base, buf_off[cur], g, c->C, c->nbp, c->d_w_final, c->d_bias_final, c->final_relu,
-                                  partial, launch_cu(c), s);
+            const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
+            e = launch_conv_final(base, buf_off[cur], g, c->C, c->nbp, c->d_w_final, c->final_relu ? c->d_bias_final : nullptr,
+                                  c->final_relu, partial, pl, s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_final launch");
-            e = launch_linear_pack(partial, L.n_part, c->nbp, cnt, c->n_bits, inv_hw,
+            e = launch_linear_pack(partial, LastSums{pl.slots * pl.sub, pl.sub, pl.per, tpi, 0, 0, 0, 0, 0, 0}, c->nbp, cnt, c->n_bits, inv_hw,
                                    c->final_relu ? nullptr : c->d_bias_final, c->d_lin_w, c->d_lin_b, lg, bt, sy,
                                    m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "linear_pack launch");

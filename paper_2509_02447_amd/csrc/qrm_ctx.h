@@ -87,7 +87,7 @@ qrm_status hip_fail(qrm_ctx *c, hipError_t e, const char *what);
 // columns a fused launch on wide tiles hands from one column block to the next, symbols).
 struct WsLayout {
     size_t act, partial, stats, seam, symbols, total;
-    int mb, n_part;
+    int mb;
 };
 // act_budget: bytes one activation buffer may take (0: the context's micro-batch setting decides)
 WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols, size_t act_budget = 0);

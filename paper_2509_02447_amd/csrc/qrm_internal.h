@@ -20,7 +20,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kRows = 4;     // output rows per strip of the conv kernels
 constexpr int kTileW = 64;   // output columns per strip
 constexpr int kHaloW = kTileW + 2;
-constexpr int kMaxPart = 64; // upper bound on pooled partial sums per image handled by the linear kernel
 
 // Geometry of one extractor pass over a micro-batch.
 struct ConvGeom {
@@ -119,15 +118,15 @@ hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n
                        const float *wft, const float *fbias, const float *lin_w, const float *lin_b, float *logits,
                        uint8_t *bits, uint8_t *symbols, int m, hipStream_t s);
 
-// final conv3x3 C -> nbp (n_bits padded to 32s) (+bias, optional ReLU) + sum over pixels -> partial sums
-// partial: f32 [n_img][colblks*2][nbp]
-hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp,
-                             const bf16_t *wfrag, const float *bias, int relu, float *partial, int num_cu,
-                             hipStream_t s);
+// final conv3x3 C -> nbp (n_bits padded to 64s) (+bias, optional ReLU) + sum over pixels -> partial sums
+// partial: f32 [n_img][part.slots * part.sub][nbp]; part: conv_final_partition()
+Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int C, int nbp);
+hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
+                             const float *bias, int relu, float *partial, const Partition &part, hipStream_t s);
 
 // pooled = sum(partials)/(h*w); logits = lin_w * pooled + lin_b; bits; symbols (MSB first, m bits each)
 // fbias: optional bias of the final convolution, added to the pooled value
-hipError_t launch_linear_pack(const float *partial, int n_part, int nbp, int64_t n_img, int n_bits, float inv_hw,
+hipError_t launch_linear_pack(const float *partial, const LastSums &sums, int nbp, int64_t n_img, int n_bits, float inv_hw,
                               const float *fbias, const float *lin_w, const float *lin_b, float *logits, uint8_t *bits,
                               uint8_t *symbols, int m, hipStream_t s);
 

@@ -474,6 +474,30 @@ def test_extractor_final_relu_and_affine(qrm):
         ctx.close()
 
 
+@pytest.mark.parametrize("C,nb,nbits,h,w,relu", [(64, 3, 16, 5, 64, 1), (64, 2, 64, 13, 70, 1), (64, 3, 65, 20, 128, 1),
+                                                 (32, 2, 33, 17, 30, 1), (32, 3, 128, 9, 65, 1), (64, 1, 30, 12, 40, 0),
+                                                 (32, 1, 70, 8, 66, 1)])
+def test_extractor_final_convolution_over_all_pixels(qrm, C, nb, nbits, h, w, relu):
+    """The final convolution evaluated pixel by pixel (with a ReLU behind it, or a single block before it): one and two
+    groups of output channels, ragged rows and columns, a tile alone, a few, and more strips than compute units."""
+    wts = small_weights(C, nb, nbits, C + nb + nbits)
+    rng = np.random.default_rng(nbits)
+    if relu:
+        wts["scale"] = np.concatenate([wts["scale"], rng.normal(1, 0.1, nbits).astype(np.float32)])
+        wts["bias"] = np.concatenate([wts["bias"], rng.normal(0, 0.1, nbits).astype(np.float32)])
+    tiles = rng.integers(0, 256, size=(400, 3, h, w), dtype=np.uint8)
+    ctx = qrm.Context(weights=wts, final_relu=relu)
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_POISON_WORKSPACE)
+    for N in (1, 7, 400):
+        d_logits, d_bits = empty((N, nbits), torch.float32), empty((N, nbits), torch.uint8)
+        ctx.qrm_extractor_forward(dev(tiles[:N]), N, h, w, d_logits, d_bits)
+        torch.cuda.synchronize()
+        some = sorted({0, N // 2, N - 1})
+        ref, _ = oracle.extractor_forward(wts, tiles[some], final_relu=relu)
+        check_logits(d_logits.cpu().numpy()[some], ref, d_bits.cpu().numpy()[some], what=f"final convolution C={C} {h}x{w} N={N}")
+    ctx.close()
+
+
 # ---------------------------------------------------------------- whole path
 
 def run_detect(ctx, cfg, imgs, off, want_all=True):
