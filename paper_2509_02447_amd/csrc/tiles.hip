@@ -415,8 +415,10 @@ hipError_t launch_preprocess(const uint8_t *raw, int64_t N, int H_in, int W_in, 
     a.cx = (a.Wr - x) / 2;
     const bool vec = T % 4 == 0 && ((uintptr_t)out & 3u) == 0;
     const int64_t kMaxGrid = 1LL << 30;
-    // enough workgroups for the chip when there are few images, few column-tap computations otherwise
-    int strips = (int)std::min<int64_t>((T + 7) / 8, std::max<int64_t>(1, 2048 / N));
+    // Enough workgroups for the chip several times over (six fit a compute unit), so that no last wave of them is nearly
+    // empty: 600 images of 480 x 640 to 256 x 256 take 158 us in 3 strips an image (1.2 waves), 149 in 6, 144 in 13, the
+    // same from there on; one strip once there are as many images, as the column taps are computed per strip.
+    int strips = (int)std::min<int64_t>((T + 7) / 8, std::max<int64_t>(1, 8192 / N));
     a.rows_per_block = (T + strips - 1) / strips;
     strips = (T + a.rows_per_block - 1) / a.rows_per_block;
     for (int64_t n0 = 0; n0 < N; n0 += kMaxGrid) {
