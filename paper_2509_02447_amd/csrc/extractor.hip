@@ -495,7 +495,7 @@ struct StatArgs {
                         // MODE_FINAL [n_img][out_recs][C * slices]
     int out_recs;       // records per image
     int per;            // strips per workgroup
-    float low;          // MODE_FINAL: lower bound of an output (0: ReLU, -inf: none)
+    float low;          // MODE_FINAL: lower bound of an output (0: ReLU; NaN: none, fmaxf(v, NaN) is v, also where v is NaN)
 };
 
 constexpr int MODE_MID = 0;  // write activations, sample channel sums from every eighth strip
@@ -2046,7 +2046,7 @@ Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, i
 hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
                              const float *bias, int relu, float *partial, const Partition &part, hipStream_t s)
 {
-    StatArgs st{MeanIn{}, nullptr, partial, part.slots * part.sub, part.per, relu ? 0.f : -__builtin_inff()};
+    StatArgs st{MeanIn{}, nullptr, partial, part.slots * part.sub, part.per, relu ? 0.f : __builtin_nanf("")};
     const dim3 grid(part.blocks, nbp / C), block(64 * kMidWaves);
     if (C == 64) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
     else hipLaunchKernelGGL((conv_mid_kernel<32, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);

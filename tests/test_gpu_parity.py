@@ -498,6 +498,21 @@ def test_extractor_final_convolution_over_all_pixels(qrm, C, nb, nbits, h, w, re
     ctx.close()
 
 
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+def test_final_convolution_keeps_what_is_not_a_number(qrm, value):
+    """Without a ReLU a final convolution that is not finite gives logits that are not: an infinite weight meets the zeros
+    of the padding, so both are NaN at every border pixel and so is the sum over the tile."""
+    wts = small_weights(64, 1, 30, 5)
+    wts["conv_w"][-30 * 64 * 9:] = value
+    tiles = np.random.default_rng(3).integers(0, 256, size=(2, 3, 12, 40), dtype=np.uint8)
+    ctx = qrm.Context(weights=wts)
+    d_logits, d_bits = empty((2, 30), torch.float32), empty((2, 30), torch.uint8)
+    ctx.qrm_extractor_forward(dev(tiles), 2, 12, 40, d_logits, d_bits)
+    torch.cuda.synchronize()
+    assert np.isnan(d_logits.cpu().numpy()).all() and not d_bits.cpu().numpy().any()
+    ctx.close()
+
+
 # ---------------------------------------------------------------- whole path
 
 def run_detect(ctx, cfg, imgs, off, want_all=True):
