@@ -33,7 +33,13 @@ constexpr int kCodeAt = kQuadAt + 256;        // what follows depends on the ker
 //   lane kernel : u32 [4 ceil(n/4)][q], the (up to four) syndrome terms of symbol value v at position i, a byte each
 //   group kernel: u8 [2t + t][q], v * alpha^(G (fcr + j)) for j < 2t, then v * alpha^(G j) for j = 1 .. t
 constexpr int kMaxGroupTables = 24 * 256;
-constexpr int64_t kDecodeBlocks = 2048; // eight workgroups per compute unit; each reads the tables once and takes every 2048th run of words
+constexpr int64_t kDecodeBlocks = 2048; // lane kernel: eight workgroups per compute unit; each reads the tables once and takes every 2048th run of words
+// Group kernel: its 56 .. 80 registers let six to eight workgroups onto a compute unit, so 2048 left some waiting for a second
+// turn and others with a second run of words while the rest of the chip was done.  Five per compute unit, and every workgroup
+// the same number of runs: 20000 words of RS(255,239) 50.2 -> 37.1 us, 65536 of them 117 -> 110, 100000 of RS(63,55) 37.6 ->
+// 31.0, 400000 of RS(31,25) 78.8 -> 69.8, up to 13000 words unchanged; with 1024, 1536 and 2048 runs dealt evenly 45, 37 and 37
+// us for the first, 113, 152 and 117 for the second.
+constexpr int64_t kGroupBlocks = 1280;
 
 bool lane_code(int n, int two_t) { return n <= 16 && two_t <= 4; }
 int group_lanes(int two_t) { return two_t > 8 ? 32 : 16; } // 3t + 1 coefficients of the systolic recursion, one per lane
@@ -248,7 +254,7 @@ __global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const u
 //   Forney      error value X^(-fcr-2t) Omega_h(1/X) / (sum of the odd terms of Lambda at 1/X); Omega(1/X) equals
 //               X^(-2t) Omega_h(1/X) because Lambda(1/X) = 0.
 // A wavefront whose words are all error free stops after the syndromes.
-// Bound by vector instructions and LDS look-ups; 20000 words of RS(255,239): 51 us a pass (the recursion
+// Bound by vector instructions and LDS look-ups; 20000 words of RS(255,239): 37 us a pass (the recursion
 // repeated on all 64 lanes of a word: 388 us).
 // ------------------------------------------------------------------------------------------------
 template <int G>
@@ -477,7 +483,8 @@ hipError_t launch_group(const RsParams &p, const uint8_t *sym, int64_t N, uint8_
 {
     constexpr int GPB = 256 / G;
     int64_t blocks = (N + GPB - 1) / GPB;
-    if (blocks > kDecodeBlocks) blocks = kDecodeBlocks;
+    const int64_t rounds = (blocks + kGroupBlocks - 1) / kGroupBlocks;
+    if (rounds > 1) blocks = (blocks + rounds - 1) / rounds;
     hipLaunchKernelGGL((rs_decode_group_kernel<G, TMAX, SPL>), dim3((unsigned)blocks), dim3(256), 0, s, p, sym, N, msg,
                        cw, nerr, key);
     return hipGetLastError();

@@ -94,6 +94,22 @@ def test_rs_decode_small_batches(qrm, N):
     ctx.close()
 
 
+@pytest.mark.parametrize("m,n,t,per", [(8, 100, 8, 8), (5, 31, 3, 16)])
+def test_rs_decode_runs_shared_out_evenly(qrm, m, n, t, per):
+    """Word counts around those at which the workgroups of a long code take one, two and three runs of `per` words each."""
+    code = dict(m=m, prim_poly={5: 0x25, 8: 0x11D}[m], n=n, k=n - 2 * t, fcr=1)
+    full = 1280 * per
+    count = 2 * full + 1
+    msgs, err, _ = synth.rs_cases(90 + n, count, n, n - 2 * t, m, max_err=t + 1)
+    words = oracle.rs_encode(msgs, **code) ^ err
+    om, oc, oe = oracle.rs_decode(words, **code)
+    ctx = qrm.Context(rs=code)
+    for N in (full - 1, full, full + 1, full + per + 1, 2 * full - 1, 2 * full, count):
+        gm, gc, ge = gpu_rs_decode(ctx, words[:N])
+        assert np.array_equal(ge, oe[:N]) and np.array_equal(gm, om[:N]) and np.array_equal(gc, oc[:N]), N
+    ctx.close()
+
+
 def _random_codes(count, seed):
     """Seeded random code parameters over every supported field: (m, prim_poly, n, k, fcr)."""
     prim = {2: 0x7, 3: 0xB, 4: 0x13, 5: 0x25, 6: 0x43, 7: 0x89, 8: 0x11D}
