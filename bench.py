@@ -513,7 +513,7 @@ def bench_stream(env, passes: int, warm_passes: int) -> dict:
         "roofline": {"bound": "host link", "achieved": round(value * 3 * cfg.H * cfg.W / 1e9, 2),
                      "peak": round(link_gbs, 2), "unit": "GB/s",
                      "frac": round(value * 3 * cfg.H * cfg.W / 1e9 / link_gbs, 4), "traffic": None,
-                     "note": "peak = bare pinned upload of the same chunks measured in this run (not a published figure)"},
+                     "note": "peak = bare pinned upload of the same chunks measured in this run (not a published figure); achieved counts whole images, of which only the tiles cross the link, so it may exceed the peak"},
         "extractor_mfma_tflops": round(mfma_flops_per_image * value / 1e12, 2),
         "extractor_frac_of_bf16_peak": round(mfma_flops_per_image * value / 1e12 / PEAK_BF16_TFLOPS, 4),
         "stages": {"bare_upload_GBs": round(link_gbs, 2), "bare_upload_images_per_s": round(link_gbs * 1e9 / (3 * cfg.H * cfg.W), 1),
