@@ -282,29 +282,33 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
     if (c->has_ext) {
         L.mb = effective_micro_batch(c, N, h, w, act_budget);
         L.act = align_up((size_t)L.mb * h * w * c->C * 2);
-        // statistics records: sized for the fullest micro-batch and for the ragged last one
+        // sized for the fullest micro-batch and for the ragged last one, each for the schedule it runs
         const int tpi = tiles_per_image(h, w);
-        size_t recs = 0; // floats
         const int64_t counts[2] = {L.mb, L.mb ? N % L.mb : 0};
         for (int64_t cnt : counts) {
             if (cnt <= 0) continue;
-            const Partition pm = make_partition(cnt, tpi, mid_blocks(c), conv_mid_records_per_workgroup(c->C));
             const ConvGeom g{(int)cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
+            const bool fused = use_fused(c, (int)cnt, h, w, c->n_blocks);
+            // floats per image that the last convolution leaves for the head
+            size_t tail;
             if (!c->collapse) {
                 const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
-                L.partial = std::max(L.partial, align_up((size_t)cnt * pl.slots * pl.sub * c->nbp * 4));
+                tail = (size_t)pl.slots * pl.sub * c->nbp;
+            } else if (fused && c->n_blocks % 2 == 0) {
+                tail = (size_t)conv_pair_last_sums(g).lines * c->C;
+            } else {
+                const Partition pm = make_partition(cnt, tpi, mid_blocks(c), conv_mid_records_per_workgroup(c->C));
+                tail = (size_t)pm.slots * pm.sub * last_record_floats(c->C);
             }
-            // floats per image: what the last block leaves for the head, or sampled channel sums of any other
-            const size_t last = !c->collapse ? 0 : std::max(c->pairable ? (size_t)conv_pair_last_sums(g).lines * c->C : 0, pm.slots * pm.sub * last_record_floats(c->C));
+            L.tail = std::max(L.tail, align_up((size_t)cnt * tail * 4));
             const int samples = std::max(c->pairable ? conv_pair_samples(g).recs : 0,
                                          std::max(conv_first_samples(g, c->C).recs, conv_mid_samples(g, c->C).recs));
-            recs = std::max(recs, (size_t)cnt * std::max(last, (size_t)samples * c->C));
-            if (c->pairable) L.seam = std::max(L.seam, align_up(conv_pair_seam_bytes(g, launch_cu(c))));
+            L.stats = std::max(L.stats, align_up((size_t)cnt * samples * c->C * 4));
+            if (fused) L.seam = std::max(L.seam, align_up(conv_pair_seam_bytes(g, launch_cu(c))));
         }
-        L.stats = align_up(recs * 4);
     }
     L.symbols = (want_symbols && c->has_rs) ? align_up((size_t)N * c->rs.n) : 0;
-    L.total = kZeroBytes + 2 * L.act + L.partial + 2 * L.stats + L.seam + L.symbols;
+    L.total = kZeroBytes + 2 * L.act + L.tail + 2 * L.stats + L.seam + L.symbols;
     return L;
 }
 
@@ -411,11 +415,11 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                          hipStream_t s)
 {
     const size_t buf_off[2] = {kZeroBytes, kZeroBytes + L.act};
-    uint8_t *seam = base + kZeroBytes + 2 * L.act + L.partial + 2 * L.stats;
+    uint8_t *seam = base + kZeroBytes + 2 * L.act + L.tail + 2 * L.stats;
     bf16_t *buf[2] = {(bf16_t *)(base + buf_off[0]), (bf16_t *)(base + buf_off[1])};
-    float *partial = (float *)(base + kZeroBytes + 2 * L.act);
-    float *tb[2] = {(float *)(base + kZeroBytes + 2 * L.act + L.partial),
-                    (float *)(base + kZeroBytes + 2 * L.act + L.partial + L.stats)};
+    float *tail = (float *)(base + kZeroBytes + 2 * L.act); // what the last convolution leaves for the head
+    float *tb[2] = {(float *)(base + kZeroBytes + 2 * L.act + L.tail),
+                    (float *)(base + kZeroBytes + 2 * L.act + L.tail + L.stats)};
     const int nsym = (d_symbols && m_sym > 0) ? c->n_bits / m_sym : 0;
     const uint8_t *img0 = src.img;
     const int32_t *off0 = src.off;
@@ -444,7 +448,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             qrm_ctx::Timed *t = time_begin(c, may_time, is_last(1) ? QRM_PROFILE_PAIR_LAST : QRM_PROFILE_PAIR_FIRST,
                                            (first_flops + block_flops) * cnt, s);
             e = launch_conv_pair(base, nullptr, &src, g, c->C, c->d_w_first, c->d_w_mid[0], c->d_bias, c->d_bias + (size_t)c->C, MeanIn{},
-                                 nullptr, tb[tcur], is_last(1), launch_cu(c), seam, buf[cur], s);
+                                 nullptr, is_last(1) ? tail : tb[tcur], is_last(1), launch_cu(c), seam, buf[cur], s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_pair (first) launch");
             time_end(t, s);
             if (is_last(1)) last_sums = conv_pair_last_sums(g);
@@ -467,7 +471,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                                                2.0 * block_flops * cnt, s);
                 e = launch_conv_pair(base, base + buf_off[cur], nullptr, g, c->C, c->d_w_mid[m], c->d_w_mid[m + 1],
                                      c->d_bias + (size_t)b * c->C, c->d_bias + (size_t)(b + 1) * c->C, means, rsum,
-                                     tb[tcur ^ 1], is_last(b + 1), launch_cu(c), seam, buf[cur ^ 1], s);
+                                     is_last(b + 1) ? tail : tb[tcur ^ 1], is_last(b + 1), launch_cu(c), seam, buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_pair launch");
                 time_end(t, s);
                 if (is_last(b + 1)) last_sums = conv_pair_last_sums(g);
@@ -476,7 +480,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                 qrm_ctx::Timed *t = time_begin(c, may_time, is_last(b) ? QRM_PROFILE_BLOCK_LAST : QRM_PROFILE_BLOCK_MID,
                                                block_flops * cnt, s);
                 e = launch_conv_mid(base, buf_off[cur], g, c->C, c->d_w_mid[m], c->d_bias + (size_t)b * c->C, means,
-                                    rsum, tb[tcur ^ 1], pm, is_last(b), buf[cur ^ 1], s);
+                                    rsum, is_last(b) ? tail : tb[tcur ^ 1], pm, is_last(b), buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_mid launch");
                 time_end(t, s);
                 if (is_last(b)) last_sums = LastSums{pm.slots * pm.sub, pm.sub, pm.per, tpi, 0, 0, 0, 0, 0, 0};
@@ -496,15 +500,15 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         uint8_t *sy = nsym ? d_symbols + n0 * nsym : nullptr;
         qrm_ctx::Timed *t = time_begin(c, may_time, QRM_PROFILE_HEAD, 0.0, s);
         if (c->collapse) {
-            e = launch_head(tb[tcur], last_sums, c->C, cnt, c->n_bits, c->nbp, inv_hw, c->d_wft, c->d_bias_final,
+            e = launch_head(tail, last_sums, c->C, cnt, c->n_bits, c->nbp, inv_hw, c->d_wft, c->d_bias_final,
                             c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {
             const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
             e = launch_conv_final(base, buf_off[cur], g, c->C, c->nbp, c->d_w_final, c->final_relu ? c->d_bias_final : nullptr,
-                                  c->final_relu, partial, pl, s);
+                                  c->final_relu, tail, pl, s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_final launch");
-            e = launch_linear_pack(partial, LastSums{pl.slots * pl.sub, pl.sub, pl.per, tpi, 0, 0, 0, 0, 0, 0}, c->nbp, cnt, c->n_bits, inv_hw,
+            e = launch_linear_pack(tail, LastSums{pl.slots * pl.sub, pl.sub, pl.per, tpi, 0, 0, 0, 0, 0, 0}, c->nbp, cnt, c->n_bits, inv_hw,
                                    c->final_relu ? nullptr : c->d_bias_final, c->d_lin_w, c->d_lin_b, lg, bt, sy,
                                    m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "linear_pack launch");

@@ -62,3 +62,24 @@ def test_detect_static_equals_detect_on_two_calls_in_a_row():
     ctx.qrm_detect_static(d_img, 0, cfg.H, cfg.W, d_off, tile, None, None, m1, None, e1)      # N == 0: no-op
     ctx.close()
     ref_ctx.close()
+
+
+@pytest.mark.parametrize("tile,n_blocks", [(305, 8), (308, 3), (502, 2)])
+def test_detect_static_takes_tiles_up_to_the_size_of_its_array(tile, n_blocks):
+    """Tiles of 64 channels, the last of them the largest whose activations fit the array one image at a time; same bytes
+    as qrm_detect with the same micro-batch."""
+    import paper_2509_02447_amd as q
+    cfg = synth.CONFIGS["C2"]
+    wts = synth.extractor_weights(3, n_blocks, 64, cfg.n_bits, seed_index=tile)
+    rs = dict(m=cfg.m, prim_poly=cfg.prim_poly, n=cfg.n, k=cfg.k, fcr=cfg.fcr)
+    ctx, ref_ctx = q.Context(weights=wts, rs=rs), q.Context(weights=wts, rs=rs)
+    N = 2 if tile < 400 else 1
+    d_img = dev(np.random.default_rng(tile).integers(0, 256, size=(N, 3, tile, tile), dtype=np.uint8))
+    a, b = outputs(cfg, N), outputs(cfg, N)
+    ctx.qrm_detect_static(d_img, N, tile, tile, None, tile, *a)
+    ref_ctx.qrm_detect(d_img, N, tile, tile, None, tile, *b)
+    torch.cuda.synchronize()
+    for name, x, y in zip(("logits", "bits", "msg", "codeword", "nerr"), a, b):
+        assert np.array_equal(x.cpu().numpy(), y.cpu().numpy()), name
+    ctx.close()
+    ref_ctx.close()
