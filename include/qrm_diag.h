@@ -39,6 +39,15 @@ QRM_API qrm_status qrm_diag_set_flags(qrm_ctx *ctx, int32_t flags);
  */
 QRM_API qrm_status qrm_diag_matrix_rate(qrm_ctx *ctx, int32_t data, double *tflops);
 
+/*
+ * How a fused launch (64 channels, two blocks; `last`: the second one is the network's last) deals the row pairs of
+ * n_img tiles of h x w to num_cu compute units: *part = 1 runs that begin and end inside images, 0 whole images per
+ * workgroup; *per = pieces per workgroup (row pairs; with `last` four of them); *cost = cost of the longest
+ * workgroup: eight for each of its steps, one for each row pair that either block multiplies in them.  Host code, no device needed.
+ */
+QRM_API qrm_status qrm_diag_pair_split(int32_t n_img, int32_t h, int32_t w, int32_t last, int32_t num_cu, int32_t *part,
+                                       int32_t *per, int32_t *cost);
+
 #ifdef __cplusplus
 }
 #endif

@@ -1956,6 +1956,47 @@ size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu)
     return half * (2 * (size_t)num_cu + (g.w % kTileW == 0 ? (size_t)g.n_img : 0));
 }
 
+// What the longest workgroup has to do when a launch's pieces of `quant` row pairs are dealt in runs of `per`: eight for each
+// of its steps (positions of the kernel's stream and two to drain), one for each row pair that either group multiplies in them.
+static int pair_cost(const ConvGeom &g, int quant, int per)
+{
+    const int S = (g.h + 1) / 2, ppi = (S + quant - 1) / quant;
+    const int64_t pieces = (int64_t)g.n_img * ppi, runs = (pieces + per - 1) / per;
+    int longest = 0;
+    for (int64_t v = 0; v < std::min<int64_t>(runs, ppi); ++v) { // (where a run begins in its image repeats after ppi runs)
+        const int64_t q0 = v * per, q1 = std::min(pieces, q0 + per);
+        const int images = (int)((q1 - 1) / ppi - q0 / ppi) + 1;
+        const int ja = (int)(q0 % ppi) * quant, jb = std::min(S, (int)((q1 - 1) % ppi + 1) * quant);
+        const int own = images * S - ja - (S - jb);   // row pairs of the run, per column block
+        const int halo = (ja > 0) + (jb < S);         // computed by the first group only
+        longest = std::max(longest, (8 * (own + halo + images) + 2 * own + halo) * g.colblks + 16);
+    }
+    return longest;
+}
+
+// Whole images per workgroup, or every compute unit one run of the launch's row pairs.  A run that begins and ends inside
+// images has up to two halo pairs and an opening position more than its row pairs, and its code has more scalar
+// instructions a step: runs where the longest workgroup gets shorter by more than 3 %.  Short launches are bound by the
+// steps' latency, which is why a step counts for more than the matrix work in it (fitted to 47 shapes from 40 x 5 x 64 to
+// 450 x 24 x 200, of which the rule picks the slower way by 1.5 % at most).  Eight blocks, whole images / runs, cost of a
+// middle pair: 192 tiles of 8 x 64 89 / 94 us (64 / 80), 224 of 16 x 64 132 / 141 (104 / 120), 245 of 64 x 64 425 / 439 (344 / 360), 480
+// of 64 x 64 830 / 842 (672 / 658), 240 of 128 x 128 1712 / 1741 (1312 / 1284); 40 of 5 x 64 70 / 62 (54 / 52), 160 of 16 x 64 126 / 122
+// (104 / 100), 333 of 16 x 64 209 / 190 (192 / 168), 300 of 64 x 64 651 / 535 (672 / 438), 200 of 128 x 128 1528 / 1459 (1312 / 1084).
+PairSplit conv_pair_split(const ConvGeom &g, bool last, int num_cu)
+{
+    const int quant = last ? kChunk : 1;
+    const int ppi = ((g.h + 1) / 2 + quant - 1) / quant;
+    const int64_t pieces = (int64_t)g.n_img * ppi;
+    const int whole = (g.n_img + num_cu - 1) / num_cu * ppi, run = (int)((pieces + num_cu - 1) / num_cu);
+    const int whole_cost = pair_cost(g, quant, whole), run_cost = pair_cost(g, quant, run);
+    PairSplit p{};
+    p.part = (int64_t)103 * run_cost < (int64_t)100 * whole_cost;
+    p.per = p.part ? run : whole;
+    p.cost = p.part ? run_cost : whole_cost;
+    p.workgroups = (int)((pieces + p.per - 1) / p.per);
+    return p;
+}
+
 template <bool FIRST, bool LASTB, bool PART>
 static void launch_pair_variant(bool wide, dim3 grid, hipStream_t s, const uint8_t *zeros, const uint8_t *in, const TileSrc &src,
                                 const ConvGeom &g, const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a,
@@ -1974,21 +2015,14 @@ hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileS
     const bool wide = g.colblks > 1;
     const bool seam_column = wide && g.w % kTileW == 0;
     if (wide && !seam) return hipErrorInvalidValue;
-    // Whole images per workgroup if that keeps all but 4 % of the compute units busy, else every compute unit one run of
-    // the launch's row pairs.
-    const int quant = last ? kChunk : 1;
-    const int ppi = ((g.h + 1) / 2 + quant - 1) / quant;
-    const int64_t pieces = (int64_t)g.n_img * ppi;
-    const int whole = (g.n_img + num_cu - 1) / num_cu;
-    const bool part = (int64_t)g.n_img * 100 < (int64_t)whole * num_cu * 96;
-    const int per = part ? (int)((pieces + num_cu - 1) / num_cu) : whole * ppi;
-    const dim3 grid((unsigned)((pieces + per - 1) / per));
+    const PairSplit split = conv_pair_split(g, last, num_cu);
+    const dim3 grid((unsigned)split.workgroups);
     if ((int)grid.x > num_cu) return hipErrorInvalidValue; // the seam buffer holds num_cu workgroups
     const size_t half = (size_t)(2 * ((g.h + 1) / 2)) * kSeamRowBytes;
     uint8_t *seam_last = seam_column ? seam + 2 * (size_t)num_cu * half : nullptr;
     const LastSums sums = conv_pair_last_sums(g);
     const int out_recs = last ? sums.lines : conv_pair_samples(g).recs;
-    PairArgs st{tin, rsum_a, tout, out_recs, per, sums.rows, seam, seam_last};
+    PairArgs st{tin, rsum_a, tout, out_recs, split.per, sums.rows, seam, seam_last};
     const TileSrc src = first ? *first : TileSrc{};
     auto launch = [&](auto part) {
         constexpr bool PART = decltype(part)::value;
@@ -2000,7 +2034,7 @@ hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileS
             else launch_pair_variant<false, false, PART>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
         }
     };
-    if (part) launch(std::true_type{});
+    if (split.part) launch(std::true_type{});
     else launch(std::false_type{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !seam_column) return e;

@@ -100,5 +100,16 @@ qrm_status qrm_diag_matrix_rate(qrm_ctx *c, int32_t data, double *tflops)
     return QRM_OK;
 }
 
+qrm_status qrm_diag_pair_split(int32_t n_img, int32_t h, int32_t w, int32_t last, int32_t num_cu, int32_t *part, int32_t *per,
+                               int32_t *cost)
+{
+    if (n_img < 1 || h < 1 || w < 1 || num_cu < 1 || !part || !per || !cost) return QRM_E_INVALID;
+    const ConvGeom g{n_img, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
+    const PairSplit p = conv_pair_split(g, last != 0, num_cu);
+    *part = p.part;
+    *per = p.per;
+    *cost = p.cost;
+    return QRM_OK;
+}
 
 } // extern "C"

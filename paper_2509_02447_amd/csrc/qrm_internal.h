@@ -105,6 +105,14 @@ hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, 
 // tout: channel sums of the output (conv_pair_samples()).  last: the second block is the network's last one: no
 // activations are written, tout receives lines of channel sums (conv_pair_last_sums()).
 bool conv_pair_supported(int C, const ConvGeom &g);
+// How the row pairs of a launch are dealt to workgroups.
+struct PairSplit {
+    bool part;      // runs that begin and end inside images; otherwise whole images
+    int per;        // pieces (kChunk row pairs each with `last`, one otherwise) per workgroup
+    int workgroups;
+    int cost;       // of the longest workgroup (pair_cost)
+};
+PairSplit conv_pair_split(const ConvGeom &g, bool last, int num_cu);
 LastSums conv_pair_last_sums(const ConvGeom &g);
 size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu);
 hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,

@@ -1,0 +1,82 @@
+"""Host logic of the library without a GPU: how a fused launch deals its row pairs to workgroups."""
+import ctypes as C
+import random
+
+import pytest
+
+CU = 256
+
+
+@pytest.fixture(scope="module")
+def split():
+    from paper_2509_02447_amd import binding as b
+    lib = b.load_library()
+
+    def call(n, h, w, last):
+        part, per, cost = C.c_int32(), C.c_int32(), C.c_int32()
+        assert lib.qrm_diag_pair_split(n, h, w, last, CU, C.byref(part), C.byref(per), C.byref(cost)) == 0
+        return part.value, per.value, cost.value
+    return call
+
+
+def longest_walk(n_img, h, w, last, per):
+    """Cost of the longest workgroup, counted by walking through its stream of positions one at a time."""
+    S, J, quant = (h + 1) // 2, -(-w // 64), 4 if last else 1
+    ppi = -(-S // quant)
+    longest = 0
+    for q0 in range(0, n_img * ppi, per):
+        q1 = min(n_img * ppi, q0 + per)
+        units = []                                # (first, behind the last row pair) of each unit of the run
+        for n in range(q0 // ppi, (q1 - 1) // ppi + 1):
+            lo, hi = max(q0, n * ppi) - n * ppi, min(q1, (n + 1) * ppi) - n * ppi
+            units += [(lo * quant, min(S, hi * quant))] * J
+        steps = 2                                 # the second block and its epilogue run two positions behind
+        pairs = 0                                 # row pairs multiplied by the first and by the second block
+        for lo, hi in units:
+            steps += 1                            # opening position (of the first unit: the one behind the last unit)
+            for j in range(lo - (lo > 0), hi + (hi < S)):
+                steps += 1
+                pairs += 2 if lo <= j < hi else 1  # a halo pair is not the second block's
+        longest = max(longest, 8 * steps + pairs)
+    return longest
+
+
+def runs_per(n_img, h, last):
+    pieces = n_img * -(-((h + 1) // 2) // (4 if last else 1))
+    return -(-pieces // CU)
+
+
+def whole_per(n_img, h, last):
+    return -(-n_img // CU) * -(-((h + 1) // 2) // (4 if last else 1))
+
+
+def check(split, n, h, w, last):
+    part, per, cost = split(n, h, w, last)
+    whole, runs = (longest_walk(n, h, w, last, f(n, h, last)) for f in (whole_per, runs_per))
+    assert per == (runs_per if part else whole_per)(n, h, last)
+    assert cost == (runs if part else whole), (n, h, w, last)
+    assert bool(part) == (103 * runs < 100 * whole), (n, h, w, last, whole, runs)
+    assert cost <= whole
+
+
+@pytest.mark.parametrize("n,h,w", [(192, 8, 64), (224, 16, 64), (240, 32, 64), (480, 16, 128), (245, 64, 64)])
+def test_whole_images_where_runs_would_be_longer(split, n, h, w):
+    for last in (0, 1):
+        assert split(n, h, w, last)[0] == 0
+        check(split, n, h, w, last)
+
+
+@pytest.mark.parametrize("n,h,w", [(1, 64, 64), (7, 128, 128), (300, 64, 64), (333, 64, 64), (140, 32, 64), (40, 5, 64), (160, 16, 64), (200, 128, 128)])
+def test_runs_where_whole_images_leave_compute_units_idle(split, n, h, w):
+    assert split(n, h, w, 0)[0] == 1
+    for last in (0, 1):
+        check(split, n, h, w, last)
+
+
+def test_cost_of_the_longest_workgroup(split):
+    rng = random.Random(5)
+    for _ in range(300):
+        check(split, rng.choice([1, 2, rng.randint(1, 40), rng.randint(1, 1200)]), rng.randint(1, 140), rng.randint(1, 260),
+              rng.randint(0, 1))
+    check(split, 5, 1, 1, 0)
+    check(split, 5, 2, 1, 1)
