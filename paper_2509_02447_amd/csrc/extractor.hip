@@ -311,12 +311,12 @@ __device__ __forceinline__ void load_weight_frags(bf16x8 (&Wr)[9][C / 16], const
 //      zero, took a consumer longer to read (30 of a block's 42 us for 7 tiles of 128 x 128) than its matrix work.
 //  (2) the last conv (C -> n_bits, no ReLU) followed by the global average pool is linear, so it only
 //      needs, per channel of the last block's output, the sums over the whole tile, its first / last
-//      row, first / last column and four corners (9 numbers): the last block writes no activations.  The
-//      single-block kernel writes a record of nine sums per (image, workgroup that touched it, wavefront),
-//      rec[q*C + c]; the fused kernel writes lines of C sums, each over a part of the image that does not depend on
-//      how the rows were dealt to workgroups (LastSums), so that its results do not either.
+//      row, first / last column and four corners (9 numbers): the last block writes no activations but lines
+//      of C sums, each over a part of the image that does not depend on how the rows were dealt to workgroups
+//      (LastSums), so that its results do not either: the same image gives the same bits whatever the batch around it
+//      and however many compute units the launch has.  (A record of nine sums per workgroup, wavefront and image, the
+//      alternative, also was 295 KB per image for the head to read in a launch of 7 tiles of 128 x 128; the lines are 52.)
 // Accumulation order is fixed, so results do not depend on scheduling.
-__host__ __device__ constexpr int stat_rec(int C) { return 9 * C; }
 __host__ __device__ constexpr int sampled_strip(int strips) { return strips < 4 ? strips - 1 : 3; }
 
 // The sampled channel means of image n, from its mi.recs records, into dst[0 .. C) (LDS) by one wavefront: 16 bytes
@@ -423,17 +423,13 @@ __device__ __forceinline__ void lds_accumulate4(float *slot4, const float (&tv)[
 }
 
 // Channel sums of the RW output rows (first row yw, column x) held in `acc`, after bias `si` (this lane's
-// 16 channels) and ReLU.  LAST = false: written to the record at `dst` (global memory, already offset to the lane's
-// 16 channels).  LAST = true: the nine border-aware sums of the last block, added to this wavefront's accumulators
-// `dst` ([sum index][32 channels] floats in LDS, offset likewise): 0 all, 1 / 2 first / last row, 3 / 4 first / last
-// column, 5 .. 8 the corners (top-left, top-right, bottom-left, bottom-right).  Four channels at a time: registers
-// are scarce next to weights and accumulators.
-template <int RW, bool LAST>
+// 16 channels) and ReLU, written to the line of C sums at `dst` (global memory, already offset to the lane's 16
+// channels).  Four channels at a time: registers are scarce next to weights and accumulators.
+template <int RW>
 __device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const float *si, float *dst, int x, int yw,
                                                  int h, int w, int px)
 {
     const bool colok = (uint32_t)x < (uint32_t)w; // (x = -1: the column left of a wide tile's first block)
-    const int rl = h - 1 - yw; // image row h-1 relative to this wavefront's rows
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const f32x4 bq = *(const f32x4 *)(si + 4 * q);
@@ -448,67 +444,97 @@ __device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const 
 #pragma unroll
             for (int e = 0; e < 4; ++e) tv[e] = 0.f;
         }
-        if (LAST) {
-            lds_accumulate4(dst + 3 * 32 + 4 * q, tv, x == 0);       // first column
-            lds_accumulate4(dst + 4 * 32 + 4 * q, tv, x == w - 1);   // last column
-        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) tv[e] = half_sum(tv[e]);
-        if (!LAST) {
-            if (px == kSumLane) *(f32x4 *)(dst + 4 * q) = (f32x4){tv[0], tv[1], tv[2], tv[3]};
-        } else {
-            lds_accumulate4(dst + 4 * q, tv, px == kSumLane);        // whole tile
-            if (yw == 0) { // image row 0 is this wavefront's first row
-                float rv[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) rv[e] = colok ? fmaxf(acc[0][4 * q + e] + bq[e], 0.f) : 0.f;
-                lds_accumulate4(dst + 5 * 32 + 4 * q, rv, x == 0);
-                lds_accumulate4(dst + 6 * 32 + 4 * q, rv, x == w - 1);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) rv[e] = half_sum(rv[e]);
-                lds_accumulate4(dst + 1 * 32 + 4 * q, rv, px == kSumLane);
-            }
-            if (rl >= 0 && rl < RW) {
-                float rv[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float a = acc[0][4 * q + e];
-#pragma unroll
-                    for (int r = 1; r < RW; ++r) a = rl == r ? acc[r][4 * q + e] : a;
-                    rv[e] = colok ? fmaxf(a + bq[e], 0.f) : 0.f;
-                }
-                lds_accumulate4(dst + 7 * 32 + 4 * q, rv, x == 0);
-                lds_accumulate4(dst + 8 * 32 + 4 * q, rv, x == w - 1);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) rv[e] = half_sum(rv[e]);
-                lds_accumulate4(dst + 2 * 32 + 4 * q, rv, px == kSumLane);
-            }
-        }
+        if (px == kSumLane) *(f32x4 *)(dst + 4 * q) = (f32x4){tv[0], tv[1], tv[2], tv[3]};
         __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// This lane's sums over the RW output rows (first row yw), after bias `si` and a lower bound `low`: 16 channels, zero in
+// columns beyond the tile.
+template <int RW>
+__device__ __forceinline__ void column_sums(float (&t)[16], const f32x16 (&acc)[RW], const float *si, float low, bool colok, int yw, int h)
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const f32x4 b = *(const f32x4 *)(si + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float v = 0.f;
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+                if (yw + r < h) v += fmaxf(acc[r][4 * q + e] + b[e], low); // (the same for the whole wavefront)
+            t[4 * q + e] = colok ? v : 0.f;
+        }
+    }
+}
+
+// Last block: the lines of channel sums (LastSums) of the RW output rows held in `acc`.  `lines`: the image's first line,
+// offset to the lane's 16 channels; whole / col / row: which of its lines for the whole tile, for the first / last column
+// and for the first / last row these are; the latter and the corners are written by the wavefronts that hold a border.
+// A sum over the 32 pixel lanes is one butterfly for all 16 channels (reduce16_over_half), as in the fused kernel.
+struct LinePlaces {
+    int first_col, last_col, rows, last_rows, corners; // as in LastSums
+    int whole, col, row;
+};
+template <int C, int RW>
+__device__ __forceinline__ void last_lines(const f32x16 (&acc)[RW], const float *si, float *lines, const LinePlaces &at, int x, int x0w,
+                                           int yw, int h, int w, int px)
+{
+    const bool colok = x < w;
+    const bool has_first = x0w == 0, has_last = x0w <= w - 1 && w - 1 < x0w + 32; // same for the whole wavefront
+    auto summed = [&](int line, const float (&v)[16]) {
+        const float y = reduce16_over_half(v, px);
+        if ((px & 1) == 0) lines[line * C + reduce16_index(px)] = y;
+    };
+    auto single = [&](int line, const float (&v)[16], bool pred) {
+        if (pred) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *(f32x4 *)(lines + line * C + 4 * q) = (f32x4){v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+        }
+    };
+    float t[16];
+    column_sums<RW>(t, acc, si, 0.f, colok, yw, h);
+    if (has_first) single(at.first_col + at.col, t, x == 0);
+    if (has_last) single(at.last_col + at.col, t, x == w - 1);
+    summed(at.whole, t);
+    const int rl = h - 1 - yw; // image row h-1 relative to this wavefront's rows
+    if (yw == 0 || (rl >= 0 && rl < RW)) {
+#pragma unroll 1
+        for (int which = 0; which < 2; ++which) { // the tile's first row, its last one
+            if (which == 0 ? yw != 0 : (rl < 0 || rl >= RW)) continue;
+            const int row = which == 0 ? 0 : rl;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                float a = acc[0][v];
+#pragma unroll
+                for (int r = 1; r < RW; ++r) a = row == r ? acc[r][v] : a;
+                t[v] = colok ? fmaxf(a + si[v], 0.f) : 0.f;
+            }
+            summed((which ? at.last_rows : at.rows) + at.row, t);
+            if (has_first) single(at.corners + 2 * which, t, x == 0);
+            if (has_last) single(at.corners + 2 * which + 1, t, x == w - 1);
+        }
     }
 }
 
 struct StatArgs {
     MeanIn tin;         // channel sums of the input (rec null: no correction)
     const float *rsum;  // [c_in][c_out] residual-weight sums of this layer (fp32)
-    float *tout;        // records written by this launch: MODE_MID [n_img][out_recs][C], MODE_LAST [n_img][out_recs][9 C],
-                        // MODE_FINAL [n_img][out_recs][C * slices]
-    int out_recs;       // records per image
+    float *tout;        // lines of sums written by this launch: [n_img][out_recs][C], MODE_FINAL [n_img][out_recs][C * slices]
+    int out_recs;       // lines per image
     int per;            // strips per workgroup
     float low;          // MODE_FINAL: lower bound of an output (0: ReLU; NaN: none, fmaxf(v, NaN) is v, also where v is NaN)
 };
 
 constexpr int MODE_MID = 0;  // write activations, sample channel sums from every eighth strip
-constexpr int MODE_LAST = 1; // last block: no activations, the nine border-aware channel sums
+constexpr int MODE_LAST = 1; // last block: no activations, lines of channel sums (LastSums)
 constexpr int MODE_FINAL = 2; // final convolution (C output channels per grid.y slice), summed over the pixels: no activations
 
 constexpr int kMidWaves = 8; // wavefronts of a conv_mid workgroup: two groups of four
 
-template <int C, int MODE>
-struct MidRing {
-    static constexpr int NSLOT = MODE == MODE_LAST ? 14 : 15; // row slots of the LDS ring (>= 12)
-    static constexpr int NSUB = kMidWaves / MidCfg<C>::NCB;   // MODE_LAST, MODE_FINAL: records a workgroup writes per image
-};
+constexpr int kMidSlots = 15;   // row slots of its LDS ring (>= 12)
 
 // C -> C (+bias, ReLU), bf16 NHWC in / out.  One persistent workgroup of eight wavefronts per CU, two
 // wavefronts per SIMD.  The workgroup walks down its run of strips; the two groups of four wavefronts
@@ -517,7 +543,7 @@ struct MidRing {
 // issues the direct-to-LDS loads of strip p+2.  One workgroup barrier ends a phase.  The matrix cores thus always have one wavefront per SIMD feeding them while the other
 // does the vector / memory work, and every load has a whole phase to land before anyone waits for it.
 //
-// Staged rows live in a ring of NSLOT row slots.  Rows are loaded in the order the run needs them, so
+// Staged rows live in a ring of kMidSlots row slots.  Rows are loaded in the order the run needs them, so
 // ring position = number of rows loaded before: strip i of the run loads nr(i) new rows at positions
 // base(i).. and reads the six rows from wstart(i):
 //   i = 0                      : 6 rows,             wstart = base
@@ -531,14 +557,11 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                                                                      bf16_t *__restrict__ out)
 {
     typedef MidCfg<C> K;
-    typedef MidRing<C, MODE> R;
     constexpr int RG = 2 / K::NCB;     // row groups among the 4 wavefronts of a group
     constexpr int RW = kRows / RG;     // output rows per wavefront
-    constexpr int NSLOT = R::NSLOT;
-    constexpr int NQ = MODE == MODE_LAST ? 9 : 0; // sums per channel gathered in LDS
+    constexpr int NSLOT = kMidSlots;
     constexpr int WIN = kRows + 2;     // staged rows one strip reads
     __shared__ __attribute__((aligned(1024))) uint8_t lds[NSLOT * K::ROWB];
-    __shared__ __attribute__((aligned(16))) float s_stat[kMidWaves][NQ ? NQ : 1][32]; // MODE_LAST: per wavefront, 32 channels of its block
     // bias + rounding-residual correction per image, indexed by image mod 4: it is written two phases
     // before the image's first strip is multiplied and read until one phase after its last, and an
     // image may be a single strip
@@ -620,30 +643,6 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
         }
         if (part == 0) s_init[n & 3][o] = (MODE != MODE_FINAL || bias ? bias[slice * C + o] : 0.f) + d;
     };
-    // MODE_LAST, MODE_FINAL: this wavefront's sums of image n -> its record; accumulators cleared
-    float run_sum = 0.f; // MODE_FINAL: one channel per lane (reduce16_over_half)
-    auto flush = [&](int n) {
-        if (MODE == MODE_FINAL) {
-            const int lane = pin_in_loop(tid & 63);
-            const int px = lane & 31, half = lane >> 5;
-            const int slot = vb - (n * tpi) / st.per;
-            float *rec = st.tout + (((int64_t)n * st.out_recs + slot * R::NSUB + wave / K::NCB) * gridDim.y + slice) * C;
-            if ((px & 1) == 0) rec[cb * 32 + half * 16 + reduce16_index(px)] = run_sum;
-            run_sum = 0.f;
-        }
-        if (MODE == MODE_LAST && st.tout) {
-            const int lane = pin_in_loop(tid & 63);
-            const int slot = vb - (n * tpi) / st.per; // which of the workgroups that touch the image this is
-            float *rec = st.tout + ((int64_t)n * st.out_recs + slot * R::NSUB + wave / K::NCB) * stat_rec(C);
-            if (lane < 32) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    rec[q * C + cb * 32 + lane] = s_stat[wave][q][lane];
-                    s_stat[wave][q][lane] = 0.f;
-                }
-            }
-        }
-    };
     f32x16 acc[RW];
     const int sample_phase = sampled_strip(g.strips); // strips 3, 11, 19, .. are sampled (the last one of a short tile)
     // bias, ReLU, bf16, stores and statistics of strip i (accumulated by this wavefront)
@@ -682,38 +681,35 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                 }
             }
         }
+        const int piece = rg * 2 + xb; // which of the strip's lines is this wavefront's: row group, pixel block
         if (MODE == MODE_FINAL) {
-            const bool colok = x < g.w;
             float t[16];
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const f32x4 b = *(const f32x4 *)(si + 4 * q4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float v = 0.f;
-#pragma unroll
-                    for (int r = 0; r < RW; ++r)
-                        if (yw + r < g.h) v += fmaxf(acc[r][4 * q4 + e] + b[e], st.low); // (the same for the whole wavefront)
-                    t[4 * q4 + e] = colok ? v : 0.f;
-                }
-            }
-            run_sum += reduce16_over_half(t, px);
+            column_sums<RW>(t, acc, si, st.low, x < g.w, yw, g.h);
+            const float sum = reduce16_over_half(t, px); // one channel per lane
+            const int line = (q.colblk * g.strips + strip) * (2 * RG) + piece;
+            float *rec = st.tout + (((int64_t)n * st.out_recs + line) * gridDim.y + slice) * C;
+            if ((px & 1) == 0) rec[cb * 32 + half * 16 + reduce16_index(px)] = sum;
         } else if (st.tout) {
-            if (MODE == MODE_LAST) {
-                strip_statistics<RW, true>(acc, si, &s_stat[wave][0][half * 16], x, yw, g.h, g.w, px);
-            } else if ((strip & 7) == sample_phase) { // records of a sampled strip: column block, row group, pixel block
-                const int ri = (((strip >> 3) * g.colblks + q.colblk) * RG + rg) * 2 + xb;
-                strip_statistics<RW, false>(acc, si, st.tout + ((int64_t)n * st.out_recs + ri) * C + cb * 32 + half * 16, x, yw,
-                                            g.h, g.w, px);
+            float *lines = st.tout + (int64_t)n * st.out_recs * C + cb * 32 + half * 16;
+            if (MODE == MODE_LAST) { // (the places are those of conv_mid_last_sums())
+                LinePlaces at;
+                at.first_col = tpi * 2 * RG;
+                at.last_col = at.first_col + g.strips * RG;
+                at.rows = at.last_col + g.strips * RG;
+                at.last_rows = at.rows + 2 * g.colblks;
+                at.corners = at.last_rows + 2 * g.colblks;
+                at.whole = (q.colblk * g.strips + strip) * (2 * RG) + piece;
+                at.col = strip * RG + rg;
+                at.row = q.colblk * 2 + xb;
+                last_lines<C, RW>(acc, si, lines, at, x, x0 + xb * 32, yw, g.h, g.w, px);
+            } else if ((strip & 7) == sample_phase) {
+                const int line = ((strip >> 3) * g.colblks + q.colblk) * (2 * RG) + piece;
+                strip_statistics<RW>(acc, si, lines + line * C, x, yw, g.h, g.w, px);
             }
         }
     };
 
-    // ---- prologue: statistics cleared, corrections of the first image(s), strips 0 and 1 on their way
-    if (lane < 32) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) s_stat[wave][q][lane] = 0.f;
-    }
+    // ---- prologue: corrections of the first image(s), strips 0 and 1 on their way
     if (grp == 0) prepare_init(gc.n);
     else if (ns > 1 && g1.n != gc.n) prepare_init(g1.n);
     if (grp == 1) {
@@ -755,7 +751,6 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
             issued_upto = p + 2;
         }
         if (!mma_phase && p + 2 < ns && g2.n != g1.n) prepare_init(g2.n);
-        if (p >= 1 && (p == ns || gc.n != gp.n)) flush(gp.n); // strip p - 1 was the last of its image in this run
         // what this group issued a phase ago (or, late, just now) must have landed before the barrier
         if (mma_phase || late) __builtin_amdgcn_s_waitcnt(kWaitVm0);
         lds_barrier();
@@ -827,8 +822,8 @@ constexpr int kChunk = 4;
 // FIRST: the first of the two blocks is the network's first block (3 -> C on the raw u8 tile: crop and
 //        normalisation fused, weights as bf16 high part + residual, see conv_first_kernel) instead of a
 //        C -> C block; `src` replaces ws / in_off, wfragA holds that block's fragments.
-// LASTB: the second block is the network's last block: no activations are written, its records carry the
-//        nine border-aware channel sums (see strip_statistics).
+// LASTB: the second block is the network's last block: no activations are written, but lines of its channel
+//        sums (see last_block_statistics).
 // WIDE : tiles of more than one column block (see above); the other instantiations keep the straight-line code
 //        of the one-block case.
 // PART : workgroups take runs of row pairs that begin and end inside images; otherwise every workgroup takes whole
@@ -1076,7 +1071,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
     __syncthreads();
 
-    // LASTB: the nine border-aware channel sums of the last block's output (see strip_statistics) from the two
+    // LASTB: the nine border-aware channel sums of the last block's output from the two
     // rows in `a`, written as lines of C sums (LastSums).  The sum over the whole tile, the only one every pixel goes
     // into, is kept in a register per lane: the 16 channel values of a lane (both rows added) go through one butterfly
     // over the 32 pixel lanes, after which every lane holds the sum of one channel and adds it to its running total
@@ -1210,8 +1205,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
             if (st.tout) last_block_statistics(a, si, p, x, x_lo + xb * 32, pxl, hf);
         } else if (st.tout && ((j >> 1) & 7) == sample_phase) { // (the rows conv_mid would sample)
             const int ri = (((j >> 4) * 2 + (j & 1)) * J + blk) * 2 + xb; // sampled row pair, column block, pixel block
-            strip_statistics<RW, false>(a, si, st.tout + ((int64_t)n * st.out_recs + ri) * C + cb * 32 + hf * 16, x, 2 * j, g.h,
-                                        g.w, pxl);
+            strip_statistics<RW>(a, si, st.tout + ((int64_t)n * st.out_recs + ri) * C + cb * 32 + hf * 16, x, 2 * j, g.h, g.w, pxl);
         }
     };
 
@@ -1671,27 +1665,21 @@ __device__ __forceinline__ f32x4 sum_lines(const f32x4 *p, int stride, int start
     return sum;
 }
 
-// Records of image n: those of the workgroups that touched it.
-__device__ __forceinline__ int sums_of_image(const LastSums &sums, int64_t n)
-{
-    const int first = (int)(n * sums.strips) / sums.per, last = (int)(n * sums.strips + sums.strips - 1) / sums.per;
-    return (last - first + 1) * sums.sub;
-}
-
 constexpr int kHeadIpb = 1;   // images per block (a launch of a few hundred images should reach every compute unit)
 constexpr int kHeadKParts = 8; // the k = (channel, tap) range is cut in eight, one part per 64 threads
 constexpr int kHeadThreads = 64 * kHeadKParts;
 
-__global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restrict__ recs, LastSums sums, int C, int n_img,
+template <int C>
+__global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restrict__ recs, LastSums sums, int n_img,
                                                    int n_bits, int nbp, float inv_hw,
                                                    const float *__restrict__ wft /*[C*9][nbp]*/,
                                                    const float *__restrict__ fbias, const float *__restrict__ lin_w,
                                                    const float *__restrict__ lin_b, float *__restrict__ logits,
                                                    uint8_t *__restrict__ bits, uint8_t *__restrict__ symbols, int m)
 {
-    __shared__ __attribute__((aligned(16))) float Q[kHeadIpb][9 * 64];       // the image's sums, [q*C + c]
-    __shared__ __attribute__((aligned(16))) float Qp[kHeadThreads * 4];      // partial sums over the records
-    __shared__ float S[kHeadIpb][9 * 64]; // [c*9 + tap]
+    __shared__ __attribute__((aligned(16))) float Q[kHeadIpb][9 * C];        // the image's sums, [q*C + c]
+    __shared__ __attribute__((aligned(16))) float Qp[4 * C];                 // partial sums over the whole-tile lines
+    __shared__ float S[kHeadIpb][9 * C]; // [c*9 + tap]
     __shared__ float part[kHeadKParts][kHeadIpb][128];
     __shared__ float pooled[kHeadIpb][128];
     __shared__ uint8_t sbit[kHeadIpb][128];
@@ -1699,55 +1687,37 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
     const int64_t n0 = (int64_t)blockIdx.x * kHeadIpb;
     for (int i = 0; i < kHeadIpb; ++i) {
         const bool have = n0 + i < n_img;
-        if (sums.records) {
-            // records -> Q: groups of 9 C / 4 threads (16 bytes each) take every `groups`-th record, four loads in
-            // flight; a launch of few images has a record per workgroup and wavefront that worked on one, 128 of them for
-            // a 128 x 128 tile, which cost 71 us when every thread added up its entries one load after the other
-            const int lpr = 9 * C / 4, groups = kHeadThreads / lpr;
-            const int grp = tid / lpr, l = tid - grp * lpr;
-            if (grp < groups) {
-                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-                if (have) sum = sum_lines((const f32x4 *)recs + (n0 + i) * sums.records * lpr + l, lpr, grp, groups, sums_of_image(sums, n0 + i));
-                *(f32x4 *)&Qp[(grp * lpr + l) * 4] = sum;
-            }
-            __syncthreads();
-            for (int r = tid; r < 9 * C; r += kHeadThreads) {
-                float v = 0.f;
-                for (int g2 = 0; g2 < groups; ++g2) v += Qp[g2 * 9 * C + r];
-                Q[i][r] = v;
-            }
-        } else {
-            // lines (C = 64) -> Q: wavefronts 0 .. 3 the whole-tile lines, 4 and 5 the columns, 6 the rows, 7 the
-            // corners; 16 bytes per lane, i.e. four lines per load and four loads in flight
-            const int wave = tid >> 6, lane = tid & 63, l = lane & 15, sub = lane >> 4;
-            const f32x4 *p = (const f32x4 *)recs + (n0 + i) * sums.lines * 16 + l;
-            auto total = [&](int first, int count, int start, int step, float *dst) {
-                f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                if (have) v = sum_lines(p + first * 16, 16, start, step, count);
+        // lines -> Q: wavefronts 0 .. 3 the whole-tile lines, 4 and 5 the columns, 6 the rows, 7 the corners; 16 bytes per
+        // lane, i.e. 256 / C lines per load and four loads in flight
+        constexpr int LPL = C / 4, LPW = 64 / LPL; // lanes per line, lines per wavefront-wide load
+        const int wave = tid >> 6, lane = tid & 63, l = lane % LPL, sub = lane / LPL;
+        const f32x4 *p = (const f32x4 *)recs + (n0 + i) * sums.lines * LPL + l;
+        auto total = [&](int first, int count, int start, int step, float *dst) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (have) v = sum_lines(p + first * LPL, LPL, start, step, count);
 #pragma unroll
-                for (int sh = 16; sh < 64; sh <<= 1)
+            for (int sh = LPL; sh < 64; sh <<= 1)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], sh);
-                if (sub == 0) *(f32x4 *)(dst + 4 * l) = v;
-            };
-            if (wave < 4) total(0, sums.first_col, wave * 4 + sub, 16, &Qp[wave * 64]);
-            else if (wave == 4) total(sums.first_col, sums.last_col - sums.first_col, sub, 4, &Q[i][3 * 64]);
-            else if (wave == 5) total(sums.last_col, sums.rows - sums.last_col, sub, 4, &Q[i][4 * 64]);
-            else if (wave == 6) {
-                const int half = (sums.corners - sums.rows) / 2;
-                total(sums.rows, half, sub, 4, &Q[i][1 * 64]);
-                total(sums.rows + half, half, sub, 4, &Q[i][2 * 64]);
-            } else {
-                *(f32x4 *)&Q[i][(5 + sub) * 64 + 4 * l] = have ? p[(sums.corners + sub) * 16] : (f32x4){0.f, 0.f, 0.f, 0.f};
-            }
-            __syncthreads();
-            if (tid < 64) {
-                Q[i][tid] = (Qp[tid] + Qp[64 + tid]) + (Qp[128 + tid] + Qp[192 + tid]);
-                if (sums.seam) { // the last column was computed apart: it is not in the whole-tile and row lines yet
-                    Q[i][tid] += Q[i][4 * 64 + tid];
-                    Q[i][1 * 64 + tid] += Q[i][6 * 64 + tid];
-                    Q[i][2 * 64 + tid] += Q[i][8 * 64 + tid];
-                }
+                for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], sh);
+            if (sub == 0) *(f32x4 *)(dst + 4 * l) = v;
+        };
+        if (wave < 4) total(0, sums.first_col, wave * LPW + sub, 4 * LPW, &Qp[wave * C]);
+        else if (wave == 4) total(sums.first_col, sums.last_col - sums.first_col, sub, LPW, &Q[i][3 * C]);
+        else if (wave == 5) total(sums.last_col, sums.rows - sums.last_col, sub, LPW, &Q[i][4 * C]);
+        else if (wave == 6) {
+            const int half = (sums.corners - sums.rows) / 2;
+            total(sums.rows, half, sub, LPW, &Q[i][1 * C]);
+            total(sums.rows + half, half, sub, LPW, &Q[i][2 * C]);
+        } else if (sub < 4) {
+            *(f32x4 *)&Q[i][(5 + sub) * C + 4 * l] = have ? p[(sums.corners + sub) * LPL] : (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+        __syncthreads();
+        if (tid < C) {
+            Q[i][tid] = (Qp[tid] + Qp[C + tid]) + (Qp[2 * C + tid] + Qp[3 * C + tid]);
+            if (sums.seam) { // the last column was computed apart: it is not in the whole-tile and row lines yet
+                Q[i][tid] += Q[i][4 * C + tid];
+                Q[i][1 * C + tid] += Q[i][6 * C + tid];
+                Q[i][2 * C + tid] += Q[i][8 * C + tid];
             }
         }
         __syncthreads();
@@ -1827,10 +1797,10 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
 }
 
 // ------------------------------------------------------------------------------------------------
-// pooled -> linear -> logits -> bits -> symbols.  One block per image; its threads share the records of the image
-// (16 bytes each, four loads in flight), which a launch of few images has hundreds of.
+// pooled -> linear -> logits -> bits -> symbols.  One block per image; its threads share the lines of sums of the image
+// (16 bytes each, four loads in flight).
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *__restrict__ partial, LastSums sums, int nbp,
+__global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *__restrict__ partial, int lines, int nbp,
                                                                    int n_bits, float inv_hw, const float *__restrict__ fbias,
                                                                    const float *__restrict__ lin_w,
                                                                    const float *__restrict__ lin_b, float *__restrict__ logits,
@@ -1842,9 +1812,8 @@ __global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *
     __shared__ uint8_t sbit[128];
     const int64_t n = blockIdx.x;
     const int tid = threadIdx.x, o = tid;
-    const int lpr = nbp / 4, groups = kHeadThreads / lpr; // lanes per record
-    *(f32x4 *)&part[tid * 4] = sum_lines((const f32x4 *)partial + n * sums.records * lpr + tid % lpr, lpr, tid / lpr, groups,
-                                         sums_of_image(sums, n));
+    const int lpl = nbp / 4, groups = kHeadThreads / lpl; // lanes per line
+    *(f32x4 *)&part[tid * 4] = sum_lines((const f32x4 *)partial + n * lines * lpl + tid % lpl, lpl, tid / lpl, groups, lines);
     __syncthreads();
     if (o < n_bits) {
         float s = 0.f;
@@ -1918,11 +1887,26 @@ hipError_t launch_conv_first(const TileSrc &src, const ConvGeom &g, int C, const
     return hipGetLastError();
 }
 
+// (the same places in conv_mid_kernel's epilogue)
+LastSums conv_mid_last_sums(const ConvGeom &g, int C)
+{
+    const int row_groups = 2 / (C / 32);
+    LastSums l{};
+    l.first_col = conv_final_lines(g, C);
+    l.last_col = l.first_col + g.strips * row_groups;
+    l.rows = l.last_col + g.strips * row_groups;
+    l.corners = l.rows + 4 * g.colblks;
+    l.lines = l.corners + 4;
+    return l;
+}
+
+int conv_final_lines(const ConvGeom &g, int C) { return g.strips * g.colblks * 2 * (2 / (C / 32)); }
+
 hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, const bf16_t *wfrag,
                            const float *bias, const MeanIn &tin, const float *rsum, float *tout,
                            const Partition &part, bool last, bf16_t *out, hipStream_t s)
 {
-    StatArgs st{tin, rsum, tout, last ? part.slots * part.sub : conv_mid_samples(g, C).recs, part.per, 0.f};
+    StatArgs st{tin, rsum, tout, last ? conv_mid_last_sums(g, C).lines : conv_mid_samples(g, C).recs, part.per, 0.f};
     const dim3 grid(part.blocks), block(64 * kMidWaves);
     if (C == 64) {
         if (last) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_LAST>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, out);
@@ -2050,52 +2034,47 @@ hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n
 {
     if (n_img <= 0) return hipSuccess;
     const unsigned blocks = (unsigned)((n_img + kHeadIpb - 1) / kHeadIpb);
-    hipLaunchKernelGGL(head_kernel, dim3(blocks), dim3(kHeadThreads), 0, s, recs, sums, C, (int)n_img, n_bits, nbp, inv_hw, wft,
-                       fbias, lin_w, lin_b, logits, bits, symbols, m);
+    if (C == 64)
+        hipLaunchKernelGGL(head_kernel<64>, dim3(blocks), dim3(kHeadThreads), 0, s, recs, sums, (int)n_img, n_bits, nbp, inv_hw, wft,
+                           fbias, lin_w, lin_b, logits, bits, symbols, m);
+    else
+        hipLaunchKernelGGL(head_kernel<32>, dim3(blocks), dim3(kHeadThreads), 0, s, recs, sums, (int)n_img, n_bits, nbp, inv_hw, wft,
+                           fbias, lin_w, lin_b, logits, bits, symbols, m);
     return hipGetLastError();
 }
 
-// Strips are dealt to workgroups in contiguous runs of `per` that begin and end anywhere; an image is touched by at most
-// `slots` workgroups.  (Runs that divide an image, or are whole images, left workgroups without work: 16 tiles of
-// 75 x 100, 38 strips each, went to 32 of 256 compute units.)
-Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks, int sub)
+// Strips are dealt to workgroups in contiguous runs of `per` that begin and end anywhere.  (Runs that divide an image, or
+// are whole images, left workgroups without work: 16 tiles of 75 x 100, 38 strips each, went to 32 of 256 compute units.)
+Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks)
 {
     Partition p{};
-    p.sub = sub;
     const int64_t total = n_img * tiles_per_image;
     p.per = (int)std::max<int64_t>(1, (total + target_blocks - 1) / target_blocks);
-    if (p.per % tiles_per_image == 0) p.slots = 1;
-    else if (tiles_per_image % p.per == 0) p.slots = tiles_per_image / p.per;
-    else p.slots = (tiles_per_image + p.per - 2) / p.per + 1;
     p.blocks = (int)((total + p.per - 1) / p.per);
     return p;
 }
 
-size_t last_record_floats(int C) { return (size_t)stat_rec(C); }
-
-int conv_mid_records_per_workgroup(int C) { return kMidWaves / (C / 32); }
-
 Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int C, int nbp)
 {
-    return make_partition(n_img, tiles_per_image, std::max(1, num_cu / (nbp / C)), conv_mid_records_per_workgroup(C));
+    return make_partition(n_img, tiles_per_image, std::max(1, num_cu / (nbp / C)));
 }
 
 hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
                              const float *bias, int relu, float *partial, const Partition &part, hipStream_t s)
 {
-    StatArgs st{MeanIn{}, nullptr, partial, part.slots * part.sub, part.per, relu ? 0.f : __builtin_nanf("")};
+    StatArgs st{MeanIn{}, nullptr, partial, conv_final_lines(g, C), part.per, relu ? 0.f : __builtin_nanf("")};
     const dim3 grid(part.blocks, nbp / C), block(64 * kMidWaves);
     if (C == 64) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
     else hipLaunchKernelGGL((conv_mid_kernel<32, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
     return hipGetLastError();
 }
 
-hipError_t launch_linear_pack(const float *partial, const LastSums &sums, int nbp, int64_t n_img, int n_bits, float inv_hw,
+hipError_t launch_linear_pack(const float *partial, int lines, int nbp, int64_t n_img, int n_bits, float inv_hw,
                               const float *fbias, const float *lin_w, const float *lin_b, float *logits,
                               uint8_t *bits, uint8_t *symbols, int m, hipStream_t s)
 {
     if (n_img <= 0) return hipSuccess;
-    hipLaunchKernelGGL(linear_pack_kernel, dim3((unsigned)n_img), dim3(kHeadThreads), 0, s, partial, sums, nbp, n_bits, inv_hw,
+    hipLaunchKernelGGL(linear_pack_kernel, dim3((unsigned)n_img), dim3(kHeadThreads), 0, s, partial, lines, nbp, n_bits, inv_hw,
                        fbias, lin_w, lin_b, logits, bits, symbols, m);
     return hipGetLastError();
 }

@@ -283,24 +283,18 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
         L.mb = effective_micro_batch(c, N, h, w, act_budget);
         L.act = align_up((size_t)L.mb * h * w * c->C * 2);
         // sized for the fullest micro-batch and for the ragged last one, each for the schedule it runs
-        const int tpi = tiles_per_image(h, w);
         const int64_t counts[2] = {L.mb, L.mb ? N % L.mb : 0};
         for (int64_t cnt : counts) {
             if (cnt <= 0) continue;
             const ConvGeom g{(int)cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
             const bool fused = use_fused(c, (int)cnt, h, w, c->n_blocks);
-            // floats per image that the last convolution leaves for the head
+            // floats per image that the last convolution leaves for the head: it writes no activations, so the buffer those
+            // would go to takes them; only tiles of a few pixels need more than that
             size_t tail;
-            if (!c->collapse) {
-                const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
-                tail = (size_t)pl.slots * pl.sub * c->nbp;
-            } else if (fused && c->n_blocks % 2 == 0) {
-                tail = (size_t)conv_pair_last_sums(g).lines * c->C;
-            } else {
-                const Partition pm = make_partition(cnt, tpi, mid_blocks(c), conv_mid_records_per_workgroup(c->C));
-                tail = (size_t)pm.slots * pm.sub * last_record_floats(c->C);
-            }
-            L.tail = std::max(L.tail, align_up((size_t)cnt * tail * 4));
+            if (!c->collapse) tail = (size_t)conv_final_lines(g, c->C) * c->nbp;
+            else if (fused && c->n_blocks % 2 == 0) tail = (size_t)conv_pair_last_sums(g).lines * c->C;
+            else tail = (size_t)conv_mid_last_sums(g, c->C).lines * c->C;
+            if ((size_t)cnt * tail * 4 > L.act) L.tail = std::max(L.tail, align_up((size_t)cnt * tail * 4));
             const int samples = std::max(c->pairable ? conv_pair_samples(g).recs : 0,
                                          std::max(conv_first_samples(g, c->C).recs, conv_mid_samples(g, c->C).recs));
             L.stats = std::max(L.stats, align_up((size_t)cnt * samples * c->C * 4));
@@ -417,7 +411,8 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
     const size_t buf_off[2] = {kZeroBytes, kZeroBytes + L.act};
     uint8_t *seam = base + kZeroBytes + 2 * L.act + L.tail + 2 * L.stats;
     bf16_t *buf[2] = {(bf16_t *)(base + buf_off[0]), (bf16_t *)(base + buf_off[1])};
-    float *tail = (float *)(base + kZeroBytes + 2 * L.act); // what the last convolution leaves for the head
+    // what the last convolution, which reads buf[reading], leaves for the head
+    auto tail_of = [&](int reading) { return L.tail ? (float *)(base + kZeroBytes + 2 * L.act) : (float *)buf[reading ^ 1]; };
     float *tb[2] = {(float *)(base + kZeroBytes + 2 * L.act + L.tail),
                     (float *)(base + kZeroBytes + 2 * L.act + L.tail + L.stats)};
     const int nsym = (d_symbols && m_sym > 0) ? c->n_bits / m_sym : 0;
@@ -432,12 +427,13 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         const int cnt = (int)((N - n0 < L.mb) ? (N - n0) : L.mb);
         ConvGeom g{cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
         const Partition pf = make_partition(cnt, tpi, first_blocks(c));
-        const Partition pm = make_partition(cnt, tpi, mid_blocks(c), conv_mid_records_per_workgroup(c->C));
+        const Partition pm = make_partition(cnt, tpi, mid_blocks(c));
         src.img = img0 + n0 * 3 * (int64_t)src.H * src.W;
         src.off = off0 ? off0 + 2 * n0 : nullptr;
         int cur = 0, tcur = 0;
         MeanIn means{};         // channel sums the next block reads
-        LastSums last_sums{};   // what the last block has left
+        LastSums last_sums{};   // what the last block has left, and where
+        float *tail = nullptr;
         const int blocks = n_run > 0 ? n_run : c->n_blocks; // blocks to run: the first one and C -> C layers m = b - 1
         // Fused schedule (64 channels; see use_fused): [first + layer 0], (1,2), (3,4), ..; what is left over
         // runs alone.
@@ -447,6 +443,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         if (fused) {
             qrm_ctx::Timed *t = time_begin(c, may_time, is_last(1) ? QRM_PROFILE_PAIR_LAST : QRM_PROFILE_PAIR_FIRST,
                                            (first_flops + block_flops) * cnt, s);
+            tail = tail_of(cur); // (it reads no activations)
             e = launch_conv_pair(base, nullptr, &src, g, c->C, c->d_w_first, c->d_w_mid[0], c->d_bias, c->d_bias + (size_t)c->C, MeanIn{},
                                  nullptr, is_last(1) ? tail : tb[tcur], is_last(1), launch_cu(c), seam, buf[cur], s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_pair (first) launch");
@@ -466,6 +463,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             const bool pair = fused && (m & 1) == 1 && b + 1 < blocks;
             const float *rsum = c->d_rsum + (size_t)m * c->C * c->C;
             means.rec = tb[tcur];
+            tail = tail_of(cur);
             if (pair) {
                 qrm_ctx::Timed *t = time_begin(c, may_time, is_last(b + 1) ? QRM_PROFILE_PAIR_LAST : QRM_PROFILE_PAIR_MID,
                                                2.0 * block_flops * cnt, s);
@@ -483,7 +481,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                                     rsum, is_last(b) ? tail : tb[tcur ^ 1], pm, is_last(b), buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_mid launch");
                 time_end(t, s);
-                if (is_last(b)) last_sums = LastSums{pm.slots * pm.sub, pm.sub, pm.per, tpi, 0, 0, 0, 0, 0, 0};
+                if (is_last(b)) last_sums = conv_mid_last_sums(g, c->C);
                 else means = conv_mid_samples(g, c->C);
             }
             cur ^= 1;
@@ -505,10 +503,11 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {
             const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
+            tail = tail_of(cur);
             e = launch_conv_final(base, buf_off[cur], g, c->C, c->nbp, c->d_w_final, c->final_relu ? c->d_bias_final : nullptr,
                                   c->final_relu, tail, pl, s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_final launch");
-            e = launch_linear_pack(tail, LastSums{pl.slots * pl.sub, pl.sub, pl.per, tpi, 0, 0, 0, 0, 0, 0}, c->nbp, cnt, c->n_bits, inv_hw,
+            e = launch_linear_pack(tail, conv_final_lines(g, c->C), c->nbp, cnt, c->n_bits, inv_hw,
                                    c->final_relu ? nullptr : c->d_bias_final, c->d_lin_w, c->d_lin_b, lg, bt, sy,
                                    m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "linear_pack launch");

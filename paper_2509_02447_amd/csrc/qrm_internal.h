@@ -53,13 +53,9 @@ hipError_t launch_gather_host_tiles(const uint8_t *img, int64_t N, int H, int W,
 // How the tiles of a launch are dealt to workgroups (see make_partition).
 struct Partition {
     int per;    // tiles per workgroup
-    int slots;  // workgroups that touch one image, at most
-    int sub;    // records of nine sums a workgroup writes per image (last block); room per image: slots * sub
     int blocks; // grid size
 };
-Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks, int sub = 1);
-int conv_mid_records_per_workgroup(int C);
-size_t last_record_floats(int C); // floats per record of the last block (nine sums per channel)
+Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks);
 
 // Sampled per-image channel sums of a launch's output, as its consumer reads them.
 struct MeanIn {
@@ -67,14 +63,13 @@ struct MeanIn {
     int recs;         // records per image
     float inv_cnt;    // 1 / pixels of an image behind its records
 };
-// What the last block leaves of an image for the head: room for `records` records of nine sums per channel, `sub` for
-// each workgroup that touched it (workgroups take runs of `per` of the launch's strips, `strips` an image), or (records
-// = 0) `lines` lines of C sums.  Lines 0 .. first_col-1: the whole tile, a line per chunk of row pairs, column block and block
-// of 32 columns; from first_col / last_col on: the first / last column, a line per chunk; from rows on: the first, then
-// the last row, a line per column block and block of 32 columns; from corners on: top left, top right, bottom left,
-// bottom right.  seam: the last column was computed apart and is missing from the whole-tile and the row lines.
+// What the last block leaves of an image for the head: `lines` lines of C sums.  Lines 0 .. first_col-1: the whole tile, a
+// line per piece of its rows, column block and block of 32 columns; from first_col / last_col on: the first / last column, a
+// line per piece; from rows on: the first, then the last row, a line per column block and block of 32 columns; from corners
+// on: top left, top right, bottom left, bottom right.  A piece is kChunk row pairs in the fused kernel, the rows one
+// wavefront finishes at a time in the single-block one.  seam: the last column was computed apart and is missing from the
+// whole-tile and the row lines.
 struct LastSums {
-    int records, sub, per, strips;
     int lines, first_col, last_col, rows, corners, seam;
 };
 MeanIn conv_first_samples(const ConvGeom &g, int C); // (rec null)
@@ -90,8 +85,9 @@ hipError_t launch_conv_first(const TileSrc &src, const ConvGeom &g, int C, const
 // (+ 32-bit offsets inside an image); the first kZeroBytes of ws must be zero: the source of the zero padding.
 // tin / rsum: channel sums of the input and the summed weight-rounding residual [c_in][c_out] used to correct the
 // bias (tin.rec and rsum may be null).  tout: channel sums of the output (conv_mid_samples()).  last: no activations
-// are written, tout receives the nine border-aware sums per channel (LastSums::records).
+// are written, tout receives lines of channel sums (conv_mid_last_sums()).
 constexpr size_t kZeroBytes = 256;
+LastSums conv_mid_last_sums(const ConvGeom &g, int C);
 hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, const bf16_t *wfrag,
                            const float *bias, const MeanIn &tin, const float *rsum, float *tout,
                            const Partition &part, bool last, bf16_t *out, hipStream_t s);
@@ -127,14 +123,16 @@ hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n
                        uint8_t *bits, uint8_t *symbols, int m, hipStream_t s);
 
 // final conv3x3 C -> nbp (n_bits padded to 64s) (+bias, optional ReLU) + sum over pixels -> partial sums
-// partial: f32 [n_img][part.slots * part.sub][nbp]; part: conv_final_partition()
+// partial: f32 [n_img][conv_final_lines()][nbp], each line over a part of the image that does not depend on `part`
+// (conv_final_partition())
+int conv_final_lines(const ConvGeom &g, int C);
 Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int C, int nbp);
 hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
                              const float *bias, int relu, float *partial, const Partition &part, hipStream_t s);
 
 // pooled = sum(partials)/(h*w); logits = lin_w * pooled + lin_b; bits; symbols (MSB first, m bits each)
 // fbias: optional bias of the final convolution, added to the pooled value
-hipError_t launch_linear_pack(const float *partial, const LastSums &sums, int nbp, int64_t n_img, int n_bits, float inv_hw,
+hipError_t launch_linear_pack(const float *partial, int lines, int nbp, int64_t n_img, int n_bits, float inv_hw,
                               const float *fbias, const float *lin_w, const float *lin_b, float *logits, uint8_t *bits,
                               uint8_t *symbols, int m, hipStream_t s);
 

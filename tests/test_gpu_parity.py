@@ -290,6 +290,36 @@ def test_results_do_not_depend_on_the_batch_around_a_tile(qrm, C, nb, h, w, flag
         check_logits(lg[None], ref, what=f"C={C} {h}x{w} flags {flags}")
 
 
+# (channels, blocks, height, width, flags, final ReLU): the last block or the final convolution alone in its launch
+# (single-block schedule), on tiles of a strip or less, ragged in both directions, of several column blocks
+SPLIT_CASES = [(32, 2, 3, 5, 0, 0), (32, 3, 13, 64, 0, 0), (32, 4, 46, 100, 0, 0), (64, 3, 14, 33, 1, 0), (64, 4, 37, 130, 1, 0),
+               (32, 2, 3, 5, 0, 1), (32, 3, 46, 100, 0, 1), (64, 4, 37, 50, 0, 1), (64, 3, 13, 130, 1, 1)]
+
+
+@pytest.mark.parametrize("C,nb,h,w,flags,relu", SPLIT_CASES)
+def test_single_block_logits_do_not_depend_on_the_split(qrm, C, nb, h, w, flags, relu):
+    """The lines of sums that the last launch leaves for the head cover parts of the image that do not depend on how its
+    strips are dealt to workgroups (batch size, compute units lent to an upload): the same bits for a tile alone, in a
+    batch of a few and in one of more tiles than compute units.  Workspaces are filled with NaN first."""
+    wts = small_weights(C, nb, 16, C + nb + h)
+    rng = np.random.default_rng(h * w + C + relu)
+    tile = rng.integers(0, 256, size=(1, 3, h, w), dtype=np.uint8)
+    logits = []
+    for N, at in ((1, 0), (7, 5), (300, 299), (611, 411)):
+        ctx = qrm.Context(weights=wts, final_relu=relu)
+        ctx.qrm_diag_set_flags(flags | qrm.binding.QRM_DIAG_POISON_WORKSPACE)
+        tiles = rng.integers(0, 256, size=(N, 3, h, w), dtype=np.uint8)
+        tiles[at] = tile[0]
+        d_tiles, d_log = dev(tiles), empty((N, 16), torch.float32)
+        ctx.qrm_extractor_forward(d_tiles, N, h, w, d_log, None)
+        torch.cuda.synchronize()
+        logits.append(d_log[at].cpu().numpy())
+        ctx.close()
+    for lg in logits[1:]:
+        assert np.array_equal(lg, logits[0])
+    check_logits(logits[0][None], oracle.extractor_forward(wts, tile, final_relu=relu)[0], what=f"C={C} {h}x{w} relu {relu}")
+
+
 EXT_CASES = [
     ("C1 shape 32x32 c32 b4 60bit", 32, 4, 60, 32, 32, 16),
     ("C2 shape 64x64 c64 b8 48bit", 64, 8, 48, 64, 64, 6),
