@@ -522,7 +522,7 @@ __device__ __forceinline__ void last_lines(const f32x16 (&acc)[RW], const float 
 struct StatArgs {
     MeanIn tin;         // channel sums of the input (rec null: no correction)
     const float *rsum;  // [c_in][c_out] residual-weight sums of this layer (fp32)
-    float *tout;        // lines of sums written by this launch: [n_img][out_recs][C], MODE_FINAL [n_img][out_recs][C * slices]
+    float *tout;        // lines of sums written by this launch: [n_img][out_recs][C], MODE_FINAL [n_img][out_recs][64 * slices]
     int out_recs;       // lines per image
     int per;            // strips per workgroup
     float low;          // MODE_FINAL: lower bound of an output (0: ReLU; NaN: none, fmaxf(v, NaN) is v, also where v is NaN)
@@ -530,7 +530,10 @@ struct StatArgs {
 
 constexpr int MODE_MID = 0;  // write activations, sample channel sums from every eighth strip
 constexpr int MODE_LAST = 1; // last block: no activations, lines of channel sums (LastSums)
-constexpr int MODE_FINAL = 2; // final convolution (C output channels per grid.y slice), summed over the pixels: no activations
+// Final convolution, summed over the pixels: no activations.  64 output channels per grid.y slice whatever C is: slices of 32
+// read the whole input once more for every other one, which took 368 us instead of
+// 269 for 512 tiles of 128 x 128 (32 channels, 48 bits) and 143 instead of 103 for 700 of 64 x 64.
+constexpr int MODE_FINAL = 2;
 
 constexpr int kMidWaves = 8; // wavefronts of a conv_mid workgroup: two groups of four
 
@@ -557,7 +560,8 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                                                                      bf16_t *__restrict__ out)
 {
     typedef MidCfg<C> K;
-    constexpr int RG = 2 / K::NCB;     // row groups among the 4 wavefronts of a group
+    constexpr int NCB = MODE == MODE_FINAL ? 2 : K::NCB, CO = 32 * NCB; // blocks of 32 output channels, output channels
+    constexpr int RG = 2 / NCB;        // row groups among the 4 wavefronts of a group
     constexpr int RW = kRows / RG;     // output rows per wavefront
     constexpr int NSLOT = kMidSlots;
     constexpr int WIN = kRows + 2;     // staged rows one strip reads
@@ -565,20 +569,20 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
     // bias + rounding-residual correction per image, indexed by image mod 4: it is written two phases
     // before the image's first strip is multiplied and read until one phase after its last, and an
     // image may be a single strip
-    __shared__ __attribute__((aligned(16))) float s_init[4][C];
+    __shared__ __attribute__((aligned(16))) float s_init[4][CO];
     __shared__ __attribute__((aligned(16))) float s_mean[kMidWaves][C];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave >> 2, w4 = wave & 3;
     const int px = lane & 31, half = lane >> 5;
-    const int cb = w4 % K::NCB;
-    const int xb = (w4 / K::NCB) & 1;
-    const int rg = w4 / (K::NCB * 2);
+    const int cb = w4 % NCB;
+    const int xb = (w4 / NCB) & 1;
+    const int rg = w4 / (NCB * 2);
 
     bf16x8 Wr[9][K::KC];
-    const int slice = MODE == MODE_FINAL ? blockIdx.y : 0; // C output channels of the launch
-    load_weight_frags<C>(Wr, wfrag, slice * K::NCB + cb, lane);
+    const int slice = MODE == MODE_FINAL ? blockIdx.y : 0; // CO output channels of the launch
+    load_weight_frags<C>(Wr, wfrag, slice * NCB + cb, lane);
 
     const int tpi = g.strips * g.colblks; // tiles per image
     const int total = g.n_img * tpi;
@@ -624,14 +628,14 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                              pin_in_loop(lane), first_row(q), wstart(q), NSLOT);
     };
     // s_init[n & 3][o] = bias[o] + sum_c rsum[c][o] * mean_n[c], by the four wavefronts of one group:
-    // each takes C/4 outputs, its lanes split the sum over c in 64 / (C/4) parts
+    // each takes CO/4 outputs, its lanes split the sum over c in 64 / (CO/4) parts
     auto prepare_init = [&](int n) {
-        constexpr int OPW = C / 4, PARTS = 64 / OPW, CP = C / PARTS;
+        constexpr int OPW = CO / 4, PARTS = 64 / OPW, CP = C / PARTS;
         const int lane = pin_in_loop(tid & 63);
         const int o = w4 * OPW + lane % OPW, part = lane / OPW;
         float d = 0.f;
         const float *rsum = st.rsum;
-        if (st.tin.rec && rsum) {
+        if (MODE != MODE_FINAL && st.tin.rec && rsum) {
             image_means<C>(st.tin, n, s_mean[wave], lane);
 #pragma unroll 4
             for (int k = 0; k < CP; ++k) { // (little unrolling: registers are scarce here)
@@ -641,7 +645,7 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 #pragma unroll
             for (int sh = OPW; sh < 64; sh <<= 1) d += __shfl_xor(d, sh);
         }
-        if (part == 0) s_init[n & 3][o] = (MODE != MODE_FINAL || bias ? bias[slice * C + o] : 0.f) + d;
+        if (part == 0) s_init[n & 3][o] = (MODE != MODE_FINAL || bias ? bias[slice * CO + o] : 0.f) + d;
     };
     f32x16 acc[RW];
     const int sample_phase = sampled_strip(g.strips); // strips 3, 11, 19, .. are sampled (the last one of a short tile)
@@ -687,7 +691,7 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
             column_sums<RW>(t, acc, si, st.low, x < g.w, yw, g.h);
             const float sum = reduce16_over_half(t, px); // one channel per lane
             const int line = (q.colblk * g.strips + strip) * (2 * RG) + piece;
-            float *rec = st.tout + (((int64_t)n * st.out_recs + line) * gridDim.y + slice) * C;
+            float *rec = st.tout + (((int64_t)n * st.out_recs + line) * gridDim.y + slice) * CO;
             if ((px & 1) == 0) rec[cb * 32 + half * 16 + reduce16_index(px)] = sum;
         } else if (st.tout) {
             float *lines = st.tout + (int64_t)n * st.out_recs * C + cb * 32 + half * 16;
@@ -1892,7 +1896,7 @@ LastSums conv_mid_last_sums(const ConvGeom &g, int C)
 {
     const int row_groups = 2 / (C / 32);
     LastSums l{};
-    l.first_col = conv_final_lines(g, C);
+    l.first_col = g.strips * g.colblks * 2 * row_groups;
     l.last_col = l.first_col + g.strips * row_groups;
     l.rows = l.last_col + g.strips * row_groups;
     l.corners = l.rows + 4 * g.colblks;
@@ -1900,7 +1904,7 @@ LastSums conv_mid_last_sums(const ConvGeom &g, int C)
     return l;
 }
 
-int conv_final_lines(const ConvGeom &g, int C) { return g.strips * g.colblks * 2 * (2 / (C / 32)); }
+int conv_final_lines(const ConvGeom &g) { return g.strips * g.colblks * 2; }
 
 hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, const bf16_t *wfrag,
                            const float *bias, const MeanIn &tin, const float *rsum, float *tout,
@@ -2054,16 +2058,16 @@ Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks)
     return p;
 }
 
-Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int C, int nbp)
+Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int nbp)
 {
-    return make_partition(n_img, tiles_per_image, std::max(1, num_cu / (nbp / C)));
+    return make_partition(n_img, tiles_per_image, std::max(1, num_cu / (nbp / 64)));
 }
 
 hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
                              const float *bias, int relu, float *partial, const Partition &part, hipStream_t s)
 {
-    StatArgs st{MeanIn{}, nullptr, partial, conv_final_lines(g, C), part.per, relu ? 0.f : __builtin_nanf("")};
-    const dim3 grid(part.blocks, nbp / C), block(64 * kMidWaves);
+    StatArgs st{MeanIn{}, nullptr, partial, conv_final_lines(g), part.per, relu ? 0.f : __builtin_nanf("")};
+    const dim3 grid(part.blocks, nbp / 64), block(64 * kMidWaves);
     if (C == 64) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
     else hipLaunchKernelGGL((conv_mid_kernel<32, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
     return hipGetLastError();

@@ -291,7 +291,7 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
             // floats per image that the last convolution leaves for the head: it writes no activations, so the buffer those
             // would go to takes them; only tiles of a few pixels need more than that
             size_t tail;
-            if (!c->collapse) tail = (size_t)conv_final_lines(g, c->C) * c->nbp;
+            if (!c->collapse) tail = (size_t)conv_final_lines(g) * c->nbp;
             else if (fused && c->n_blocks % 2 == 0) tail = (size_t)conv_pair_last_sums(g).lines * c->C;
             else tail = (size_t)conv_mid_last_sums(g, c->C).lines * c->C;
             if ((size_t)cnt * tail * 4 > L.act) L.tail = std::max(L.tail, align_up((size_t)cnt * tail * 4));
@@ -502,12 +502,12 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                             c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {
-            const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
+            const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->nbp);
             tail = tail_of(cur);
             e = launch_conv_final(base, buf_off[cur], g, c->C, c->nbp, c->d_w_final, c->final_relu ? c->d_bias_final : nullptr,
                                   c->final_relu, tail, pl, s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_final launch");
-            e = launch_linear_pack(tail, conv_final_lines(g, c->C), c->nbp, cnt, c->n_bits, inv_hw,
+            e = launch_linear_pack(tail, conv_final_lines(g), c->nbp, cnt, c->n_bits, inv_hw,
                                    c->final_relu ? nullptr : c->d_bias_final, c->d_lin_w, c->d_lin_b, lg, bt, sy,
                                    m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "linear_pack launch");
