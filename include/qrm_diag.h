@@ -48,6 +48,13 @@ QRM_API qrm_status qrm_diag_matrix_rate(qrm_ctx *ctx, int32_t data, double *tflo
 QRM_API qrm_status qrm_diag_pair_split(int32_t n_img, int32_t h, int32_t w, int32_t last, int32_t num_cu, int32_t *part,
                                        int32_t *per, int32_t *cost);
 
+/*
+ * The schedule of n_img tiles of h x w, w > 64, on num_cu compute units (64 channels): *fused = 1 two blocks per launch,
+ * 0 one; *single_us / *fused_us: what eight blocks are estimated to take either way.  Host code, no device needed.
+ */
+QRM_API qrm_status qrm_diag_wide_schedule(int32_t n_img, int32_t h, int32_t w, int32_t num_cu, int32_t *fused,
+                                          double *single_us, double *fused_us);
+
 #ifdef __cplusplus
 }
 #endif

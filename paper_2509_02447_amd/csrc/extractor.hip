@@ -1985,6 +1985,24 @@ PairSplit conv_pair_split(const ConvGeom &g, bool last, int num_cu)
     return p;
 }
 
+// Microseconds of eight blocks on tiles of more than one column block, either schedule.  Single blocks: a launch deals strips
+// evenly, its workgroups pay for each strip, for the extra rows a column of strips begins with, and for the activations of
+// every block; fused: a run's halo and opening positions (pair_cost), a launch for the last column of widths that are multiples
+// of 64, half the activations.  Fitted to 231 shapes of 128 .. 700 tiles, 4 .. 44 rows, 66 .. 256 columns with fewer than 12 row
+// pairs per compute unit (standard deviation 3.5 and 2.6 %): the faster way by the estimates is 4 % slower than the other at
+// most.  Measured, single / fused: 256 tiles of 8 x 100 191 / 144 us, 256 of 20 x 200 621 / 540, 200 of 30 x 200 741 / 681;
+// 128 of 24 x 66 203 / 216, 160 of 20 x 128 254 / 265.
+WideCost conv_wide_cost(const ConvGeom &g, int num_cu)
+{
+    const int64_t strips = (int64_t)g.n_img * g.strips * g.colblks;
+    const double per = (double)((strips + num_cu - 1) / num_cu), mpx = 1e-6 * g.n_img * g.h * g.w;
+    WideCost c{};
+    c.single_us = 66.2 + 16.1 * per + 6.8 * per / g.strips + 174.0 * mpx;
+    c.fused_us = 31.5 + 0.218 * (3 * conv_pair_split(g, false, num_cu).cost + conv_pair_split(g, true, num_cu).cost) +
+                 (g.w % kTileW == 0 ? 14.5 : 0.0) + 71.6 * mpx;
+    return c;
+}
+
 template <bool FIRST, bool LASTB, bool PART>
 static void launch_pair_variant(bool wide, dim3 grid, hipStream_t s, const uint8_t *zeros, const uint8_t *in, const TileSrc &src,
                                 const ConvGeom &g, const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a,

@@ -244,17 +244,12 @@ int default_micro_batch(const qrm_ctx *c, int h, int w)
 }
 
 // Whether a launch of cnt images of h x w runs the fused schedule (two blocks per launch).  Narrow tiles always
-// do (1.04 .. 1.3 times as fast at 1 .. 400 tiles of 16 x 64 .. 64 x 64).  On wide tiles a workgroup's run of row pairs costs three
-// steps more per column block than it has row pairs, the single-block kernel's run of strips costs none: fused is 0.45 ..
-// 0.85 times as fast below two row pairs per compute unit, 0.92 .. 1.03 at four to ten, 0.97 .. 1.08 at 12 to 16 and 1.06 ..
-// 1.10 from 25 on (75 x 100, 96 x 96, 128 x 128, 256 x 256, 32 x 200, 200 x 66; eight blocks).  The single-block schedule also
-// corrects the bias of every block, not of every other one (logits within 1.3 .. 4.4e-4 of the exact ones against 2.7 .. 5.5e-4):
-// batches of fewer images than half the compute units keep it, at a cost of up to 10 %.
+// do (1.04 .. 1.3 times as fast at 1 .. 400 tiles of 16 x 64 .. 64 x 64).
 bool use_fused(const qrm_ctx *c, int cnt, int h, int w, int blocks)
 {
     if ((c->diag_flags & QRM_DIAG_NO_FUSED_PAIRS) || !c->pairable || blocks < 2) return false;
     if (w <= kTileW || (c->diag_flags & QRM_DIAG_FUSE_ALWAYS)) return true;
-    return 2 * cnt >= c->num_cu && (int64_t)cnt * ((h + 1) / 2) >= 12 * (int64_t)c->num_cu;
+    return wide_tiles_fused(ConvGeom{cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW}, c->num_cu);
 }
 
 int effective_micro_batch(const qrm_ctx *c, int64_t N, int h, int w, size_t act_budget)
@@ -275,6 +270,19 @@ int mid_blocks(const qrm_ctx *c) { return launch_cu(c); } // one persistent work
 } // namespace
 
 namespace qrm {
+
+// Few images: the single-block schedule, whose runs of strips cost nothing extra (fused is 0.45 .. 0.85 times as fast below two
+// row pairs per compute unit) and which corrects the bias of every block, not of every other one (logits within 1.3 .. 4.4e-4
+// of the exact ones against 2.7 .. 5.5e-4): batches of fewer images than half the compute units keep it, at a cost of up to
+// 10 %.  From 12 row pairs per compute unit on the fused one is 0.97 .. 1.08 times as fast, from 25 on 1.06 .. 1.10 (75 x 100, 96 x
+// 96, 128 x 128, 256 x 256, 32 x 200, 200 x 66; eight blocks); in between the estimates decide.
+bool wide_tiles_fused(const ConvGeom &g, int num_cu)
+{
+    if (2 * g.n_img < num_cu) return false;
+    if ((int64_t)g.n_img * ((g.h + 1) / 2) >= 12 * (int64_t)num_cu) return true;
+    const WideCost c = conv_wide_cost(g, num_cu);
+    return c.fused_us < c.single_us;
+}
 
 WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols, size_t act_budget)
 {

@@ -112,4 +112,16 @@ qrm_status qrm_diag_pair_split(int32_t n_img, int32_t h, int32_t w, int32_t last
     return QRM_OK;
 }
 
+qrm_status qrm_diag_wide_schedule(int32_t n_img, int32_t h, int32_t w, int32_t num_cu, int32_t *fused, double *single_us,
+                                  double *fused_us)
+{
+    if (n_img < 1 || h < 1 || w <= kTileW || num_cu < 1 || !fused || !single_us || !fused_us) return QRM_E_INVALID;
+    const ConvGeom g{n_img, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
+    const WideCost c = conv_wide_cost(g, num_cu);
+    *fused = wide_tiles_fused(g, num_cu);
+    *single_us = c.single_us;
+    *fused_us = c.fused_us;
+    return QRM_OK;
+}
+
 } // extern "C"

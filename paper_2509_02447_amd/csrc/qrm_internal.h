@@ -108,6 +108,12 @@ struct PairSplit {
     int workgroups;
     int cost;       // of the longest workgroup (pair_cost)
 };
+struct WideCost {
+    double single_us, fused_us; // estimates for eight blocks
+};
+WideCost conv_wide_cost(const ConvGeom &g, int num_cu);
+// Whether tiles wider than one column block run the fused schedule.
+bool wide_tiles_fused(const ConvGeom &g, int num_cu);
 PairSplit conv_pair_split(const ConvGeom &g, bool last, int num_cu);
 LastSums conv_pair_last_sums(const ConvGeom &g);
 size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu);
