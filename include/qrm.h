@@ -313,8 +313,9 @@ QRM_API qrm_status qrm_plan_streams(int32_t n_stages, const double *h_t, const d
  * h_chunks: n_chunks HOST pointers, each to u8 [chunk_images,3,H,W]; the same buffer may appear more
  * than once (a caller that refills a few buffers round-robin).  For copies that overlap with kernels
  * the buffers must be page-locked (hipHostMalloc); pageable memory works but serialises.  When every
- * chunk is page-locked and the tiles are a small part of the images, only the tiles cross the link: a
- * kernel reads their rows out of host memory (a staging buffer is then chunk_images * 3*tile*tile bytes).
+ * chunk is page-locked and the tiles are a small part of the images, a kernel reads the tiles' rows out of
+ * host memory and only those cross the link: for the first chunk, and for all of them where copies would
+ * take longer than the kernels (a staging buffer is then chunk_images * 3*tile*tile bytes).
  * h_off_chunks: n_chunks HOST pointers to i32 [chunk_images,2], or NULL (= origin 0,0 everywhere).
  * h_msg u8 [n_chunks*chunk_images,k]; h_codeword u8 [n_chunks*chunk_images,n] or NULL;
  * h_nerr i8 [n_chunks*chunk_images]: HOST buffers, chunk after chunk.

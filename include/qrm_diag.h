@@ -55,6 +55,14 @@ QRM_API qrm_status qrm_diag_pair_split(int32_t n_img, int32_t h, int32_t w, int3
 QRM_API qrm_status qrm_diag_wide_schedule(int32_t n_img, int32_t h, int32_t w, int32_t num_cu, int32_t *fused,
                                           double *single_us, double *fused_us);
 
+/*
+ * How qrm_detect_host brings its chunks in (page-locked images of H x W, a network of `channels` and n_blocks without a
+ * final ReLU, `used` staging buffers in use): *first / *rest = 1 the first / the later chunks as tiles, 0 as whole images;
+ * *lent = compute units the kernels leave to the gather of the next chunk.  Host code, no device needed.
+ */
+QRM_API qrm_status qrm_diag_host_plan(int32_t channels, int32_t n_blocks, int32_t H, int32_t W, int32_t tile, int32_t chunk_images,
+                                      int32_t used, int32_t num_cu, int32_t *first, int32_t *rest, int32_t *lent);
+
 #ifdef __cplusplus
 }
 #endif

@@ -1111,28 +1111,23 @@ qrm_status qrm_detect_host(qrm_ctx *c, const uint8_t *const *h_chunks, int32_t n
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
 
-    // Chunks whose tiles are a small part of the images come as tiles (see launch_gather_host_tiles), when every chunk
-    // lies in memory a kernel can read.
+    // Which chunks come as tiles (see plan_host_upload), if every chunk lies in memory a kernel can read.
     const size_t chunk_bytes = (size_t)chunk_images * 3 * H * W;
+    const int used = depth < n_chunks ? depth : n_chunks;
+    HostPlan plan = plan_host_upload(c->C, c->n_blocks, c->collapse ? 0 : c->nbp / 64, H, W, tile, chunk_images, used, c->num_cu);
     std::vector<const uint8_t *> d_chunks;
-    bool gather = gather_host_tiles_pays(H, W, tile);
-    for (int i = 0; gather && i < n_chunks; ++i) {
+    for (int i = 0; plan.first && i < n_chunks; ++i) {
         const uint8_t *p = host_chunk_on_device(h_chunks[i], chunk_bytes);
         if (p) d_chunks.push_back(p);
-        else gather = false;
+        else plan = HostPlan{};
     }
-    // The gather of a chunk runs beside the kernels of the chunk before (with one staging buffer, or one chunk, beside
-    // nothing), which then leave it its compute units: a persistent workgroup that found none free would double the
-    // time of its launch.
-    const int used = depth < n_chunks ? depth : n_chunks;
-    const bool beside = gather && used > 1 && c->num_cu >= 64;
-    const int gather_wgs = beside ? gather_host_tiles_workgroups(tile, 18.0 * c->C * c->C * (c->n_blocks - 1) * tile * tile) : 32;
-    struct Lend {
+    struct Lend { // (a persistent workgroup that found no free compute unit would double the time of its launch)
         qrm_ctx *c;
         ~Lend() { c->lent_cu = 0; }
     } lend{c};
-    if (beside) c->lent_cu = gather_wgs;
-    const size_t img_bytes = gather ? (size_t)chunk_images * 3 * tile * tile : chunk_bytes, off_bytes = (size_t)chunk_images * 2 * sizeof(int32_t);
+    c->lent_cu = plan.lent_cu;
+    const size_t img_bytes = plan.rest ? (size_t)chunk_images * 3 * tile * tile : chunk_bytes;
+    const size_t off_bytes = (size_t)chunk_images * 2 * sizeof(int32_t);
     const int k = c->rs.k, n = c->rs.n;
     const size_t msg_bytes = (size_t)chunk_images * k, cw_bytes = (size_t)chunk_images * n;
     const size_t out_bytes = msg_bytes + cw_bytes + (size_t)chunk_images;
@@ -1195,6 +1190,7 @@ qrm_status qrm_detect_host(qrm_ctx *c, const uint8_t *const *h_chunks, int32_t n
         qrm_ctx::Stage &sg = c->stages[i % used];
         uint8_t *d_msg = sg.d_out, *d_cw = sg.d_out + msg_bytes;
         int8_t *d_ne = (int8_t *)(sg.d_out + msg_bytes + cw_bytes);
+        const bool gather = i == 0 ? plan.first : plan.rest;
         e = hipSuccess;
         if (i >= used) e = hipStreamWaitEvent(c->s_up, sg.computed, 0); // the kernels of chunk i - depth have read d_img
         mark(i, 0, c->s_up);
@@ -1202,7 +1198,7 @@ qrm_status qrm_detect_host(qrm_ctx *c, const uint8_t *const *h_chunks, int32_t n
             e = hipMemcpyAsync(sg.d_off, h_off_chunks[i], off_bytes, hipMemcpyHostToDevice, c->s_up);
         if (e == hipSuccess && gather)
             e = launch_gather_host_tiles(d_chunks[i], chunk_images, H, W, h_off_chunks ? sg.d_off : nullptr, tile, sg.d_img,
-                                         i == 0 ? 32 : gather_wgs, c->s_up);
+                                         i == 0 ? plan.first_workgroups : plan.rest_workgroups, c->s_up);
         else if (e == hipSuccess)
             e = hipMemcpyAsync(sg.d_img, h_chunks[i], img_bytes, hipMemcpyHostToDevice, c->s_up);
         if (e == hipSuccess) e = hipEventRecord(sg.uploaded, c->s_up);

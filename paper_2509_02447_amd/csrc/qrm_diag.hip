@@ -124,4 +124,17 @@ qrm_status qrm_diag_wide_schedule(int32_t n_img, int32_t h, int32_t w, int32_t n
     return QRM_OK;
 }
 
+qrm_status qrm_diag_host_plan(int32_t channels, int32_t n_blocks, int32_t H, int32_t W, int32_t tile, int32_t chunk_images,
+                              int32_t used, int32_t num_cu, int32_t *first, int32_t *rest, int32_t *lent)
+{
+    if ((channels != 32 && channels != 64) || n_blocks < 1 || tile < 1 || tile > H || tile > W || chunk_images < 1 || used < 1 ||
+        num_cu < 1 || !first || !rest || !lent)
+        return QRM_E_INVALID;
+    const HostPlan p = plan_host_upload(channels, n_blocks, 0, H, W, tile, chunk_images, used, num_cu);
+    *first = p.first;
+    *rest = p.rest;
+    *lent = p.lent_cu;
+    return QRM_OK;
+}
+
 } // extern "C"

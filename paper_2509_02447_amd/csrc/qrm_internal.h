@@ -42,13 +42,18 @@ struct TileSrc {
 hipError_t launch_extract_tiles(const uint8_t *img, int64_t N, int H, int W, const int32_t *off, int tile,
                                 uint8_t *out, hipStream_t s);
 
-// The same crops out of images in page-locked host memory the device can read (img: its device address), and whether
-// that beats copying the images.  workgroups: compute units it takes; gather_host_tiles_workgroups(): how many of them
-// when tiles that take `flops` of work each are being worked on at the same time.
-bool gather_host_tiles_pays(int H, int W, int tile);
-int gather_host_tiles_workgroups(int tile, double flops);
+// The same crops out of images in page-locked host memory the device can read (img: its device address), on `workgroups`
+// compute units.
 hipError_t launch_gather_host_tiles(const uint8_t *img, int64_t N, int H, int W, const int32_t *off, int tile, uint8_t *out,
                                     int workgroups, hipStream_t s);
+// Which chunks of a streamed pass come as tiles that way and which as whole images: the first one (nothing runs beside its
+// upload), the rest; on how many compute units, and how many of those the kernels that run beside it leave free.
+// final_slices: groups of 64 output channels of a final convolution that runs per pixel; used: staging buffers in use.
+struct HostPlan {
+    bool first, rest;
+    int first_workgroups, rest_workgroups, lent_cu;
+};
+HostPlan plan_host_upload(int C, int n_blocks, int final_slices, int H, int W, int tile, int chunk_images, int used, int num_cu);
 
 // How the tiles of a launch are dealt to workgroups (see make_partition).
 struct Partition {

@@ -470,18 +470,32 @@ hipError_t launch_select_tiles_variance(const uint8_t *img, int64_t N, int H, in
     return hipGetLastError();
 }
 
-bool gather_host_tiles_pays(int H, int W, int tile)
+HostPlan plan_host_upload(int C, int n_blocks, int final_slices, int H, int W, int tile, int chunk_images, int used, int num_cu)
 {
-    // bytes a tile's rows touch on average, in pieces of 64, against the image's: 64 x 64 tiles of 256 x 256 images 0.12 (0.63 ms
+    HostPlan p{};
+    p.first_workgroups = 32;
+    // Bytes a tile's rows touch on average, in pieces of 64, against the image's: 64 x 64 tiles of 256 x 256 images 0.12 (0.63 ms
     // for 1024 against 3.52 for the copy), 128: 0.37 (1.75), 192: 0.75 (2.66), 256: 1.2 (3.50).  The copy needs no compute units:
     // the gather has to halve the bytes.
-    return 2 * (int64_t)tile * (tile + 63) <= (int64_t)H * W;
-}
-
-int gather_host_tiles_workgroups(int tile, double flops)
-{
-    // 8 or 16 (figures above): 8 where the tile's own work on the rest of the chip takes longer than they do
-    return flops / 1.2e15 > 3.0 * tile * 5.5e-9 ? 8 : 16;
+    if (2 * (int64_t)tile * (tile + 63) > (int64_t)H * W) return p;
+    p.first = true; // nothing runs beside it
+    if (used < 2) {
+        p.rest = true;
+        p.rest_workgroups = p.first_workgroups;
+        return p;
+    }
+    // The gather of a later chunk runs beside the kernels of the chunk before, which leave it its compute units and take 1.07 ..
+    // 1.16 times as long for it: it is worth having only where the copy takes longer than that, i.e. where the link is the
+    // bound.  (24 chunks of 1024 images of 256 x 256, milliseconds a chunk, kernels alone / beside a gather / copy: tiles of
+    // 64 1.7 / 1.98 / 3.5, of 80 4.2 / 4.5 / 3.5, of 96 5.3 / 5.7 / 3.5, of 128 7.3 / 8.4 / 3.5.)  The estimate: picoseconds per block and
+    // pixel of the tiles' column blocks, 57 GB/s.
+    const double columns = 64.0 * ((tile + 63) / 64);
+    const double tile_s = tile * columns * 1e-12 * (n_blocks * (C == 64 ? 50.0 : 26.0) + final_slices * (C == 64 ? 50.0 : 32.0));
+    p.rest = num_cu >= 64 && 1.1 * tile_s * chunk_images < 3.0 * H * W * chunk_images / 57e9;
+    // 8 or 16 workgroups (figures above): 8 where the work on a tile's own pixels takes longer than they do.  (On the column
+    // blocks tiles of 32 would get 8 as well: 6 chunks of 1024 5.84 ms instead of 5.53 with 16.)
+    if (p.rest) p.rest_workgroups = p.lent_cu = tile_s * tile / columns > 3.0 * tile * 5.5e-9 ? 8 : 16;
+    return p;
 }
 
 hipError_t launch_gather_host_tiles(const uint8_t *img, int64_t N, int H, int W, const int32_t *off, int tile, uint8_t *out,

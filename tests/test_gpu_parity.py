@@ -3,6 +3,7 @@
 Bit-exact for tile crops, symbols and Reed-Solomon outputs; extractor logits within
 2e-2 * max(1, |ref|) and hard bits equal wherever |oracle logit| > 1e-2.
 """
+import ctypes as C
 import os
 from fractions import Fraction
 
@@ -939,6 +940,38 @@ def test_detect_host_tiles_read_from_host_memory(qrm, H, W, tile):
                                     depth, h_msg, h_cw, h_ne)
                 assert np.array_equal(h_msg.numpy(), msg.cpu().numpy()) and np.array_equal(h_cw.numpy(), cw.cpu().numpy())
                 assert np.array_equal(h_ne.numpy(), ne.cpu().numpy())
+    ctx.close()
+
+
+def test_detect_host_first_chunk_as_tiles_the_rest_as_images(qrm):
+    """Kernels that take longer than the copies: the first chunk's tiles are read out of host memory, later chunks are copied
+    whole into the same staging buffers; all as qrm_detect on the same images in device memory, whatever the depth."""
+    H, W, tile, chunk, n_chunks = 200, 223, 68, 5, 4
+    first, rest, lent = C.c_int32(), C.c_int32(), C.c_int32()
+    assert qrm.binding.load_library().qrm_diag_host_plan(64, 8, H, W, tile, chunk, 2, 256, C.byref(first), C.byref(rest), C.byref(lent)) == 0
+    assert (first.value, rest.value, lent.value) == (1, 0, 0)
+    wts = small_weights(64, 8, 60, tile)
+    n = chunk * n_chunks
+    imgs = np.random.default_rng(tile).integers(0, 256, size=(n, 3, H, W), dtype=np.uint8)
+    off = np.random.default_rng(W).integers(-9, H + 9, size=(n, 2), dtype=np.int32)
+    ctx = qrm.Context(weights=wts, rs=dict(m=4, prim_poly=0x13, n=15, k=11, fcr=1))
+    pinned = torch.empty((n, 3, H, W), dtype=torch.uint8, pin_memory=True).copy_(torch.from_numpy(imgs))
+    offs = torch.empty((n, 2), dtype=torch.int32, pin_memory=True).copy_(torch.from_numpy(off))
+    want = [[], [], []]
+    for i in range(n_chunks):
+        msg, cw, ne = empty((chunk, 11), torch.uint8), empty((chunk, 15), torch.uint8), empty((chunk,), torch.int8)
+        ctx.qrm_detect(dev(imgs[i * chunk:(i + 1) * chunk]), chunk, H, W, dev(off[i * chunk:(i + 1) * chunk]), tile, None, None, msg, cw, ne)
+        torch.cuda.synchronize()
+        for w, t in zip(want, (msg, cw, ne)):
+            w.append(t.cpu().numpy())
+    for depth in (2, 3, 1):
+        h_msg = torch.zeros((n, 11), dtype=torch.uint8, pin_memory=True)
+        h_cw = torch.zeros((n, 15), dtype=torch.uint8, pin_memory=True)
+        h_ne = torch.zeros((n,), dtype=torch.int8, pin_memory=True)
+        ctx.qrm_detect_host([pinned[i * chunk:(i + 1) * chunk] for i in range(n_chunks)], chunk, H, W,
+                            [offs[i * chunk:(i + 1) * chunk] for i in range(n_chunks)], tile, depth, h_msg, h_cw, h_ne)
+        for w, t in zip(want, (h_msg, h_cw, h_ne)):
+            assert np.array_equal(np.concatenate(w), t.numpy())
     ctx.close()
 
 
