@@ -63,6 +63,9 @@ QRM_API qrm_status qrm_diag_wide_schedule(int32_t n_img, int32_t h, int32_t w, i
 QRM_API qrm_status qrm_diag_host_plan(int32_t channels, int32_t n_blocks, int32_t H, int32_t W, int32_t tile, int32_t chunk_images,
                                       int32_t used, int32_t num_cu, int32_t *first, int32_t *rest, int32_t *lent);
 
+/* How many strips (workgroups) qrm_preprocess cuts each of N windows of T x T into.  Host code, no device needed. */
+QRM_API qrm_status qrm_diag_preprocess_strips(int64_t N, int32_t T, int32_t *strips);
+
 #ifdef __cplusplus
 }
 #endif

@@ -137,4 +137,11 @@ qrm_status qrm_diag_host_plan(int32_t channels, int32_t n_blocks, int32_t H, int
     return QRM_OK;
 }
 
+qrm_status qrm_diag_preprocess_strips(int64_t N, int32_t T, int32_t *strips)
+{
+    if (N < 1 || T < 1 || !strips) return QRM_E_INVALID;
+    *strips = preprocess_strips(N, T, T % 4 == 0);
+    return QRM_OK;
+}
+
 } // extern "C"

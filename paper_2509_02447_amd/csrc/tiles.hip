@@ -404,6 +404,20 @@ bool preprocess_supported(int H_in, int W_in, int x, int T)
            (int64_t)2 * std::max(Hr, Wr) * 2048 < (1LL << 31);
 }
 
+// Strips a T x T window is cut into when a launch has N of them.  Enough workgroups for the chip several times over (six fit
+// a compute unit), so that no last wave of them is nearly empty: 600 images of 480 x 640 to 256 x 256 take 153 us in 3
+// strips an image (1.2 waves), 144 in 6, 139 in 13, the same from there on.  But a strip's column taps are its own, so
+// beyond one wave a strip keeps four turns of 256 pixel groups: 1024 tiles of 64 x 64 out of 512 x 512 images 12.0 us in 1
+// to 4 strips, 15.2 in 8; 3000 of 30 x 30 10.6 in one, 12.1 in two.
+int preprocess_strips(int64_t N, int T, bool vec)
+{
+    const int64_t turns = (int64_t)T * (vec ? T / 4 : T) / 256;
+    const int64_t one_wave = 2048 / N, several = std::min<int64_t>(8192 / N, turns / 4);
+    const int strips = (int)std::min<int64_t>((T + 7) / 8, std::max<int64_t>(1, std::max(one_wave, several)));
+    const int rows = (T + strips - 1) / strips;
+    return (T + rows - 1) / rows;
+}
+
 hipError_t launch_preprocess(const uint8_t *raw, int64_t N, int H_in, int W_in, int x, const int32_t *off, int T,
                              uint8_t *out, hipStream_t s)
 {
@@ -415,12 +429,8 @@ hipError_t launch_preprocess(const uint8_t *raw, int64_t N, int H_in, int W_in, 
     a.cx = (a.Wr - x) / 2;
     const bool vec = T % 4 == 0 && ((uintptr_t)out & 3u) == 0;
     const int64_t kMaxGrid = 1LL << 30;
-    // Enough workgroups for the chip several times over (six fit a compute unit), so that no last wave of them is nearly
-    // empty: 600 images of 480 x 640 to 256 x 256 take 158 us in 3 strips an image (1.2 waves), 149 in 6, 144 in 13, the
-    // same from there on; one strip once there are as many images, as the column taps are computed per strip.
-    int strips = (int)std::min<int64_t>((T + 7) / 8, std::max<int64_t>(1, 8192 / N));
+    const int strips = preprocess_strips(N, T, vec);
     a.rows_per_block = (T + strips - 1) / strips;
-    strips = (T + a.rows_per_block - 1) / a.rows_per_block;
     for (int64_t n0 = 0; n0 < N; n0 += kMaxGrid) {
         const int64_t cnt = N - n0 < kMaxGrid ? N - n0 : kMaxGrid;
         const uint8_t *raw0 = raw + n0 * (int64_t)H_in * W_in * 3;

@@ -37,3 +37,26 @@ def test_small_devices_lend_nothing():
     for num_cu in (32, 63):
         assert plan(64, 8, 256, 256, 64, 3, num_cu) == (1, 0, 0) and plan(64, 8, 256, 256, 64, 1, num_cu) == (1, 1, 0)
     assert plan(64, 8, 256, 256, 64, 3, 64)[1] == 1
+
+
+def strips(N, T):
+    from paper_2509_02447_amd import binding as b
+    got = C.c_int32()
+    assert b.load_library().qrm_diag_preprocess_strips(N, T, C.byref(got)) == 0
+    return got.value
+
+
+def test_small_windows_are_not_cut_for_more_than_one_wave():
+    """Where cutting further was measured slower: 1024 windows of 64 (2 strips 12.0 us, 8 15.2), 3000 of 30 (1 strip 10.6 us, 2 12.1)."""
+    for N, T in ((1024, 64), (3000, 30), (3000, 48), (1000, 32), (2048, 64), (5000, 17)):
+        assert strips(N, T) <= max(1, 2048 // N), (N, T)
+
+
+def test_large_windows_get_several_waves_of_strips():
+    for N, T, least in ((600, 256, 12), (300, 256, 14), (700, 256, 10), (150, 384, 24), (1, 256, 32), (20000, 32, 1)):
+        assert least <= strips(N, T) <= (T + 7) // 8, (N, T)
+    for N in (1, 7, 255, 256, 300, 1024, 2047, 2048, 2049, 8192, 8193, 1 << 31):      # no strip is empty
+        for T in (1, 2, 3, 4, 7, 8, 9, 17, 31, 32, 33, 100, 255, 256, 1000, 1024):
+            c = strips(N, T)
+            rows = -(-T // c)
+            assert 1 <= c <= (T + 7) // 8 and (c - 1) * rows < T <= c * rows, (N, T)
