@@ -66,6 +66,9 @@ QRM_API qrm_status qrm_diag_host_plan(int32_t channels, int32_t n_blocks, int32_
 /* How many strips (workgroups) qrm_preprocess cuts each of N windows of T x T into.  Host code, no device needed. */
 QRM_API qrm_status qrm_diag_preprocess_strips(int64_t N, int32_t T, int32_t *strips);
 
+/* Lanes that decode one word of a code (n symbols, k of them message) in a launch of N words.  Host code, no device needed. */
+QRM_API qrm_status qrm_diag_rs_lanes(int32_t n, int32_t k, int64_t N, int32_t *lanes);
+
 #ifdef __cplusplus
 }
 #endif

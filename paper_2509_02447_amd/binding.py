@@ -43,7 +43,7 @@ EXPORTS = ["qrm_create", "qrm_destroy", "qrm_last_error", "qrm_set_micro_batch",
            "qrm_profile_enable", "qrm_profile_read", "qrm_profile_read_chunks", "qrm_release_stream", "qrm_detect_static", "qrm_version"]
 DIAG_EXPORTS = ["qrm_diag_set_flags", "qrm_diag_matrix_rate", "qrm_diag_pair_split",
                 "qrm_diag_wide_schedule", "qrm_diag_host_plan",
-                "qrm_diag_preprocess_strips"]   # include/qrm_diag.h: bench and test tooling
+                "qrm_diag_preprocess_strips", "qrm_diag_rs_lanes"]   # include/qrm_diag.h: bench and test tooling
 
 QRM_MAX_STREAMS = 8   # include/qrm.h
 QRM_DIAG_NO_FUSED_PAIRS, QRM_DIAG_POISON_WORKSPACE, QRM_DIAG_FUSE_ALWAYS = 1, 2, 4
@@ -126,6 +126,8 @@ def load_library():
     lib.qrm_diag_host_plan.restype = C.c_int
     lib.qrm_diag_preprocess_strips.argtypes = [i64, i32, C.POINTER(i32)]
     lib.qrm_diag_preprocess_strips.restype = C.c_int
+    lib.qrm_diag_rs_lanes.argtypes = [i32, i32, i64, C.POINTER(i32)]
+    lib.qrm_diag_rs_lanes.restype = C.c_int
     lib.qrm_version.argtypes = []
     lib.qrm_version.restype = C.c_char_p
     _lib = lib

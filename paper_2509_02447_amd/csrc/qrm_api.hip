@@ -688,7 +688,6 @@ qrm_status qrm_create(const qrm_extractor_desc *ext, const qrm_rs_desc *rs, int 
             return hip_fail(nullptr, e, "hipMemcpy(tables)");
         }
         c->rs.tab = (const uint8_t *)c->d_tables + kKeyBytes;
-        c->rs.tab_bytes = (int)image.size();
     }
     *out = c;
     return QRM_OK;

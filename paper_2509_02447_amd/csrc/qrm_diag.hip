@@ -144,4 +144,15 @@ qrm_status qrm_diag_preprocess_strips(int64_t N, int32_t T, int32_t *strips)
     return QRM_OK;
 }
 
+qrm_status qrm_diag_rs_lanes(int32_t n, int32_t k, int64_t N, int32_t *lanes)
+{
+    if (k < 1 || n <= k || n > 255 || N < 1 || !lanes) return QRM_E_INVALID;
+    RsParams p{};
+    p.n = n;
+    p.k = k;
+    p.two_t = n - k;
+    *lanes = rs_lanes_per_word(p, N);
+    return QRM_OK;
+}
+
 } // extern "C"

@@ -153,7 +153,7 @@ hipError_t launch_nhwc_to_nchw(const bf16_t *in, int64_t n_img, int h, int w, in
 struct RsParams {
     int m, q, n, k, two_t, fcr;
     const uint8_t *tab; // device, the table image of the code (rs_table_image), 16-byte aligned
-    int tab_bytes;      // its size, a multiple of 16
+    int tab_bytes;      // what a launch takes of it into LDS, a multiple of 16
 };
 
 // Key verification: `key` device [k] symbols; matches null = no verification.
@@ -164,9 +164,11 @@ struct KeyArgs {
     uint8_t *detected = nullptr; // [N] matches >= tau, or null
 };
 
-// The tables the decoding kernels keep in LDS for this code, laid out once per context (p.tab / p.tab_bytes unused);
+// The tables the decoding kernels keep in LDS for this code, laid out once per context (p.tab unused; sets p.tab_bytes; codes
+// with two ways of dealing a word to lanes have an image for either, of equal size, one behind the other);
 // exp2: alpha^0 .. alpha^(2 ord - 1), lg: logarithms of 1 .. q - 1
-std::vector<uint8_t> rs_table_image(const RsParams &p, const std::vector<uint8_t> &exp2, const std::vector<uint8_t> &lg);
+std::vector<uint8_t> rs_table_image(RsParams &p, const std::vector<uint8_t> &exp2, const std::vector<uint8_t> &lg);
+int rs_lanes_per_word(const RsParams &p, int64_t N); // of a launch of N words
 hipError_t launch_rs_decode(const RsParams &p, const uint8_t *sym, int64_t N, uint8_t *msg, uint8_t *cw, int8_t *nerr,
                             const KeyArgs &key, hipStream_t s);
 // matches / detected for messages already in memory (msg device [N,k])

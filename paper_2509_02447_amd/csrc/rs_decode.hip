@@ -6,7 +6,7 @@
 // result from the 2t syndromes S_j = sum over positions of r * alpha^((fcr+j) * power):
 //
 //  * t <= 2, n <= 16 (rs_decode_lane_kernel): one word per lane, the error locator in closed form;
-//  * every other code (rs_decode_group_kernel): 16 or 32 lanes per word, Berlekamp-Massey in its
+//  * every other code (rs_decode_group_kernel): 16 or 32 lanes per word (rs_lanes_per_word), Berlekamp-Massey in its
 //    inversion-free systolic form with one polynomial coefficient per lane, Chien search and Forney with
 //    the positions dealt to the lanes.
 //
@@ -43,6 +43,12 @@ constexpr int64_t kGroupBlocks = 1280;
 
 bool lane_code(int n, int two_t) { return n <= 16 && two_t <= 4; }
 int group_lanes(int two_t) { return two_t > 8 ? 32 : 16; } // 3t + 1 coefficients of the systolic recursion, one per lane
+// Words of more than 128 symbols keep 16 lanes busy for 16 steps one after the other, which shows where a launch has so few
+// of them that every workgroup takes one run: while 32 lanes a word still fit the chip that way, they have 32.  RS(255,251),
+// 300 words 11.4 -> 7.8 us, 4096 11.7 -> 8.8, 8192 12.8 -> 10.6; RS(255,247) 14.3 -> 9.7, 14.7 -> 10.7, 15.7 -> 12.5; 20000
+// words are 16.9 us with 16 lanes and 17.1 with 32, 21.1 and 22.3.
+bool second_split(int n, int two_t) { return n > 128 && two_t <= 8; }
+bool takes_second_split(const RsParams &p, int64_t N) { return second_split(p.n, p.two_t) && N <= kGroupBlocks * (256 / 32); }
 
 struct Gf {
     const uint8_t *exp; // LDS
@@ -239,7 +245,7 @@ __global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const u
 }
 
 // ------------------------------------------------------------------------------------------------
-// All other codes: G = 16 (t <= 4) or 32 (t <= 8) lanes per word, four or two words per wavefront.  Lane l holds the
+// All other codes: G = 16 (t <= 4) or 32 (t <= 8, or few long words) lanes per word, four or two words per wavefront.  Lane l holds the
 // symbols l, l + G, l + 2G, .. (SPL of them).
 //   Syndromes   each lane evaluates its own symbols by Horner's rule in alpha^(G (fcr + j)): a step is one look-up in
 //               that constant's table (256 bytes: one dword per LDS bank, so no bank conflicts) and one XOR for
@@ -477,6 +483,7 @@ __global__ __launch_bounds__(256) void verify_kernel(const uint8_t *__restrict__
     }
 }
 
+// G lanes a word; p's tables are the ones for G
 template <int G, int TMAX, int SPL>
 hipError_t launch_group(const RsParams &p, const uint8_t *sym, int64_t N, uint8_t *msg, uint8_t *cw, int8_t *nerr,
                         const KeyArgs &key, hipStream_t s)
@@ -508,7 +515,7 @@ hipError_t launch_lane(const RsParams &p, const uint8_t *sym, int64_t N, uint8_t
 
 } // namespace
 
-std::vector<uint8_t> rs_table_image(const RsParams &p, const std::vector<uint8_t> &exp2, const std::vector<uint8_t> &lg)
+std::vector<uint8_t> rs_table_image(RsParams &p, const std::vector<uint8_t> &exp2, const std::vector<uint8_t> &lg)
 {
     const int q = p.q, ord = q - 1;
     auto mul_pow = [&](int v, int e) { return v ? exp2[lg[v] + e % ord] : (uint8_t)0; };
@@ -525,15 +532,30 @@ std::vector<uint8_t> rs_table_image(const RsParams &p, const std::vector<uint8_t
             for (int v = 0; v < q; ++v)
                 for (int j = 0; j < 4; ++j)
                     img.push_back(i < p.n && j < p.two_t ? mul_pow(v, (p.fcr + j) * (p.n - 1 - i)) : (uint8_t)0);
-    } else {
-        const int G = group_lanes(p.two_t), t = p.two_t / 2;
+        img.resize((img.size() + 15) / 16 * 16, 0);
+        p.tab_bytes = (int)img.size();
+        return img;
+    }
+    const std::vector<uint8_t> common = img;
+    auto add_group = [&](int G) {
         for (int j = 0; j < p.two_t; ++j)
             for (int v = 0; v < q; ++v) img.push_back(mul_pow(v, G * (p.fcr + j)));
-        for (int j = 1; j <= t; ++j)
+        for (int j = 1; j <= p.two_t / 2; ++j)
             for (int v = 0; v < q; ++v) img.push_back(mul_pow(v, G * j));
+        img.resize((img.size() + 15) / 16 * 16, 0);
+    };
+    add_group(group_lanes(p.two_t));
+    p.tab_bytes = (int)img.size();
+    if (second_split(p.n, p.two_t)) { // a second image behind the first
+        img.insert(img.end(), common.begin(), common.end());
+        add_group(32);
     }
-    img.resize((img.size() + 15) / 16 * 16, 0);
     return img;
+}
+
+int rs_lanes_per_word(const RsParams &p, int64_t N)
+{
+    return lane_code(p.n, p.two_t) ? 1 : takes_second_split(p, N) ? 32 : group_lanes(p.two_t);
 }
 
 hipError_t launch_rs_decode(const RsParams &p, const uint8_t *sym, int64_t N, uint8_t *msg, uint8_t *cw, int8_t *nerr,
@@ -547,6 +569,11 @@ hipError_t launch_rs_decode(const RsParams &p, const uint8_t *sym, int64_t N, ui
         case 3: return launch_lane<3>(p, sym, N, msg, cw, nerr, key, s);
         default: return launch_lane<4>(p, sym, N, msg, cw, nerr, key, s);
         }
+    }
+    if (takes_second_split(p, N)) {
+        RsParams second = p;
+        second.tab += p.tab_bytes;
+        return launch_group<32, 4, 8>(second, sym, N, msg, cw, nerr, key, s);
     }
     if (group_lanes(p.two_t) == 16) {
         if (p.n <= 16) return launch_group<16, 4, 1>(p, sym, N, msg, cw, nerr, key, s);

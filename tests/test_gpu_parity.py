@@ -111,6 +111,22 @@ def test_rs_decode_runs_shared_out_evenly(qrm, m, n, t, per):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,t,fcr", [(129, 1, 0), (129, 4, 3), (200, 3, 1), (255, 2, 1), (255, 4, 1)])
+def test_rs_decode_long_words_of_small_t_on_either_split(qrm, n, t, fcr):
+    """Words of more than 128 symbols with t <= 4 in launches on both sides of where 16 lanes a word replace 32."""
+    code = dict(m=8, prim_poly=0x11D, n=n, k=n - 2 * t, fcr=fcr)
+    count = 10241
+    msgs, err, _ = synth.rs_cases(130 + n + t, count, n, n - 2 * t, 8, max_err=t + 1)
+    words = oracle.rs_encode(msgs, **code) ^ err
+    words[5000:5050] = synth.random_words(7 + n, 50, n, 8)
+    om, oc, oe = oracle.rs_decode(words, **code)
+    ctx = qrm.Context(rs=code)
+    for N in (1, 9, 10239, 10240, 10241):
+        gm, gc, ge = gpu_rs_decode(ctx, words[:N])
+        assert np.array_equal(ge, oe[:N]) and np.array_equal(gm, om[:N]) and np.array_equal(gc, oc[:N]), N
+    ctx.close()
+
+
 def _random_codes(count, seed):
     """Seeded random code parameters over every supported field: (m, prim_poly, n, k, fcr)."""
     prim = {2: 0x7, 3: 0xB, 4: 0x13, 5: 0x25, 6: 0x43, 7: 0x89, 8: 0x11D}
