@@ -376,9 +376,8 @@ __global__ __launch_bounds__(256) void rs_decode_group_kernel(RsParams p, const 
             }
             L = (two_t - kk) >> 1; // the recursion's length; kk < 0: longer than t
             fail = kk < 0;
-            // degree of Lambda must equal L
+            // degree of Lambda must equal L (a group's lanes agree on L and fail)
             if (!fail && L > 0) fail = __shfl(ldelta, t + L, G) == kZeroLog;
-            else (void)__shfl(ldelta, t, G);
 
             // ---- Chien: terms at this lane's first position, then stepped
             int lam[TMAX + 1], om[TMAX];
