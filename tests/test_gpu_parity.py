@@ -143,7 +143,7 @@ def _random_codes(count, seed):
 def test_rs_decode_random_code_parameters(qrm):
     """Thirty random codes over GF(4) .. GF(256), full length and shortened, t = 1..8, several first roots: words with
     0 .. t+1 injected errors and plain random words, bit-exact against the oracle (which kernel a code takes - one
-    word per lane, 16 or 64 lanes per word - follows from n and t)."""
+    word per lane, 16 or 32 lanes per word - follows from n and t)."""
     for i, code in enumerate(_random_codes(30, 20250902)):
         t = (code["n"] - code["k"]) // 2
         msgs, err, ninj = synth.rs_cases(20 + i, 300, code["n"], code["k"], code["m"], max_err=t + 1)
@@ -771,10 +771,9 @@ def test_diagnostic_flags_do_not_change_results(qrm, flag, tol):
 
 
 def test_results_are_reproducible_bit_for_bit(qrm):
-    """Two calls give the same bytes: every sum inside the kernels is formed in a fixed order.  On the fused path
-    (64 channels) that order depends on the image alone, so other splits of the batch into micro-batches give the
-    same bytes too; on the single-block path (32 channels) a split deals an image's strips to other workgroups, and
-    the last fp32 bits of the channel sums may then differ.  (The wide-tile cases launch many co-resident workgroups
+    """Two calls give the same bytes: every sum inside the kernels is formed in a fixed order, which depends on
+    the image alone, on the fused path (64 channels) as on the single-block path (32 channels): other splits of the
+    batch into micro-batches give the same bytes too.  (The wide-tile cases launch many co-resident workgroups
     of the first-layer kernel per compute unit: matrix results read too early once showed there as run-to-run
     differences of one bf16 step.)"""
     for name, N, mbs in (("C2", 1300, (0, 300, 1024)), ("C1", 300, (0, 7)), ("C3", 3, (0,)), ("C4", 40, (0,))):
@@ -790,11 +789,8 @@ def test_results_are_reproducible_bit_for_bit(qrm):
             runs.append(run_detect(ctx, cfg, imgs, off))
         ctx.close()
         for r, mb in zip(runs[1:], (mbs + (mbs[0],))[1:]):
-            exact = name == "C2" or mb == mbs[0]   # single-block path: other splits deal the strips to other workgroups
             for key in ("logits", "bits", "msg", "codeword", "nerr"):
-                if exact:
-                    assert np.array_equal(runs[0][key], r[key]), (name, key, mb)
-            assert np.allclose(runs[0]["logits"], r["logits"], rtol=0, atol=2e-5), (name, mb)
+                assert np.array_equal(runs[0][key], r[key]), (name, key, mb)
 
 
 def test_more_streams_than_workspaces(qrm):
@@ -924,7 +920,8 @@ def test_detect_host_chunked_pipeline_equals_resident_detect(qrm):
     ctx.close()
 
 
-@pytest.mark.parametrize("H,W,tile", [(256, 256, 64), (100, 117, 30), (91, 75, 23), (128, 100, 32), (64, 64, 40)])
+@pytest.mark.parametrize("H,W,tile", [(256, 256, 64), (100, 117, 30), (91, 75, 23), (128, 100, 32), (64, 64, 40), (101, 117, 32),
+                                         (91, 75, 20)])
 def test_detect_host_tiles_read_from_host_memory(qrm, H, W, tile):
     """Chunks whose tiles are read out of page-locked memory by a kernel (whole dwords or bytes, rows at every alignment,
     a chunk that begins inside an allocation, origins beyond the border), chunks in pageable memory and tiles large
