@@ -16,6 +16,7 @@ Prints ONE JSON line.
 from __future__ import annotations
 
 import argparse
+import ctypes
 import json
 import os
 import sys
@@ -403,8 +404,9 @@ def bench_stage_kernels(env, ctx, cfg, N, d_img, d_off, stream) -> dict:
 def bench_stream(env, passes: int, warm_passes: int) -> dict:
     """Streaming configuration: images start in pinned HOST memory; upload, kernels and result download of
     different chunks overlap on the library's own streams (qrm_detect_host).  Three pre-generated chunks
-    are recycled, so nothing is generated inside the timed region.  The number is bound by the host
-    link, not by the GPU: the bare pinned upload rate of the same chunks is measured beside it."""
+    are recycled, so nothing is generated inside the timed region.  Chunks whose tiles are a small part of the
+    images come as tiles, the others whole (qrm_diag_host_plan): which of link and kernels bounds the pass follows
+    from the bytes that cross, the bare pinned upload rate and the rate of resident images, all measured beside it."""
     args, np, torch, synth, q = (env[k] for k in ("args", "np", "torch", "synth", "q"))
     cfg = synth.CONFIGS["C5"]
     chunk, n_chunks, lanes = args.chunk_images, args.chunks, args.streams
@@ -438,6 +440,13 @@ def bench_stream(env, passes: int, warm_passes: int) -> dict:
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
     value = n_total * passes / dt
+    # how the chunks come in, and the bytes of an image that cross the link: a tile's rows in whole 64-byte pieces, or all
+    first, rest, lent = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
+    q.load_library().qrm_diag_host_plan(cfg.channels, cfg.n_blocks, cfg.H, cfg.W, cfg.tile, chunk, min(lanes, n_chunks),
+                                        torch.cuda.get_device_properties(0).multi_processor_count,
+                                        ctypes.byref(first), ctypes.byref(rest), ctypes.byref(lent))
+    tiles_only = bool(rest.value)
+    link_bytes = 3 * cfg.tile * (cfg.tile + 63) if tiles_only else 3 * cfg.H * cfg.W
     # the pipeline's time line, chunk by chunk (events recorded inside the library): one more pass
     ctx.qrm_profile_enable(True)
     step()
@@ -461,15 +470,15 @@ def bench_stream(env, passes: int, warm_passes: int) -> dict:
             "last_download_end_after_last_upload_end_ms": round(float(tl[-1, 4] - tl[-1, 1]), 3),
             "first_chunks_ms": [[round(float(v), 2) for v in row] for row in tl[:6]],
             "columns": "upload start, upload end, kernels start, kernels end, download end (ms since the first upload started)",
-            "note": "the uploads follow each other with no gap and the kernels of a chunk take about half as long as its upload: "
-                    "the pipeline is bound by the host link, and there is no idle time for a stream tuner to fill",
+            "note": ("the kernels of a chunk take longer than its upload: the pass is bound by the kernels" if run.mean() > up.mean()
+                     else "the upload of a chunk takes longer than its kernels: the pass is bound by the host link"),
         }
     # what the paper's stream planner (Section 5, Algorithm 1) makes of these measurements: the three roles as
     # stages, one chunk as the baseline batch, the staging buffers and the workspace as the memory per image
     plan = None
     if timeline is not None:
         t_stage = [float(up.mean()) * 1e-3, float(run.mean()) * 1e-3, max(float((tl[:, 4] - tl[:, 3]).mean()) * 1e-3, 1e-6)]
-        u_stage = [3.0 * cfg.H * cfg.W, ctx.qrm_workspace_bytes(chunk, cfg.tile, cfg.tile) / chunk, float(cfg.k + cfg.n + 1)]
+        u_stage = [3.0 * cfg.tile ** 2 if tiles_only else 3.0 * cfg.H * cfg.W, ctx.qrm_workspace_bytes(chunk, cfg.tile, cfg.tile) / chunk, float(cfg.k + cfg.n + 1)]
         in_flight, cap = lanes * chunk, 16.0 * 2 ** 30   # the batch the pipeline holds at a time; memory it may plan with
         st, s_plan, m_plan, j_plan, acc = q.qrm_plan_streams(t_stage, u_stage, in_flight, chunk, q.QRM_MAX_STREAMS, cap,
                                                              0.01 * max(t_stage), 2)
@@ -477,9 +486,9 @@ def bench_stream(env, passes: int, warm_passes: int) -> dict:
                 "bytes_per_image": [round(v, 1) for v in u_stage], "global_batch": in_flight, "memory_cap_bytes": cap,
                 "stream_budget": q.QRM_MAX_STREAMS, "status": st, "streams": s_plan, "micro_batch": m_plan,
                 "predicted_bottleneck_s": round(j_plan, 6),
-                "note": "the planner's cost model divides a stage's time by its streams; the upload stage is one host link, "
-                        "which two concurrent copies share (an earlier version with two uploads in flight reached 0.73 "
-                        "of the link against 0.93-0.95 with one): qrm_detect_host keeps one stream per role"}
+                "note": "the planner's cost model divides a stage's time by its streams; two streams of kernels share the "
+                        "compute units and two uploads the link (copies of whole images: 0.73 of the link with two in "
+                        "flight, 0.93-0.95 with one): qrm_detect_host keeps one stream per role"}
     # the link on its own: the same chunks uploaded back to back, nothing else running
     d_stage = torch.empty((chunk, 3, cfg.H, cfg.W), dtype=torch.uint8, device="cuda")
     d_stage.copy_(bufs[0], non_blocking=True)
@@ -504,22 +513,30 @@ def bench_stream(env, passes: int, warm_passes: int) -> dict:
     resident = 3 * chunk / (time.perf_counter() - t2)
     l2 = cfg.tile * cfg.tile
     mfma_flops_per_image = 2 * 9 * 3 * cfg.channels * l2 + (cfg.n_blocks - 1) * 2 * 9 * cfg.channels ** 2 * l2
+    if resident < link_gbs * 1e9 / link_bytes:     # images/s of the kernels alone and of the link alone
+        tflops = mfma_flops_per_image * value / 1e12
+        roofline = {"bound": "mfma", "achieved": round(tflops, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
+                    "frac": round(tflops / PEAK_BF16_TFLOPS, 4)}
+    else:
+        roofline = {"bound": "host link", "achieved": round(value * link_bytes / 1e9, 2), "peak": round(link_gbs, 2), "unit": "GB/s",
+                    "frac": round(value * link_bytes / 1e9 / link_gbs, 4),
+                    "note": "peak = bare pinned upload of the same chunks measured in this run (not a published figure)"}
+    roofline["traffic"] = None
     res = {
         "value": round(value, 1), "steps": passes, "warmup": warm_passes, "ms_per_step": round(dt * 1e3 / passes, 3),
         "config": {"workload": f"C5 (streamed): {n_chunks} chunks x {chunk} images 3x{cfg.H}x{cfg.W} u8 per step from "
                                f"pinned host memory ({n_buf} buffers recycled), {lanes} chunks in flight; one {cfg.tile}x{cfg.tile} "
                                f"tile each, {cfg.n_blocks}x conv3x3 {cfg.channels}ch, RS({cfg.n},{cfg.k}) over GF(2^{cfg.m})",
                    "images": n_total, "inputs": "pinned HOST memory: the upload is inside the timed region"},
-        "roofline": {"bound": "host link", "achieved": round(value * 3 * cfg.H * cfg.W / 1e9, 2),
-                     "peak": round(link_gbs, 2), "unit": "GB/s",
-                     "frac": round(value * 3 * cfg.H * cfg.W / 1e9 / link_gbs, 4), "traffic": None,
-                     "note": "peak = bare pinned upload of the same chunks measured in this run (not a published figure); achieved counts whole images, of which only the tiles cross the link, so it may exceed the peak"},
+        "roofline": roofline,
         "extractor_mfma_tflops": round(mfma_flops_per_image * value / 1e12, 2),
         "extractor_frac_of_bf16_peak": round(mfma_flops_per_image * value / 1e12 / PEAK_BF16_TFLOPS, 4),
         "stages": {"bare_upload_GBs": round(link_gbs, 2), "bare_upload_images_per_s": round(link_gbs * 1e9 / (3 * cfg.H * cfg.W), 1),
+                   "chunks_cross_the_link_as": "tiles" if tiles_only else "whole images",
+                   "link_bytes_per_image": link_bytes, "link_GBs": round(value * link_bytes / 1e9, 2),
                    "resident_images_per_s": round(resident, 1), "timeline": timeline, "stream_plan": plan},
     }
-    log(f"C5: {value:.0f} images/s = {res['roofline']['frac']:.3f} of the bare upload rate ({link_gbs:.1f} GB/s)")
+    log(f"C5: {value:.0f} images/s, {value * link_bytes / 1e9:.1f} of {link_gbs:.1f} GB/s over the link, resident images {resident:.0f} images/s")
     ctx.close()
     del bufs, d_stage
     torch.cuda.empty_cache()
