@@ -770,7 +770,7 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 //
 // conv_mid is bound by activation traffic as much as by the matrix cores (288 FLOP per byte against a
 // machine balance of ~310).  Here the activations between the two blocks never leave the CU: a
-// workgroup walks down one image, group A (wavefronts 0-3, weights of the first block) turns input rows
+// workgroup walks down its images, group A (wavefronts 0-3, weights of the first block) turns input rows
 // into rows of the intermediate activation map, which it writes as bf16 into a second LDS ring, and
 // group B (wavefronts 4-7, weights of the second block) turns those into output rows.  Global traffic
 // per FLOP halves; both wavefronts of a SIMD carry matrix work, so each fills the other's gaps.

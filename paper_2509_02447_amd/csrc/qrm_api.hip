@@ -236,8 +236,8 @@ int default_micro_batch(const qrm_ctx *c, int h, int w)
     const size_t per_img = (size_t)h * w * c->C * 2;
     size_t mb = ((size_t)512 << 20) / (per_img ? per_img : 1);
     if (mb < 64) mb = 64;
-    // The fused kernels give every compute unit whole images: tiles wider than one column block (where an image
-    // is a long run of work) get at least one image per compute unit, as long as a buffer stays below 4 GiB.
+    // Tiles wider than one column block get at least one image per compute unit, as long as a buffer stays below 4 GiB: the
+    // fused kernels then fill the chip with whole images, without runs that end inside one (see conv_pair_split).
     if (c->pairable && w > kTileW && mb < (size_t)c->num_cu && (size_t)c->num_cu * per_img <= ((size_t)4 << 30)) mb = c->num_cu;
     if (mb > 8192) mb = 8192;
     return (int)mb;
