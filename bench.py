@@ -35,23 +35,23 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, published
 # kernel, the micro-batch and the image count it was taken on are unchanged; otherwise the line reports null.
 RECORDED_TRAFFIC = {
     # (configuration, launch kind): bytes per launch, where it was measured
-    ("C2", "pair_mid"): {"bytes": 1076929521, "commit": "f08133f", "images_per_launch": 1024,
+    ("C2", "pair_mid"): {"bytes": 1079908378, "commit": "bf5163f", "images_per_launch": 1024,
                          "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C2", "pair_last"): {"bytes": 544245792, "commit": "f08133f", "images_per_launch": 1024,
+    ("C2", "pair_last"): {"bytes": 551404595, "commit": "bf5163f", "images_per_launch": 1024,
                          "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C2", "pair_first"): {"bytes": 571728051, "commit": "f08133f", "images_per_launch": 1024,
+    ("C2", "pair_first"): {"bytes": 573236339, "commit": "bf5163f", "images_per_launch": 1024,
                          "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C3", "pair_mid"): {"bytes": 4456336948, "commit": "f08133f", "images_per_launch": 256,
+    ("C3", "pair_mid"): {"bytes": 4472813544, "commit": "bf5163f", "images_per_launch": 256,
                          "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C3", "pair_last"): {"bytes": 2318194705, "commit": "f08133f", "images_per_launch": 256,
+    ("C3", "pair_last"): {"bytes": 2345266451, "commit": "bf5163f", "images_per_launch": 256,
                          "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C3", "pair_first"): {"bytes": 2408639194, "commit": "f08133f", "images_per_launch": 256,
+    ("C3", "pair_first"): {"bytes": 2416851750, "commit": "bf5163f", "images_per_launch": 256,
                          "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C4", "pair_mid"): {"bytes": 1104996974, "commit": "f08133f", "images_per_launch": 256,
+    ("C4", "pair_mid"): {"bytes": 1108868512, "commit": "bf5163f", "images_per_launch": 256,
                          "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C4", "pair_last"): {"bytes": 573363200, "commit": "f08133f", "images_per_launch": 256,
+    ("C4", "pair_last"): {"bytes": 579987572, "commit": "bf5163f", "images_per_launch": 256,
                          "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C4", "pair_first"): {"bytes": 596632402, "commit": "f08133f", "images_per_launch": 256,
+    ("C4", "pair_first"): {"bytes": 598561627, "commit": "bf5163f", "images_per_launch": 256,
                          "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
 }
 
