@@ -25,7 +25,8 @@
 //  * The last block writes no activations when the final convolution has no ReLU: final conv + global
 //    average pool are linear, so nine border-aware channel sums per image are all head_kernel needs to
 //    apply the final convolution (fp32 weights), the linear layer, the threshold and the symbol packing.
-//    With a final ReLU, conv_mid_kernel<C, MODE_FINAL> sums the final convolution's output over the pixels.
+//    With a final ReLU, conv_mid_kernel<64, MODE_FINAL> or conv_final32_kernel sums the final convolution's output
+//    over the pixels.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -530,10 +531,7 @@ struct StatArgs {
 
 constexpr int MODE_MID = 0;  // write activations, sample channel sums from every eighth strip
 constexpr int MODE_LAST = 1; // last block: no activations, lines of channel sums (LastSums)
-// Final convolution, summed over the pixels: no activations.  64 output channels per grid.y slice whatever C is: slices of 32
-// read the whole input once more for every other one, which took 368 us instead of
-// 269 for 512 tiles of 128 x 128 (32 channels, 48 bits) and 143 instead of 103 for 700 of 64 x 64.
-constexpr int MODE_FINAL = 2;
+constexpr int MODE_FINAL = 2; // final convolution (C output channels per grid.y slice), summed over the pixels: no activations
 
 constexpr int kMidWaves = 8; // wavefronts of a conv_mid workgroup: two groups of four
 
@@ -560,8 +558,8 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                                                                      bf16_t *__restrict__ out)
 {
     typedef MidCfg<C> K;
-    constexpr int NCB = MODE == MODE_FINAL ? 2 : K::NCB, CO = 32 * NCB; // blocks of 32 output channels, output channels
-    constexpr int RG = 2 / NCB;        // row groups among the 4 wavefronts of a group
+    static_assert(MODE != MODE_FINAL || C == 64, "conv_final32_kernel");
+    constexpr int RG = 2 / K::NCB;     // row groups among the 4 wavefronts of a group
     constexpr int RW = kRows / RG;     // output rows per wavefront
     constexpr int NSLOT = kMidSlots;
     constexpr int WIN = kRows + 2;     // staged rows one strip reads
@@ -569,20 +567,20 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
     // bias + rounding-residual correction per image, indexed by image mod 4: it is written two phases
     // before the image's first strip is multiplied and read until one phase after its last, and an
     // image may be a single strip
-    __shared__ __attribute__((aligned(16))) float s_init[4][CO];
+    __shared__ __attribute__((aligned(16))) float s_init[4][C];
     __shared__ __attribute__((aligned(16))) float s_mean[kMidWaves][C];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave >> 2, w4 = wave & 3;
     const int px = lane & 31, half = lane >> 5;
-    const int cb = w4 % NCB;
-    const int xb = (w4 / NCB) & 1;
-    const int rg = w4 / (NCB * 2);
+    const int cb = w4 % K::NCB;
+    const int xb = (w4 / K::NCB) & 1;
+    const int rg = w4 / (K::NCB * 2);
 
     bf16x8 Wr[9][K::KC];
-    const int slice = MODE == MODE_FINAL ? blockIdx.y : 0; // CO output channels of the launch
-    load_weight_frags<C>(Wr, wfrag, slice * NCB + cb, lane);
+    const int slice = MODE == MODE_FINAL ? blockIdx.y : 0; // C output channels of the launch
+    load_weight_frags<C>(Wr, wfrag, slice * K::NCB + cb, lane);
 
     const int tpi = g.strips * g.colblks; // tiles per image
     const int total = g.n_img * tpi;
@@ -628,9 +626,9 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                              pin_in_loop(lane), first_row(q), wstart(q), NSLOT);
     };
     // s_init[n & 3][o] = bias[o] + sum_c rsum[c][o] * mean_n[c], by the four wavefronts of one group:
-    // each takes CO/4 outputs, its lanes split the sum over c in 64 / (CO/4) parts
+    // each takes C/4 outputs, its lanes split the sum over c in 64 / (C/4) parts
     auto prepare_init = [&](int n) {
-        constexpr int OPW = CO / 4, PARTS = 64 / OPW, CP = C / PARTS;
+        constexpr int OPW = C / 4, PARTS = 64 / OPW, CP = C / PARTS;
         const int lane = pin_in_loop(tid & 63);
         const int o = w4 * OPW + lane % OPW, part = lane / OPW;
         float d = 0.f;
@@ -645,7 +643,7 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 #pragma unroll
             for (int sh = OPW; sh < 64; sh <<= 1) d += __shfl_xor(d, sh);
         }
-        if (part == 0) s_init[n & 3][o] = (MODE != MODE_FINAL || bias ? bias[slice * CO + o] : 0.f) + d;
+        if (part == 0) s_init[n & 3][o] = (MODE != MODE_FINAL || bias ? bias[slice * C + o] : 0.f) + d;
     };
     f32x16 acc[RW];
     const int sample_phase = sampled_strip(g.strips); // strips 3, 11, 19, .. are sampled (the last one of a short tile)
@@ -691,7 +689,7 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
             column_sums<RW>(t, acc, si, st.low, x < g.w, yw, g.h);
             const float sum = reduce16_over_half(t, px); // one channel per lane
             const int line = (q.colblk * g.strips + strip) * (2 * RG) + piece;
-            float *rec = st.tout + (((int64_t)n * st.out_recs + line) * gridDim.y + slice) * CO;
+            float *rec = st.tout + (((int64_t)n * st.out_recs + line) * gridDim.y + slice) * C;
             if ((px & 1) == 0) rec[cb * 32 + half * 16 + reduce16_index(px)] = sum;
         } else if (st.tout) {
             float *lines = st.tout + (int64_t)n * st.out_recs * C + cb * 32 + half * 16;
@@ -763,6 +761,100 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
         g1 = g2;
         advance(g2);
     }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Final convolution of 32-channel networks, 64 output channels per grid.y slice, summed over the pixels: the lines of
+// conv_mid_kernel<64, MODE_FINAL>.  Half the matrix instructions of a 64-channel strip are too few for that kernel's phases,
+// of which each end costs the same (51 % of the matrix pipes' rate): here two workgroups of four wavefronts share a compute
+// unit, each with weights, accumulators and two strips' rows of its own, and fill each other's gaps.  A workgroup asks for
+// the next strip's rows before it multiplies this one's.  The line of a strip is written behind the next strip's loads, so
+// that the wait for them never waits for a store just issued.  Measured against conv_mid_kernel in that place (two blocks and
+// this, us a call): 2404 tiles of 40 x 5, 107 bits 571 -> 485; 512 of 128 x 128, 60 bits 682 -> 663; 700 of 64 x 64, 120 bits 344 ->
+// 331; 20 of 64 x 64, 128 bits 34.9 -> 31.5.  Loading only the rows that the strip above does not share: no gain (504, 651).
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__restrict__ ws, size_t in_off, ConvGeom g,
+                                                              const bf16_t *__restrict__ wfrag, const float *__restrict__ bias,
+                                                              StatArgs st)
+{
+    constexpr int C = 32, RW = kRows, WIN = kRows + 2;
+    typedef MidCfg<C> K;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * WIN * K::ROWB];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int px = lane & 31, half = lane >> 5;
+    const int cb = wave & 1, xb = wave >> 1, slice = blockIdx.y;
+    bf16x8 Wr[9][K::KC];
+    load_weight_frags<C>(Wr, wfrag, slice * 2 + cb, lane);
+    float bias16[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) bias16[v] = bias ? bias[slice * 64 + cb * 32 + half * 16 + v] : 0.f;
+    const int tpi = g.strips * g.colblks, total = g.n_img * tpi;
+    const int t_begin = xcd_virtual_block(blockIdx.x, gridDim.x) * st.per;
+    const int ns = min(total, t_begin + st.per) - t_begin; // strips of this workgroup's run
+    if (ns <= 0) return;
+    const lrow_t lbase = lds_address(lds) + (xb * 32 + px) * K::PS + half * 16;
+    const size_t img_bytes = (size_t)g.h * g.w * C * 2;
+    struct Geo {
+        int strip, colblk, n;
+    };
+    auto advance = [&](Geo &q) {
+        if (++q.strip == g.strips) {
+            q.strip = 0;
+            if (++q.colblk == g.colblks) {
+                q.colblk = 0;
+                ++q.n;
+            }
+        }
+    };
+    auto issue = [&](const Geo &q, int buf) {
+        issue_strip_loads<C>(lds, ws, ws + in_off + (size_t)q.n * img_bytes, g.h, g.w, q.strip * kRows, q.colblk * kTileW, wave,
+                             pin_in_loop(lane), 0, buf * WIN, 2 * WIN);
+    };
+    Geo gc{t_begin % g.strips, (t_begin / g.strips) % g.colblks, t_begin / tpi}, g1 = gc;
+    advance(g1);
+    float *rec = nullptr; // where the sums of the strip before go
+    float sum = 0.f;
+    auto write_line = [&]() {
+        if ((px & 1) == 0) rec[cb * 32 + half * 16 + reduce16_index(px)] = sum;
+    };
+    issue(gc, 0);
+    for (int i = 0; i < ns; ++i) {
+        __builtin_amdgcn_s_waitcnt(kWaitVm0); // this strip's rows, asked for a strip ago
+        lds_barrier();                        // .. by all wavefronts, which also have read the other buffer
+        if (i + 1 < ns) issue(g1, (i + 1) & 1);
+        if (i > 0) write_line();
+        lrow_t rowp[RW + 2];
+#pragma unroll
+        for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((i & 1) * WIN + r) * K::ROWB;
+        f32x16 acc[RW];
+        __builtin_amdgcn_s_setprio(3);
+        strip_mma<C, RW>(rowp, Wr, acc);
+        __builtin_amdgcn_s_setprio(0);
+        float t[16];
+        auto row_sums = [&](auto full) { // as column_sums(), without a test per value where the strip has all of its rows
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                t[v] = fmaxf(acc[0][v] + bias16[v], st.low);
+#pragma unroll
+                for (int r = 1; r < RW; ++r)
+                    if (decltype(full)::value || gc.strip * kRows + r < g.h) t[v] += fmaxf(acc[r][v] + bias16[v], st.low);
+            }
+        };
+        if (gc.strip * kRows + RW <= g.h) row_sums(std::true_type{});
+        else row_sums(std::false_type{});
+        const int x0 = gc.colblk * kTileW + xb * 32;
+        if (x0 + 32 > g.w) { // (the same for the whole wavefront)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) t[v] = x0 + px < g.w ? t[v] : 0.f;
+        }
+        sum = reduce16_over_half(t, px); // one channel per lane
+        const int line = (gc.colblk * g.strips + gc.strip) * 2 + xb;
+        rec = st.tout + (((int64_t)gc.n * st.out_recs + line) * gridDim.y + slice) * 64;
+        gc = g1;
+        advance(g1);
+    }
+    write_line();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2076,18 +2168,18 @@ Partition make_partition(int64_t n_img, int tiles_per_image, int target_blocks)
     return p;
 }
 
-Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int nbp)
+Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int C, int nbp)
 {
-    return make_partition(n_img, tiles_per_image, std::max(1, num_cu / (nbp / 64)));
+    return make_partition(n_img, tiles_per_image, std::max(1, num_cu * (C == 64 ? 1 : 2) / (nbp / 64))); // (two to a compute unit)
 }
 
 hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
                              const float *bias, int relu, float *partial, const Partition &part, hipStream_t s)
 {
     StatArgs st{MeanIn{}, nullptr, partial, conv_final_lines(g), part.per, relu ? 0.f : __builtin_nanf("")};
-    const dim3 grid(part.blocks, nbp / 64), block(64 * kMidWaves);
-    if (C == 64) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
-    else hipLaunchKernelGGL((conv_mid_kernel<32, MODE_FINAL>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
+    const dim3 grid(part.blocks, nbp / 64);
+    if (C == 64) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_FINAL>), grid, dim3(64 * kMidWaves), 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
+    else hipLaunchKernelGGL(conv_final32_kernel, grid, dim3(256), 0, s, ws, in_off, g, wfrag, bias, st);
     return hipGetLastError();
 }
 

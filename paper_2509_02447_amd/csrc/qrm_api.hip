@@ -510,7 +510,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                             c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, s);
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {
-            const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->nbp);
+            const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
             tail = tail_of(cur);
             e = launch_conv_final(base, buf_off[cur], g, c->C, c->nbp, c->d_w_final, c->final_relu ? c->d_bias_final : nullptr,
                                   c->final_relu, tail, pl, s);

@@ -137,7 +137,7 @@ hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n
 // partial: f32 [n_img][conv_final_lines()][nbp], each line over a part of the image that does not depend on `part`
 // (conv_final_partition())
 int conv_final_lines(const ConvGeom &g);
-Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int nbp);
+Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int C, int nbp);
 hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
                              const float *bias, int relu, float *partial, const Partition &part, hipStream_t s);
 

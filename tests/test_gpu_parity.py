@@ -539,7 +539,7 @@ def test_extractor_final_relu_and_affine(qrm):
 
 @pytest.mark.parametrize("C,nb,nbits,h,w,relu", [(64, 3, 16, 5, 64, 1), (64, 2, 64, 13, 70, 1), (64, 3, 65, 20, 128, 1),
                                                  (32, 2, 33, 17, 30, 1), (32, 3, 128, 9, 65, 1), (64, 1, 30, 12, 40, 0),
-                                                 (32, 1, 70, 8, 66, 1)])
+                                                 (32, 1, 70, 8, 66, 1), (32, 1, 30, 12, 40, 0), (32, 2, 64, 30, 130, 1)])
 def test_extractor_final_convolution_over_all_pixels(qrm, C, nb, nbits, h, w, relu):
     """The final convolution evaluated pixel by pixel (with a ReLU behind it, or a single block before it): one and two
     groups of output channels, ragged rows and columns, a tile alone, a few, and more strips than compute units."""
@@ -561,12 +561,12 @@ def test_extractor_final_convolution_over_all_pixels(qrm, C, nb, nbits, h, w, re
     ctx.close()
 
 
-@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
-def test_final_convolution_keeps_what_is_not_a_number(qrm, value):
+@pytest.mark.parametrize("C,value", [(64, np.nan), (64, np.inf), (64, -np.inf), (32, np.nan), (32, np.inf)])
+def test_final_convolution_keeps_what_is_not_a_number(qrm, C, value):
     """Without a ReLU a final convolution that is not finite gives logits that are not: an infinite weight meets the zeros
     of the padding, so both are NaN at every border pixel and so is the sum over the tile."""
-    wts = small_weights(64, 1, 30, 5)
-    wts["conv_w"][-30 * 64 * 9:] = value
+    wts = small_weights(C, 1, 30, 5)
+    wts["conv_w"][-30 * C * 9:] = value
     tiles = np.random.default_rng(3).integers(0, 256, size=(2, 3, 12, 40), dtype=np.uint8)
     ctx = qrm.Context(weights=wts)
     d_logits, d_bits = empty((2, 30), torch.float32), empty((2, 30), torch.uint8)
