@@ -12,8 +12,8 @@
 //    applied to the accumulators on the way out, before the single bf16 rounding per layer.
 //  * Workgroups are persistent (one per compute unit, eight wavefronts in two groups of four) and stage
 //    rows of pixels in LDS rings with direct-to-LDS loads: a pixel takes C * 2 + 16 bytes, so that the
-//    16-byte fragment reads are bank-conflict free, and whatever lies outside the tile is loaded from a
-//    block of zeros.  Each fragment read from LDS feeds up to three matrix instructions (the three
+//    16-byte fragment reads are bank-conflict free, and whatever lies outside the tile arrives as zeros (the
+//    bounds check of buffer loads, RowLoader).  Each fragment read from LDS feeds up to three matrix instructions (the three
 //    vertical taps that touch that input row).  conv_mid_kernel computes one block per launch (strips of
 //    4 rows x 64 columns, the two groups in opposite phases); conv_pair_kernel computes two consecutive
 //    blocks per launch and keeps the activations between them in a second LDS ring.
@@ -139,7 +139,7 @@ struct MidCfg {
     static constexpr int SPP = PS / 16;               // 16-byte slots per pixel
     static constexpr int ROW_SLOTS = kHaloW * SPP;    // slots of one staged row (halo columns included)
     static constexpr int PIECES = (ROW_SLOTS + 63) / 64; // wavefront-wide direct-to-LDS loads per row
-    static constexpr int ROWB = PIECES * 1024;        // LDS bytes per staged row
+    static constexpr int ROWB = ROW_SLOTS * 16;       // LDS bytes per staged row: rows are packed, the last piece is partial
     static constexpr int QPW = (PIECES + 3) / 4;      // pieces of a row one wavefront is responsible for
 };
 
@@ -151,50 +151,83 @@ __device__ __forceinline__ lrow_t lds_address(const void *p)
     return (lrow_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)p;
 }
 
-// Asynchronous staging of the rows of one strip (kRows + 2 rows, halo included) into LDS with
-// direct-to-LDS loads.  A staged row is cut into PIECES pieces of 64 slots of 16 bytes; one
-// wavefront-wide load fills one piece (1 KiB of LDS at slot*ROWB + piece*1024), lane l supplying slot
-// piece*64 + l = (column, 8-channel chunk).  Wavefront w (0..3) of the loading group always handles
-// pieces w, w+4, ..., so the per-lane column decoding is done once per strip, not once per load.
-// Pixels outside the tile must read as zero (zero padding of the convolution): rows above / below the
-// tile, halo columns outside it, and the padding slots of a pixel all load from the block of zeros that
-// opens the workspace (`ws`).  A pixel is addressed as the image's base `img` + a 32-bit byte offset.
-// Window rows first_row..kRows+1 are loaded; window row r goes to row slot (ring_pos + r) mod nslot.
+// Asynchronous staging of rows of activations into LDS with direct-to-LDS buffer loads.  A staged row (the halo columns
+// included) is cut into PIECES pieces of 64 slots of 16 bytes; one wavefront-wide load fills one piece (1 KiB of LDS from
+// row + piece * 1024 on), lane l supplying slot piece * 64 + l = (column, 8-channel chunk).  Wavefront w (0..3) of the
+// loading group always handles pieces w, w + 4, ..
+// Pixels outside the tile must read as zero (zero padding of the convolution).  That is the bounds check of the buffer
+// instruction: what lies outside the image's buffer arrives as zeros and asks nothing of memory.  Rows above / below the tile
+// see a buffer of no bytes; halo columns outside the tile and the padding slots of a pixel get an offset beyond any image
+// (kOutside).  A load is then a scalar row offset and a per-lane offset that only changes with the column block: two or three
+// scalar instructions where 64-bit addresses selected per lane against a block of zeros took eight vector ones, which made the
+// loading group of conv_mid_kernel the longer one (3200 of a phase's 6200 cycles went into the loads of a strip): 100 tiles of
+// 75 x 100, seven blocks and a final ReLU 438.0 -> 415.8 us, 333 of 64 x 64 588.6 -> 580.0, 4096 of them 6654 -> 6592.
 // The caller waits (s_waitcnt vmcnt) and passes a barrier before anyone reads the rows.
-constexpr uint32_t kSlotZero = 0xffffffffu; // lane loads zeros
+constexpr uint32_t kOutside = 0x80000000u; // above kMaxImageActBytes
+
+// one wavefront-wide load: 16 bytes per lane from offset voff (per lane) + soff of the `bytes` bytes at `buf`
+__device__ __forceinline__ void load_lds16(const uint8_t *buf, uint32_t bytes, uint32_t voff, int soff, uint8_t *dst)
+{
+    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(buf), 0, (int)bytes, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)dst, 16, voff, soff, 0, 0);
+}
 
 template <int C>
-__device__ __forceinline__ void issue_strip_loads(uint8_t *lds, const uint8_t *ws, const uint8_t *img, int h, int w,
-                                                  int y0, int x0, int wave, int lane, int first_row = 0,
-                                                  int ring_pos = 0, int nslot = kRows + 2)
-{
+struct RowLoader {
     typedef MidCfg<C> K;
-    uint32_t coff[K::QPW]; // byte offset of this lane's slot inside an image row, or the mark
+    // per lane and piece: byte offset of the lane's slot in an image row for the column block at column 0 (negative for the
+    // halo column left of the tile), or far below zero: no slot (the last piece of a row is partial, the next row starts
+    // right behind it), or one of a pixel's padding slots
+    static constexpr int32_t kNone = INT32_MIN, kPad = INT32_MIN + 1; // (a row has at most 1900 MiB)
+    int32_t off[K::QPW];
+    __device__ __forceinline__ RowLoader(int w4, int lane)
+    {
 #pragma unroll
-    for (int qi = 0; qi < K::QPW; ++qi) {
-        const int slot = (wave + 4 * qi) * 64 + lane;
-        const int col = slot / K::SPP, cpos = slot - col * K::SPP;
-        const int gx = x0 - 1 + col;
-        coff[qi] = (cpos < C / 8 && col < kHaloW && gx >= 0 && gx < w) ? (uint32_t)((gx * C + cpos * 8) * 2) : kSlotZero;
-    }
-#pragma unroll
-    for (int r = 0; r < kRows + 2; ++r) {
-        if (r < 2 && r < first_row) continue;                       // already in LDS (or known to be zero there)
-        const int gy = y0 - 1 + r;                                  // same for the whole workgroup
-        const bool rowok = gy >= 0 && gy < h;
-        const uint32_t rowoff = (uint32_t)(gy * w * C * 2);
-        const int rslot = (ring_pos + r) % nslot;
-#pragma unroll
-        for (int qi = 0; qi < K::QPW; ++qi) {
-            const int q = wave + 4 * qi;                            // same for the whole wavefront
-            if (4 * qi + 3 < K::PIECES || q < K::PIECES) {
-                const uint8_t *p = (rowok && coff[qi] != kSlotZero) ? img + (rowoff + coff[qi]) : ws;
-                __builtin_amdgcn_global_load_lds((gptr_t)p, (lptr_t)(lds + rslot * K::ROWB + q * 1024), 16, 0, 0);
-            }
+        for (int k = 0; k < K::QPW; ++k) {
+            const int sl = (w4 + 4 * k) * 64 + lane, col = sl / K::SPP, cpos = sl - col * K::SPP;
+            off[k] = sl >= K::ROW_SLOTS ? kNone : (cpos < C / 8 ? ((col - 1) * C + cpos * 8) * 2 : kPad);
         }
-        __builtin_amdgcn_sched_barrier(0); // one row's addresses at a time
     }
-}
+    // the offsets for the column block at column x0 of rows of row_bytes bytes
+    struct Block {
+        uint32_t voff[K::QPW];
+    };
+    __device__ __forceinline__ Block at(int x0, uint32_t row_bytes) const
+    {
+        Block b;
+#pragma unroll
+        for (int k = 0; k < K::QPW; ++k) {
+            const uint32_t o = (uint32_t)(off[k] + x0 * (C * 2)); // (the marks stay below zero)
+            b.voff[k] = o < row_bytes ? o : kOutside;
+        }
+        return b;
+    }
+    // row y (of h) of the image at `img` (img_bytes bytes; all the same for the whole wavefront) -> dst
+    __device__ __forceinline__ void row(const Block &b, const uint8_t *img, uint32_t img_bytes, int y, int h, uint32_t row_bytes, uint8_t *dst, int w4) const
+    {
+        const bool rowok = (uint32_t)y < (uint32_t)h;
+        const uint32_t bytes = rowok ? img_bytes : 0;
+        const int soff = rowok ? y * (int)row_bytes : 0;
+#pragma unroll
+        for (int k = 0; k < K::QPW; ++k) {
+            const int q = w4 + 4 * k; // the same for the whole wavefront
+            if (4 * k + 3 < K::PIECES - 1 || (q < K::PIECES && off[k] != kNone))
+                load_lds16(img, bytes, b.voff[k], soff, dst + q * 1024);
+        }
+    }
+    // Window rows first_row .. kRows + 1 of the strip whose first output row is y0 (window row r is image row y0 - 1 + r) into
+    // row slots (ring_pos + r) mod nslot, a power of two.
+    __device__ __forceinline__ void strip(uint8_t *lds, int nslot, const uint8_t *img, uint32_t img_bytes, int h, uint32_t row_bytes, int y0, int x0,
+                                          int w4, int first_row = 0, int ring_pos = 0) const
+    {
+        const Block b = at(x0, row_bytes);
+#pragma unroll
+        for (int r = 0; r < kRows + 2; ++r) {
+            if (r < 2 && r < first_row) continue; // already in LDS (or known to be zero there)
+            row(b, img, img_bytes, y0 - 1 + r, h, row_bytes, lds + ((ring_pos + r) & (nslot - 1)) * K::ROWB, w4);
+        }
+    }
+};
 
 // body(std::integral_constant<int, 0>) ... body(std::integral_constant<int, N - 1>) in this order: a loop whose
 // counter is a compile-time constant inside the body (assembly operands with immediate constraints need one)
@@ -320,36 +353,82 @@ __device__ __forceinline__ void load_weight_frags(bf16x8 (&Wr)[9][C / 16], const
 // Accumulation order is fixed, so results do not depend on scheduling.
 __host__ __device__ constexpr int sampled_strip(int strips) { return strips < 4 ? strips - 1 : 3; }
 
-// The sampled channel means of image n, from its mi.recs records, into dst[0 .. C) (LDS) by one wavefront: 16 bytes
+// The sampled channel means of an image, from its mi.recs records, into dst[0 .. C) (LDS) by one wavefront: 16 bytes
 // per lane, four loads in flight, i.e. 16 (C = 64) or 32 (C = 32) records per round trip to memory.
 template <int C>
-__device__ __forceinline__ void image_means(const MeanIn &mi, int n, float *dst, int lane)
-{
-    constexpr int LPR = C / 4, RPL = 64 / LPR; // lanes per record, records per wavefront-wide load
-    const f32x4 *p = (const f32x4 *)(mi.rec + (int64_t)n * mi.recs * C) + lane % LPR;
-    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int r0 = 0; r0 < mi.recs; r0 += 4 * RPL) {
-        f32x4 v[4];
+struct ImageMeans {
+    static constexpr int LPR = C / 4, RPL = 64 / LPR; // lanes per record, records per wavefront-wide load
+    f32x4 v[4];
+    __device__ __forceinline__ void load(const MeanIn &mi, int n, int lane, int r0)
+    {
+        const f32x4 *p = (const f32x4 *)(mi.rec + (int64_t)n * mi.recs * C) + lane % LPR;
 #pragma unroll
         for (int u = 0; u < 4; ++u) v[u] = p[min(r0 + u * RPL + lane / LPR, mi.recs - 1) * LPR];
+    }
+    // load(.., 0) has been called
+    __device__ __forceinline__ void finish(const MeanIn &mi, int n, float *dst, int lane)
+    {
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int r0 = 0;;) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const bool ok = r0 + u * RPL + lane / LPR < mi.recs;
+            for (int u = 0; u < 4; ++u) {
+                const bool ok = r0 + u * RPL + lane / LPR < mi.recs;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum[e] += ok ? v[u][e] : 0.f;
+                for (int e = 0; e < 4; ++e) sum[e] += ok ? v[u][e] : 0.f;
+            }
+            r0 += 4 * RPL;
+            if (r0 >= mi.recs) break;
+            load(mi, n, lane, r0);
+        }
+#pragma unroll
+        for (int sh = LPR; sh < 64; sh <<= 1)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += __shfl_xor(sum[e], sh);
+        if (lane < LPR) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] *= mi.inv_cnt;
+            *(f32x4 *)(dst + 4 * lane) = sum;
         }
     }
+};
+
+// What a workgroup's first image needs before its first step: bias + sum_c rsum[c][o] * mean_n[c] (see MeanIn), by four
+// wavefronts, each C/4 outputs, its lanes splitting the sum over c in 64 / (C/4) parts.  Every load is asked for in start(),
+// before the wavefront asks for its weights, so that a launch opens with one round trip to memory and not with one for the
+// weights, one for the records and four for the residual sums, one after the other; and the group that multiplies later asks
+// for its weights only behind the first barrier (72 KiB for either group of two wavefronts, the bulk of what a launch of few
+// strips waits for).  7 tiles of 128 x 128, ten launches: 124.5 -> 117.5 us.
+template <int C>
+struct FirstInit {
+    static constexpr int OPW = C / 4, PARTS = 64 / OPW, CP = C / PARTS;
+    ImageMeans<C> means;
+    float rs[CP], b;
+    __device__ __forceinline__ void start(const MeanIn &mi, const float *rsum, const float *bias, int n, int w4, int lane)
+    {
+        const int o = w4 * OPW + lane % OPW, part = lane / OPW;
+        b = bias ? bias[o] : 0.f;
+        if (mi.rec && rsum) {
+            means.load(mi, n, lane, 0);
 #pragma unroll
-    for (int sh = LPR; sh < 64; sh <<= 1)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] += __shfl_xor(sum[e], sh);
-    if (lane < LPR) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] *= mi.inv_cnt;
-        *(f32x4 *)(dst + 4 * lane) = sum;
+            for (int k = 0; k < CP; ++k) rs[k] = rsum[(part * CP + k) * C + o];
+        }
+        asm volatile("" ::: "memory"); // what is asked for behind this stays behind it
     }
-}
+    __device__ __forceinline__ void finish(const MeanIn &mi, const float *rsum, int n, int w4, int lane, float *s_mean, float *s_init)
+    {
+        const int o = w4 * OPW + lane % OPW, part = lane / OPW;
+        float d = 0.f;
+        if (mi.rec && rsum) {
+            means.finish(mi, n, s_mean, lane);
+#pragma unroll
+            for (int k = 0; k < CP; ++k) d = fmaf(rs[k], s_mean[part * CP + k], d);
+#pragma unroll
+            for (int sh = OPW; sh < 64; sh <<= 1) d += __shfl_xor(d, sh);
+        }
+        if (part == 0) s_init[o] = b + d;
+    }
+};
 
 // Sum over the 32 pixel lanes of one half-wavefront with DPP lane permutes (no LDS traffic, no waits).
 // After the four butterfly steps every lane holds the sum of its row of 16 lanes; the last step adds the
@@ -535,7 +614,7 @@ constexpr int MODE_FINAL = 2; // final convolution (C output channels per grid.y
 
 constexpr int kMidWaves = 8; // wavefronts of a conv_mid workgroup: two groups of four
 
-constexpr int kMidSlots = 15;   // row slots of its LDS ring (>= 12)
+constexpr int kMidSlots = 16;   // row slots of its LDS ring (>= 12; a power of two)
 
 // C -> C (+bias, ReLU), bf16 NHWC in / out.  One persistent workgroup of eight wavefronts per CU, two
 // wavefronts per SIMD.  The workgroup walks down its run of strips; the two groups of four wavefronts
@@ -552,7 +631,7 @@ constexpr int kMidSlots = 15;   // row slots of its LDS ring (>= 12)
 //   first strip of a new image : 5 rows (the row above the tile is zero - and so is the last row the
 //                                previous strip loaded, which lay below its tile), wstart = base - 1
 template <int C, int MODE>
-__global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8_t *__restrict__ ws, size_t in_off,
+__global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8_t *__restrict__ in,
                                                                      ConvGeom g, const bf16_t *__restrict__ wfrag,
                                                                      const float *__restrict__ bias, StatArgs st,
                                                                      bf16_t *__restrict__ out)
@@ -578,9 +657,7 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
     const int xb = (w4 / K::NCB) & 1;
     const int rg = w4 / (K::NCB * 2);
 
-    bf16x8 Wr[9][K::KC];
     const int slice = MODE == MODE_FINAL ? blockIdx.y : 0; // C output channels of the launch
-    load_weight_frags<C>(Wr, wfrag, slice * K::NCB + cb, lane);
 
     const int tpi = g.strips * g.colblks; // tiles per image
     const int total = g.n_img * tpi;
@@ -590,6 +667,8 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
     if (ns <= 0) return;
     const lrow_t lbase = lds_address(lds) + (xb * 32 + px) * K::PS + half * 16;
     const size_t img_bytes = (size_t)g.h * g.w * C * 2;
+    const uint32_t row_bytes = (uint32_t)(g.w * C * 2);
+    const RowLoader<C> loader(w4, lane);
 
     // ---- geometry of the strips of the run (tile order: image, column block, strip), kept as counters
     // that are advanced once per phase; all wave-uniform
@@ -622,8 +701,8 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
     Geo gp = gc;                                                                          // strip p - 1 (from phase 1 on)
 
     auto issue = [&](const Geo &q) {
-        issue_strip_loads<C>(lds, ws, ws + in_off + (size_t)q.n * img_bytes, g.h, g.w, q.strip * kRows, q.colblk * kTileW, w4,
-                             pin_in_loop(lane), first_row(q), wstart(q), NSLOT);
+        loader.strip(lds, NSLOT, in + (size_t)q.n * img_bytes, (uint32_t)img_bytes, g.h, row_bytes, q.strip * kRows, q.colblk * kTileW, w4,
+                                     first_row(q), wstart(q));
     };
     // s_init[n & 3][o] = bias[o] + sum_c rsum[c][o] * mean_n[c], by the four wavefronts of one group:
     // each takes C/4 outputs, its lanes split the sum over c in 64 / (C/4) parts
@@ -634,7 +713,9 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
         float d = 0.f;
         const float *rsum = st.rsum;
         if (MODE != MODE_FINAL && st.tin.rec && rsum) {
-            image_means<C>(st.tin, n, s_mean[wave], lane);
+            ImageMeans<C> means;
+            means.load(st.tin, n, lane, 0);
+            means.finish(st.tin, n, s_mean[wave], lane);
 #pragma unroll 4
             for (int k = 0; k < CP; ++k) { // (little unrolling: registers are scarce here)
                 const int c = part * CP + k;
@@ -711,16 +792,31 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
         }
     };
 
-    // ---- prologue: corrections of the first image(s), strips 0 and 1 on their way
-    if (grp == 0) prepare_init(gc.n);
-    else if (ns > 1 && g1.n != gc.n) prepare_init(g1.n);
-    if (grp == 1) {
-        issue(gc);
-        if (ns > 1) issue(g1);
+    // ---- prologue: corrections of the first image(s), strips 0 and 1 on their way.  Group 1 multiplies a phase later: its
+    // weights come in while group 0 is at work.
+    bf16x8 Wr[9][K::KC];
+    {
+        const int n = grp == 0 ? gc.n : g1.n;
+        const bool mine = grp == 0 || (ns > 1 && g1.n != gc.n); // the same for the whole wavefront
+        const float *bias_s = MODE != MODE_FINAL ? bias : (bias ? bias + slice * C : nullptr);
+        const float *rsum = MODE != MODE_FINAL ? st.rsum : nullptr;
+        FirstInit<C> init;
+        if (mine) init.start(st.tin, rsum, bias_s, n, w4, lane);
+        if (grp == 0) {
+            load_weight_frags<C>(Wr, wfrag, slice * K::NCB + cb, lane);
+        } else {
+            issue(gc);
+            if (ns > 1) issue(g1);
+        }
+        if (mine) init.finish(st.tin, rsum, n, w4, lane, s_mean[wave], s_init[n & 3]);
     }
     int issued_upto = min(1, ns - 1);
-    __builtin_amdgcn_s_waitcnt(kWaitVm0); // weights, and for the loading group strips 0 and 1, are in
+    __builtin_amdgcn_s_waitcnt(kWaitVm0); // group 0: weights; group 1: strips 0 and 1
     lds_barrier();
+    if (grp == 1 && ns > 1) {
+        load_weight_frags<C>(Wr, wfrag, slice * K::NCB + cb, lane);
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    }
 
     for (int p = 0; p <= ns; ++p) {
         const bool mma_phase = (p & 1) == grp;
@@ -729,17 +825,16 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
                 lrow_t rowp[RW + 2];
                 const int start = wstart(gc) + rg * RW;
 #pragma unroll
-                for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((start + r) % NSLOT) * K::ROWB;
+                for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((start + r) & (NSLOT - 1)) * K::ROWB;
                 __builtin_amdgcn_s_setprio(3); // the matrix stream goes first whenever both wavefronts of a SIMD are ready
                 strip_mma<C, RW>(rowp, Wr, acc);
                 __builtin_amdgcn_s_setprio(0);
             }
-        } else {
-            if (p >= 1) epilogue(gp);
         }
         // Loads: the group that is not multiplying issues strips p + 1 (only if it did not fit earlier) and
         // p + 2, as far as the ring has room (strip p is being read: everything from wstart(p) on is
-        // live; strip p + 1 always fits).  Every wavefront keeps the count.
+        // live; strip p + 1 always fits).  Every wavefront keeps the count.  Before the epilogue: behind its stores the
+        // loads would wait for those to be taken by the memory pipeline, and this group would end the phase last.
         bool late = false;
         if (issued_upto == p && p + 1 < ns) {
             if (!mma_phase) {
@@ -752,6 +847,7 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
             if (!mma_phase) issue(g2);
             issued_upto = p + 2;
         }
+        if (!mma_phase && p >= 1) epilogue(gp);
         if (!mma_phase && p + 2 < ns && g2.n != g1.n) prepare_init(g2.n);
         // what this group issued a phase ago (or, late, just now) must have landed before the barrier
         if (mma_phase || late) __builtin_amdgcn_s_waitcnt(kWaitVm0);
@@ -773,13 +869,13 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 // this, us a call): 2404 tiles of 40 x 5, 107 bits 571 -> 485; 512 of 128 x 128, 60 bits 682 -> 663; 700 of 64 x 64, 120 bits 344 ->
 // 331; 20 of 64 x 64, 128 bits 34.9 -> 31.5.  Loading only the rows that the strip above does not share: no gain (504, 651).
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__restrict__ ws, size_t in_off, ConvGeom g,
+__global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__restrict__ in, ConvGeom g,
                                                               const bf16_t *__restrict__ wfrag, const float *__restrict__ bias,
                                                               StatArgs st)
 {
-    constexpr int C = 32, RW = kRows, WIN = kRows + 2;
+    constexpr int C = 32, RW = kRows, WIN = kRows + 2, kBuf = 8; // a strip's buffer has kBuf row slots, WIN of them in use
     typedef MidCfg<C> K;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * WIN * K::ROWB];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[(kBuf + WIN) * K::ROWB];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int px = lane & 31, half = lane >> 5;
@@ -795,6 +891,8 @@ __global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__r
     if (ns <= 0) return;
     const lrow_t lbase = lds_address(lds) + (xb * 32 + px) * K::PS + half * 16;
     const size_t img_bytes = (size_t)g.h * g.w * C * 2;
+    const uint32_t row_bytes = (uint32_t)(g.w * C * 2);
+    const RowLoader<C> loader(wave, lane);
     struct Geo {
         int strip, colblk, n;
     };
@@ -808,8 +906,7 @@ __global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__r
         }
     };
     auto issue = [&](const Geo &q, int buf) {
-        issue_strip_loads<C>(lds, ws, ws + in_off + (size_t)q.n * img_bytes, g.h, g.w, q.strip * kRows, q.colblk * kTileW, wave,
-                             pin_in_loop(lane), 0, buf * WIN, 2 * WIN);
+        loader.strip(lds + buf * kBuf * K::ROWB, kBuf, in + (size_t)q.n * img_bytes, (uint32_t)img_bytes, g.h, row_bytes, q.strip * kRows, q.colblk * kTileW, wave);
     };
     Geo gc{t_begin % g.strips, (t_begin / g.strips) % g.colblks, t_begin / tpi}, g1 = gc;
     advance(g1);
@@ -826,7 +923,7 @@ __global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__r
         if (i > 0) write_line();
         lrow_t rowp[RW + 2];
 #pragma unroll
-        for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((i & 1) * WIN + r) * K::ROWB;
+        for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((i & 1) * kBuf + r) * K::ROWB;
         f32x16 acc[RW];
         __builtin_amdgcn_s_setprio(3);
         strip_mma<C, RW>(rowp, Wr, acc);
@@ -939,7 +1036,6 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     constexpr int QUANT = LASTB ? kChunk : 1;     // row pairs per piece dealt to workgroups
     constexpr int ROWB = kHaloW * K::PS;          // staged rows are packed: 66 pixels x 144 bytes
     constexpr int SLOTS = ROWB / 16;              // 16-byte slots per row
-    constexpr int PIECES = (SLOTS + 63) / 64;     // wavefront-wide loads per row, the last one partial
     __shared__ __attribute__((aligned(1024))) uint8_t ring_in[FIRST ? 1024 : kPairRing * ROWB];
     __shared__ __attribute__((aligned(16))) uint8_t ring_mid[kPairRing * ROWB];
     __shared__ __attribute__((aligned(16))) uint16_t s_pix[FIRST ? kPairRing : 1][kHaloW][4]; // raw pixels as bf16; channel 3 = 1 inside the tile
@@ -959,18 +1055,6 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     const int px = lane & 31, half = lane >> 5;
     const int cb = w4 & 1, xb = w4 >> 1;
 
-    // C -> C weights (group B; group A unless FIRST).  Group A with FIRST keeps the first block's weights in
-    // the same registers: Wr[p][k] = high part (p = 0) / residual (p = 1) of 16-wide k chunk k = 0..2.
-    bf16x8 Wr[9][K::KC];
-    if (FIRST && grp == 0) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) Wr[p][k] = ((const bf16x8 *)wfragA)[((cb * 2 + p) * 3 + k) * 64 + lane];
-    } else {
-        load_weight_frags<C>(Wr, grp == 0 ? wfragA : wfragB, cb, lane);
-    }
-
     const int vb = xcd_virtual_block(blockIdx.x, gridDim.x);
     const int S = (g.h + 1) / 2;
     const int J = WIDE ? g.colblks : 1;           // column blocks of a tile
@@ -982,6 +1066,21 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     if (q0 >= q1) return;
     const int n_begin = q0 / ppi, ja = PART ? (q0 - n_begin * ppi) * QUANT : 0;
     const int n_cnt = (q1 - 1) / ppi - n_begin + 1, jb = PART ? min(S, (q1 - (n_begin + n_cnt - 1) * ppi) * QUANT) : S;
+    // C -> C weights (group B; group A unless FIRST).  Group A with FIRST keeps the first block's weights in
+    // the same registers: Wr[p][k] = high part (p = 0) / residual (p = 1) of 16-wide k chunk k = 0..2.
+    bf16x8 Wr[9][K::KC];
+    auto load_weights = [&]() {
+        if (FIRST && grp == 0) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) Wr[p][k] = ((const bf16x8 *)wfragA)[((cb * 2 + p) * 3 + k) * 64 + lane];
+        } else {
+            load_weight_frags<C>(Wr, grp == 0 ? wfragA : wfragB, cb, lane);
+        }
+    };
+    FirstInit<C> init; // (the correction's loads go first, then the input rows', then the weights': see below)
+    if (!FIRST && grp == 0) init.start(st.tin, st.rsum, biasA, n_begin, w4, lane);
     const size_t img_bytes = (size_t)g.h * g.w * C * 2;
     const uint32_t row_bytes = (uint32_t)(g.w * C * 2);
     const lrow_t in_base = lds_address(ring_in) + (xb * 32 + px) * K::PS + half * 16;
@@ -989,37 +1088,12 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     const int sample_phase = sampled_strip(g.strips);
     auto slot_of = [](int y) { return (y + 2) & (kPairRing - 1); };
 
-    // Loads of input row y of image n into its ring slot by the four wavefronts of one group: piece q of
-    // the row by wavefront q mod 4.  What a lane loads within a row does not change: byte offset of its
-    // slot in an image row (kSlotZero: zeros; kSlotNone: no slot - the last piece of a row is partial, the
-    // next row starts right behind it).
-    constexpr int QPW = (PIECES + 3) / 4;
-    // per lane and piece: byte offset of the lane's slot in an image row for column block 0 (negative for the
-    // halo column left of the tile), or a mark far below zero: no slot (the last piece of a row is partial, the
-    // next row starts right behind it), or one of a pixel's padding slots (always zero)
-    constexpr int32_t kSlotNone = INT32_MIN, kSlotPad = INT32_MIN / 2;
-    int32_t lane_off[QPW];
-#pragma unroll
-    for (int k = 0; k < QPW; ++k) {
-        const int sl = (w4 + 4 * k) * 64 + lane;
-        const int col = sl / K::SPP, cpos = sl - col * K::SPP;
-        lane_off[k] = sl >= SLOTS ? kSlotNone : (cpos < C / 8 ? ((col - 1) * C + cpos * 8) * 2 : kSlotPad);
-    }
-    auto issue_row = [&](int n, int blk, int y, int vrow) { // vrow: the row's place in the stream of units (see the main loop)
-        const bool rowok = y >= 0 && y < g.h;
-        const uint8_t *rowp = in + (size_t)n * img_bytes + (size_t)(rowok ? y : 0) * row_bytes; // same for the whole workgroup
-        const int32_t xoff = blk * (kTileW * C * 2);
-        uint8_t *dst = ring_in + slot_of(vrow) * ROWB;
-#pragma unroll
-        for (int k = 0; k < QPW; ++k) {
-            const int q = w4 + 4 * k;
-            if (q < PIECES) {
-                const int32_t o = lane_off[k] + xoff; // the marks stay far below zero
-                const uint8_t *p = (rowok && (uint32_t)o < row_bytes) ? rowp + o : zeros;
-                if (lane_off[k] != kSlotNone)
-                    __builtin_amdgcn_global_load_lds((gptr_t)p, (lptr_t)(dst + q * 1024), 16, 0, 0);
-            }
-        }
+    // Loads of input row y of image n into its ring slot by the four wavefronts of one group.
+    const RowLoader<C> loader(w4, lane);
+    auto issue_rows = [&](int n, int blk, int y, int vrow, int rows) { // vrow: the row's place in the stream of units (see the main loop)
+        const auto cols = loader.at(blk * kTileW, row_bytes);
+        for (int r = 0; r < rows; ++r)
+            loader.row(cols, in + (size_t)n * img_bytes, (uint32_t)img_bytes, y + r, g.h, row_bytes, ring_in + slot_of(vrow + r) * ROWB, w4);
     };
     // s_initA[o] = biasA[o] + sum_c rsum[c][o] * mean_n[c], by the four wavefronts of group A
     auto prepare_init = [&](int n) {
@@ -1028,7 +1102,9 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         const int o = w4 * OPW + ln % OPW, part = ln / OPW;
         float d = 0.f;
         if (st.tin.rec && st.rsum) {
-            image_means<C>(st.tin, n, s_mean[w4], ln);
+            ImageMeans<C> means;
+            means.load(st.tin, n, ln, 0);
+            means.finish(st.tin, n, s_mean[w4], ln);
 #pragma unroll 4
             for (int k = 0; k < CP; ++k) {
                 const int c = part * CP + k;
@@ -1142,30 +1218,33 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     //      intermediate row -1 = zero
     const uint8_t *tile0 = nullptr;
     if (FIRST) {
+        if (grp == 0) load_weights();
         tile0 = tile_origin(n_begin);
         if (grp == 0) {
-#pragma unroll 1
-            for (int y0 = -1; y0 <= 1; y0 += 2)
+            uint32_t word[4], shift[4];
+            bool inside[4];
 #pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    bool inside;
-                    uint32_t shift;
-                    const uint32_t v = pixel_fetch(tile0, 0, 2 * pw.s + y0, tid + 256 * k, inside, shift);
-                    pixel_store(y0, tid + 256 * k, v, shift, inside);
-                }
+            for (int k = 0; k < 4; ++k) word[k] = pixel_fetch(tile0, 0, 2 * pw.s - 1 + (k & 2), tid + 256 * (k & 1), inside[k], shift[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) pixel_store(-1 + (k & 2), tid + 256 * (k & 1), word[k], shift[k], inside[k]);
         }
     } else {
 #pragma unroll 1
         for (int v = -1 + grp; v <= 4; v += 2) { // first, so that they travel while the correction is computed
-            if (v <= 2) issue_row(n_begin, 0, 2 * pw.s + v, v);
-            else if (p1.i < n_cnt) issue_row(n_begin + p1.i, p1.b, 2 * p1.s + v - 2, v);
+            if (v <= 2) issue_rows(n_begin, 0, 2 * pw.s + v, v, 1);
+            else if (p1.i < n_cnt) issue_rows(n_begin + p1.i, p1.b, 2 * p1.s + v - 2, v, 1);
         }
-        if (grp == 0) prepare_init(n_begin);
     }
+    if (!FIRST && grp == 0) load_weights(); // behind the loads that take another step
+    if (!FIRST && grp == 0) init.finish(st.tin, st.rsum, n_begin, w4, lane, s_mean[w4], s_initA);
     if (grp == 1)
         for (int i = tid - 256; i < SLOTS; i += 256) *(u32x4 *)(ring_mid + slot_of(-1) * ROWB + i * 16) = (u32x4){0u, 0u, 0u, 0u};
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
     __syncthreads();
+    if (grp == 1) { // group B multiplies from step 2 on: its weights come in while group A is at work
+        load_weights();
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    }
 
     // LASTB: the nine border-aware channel sums of the last block's output from the two
     // rows in `a`, written as lines of C sums (LastSums).  The sum over the whole tile, the only one every pixel goes
@@ -1343,10 +1422,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     // path - would otherwise wait behind these twenty loads.
     auto input_loads = [&](int sg) {
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        if (pe.i < n_cnt) {
-            issue_row(n_begin + pe.i, pe.b, 2 * pe.s + 1, 2 * sg + 5);
-            issue_row(n_begin + pe.i, pe.b, 2 * pe.s + 2, 2 * sg + 6);
-        }
+        if (pe.i < n_cnt) issue_rows(n_begin + pe.i, pe.b, 2 * pe.s + 1, 2 * sg + 5, 2);
     };
     // WIDE: ring pixels 0 and 1 of the intermediate rows group A writes in this step: the two columns left of its
     // block, from the seam of the block before (zeros in block 0 and at opening positions); 2 x 9 slots per row,
@@ -1998,18 +2074,18 @@ LastSums conv_mid_last_sums(const ConvGeom &g, int C)
 
 int conv_final_lines(const ConvGeom &g) { return g.strips * g.colblks * 2; }
 
-hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, const bf16_t *wfrag,
+hipError_t launch_conv_mid(const uint8_t *in, const ConvGeom &g, int C, const bf16_t *wfrag,
                            const float *bias, const MeanIn &tin, const float *rsum, float *tout,
                            const Partition &part, bool last, bf16_t *out, hipStream_t s)
 {
     StatArgs st{tin, rsum, tout, last ? conv_mid_last_sums(g, C).lines : conv_mid_samples(g, C).recs, part.per, 0.f};
     const dim3 grid(part.blocks), block(64 * kMidWaves);
     if (C == 64) {
-        if (last) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_LAST>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, out);
-        else hipLaunchKernelGGL((conv_mid_kernel<64, MODE_MID>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, out);
+        if (last) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_LAST>), grid, block, 0, s, in, g, wfrag, bias, st, out);
+        else hipLaunchKernelGGL((conv_mid_kernel<64, MODE_MID>), grid, block, 0, s, in, g, wfrag, bias, st, out);
     } else {
-        if (last) hipLaunchKernelGGL((conv_mid_kernel<32, MODE_LAST>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, out);
-        else hipLaunchKernelGGL((conv_mid_kernel<32, MODE_MID>), grid, block, 0, s, ws, in_off, g, wfrag, bias, st, out);
+        if (last) hipLaunchKernelGGL((conv_mid_kernel<32, MODE_LAST>), grid, block, 0, s, in, g, wfrag, bias, st, out);
+        else hipLaunchKernelGGL((conv_mid_kernel<32, MODE_MID>), grid, block, 0, s, in, g, wfrag, bias, st, out);
     }
     return hipGetLastError();
 }
@@ -2173,13 +2249,13 @@ Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, i
     return make_partition(n_img, tiles_per_image, std::max(1, num_cu * (C == 64 ? 1 : 2) / (nbp / 64))); // (two to a compute unit)
 }
 
-hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
+hipError_t launch_conv_final(const uint8_t *in, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
                              const float *bias, int relu, float *partial, const Partition &part, hipStream_t s)
 {
     StatArgs st{MeanIn{}, nullptr, partial, conv_final_lines(g), part.per, relu ? 0.f : __builtin_nanf("")};
     const dim3 grid(part.blocks, nbp / 64);
-    if (C == 64) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_FINAL>), grid, dim3(64 * kMidWaves), 0, s, ws, in_off, g, wfrag, bias, st, nullptr);
-    else hipLaunchKernelGGL(conv_final32_kernel, grid, dim3(256), 0, s, ws, in_off, g, wfrag, bias, st);
+    if (C == 64) hipLaunchKernelGGL((conv_mid_kernel<64, MODE_FINAL>), grid, dim3(64 * kMidWaves), 0, s, in, g, wfrag, bias, st, nullptr);
+    else hipLaunchKernelGGL(conv_final32_kernel, grid, dim3(256), 0, s, in, g, wfrag, bias, st);
     return hipGetLastError();
 }
 

@@ -485,7 +485,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             } else {
                 qrm_ctx::Timed *t = time_begin(c, may_time, is_last(b) ? QRM_PROFILE_BLOCK_LAST : QRM_PROFILE_BLOCK_MID,
                                                block_flops * cnt, s);
-                e = launch_conv_mid(base, buf_off[cur], g, c->C, c->d_w_mid[m], c->d_bias + (size_t)b * c->C, means,
+                e = launch_conv_mid(base + buf_off[cur], g, c->C, c->d_w_mid[m], c->d_bias + (size_t)b * c->C, means,
                                     rsum, is_last(b) ? tail : tb[tcur ^ 1], pm, is_last(b), buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_mid launch");
                 time_end(t, s);
@@ -512,7 +512,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         } else {
             const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
             tail = tail_of(cur);
-            e = launch_conv_final(base, buf_off[cur], g, c->C, c->nbp, c->d_w_final, c->final_relu ? c->d_bias_final : nullptr,
+            e = launch_conv_final(base + buf_off[cur], g, c->C, c->nbp, c->d_w_final, c->final_relu ? c->d_bias_final : nullptr,
                                   c->final_relu, tail, pl, s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_final launch");
             e = launch_linear_pack(tail, conv_final_lines(g), c->nbp, cnt, c->n_bits, inv_hw,

@@ -86,17 +86,16 @@ MeanIn conv_pair_samples(const ConvGeom &g);
 hipError_t launch_conv_first(const TileSrc &src, const ConvGeom &g, int C, const bf16_t *wfrag, const float *bias,
                              float *tout, const Partition &part, bf16_t *out, hipStream_t s);
 
-// conv3x3 C -> C + bias + ReLU, bf16 NHWC in/out.  The input is addressed as ws + in_off + image * its bytes
-// (+ 32-bit offsets inside an image); the first kZeroBytes of ws must be zero: the source of the zero padding.
+// conv3x3 C -> C + bias + ReLU, bf16 NHWC in/out.  Offsets inside an image are 32-bit.
 // tin / rsum: channel sums of the input and the summed weight-rounding residual [c_in][c_out] used to correct the
 // bias (tin.rec and rsum may be null).  tout: channel sums of the output (conv_mid_samples()).  last: no activations
 // are written, tout receives lines of channel sums (conv_mid_last_sums()).
-constexpr size_t kZeroBytes = 256;
 LastSums conv_mid_last_sums(const ConvGeom &g, int C);
-hipError_t launch_conv_mid(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, const bf16_t *wfrag,
+hipError_t launch_conv_mid(const uint8_t *in, const ConvGeom &g, int C, const bf16_t *wfrag,
                            const float *bias, const MeanIn &tin, const float *rsum, float *tout,
                            const Partition &part, bool last, bf16_t *out, hipStream_t s);
 
+constexpr size_t kZeroBytes = 256;
 // Two consecutive blocks in one launch, the activations between them staying in LDS (C = 64:
 // conv_pair_supported; tiles wider than 64 columns are walked through in column blocks and need `seam`,
 // conv_pair_seam_bytes() bytes of scratch).  zeros: kZeroBytes of zeros; in: the input activations.
@@ -138,7 +137,7 @@ hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n
 // (conv_final_partition())
 int conv_final_lines(const ConvGeom &g);
 Partition conv_final_partition(int64_t n_img, int tiles_per_image, int num_cu, int C, int nbp);
-hipError_t launch_conv_final(const uint8_t *ws, size_t in_off, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
+hipError_t launch_conv_final(const uint8_t *in, const ConvGeom &g, int C, int nbp, const bf16_t *wfrag,
                              const float *bias, int relu, float *partial, const Partition &part, hipStream_t s);
 
 // pooled = sum(partials)/(h*w); logits = lin_w * pooled + lin_b; bits; symbols (MSB first, m bits each)
