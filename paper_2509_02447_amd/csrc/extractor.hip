@@ -269,9 +269,11 @@ __device__ __forceinline__ void frag_wait(bf16x8 &frag)
 // bytes, would otherwise drain the whole vector-memory queue (stores included) before the first read.
 // `rowp` holds the LDS byte address of each staged row for this lane.
 // The accumulators are not read; the first matrix instruction of every output row starts from zero.
-template <int C, int RW>
+// rows_read() is called when the wavefront has read all it needs of the rows, with the last few matrix instructions still to
+// be issued: a step's barrier put there lets the others go on meanwhile.
+template <int C, int RW, typename F>
 __device__ __forceinline__ void strip_mma(const lrow_t (&rowp)[RW + 2], const bf16x8 (&Wr)[9][C / 16],
-                                          f32x16 (&acc)[RW])
+                                          f32x16 (&acc)[RW], F &&rows_read)
 {
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     bool started[RW] = {};
@@ -296,6 +298,10 @@ __device__ __forceinline__ void strip_mma(const lrow_t (&rowp)[RW + 2], const bf
         constexpr int dx = set_dx(s2);
         constexpr int r = set_row(s2, j), kc = set_kc(s2, j);
         bf16x8 &fr = f[t % NF];
+        if constexpr (t == NT - NF + 1) {
+            rows_read();
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // LDS reads return in order: fragment t has landed once at most the NF - 1 reads issued after it
         // (fewer near the end) are outstanding
         frag_wait<(t + NF <= NT ? NF - 1 : NT - 1 - t)>(fr);
@@ -820,6 +826,19 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 
     for (int p = 0; p <= ns; ++p) {
         const bool mma_phase = (p & 1) == grp;
+        // Loads: the group that is not multiplying issues strips p + 1 (only if it did not fit earlier) and
+        // p + 2, as far as the ring has room (strip p is being read: everything from wstart(p) on is
+        // live; strip p + 1 always fits).  Every wavefront keeps the count.  Before the epilogue: behind its stores the
+        // loads would wait for those to be taken by the memory pipeline.
+        const bool load1 = issued_upto == p && p + 1 < ns;
+        if (load1) issued_upto = p + 1;
+        const bool load2 = issued_upto == p + 1 && p + 2 < ns && g2.base + rows_loaded(g2) - wstart(gc) <= NSLOT;
+        if (load2) issued_upto = p + 2;
+        // the end of a phase: what this group issued a phase ago (or, strip p + 1, just now) has landed
+        auto end_of_phase = [&](bool wait) {
+            if (wait) __builtin_amdgcn_s_waitcnt(kWaitVm0);
+            lds_barrier();
+        };
         if (mma_phase) {
             if (p < ns) {
                 lrow_t rowp[RW + 2];
@@ -827,31 +846,18 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 #pragma unroll
                 for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((start + r) & (NSLOT - 1)) * K::ROWB;
                 __builtin_amdgcn_s_setprio(3); // the matrix stream goes first whenever both wavefronts of a SIMD are ready
-                strip_mma<C, RW>(rowp, Wr, acc);
+                strip_mma<C, RW>(rowp, Wr, acc, [&]() { end_of_phase(true); });
                 __builtin_amdgcn_s_setprio(0);
+            } else {
+                end_of_phase(true);
             }
+        } else {
+            if (load1) issue(g1);
+            if (load2) issue(g2);
+            if (p >= 1) epilogue(gp);
+            if (p + 2 < ns && g2.n != g1.n) prepare_init(g2.n);
+            end_of_phase(load1);
         }
-        // Loads: the group that is not multiplying issues strips p + 1 (only if it did not fit earlier) and
-        // p + 2, as far as the ring has room (strip p is being read: everything from wstart(p) on is
-        // live; strip p + 1 always fits).  Every wavefront keeps the count.  Before the epilogue: behind its stores the
-        // loads would wait for those to be taken by the memory pipeline, and this group would end the phase last.
-        bool late = false;
-        if (issued_upto == p && p + 1 < ns) {
-            if (!mma_phase) {
-                issue(g1);
-                late = true; // this group reads it in the very next phase
-            }
-            issued_upto = p + 1;
-        }
-        if (issued_upto == p + 1 && p + 2 < ns && g2.base + rows_loaded(g2) - wstart(gc) <= NSLOT) {
-            if (!mma_phase) issue(g2);
-            issued_upto = p + 2;
-        }
-        if (!mma_phase && p >= 1) epilogue(gp);
-        if (!mma_phase && p + 2 < ns && g2.n != g1.n) prepare_init(g2.n);
-        // what this group issued a phase ago (or, late, just now) must have landed before the barrier
-        if (mma_phase || late) __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        lds_barrier();
         gp = gc;
         gc = g1;
         g1 = g2;
@@ -926,7 +932,7 @@ __global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__r
         for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((i & 1) * kBuf + r) * K::ROWB;
         f32x16 acc[RW];
         __builtin_amdgcn_s_setprio(3);
-        strip_mma<C, RW>(rowp, Wr, acc);
+        strip_mma<C, RW>(rowp, Wr, acc, []() {});
         __builtin_amdgcn_s_setprio(0);
         float t[16];
         auto row_sums = [&](auto full) { // as column_sums(), without a test per value where the strip has all of its rows
@@ -1450,6 +1456,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     for (int sg = 0; sg < n_steps; ++sg) {
         const bool fin = (FIRST || grp == 1) && sg >= 3 && pe.i < n_cnt && owns(pe); // rows accumulated in the previous step wait for their epilogue
         uint8_t *seam_rows_step = nullptr;
+        bool ended = false; // group B has passed the step's barrier
         if (grp == 0) {
             const int ln = pin_in_loop(tid & 63);
             const int pxl = ln & 31, hf = ln >> 5;
@@ -1495,7 +1502,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                     lrow_t rowp[RW + 2];
 #pragma unroll
                     for (int r = 0; r < RW + 2; ++r) rowp[r] = in_base + (uint32_t)slot_of(2 * sg - 1 + r) * ROWB;
-                    strip_mma<C, RW>(rowp, Wr, acc);
+                    strip_mma<C, RW>(rowp, Wr, acc, []() {});
                     input_loads(sg);
                 }
                 // epilogue: + bias and correction, ReLU, bf16 -> intermediate ring (zeros outside the tile)
@@ -1564,7 +1571,10 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                 lrow_t rowp[RW + 2];
 #pragma unroll
                 for (int r = 0; r < RW + 2; ++r) rowp[r] = mid_base + (uint32_t)slot_of(2 * (sg - 2) - 1 + r) * ROWB;
-                strip_mma<C, RW>(rowp, Wr, acc);
+                strip_mma<C, RW>(rowp, Wr, acc, [&]() {
+                    if (!FIRST) lds_barrier(); // the end of this group's step
+                });
+                ended = !FIRST;
                 if (FIRST) { // group A finishes these rows in the next step
                     float *dst = &s_accx[((((sg - 2) & 1) * 4 + w4) * 8) * 256 + ln * 4];
 #pragma unroll
@@ -1578,7 +1588,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         // End of the step
         if (!FIRST && WIDE && grp == 0) seam_flush(seam_rows_step, sg);
         if (WIDE && FIRST && grp == 1 && w4 == 0) __builtin_amdgcn_s_waitcnt(kWaitVm0); // the seam columns have landed
-        lds_barrier();
+        if (!ended) lds_barrier();
         if (sg >= w_start) advance(pw);
         if (sg >= e_start) advance(pe);
         if (FIRST) advance(p1);
