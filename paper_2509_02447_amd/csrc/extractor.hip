@@ -1420,42 +1420,55 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                 }
         }
     };
-    // !FIRST, group A, in the middle of its step (between its matrix work and its epilogue): what the wavefront
-    // issued a step ago - the two input rows of the step after this one, the seam columns - is waited for, then the
-    // two rows needed two steps from now are put on their way: rows 2s+1, 2s+2 of the position of step sg + 2.  Their
-    // ring slots were last read in the step before this one.  In the middle of the step, not at its end: the vector-memory instructions of a
-    // compute unit queue up behind each other, and group B's stores at the start of the next step - the critical
-    // path - would otherwise wait behind these twenty loads.
-    auto input_loads = [&](int sg) {
-        __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        if (pe.i < n_cnt) issue_rows(n_begin + pe.i, pe.b, 2 * pe.s + 1, 2 * sg + 5, 2);
-    };
     // WIDE: ring pixels 0 and 1 of the intermediate rows group A writes in this step: the two columns left of its
     // block, from the seam of the block before (zeros in block 0 and at opening positions); 2 x 9 slots per row,
-    // straight into LDS.  One wavefront issues them at the start of the step - a wavefront of the group that is
-    // not the step's critical path: vector-memory instructions of a compute unit queue up behind each other, and
-    // right after the barrier the queue still holds what was issued at the end of the previous step - and waits
-    // for them before the step's barrier.
+    // straight into LDS.  One wavefront issues them and waits for them before the step's barrier; the step in which their
+    // slots were last read is the one before.
     const size_t seam_half = (size_t)(2 * S) * kSeamRowBytes; // one of a workgroup's two seam buffers
     auto seam_loads = [&](int sg, const Pos &p) {
-        if (w4 != 0) return;
         const int ln = pin_in_loop(tid & 63);
         const bool have = p.b > 0 && computes(p);
-        const uint8_t *sp = st.seam + ((size_t)blockIdx.x * 2 + ((p.b & 1) ^ 1)) * seam_half + (size_t)(2 * p.s) * kSeamRowBytes;
+        const uint8_t *sp = st.seam + ((size_t)blockIdx.x * 2 + ((p.b & 1) ^ 1)) * seam_half + (size_t)(2 * (have ? p.s : 0)) * kSeamRowBytes;
         const int spx = ln / K::SPP, sslot = ln - spx * K::SPP;
+        const uint32_t voff = sslot < C / 8 ? (uint32_t)(spx * (C * 2) + sslot * 16) : kOutside;
+        if (ln < 2 * K::SPP) {
 #pragma unroll
-        for (int r = 0; r < RW; ++r) {
-            const uint8_t *src16 = (have && sslot < C / 8) ? sp + r * kSeamRowBytes + spx * (C * 2) + sslot * 16 : zeros;
-            if (ln < 2 * K::SPP)
-                __builtin_amdgcn_global_load_lds((gptr_t)src16, (lptr_t)(ring_mid + slot_of(2 * sg + r) * ROWB), 16, 0, 0);
+            for (int r = 0; r < RW; ++r)
+                load_lds16(sp, have ? RW * kSeamRowBytes : 0, voff, r * kSeamRowBytes, ring_mid + slot_of(2 * sg + r) * ROWB);
         }
     };
+    // !FIRST, group A, in the middle of its step (between its matrix work and its epilogue): what the wavefront
+    // issued a step ago - the two input rows of the step after this one, the seam columns it handed over - is waited for, then
+    // this step's seam columns and the two rows needed two steps from now are put on their way: rows 2s+1, 2s+2 of the position
+    // of step sg + 2.  Their ring slots were last read in the step before this one.  In the middle of the step, not at its end:
+    // the vector-memory instructions of a compute unit queue up behind each other, and group B's stores at the start of the
+    // next step - the critical path - would otherwise wait behind these twenty loads.
+    auto input_loads = [&](int sg) {
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        if (WIDE && w4 == 0) seam_loads(sg, pw);
+        if (pe.i < n_cnt) issue_rows(n_begin + pe.i, pe.b, 2 * pe.s + 1, 2 * sg + 5, 2);
+    };
+    constexpr int kFirstWaveLoads = RW * ((K::PIECES + 3) / 4); // of those, the first wavefront's for the rows
     f32x16 acc[RW];
     const int n_steps = n_pos + 2;
+    // !FIRST, group A: where its rows of the step lie and whether it multiplies them.  Found before the barrier in front of the
+    // step, where this group has time to spare: between the barrier and its first matrix instruction the matrix pipes
+    // would stand idle for it (a step of a middle pair 5720 -> 5360 cycles; 4096 tiles of 64 x 64 6540 -> 6460 us: the clock gives
+    // way as the pipes fill up).
+    lrow_t rowp_a[RW + 2];
+    bool a_computes = false;
+    auto prepare_step = [&](int sg) {
+#pragma unroll
+        for (int r = 0; r < RW + 2; ++r) {
+            rowp_a[r] = in_base + (uint32_t)slot_of(2 * sg - 1 + r) * ROWB;
+            asm volatile("" : "+v"(rowp_a[r])); // here, not where it is used
+        }
+        a_computes = pw.i < n_cnt && computes(pw);
+    };
+    if (!FIRST && grp == 0) prepare_step(0);
 #pragma unroll 1
     for (int sg = 0; sg < n_steps; ++sg) {
         const bool fin = (FIRST || grp == 1) && sg >= 3 && pe.i < n_cnt && owns(pe); // rows accumulated in the previous step wait for their epilogue
-        uint8_t *seam_rows_step = nullptr;
         bool ended = false; // group B has passed the step's barrier
         if (grp == 0) {
             const int ln = pin_in_loop(tid & 63);
@@ -1463,7 +1476,6 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
             const int xl = xb * 32 + pxl;          // this lane's column within the block
             const int x = pw.b * kTileW + xl;      // and within the tile
             uint8_t *seam_rows = nullptr;          // WIDE: where the seam columns of this step's rows go, if anywhere
-            if (WIDE && !FIRST) seam_loads(sg, pw); // (waited for at the end of the step, with this group's other loads)
             // FIRST: the raw pixels of virtual rows 2sg+3, 2sg+4 (window of step sg+1) start their way into registers
             uint32_t pv[2] = {0, 0}, psh[2] = {0, 0};
             bool pin[2] = {false, false};
@@ -1473,7 +1485,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
 #pragma unroll
                 for (int k = 0; k < 2; ++k) pv[k] = pixel_fetch(tile0, p1.b * kTileW, 2 * p1.s + 1, tid + 256 * k, pin[k], psh[k]);
             }
-            if (pw.i < n_cnt && computes(pw)) {
+            if (FIRST ? pw.i < n_cnt && computes(pw) : a_computes) {
                 if (FIRST) {
                     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1499,10 +1511,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                         for (int k = 0; k < 3; ++k) acc[r] = mfma32(Wr[1][k], bfrag[k], acc[r]);
                     }
                 } else {
-                    lrow_t rowp[RW + 2];
-#pragma unroll
-                    for (int r = 0; r < RW + 2; ++r) rowp[r] = in_base + (uint32_t)slot_of(2 * sg - 1 + r) * ROWB;
-                    strip_mma<C, RW>(rowp, Wr, acc, []() {});
+                    strip_mma<C, RW>(rowp_a, Wr, acc, []() {});
                     input_loads(sg);
                 }
                 // epilogue: + bias and correction, ReLU, bf16 -> intermediate ring (zeros outside the tile)
@@ -1550,7 +1559,19 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                 for (int k = 0; k < 2; ++k) pixel_store(2 * sg + 3, tid + 256 * k, pv[k], psh[k], pin[k]);
             }
             if (FIRST && WIDE) seam_flush(seam_rows, sg);
-            seam_rows_step = seam_rows;
+            if (!FIRST) { // the end of this group's step
+                if (WIDE) seam_flush(seam_rows, sg);
+                const bool rows_issued = pe.i < n_cnt;
+                advance(pw);
+                advance(pe);
+                prepare_step(sg + 1);
+                if (WIDE && w4 == 0) { // the seam columns have landed
+                    if (rows_issued) __builtin_amdgcn_s_waitcnt(kWaitVm0 | kFirstWaveLoads);
+                    else __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                }
+                lds_barrier();
+                continue;
+            }
             if (FIRST && fin) { // the rows group B accumulated in the previous step
                 const float *srcx = &s_accx[((((sg - 3) & 1) * 4 + w4) * 8) * 256 + ln * 4];
                 f32x16 a[RW];
@@ -1565,7 +1586,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
             }
         } else {
             const int ln = pin_in_loop(tid & 63);
-            if (WIDE && FIRST) seam_loads(sg, p1); // (group A is the critical path of this variant)
+            if (WIDE && FIRST && w4 == 0) seam_loads(sg, p1); // (group A is the critical path of this variant)
             if (!FIRST && fin) finish(acc, pe); // the rows accumulated in the previous step
             if (sg >= 2 && pw.i < n_cnt && owns(pw)) {
                 lrow_t rowp[RW + 2];
@@ -1586,7 +1607,6 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
             }
         }
         // End of the step
-        if (!FIRST && WIDE && grp == 0) seam_flush(seam_rows_step, sg);
         if (WIDE && FIRST && grp == 1 && w4 == 0) __builtin_amdgcn_s_waitcnt(kWaitVm0); // the seam columns have landed
         if (!ended) lds_barrier();
         if (sg >= w_start) advance(pw);
