@@ -21,7 +21,7 @@
 //    channels of one pixel: the epilogue writes two 16-byte stores per lane.
 //  * The first layer reads the u8 image directly (tile crop + normalisation fused: zero padding is
 //    applied in the normalised domain and never looks outside the tile); K = 9 taps x 4 channels (r, g,
-//    b, 0) = 36, padded to 48, with the weights as bf16 high part + bf16 residual.
+//    b, 1 inside the tile) = 36, with the weights as bf16 high part + bf16 residual: 72 of 80.
 //  * The last block writes no activations when the final convolution has no ReLU: final conv + global
 //    average pool are linear, so nine border-aware channel sums per image are all head_kernel needs to
 //    apply the final convolution (fp32 weights), the linear layer, the threshold and the symbol packing.
@@ -102,6 +102,18 @@ __device__ __forceinline__ uint32_t dither16(int x, int y)
     return h >> 16;
 }
 
+// 16 consecutive floats of LDS, e.g. a lane's biases
+__device__ __forceinline__ f32x16 load16(const float *p)
+{
+    f32x16 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const f32x4 w = *(const f32x4 *)(p + 4 * q);
+        v[4 * q] = w[0]; v[4 * q + 1] = w[1]; v[4 * q + 2] = w[2]; v[4 * q + 3] = w[3];
+    }
+    return v;
+}
+
 // two fp32 -> packed bf16, each truncated after `dither` (< 2^16) has been added to its bits, with ReLU
 // applied on the packed pair: a negative bf16 has its sign bit set, i.e. is negative as a 16-bit integer, so
 // max(.,0) on the halves clamps it.  (Plain instructions: the compiler puts the wait states a matrix result
@@ -170,6 +182,13 @@ __device__ __forceinline__ void load_lds16(const uint8_t *buf, uint32_t bytes, u
 {
     __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(buf), 0, (int)bytes, 0x00020000);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)dst, 16, voff, soff, 0, 0);
+}
+
+// 16 bytes per lane to offset voff + soff of the `bytes` bytes at `buf`; what lies outside is dropped
+__device__ __forceinline__ void store16(void *buf, uint32_t bytes, uint32_t voff, int soff, u32x4 v)
+{
+    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(buf, 0, (int)bytes, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, voff, soff, 0);
 }
 
 template <int C>
@@ -268,14 +287,18 @@ __device__ __forceinline__ void frag_wait(bf16x8 &frag)
 // their waits are written as assembly: the compiler, not knowing which direct-to-LDS load fills which
 // bytes, would otherwise drain the whole vector-memory queue (stores included) before the first read.
 // `rowp` holds the LDS byte address of each staged row for this lane.
-// The accumulators are not read; the first matrix instruction of every output row starts from zero.
+// The accumulators are not read; the first matrix instruction of every output row starts from `first`.
+// `first` (zero, or the bias) starts the sums.
 // rows_read() is called when the wavefront has read all it needs of the rows, with the last few matrix instructions still to
 // be issued: a step's barrier put there lets the others go on meanwhile.
+// The code begins on a boundary of 32 bytes: where its eight-byte instructions happened to straddle those of the instruction
+// fetch, a launch took up to a fifth longer (the last pair of 1024 tiles of 64 x 64: 406 us, 487 without).
+constexpr f32x16 kZeroAcc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 template <int C, int RW, typename F>
 __device__ __forceinline__ void strip_mma(const lrow_t (&rowp)[RW + 2], const bf16x8 (&Wr)[9][C / 16],
-                                          f32x16 (&acc)[RW], F &&rows_read)
+                                          f32x16 (&acc)[RW], const f32x16 &first, F &&rows_read)
 {
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    asm volatile(".p2align 5");
     bool started[RW] = {};
     typedef MidCfg<C> K;
     constexpr int NP = (RW + 2) / 2;  // row pairs
@@ -310,7 +333,7 @@ __device__ __forceinline__ void strip_mma(const lrow_t (&rowp)[RW + 2], const bf
             const int orow = r - dy;
             if (orow >= 0 && orow < RW) {
                 if (!started[orow]) {
-                    acc[orow] = mfma32(Wr[dy * 3 + dx][kc], fr, zero);
+                    acc[orow] = mfma32(Wr[dy * 3 + dx][kc], fr, first);
                     started[orow] = true;
                 } else {
                     acc[orow] = mfma32(Wr[dy * 3 + dx][kc], fr, acc[orow]);
@@ -846,7 +869,7 @@ __global__ __launch_bounds__(64 * kMidWaves, 1) void conv_mid_kernel(const uint8
 #pragma unroll
                 for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((start + r) & (NSLOT - 1)) * K::ROWB;
                 __builtin_amdgcn_s_setprio(3); // the matrix stream goes first whenever both wavefronts of a SIMD are ready
-                strip_mma<C, RW>(rowp, Wr, acc, [&]() { end_of_phase(true); });
+                strip_mma<C, RW>(rowp, Wr, acc, kZeroAcc, [&]() { end_of_phase(true); });
                 __builtin_amdgcn_s_setprio(0);
             } else {
                 end_of_phase(true);
@@ -932,7 +955,7 @@ __global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__r
         for (int r = 0; r < RW + 2; ++r) rowp[r] = lbase + (uint32_t)((i & 1) * kBuf + r) * K::ROWB;
         f32x16 acc[RW];
         __builtin_amdgcn_s_setprio(3);
-        strip_mma<C, RW>(rowp, Wr, acc, []() {});
+        strip_mma<C, RW>(rowp, Wr, acc, kZeroAcc, []() {});
         __builtin_amdgcn_s_setprio(0);
         float t[16];
         auto row_sums = [&](auto full) { // as column_sums(), without a test per value where the strip has all of its rows
@@ -974,11 +997,15 @@ __global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__r
 // of an image of h rows, S = ceil(h/2):
 //   A   : s < S: intermediate rows 2s, 2s+1 from input rows 2s-1 .. 2s+2; behind its matrix instructions it
 //         waits for the loads it issued a step ago and issues the direct-to-LDS loads of input rows 2s+5, 2s+6
-//         (needed in step s+2); then +bias (+correction), ReLU, bf16 -> intermediate ring (zeros outside the
+//         (needed in step s+2); then ReLU, bf16 -> intermediate ring (zeros outside the
 //         tile);  s == S: rows 2S, 2S+1 = zero padding
 //   B   : first the epilogue of the rows it accumulated in step s-1 (stores behind which its matrix
 //         instructions then run), then output rows 2j, 2j+1, j = s-2, from intermediate rows 2j-1 .. 2j+2
 //   end : one workgroup barrier
+// The sums start from bias (+ correction), which either group keeps in 16 registers: a third of an epilogue's vector
+// instructions and all of its LDS reads were the bias.  The groups have loops of their own: 219 registers instead of 243 and no
+// scalar ones spilled, which is where the bias found room.  A step of a middle pair takes 5200 cycles, 4608 of them matrix
+// instructions; what bounds a launch of bulk size is the clock that its power leaves (1.7 GHz of 2.4).
 // (All loads are group A's: the vector-memory instructions of a compute unit issue in order, and loads issued
 // by group B at the end of a step would sit in front of its own stores at the start of the next.)
 // Row y of either map lives in ring slot (y + 2) mod 8.
@@ -1047,12 +1074,14 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     __shared__ __attribute__((aligned(16))) uint16_t s_pix[FIRST ? kPairRing : 1][kHaloW][4]; // raw pixels as bf16; channel 3 = 1 inside the tile
     __shared__ __attribute__((aligned(16))) float s_initA[C]; // first block: bias (+ rounding-residual correction of the image)
     __shared__ __attribute__((aligned(16))) float s_biasB[C];
+    __shared__ __attribute__((aligned(16))) float s_zero[LASTB ? 4 : 16]; // (the sums that the statistics read hold their bias)
     __shared__ __attribute__((aligned(16))) float s_stat[LASTB ? 4 : 1][2][32]; // LASTB: sums of the first / last column
     __shared__ __attribute__((aligned(16))) float s_mean[4][C];
-    // FIRST: group B hands its fp32 accumulators to group A, which has time to spare, for the epilogue:
-    // [buffer = row pair parity][wavefront][row * 4 + channel quad][lane] x 4 floats
-    __shared__ __attribute__((aligned(16))) float s_accx[FIRST ? 2 * 4 * 8 * 256 : 4];
-    constexpr int kFinishGroup = FIRST ? 0 : 1; // the group that finishes output rows (stores, statistics)
+    // FIRST: group A has little matrix work, group B hands it the fp32 accumulators of the first of its two rows for the epilogue
+    // ([buffer = row pair parity][wavefront][channel quad][lane] x 4 floats): either group then has about 3700 cycles of a
+    // step's 4300 (both rows handed over: group A 4300, group B 3200 of 4400).
+    constexpr bool kHandOver = FIRST && !LASTB;
+    __shared__ __attribute__((aligned(16))) float s_accx[kHandOver ? 2 * 4 * 4 * 256 : 4];
     constexpr int kSkew = WIDE ? 1 : 0;         // group B's columns lie this far left of group A's
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1073,14 +1102,12 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     const int n_begin = q0 / ppi, ja = PART ? (q0 - n_begin * ppi) * QUANT : 0;
     const int n_cnt = (q1 - 1) / ppi - n_begin + 1, jb = PART ? min(S, (q1 - (n_begin + n_cnt - 1) * ppi) * QUANT) : S;
     // C -> C weights (group B; group A unless FIRST).  Group A with FIRST keeps the first block's weights in
-    // the same registers: Wr[p][k] = high part (p = 0) / residual (p = 1) of 16-wide k chunk k = 0..2.
+    // the same registers: Wr[p][k] = high part (p = 0) / residual (p = 1) of 16-wide k chunk k.
     bf16x8 Wr[9][K::KC];
     auto load_weights = [&]() {
         if (FIRST && grp == 0) {
 #pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) Wr[p][k] = ((const bf16x8 *)wfragA)[((cb * 2 + p) * 3 + k) * 64 + lane];
+            for (int f = 0; f < kFirstFrags; ++f) Wr[f / 3][f % 3] = ((const bf16x8 *)wfragA)[(cb * kFirstFrags + f) * 64 + lane];
         } else {
             load_weight_frags<C>(Wr, grp == 0 ? wfragA : wfragB, cb, lane);
         }
@@ -1121,42 +1148,43 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         }
         if (part == 0) s_initA[o] = biasA[o] + d;
     };
-    // FIRST: rows of the raw tile -> normalised bf16 pixels in s_pix, by the 256 threads of group A.
-    // Element e of a row pair: row e / 198, channel (e % 198) / 66, staged column (e % 198) % 66.
-    constexpr int kRowElems = 3 * kHaloW;
-    const int plane = src.H * src.W;
+    // FIRST: rows of the raw tile -> bf16 pixels in s_pix, by the 256 threads of group A: thread 66 c + col fetches channel c of
+    // staged column col, one row per load.  What stays the same from row to row is found once per unit (pixel_unit): the
+    // address in the tile's first row, and whether the column lies inside the tile.
     // The load is unconditional (coordinates clamped into the tile, the value dropped later when it lies
     // outside) and fetches the aligned dword that holds the byte (it never leaves the byte's page): a load under
     // a lane mask, or a byte load with its widening, would be waited for on the spot, and a step would then
     // contain two round trips to memory instead of hiding them behind its matrix work.
-    auto pixel_fetch = [&](const uint8_t *tile0, int x0, int y0, int e, bool &inside, uint32_t &shift) -> uint32_t {
-        const int ec = min(e, 2 * kRowElems - 1);
-        const int row = ec / kRowElems, rem = ec - row * kRowElems;
-        const int c = rem / kHaloW, col = rem - c * kHaloW;
-        const int ty = y0 + row, tx = x0 + col - 1;
-        inside = e < 2 * kRowElems && ty >= 0 && ty < g.h && tx >= 0 && tx < g.w;
-        const int tyc = clampi(ty, 0, g.h - 1), txc = clampi(tx, 0, g.w - 1);
-        const uintptr_t p = (uintptr_t)(tile0 + ((int64_t)c * plane + (int64_t)tyc * src.W + txc));
-        shift = (uint32_t)(p & 3u) * 8u;
+    constexpr int kRowElems = 3 * kHaloW;
+    const int plane = src.H * src.W;
+    const int pix_c = min(tid, kRowElems - 1) / kHaloW, pix_col = min(tid, kRowElems - 1) - pix_c * kHaloW;
+    const uint8_t *pix_at = nullptr; // this thread's byte in the unit's first row
+    bool pix_inside = false;
+    auto pixel_unit = [&](const uint8_t *tile0, int x0) {
+        const int tx = x0 + pix_col - 1;
+        pix_inside = (uint32_t)tx < (uint32_t)g.w;
+        pix_at = tile0 + ((int64_t)pix_c * plane + clampi(tx, 0, g.w - 1));
+    };
+    auto pixel_fetch = [&](int y, uint32_t &shift) -> uint32_t {
+        const uintptr_t p = (uintptr_t)(pix_at + (int64_t)clampi(y, 0, g.h - 1) * src.W);
+        shift = (uint32_t)p * 8u; // (the shift instruction looks at the low five bits)
         typedef const uint32_t __attribute__((address_space(1))) *global_word_t; // a global load, not a flat one
         return *(global_word_t)(p & ~(uintptr_t)3);
     };
-    auto pixel_store = [&](int y0, int e, uint32_t word, uint32_t shift, bool inside) { // y0: place of the first row in the stream of images
+    auto pixel_store = [&](int vrow, bool inside, uint32_t word, uint32_t shift) { // vrow: the row's place in the stream of units; inside: the pixel lies in the tile
         asm volatile("" : "+v"(word)); // the value is first looked at here, not where it was asked for
-        if (e < 2 * kRowElems) {
-            const int row = e / kRowElems, rem = e - row * kRowElems;
-            const int c = rem / kHaloW, col = rem - c * kHaloW;
-            // the byte itself, exact as bf16: the normalisation lives in the weights (see conv_first_kernel)
-            const float f = inside ? (float)((word >> shift) & 0xffu) : 0.f;
-            s_pix[slot_of(y0 + row)][col][c] = __builtin_bit_cast(uint16_t, (bf16_t)f);
-            if (c == 0) s_pix[slot_of(y0 + row)][col][3] = inside ? (uint16_t)0x3F80 : (uint16_t)0; // 1 inside the tile
-        }
+        // the byte itself, exact as bf16: the normalisation lives in the weights (see conv_first_kernel)
+        const uint32_t f = __builtin_bit_cast(uint32_t, (float)((word >> (shift & 31u)) & 0xffu)) >> 16;
+        uint8_t *dst = (uint8_t *)&s_pix[slot_of(vrow)][pix_col][pix_c];
+        if (tid < 2 * kHaloW) *(uint16_t *)dst = (uint16_t)(inside ? f : 0u);
+        else if (tid < kRowElems) *(uint32_t *)dst = inside ? f | 0x3F800000u : 0u; // the last colour and the fourth channel: 1 inside the tile
     };
 
     // ---- once per workgroup: biases, the halo columns of the intermediate ring, statistics
-    if (LASTB && grp == kFinishGroup) (&s_stat[w4][0][0])[lane] = 0.f;
+    if (LASTB && grp == 1) (&s_stat[w4][0][0])[lane] = 0.f;
     if (grp == 1) {
         if (tid - 256 < C) s_biasB[tid - 256] = biasB[tid - 256];
+        if (!LASTB && tid - 256 < 16) s_zero[tid - 256] = 0.f;
     } else if (FIRST) {
         if (tid < C) s_initA[tid] = biasA[tid];
     }
@@ -1200,17 +1228,16 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     int n_pos = n_cnt > 2 ? (n_cnt - 2) * J * (S + 1) : 0; // positions, opening position behind the last unit included
     n_pos += J * (closing(0) - opening(0) + 1);
     if (n_cnt > 1) n_pos += J * (closing(n_cnt - 1) + 2);
-    // A wavefront keeps the positions its group needs, no others: the loop is short of scalar registers (six positions
-    // in every wavefront spilled 16 to 35 of them and cost 1 .. 5 % of a launch).
+    // The two groups have loops of their own, and each keeps the positions it needs, no others: the loops are short of scalar
+    // registers (six positions in every wavefront of one loop spilled 16 to 35 of them and cost 1 .. 5 % of a launch).
     Pos pw{0, 0, max(ja - 1, 0)}; // group A: position sg; group B: position sg - 2
     Pos p1 = pw;                  // FIRST: group A's pixel loads, position sg + 1; group B's seam loads, position sg
     if (!FIRST || grp == 0) advance(p1);
-    Pos pe = pw;                  // epilogue, position sg - 3 (group B; FIRST: group A); otherwise group A's loads, sg + 2
+    Pos pe = pw;                  // epilogue of B's rows, position sg - 3 (group B), sg - 4 (kHandOver: group A); otherwise group A's loads, sg + 2
     if (!FIRST && grp == 0) {
         pe = p1;
         advance(pe);
     }
-    const int w_start = grp == 0 ? 0 : 2, e_start = !FIRST && grp == 0 ? 0 : 3; // the steps the positions move from
     auto tile_origin = [&](int n) {
         int oy = 0, ox = 0;
         if (src.off) {
@@ -1220,19 +1247,26 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         return src.img + (int64_t)n * 3 * plane + (int64_t)oy * src.W + ox;
     };
 
+    // FIRST, group A: the unit of position p begins
+    const uint8_t *tile0 = nullptr;
+    auto pixel_first_unit = [&](const Pos &p) {
+        if (p.b == 0) tile0 = tile_origin(n_begin + p.i); // the next image
+        pixel_unit(tile0, p.b * kTileW);
+    };
+
     // ---- before the first step: correction of the first image, its input rows -1 .. 4 (FIRST: -1 .. 2),
     //      intermediate row -1 = zero
-    const uint8_t *tile0 = nullptr;
     if (FIRST) {
         if (grp == 0) load_weights();
         tile0 = tile_origin(n_begin);
         if (grp == 0) {
             uint32_t word[4], shift[4];
-            bool inside[4];
+            pixel_unit(tile0, 0);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) word[k] = pixel_fetch(tile0, 0, 2 * pw.s - 1 + (k & 2), tid + 256 * (k & 1), inside[k], shift[k]);
+            for (int k = 0; k < 4; ++k) word[k] = pixel_fetch(2 * pw.s - 1 + k, shift[k]);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) pixel_store(-1 + (k & 2), tid + 256 * (k & 1), word[k], shift[k], inside[k]);
+            for (int k = 0; k < 4; ++k) pixel_store(-1 + k, pix_inside && (uint32_t)(2 * pw.s - 1 + k) < (uint32_t)g.h, word[k], shift[k]);
+            if (p1.i < n_cnt && p1.s == opening(p1.i)) pixel_first_unit(p1);
         }
     } else {
 #pragma unroll 1
@@ -1260,7 +1294,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     // 16 values to the LDS accumulators, in the wavefronts that contain such a column only; a line per chunk.  First /
     // last row and the four corners: lines of their own, in the (two) steps that contain those rows.
     float run_sum = 0.f;
-    auto last_block_statistics = [&](const f32x16 (&a)[RW], const float *si, const Pos &p, int x, int x0w, int pxl, int hf) {
+    auto last_block_statistics = [&](const f32x16 (&a)[RW], const Pos &p, int x, int x0w, int pxl, int hf) {
         const int j = p.s;
         float *stat = &s_stat[w4][0][hf * 16];
         float *lines = st.tout + (int64_t)(n_begin + p.i) * st.out_recs * C + cb * 32 + hf * 16;
@@ -1268,16 +1302,11 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         const bool allcols = x0w >= 0 && x0w + 32 <= g.w; // same for the whole wavefront
         const bool row1 = 2 * j + 1 < g.h;                // (row 2j always lies in the tile)
         const bool has_first = x0w <= 0 && x0w + 32 > 0, has_last = x0w <= g.w - 1 && g.w - 1 < x0w + 32;
-        float bias[16], t[16];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const f32x4 bq = *(const f32x4 *)(si + 4 * q);
-            bias[4 * q] = bq[0]; bias[4 * q + 1] = bq[1]; bias[4 * q + 2] = bq[2]; bias[4 * q + 3] = bq[3];
-        }
+        float t[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const float r1 = fmaxf(a[1][v] + bias[v], 0.f);
-            t[v] = fmaxf(a[0][v] + bias[v], 0.f) + (row1 ? r1 : 0.f);
+            const float r1 = fmaxf(a[1][v], 0.f);
+            t[v] = fmaxf(a[0][v], 0.f) + (row1 ? r1 : 0.f);
         }
         if (!allcols) {
 #pragma unroll
@@ -1324,7 +1353,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const float av = second ? a[1][v] : a[0][v];
-                    rv[v] = colok ? fmaxf(av + bias[v], 0.f) : 0.f;
+                    rv[v] = colok ? fmaxf(av, 0.f) : 0.f;
                 }
                 const float y = reduce16_over_half(rv, pxl);
                 if ((pxl & 1) == 0) lines[(st.sum_rows + (which * J + p.b) * 2 + xb) * C + reduce16_index(pxl)] = y;
@@ -1334,75 +1363,38 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         }
     };
 
-    // bias, ReLU, bf16, stores (or nothing: LASTB) and statistics of output rows 2j, 2j+1 of column block blk of
-    // image n held in `a`
-    auto finish = [&](const f32x16 (&a)[RW], const Pos &p) {
+    // Output row 2j + r of column block blk of image n held in `a`: ReLU and bf16, then the stores.
+    auto packed_row = [&](const f32x16 &a, uint32_t dither, u32x4 (&pk)[2]) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) pk[v / 4][v % 4] = pack_bf16_relu(a[2 * v], a[2 * v + 1], dither, true);
+    };
+    auto finish_pack = [&](const f32x16 &a, int r, const Pos &p, u32x4 (&pk)[2]) {
+        const int ln = pin_in_loop(tid & 63);
+        packed_row(a, dither16(p.b * kTileW - kSkew + xb * 32 + (ln & 31), 2 * p.s) ^ ((uint32_t)r << 15), pk); // the pair's second row: half a step apart
+    };
+    auto finish_store = [&](int r, const Pos &p, const u32x4 (&pk)[2]) {
+        const int ln = pin_in_loop(tid & 63);
+        const int x = p.b * kTileW - kSkew + xb * 32 + (ln & 31), y = 2 * p.s + r; // (x = -1 in block 0 of a wide tile)
+        const uint32_t voff = (uint32_t)x < (uint32_t)g.w ? (uint32_t)((x * C + cb * 32 + (ln >> 5) * 16) * 2) : kOutside;
+        uint8_t *dst = (uint8_t *)out + (size_t)(n_begin + p.i) * img_bytes; // y: the same for the whole workgroup
+#pragma unroll
+        for (int hq = 0; hq < 2; ++hq) store16(dst, y < g.h ? (uint32_t)img_bytes : 0, voff, y < g.h ? y * (int)row_bytes + hq * 16 : 0, pk[hq]);
+    };
+    // Statistics of output rows 2j, 2j+1
+    auto finish_statistics = [&](const f32x16 (&a)[RW], const Pos &p) {
         const int n = n_begin + p.i, blk = p.b, j = p.s;
         const int ln = pin_in_loop(tid & 63);
         const int pxl = ln & 31, hf = ln >> 5;
-        const int x_lo = blk * kTileW - kSkew;     // first of the workgroup's 64 output columns (-1 in block 0 of a wide tile)
+        const int x_lo = blk * kTileW - kSkew;
         const int x = x_lo + xb * 32 + pxl;
-        const float *si = &s_biasB[cb * 32 + hf * 16];
-        if (!LASTB) {
-            // address = uniform start of the row pair + what the lane adds
-            bf16_t *rows = out + ((size_t)n * g.h + 2 * j) * ((size_t)g.w * C);
-            const int le = x * C + cb * 32 + hf * 16;
-            const int rstride = g.w * C;
-            const uint32_t dbase = dither16(x, 2 * j);
-            const bool full = 2 * j + RW <= g.h && x_lo >= 0 && x_lo + kTileW <= g.w; // same for the whole workgroup
-            if (full) { // the common case: straight-line code, no predicates
-#pragma unroll
-                for (int hq = 0; hq < 2; ++hq) {
-                    const f32x4 b0 = *(const f32x4 *)(si + 8 * hq), b1 = *(const f32x4 *)(si + 8 * hq + 4);
-#pragma unroll
-                    for (int r = 0; r < RW; ++r) {
-                        const uint32_t dth = dbase ^ ((uint32_t)r << 15); // the pair's second row: half a step apart
-                        u32x4 pk;
-                        pk[0] = pack_bf16_relu(a[r][8 * hq + 0] + b0[0], a[r][8 * hq + 1] + b0[1], dth, true);
-                        pk[1] = pack_bf16_relu(a[r][8 * hq + 2] + b0[2], a[r][8 * hq + 3] + b0[3], dth, true);
-                        pk[2] = pack_bf16_relu(a[r][8 * hq + 4] + b1[0], a[r][8 * hq + 5] + b1[1], dth, true);
-                        pk[3] = pack_bf16_relu(a[r][8 * hq + 6] + b1[2], a[r][8 * hq + 7] + b1[3], dth, true);
-                        *(u32x4 *)(rows + (le + r * rstride + 8 * hq)) = pk;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int hq = 0; hq < 2; ++hq) {
-                    const f32x4 b0 = *(const f32x4 *)(si + 8 * hq), b1 = *(const f32x4 *)(si + 8 * hq + 4);
-#pragma unroll
-                    for (int r = 0; r < RW; ++r) {
-                        const uint32_t dth = dbase ^ ((uint32_t)r << 15); // the pair's second row: half a step apart
-                        u32x4 pk;
-                        pk[0] = pack_bf16_relu(a[r][8 * hq + 0] + b0[0], a[r][8 * hq + 1] + b0[1], dth, true);
-                        pk[1] = pack_bf16_relu(a[r][8 * hq + 2] + b0[2], a[r][8 * hq + 3] + b0[3], dth, true);
-                        pk[2] = pack_bf16_relu(a[r][8 * hq + 4] + b1[0], a[r][8 * hq + 5] + b1[1], dth, true);
-                        pk[3] = pack_bf16_relu(a[r][8 * hq + 6] + b1[2], a[r][8 * hq + 7] + b1[3], dth, true);
-                        if (2 * j + r < g.h && (uint32_t)x < (uint32_t)g.w) *(u32x4 *)(rows + (le + r * rstride + 8 * hq)) = pk;
-                    }
-                }
-            }
-        }
-        if (LASTB) {
-            if (st.tout) last_block_statistics(a, si, p, x, x_lo + xb * 32, pxl, hf);
-        } else if (st.tout && ((j >> 1) & 7) == sample_phase) { // (the rows conv_mid would sample)
+        if (!st.tout) return;
+        if (LASTB) last_block_statistics(a, p, x, x_lo + xb * 32, pxl, hf);
+        else if (((j >> 1) & 7) == sample_phase) { // (the rows conv_mid would sample)
             const int ri = (((j >> 4) * 2 + (j & 1)) * J + blk) * 2 + xb; // sampled row pair, column block, pixel block
-            strip_statistics<RW>(a, si, st.tout + ((int64_t)n * st.out_recs + ri) * C + cb * 32 + hf * 16, x, 2 * j, g.h, g.w, pxl);
+            strip_statistics<RW>(a, s_zero, st.tout + ((int64_t)n * st.out_recs + ri) * C + cb * 32 + hf * 16, x, 2 * j, g.h, g.w, pxl);
         }
     };
 
-    // FIRST, group A: where in the pixel ring this lane's two taps of every k chunk lie (chunk k, half hf: taps
-    // 4k + 2hf and 4k + 2hf + 1; beyond 8: zero weights, tap 8 re-read): row offset dy and byte offset of
-    // column xl + dx, fixed for the lifetime of the workgroup
-    int tap_dy[3][2], tap_col8[3][2];
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int j2 = 0; j2 < 2; ++j2) {
-            int tap = 4 * k + 2 * half + j2;
-            tap = tap > 8 ? 8 : tap;
-            tap_dy[k][j2] = tap / 3;
-            tap_col8[k][j2] = (xb * 32 + px + tap % 3) * 8;
-        }
     // WIDE, group A: the last two columns (62, 63) of the intermediate rows written in this step, read back from
     // the ring (the wavefront's own writes) and stored to the seam rows at `rows` (null: nothing to hand over).
     // Issued behind the step's wait for global memory, so that the wait never has to sit out these stores.
@@ -1450,72 +1442,96 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     };
     constexpr int kFirstWaveLoads = RW * ((K::PIECES + 3) / 4); // of those, the first wavefront's for the rows
     f32x16 acc[RW];
-    const int n_steps = n_pos + 2;
-    // !FIRST, group A: where its rows of the step lie and whether it multiplies them.  Found before the barrier in front of the
-    // step, where this group has time to spare: between the barrier and its first matrix instruction the matrix pipes
-    // would stand idle for it (a step of a middle pair 5720 -> 5360 cycles; 4096 tiles of 64 x 64 6540 -> 6460 us: the clock gives
-    // way as the pipes fill up).
-    lrow_t rowp_a[RW + 2];
-    bool a_computes = false;
-    auto prepare_step = [&](int sg) {
+    const int n_steps = n_pos + (kHandOver ? 3 : 2);
+
+    if (grp == 0) {
+        // ---- group A
+        // !FIRST: where its rows of the step lie and whether it multiplies them.  Found before the barrier in front of the
+        // step, where this group has time to spare: between the barrier and its first matrix instruction the matrix pipes
+        // would stand idle for it (a step of a middle pair 5720 -> 5360 cycles; 4096 tiles of 64 x 64 6540 -> 6460 us: the clock
+        // gives way as the pipes fill up).
+        lrow_t rowp[RW + 2];
+        bool multiplies = false;
+        auto prepare_step = [&](int sg) {
 #pragma unroll
-        for (int r = 0; r < RW + 2; ++r) {
-            rowp_a[r] = in_base + (uint32_t)slot_of(2 * sg - 1 + r) * ROWB;
-            asm volatile("" : "+v"(rowp_a[r])); // here, not where it is used
-        }
-        a_computes = pw.i < n_cnt && computes(pw);
-    };
-    if (!FIRST && grp == 0) prepare_step(0);
+            for (int r = 0; r < RW + 2; ++r) {
+                rowp[r] = in_base + (uint32_t)slot_of(2 * sg - 1 + r) * ROWB;
+                asm volatile("" : "+v"(rowp[r])); // here, not where it is used
+            }
+            multiplies = pw.i < n_cnt && computes(pw);
+        };
+        if (!FIRST) prepare_step(0);
+        // Sums start from bias (+ correction of the image), this lane's 16 channels: kept in registers, read anew behind an opening
+        // position that prepared those of the next image
+        f32x16 init16 = load16(&s_initA[cb * 32 + half * 16]);
+        bool new_init = false;
 #pragma unroll 1
-    for (int sg = 0; sg < n_steps; ++sg) {
-        const bool fin = (FIRST || grp == 1) && sg >= 3 && pe.i < n_cnt && owns(pe); // rows accumulated in the previous step wait for their epilogue
-        bool ended = false; // group B has passed the step's barrier
-        if (grp == 0) {
+        for (int sg = 0; sg < n_steps; ++sg) {
             const int ln = pin_in_loop(tid & 63);
             const int pxl = ln & 31, hf = ln >> 5;
             const int xl = xb * 32 + pxl;          // this lane's column within the block
-            const int x = pw.b * kTileW + xl;      // and within the tile
-            uint8_t *seam_rows = nullptr;          // WIDE: where the seam columns of this step's rows go, if anywhere
             // FIRST: the raw pixels of virtual rows 2sg+3, 2sg+4 (window of step sg+1) start their way into registers
-            uint32_t pv[2] = {0, 0}, psh[2] = {0, 0};
-            bool pin[2] = {false, false};
-            const bool fetch = FIRST && p1.i < n_cnt;
-            if (fetch) {
-                if (p1.s == -1 && p1.b == 0) tile0 = tile_origin(n_begin + p1.i); // the next image opens
+            // (behind the last unit: pixels of its tile that nobody looks at, as a load under a condition would be waited for, and
+            // with it the stores of the step before, where the next step sets its register)
+            const int ty = 2 * p1.s + 1; // image row of the first
+            uint32_t pv[2], psh[2];
+            if (FIRST) {
 #pragma unroll
-                for (int k = 0; k < 2; ++k) pv[k] = pixel_fetch(tile0, p1.b * kTileW, 2 * p1.s + 1, tid + 256 * k, pin[k], psh[k]);
+                for (int k = 0; k < 2; ++k) pv[k] = pixel_fetch(ty + k, psh[k]);
             }
-            if (FIRST ? pw.i < n_cnt && computes(pw) : a_computes) {
+            if (FIRST) multiplies = pw.i < n_cnt && computes(pw);
+            if (!FIRST && new_init) init16 = load16(&s_initA[cb * 32 + half * 16]);
+            new_init = false;
+            if (multiplies) {
                 if (FIRST) {
-                    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    // Operands (first_tap): the four rows of the window at this lane's column + its half, and at column + 2
+                    const uint8_t *pix = (const uint8_t *)&s_pix[0][0][0] + (xb * 32 + pxl) * 8;
+                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                    u32x2 near[RW + 2], far[RW], corner[RW];
+#pragma unroll
+                    for (int r = 0; r < RW + 2; ++r) near[r] = *(const u32x2 *)(pix + slot_of(2 * sg - 1 + r) * (kHaloW * 8) + hf * 8);
 #pragma unroll
                     for (int r = 0; r < RW; ++r) {
-                        const int vy = 2 * sg + r;
-                        bf16x8 bfrag[3];
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) {
-                            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                            u32x2 two[2];
-#pragma unroll
-                            for (int j2 = 0; j2 < 2; ++j2) {
-                                const int slot = (vy + 1 + tap_dy[k][j2]) & (kPairRing - 1); // slot_of(vy - 1 + dy)
-                                two[j2] = *(const u32x2 *)((const uint8_t *)&s_pix[0][0][0] + slot * (kHaloW * 8) + tap_col8[k][j2]);
-                            }
-                            const u32x4 both = {two[0][0], two[0][1], two[1][0], two[1][1]};
-                            bfrag[k] = __builtin_bit_cast(bf16x8, both);
-                        }
-                        acc[r] = mfma32(Wr[0][0], bfrag[0], zero);
-                        acc[r] = mfma32(Wr[0][1], bfrag[1], acc[r]);
-                        acc[r] = mfma32(Wr[0][2], bfrag[2], acc[r]);
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) acc[r] = mfma32(Wr[1][k], bfrag[k], acc[r]);
+                        const int up = slot_of(2 * sg - 1 + r), mid = slot_of(2 * sg + r), low = slot_of(2 * sg + 1 + r); // the same for the whole wavefront
+                        far[r] = *(const u32x2 *)(pix + (hf ? mid : up) * (kHaloW * 8) + 16);
+                        corner[r] = *(const u32x2 *)(pix + low * (kHaloW * 8) + 16);
                     }
+                    bf16x8 bfrag[RW][3];
+#pragma unroll
+                    for (int r = 0; r < RW; ++r) {
+                        auto taps = [](u32x2 t0, u32x2 t1) { return __builtin_bit_cast(bf16x8, (u32x4){t0[0], t0[1], t1[0], t1[1]}); };
+                        bfrag[r][0] = taps(near[r], near[r + 1]);
+                        bfrag[r][1] = taps(near[r + 2], far[r]);
+                        bfrag[r][2] = taps(corner[r], corner[r]);
+                    }
+#pragma unroll
+                    for (int r = 0; r < RW; ++r) acc[r] = mfma32(Wr[0][0], bfrag[r][0], init16);
+#pragma unroll
+                    for (int f = 1; f < kFirstFrags; ++f)
+#pragma unroll
+                        for (int r = 0; r < RW; ++r) acc[r] = mfma32(Wr[f / 3][f % 3], bfrag[r][f % 3], acc[r]);
                 } else {
-                    strip_mma<C, RW>(rowp_a, Wr, acc, []() {});
-                    input_loads(sg);
+                    strip_mma<C, RW>(rowp, Wr, acc, init16, []() {});
                 }
-                // epilogue: + bias and correction, ReLU, bf16 -> intermediate ring (zeros outside the tile)
-                const float *si = &s_initA[cb * 32 + hf * 16];
+            }
+            if (!FIRST) input_loads(sg);
+            // kHandOver: the first of the rows group B accumulated two steps ago, beside the matrix instructions just issued
+            const bool fin = kHandOver && sg >= 4 && pe.i < n_cnt && owns(pe);
+            u32x4 pk_b[2];
+            if (fin) {
+                const float *srcx = &s_accx[(((sg & 1) * 4 + w4) * 4) * 256 + ln * 4];
+                f32x16 a;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 v = *(const f32x4 *)(srcx + q * 256);
+                    a[4 * q] = v[0]; a[4 * q + 1] = v[1]; a[4 * q + 2] = v[2]; a[4 * q + 3] = v[3];
+                }
+                finish_pack(a, 0, pe, pk_b);
+            }
+            uint8_t *seam_rows = nullptr;          // WIDE: where the seam columns of this step's rows go, if anywhere
+            if (multiplies) {
+                // epilogue: ReLU, bf16 -> intermediate ring (zeros outside the tile)
+                const int x = pw.b * kTileW + xl;  // this lane's column within the tile
                 const uint32_t dbase = dither16(x, 2 * pw.s);
                 // WIDE: the last two columns of the block also go to the seam (seam_flush below): the workgroup's
                 // own (for its next column block) or the image's (the tile's last two columns, for conv_seam_kernel)
@@ -1525,92 +1541,97 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
                     if (seam_rows) seam_rows += (size_t)(2 * pw.s) * kSeamRowBytes;
                 }
 #pragma unroll
-                for (int hq = 0; hq < 2; ++hq) {
-                    const f32x4 b0 = *(const f32x4 *)(si + 8 * hq), b1 = *(const f32x4 *)(si + 8 * hq + 4);
+                for (int r = 0; r < RW; ++r) {
+                    const int y = 2 * pw.s + r;
+                    u32x4 pk[2];
+                    packed_row(acc[r], dbase ^ ((uint32_t)r << 15), pk);
 #pragma unroll
-                    for (int r = 0; r < RW; ++r) {
-                        const int y = 2 * pw.s + r;
-                        const uint32_t dth = dbase ^ ((uint32_t)r << 15);
-                        u32x4 pk;
-                        pk[0] = pack_bf16_relu(acc[r][8 * hq + 0] + b0[0], acc[r][8 * hq + 1] + b0[1], dth, true);
-                        pk[1] = pack_bf16_relu(acc[r][8 * hq + 2] + b0[2], acc[r][8 * hq + 3] + b0[3], dth, true);
-                        pk[2] = pack_bf16_relu(acc[r][8 * hq + 4] + b1[0], acc[r][8 * hq + 5] + b1[1], dth, true);
-                        pk[3] = pack_bf16_relu(acc[r][8 * hq + 6] + b1[2], acc[r][8 * hq + 7] + b1[3], dth, true);
-                        if (y >= g.h || x >= g.w) pk = (u32x4){0u, 0u, 0u, 0u};
-                        *(u32x4 *)(ring_mid + slot_of(2 * sg + r) * ROWB + (1 + kSkew + xl) * K::PS + (cb * 32 + hf * 16 + 8 * hq) * 2) = pk;
+                    for (int hq = 0; hq < 2; ++hq) {
+                        if (y >= g.h || x >= g.w) pk[hq] = (u32x4){0u, 0u, 0u, 0u};
+                        *(u32x4 *)(ring_mid + slot_of(2 * sg + r) * ROWB + (1 + kSkew + xl) * K::PS + (cb * 32 + hf * 16 + 8 * hq) * 2) = pk[hq];
                     }
                 }
             } else { // opening position: zero padding of the second block, below the unit before and above this one
-                if (!FIRST) input_loads(sg);
 #pragma unroll
                 for (int r = 0; r < RW; ++r)
 #pragma unroll
                     for (int hq = 0; hq < 2; ++hq)
                         *(u32x4 *)(ring_mid + slot_of(2 * sg + r) * ROWB + (1 + kSkew + xl) * K::PS + (cb * 32 + hf * 16 + 8 * hq) * 2) =
                             (u32x4){0u, 0u, 0u, 0u};
-                if (!FIRST && pw.b == 0 && pw.i < n_cnt) prepare_init(n_begin + pw.i); // nobody reads s_initA in this step
+                if (!FIRST && pw.b == 0 && pw.i < n_cnt) { // nobody reads s_initA in this step
+                    prepare_init(n_begin + pw.i);
+                    new_init = true;
+                }
             }
-            // WIDE: once per step this group waits for all of its global memory traffic, at a point where it has
-            // to wait for its loads anyway; the stores of the previous step are then known to be done, among them
-            // the seam rows, which are read back a whole unit - at least two steps - after they were written.
-            if (FIRST && WIDE) __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            if (FIRST && fetch) { // their slots were last read two steps ago; before the stores below, which need not be waited for
+            if (FIRST) {
+                // WIDE: once per step this group waits for all of its global memory traffic, at a point where it has
+                // to wait for its loads anyway; the stores of the previous step are then known to be done, among them
+                // the seam rows, which are read back a whole unit - at least two steps - after they were written.
+                if (WIDE) __builtin_amdgcn_s_waitcnt(kWaitVm0);
 #pragma unroll
-                for (int k = 0; k < 2; ++k) pixel_store(2 * sg + 3, tid + 256 * k, pv[k], psh[k], pin[k]);
+                for (int k = 0; k < 2; ++k) // their slots were last read two steps ago
+                    pixel_store(2 * sg + 3 + k, pix_inside && (uint32_t)(ty + k) < (uint32_t)g.h, pv[k], psh[k]);
+                if (fin) finish_store(0, pe, pk_b); // behind the wait for the pixels, which would sit these stores out
             }
-            if (FIRST && WIDE) seam_flush(seam_rows, sg);
-            if (!FIRST) { // the end of this group's step
-                if (WIDE) seam_flush(seam_rows, sg);
-                const bool rows_issued = pe.i < n_cnt;
-                advance(pw);
-                advance(pe);
+            if (WIDE) seam_flush(seam_rows, sg);
+            // the end of this group's step
+            const bool rows_issued = pe.i < n_cnt;
+            advance(pw);
+            if (FIRST) {
+                advance(p1);
+                if (p1.i < n_cnt && p1.s == opening(p1.i)) pixel_first_unit(p1);
+            }
+            if (!FIRST || sg >= 4) advance(pe);
+            if (!FIRST) {
                 prepare_step(sg + 1);
                 if (WIDE && w4 == 0) { // the seam columns have landed
                     if (rows_issued) __builtin_amdgcn_s_waitcnt(kWaitVm0 | kFirstWaveLoads);
                     else __builtin_amdgcn_s_waitcnt(kWaitVm0);
                 }
-                lds_barrier();
-                continue;
             }
-            if (FIRST && fin) { // the rows group B accumulated in the previous step
-                const float *srcx = &s_accx[((((sg - 3) & 1) * 4 + w4) * 8) * 256 + ln * 4];
-                f32x16 a[RW];
-#pragma unroll
-                for (int r = 0; r < RW; ++r)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const f32x4 v = *(const f32x4 *)(srcx + (r * 4 + q) * 256);
-                        a[r][4 * q] = v[0]; a[r][4 * q + 1] = v[1]; a[r][4 * q + 2] = v[2]; a[r][4 * q + 3] = v[3];
-                    }
-                finish(a, pe);
-            }
-        } else {
-            const int ln = pin_in_loop(tid & 63);
-            if (WIDE && FIRST && w4 == 0) seam_loads(sg, p1); // (group A is the critical path of this variant)
-            if (!FIRST && fin) finish(acc, pe); // the rows accumulated in the previous step
-            if (sg >= 2 && pw.i < n_cnt && owns(pw)) {
-                lrow_t rowp[RW + 2];
-#pragma unroll
-                for (int r = 0; r < RW + 2; ++r) rowp[r] = mid_base + (uint32_t)slot_of(2 * (sg - 2) - 1 + r) * ROWB;
-                strip_mma<C, RW>(rowp, Wr, acc, [&]() {
-                    if (!FIRST) lds_barrier(); // the end of this group's step
-                });
-                ended = !FIRST;
-                if (FIRST) { // group A finishes these rows in the next step
-                    float *dst = &s_accx[((((sg - 2) & 1) * 4 + w4) * 8) * 256 + ln * 4];
-#pragma unroll
-                    for (int r = 0; r < RW; ++r)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            *(f32x4 *)(dst + (r * 4 + q) * 256) = (f32x4){acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]};
-                }
-            }
+            lds_barrier();
         }
-        // End of the step
-        if (WIDE && FIRST && grp == 1 && w4 == 0) __builtin_amdgcn_s_waitcnt(kWaitVm0); // the seam columns have landed
-        if (!ended) lds_barrier();
-        if (sg >= w_start) advance(pw);
-        if (sg >= e_start) advance(pe);
+        return;
+    }
+
+    // ---- group B
+    const f32x16 bias16 = load16(&s_biasB[cb * 32 + half * 16]); // the sums start from it
+    bool accumulated = false; // rows of the step before wait for their epilogue
+#pragma unroll 1
+    for (int sg = 0; sg < n_steps; ++sg) {
+        const int ln = pin_in_loop(tid & 63);
+        if (accumulated) {
+            if (kHandOver) { // the first row to group A, which finishes it in the next step
+                float *dst = &s_accx[((((sg - 1) & 1) * 4 + w4) * 4) * 256 + ln * 4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *(f32x4 *)(dst + q * 256) = (f32x4){acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]};
+            }
+            if (!LASTB) {
+                u32x4 pk[RW][2];
+#pragma unroll
+                for (int r = kHandOver ? 1 : 0; r < RW; ++r) finish_pack(acc[r], r, pe, pk[r]);
+#pragma unroll
+                for (int r = kHandOver ? 1 : 0; r < RW; ++r) finish_store(r, pe, pk[r]);
+            }
+            finish_statistics(acc, pe);
+        }
+        if (WIDE && FIRST && w4 == 0) seam_loads(sg, p1); // (group A is the critical path of this variant)
+        auto end_of_step = [&]() {
+            if (WIDE && FIRST && w4 == 0) __builtin_amdgcn_s_waitcnt(kWaitVm0); // the seam columns have landed
+            lds_barrier();
+        };
+        accumulated = sg >= 2 && pw.i < n_cnt && owns(pw);
+        if (accumulated) {
+            lrow_t rowp[RW + 2];
+#pragma unroll
+            for (int r = 0; r < RW + 2; ++r) rowp[r] = mid_base + (uint32_t)slot_of(2 * (sg - 2) - 1 + r) * ROWB;
+            strip_mma<C, RW>(rowp, Wr, acc, bias16, end_of_step);
+        } else {
+            end_of_step();
+        }
+        if (sg >= 2) advance(pw);
+        if (sg >= 3) advance(pe);
         if (FIRST) advance(p1);
     }
 }
@@ -1728,11 +1749,9 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
     const int cb = wave % NCB;
     const int rbase = (wave / NCB) * NCB;
     // weights as bf16 high part + bf16 residual: this layer is tiny, so it is computed to ~16 bits
-    bf16x8 Wr[2][3];
+    bf16x8 Wr[kFirstFrags];
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) Wr[p][q] = ((const bf16x8 *)wfrag)[((cb * 2 + p) * 3 + q) * 64 + lane];
+    for (int f = 0; f < kFirstFrags; ++f) Wr[f] = ((const bf16x8 *)wfrag)[(cb * kFirstFrags + f) * 64 + lane];
     f32x16 bias16;
     {
         const float4 *bp = (const float4 *)(bias + cb * 32 + half * 16);
@@ -1743,15 +1762,13 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
         }
     }
 
-    // LDS byte offsets (relative to the lane's output pixel) of the two taps of each k chunk:
-    // chunk q, half h -> taps 4q + 2h and 4q + 2h + 1; taps >= 9 carry zero weights and re-read tap 8.
+    // LDS byte offsets (relative to the lane's output pixel) of the two taps of each k chunk
     int toff[3][2];
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            int tap = 4 * q + 2 * half + j;
-            tap = tap > 8 ? 8 : tap;
+            const int tap = first_tap(q, half, j);
             toff[q][j] = ((tap / 3) * kHaloW + tap % 3) * 8;
         }
 
@@ -1812,11 +1829,9 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
                     bfrag[q] = __builtin_bit_cast(bf16x8, both);
                 }
                 const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                f32x16 sum = mfma32(Wr[0][0], bfrag[0], zero);
-                sum = mfma32(Wr[0][1], bfrag[1], sum);
-                sum = mfma32(Wr[0][2], bfrag[2], sum);
+                f32x16 sum = mfma32(Wr[0], bfrag[0], zero);
 #pragma unroll
-                for (int q = 0; q < 3; ++q) sum = mfma32(Wr[1][q], bfrag[q], sum);
+                for (int f = 1; f < kFirstFrags; ++f) sum = mfma32(Wr[f], bfrag[f % 3], sum);
                 f32x16 acc;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[v] = sum[v] + bias16[v];

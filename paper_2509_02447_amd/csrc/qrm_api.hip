@@ -179,32 +179,32 @@ void pack_mid(const std::vector<uint16_t> &r, int cout, int cout_pad, int cin, s
                     }
 }
 
-// first layer: k = q*16 + (lane/32)*8 + e  ->  tap = k/4 (0..8, beyond: zero), channel = k%4.
+// first layer: a lane's value e of a fragment belongs to tap first_tap(q, lane / 32, e / 4) and channel e % 4.
 // The kernels feed the raw bytes p_c (exact in bf16) and a fourth channel that is 1 inside the tile, so the
 // normalisation x_c = (p_c / 255 - mean_c) / std_c is folded into the weights: channel c < 3 carries
 // w / (255 std_c), channel 3 carries - sum_c w mean_c / std_c (per tap).
-// Per output block two fragment sets: bf16(v) and bf16(v - bf16(v)).
+// Per output block kFirstFrags fragments: bf16(v) of the three chunks, bf16(v - bf16(v)) of the first two; chunk 2 holds one tap
+// only, 8, whose residual takes the place of the lower half's second tap.
 void pack_first(const float *w, const float *scale, int cout, const float *mean, const float *std, std::vector<uint16_t> &dst)
 {
     for (int blk = 0; blk < cout / 32; ++blk)
-        for (int part = 0; part < 2; ++part)
-            for (int q = 0; q < 3; ++q)
-                for (int lane = 0; lane < 64; ++lane)
-                    for (int e = 0; e < 8; ++e) {
-                        const int o = blk * 32 + perm32(lane & 31);
-                        const int k = q * 16 + (lane >> 5) * 8 + e;
-                        const int tap = k / 4, ch = k % 4;
-                        double v = 0.0;
-                        if (tap < 9) {
-                            const double sc = scale ? (double)scale[o] : 1.0;
-                            if (ch < 3) v = (double)w[((size_t)o * 3 + ch) * 9 + tap] * sc / (255.0 * (double)std[ch]);
-                            else
-                                for (int c = 0; c < 3; ++c)
-                                    v -= (double)w[((size_t)o * 3 + c) * 9 + tap] * sc * (double)mean[c] / (double)std[c];
-                        }
-                        const uint16_t hi = f32_to_bf16_rne((float)v);
-                        dst.push_back(part == 0 ? hi : f32_to_bf16_rne((float)(v - (double)bf16_to_f32(hi))));
+        for (int f = 0; f < kFirstFrags; ++f)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int e = 0; e < 8; ++e) {
+                    const int o = blk * 32 + perm32(lane & 31), q = f % 3, half = lane >> 5, j = e / 4;
+                    const int tap = first_tap(q, half, j), ch = e % 4;
+                    const bool residual = f >= 3 || (q == 2 && j == 1);
+                    double v = 0.0;
+                    if (q < 2 || half == 0) {
+                        const double sc = scale ? (double)scale[o] : 1.0;
+                        if (ch < 3) v = (double)w[((size_t)o * 3 + ch) * 9 + tap] * sc / (255.0 * (double)std[ch]);
+                        else
+                            for (int c = 0; c < 3; ++c)
+                                v -= (double)w[((size_t)o * 3 + c) * 9 + tap] * sc * (double)mean[c] / (double)std[c];
                     }
+                    const uint16_t hi = f32_to_bf16_rne((float)v);
+                    dst.push_back(residual ? f32_to_bf16_rne((float)(v - (double)bf16_to_f32(hi))) : hi);
+                }
 }
 
 // rsum[o][c] = sum over the 9 taps of (w*scale - bf16(w*scale)): what the bf16 weights leave out, as it

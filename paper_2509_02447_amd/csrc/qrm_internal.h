@@ -21,6 +21,15 @@ constexpr int kRows = 4;     // output rows per strip of the conv kernels
 constexpr int kTileW = 64;   // output columns per strip
 constexpr int kHaloW = kTileW + 2;
 
+// First layer: K = 9 taps x 4 channels in 16-wide k chunks of two taps for either half of a wavefront.  Tap (3 dy + dx) that
+// half `half` reads as its tap j of chunk q.  dy is the same for both halves where it can be: the kernels then find an operand's
+// row without vector instructions.
+constexpr int kFirstFrags = 5; // chunks 0 .. 2 with the weights' bf16 high parts, chunks 0, 1 with the residuals; tap 8's residual is chunk 2's second tap
+__host__ __device__ constexpr int first_tap(int q, int half, int j)
+{
+    return q == 0 ? 3 * j + half : q == 1 ? (j == 0 ? 6 + half : 3 * half + 2) : 8;
+}
+
 // Geometry of one extractor pass over a micro-batch.
 struct ConvGeom {
     int n_img;      // images in this launch
