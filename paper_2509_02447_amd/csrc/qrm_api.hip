@@ -676,7 +676,7 @@ qrm_status qrm_create(const qrm_extractor_desc *ext, const qrm_rs_desc *rs, int 
         c->has_rs = true;
         const int q = 1 << rs->m;
         // alpha has order q - 1: only fcr mod (q - 1) matters, and the kernels multiply it by positions in 32 bits
-        c->rs = RsParams{rs->m, q, rs->n, rs->k, rs->n - rs->k, rs->fcr % (q - 1), nullptr, 0};
+        c->rs = RsParams{rs->m, q, rs->n, rs->k, rs->n - rs->k, rs->fcr % (q - 1), nullptr, 0, 0};
         const std::vector<uint8_t> image = rs_table_image(c->rs, exp2, lg);
         e = hipMalloc(&c->d_tables, kKeyBytes + image.size());
         if (e != hipSuccess) { if (c->d_weights) (void)hipFree(c->d_weights); delete c; return hip_fail(nullptr, e, "hipMalloc(tables)"); }

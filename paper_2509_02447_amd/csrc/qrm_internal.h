@@ -162,6 +162,7 @@ struct RsParams {
     int m, q, n, k, two_t, fcr;
     const uint8_t *tab; // device, the table image of the code (rs_table_image), 16-byte aligned
     int tab_bytes;      // what a launch takes of it into LDS, a multiple of 16
+    int tab2_bytes;     // of the second image behind it, if there is one
 };
 
 // Key verification: `key` device [k] symbols; matches null = no verification.
@@ -173,7 +174,7 @@ struct KeyArgs {
 };
 
 // The tables the decoding kernels keep in LDS for this code, laid out once per context (p.tab unused; sets p.tab_bytes; codes
-// with two ways of dealing a word to lanes have an image for either, of equal size, one behind the other);
+// with two ways of dealing a word to lanes have an image for either, one behind the other);
 // exp2: alpha^0 .. alpha^(2 ord - 1), lg: logarithms of 1 .. q - 1
 std::vector<uint8_t> rs_table_image(RsParams &p, const std::vector<uint8_t> &exp2, const std::vector<uint8_t> &lg);
 int rs_lanes_per_word(const RsParams &p, int64_t N); // of a launch of N words

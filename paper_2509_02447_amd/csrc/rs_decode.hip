@@ -18,6 +18,8 @@
 // the decoder's epilogue when a key is given: the number of message bits that agree with the key's and
 // (count >= tau) are written.  The same count for messages already in memory is `verify_kernel`, a plain
 // streaming pass.
+#include <algorithm>
+
 #include "qrm_internal.h"
 
 namespace qrm {
@@ -31,24 +33,34 @@ constexpr int kLogAt = kExpBytes;             // u16 [256]
 constexpr int kQuadAt = kLogAt + 512;         // u8 [256]: a y with y^2 + y = index, 0 when there is none
 constexpr int kCodeAt = kQuadAt + 256;        // what follows depends on the kernel:
 //   lane kernel : u32 [4 ceil(n/4)][q], the (up to four) syndrome terms of symbol value v at position i, a byte each
-//   group kernel: u8 [2t + t][q], v * alpha^(G (fcr + j)) for j < 2t, then v * alpha^(G j) for j = 1 .. t
-constexpr int kMaxGroupTables = 24 * 256;
+//   group kernel: syndromes: u8 [SPL][q][2 TMAX], byte j of entry (s, v): v * alpha^(G (SPL - 1 - s) (fcr + j)), 0 from 2t on;
+//                 Chien: u8 [TMAX][q][chien_bytes(SPL)], byte s of entry (j - 1, v): v * alpha^(G j s), 0 for j > t
+//                 what differs from lane to lane: u8 [G][kLaneBytes]: exponents of alpha, (fcr + j) last_pw for j < 2 TMAX
+//                 (last_pw: the power of the lane's symbol SPL - 1), then j first_x for j <= TMAX (first_x: minus the power of its
+//                 symbol 0)
+constexpr int kLaneBytes = 28;
+constexpr int group_tmax(int two_t) { return two_t > 8 ? 8 : 4; }
+constexpr int chien_bytes(int spl) { return spl < 4 ? 4 : spl; }
 constexpr int64_t kDecodeBlocks = 2048; // lane kernel: eight workgroups per compute unit; each reads the tables once and takes every 2048th run of words
-// Group kernel: its 56 .. 80 registers let six to eight workgroups onto a compute unit, so 2048 left some waiting for a second
-// turn and others with a second run of words while the rest of the chip was done.  Five per compute unit, and every workgroup
-// the same number of runs: 20000 words of RS(255,239) 50.2 -> 37.1 us, 65536 of them 117 -> 110, 100000 of RS(63,55) 37.6 ->
-// 31.0, 400000 of RS(31,25) 78.8 -> 69.8, up to 13000 words unchanged; with 1024, 1536 and 2048 runs dealt evenly 45, 37 and 37
-// us for the first, 113, 152 and 117 for the second.
-constexpr int64_t kGroupBlocks = 1280;
+// Group kernel: three workgroups of eight wavefronts to a compute unit (up to 51 KiB of tables each), every 768th run of words.
+// 20000 words of RS(255,239) 20.7 us, with two workgroups of the same size 22.
+constexpr int kGroupThreads = 512;
+constexpr int64_t kGroupBlocks = 768;
+constexpr int64_t kSecondSplitWords = 10240;
 
 bool lane_code(int n, int two_t) { return n <= 16 && two_t <= 4; }
+int group_symbols(int n, int G) // SPL: symbols per lane, rounded up to a power of two
+{
+    int spl = 1;
+    while (spl * G < n) spl *= 2;
+    return spl;
+}
 int group_lanes(int two_t) { return two_t > 8 ? 32 : 16; } // 3t + 1 coefficients of the systolic recursion, one per lane
-// Words of more than 128 symbols keep 16 lanes busy for 16 steps one after the other, which shows where a launch has so few
-// of them that every workgroup takes one run: while 32 lanes a word still fit the chip that way, they have 32.  RS(255,251),
-// 300 words 11.4 -> 7.8 us, 4096 11.7 -> 8.8, 8192 12.8 -> 10.6; RS(255,247) 14.3 -> 9.7, 14.7 -> 10.7, 15.7 -> 12.5; 20000
-// words are 16.9 us with 16 lanes and 17.1 with 32, 21.1 and 22.3.
+// Words of more than 128 symbols take 16 look-ups of a lane one behind the other, which shows where a launch has so few
+// of them that every workgroup takes one run: while 32 lanes a word still fit the chip that way, they have 32.  RS(255,247), 16 /
+// 32 lanes: 4096 words 8.2 / 7.4 us, 10240 10.6 / 10.2, 16000 11.3 / 13.0; RS(255,251) 7.9 / 7.7, 9.8 / 9.6, 10.5 / 12.4.
 bool second_split(int n, int two_t) { return n > 128 && two_t <= 8; }
-bool takes_second_split(const RsParams &p, int64_t N) { return second_split(p.n, p.two_t) && N <= kGroupBlocks * (256 / 32); }
+bool takes_second_split(const RsParams &p, int64_t N) { return second_split(p.n, p.two_t) && N <= kSecondSplitWords; }
 
 struct Gf {
     const uint8_t *exp; // LDS
@@ -60,9 +72,10 @@ struct Gf {
 __device__ __forceinline__ int mod_once(int e, int ord) { return (int)min((uint32_t)e, (uint32_t)(e - ord)); } // 0 <= e < 2 ord
 
 // table image -> LDS, 16 bytes per lane and step
+template <int THREADS>
 __device__ __forceinline__ void load_tables(uint8_t *dst, const RsParams &p)
 {
-    for (int i = threadIdx.x * 16; i < p.tab_bytes; i += 256 * 16) *(u32x4 *)(dst + i) = *(const u32x4 *)(p.tab + i);
+    for (int i = threadIdx.x * 16; i < p.tab_bytes; i += THREADS * 16) *(u32x4 *)(dst + i) = *(const u32x4 *)(p.tab + i);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -92,7 +105,7 @@ __global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const u
     __shared__ __attribute__((aligned(16))) uint8_t s_msg[WORDS ? 16 : 256 * 16];
     const int tid = threadIdx.x;
     const int n = p.n, k = p.k, ord = p.q - 1, fcr = p.fcr;
-    load_tables(s_tab, p);
+    load_tables<256>(s_tab, p);
     const Gf gf{s_tab, (const uint16_t *)(s_tab + kLogAt)};
     const uint8_t *quad = s_tab + kQuadAt;
     const uint32_t *syn = (const uint32_t *)(s_tab + kCodeAt);
@@ -247,27 +260,35 @@ __global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const u
 // ------------------------------------------------------------------------------------------------
 // All other codes: G = 16 (t <= 4) or 32 (t <= 8, or few long words) lanes per word, four or two words per wavefront.  Lane l holds the
 // symbols l, l + G, l + 2G, .. (SPL of them).
-//   Syndromes   each lane evaluates its own symbols by Horner's rule in alpha^(G (fcr + j)): a step is one look-up in
-//               that constant's table (256 bytes: one dword per LDS bank, so no bank conflicts) and one XOR for
-//               each j; the lane's own power is multiplied on at the end and the terms are added up over the lanes.
+//   Syndromes   symbol s of a lane enters syndrome j with alpha^((fcr + j) (last_pw + G (SPL - 1 - s))): the lane's part is
+//               multiplied on at the end, the rest is the same for all lanes and ONE look-up of a symbol gives its terms of
+//               all 2t syndromes, a byte each.  The lanes' terms are then added up.
 //   Recursion   Berlekamp-Massey without inversions in its systolic form (the "RiBM" of Sarwate and Shanbhag): lane i
 //               holds coefficient i of the 3t + 1 of one polynomial, an iteration is two products per lane and a
 //               shift by one lane, and at the end lanes t .. 2t hold the locator Lambda and lanes 0 .. t-1 the
-//               high part Omega_h of Lambda S = Omega + x^(2t) Omega_h.  It replaces a recursion that every lane
-//               repeated over all coefficients: 2t (3t + 2) products per lane are now 4t.
-//   Chien       every lane steps through its positions; the terms Lambda_j x^j and Omega_h,j x^j are carried along,
-//               each multiplied by alpha^(G j) per step.
-//   Forney      error value X^(-fcr-2t) Omega_h(1/X) / (sum of the odd terms of Lambda at 1/X); Omega(1/X) equals
-//               X^(-2t) Omega_h(1/X) because Lambda(1/X) = 0.
+//               high part Omega_h of Lambda S = Omega + x^(2t) Omega_h.
+//   Chien       likewise: ONE look-up of the term Lambda_j x^j at the lane's first position gives that term at all of the
+//               lane's positions, a byte each; a byte in which the t + 1 of them cancel is an error's position.
+//   Forney      at those positions only: error value X^(-fcr-2t) Omega_h(1/X) / (sum of the odd terms of Lambda at 1/X);
+//               Omega(1/X) equals X^(-2t) Omega_h(1/X) because Lambda(1/X) = 0.
 // A wavefront whose words are all error free stops after the syndromes.
-// Bound by vector instructions and LDS look-ups; 20000 words of RS(255,239): 37 us a pass (the recursion
-// repeated on all 64 lanes of a word: 388 us).
+// Bound by vector instructions and LDS look-ups, about 700 and 150 of a wavefront for its words; 20000 words of RS(255,239):
+// 20.7 us a pass (with a look-up for every symbol and syndrome, every position and coefficient, and Omega_h carried along at
+// every position, 1270 and 390: 37 us; the recursion repeated on all 64 lanes of a word: 388).
 // ------------------------------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ uint32_t xor_dpp(uint32_t v)
+{
+    return v ^ (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
 template <int G>
 __device__ __forceinline__ uint32_t group_xor(uint32_t v)
 {
-#pragma unroll
-    for (int off = G / 2; off >= 1; off >>= 1) v ^= (uint32_t)__shfl_xor((int)v, off, G);
+    v = xor_dpp<0xB1>(v);  // quad_perm [1,0,3,2]
+    v = xor_dpp<0x4E>(v);  // quad_perm [2,3,0,1]
+    v = xor_dpp<0x141>(v); // row_half_mirror
+    v = xor_dpp<0x140>(v); // row_mirror
+    if (G == 32) v ^= (uint32_t)__shfl_xor((int)v, 16, 32);
     return v;
 }
 
@@ -278,76 +299,147 @@ __device__ __forceinline__ uint32_t group_mask(bool pred, int lane) // lanes of 
     return (uint32_t)(mask >> (lane / G * G)) & (uint32_t)((1ull << G) - 1ull);
 }
 
+template <int CTRL>
+__device__ __forceinline__ int add_dpp(int v)
+{
+    return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int G>
+__device__ __forceinline__ int group_add(int v)
+{
+    v = add_dpp<0xB1>(v); // (as group_xor)
+    v = add_dpp<0x4E>(v);
+    v = add_dpp<0x141>(v);
+    v = add_dpp<0x140>(v);
+    if (G == 32) v += __shfl_xor(v, 16, 32);
+    return v;
+}
+
 // The value of the lane above within the group; the top lane gets `fill`.
 template <int G>
 __device__ __forceinline__ int from_above(int v, int fill, int lane_g)
 {
     if (G == 16) return __builtin_amdgcn_update_dpp(fill, v, 0x101, 0xf, 0xf, false); // row_shl:1
-    const int up = __shfl_down(v, 1);
+    const int up = __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true);         // wave_shl:1
     return lane_g == G - 1 ? fill : up;
 }
 
 // The value of the group's lane 0.
 template <int G>
-__device__ __forceinline__ int from_first(int v, int lane)
+__device__ __forceinline__ int from_first(int v)
 {
-    if (G == 16) return __builtin_amdgcn_update_dpp(0, v, 0x150, 0xf, 0xf, false); // row_newbcast:0
-    const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 32);
-    return lane < 32 ? a : b;
+    v = __builtin_amdgcn_update_dpp(0, v, 0x150, 0xf, 0xf, true);                   // row_newbcast:0
+    if (G == 32) v = __builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false);     // row_bcast:15 into rows 1 and 3
+    return v;
 }
 
+// BYTES consecutive bytes of LDS as dwords
+template <int BYTES>
+struct Packed {
+    uint32_t d[BYTES / 4];
+    __device__ __forceinline__ void load(const uint8_t *p)
+    {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        if constexpr (BYTES == 4) d[0] = *(const uint32_t *)p;
+        else if constexpr (BYTES == 8) {
+            const u32x2 v = *(const u32x2 *)p;
+            d[0] = v[0]; d[1] = v[1];
+        } else {
+            const u32x4 v = *(const u32x4 *)p;
+            d[0] = v[0]; d[1] = v[1]; d[2] = v[2]; d[3] = v[3];
+        }
+    }
+};
+
 template <int G, int TMAX, int SPL>
-__global__ __launch_bounds__(256) void rs_decode_group_kernel(RsParams p, const uint8_t *__restrict__ sym, int64_t N,
-                                                              uint8_t *__restrict__ msg, uint8_t *__restrict__ cw,
-                                                              int8_t *__restrict__ nerr, KeyArgs key)
+__global__ __launch_bounds__(kGroupThreads, 6) void rs_decode_group_kernel(RsParams p, const uint8_t *__restrict__ sym, int64_t N,
+                                                                           uint8_t *__restrict__ msg, uint8_t *__restrict__ cw,
+                                                                           int8_t *__restrict__ nerr, KeyArgs key)
 {
     static_assert(3 * TMAX + 1 <= G, "one lane per coefficient");
-    __shared__ __attribute__((aligned(16))) uint8_t s_tab[kCodeAt + kMaxGroupTables];
+    extern __shared__ __attribute__((aligned(16))) uint8_t s_tab[];
     __shared__ uint8_t s_key[256];
     const int tid = threadIdx.x, lane = tid & 63, l = tid % G;
     const int n = p.n, k = p.k, ord = p.q - 1, q = p.q, two_t = p.two_t, t = p.two_t / 2;
+    const uint32_t field = (uint32_t)ord * 0x01010101u;
     const bool with_key = key.matches != nullptr;
-    load_tables(s_tab, p);
-    s_key[tid] = (with_key && tid < k) ? key.key[tid] : 0;
+    load_tables<kGroupThreads>(s_tab, p);
+    if (tid < 256) s_key[tid] = (with_key && tid < k) ? key.key[tid] : 0;
     __syncthreads();
     const Gf gf{s_tab, (const uint16_t *)(s_tab + kLogAt)};
-    const uint8_t *mul_syn = s_tab + kCodeAt, *mul_chien = mul_syn + two_t * q - q; // + j q: times alpha^(G j)
+    constexpr int SB = 2 * TMAX, CB = chien_bytes(SPL); // bytes of an entry
+    const uint8_t *syn = s_tab + kCodeAt, *chien = syn + SPL * q * SB;
 
-    // this lane's fixed exponents: its last symbol's power (as an exponent of alpha) and where Chien starts
-    const int last_pw = ((n - 1 - l - G * (SPL - 1)) % ord + ord) % ord;
-    const int first_x = ((l - (n - 1)) % ord + ord) % ord; // exponent of x = alpha^(-power) at symbol l
-    const int last_e0 = (int)((uint32_t)(p.fcr * last_pw) % (uint32_t)ord);
+    // this lane's fixed exponents, a byte each: (fcr + j) last_pw, j first_x (1 / X of its symbol 0)
     const int lift = (p.fcr + two_t) % ord;                // X^(-fcr-2t) = x^(fcr+2t)
-    const int lift0 = (int)((uint32_t)(lift * first_x) % (uint32_t)ord), lift_step = (int)((uint32_t)(lift * G) % (uint32_t)ord);
+    const float inv_ord = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, 1.0f / (float)ord))); // (a scalar register)
+    constexpr int ND = SB / 4, NL = (TMAX + 4) / 4;
+    auto byte_of = [](const uint32_t *v, int j) { return (int)((v[j / 4] >> (8 * (j % 4))) & 0xffu); };
+    // symbols l + s G of a word of `len` symbols: all lanes have one, some do, none does
+    auto each_symbol = [&](int len, auto &&body) {
+        int full = len / G;
+        asm volatile("" : "+s"(full)); // compared where it is used: kept for the whole loop, the conditions would not fit the scalar registers
+        const int rest = l < len - full * G ? full : -1;
+#pragma unroll
+        for (int s = 0; s < SPL; ++s) {
+            if (s < full || s == rest) body(s);
+        }
+    };
 
-    constexpr int GPB = 256 / G; // words per workgroup and iteration
+    constexpr int GPB = kGroupThreads / G; // words per workgroup and iteration
     const int64_t stride = (int64_t)gridDim.x * GPB;
     const int64_t iters = (N + stride - 1) / stride; // the same for every lane: cross-lane operations see full wavefronts
     for (int64_t it = 0; it < iters; ++it) {
-        const int64_t w = it * stride + (int64_t)blockIdx.x * GPB + tid / G;
+        auto word_index = [&]() { // found again for the write-back: the registers between are scarce
+            int id = tid;
+            asm volatile("" : "+v"(id));
+            return it * stride + (int64_t)blockIdx.x * GPB + id / G;
+        };
+        const int64_t w = word_index();
         const bool valid = w < N;
-        int r[SPL];
+        constexpr int NR = (SPL + 3) / 4;
+        uint32_t r[NR] = {}; // the lane's symbols, a byte each
+        {
+            uint32_t one[SPL] = {};
+            if (valid) {
+                const uint8_t *word = sym + w * n + l;
+                each_symbol(n, [&](int s) { one[s] = word[s * G]; });
+            }
 #pragma unroll
-        for (int s = 0; s < SPL; ++s) {
-            const int i = l + s * G;
-            r[s] = (valid && i < n) ? sym[w * n + i] & (q - 1) : 0;
+            for (int s = 0; s < SPL; ++s) r[s / 4] |= one[s] << (8 * (s % 4));
+#pragma unroll
+            for (int d = 0; d < NR; ++d) r[d] &= field;
         }
         // ---- syndromes
-        constexpr int ND = (2 * TMAX + 3) / 4;
+        uint32_t last_e[ND], first_e[NL];
+        {
+            int at = l * kLaneBytes;
+            asm volatile("" : "+v"(at)); // read for every word: the registers are scarce
+            const uint32_t *mine = (const uint32_t *)(chien + TMAX * q * CB + at);
+#pragma unroll
+            for (int d = 0; d < ND; ++d) last_e[d] = mine[d];
+#pragma unroll
+            for (int d = 0; d < NL; ++d) first_e[d] = mine[ND + d];
+        }
         uint32_t Spk[ND];
 #pragma unroll
-        for (int d = 0; d < ND; ++d) Spk[d] = 0;
-        {
-            int e = last_e0;
+        for (int s = 0; s < SPL; ++s) {
+            Packed<SB> term;
+            term.load(syn + (s * q + byte_of(r, s)) * SB);
 #pragma unroll
-            for (int j = 0; j < 2 * TMAX; ++j)
-                if (j < two_t) {
-                    int v = r[0];
+            for (int d = 0; d < ND; ++d) Spk[d] = s == 0 ? term.d[d] : Spk[d] ^ term.d[d];
+            if (SB == 16 && s % 4 == 3) __builtin_amdgcn_sched_barrier(0); // four look-ups of 16 bytes at a time: registers
+        }
 #pragma unroll
-                    for (int s = 1; s < SPL; ++s) v = mul_syn[j * q + v] ^ r[s];
-                    Spk[j / 4] |= (uint32_t)gf.E(gf.L(v) + e) << (8 * (j % 4));
-                    e = mod_once(e + last_pw, ord);
-                }
+        for (int j0 = 0; j0 < SB; j0 += 8) { // eight at a time: registers
+            int v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = gf.L(byte_of(Spk, j0 + j));
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = gf.E(v[j] + byte_of(last_e, j0 + j));
+#pragma unroll
+            for (int j = 0; j < 8; j += 4) Spk[(j0 + j) / 4] = (uint32_t)v[j] | (uint32_t)v[j + 1] << 8 | (uint32_t)v[j + 2] << 16 | (uint32_t)v[j + 3] << 24;
+            if (SB > 8) __builtin_amdgcn_sched_barrier(0);
         }
         uint32_t any = 0;
 #pragma unroll
@@ -359,15 +451,17 @@ __global__ __launch_bounds__(256) void rs_decode_group_kernel(RsParams p, const 
         bool fail = false;
         if (__ballot(any != 0)) {
             // ---- recursion: coefficient l of this word's polynomial
-            int delta = 0;
+            uint32_t mine = 0;
 #pragma unroll
-            for (int d = 0; d < ND; ++d)
-                if ((l >> 2) == d) delta = (int)((Spk[d] >> (8 * (l & 3))) & 0xffu);
+            for (int d = 0; d < ND; ++d) mine = (l >> 2) == d ? Spk[d] : mine;
+            int delta = (int)((mine >> (8 * (l & 3))) & 0xffu);
             delta = l < two_t ? delta : (l == 3 * t ? 1 : 0);
             int ldelta = gf.L(delta), ltheta = ldelta, lgamma = 0, kk = 0;
             for (int rr = 0; rr < two_t; ++rr) {
-                const int up = from_above<G>(ldelta, kZeroLog, l), d0 = from_first<G>(ldelta, lane);
-                delta = gf.E(lgamma + up) ^ gf.E(d0 + ltheta);
+                const int up = from_above<G>(ldelta, kZeroLog, l), d0 = from_first<G>(ldelta);
+                int a = gf.E(lgamma + up), b = gf.E(d0 + ltheta);
+                asm volatile("" : "+v"(a), "+v"(b)); // (whole registers: the compiler otherwise cuts their sum to a byte once more)
+                delta = a ^ b;
                 const bool grow = d0 != kZeroLog && kk >= 0;
                 ltheta = grow ? up : ltheta;
                 lgamma = grow ? d0 : lgamma;
@@ -379,81 +473,93 @@ __global__ __launch_bounds__(256) void rs_decode_group_kernel(RsParams p, const 
             // degree of Lambda must equal L (a group's lanes agree on L and fail)
             if (!fail && L > 0) fail = __shfl(ldelta, t + L, G) == kZeroLog;
 
-            // ---- Chien: terms at this lane's first position, then stepped
-            int lam[TMAX + 1], om[TMAX];
-            {
-                int e = 0;
+            // ---- Chien: logarithms of the coefficients (zero beyond t), terms at this lane's first position, then at all of them
+            int llam[TMAX + 1], lam[TMAX + 1];
+            const int lhigh = l <= 2 * t ? ldelta : kZeroLog;
+#pragma unroll
+            for (int j = 0; j <= TMAX; ++j) {
+                llam[j] = __shfl(lhigh, t + j, G);
+            }
+#pragma unroll
+            for (int j = 0; j <= TMAX; ++j) lam[j] = gf.E(llam[j] + byte_of(first_e, j));
+            uint32_t sum[CB / 4];
+#pragma unroll
+            for (int d = 0; d < CB / 4; ++d) sum[d] = (uint32_t)lam[0] * 0x01010101u;
+#pragma unroll
+            for (int j = 1; j <= TMAX; ++j) {
+                Packed<CB> term;
+                term.load(chien + ((j - 1) * q + lam[j]) * CB);
+#pragma unroll
+                for (int d = 0; d < CB / 4; ++d) sum[d] ^= term.d[d];
+            }
+            uint32_t roots = 0; // bit s: symbol l + s G is in error
+#pragma unroll
+            for (int d = 0; d < CB / 4; ++d) {
+                const uint32_t some = ((sum[d] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | sum[d]; // bit 7 of a byte: it is not zero
+                roots |= (((~some >> 7) & 0x01010101u) * 0x01020408u >> 24) << (4 * d);
+            }
+            const int slots = (n - l + G - 1) / G; // symbols this lane holds
+            roots &= !fail && L > 0 ? (1u << max(slots, 0)) - 1u : 0u;
+            if (group_add<G>(__popc(roots)) != L) fail = true;
+            // ---- Forney: the lane's noted positions one after the other, all lanes together
+            if (fail) roots = 0;
+            bool bad = false;
+            uint32_t ev[NR] = {}; // error values, a byte each
+            int lom[TMAX];
+            if (__ballot(roots != 0)) {
+#pragma unroll
+                for (int j = 0; j < TMAX; ++j) lom[j] = __shfl(l < t ? ldelta : kZeroLog, j, G);
+            }
+            while (__ballot(roots != 0)) {
+                const bool has = roots != 0;
+                const int s = has ? __ffs(roots) - 1 : 0;
+                roots &= roots - 1;
+                const int x = mod_once(byte_of(first_e, 1) + s * G, ord); // exponent of 1 / X
+                int e = 0, odd = 0, num = 0;
 #pragma unroll
                 for (int j = 0; j <= TMAX; ++j) {
-                    lam[j] = 0;
-                    if (j < TMAX) om[j] = 0;
-                    if (j <= t) {
-                        lam[j] = gf.E(__shfl(ldelta, t + j, G) + e);
-                        if (j < TMAX) if (j < t) om[j] = gf.E(__shfl(ldelta, j, G) + e);
-                        e = mod_once(e + first_x, ord);
-                    }
+                    if (j < TMAX) num ^= gf.E(lom[j] + e);
+                    if (j & 1) odd ^= gf.E(llam[j] + e);
+                    e = mod_once(e + x, ord);
                 }
+                bad = bad || (has && (odd == 0 || num == 0));
+                const int quot = gf.E(gf.L(num) + (odd ? ord - gf.L(odd) : 0));
+                int lx = lift * x;                            // below 2^16: the quotient is off by one at most
+                lx -= (int)((float)lx * inv_ord) * ord;
+                lx = lx < 0 ? lx + ord : lx >= ord ? lx - ord : lx;
+                const uint32_t v = has ? (uint32_t)gf.E(gf.L(quot) + lx) << (8 * (s & 3)) : 0u;
+#pragma unroll
+                for (int d = 0; d < NR; ++d) ev[d] |= (s >> 2) == d ? v : 0u;
             }
-            int nroots = 0;
-            bool bad = false;
-            int lx = lift0;
-            uint32_t ev[(SPL + 3) / 4]; // error values, a byte each
-#pragma unroll
-            for (int s = 0; s < SPL; ++s) {
-                if (s % 4 == 0) ev[s / 4] = 0;
-                int odd = 0, even = lam[0], num = om[0];
-#pragma unroll
-                for (int j = 1; j <= TMAX; ++j) {
-                    if (j & 1) odd ^= lam[j];
-                    else even ^= lam[j];
-                    if (j < TMAX) num ^= om[j];
-                }
-                const bool root = odd == even && l + s * G < n && !fail && L > 0;
-                if (__ballot(root)) {
-                    nroots += __popc(group_mask<G>(root, lane));
-                    if (root) {
-                        bad = bad || odd == 0 || num == 0;
-                        const int quot = gf.E(gf.L(num) + (odd ? ord - gf.L(odd) : 0));
-                        ev[s / 4] |= (uint32_t)gf.E(gf.L(quot) + lx) << (8 * (s % 4));
-                    }
-                }
-                if (s + 1 < SPL) {
-#pragma unroll
-                    for (int j = 1; j <= TMAX; ++j)
-                        if (j <= t) {
-                            lam[j] = mul_chien[j * q + lam[j]];
-                            if (j < TMAX) om[j] = mul_chien[j * q + om[j]];
-                        }
-                    lx = mod_once(lx + lift_step, ord);
-                }
-            }
-            if (nroots != L || group_mask<G>(bad, lane) != 0) fail = true;
+            if (group_mask<G>(bad, lane) != 0) fail = true;
             if (!fail) {
 #pragma unroll
-                for (int s = 0; s < SPL; ++s) r[s] ^= (int)((ev[s / 4] >> (8 * (s % 4))) & 0xffu);
+                for (int d = 0; d < NR; ++d) r[d] ^= ev[d];
             }
         }
 
         // ---- write back
         int agree = 0;
-#pragma unroll
-        for (int s = 0; s < SPL; ++s) {
-            const int i = l + s * G;
-            if (valid && i < n) {
-                if (cw) cw[w * n + i] = (uint8_t)r[s];
-                if (i < k) {
-                    msg[w * k + i] = (uint8_t)r[s];
-                    if (with_key) agree += p.m - __popc((unsigned)(r[s] ^ s_key[i]) & (unsigned)ord);
-                }
+        const int64_t wo = word_index();
+        if (wo < N) {
+            if (cw) {
+                uint8_t *dst = cw + wo * n + l;
+                each_symbol(n, [&](int s) { dst[s * G] = (uint8_t)(r[s / 4] >> (8 * (s % 4))); });
             }
+            uint8_t *dst = msg + wo * k + l;
+            each_symbol(k, [&](int s) {
+                const uint32_t v = r[s / 4] >> (8 * (s % 4));
+                dst[s * G] = (uint8_t)v;
+                if (with_key) agree += p.m - __popc((v ^ s_key[l + s * G]) & (uint32_t)ord);
+            });
         }
-        if (valid && l == 0) nerr[w] = (int8_t)(fail ? -1 : L);
+        if (wo < N && l == 0) nerr[wo] = (int8_t)(fail ? -1 : L);
         if (with_key) {
 #pragma unroll
             for (int off = G / 2; off >= 1; off >>= 1) agree += __shfl_xor(agree, off, G);
-            if (valid && l == 0) {
-                key.matches[w] = agree;
-                if (key.detected) key.detected[w] = (uint8_t)(agree >= key.tau);
+            if (wo < N && l == 0) {
+                key.matches[wo] = agree;
+                if (key.detected) key.detected[wo] = (uint8_t)(agree >= key.tau);
             }
         }
     }
@@ -487,12 +593,10 @@ template <int G, int TMAX, int SPL>
 hipError_t launch_group(const RsParams &p, const uint8_t *sym, int64_t N, uint8_t *msg, uint8_t *cw, int8_t *nerr,
                         const KeyArgs &key, hipStream_t s)
 {
-    constexpr int GPB = 256 / G;
-    int64_t blocks = (N + GPB - 1) / GPB;
-    const int64_t rounds = (blocks + kGroupBlocks - 1) / kGroupBlocks;
-    if (rounds > 1) blocks = (blocks + rounds - 1) / rounds;
-    hipLaunchKernelGGL((rs_decode_group_kernel<G, TMAX, SPL>), dim3((unsigned)blocks), dim3(256), 0, s, p, sym, N, msg,
-                       cw, nerr, key);
+    constexpr int GPB = kGroupThreads / G;
+    const int64_t blocks = std::min<int64_t>((N + GPB - 1) / GPB, kGroupBlocks);
+    hipLaunchKernelGGL((rs_decode_group_kernel<G, TMAX, SPL>), dim3((unsigned)blocks), dim3(kGroupThreads), (unsigned)p.tab_bytes, s, p,
+                       sym, N, msg, cw, nerr, key);
     return hipGetLastError();
 }
 
@@ -537,10 +641,20 @@ std::vector<uint8_t> rs_table_image(RsParams &p, const std::vector<uint8_t> &exp
     }
     const std::vector<uint8_t> common = img;
     auto add_group = [&](int G) {
-        for (int j = 0; j < p.two_t; ++j)
-            for (int v = 0; v < q; ++v) img.push_back(mul_pow(v, G * (p.fcr + j)));
-        for (int j = 1; j <= p.two_t / 2; ++j)
-            for (int v = 0; v < q; ++v) img.push_back(mul_pow(v, G * j));
+        const int tmax = group_tmax(p.two_t), spl = group_symbols(p.n, G);
+        for (int s = 0; s < spl; ++s)
+            for (int v = 0; v < q; ++v)
+                for (int j = 0; j < 2 * tmax; ++j) img.push_back(j < p.two_t ? mul_pow(v, G * (spl - 1 - s) * (p.fcr + j)) : (uint8_t)0);
+        for (int j = 1; j <= tmax; ++j)
+            for (int v = 0; v < q; ++v)
+                for (int s = 0; s < chien_bytes(spl); ++s) img.push_back(j <= p.two_t / 2 && s < spl ? mul_pow(v, G * j * s) : (uint8_t)0);
+        for (int l = 0; l < G; ++l) {
+            const int last_pw = ((p.n - 1 - l - G * (spl - 1)) % ord + ord) % ord, first_x = ((l - (p.n - 1)) % ord + ord) % ord;
+            const size_t end = img.size() + kLaneBytes;
+            for (int j = 0; j < 2 * tmax; ++j) img.push_back((uint8_t)((p.fcr + j) * last_pw % ord));
+            for (int j = 0; j <= tmax; ++j) img.push_back((uint8_t)(j * first_x % ord));
+            img.resize(end, 0);
+        }
         img.resize((img.size() + 15) / 16 * 16, 0);
     };
     add_group(group_lanes(p.two_t));
@@ -548,6 +662,7 @@ std::vector<uint8_t> rs_table_image(RsParams &p, const std::vector<uint8_t> &exp
     if (second_split(p.n, p.two_t)) { // a second image behind the first
         img.insert(img.end(), common.begin(), common.end());
         add_group(32);
+        p.tab2_bytes = (int)img.size() - p.tab_bytes;
     }
     return img;
 }
@@ -572,19 +687,17 @@ hipError_t launch_rs_decode(const RsParams &p, const uint8_t *sym, int64_t N, ui
     if (takes_second_split(p, N)) {
         RsParams second = p;
         second.tab += p.tab_bytes;
+        second.tab_bytes = p.tab2_bytes;
         return launch_group<32, 4, 8>(second, sym, N, msg, cw, nerr, key, s);
     }
-    if (group_lanes(p.two_t) == 16) {
-        if (p.n <= 16) return launch_group<16, 4, 1>(p, sym, N, msg, cw, nerr, key, s);
-        if (p.n <= 32) return launch_group<16, 4, 2>(p, sym, N, msg, cw, nerr, key, s);
-        if (p.n <= 64) return launch_group<16, 4, 4>(p, sym, N, msg, cw, nerr, key, s);
-        if (p.n <= 128) return launch_group<16, 4, 8>(p, sym, N, msg, cw, nerr, key, s);
-        return launch_group<16, 4, 16>(p, sym, N, msg, cw, nerr, key, s);
+    const bool half = group_lanes(p.two_t) == 16;
+    switch (group_symbols(p.n, half ? 16 : 32)) {
+    case 1: return half ? launch_group<16, 4, 1>(p, sym, N, msg, cw, nerr, key, s) : launch_group<32, 8, 1>(p, sym, N, msg, cw, nerr, key, s);
+    case 2: return half ? launch_group<16, 4, 2>(p, sym, N, msg, cw, nerr, key, s) : launch_group<32, 8, 2>(p, sym, N, msg, cw, nerr, key, s);
+    case 4: return half ? launch_group<16, 4, 4>(p, sym, N, msg, cw, nerr, key, s) : launch_group<32, 8, 4>(p, sym, N, msg, cw, nerr, key, s);
+    case 8: return half ? launch_group<16, 4, 8>(p, sym, N, msg, cw, nerr, key, s) : launch_group<32, 8, 8>(p, sym, N, msg, cw, nerr, key, s);
+    default: return launch_group<16, 4, 16>(p, sym, N, msg, cw, nerr, key, s);
     }
-    if (p.n <= 32) return launch_group<32, 8, 1>(p, sym, N, msg, cw, nerr, key, s);
-    if (p.n <= 64) return launch_group<32, 8, 2>(p, sym, N, msg, cw, nerr, key, s);
-    if (p.n <= 128) return launch_group<32, 8, 4>(p, sym, N, msg, cw, nerr, key, s);
-    return launch_group<32, 8, 8>(p, sym, N, msg, cw, nerr, key, s);
 }
 
 hipError_t launch_verify(const RsParams &p, const uint8_t *msg, int64_t N, const KeyArgs &key, hipStream_t s)

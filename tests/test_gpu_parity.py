@@ -111,6 +111,31 @@ def test_rs_decode_runs_shared_out_evenly(qrm, m, n, t, per):
     ctx.close()
 
 
+@pytest.mark.parametrize("m,n,t,fcr", [(8, 255, 8, 0), (8, 255, 5, 254), (8, 255, 3, 7), (7, 127, 8, 100), (6, 63, 1, 1)])
+def test_rs_decode_an_error_at_every_position(qrm, m, n, t, fcr):
+    """One error at every position and t errors from every position on (every exponent of the locators and error values), in
+    launches around the word count from which a workgroup takes a second run of words."""
+    code = dict(m=m, prim_poly={6: 0x43, 7: 0x89, 8: 0x11D}[m], n=n, k=n - 2 * t, fcr=fcr)
+    lanes = 32 if t > 4 else 16
+    full = 768 * (512 // lanes)
+    g = np.random.default_rng([n, t, fcr])
+    base = oracle.rs_encode(g.integers(0, 1 << m, (2 * n, n - 2 * t)).astype(np.uint8), **code)
+    err = np.zeros_like(base)
+    for i in range(n):
+        err[i, i] = g.integers(1, 1 << m)
+        err[n + i, (i + np.arange(t)) % n] = g.integers(1, 1 << m, t)
+    words = np.tile(base ^ err, ((full + 2 * n) // (2 * n) + 1, 1))
+    om, oc, oe = oracle.rs_decode(words[:2 * n], **code)
+    ctx = qrm.Context(rs=code)
+    for N in (2 * n, full - 1, full, full + 1):
+        reps = N // (2 * n) + 1
+        gm, gc, ge = gpu_rs_decode(ctx, words[:N])
+        assert np.array_equal(ge, np.tile(oe, reps)[:N]), N
+        assert np.array_equal(gm, np.tile(om, (reps, 1))[:N]) and np.array_equal(gc, np.tile(oc, (reps, 1))[:N]), N
+    assert np.array_equal(oe, np.repeat([1, t], n).astype(np.int8)) and np.array_equal(oc, base)
+    ctx.close()
+
+
 @pytest.mark.parametrize("n,t,fcr", [(129, 1, 0), (129, 4, 3), (200, 3, 1), (255, 2, 1), (255, 4, 1)])
 def test_rs_decode_long_words_of_small_t_on_either_split(qrm, n, t, fcr):
     """Words of more than 128 symbols with t <= 4 in launches on both sides of where 16 lanes a word replace 32."""
