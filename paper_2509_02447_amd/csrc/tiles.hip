@@ -107,14 +107,18 @@ __global__ __launch_bounds__(kGatherThreads) void gather_host_tiles_kernel(const
 // channel's unbiased variance up to the common factor n (n-1); the first window with the largest score
 // is the tile.  HBM-bound: every pixel that lies in some window is read exactly once.
 //
-// One workgroup per image.  The image is cut into cells of stride x stride pixels; a window is a square of
+// One workgroup per image, of THREADS threads.  The image is cut into cells of stride x stride pixels; a window is a square of
 // (win / stride)^2 cells.  Phase 1: every lane walks down a run of rows of one 16-byte (or 1-byte) column
-// chunk, sums x (v_sad_u8) and x^2 (v_dot4_u32_u8) in registers and adds them to the cell's 32-bit sums in
-// LDS when it crosses into the next cell row.  Phase 2: one lane per window adds up its cells (64 bit),
+// chunk, of one colour or of all three, sums x (v_sad_u8) and x^2 (v_dot4_u32_u8) in registers and
+// adds them to the cell's 32-bit sums in LDS when it crosses into the next cell row.  Phase 2: one lane per window adds up its cells (64 bit),
 // forms the exact integers n S2 - S1^2, and the score in float64 in a fixed order with no fused
 // multiply-add; a workgroup reduction picks the first maximum.
+// A launch of fewer images than compute units waits for the round trips of its only wave of workgroups: 1024 threads an image
+// instead of 256 (one image of 224 x 224, windows of 96 at strides of 32: 10.6 -> 7.7 us a call, 256 of them 17.1 -> 11.0; 64 of
+// 384 x 384, 64 at 16: 26.4 -> 22.7; 256 of 250 x 250, byte by byte: 54.3 -> 19.4).
 // ------------------------------------------------------------------------------------------------
 constexpr int kMaxCells = 1024; // cells per channel a workgroup can hold
+constexpr int kFewImages = 256;  // a workgroup of 1024 threads for each at most
 
 struct SelectArgs {
     int H, W, win, stride;
@@ -123,17 +127,16 @@ struct SelectArgs {
     double w[3];    // channel weights
 };
 
-template <int VEC>
-__global__ __launch_bounds__(256) void tile_variance_kernel(const uint8_t *__restrict__ img, SelectArgs a,
+template <int VEC, int THREADS>
+__global__ __launch_bounds__(THREADS) void tile_variance_kernel(const uint8_t *__restrict__ img, SelectArgs a,
                                                             int32_t *__restrict__ off_yx, double *__restrict__ scores)
 {
     __shared__ uint32_t s_sum[3][kMaxCells], s_sq[3][kMaxCells];
-    __shared__ double s_best[256];
-    __shared__ int s_idx[256];
+    __shared__ double s_best[THREADS / 64];
+    __shared__ int s_idx[THREADS / 64];
     const int tid = threadIdx.x;
     const int64_t n = blockIdx.x;
-    const int cells = a.nCy * a.nCx;
-    for (int i = tid; i < 3 * kMaxCells; i += 256) {
+    for (int i = tid; i < 3 * kMaxCells; i += THREADS) {
         (&s_sum[0][0])[i] = 0u;
         (&s_sq[0][0])[i] = 0u;
     }
@@ -142,63 +145,69 @@ __global__ __launch_bounds__(256) void tile_variance_kernel(const uint8_t *__res
     // ---- phase 1: cell sums
     const int Hc = a.nCy * a.stride, Wc = a.nCx * a.stride; // the part of the image that windows cover
     const int ncx = Wc / VEC;                                // column chunks per row
-    const int TX = ncx < 256 ? ncx : 256;
-    const int n_rg = 256 / TX;                               // row groups
+    const int TX = ncx < THREADS ? ncx : THREADS;
+    const int n_rg = THREADS / TX;                           // row groups
     const int R = (Hc + n_rg - 1) / n_rg;                    // rows per group
     const int rg = tid / TX;
-    const uint8_t *base = img + n * 3 * (int64_t)a.H * a.W;
+    const int64_t plane = (int64_t)a.H * a.W;
+    const uint8_t *base = img + n * 3 * plane;
+    // colours a lane has on their way together: all of them where few bytes are (bytes instead of 16 at a time, few images)
+    constexpr int TOGETHER = VEC == 1 || THREADS > 256 ? 3 : 1;
     if (rg < n_rg) {
         const int r0 = rg * R, r1 = min(Hc, r0 + R);
-        for (int c = 0; c < 3; ++c) {
-            const uint8_t *plane = base + (int64_t)c * a.H * a.W;
+        for (int c0 = 0; c0 < 3; c0 += TOGETHER)
             for (int cx = tid - rg * TX; cx < ncx; cx += TX) {
                 const int cellx = cx * VEC / a.stride;
-                const uint8_t *col = plane + cx * VEC;
+                const uint8_t *col = base + c0 * plane + cx * VEC;
                 for (int seg = r0; seg < r1;) { // the run's rows, one cell row at a time
                     const int cy = seg / a.stride;
                     const int seg_end = min(r1, (cy + 1) * a.stride);
-                    uint32_t s1 = 0, s2 = 0;
+                    uint32_t s1[TOGETHER] = {}, s2[TOGETHER] = {};
 #pragma unroll 4
                     for (int r = seg; r < seg_end; ++r) { // independent loads: several in flight per lane
-                        const uint8_t *p = col + (int64_t)r * a.W;
-                        if (VEC == 16) {
-                            const uint4 v = *(const uint4 *)p;
-                            s1 = __builtin_amdgcn_sad_u8(v.x, 0u, s1);
-                            s1 = __builtin_amdgcn_sad_u8(v.y, 0u, s1);
-                            s1 = __builtin_amdgcn_sad_u8(v.z, 0u, s1);
-                            s1 = __builtin_amdgcn_sad_u8(v.w, 0u, s1);
-                            s2 = __builtin_amdgcn_udot4(v.x, v.x, s2, false);
-                            s2 = __builtin_amdgcn_udot4(v.y, v.y, s2, false);
-                            s2 = __builtin_amdgcn_udot4(v.z, v.z, s2, false);
-                            s2 = __builtin_amdgcn_udot4(v.w, v.w, s2, false);
-                        } else {
-                            const uint32_t x = *p;
-                            s1 += x;
-                            s2 += x * x;
+#pragma unroll
+                        for (int c = 0; c < TOGETHER; ++c) {
+                            const uint8_t *p = col + c * plane + (int64_t)r * a.W;
+                            if (VEC == 16) {
+                                const uint4 v = *(const uint4 *)p;
+                                s1[c] = __builtin_amdgcn_sad_u8(v.x, 0u, s1[c]);
+                                s1[c] = __builtin_amdgcn_sad_u8(v.y, 0u, s1[c]);
+                                s1[c] = __builtin_amdgcn_sad_u8(v.z, 0u, s1[c]);
+                                s1[c] = __builtin_amdgcn_sad_u8(v.w, 0u, s1[c]);
+                                s2[c] = __builtin_amdgcn_udot4(v.x, v.x, s2[c], false);
+                                s2[c] = __builtin_amdgcn_udot4(v.y, v.y, s2[c], false);
+                                s2[c] = __builtin_amdgcn_udot4(v.z, v.z, s2[c], false);
+                                s2[c] = __builtin_amdgcn_udot4(v.w, v.w, s2[c], false);
+                            } else {
+                                const uint32_t x = *p;
+                                s1[c] += x;
+                                s2[c] += x * x;
+                            }
                         }
                     }
-                    atomicAdd(&s_sum[c][cy * a.nCx + cellx], s1);
-                    atomicAdd(&s_sq[c][cy * a.nCx + cellx], s2);
+#pragma unroll
+                    for (int c = 0; c < TOGETHER; ++c) {
+                        atomicAdd(&s_sum[c0 + c][cy * a.nCx + cellx], s1[c]);
+                        atomicAdd(&s_sq[c0 + c][cy * a.nCx + cellx], s2[c]);
+                    }
                     seg = seg_end;
                 }
             }
-        }
     }
     __syncthreads();
-    (void)cells;
 
     // ---- phase 2: window scores, first maximum
     const int k = a.win / a.stride;
-    const double npix = (double)a.win * (double)a.win; // exact
     double best = -1.0;                               // scores are >= 0
     int best_idx = 0x7fffffff;
-    for (int wi = tid; wi < a.nH * a.nW; wi += 256) {
+    for (int wi = tid; wi < a.nH * a.nW; wi += THREADS) {
         const int wy = wi / a.nW, wx = wi - wy * a.nW;
         double score = 0.0;
         for (int c = 0; c < 3; ++c) {
 #pragma clang fp contract(off) // each product and each sum is rounded on its own: no fused multiply-add
             unsigned long long S1 = 0, S2 = 0;
             for (int dy = 0; dy < k; ++dy)
+#pragma unroll 2
                 for (int dx = 0; dx < k; ++dx) {
                     S1 += s_sum[c][(wy + dy) * a.nCx + wx + dx];
                     S2 += s_sq[c][(wy + dy) * a.nCx + wx + dx];
@@ -207,31 +216,36 @@ __global__ __launch_bounds__(256) void tile_variance_kernel(const uint8_t *__res
             const double term = (double)v * a.w[c];
             score = c == 0 ? term : score + term;
         }
-        (void)npix;
         if (scores) scores[n * (int64_t)(a.nH * a.nW) + wi] = score;
         if (score > best) { // ascending wi: the first maximum stays
             best = score;
             best_idx = wi;
         }
     }
-    s_best[tid] = best;
-    s_idx[tid] = best_idx;
-    __syncthreads();
-    for (int half = 128; half >= 1; half >>= 1) {
-        if (tid < half) {
-            const double o = s_best[tid + half];
-            const int oi = s_idx[tid + half];
-            if (o > s_best[tid] || (o == s_best[tid] && oi < s_idx[tid])) {
-                s_best[tid] = o;
-                s_idx[tid] = oi;
-            }
+    auto take = [&](double o, int oi) {
+        if (o > best || (o == best && oi < best_idx)) {
+            best = o;
+            best_idx = oi;
+        }
+    };
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const double o = __shfl_down(best, off);
+        const int oi = __shfl_down(best_idx, off);
+        take(o, oi);
+    }
+    const int used = min(THREADS / 64, (a.nH * a.nW + 63) / 64); // wavefronts with a window
+    if (used > 1) {
+        if ((tid & 63) == 0) {
+            s_best[tid >> 6] = best;
+            s_idx[tid >> 6] = best_idx;
         }
         __syncthreads();
     }
     if (tid == 0) {
-        const int wi = s_idx[0];
-        off_yx[2 * n] = wi / a.nW * a.stride;
-        off_yx[2 * n + 1] = wi % a.nW * a.stride;
+        for (int v = 1; v < used; ++v) take(s_best[v], s_idx[v]);
+        off_yx[2 * n] = best_idx / a.nW * a.stride;
+        off_yx[2 * n + 1] = best_idx % a.nW * a.stride;
     }
 }
 
@@ -472,10 +486,11 @@ hipError_t launch_select_tiles_variance(const uint8_t *img, int64_t N, int H, in
         const int64_t cnt = N - n0 < kMaxGrid ? N - n0 : kMaxGrid;
         const uint8_t *img0 = img + n0 * 3 * (int64_t)H * W;
         double *sc0 = scores ? scores + n0 * (int64_t)(a.nH * a.nW) : nullptr;
-        if (wide)
-            hipLaunchKernelGGL(tile_variance_kernel<16>, dim3((unsigned)cnt), dim3(256), 0, s, img0, a, off_yx + 2 * n0, sc0);
-        else
-            hipLaunchKernelGGL(tile_variance_kernel<1>, dim3((unsigned)cnt), dim3(256), 0, s, img0, a, off_yx + 2 * n0, sc0);
+        auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)cnt), dim3(threads), 0, s, img0, a, off_yx + 2 * n0, sc0); };
+        if (wide && N <= kFewImages) launch(tile_variance_kernel<16, 1024>, 1024);
+        else if (wide) launch(tile_variance_kernel<16, 256>, 256);
+        else if (N <= kFewImages) launch(tile_variance_kernel<1, 1024>, 1024);
+        else launch(tile_variance_kernel<1, 256>, 256);
     }
     return hipGetLastError();
 }
