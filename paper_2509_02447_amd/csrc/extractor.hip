@@ -1035,14 +1035,16 @@ struct PairArgs {
     const float *rsum;  // [c_in][c_out] residual-weight sums of the first block (fp32)
     float *tout;        // channel sums of the output, or nullptr: [n_img][out_recs][C]
     int out_recs;       // records (LASTB: lines) per image
-    int per;            // pieces (of kChunk row pairs with LASTB, of one row pair otherwise) per workgroup
+    int per;            // pieces (of QUANT row pairs) per workgroup
     int sum_rows;       // LASTB: LastSums::rows, the other places follow from the tile's size
     uint8_t *seam;      // WIDE: [workgroup][2][2 S rows][2 pixels][C] bf16, columns handed to the next column block
     uint8_t *seam_last; // WIDE, width a multiple of 64: [image][2 S rows][2 pixels][C], intermediate columns w-2, w-1
 };
 // Row pairs behind one line of the last block's sums, and the granularity at which its images are cut between
 // workgroups: 1 would store four times as much (35 KB instead of 10 for a 64 x 64 tile), 8 would make the last launch of
-// a single tile twice as long.
+// a single tile twice as long.  Launches of so few tiles that kChunk row pairs are more than a compute unit's share leave a line
+// per row pair instead, which the head adds up in the order in which the kernel would have: the sums are the same bit for bit
+// (the last pair of one tile of 64 x 64: 18.7 -> 11.8 us).
 constexpr int kChunk = 4;
 
 // FIRST: the first of the two blocks is the network's first block (3 -> C on the raw u8 tile: crop and
@@ -1052,10 +1054,11 @@ constexpr int kChunk = 4;
 //        sums (see last_block_statistics).
 // WIDE : tiles of more than one column block (see above); the other instantiations keep the straight-line code
 //        of the one-block case.
+// QUANT: row pairs per piece dealt to workgroups, with LASTB the row pairs behind a line: kChunk or 1 there, 1 otherwise.
 // PART : workgroups take runs of row pairs that begin and end inside images; otherwise every workgroup takes whole
 //        images (st.per is a multiple of an image's pieces), which costs fewer scalar instructions per step.
 // zeros: kZeroBytes of zeros (the source of the padding); in: the input activations of the launch.
-template <int C, bool FIRST, bool LASTB, bool WIDE, bool PART>
+template <int C, bool FIRST, bool LASTB, bool WIDE, bool PART, int QUANT>
 __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__restrict__ zeros, const uint8_t *__restrict__ in, TileSrc src,
                                                            ConvGeom g, const bf16_t *__restrict__ wfragA,
                                                            const bf16_t *__restrict__ wfragB,
@@ -1066,7 +1069,6 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     typedef MidCfg<C> K;
     static_assert(K::NCB == 2, "the pair kernel is written for 64 channels");
     constexpr int RW = 2;
-    constexpr int QUANT = LASTB ? kChunk : 1;     // row pairs per piece dealt to workgroups
     constexpr int ROWB = kHaloW * K::PS;          // staged rows are packed: 66 pixels x 144 bytes
     constexpr int SLOTS = ROWB / 16;              // 16-byte slots per row
     __shared__ __attribute__((aligned(1024))) uint8_t ring_in[FIRST ? 1024 : kPairRing * ROWB];
@@ -1328,8 +1330,8 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
         if (has_first) column(stat, t, x == 0);
         if (has_last) column(stat + 32, t, x == g.w - 1);
         run_sum += reduce16_over_half(t, pxl);
-        if (j % kChunk == kChunk - 1 || j == S - 1) { // the chunk's lines
-            const int ch = j / kChunk, blk2 = p.b * 2 + xb, chunks = (S + kChunk - 1) / kChunk;
+        if (j % QUANT == QUANT - 1 || j == S - 1) { // the chunk's lines
+            const int ch = j / QUANT, blk2 = p.b * 2 + xb, chunks = ppi;
             if ((pxl & 1) == 0) lines[(ch * 2 * J + blk2) * C + reduce16_index(pxl)] = run_sum;
             run_sum = 0.f;
             if (pxl < 16) {
@@ -1882,6 +1884,27 @@ __device__ __forceinline__ f32x4 sum_lines(const f32x4 *p, int stride, int start
     return sum;
 }
 
+// The same over lines r that are `sums.sub` (kChunk) lines each, one per row pair (of sums.pairs): what the kernel
+// would have added up before it wrote them, in its order.  width: lines of one row pair.
+__device__ __forceinline__ f32x4 sum_line_groups(const f32x4 *p, int stride, int start, int step, int count, int width, int pairs)
+{
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int r = start; r < count; r += step) {
+        const int first = r / width * kChunk, b = r % width;
+        f32x4 v[kChunk];
+#pragma unroll
+        for (int u = 0; u < kChunk; ++u) v[u] = p[(int64_t)(min(first + u, pairs - 1) * width + b) * stride];
+#pragma unroll
+        for (int u = 1; u < kChunk; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[0][e] += first + u < pairs ? v[u][e] : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] += v[0][e];
+    }
+    return sum;
+}
+
 constexpr int kHeadIpb = 1;   // images per block (a launch of a few hundred images should reach every compute unit)
 constexpr int kHeadKParts = 8; // the k = (channel, tap) range is cut in eight, one part per 64 threads
 constexpr int kHeadThreads = 64 * kHeadKParts;
@@ -1909,18 +1932,20 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
         constexpr int LPL = C / 4, LPW = 64 / LPL; // lanes per line, lines per wavefront-wide load
         const int wave = tid >> 6, lane = tid & 63, l = lane % LPL, sub = lane / LPL;
         const f32x4 *p = (const f32x4 *)recs + (n0 + i) * sums.lines * LPL + l;
-        auto total = [&](int first, int count, int start, int step, float *dst) {
+        auto total = [&](int first, int count, int start, int step, float *dst, int pair_lines = 0) { // pair_lines: lines per row pair, if they are
             f32x4 v = {0.f, 0.f, 0.f, 0.f};
-            if (have) v = sum_lines(p + first * LPL, LPL, start, step, count);
+            if (have && sums.pairs && pair_lines)
+                v = sum_line_groups(p + first * LPL, LPL, start, step, (sums.pairs + kChunk - 1) / kChunk * pair_lines, pair_lines, sums.pairs);
+            else if (have) v = sum_lines(p + first * LPL, LPL, start, step, count);
 #pragma unroll
             for (int sh = LPL; sh < 64; sh <<= 1)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], sh);
             if (sub == 0) *(f32x4 *)(dst + 4 * l) = v;
         };
-        if (wave < 4) total(0, sums.first_col, wave * LPW + sub, 4 * LPW, &Qp[wave * C]);
-        else if (wave == 4) total(sums.first_col, sums.last_col - sums.first_col, sub, LPW, &Q[i][3 * C]);
-        else if (wave == 5) total(sums.last_col, sums.rows - sums.last_col, sub, LPW, &Q[i][4 * C]);
+        if (wave < 4) total(0, sums.first_col, wave * LPW + sub, 4 * LPW, &Qp[wave * C], 2);
+        else if (wave == 4) total(sums.first_col, sums.last_col - sums.first_col, sub, LPW, &Q[i][3 * C], 1);
+        else if (wave == 5) total(sums.last_col, sums.rows - sums.last_col, sub, LPW, &Q[i][4 * C], 1);
         else if (wave == 6) {
             const int half = (sums.corners - sums.rows) / 2;
             total(sums.rows, half, sub, LPW, &Q[i][1 * C]);
@@ -2137,10 +2162,21 @@ hipError_t launch_conv_mid(const uint8_t *in, const ConvGeom &g, int C, const bf
 
 bool conv_pair_supported(int C, const ConvGeom &g) { return C == 64 && g.colblks >= 1; }
 
-LastSums conv_pair_last_sums(const ConvGeom &g)
+// Whether the last pair leaves a line per row pair instead of one per kChunk of them: where the longest workgroup's run of row
+// pairs gets shorter for it, in launches whose chunks do not reach every compute unit.
+static bool fine_lines(const ConvGeom &g, int num_cu)
 {
     const int chunks = ((g.h + 1) / 2 + kChunk - 1) / kChunk;
+    if (g.colblks > 1 || (int64_t)g.n_img * chunks >= num_cu) return false;
+    return conv_pair_split(g, false, num_cu).cost < conv_pair_split(g, true, num_cu).cost;
+}
+
+LastSums conv_pair_last_sums(const ConvGeom &g, int num_cu)
+{
+    const bool fine = fine_lines(g, num_cu);
+    const int pairs = (g.h + 1) / 2, chunks = fine ? pairs : (pairs + kChunk - 1) / kChunk;
     LastSums l{};
+    l.pairs = fine ? pairs : 0;
     l.seam = g.colblks > 1 && g.w % kTileW == 0;
     l.first_col = chunks * 2 * g.colblks;
     l.last_col = l.first_col + chunks;
@@ -2216,13 +2252,18 @@ WideCost conv_wide_cost(const ConvGeom &g, int num_cu)
     return c;
 }
 
-template <bool FIRST, bool LASTB, bool PART>
+template <bool FIRST, bool LASTB, bool PART, int QUANT>
 static void launch_pair_variant(bool wide, dim3 grid, hipStream_t s, const uint8_t *zeros, const uint8_t *in, const TileSrc &src,
                                 const ConvGeom &g, const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a,
                                 const float *bias_b, const PairArgs &st, bf16_t *out)
 {
-    if (wide) hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, true, PART>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-    else hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, false, PART>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+    if constexpr (!LASTB || QUANT == kChunk) { // (wide tiles leave chunks: fine_lines)
+        if (wide) {
+            hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, true, PART, QUANT>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, false, PART, QUANT>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
 }
 
 hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
@@ -2234,24 +2275,26 @@ hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileS
     const bool wide = g.colblks > 1;
     const bool seam_column = wide && g.w % kTileW == 0;
     if (wide && !seam) return hipErrorInvalidValue;
-    const PairSplit split = conv_pair_split(g, last, num_cu);
+    const LastSums sums = conv_pair_last_sums(g, num_cu);
+    const bool fine = last && sums.pairs;
+    const PairSplit split = conv_pair_split(g, last && !fine, num_cu);
     const dim3 grid((unsigned)split.workgroups);
     if ((int)grid.x > num_cu) return hipErrorInvalidValue; // the seam buffer holds num_cu workgroups
     const size_t half = (size_t)(2 * ((g.h + 1) / 2)) * kSeamRowBytes;
     uint8_t *seam_last = seam_column ? seam + 2 * (size_t)num_cu * half : nullptr;
-    const LastSums sums = conv_pair_last_sums(g);
     const int out_recs = last ? sums.lines : conv_pair_samples(g).recs;
     PairArgs st{tin, rsum_a, tout, out_recs, split.per, sums.rows, seam, seam_last};
     const TileSrc src = first ? *first : TileSrc{};
     auto launch = [&](auto part) {
         constexpr bool PART = decltype(part)::value;
-        if (first) {
-            if (last) launch_pair_variant<true, true, PART>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-            else launch_pair_variant<true, false, PART>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-        } else {
-            if (last) launch_pair_variant<false, true, PART>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-            else launch_pair_variant<false, false, PART>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-        }
+        auto of = [&](auto is_first) {
+            constexpr bool FIRST = decltype(is_first)::value;
+            if (fine) launch_pair_variant<FIRST, true, PART, 1>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            else if (last) launch_pair_variant<FIRST, true, PART, kChunk>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            else launch_pair_variant<FIRST, false, PART, 1>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+        };
+        if (first) of(std::true_type{});
+        else of(std::false_type{});
     };
     if (split.part) launch(std::true_type{});
     else launch(std::false_type{});

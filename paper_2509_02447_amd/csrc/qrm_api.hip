@@ -300,7 +300,7 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
             // would go to takes them; only tiles of a few pixels need more than that
             size_t tail;
             if (!c->collapse) tail = (size_t)conv_final_lines(g) * c->nbp;
-            else if (fused && c->n_blocks % 2 == 0) tail = (size_t)conv_pair_last_sums(g).lines * c->C;
+            else if (fused && c->n_blocks % 2 == 0) tail = (size_t)conv_pair_last_sums(g, launch_cu(c)).lines * c->C;
             else tail = (size_t)conv_mid_last_sums(g, c->C).lines * c->C;
             if ((size_t)cnt * tail * 4 > L.act) L.tail = std::max(L.tail, align_up((size_t)cnt * tail * 4));
             const int samples = std::max(c->pairable ? conv_pair_samples(g).recs : 0,
@@ -456,7 +456,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                                  nullptr, is_last(1) ? tail : tb[tcur], is_last(1), launch_cu(c), seam, buf[cur], s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_pair (first) launch");
             time_end(t, s);
-            if (is_last(1)) last_sums = conv_pair_last_sums(g);
+            if (is_last(1)) last_sums = conv_pair_last_sums(g, launch_cu(c));
             else means = conv_pair_samples(g);
             b = 2;
         } else {
@@ -480,7 +480,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                                      is_last(b + 1) ? tail : tb[tcur ^ 1], is_last(b + 1), launch_cu(c), seam, buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_pair launch");
                 time_end(t, s);
-                if (is_last(b + 1)) last_sums = conv_pair_last_sums(g);
+                if (is_last(b + 1)) last_sums = conv_pair_last_sums(g, launch_cu(c));
                 else means = conv_pair_samples(g);
             } else {
                 qrm_ctx::Timed *t = time_begin(c, may_time, is_last(b) ? QRM_PROFILE_BLOCK_LAST : QRM_PROFILE_BLOCK_MID,

@@ -85,6 +85,7 @@ struct MeanIn {
 // whole-tile and the row lines.
 struct LastSums {
     int lines, first_col, last_col, rows, corners, seam;
+    int pairs; // not 0: a piece is one row pair, and there are this many of them
 };
 MeanIn conv_first_samples(const ConvGeom &g, int C); // (rec null)
 MeanIn conv_mid_samples(const ConvGeom &g, int C);
@@ -128,7 +129,7 @@ WideCost conv_wide_cost(const ConvGeom &g, int num_cu);
 // Whether tiles wider than one column block run the fused schedule.
 bool wide_tiles_fused(const ConvGeom &g, int num_cu);
 PairSplit conv_pair_split(const ConvGeom &g, bool last, int num_cu);
-LastSums conv_pair_last_sums(const ConvGeom &g);
+LastSums conv_pair_last_sums(const ConvGeom &g, int num_cu);
 size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu);
 hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
                             const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a, const float *bias_b,

@@ -331,6 +331,27 @@ def test_results_do_not_depend_on_the_batch_around_a_tile(qrm, C, nb, h, w, flag
         check_logits(lg[None], ref, what=f"C={C} {h}x{w} flags {flags}")
 
 
+@pytest.mark.parametrize("nb,h,w", [(4, 64, 64), (4, 37, 50), (2, 21, 33), (4, 9, 64), (4, 2, 17)])
+def test_last_pair_lines_of_one_row_pair_and_of_four(qrm, nb, h, w):
+    """Launches of few tiles leave a line of sums per row pair, others one per four: the same logits for the same tile, bit for
+    bit, on both sides of where the number of tiles changes that."""
+    border = -(-256 // -(-((h + 1) // 2) // 4))          # tiles whose groups of four row pairs reach every compute unit
+    wts = small_weights(64, nb, 16, nb + h)
+    tiles = np.random.default_rng(h * w).integers(0, 256, size=(border + 1, 3, h, w), dtype=np.uint8)
+    ctx = qrm.Context(weights=wts)
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_POISON_WORKSPACE)
+    got = []
+    for N in (border + 1, border, border - 1, 5, 2, 1):
+        d_tiles, d_log = dev(tiles[:N]), empty((N, 16), torch.float32)
+        ctx.qrm_extractor_forward(d_tiles, N, h, w, d_log, None)
+        torch.cuda.synchronize()
+        got.append(d_log.cpu().numpy())
+    for g in got[1:]:
+        assert np.array_equal(g, got[0][:len(g)])
+    check_logits(got[0][:4].astype(np.float64), oracle.extractor_forward(wts, tiles[:4]), what=f"{nb} blocks {h}x{w}")
+    ctx.close()
+
+
 # (channels, blocks, height, width, flags, final ReLU): the last block or the final convolution alone in its launch
 # (single-block schedule), on tiles of a strip or less, ragged in both directions, of several column blocks
 SPLIT_CASES = [(32, 2, 3, 5, 0, 0), (32, 3, 13, 64, 0, 0), (32, 4, 46, 100, 0, 0), (64, 3, 14, 33, 1, 0), (64, 4, 37, 130, 1, 0),
