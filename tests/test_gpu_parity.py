@@ -348,7 +348,7 @@ def test_last_pair_lines_of_one_row_pair_and_of_four(qrm, nb, h, w):
         got.append(d_log.cpu().numpy())
     for g in got[1:]:
         assert np.array_equal(g, got[0][:len(g)])
-    check_logits(got[0][:4].astype(np.float64), oracle.extractor_forward(wts, tiles[:4]), what=f"{nb} blocks {h}x{w}")
+    check_logits(got[0][:4].astype(np.float64), oracle.extractor_forward(wts, tiles[:4])[0], what=f"{nb} blocks {h}x{w}")
     ctx.close()
 
 
