@@ -32,6 +32,7 @@
 #include <utility>
 
 #include "qrm_internal.h"
+#include "rs_lane.h"
 
 namespace qrm {
 
@@ -1865,7 +1866,12 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
 //   S[c][dy][dx] = sum of channel c over the input pixels that tap (dy,dx) reaches with zero padding
 //                = whole - excluded row - excluded column + their corner
 //   (dy = 0 never reaches the last row, dy = 2 never the first; same for dx and columns).
-// IPB images per block share every weight read.
+// Few images: an image's workgroup waits for its weights (147 KB to a compute unit at 64 channels and 64 outputs), so those of the
+// final convolution and of the linear layer are asked for in 16-byte pieces before the lines of sums are read, and the tables of the
+// code with them where the word is decoded here (head_decodes).  Many images: the weights come out of the L2s again and again; there
+// kHeadShare images share a read.  Against a workgroup per image with 4-byte weight loads inside the sums: one tile of 32 x 32,
+// 32 channels 31.1 -> 29.8 us a call; the launch over 1024 tiles of 64 x 64 20.4 -> 12.6 us, over 256 of 128 x 128, 96 bits
+// 16.5 -> 12.2.
 // ------------------------------------------------------------------------------------------------
 // Sum of the 16-byte pieces p[r * stride], r = start, start + step, .. < count, four loads in flight.
 __device__ __forceinline__ f32x4 sum_lines(const f32x4 *p, int stride, int start, int step, int count)
@@ -1905,45 +1911,125 @@ __device__ __forceinline__ f32x4 sum_line_groups(const f32x4 *p, int stride, int
     return sum;
 }
 
-constexpr int kHeadIpb = 1;   // images per block (a launch of a few hundred images should reach every compute unit)
-constexpr int kHeadKParts = 8; // the k = (channel, tap) range is cut in eight, one part per 64 threads
-constexpr int kHeadThreads = 64 * kHeadKParts;
-
-template <int C>
-__global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restrict__ recs, LastSums sums, int n_img,
-                                                   int n_bits, int nbp, float inv_hw,
-                                                   const float *__restrict__ wft /*[C*9][nbp]*/,
-                                                   const float *__restrict__ fbias, const float *__restrict__ lin_w,
-                                                   const float *__restrict__ lin_b, float *__restrict__ logits,
-                                                   uint8_t *__restrict__ bits, uint8_t *__restrict__ symbols, int m)
+// The image's word from its bits (sbit), by 16 lanes, one symbol each; the errors (a chain of table look-ups) are found by all of them
+// alike.
+__device__ __forceinline__ void decode_image_word(const WordArgs &word, const uint8_t *tab, const uint8_t *sbit, int64_t img, int i)
 {
-    __shared__ __attribute__((aligned(16))) float Q[kHeadIpb][9 * C];        // the image's sums, [q*C + c]
-    __shared__ __attribute__((aligned(16))) float Qp[4 * C];                 // partial sums over the whole-tile lines
-    __shared__ float S[kHeadIpb][9 * C]; // [c*9 + tap]
-    __shared__ float part[kHeadKParts][kHeadIpb][128];
-    __shared__ float pooled[kHeadIpb][128];
-    __shared__ uint8_t sbit[kHeadIpb][128];
-    const int tid = threadIdx.x;
-    const int64_t n0 = (int64_t)blockIdx.x * kHeadIpb;
-    for (int i = 0; i < kHeadIpb; ++i) {
-        const bool have = n0 + i < n_img;
+    const RsParams &p = word.rs;
+    const int ord = p.q - 1;
+    const bool mine = i < p.n;
+    const Gf gf{tab, (const uint16_t *)(tab + kLogAt)};
+    int sym = 0;
+    for (int u = 0; u < p.m; ++u) sym |= mine ? (int)sbit[i * p.m + u] << (p.m - 1 - u) : 0;
+    uint32_t S = mine ? ((const uint32_t *)(tab + kCodeAt))[i * p.q + sym] : 0u;
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) S ^= (uint32_t)__shfl_xor((int)S, off, 16);
+    const LaneErrors err = lane_errors(gf, tab + kQuadAt, S, p.n, ord, p.two_t);
+    if (err.ok && err.count > 0) {
+        const int v1 = lane_error_value(gf, err.p1, err.a1, p.fcr, ord);
+        if (i == p.n - 1 - err.p1) sym ^= v1;
+        if (err.count == 2) {
+            const int v2 = lane_error_value(gf, err.p2, err.a2, p.fcr, ord);
+            if (i == p.n - 1 - err.p2) sym ^= v2;
+        }
+    }
+    if (mine && word.cw) word.cw[img * p.n + i] = (uint8_t)sym;
+    if (i < p.k) word.msg[img * p.k + i] = (uint8_t)sym;
+    if (i == 0) word.nerr[img] = (int8_t)(err.ok ? err.count : -1);
+    if (word.key.matches) {
+        int agree = i < p.k ? p.m - __popc((uint32_t)(sym ^ word.key.key[i]) & (uint32_t)ord) : 0;
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) agree += __shfl_xor(agree, off, 16);
+        if (i == 0) {
+            word.key.matches[img] = agree;
+            if (word.key.detected) word.key.detected[img] = (uint8_t)(agree >= word.key.tau);
+        }
+    }
+}
+
+// Linear layer of NB * 64 outputs (padded with zeros, as the weights' rows are): four lanes to an output, every fourth 16-byte
+// piece of its row each.  The weights are asked for at the start of a launch (weights) and used at its end (of).
+template <int NB>
+struct Linear {
+    f32x4 w[4 * NB];
+    __device__ __forceinline__ void weights(const float *lin_w, int tid)
+    {
+        const float *row = lin_w + min(tid >> 2, 64 * NB - 1) * (64 * NB) + 4 * (tid & 3);
+#pragma unroll
+        for (int j = 0; j < 4 * NB; ++j) w[j] = *(const f32x4 *)(row + 16 * j);
+    }
+    __device__ __forceinline__ float of(const float *pooled, int tid) const // every lane of the four has the output
+    {
+        float z = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4 * NB; ++j) {
+            const f32x4 v = *(const f32x4 *)&pooled[16 * j + 4 * (tid & 3)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z = fmaf(w[j][e], v[e], z);
+        }
+        z += __shfl_xor(z, 1);
+        return z + __shfl_xor(z, 2);
+    }
+};
+
+constexpr int kHeadWaves = 8;
+constexpr int kHeadThreads = 64 * kHeadWaves;
+// A workgroup per image while all of them are resident at once (two to a compute unit), else one per two images.  One / two images a
+// workgroup, whole calls of 32 x 32, 32 channels: 300 tiles 89.7 / 90.6 us, 512 119.3 / 120.0, 1024 196.4 / 192.9, 16384 2959 / 2921.
+// (Four: 94.2, 123.6, 195.6, 2910, but 1024 tiles of 64 x 64 14.8 us where two take 12.6.)
+constexpr int64_t kHeadAlone = 512;
+constexpr int kHeadShare = 2;
+
+// NB = nbp / 64; IPB images to a workgroup
+template <int C, int NB, int IPB>
+__global__ __launch_bounds__(kHeadThreads, 4) void head_kernel(const float *__restrict__ recs, LastSums sums, int n_img, int n_bits,
+                                                               float inv_hw, const float *__restrict__ wft /*[C*9][nbp]*/,
+                                                               const float *__restrict__ fbias, const float *__restrict__ lin_w,
+                                                               const float *__restrict__ lin_b, float *__restrict__ logits,
+                                                               uint8_t *__restrict__ bits, uint8_t *__restrict__ symbols, int m,
+                                                               WordArgs word)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t s_tab[];  // tables of the code, if the words are decoded here
+    __shared__ __attribute__((aligned(16))) float Q[IPB][9 * C];     // an image's sums, [q*C + c]
+    __shared__ __attribute__((aligned(16))) float Qp[IPB][4 * C];    // partial sums over the whole-tile lines
+    __shared__ float S[IPB][9 * C];                                  // [c*9 + tap]
+    __shared__ __attribute__((aligned(16))) float part[kHeadWaves][IPB][64 * NB];
+    __shared__ __attribute__((aligned(16))) float pooled[IPB][64 * NB];
+    __shared__ uint8_t sbit[IPB][64 * NB];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int64_t img0 = (int64_t)blockIdx.x * IPB;
+    // final conv + pool: LPO lanes share the outputs of a k = (channel, tap), four each; a part of KLEN of them
+    constexpr int nbp = 64 * NB, LPO = nbp / 4, KLEN = C * 9 * LPO / kHeadThreads, PRE = IPB > 1 ? 0 : NB == 2 ? 12 : KLEN;
+    const int ol = tid % LPO, k0 = tid / LPO * KLEN;
+    const f32x4 *wf = (const f32x4 *)wft + (int64_t)k0 * LPO + ol;
+    f32x4 wv[PRE ? PRE : 1];
+#pragma unroll
+    for (int j = 0; j < PRE; ++j) wv[j] = wf[j * LPO];
+    Linear<NB> linear;
+    if (IPB == 1) linear.weights(lin_w, tid);
+    if (word.rs.tab) { // needed last: in flight meanwhile
+        for (int i = tid * 16; i < word.rs.tab_bytes; i += kHeadThreads * 16)
+            __builtin_amdgcn_global_load_lds((gptr_t)(word.rs.tab + i), (lptr_t)(s_tab + (i & ~1023)), 16, 0, 0);
+    }
+#pragma unroll 1
+    for (int i = 0; i < IPB; ++i) {
         // lines -> Q: wavefronts 0 .. 3 the whole-tile lines, 4 and 5 the columns, 6 the rows, 7 the corners; 16 bytes per
         // lane, i.e. 256 / C lines per load and four loads in flight
         constexpr int LPL = C / 4, LPW = 64 / LPL; // lanes per line, lines per wavefront-wide load
-        const int wave = tid >> 6, lane = tid & 63, l = lane % LPL, sub = lane / LPL;
-        const f32x4 *p = (const f32x4 *)recs + (n0 + i) * sums.lines * LPL + l;
+        const int l = lane % LPL, sub = lane / LPL;
+        const f32x4 *p = (const f32x4 *)recs + min(img0 + i, (int64_t)n_img - 1) * sums.lines * LPL + l;
         auto total = [&](int first, int count, int start, int step, float *dst, int pair_lines = 0) { // pair_lines: lines per row pair, if they are
-            f32x4 v = {0.f, 0.f, 0.f, 0.f};
-            if (have && sums.pairs && pair_lines)
+            f32x4 v;
+            if (sums.pairs && pair_lines)
                 v = sum_line_groups(p + first * LPL, LPL, start, step, (sums.pairs + kChunk - 1) / kChunk * pair_lines, pair_lines, sums.pairs);
-            else if (have) v = sum_lines(p + first * LPL, LPL, start, step, count);
+            else v = sum_lines(p + first * LPL, LPL, start, step, count);
 #pragma unroll
             for (int sh = LPL; sh < 64; sh <<= 1)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] += __shfl_xor(v[e], sh);
             if (sub == 0) *(f32x4 *)(dst + 4 * l) = v;
         };
-        if (wave < 4) total(0, sums.first_col, wave * LPW + sub, 4 * LPW, &Qp[wave * C], 2);
+        if (wave < 4) total(0, sums.first_col, wave * LPW + sub, 4 * LPW, &Qp[i][wave * C], 2);
         else if (wave == 4) total(sums.first_col, sums.last_col - sums.first_col, sub, LPW, &Q[i][3 * C], 1);
         else if (wave == 5) total(sums.last_col, sums.rows - sums.last_col, sub, LPW, &Q[i][4 * C], 1);
         else if (wave == 6) {
@@ -1951,23 +2037,20 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
             total(sums.rows, half, sub, LPW, &Q[i][1 * C]);
             total(sums.rows + half, half, sub, LPW, &Q[i][2 * C]);
         } else if (sub < 4) {
-            *(f32x4 *)&Q[i][(5 + sub) * C + 4 * l] = have ? p[(sums.corners + sub) * LPL] : (f32x4){0.f, 0.f, 0.f, 0.f};
+            *(f32x4 *)&Q[i][(5 + sub) * C + 4 * l] = p[(sums.corners + sub) * LPL];
         }
-        __syncthreads();
-        if (tid < C) {
-            Q[i][tid] = (Qp[tid] + Qp[C + tid]) + (Qp[2 * C + tid] + Qp[3 * C + tid]);
-            if (sums.seam) { // the last column was computed apart: it is not in the whole-tile and row lines yet
-                Q[i][tid] += Q[i][4 * C + tid];
-                Q[i][1 * C + tid] += Q[i][6 * C + tid];
-                Q[i][2 * C + tid] += Q[i][8 * C + tid];
-            }
-        }
-        __syncthreads();
     }
-    for (int idx = tid; idx < kHeadIpb * C; idx += kHeadThreads) {
-        const int i = idx / C, c = idx - i * C;
-        const float T = Q[i][0 * C + c], R0 = Q[i][1 * C + c], Rl = Q[i][2 * C + c], C0 = Q[i][3 * C + c], Cl = Q[i][4 * C + c];
+    __syncthreads();
+    if (tid < IPB * C) {
+        const int i = tid / C, c = tid % C;
+        float T = (Qp[i][c] + Qp[i][C + c]) + (Qp[i][2 * C + c] + Qp[i][3 * C + c]), R0 = Q[i][1 * C + c], Rl = Q[i][2 * C + c];
+        const float C0 = Q[i][3 * C + c], Cl = Q[i][4 * C + c];
         const float c00 = Q[i][5 * C + c], c0l = Q[i][6 * C + c], cl0 = Q[i][7 * C + c], cll = Q[i][8 * C + c];
+        if (sums.seam) { // the last column was computed apart: it is not in the whole-tile and row lines yet
+            T += Cl;
+            R0 += c0l;
+            Rl += cll;
+        }
 #pragma unroll
         for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
@@ -1983,93 +2066,109 @@ __global__ __launch_bounds__(kHeadThreads) void head_kernel(const float *__restr
             }
     }
     __syncthreads();
-    // final conv + pool: thread (kp, ol) sums its quarter of k for outputs ol, ol + 64
     {
-        const int kp = tid >> 6, ol = tid & 63;
-        const int klen = (C * 9) / kHeadKParts, k0 = kp * klen;
-        for (int o = ol; o < nbp; o += 64) {
-            float acc[kHeadIpb];
+        f32x4 acc[IPB];
 #pragma unroll
-            for (int i = 0; i < kHeadIpb; ++i) acc[i] = 0.f;
-            // (a workgroup alone waits for its weights: 18 loads in flight, which divides 72 and 36, and 12 of the linear layer's below,
-            // instead of 8 and what the compiler takes: 7 tiles of 128 x 128 133.6 -> 131.8 us, 16 of 32 x 32 38.3 -> 37.5)
-#pragma unroll 18
-            for (int k = k0; k < k0 + klen; ++k) {
-                const float wv = wft[(int64_t)k * nbp + o];
+        for (int i = 0; i < IPB; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        auto add = [&](f32x4 w4, int j) {
 #pragma unroll
-                for (int i = 0; i < kHeadIpb; ++i) acc[i] = fmaf(wv, S[i][k], acc[i]);
+            for (int i = 0; i < IPB; ++i) {
+                const float v = S[i][k0 + j];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][e] = fmaf(w4[e], v, acc[i][e]);
             }
+        };
 #pragma unroll
-            for (int i = 0; i < kHeadIpb; ++i) part[kp][i][o] = acc[i];
+        for (int j = 0; j < PRE; ++j) add(wv[j], j);
+        if (KLEN > PRE) {
+#pragma unroll 9
+            for (int j = PRE; j < KLEN; ++j) add(wf[j * LPO], j);
+        }
+        if (IPB > 1) linear.weights(lin_w, tid);
+#pragma unroll
+        for (int i = 0; i < IPB; ++i) {
+#pragma unroll
+            for (int sh = LPO; sh < 64; sh <<= 1)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][e] += __shfl_xor(acc[i][e], sh);
+            if (lane < LPO) *(f32x4 *)&part[wave][i][4 * ol] = acc[i];
         }
     }
     __syncthreads();
-    for (int idx = tid; idx < kHeadIpb * n_bits; idx += kHeadThreads) {
-        const int i = idx / n_bits, o = idx - i * n_bits;
+    if (tid < IPB * nbp) {
+        const int i = tid / nbp, o = tid % nbp;
         float v = 0.f;
 #pragma unroll
-        for (int kp = 0; kp < kHeadKParts; ++kp) v += part[kp][i][o];
-        pooled[i][o] = v * inv_hw + (fbias ? fbias[o] : 0.f);
+        for (int kp = 0; kp < kHeadWaves; ++kp) v += part[kp][i][o];
+        pooled[i][o] = o < n_bits ? v * inv_hw + (fbias ? fbias[o] : 0.f) : 0.f;
     }
     __syncthreads();
-    for (int idx = tid; idx < kHeadIpb * n_bits; idx += kHeadThreads) {
-        const int i = idx / n_bits, o = idx - i * n_bits;
-        float z = lin_b ? lin_b[o] : 0.f;
-#pragma unroll 12
-        for (int k = 0; k < n_bits; ++k) z = fmaf(lin_w[o * n_bits + k], pooled[i][k], z);
-        const uint8_t bt = z > 0.f ? 1 : 0;
-        sbit[i][o] = bt;
-        if (n0 + i < n_img) {
-            if (logits) logits[(n0 + i) * n_bits + o] = z;
-            if (bits) bits[(n0 + i) * n_bits + o] = bt;
+#pragma unroll
+    for (int i = 0; i < IPB; ++i) {
+        float z = linear.of(pooled[i], tid);
+        const int o = tid >> 2;
+        if (o < n_bits && (tid & 3) == 0) {
+            if (lin_b) z += lin_b[o];
+            const uint8_t bt = z > 0.f ? 1 : 0;
+            sbit[i][o] = bt;
+            if (img0 + i < n_img) {
+                if (logits) logits[(img0 + i) * n_bits + o] = z;
+                if (bits) bits[(img0 + i) * n_bits + o] = bt;
+            }
         }
     }
     __syncthreads();
     if (symbols) {
         const int nsym = n_bits / m;
-        for (int idx = tid; idx < kHeadIpb * nsym; idx += kHeadThreads) {
+        for (int idx = tid; idx < IPB * nsym; idx += kHeadThreads) {
             const int i = idx / nsym, j = idx - i * nsym;
-            if (n0 + i < n_img) {
-                int sym = 0;
-                for (int u = 0; u < m; ++u) sym |= (int)sbit[i][j * m + u] << (m - 1 - u);
-                symbols[(n0 + i) * nsym + j] = (uint8_t)sym;
-            }
+            int sym = 0;
+            for (int u = 0; u < m; ++u) sym |= (int)sbit[i][j * m + u] << (m - 1 - u);
+            if (img0 + i < n_img) symbols[(img0 + i) * nsym + j] = (uint8_t)sym;
         }
     }
+    if (word.rs.tab && tid < 16 * IPB && img0 + tid / 16 < n_img) decode_image_word(word, s_tab, sbit[tid / 16], img0 + tid / 16, tid % 16);
 }
 
 // ------------------------------------------------------------------------------------------------
 // pooled -> linear -> logits -> bits -> symbols.  One block per image; its threads share the lines of sums of the image
 // (16 bytes each, four loads in flight).
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *__restrict__ partial, int lines, int nbp,
-                                                                   int n_bits, float inv_hw, const float *__restrict__ fbias,
+template <int NB>
+__global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *__restrict__ partial, int lines, int n_bits,
+                                                                   float inv_hw, const float *__restrict__ fbias,
                                                                    const float *__restrict__ lin_w,
                                                                    const float *__restrict__ lin_b, float *__restrict__ logits,
                                                                    uint8_t *__restrict__ bits, uint8_t *__restrict__ symbols,
                                                                    int m)
 {
+    constexpr int nbp = 64 * NB, lpl = nbp / 4, groups = kHeadThreads / lpl; // lanes per line
     __shared__ __attribute__((aligned(16))) float part[kHeadThreads * 4];
-    __shared__ float pooled[128];
-    __shared__ uint8_t sbit[128];
+    __shared__ __attribute__((aligned(16))) float pooled[nbp];
+    __shared__ uint8_t sbit[nbp];
     const int64_t n = blockIdx.x;
     const int tid = threadIdx.x, o = tid;
-    const int lpl = nbp / 4, groups = kHeadThreads / lpl; // lanes per line
+    Linear<NB> linear;
+    linear.weights(lin_w, tid);
     *(f32x4 *)&part[tid * 4] = sum_lines((const f32x4 *)partial + n * lines * lpl + tid % lpl, lpl, tid / lpl, groups, lines);
     __syncthreads();
-    if (o < n_bits) {
+    if (o < nbp) {
         float s = 0.f;
+#pragma unroll
         for (int g2 = 0; g2 < groups; ++g2) s += part[g2 * nbp + o];
-        pooled[o] = s * inv_hw + (fbias ? fbias[o] : 0.f);
+        pooled[o] = o < n_bits ? s * inv_hw + (fbias ? fbias[o] : 0.f) : 0.f;
     }
     __syncthreads();
-    if (o < n_bits) {
-        float z = lin_b ? lin_b[o] : 0.f;
-        for (int i = 0; i < n_bits; ++i) z = fmaf(lin_w[o * n_bits + i], pooled[i], z);
-        const uint8_t b = z > 0.f ? 1 : 0;
-        if (logits) logits[n * n_bits + o] = z;
-        if (bits) bits[n * n_bits + o] = b;
-        sbit[o] = b;
+    {
+        float z = linear.of(pooled, tid);
+        const int out = tid >> 2;
+        if (out < n_bits && (tid & 3) == 0) {
+            if (lin_b) z += lin_b[out];
+            const uint8_t b = z > 0.f ? 1 : 0;
+            if (logits) logits[n * n_bits + out] = z;
+            if (bits) bits[n * n_bits + out] = b;
+            sbit[out] = b;
+        }
     }
     __syncthreads();
     if (symbols && o < n_bits / m) {
@@ -2306,18 +2405,30 @@ hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileS
     return hipGetLastError();
 }
 
+// The word of an image in the head's launch or in one of its own behind it: a launch costs 4 us and the gap before it, the tables that
+// every workgroup of the head then reads (14 KB for RS(12,8) over GF(256)) cost little by little.  Whole calls of 32 x 32, 32
+// channels, own launch / with the head: 1 tile 34.4 / 30.7 us, 16 35.7 / 31.8, 512 125.3 / 120.3, 2048 386.8 / 382.1, 4096
+// 753.2 / 753.1, 8192 1474 / 1477.
+constexpr int64_t kHeadWords = 2048;
+bool head_decodes(const RsParams &p, int64_t N) { return lane_code(p.n, p.two_t) && N <= kHeadWords; }
+
 hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n_img, int n_bits, int nbp, float inv_hw,
                        const float *wft, const float *fbias, const float *lin_w, const float *lin_b, float *logits,
-                       uint8_t *bits, uint8_t *symbols, int m, hipStream_t s)
+                       uint8_t *bits, uint8_t *symbols, int m, const WordArgs &word, hipStream_t s)
 {
     if (n_img <= 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((n_img + kHeadIpb - 1) / kHeadIpb);
-    if (C == 64)
-        hipLaunchKernelGGL(head_kernel<64>, dim3(blocks), dim3(kHeadThreads), 0, s, recs, sums, (int)n_img, n_bits, nbp, inv_hw, wft,
-                           fbias, lin_w, lin_b, logits, bits, symbols, m);
-    else
-        hipLaunchKernelGGL(head_kernel<32>, dim3(blocks), dim3(kHeadThreads), 0, s, recs, sums, (int)n_img, n_bits, nbp, inv_hw, wft,
-                           fbias, lin_w, lin_b, logits, bits, symbols, m);
+    const unsigned tables = word.rs.tab ? (unsigned)((word.rs.tab_bytes + 1023) / 1024 * 1024) : 0u;
+    auto launch = [&](auto kernel, int per) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((n_img + per - 1) / per)), dim3(kHeadThreads), tables, s, recs, sums, (int)n_img, n_bits,
+                           inv_hw, wft, fbias, lin_w, lin_b, logits, bits, symbols, m, word);
+    };
+    auto of = [&](auto c) {
+        constexpr int CH = decltype(c)::value;
+        if (n_img <= kHeadAlone) launch(nbp == 64 ? head_kernel<CH, 1, 1> : head_kernel<CH, 2, 1>, 1);
+        else launch(nbp == 64 ? head_kernel<CH, 1, kHeadShare> : head_kernel<CH, 2, kHeadShare>, kHeadShare);
+    };
+    if (C == 64) of(std::integral_constant<int, 64>{});
+    else of(std::integral_constant<int, 32>{});
     return hipGetLastError();
 }
 
@@ -2352,8 +2463,8 @@ hipError_t launch_linear_pack(const float *partial, int lines, int nbp, int64_t 
                               uint8_t *bits, uint8_t *symbols, int m, hipStream_t s)
 {
     if (n_img <= 0) return hipSuccess;
-    hipLaunchKernelGGL(linear_pack_kernel, dim3((unsigned)n_img), dim3(kHeadThreads), 0, s, partial, lines, nbp, n_bits, inv_hw,
-                       fbias, lin_w, lin_b, logits, bits, symbols, m);
+    hipLaunchKernelGGL(nbp == 64 ? linear_pack_kernel<1> : linear_pack_kernel<2>, dim3((unsigned)n_img), dim3(kHeadThreads), 0, s, partial,
+                       lines, n_bits, inv_hw, fbias, lin_w, lin_b, logits, bits, symbols, m);
     return hipGetLastError();
 }
 

@@ -413,8 +413,8 @@ void time_end(qrm_ctx::Timed *t, hipStream_t s)
 namespace qrm {
 
 qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc src, int64_t N, int h, int w, int n_run,
-                         float *d_logits, uint8_t *d_bits, uint8_t *d_symbols, int m_sym, float *d_act, bool may_time,
-                         hipStream_t s)
+                         float *d_logits, uint8_t *d_bits, uint8_t *d_symbols, int m_sym, const WordArgs &word, float *d_act,
+                         bool may_time, hipStream_t s)
 {
     const size_t buf_off[2] = {kZeroBytes, kZeroBytes + L.act};
     uint8_t *seam = base + kZeroBytes + 2 * L.act + L.tail + 2 * L.stats;
@@ -424,6 +424,16 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
     float *tb[2] = {(float *)(base + kZeroBytes + 2 * L.act + L.tail),
                     (float *)(base + kZeroBytes + 2 * L.act + L.tail + L.stats)};
     const int nsym = (d_symbols && m_sym > 0) ? c->n_bits / m_sym : 0;
+    auto word_at = [&](int64_t n0) {
+        WordArgs a = word;
+        if (!a.rs.tab) return a;
+        a.msg += n0 * a.rs.k;
+        a.nerr += n0;
+        if (a.cw) a.cw += n0 * a.rs.n;
+        if (a.key.matches) a.key.matches += n0;
+        if (a.key.detected) a.key.detected += n0;
+        return a;
+    };
     const uint8_t *img0 = src.img;
     const int32_t *off0 = src.off;
     const int tpi = tiles_per_image(h, w);
@@ -507,7 +517,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         qrm_ctx::Timed *t = time_begin(c, may_time, QRM_PROFILE_HEAD, 0.0, s);
         if (c->collapse) {
             e = launch_head(tail, last_sums, c->C, cnt, c->n_bits, c->nbp, inv_hw, c->d_wft, c->d_bias_final,
-                            c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, s);
+                            c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, word_at(n0), s);
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {
             const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
@@ -631,7 +641,8 @@ qrm_status qrm_create(const qrm_extractor_desc *ext, const qrm_rs_desc *rs, int 
         const size_t off_fb = fl.size();
         for (int i = 0; i < nbp; ++i) fl.push_back((c->final_affine && i < nbits) ? ext->bias[(size_t)nb * C + i] : 0.f);
         const size_t off_lw = fl.size();
-        for (int i = 0; i < nbits * nbits; ++i) fl.push_back(ext->lin_w[i]);
+        for (int o = 0; o < nbp; ++o) // (rows and columns behind the last are zeros; the rows of 16-byte pieces)
+            for (int k = 0; k < nbp; ++k) fl.push_back(o < nbits && k < nbits ? ext->lin_w[(size_t)o * nbits + k] : 0.f);
         const size_t off_lb = fl.size();
         for (int i = 0; i < nbits; ++i) fl.push_back(ext->lin_b ? ext->lin_b[i] : 0.f);
         while (fl.size() % 4) fl.push_back(0.f);
@@ -885,7 +896,7 @@ static qrm_status extractor_common(qrm_ctx *c, const uint8_t *d_tiles, int64_t N
     if (st != QRM_OK) return st;
     TileSrc src{d_tiles, nullptr, h, w, {c->mean[0], c->mean[1], c->mean[2]},
                 {c->inv_std[0], c->inv_std[1], c->inv_std[2]}};
-    st = run_extractor(c, (uint8_t *)slot->ws, L, src, N, h, w, n_run, d_logits, d_bits, nullptr, 0, d_act, true, s);
+    st = run_extractor(c, (uint8_t *)slot->ws, L, src, N, h, w, n_run, d_logits, d_bits, nullptr, 0, WordArgs{}, d_act, true, s);
     const qrm_status st2 = slot_done(c, slot, s); // also after an error: kernels may have been enqueued
     return st != QRM_OK ? st : st2;
 }
@@ -1020,10 +1031,14 @@ static qrm_status detect_common(qrm_ctx *c, const uint8_t *d_images, int64_t N, 
     uint8_t *d_sym = (uint8_t *)slot->ws + symbols_offset(L);
     TileSrc src{d_images, d_off_yx, H, W, {c->mean[0], c->mean[1], c->mean[2]},
                 {c->inv_std[0], c->inv_std[1], c->inv_std[2]}};
-    st = run_extractor(c, (uint8_t *)slot->ws, L, src, N, tile, tile, -1, d_logits, d_bits, d_sym, c->rs.m, nullptr, true, s);
-    if (st == QRM_OK) {
-        KeyArgs key{};
-        if (verify) key = KeyArgs{(const uint8_t *)c->d_tables, c->key_tau, d_matches, d_detected};
+    KeyArgs key{};
+    if (verify) key = KeyArgs{(const uint8_t *)c->d_tables, c->key_tau, d_matches, d_detected};
+    // (while the two are timed apart, they are two launches)
+    const bool in_head = c->collapse && head_decodes(c->rs, N) && !c->profile;
+    const WordArgs word = in_head ? WordArgs{c->rs, d_msg, d_codeword, d_nerr, key} : WordArgs{};
+    st = run_extractor(c, (uint8_t *)slot->ws, L, src, N, tile, tile, -1, d_logits, d_bits, in_head ? nullptr : d_sym, c->rs.m, word,
+                       nullptr, true, s);
+    if (st == QRM_OK && !in_head) {
         qrm_ctx::Timed *t = time_begin(c, true, QRM_PROFILE_RS_DECODE, 0.0, s);
         e = launch_rs_decode(c->rs, d_sym, N, d_msg, d_codeword, d_nerr, key, s);
         if (e != hipSuccess) st = hip_fail(c, e, "rs_decode launch");

@@ -96,8 +96,8 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
 // `base` laid out as L.  n_run < 0: full pass -> logits / bits / symbols.  n_run >= 1: stop after that many
 // blocks -> d_act.  may_time: launches may be bracketed by events when the context's profiling is on.
 qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc src, int64_t N, int h, int w, int n_run,
-                         float *d_logits, uint8_t *d_bits, uint8_t *d_symbols, int m_sym, float *d_act, bool may_time,
-                         hipStream_t s);
+                         float *d_logits, uint8_t *d_bits, uint8_t *d_symbols, int m_sym, const WordArgs &word, float *d_act,
+                         bool may_time, hipStream_t s);
 
 // Argument checks shared by the entry points that run the whole detection path.
 qrm_status check_detect_args(qrm_ctx *c, const uint8_t *d_images, int64_t N, int32_t H, int32_t W, int32_t tile,

@@ -136,11 +136,35 @@ hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileS
                             const MeanIn &tin, const float *rsum_a, float *tout, bool last, int num_cu,
                             uint8_t *seam, bf16_t *out, hipStream_t s);
 
+struct RsParams {
+    int m, q, n, k, two_t, fcr;
+    const uint8_t *tab; // device, the table image of the code (rs_table_image), 16-byte aligned
+    int tab_bytes;      // what a launch takes of it into LDS, a multiple of 16
+    int tab2_bytes;     // of the second image behind it, if there is one
+};
+
+// Key verification: `key` device [k] symbols; matches null = no verification.
+struct KeyArgs {
+    const uint8_t *key = nullptr;
+    int tau = 0;
+    int32_t *matches = nullptr; // [N] number of message bits equal to the key's
+    uint8_t *detected = nullptr; // [N] matches >= tau, or null
+};
+
+// The word of an image, decoded where its bits are made (rs.tab null: not there).  Pointers: the first image's.
+struct WordArgs {
+    RsParams rs{};
+    uint8_t *msg = nullptr, *cw = nullptr; // cw may be null
+    int8_t *nerr = nullptr;
+    KeyArgs key{};
+};
+bool head_decodes(const RsParams &p, int64_t N); // whether the head of N images is to do that
+
 // recs / sums: channel sums of the last block -> final conv + average pool in closed form -> linear -> logits,
-// bits, symbols.  wft: final conv weights fp32, [C*9][nbp] (k = c*9 + tap major)
+// bits, symbols, decoded words.  wft: final conv weights fp32, [C*9][nbp] (k = c*9 + tap major)
 hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n_img, int n_bits, int nbp, float inv_hw,
                        const float *wft, const float *fbias, const float *lin_w, const float *lin_b, float *logits,
-                       uint8_t *bits, uint8_t *symbols, int m, hipStream_t s);
+                       uint8_t *bits, uint8_t *symbols, int m, const WordArgs &word, hipStream_t s);
 
 // final conv3x3 C -> nbp (n_bits padded to 64s) (+bias, optional ReLU) + sum over pixels -> partial sums
 // partial: f32 [n_img][conv_final_lines()][nbp], each line over a part of the image that does not depend on `part`
@@ -158,21 +182,6 @@ hipError_t launch_linear_pack(const float *partial, int lines, int nbp, int64_t 
 
 // bf16 NHWC -> f32 NCHW (diagnostic)
 hipError_t launch_nhwc_to_nchw(const bf16_t *in, int64_t n_img, int h, int w, int C, float *out, hipStream_t s);
-
-struct RsParams {
-    int m, q, n, k, two_t, fcr;
-    const uint8_t *tab; // device, the table image of the code (rs_table_image), 16-byte aligned
-    int tab_bytes;      // what a launch takes of it into LDS, a multiple of 16
-    int tab2_bytes;     // of the second image behind it, if there is one
-};
-
-// Key verification: `key` device [k] symbols; matches null = no verification.
-struct KeyArgs {
-    const uint8_t *key = nullptr;
-    int tau = 0;
-    int32_t *matches = nullptr; // [N] number of message bits equal to the key's
-    uint8_t *detected = nullptr; // [N] matches >= tau, or null
-};
 
 // The tables the decoding kernels keep in LDS for this code, laid out once per context (p.tab unused; sets p.tab_bytes; codes
 // with two ways of dealing a word to lanes have an image for either, one behind the other);

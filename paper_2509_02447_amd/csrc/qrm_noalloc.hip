@@ -81,8 +81,10 @@ extern "C" qrm_status qrm_detect_static(qrm_ctx *c, const uint8_t *d_images, int
     uint8_t *d_sym = ws + symbols_offset(L);
     TileSrc src{d_images, d_off_yx, H, W, {c->mean[0], c->mean[1], c->mean[2]},
                 {c->inv_std[0], c->inv_std[1], c->inv_std[2]}};
-    st = run_extractor(c, ws, L, src, N, tile, tile, -1, d_logits, d_bits, d_sym, c->rs.m, nullptr, false, s);
-    if (st != QRM_OK) return st;
+    const bool in_head = c->collapse && head_decodes(c->rs, N);
+    const WordArgs word = in_head ? WordArgs{c->rs, d_msg, d_codeword, d_nerr, KeyArgs{}} : WordArgs{};
+    st = run_extractor(c, ws, L, src, N, tile, tile, -1, d_logits, d_bits, in_head ? nullptr : d_sym, c->rs.m, word, nullptr, false, s);
+    if (st != QRM_OK || in_head) return st;
     e = launch_rs_decode(c->rs, d_sym, N, d_msg, d_codeword, d_nerr, KeyArgs{}, s);
     if (e != hipSuccess) return hip_fail(c, e, "rs_decode launch");
     return QRM_OK;

@@ -21,18 +21,13 @@
 #include <algorithm>
 
 #include "qrm_internal.h"
+#include "rs_lane.h"
 
 namespace qrm {
 
 namespace {
 
-// ---- the table image of a code, in global memory and (the same bytes) in LDS
-constexpr int kZeroLog = 512;                 // log of zero: any sum with it indexes the zeros of the antilog table
-constexpr int kExpBytes = 1056;               // antilogs of 0 .. 2 ord - 1, then zeros up to 2 kZeroLog
-constexpr int kLogAt = kExpBytes;             // u16 [256]
-constexpr int kQuadAt = kLogAt + 512;         // u8 [256]: a y with y^2 + y = index, 0 when there is none
-constexpr int kCodeAt = kQuadAt + 256;        // what follows depends on the kernel:
-//   lane kernel : u32 [4 ceil(n/4)][q], the (up to four) syndrome terms of symbol value v at position i, a byte each
+// ---- what the table image holds behind kCodeAt for the group kernel (rs_lane.h has the rest)
 //   group kernel: syndromes: u8 [SPL][q][2 TMAX], byte j of entry (s, v): v * alpha^(G (SPL - 1 - s) (fcr + j)), 0 from 2t on;
 //                 Chien: u8 [TMAX][q][chien_bytes(SPL)], byte s of entry (j - 1, v): v * alpha^(G j s), 0 for j > t
 //                 what differs from lane to lane: u8 [G][kLaneBytes]: exponents of alpha, (fcr + j) last_pw for j < 2 TMAX
@@ -48,7 +43,6 @@ constexpr int kGroupThreads = 512;
 constexpr int64_t kGroupBlocks = 768;
 constexpr int64_t kSecondSplitWords = 10240;
 
-bool lane_code(int n, int two_t) { return n <= 16 && two_t <= 4; }
 int group_symbols(int n, int G) // SPL: symbols per lane, rounded up to a power of two
 {
     int spl = 1;
@@ -62,15 +56,6 @@ int group_lanes(int two_t) { return two_t > 8 ? 32 : 16; } // 3t + 1 coefficient
 bool second_split(int n, int two_t) { return n > 128 && two_t <= 8; }
 bool takes_second_split(const RsParams &p, int64_t N) { return second_split(p.n, p.two_t) && N <= kSecondSplitWords; }
 
-struct Gf {
-    const uint8_t *exp; // LDS
-    const uint16_t *lg; // LDS
-    __device__ __forceinline__ int E(int i) const { return exp[i]; }
-    __device__ __forceinline__ int L(int a) const { return lg[a]; }
-};
-
-__device__ __forceinline__ int mod_once(int e, int ord) { return (int)min((uint32_t)e, (uint32_t)(e - ord)); } // 0 <= e < 2 ord
-
 // table image -> LDS, 16 bytes per lane and step
 template <int THREADS>
 __device__ __forceinline__ void load_tables(uint8_t *dst, const RsParams &p)
@@ -81,14 +66,8 @@ __device__ __forceinline__ void load_tables(uint8_t *dst, const RsParams &p)
 // ------------------------------------------------------------------------------------------------
 // Short codes with t <= 2: one word per lane, nothing repeated across lanes, no serial recursion.
 // A lane holds its word as packed bytes (N4 = ceil(n/4) dwords).  The syndromes of a symbol at its position are ONE
-// 32-bit look-up (all four in it), so the whole syndrome computation is n look-ups and n XORs.  From S0 .. S3:
-//   all zero                              no error
-//   D = S1^2 + S0 S2 = 0                  one error, X = S1 / S0, if S1 S2 = S0 S3 (and S0, S1 are not zero)
-//   D != 0                                two errors: sigma1 = (S1 S2 + S0 S3) / D, sigma2 = (S2^2 + S1 S3) / D,
-//                                         X = sigma1 y with y^2 + y = sigma2 / sigma1^2 from a table
-// and a locator outside the word, a double root or a vanishing sigma is an uncorrectable word: the same words, as
-// these are exactly the cases in which the shortest recursion for S has length 1 or 2 and distinct roots.  t = 1
-// is the one-error branch with S0, S1 alone.
+// 32-bit look-up (all four in it), so the whole syndrome computation is n look-ups and n XORs; the errors follow in closed
+// form (lane_errors).
 // Bound by vector instructions and LDS look-ups, about 200 and 40 per word, close to what the bytes alone take.
 // 2^20 words of RS(12,8) over GF(256), 34.6 MB: 12.5 us a pass = 2.8 TB/s (a
 // recursion per lane with byte-wise loads: 44.5 us); what is left is mostly the launch and the first touch of the tables.
@@ -158,54 +137,16 @@ __global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const u
         uint32_t S = 0;
 #pragma unroll
         for (int i = 0; i < 4 * N4; ++i) S ^= syn[i * p.q + ((r[i / 4] >> (8 * (i % 4))) & 0xffu)];
-        const int S0 = S & 0xff, S1 = (S >> 8) & 0xff;
-        const int l0 = gf.L(S0), l1 = gf.L(S1);
-        int D = 0, lA = kZeroLog, lB = kZeroLog;
-        bool one_ok = S0 && S1;
-        if (p.two_t == 4) {
-            const int l2 = gf.L((S >> 16) & 0xff), l3 = gf.L(S >> 24);
-            D = gf.E(l1 + l1) ^ gf.E(l0 + l2);
-            const int A = gf.E(l1 + l2) ^ gf.E(l0 + l3), B = gf.E(l2 + l2) ^ gf.E(l1 + l3);
-            one_ok = one_ok && A == 0;
-            lA = gf.L(A);
-            lB = gf.L(B);
-        }
-        // ---- locators (as powers p1, p2) and alpha^(fcr p) weighted error values a1, a2
-        int L, p1, p2 = 0, a1, a2 = 0;
-        bool ok;
-        if (D == 0) {
-            L = S ? 1 : 0;
-            ok = S == 0 || one_ok;
-            p1 = one_ok ? mod_once(l1 - l0 + ord, ord) : 0;
-            a1 = S0;
-        } else {
-            L = 2;
-            ok = lA != kZeroLog && lB != kZeroLog;
-            const int lD = gf.L(D);
-            int e = ok ? lB + lD - 2 * lA + 2 * ord : 0; // log (sigma2 / sigma1^2), below 4 ord
-            e = mod_once(e, 2 * ord);
-            const int y = quad[gf.E(e)];
-            ok = ok && y != 0;
-            const int ls = ok ? mod_once(lA - lD + ord, ord) : 0; // log sigma1
-            const int X1 = gf.E(ls + gf.L(y)), X2 = X1 ^ gf.E(ls);
-            p1 = gf.L(X1);
-            p2 = gf.L(X2);
-            a2 = gf.E(gf.L(S1 ^ gf.E(p1 + l0)) + ord - ls); // (S1 + X1 S0) / (X1 + X2)
-            a1 = S0 ^ a2;
-            ok = ok && p2 < n;
-        }
-        ok = ok && p1 < n;
-        if (ok && L > 0) {
+        const LaneErrors err = lane_errors(gf, quad, S, n, ord, p.two_t);
+        if (err.ok && err.count > 0) {
             auto fix = [&](int pw, int a) {
-                int e = pw; // error value = a * alpha^(- fcr pw)
-                if (fcr != 1) e = (int)(__umul24((uint32_t)fcr, (uint32_t)pw) % (uint32_t)ord);
                 const int i = n - 1 - pw;
-                const uint32_t v = (uint32_t)gf.E(gf.L(a) + ord - e) << (8 * (i & 3));
+                const uint32_t v = (uint32_t)lane_error_value(gf, pw, a, fcr, ord) << (8 * (i & 3));
 #pragma unroll
                 for (int j = 0; j < N4; ++j) r[j] ^= (i >> 2) == j ? v : 0u;
             };
-            fix(p1, a1);
-            if (L == 2) fix(p2, a2);
+            fix(err.p1, err.a1);
+            if (err.count == 2) fix(err.p2, err.a2);
         }
 
         // ---- write back
@@ -245,7 +186,7 @@ __global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const u
             __syncthreads();
         }
         if (mine) {
-            nerr[w] = (int8_t)(ok ? L : -1);
+            nerr[w] = (int8_t)(err.ok ? err.count : -1);
             if (key.matches) {
                 int agree = k * p.m;
 #pragma unroll

@@ -352,6 +352,43 @@ def test_last_pair_lines_of_one_row_pair_and_of_four(qrm, nb, h, w):
     ctx.close()
 
 
+@pytest.mark.parametrize("C,m,poly,n,k,fcr", [(32, 4, 0x13, 15, 11, 1), (64, 8, 0x11D, 12, 8, 1), (32, 4, 0x13, 13, 9, 0),
+                                              (32, 3, 0xB, 7, 5, 3), (64, 4, 0x13, 12, 8, 1), (32, 8, 0x11D, 16, 12, 2)])
+def test_words_decoded_by_the_head_and_by_a_launch_of_their_own(qrm, C, m, poly, n, k, fcr):
+    """Small batches have their words decoded where the bits are made, large ones by the decoder's kernel, and the head takes one
+    image a workgroup or two: on both sides of either border, and with the message at an odd address, the oracle's
+    words for the bits that came out, and the same logits for the same tile."""
+    code = dict(m=m, prim_poly=poly, n=n, k=k, fcr=fcr)
+    bits, side = n * m, 8
+    ctx = qrm.Context(weights=small_weights(C, 2, bits, n + m), rs=code)
+    imgs = np.random.default_rng(n * m).integers(0, 256, size=(2049, 3, side, side), dtype=np.uint8)
+    d_imgs, first, key = dev(imgs), None, None
+    for N in (2049, 2048, 513, 512, 1):
+        d_log, d_bits = empty((N, bits), torch.float32), empty((N, bits), torch.uint8)
+        room, d_cw, d_ne = empty((N * k + 1,), torch.uint8), empty((N, n), torch.uint8), empty((N,), torch.int8)
+        d_msg = room[1:]
+        d_matches, d_det = empty((N,), torch.int32), empty((N,), torch.uint8)
+        if key is None:
+            key = np.arange(k, dtype=np.uint8) & ((1 << m) - 1)
+            ctx.qrm_set_key(key, bits // 3)
+        ctx.qrm_detect_verify(d_imgs, N, side, side, None, side, d_log, d_bits, d_msg, d_cw, d_ne, d_matches, d_det)
+        torch.cuda.synchronize()
+        log, b = d_log.cpu().numpy(), d_bits.cpu().numpy()
+        first = log if first is None else first
+        assert np.array_equal(log, first[:N]) and np.array_equal(b, (log > 0).astype(np.uint8))
+        words = (b.reshape(N, n, m) << np.arange(m - 1, -1, -1, dtype=np.uint8)).sum(axis=2).astype(np.uint8)
+        om, oc, oe = oracle.rs_decode(words, **code)
+        msg = d_msg.cpu().numpy().reshape(N, k)
+        assert np.array_equal(d_ne.cpu().numpy(), oe) and np.array_equal(msg, om) and np.array_equal(d_cw.cpu().numpy(), oc)
+        rm, rd = keycheck.verify_key(msg, key, m, bits // 3)
+        assert np.array_equal(d_matches.cpu().numpy(), rm) and np.array_equal(d_det.cpu().numpy(), rd)
+        d_m2, d_n2 = empty((N, k), torch.uint8), empty((N,), torch.int8)  # only what a detector needs
+        ctx.qrm_detect(d_imgs, N, side, side, None, side, None, None, d_m2, None, d_n2)
+        torch.cuda.synchronize()
+        assert np.array_equal(d_m2.cpu().numpy(), om) and np.array_equal(d_n2.cpu().numpy(), oe)
+    ctx.close()
+
+
 # (channels, blocks, height, width, flags, final ReLU): the last block or the final convolution alone in its launch
 # (single-block schedule), on tiles of a strip or less, ragged in both directions, of several column blocks
 SPLIT_CASES = [(32, 2, 3, 5, 0, 0), (32, 3, 13, 64, 0, 0), (32, 4, 46, 100, 0, 0), (64, 3, 14, 33, 1, 0), (64, 4, 37, 130, 1, 0),
