@@ -231,8 +231,8 @@ QRM_API qrm_status qrm_detect(qrm_ctx *ctx, const uint8_t *d_images, int64_t N, 
  * loops, harnesses that forbid hipMalloc.  Same arguments, same results as qrm_detect, but the workspace
  * (activation buffers of a micro-batch, channel statistics, packed symbols) is a fixed array of
  * QRM_STATIC_SCRATCH_BYTES inside the library's device image instead of memory taken from the context, and
- * the call neither allocates nor frees anything, creates no event or stream, and records no memset (the
- * array's block of zeros is cleared by a kernel).  The micro-batch is the largest one that fits the array
+ * the call neither allocates nor frees anything, creates no event or stream, and records no memset.
+ * The micro-batch is the largest one that fits the array
  * (e.g. 56 images of 64 x 64 tiles at 64 channels); qrm_set_micro_batch and the profiling switch do not apply.
  * Every call on a device shares that device's one array (each device holds its own copy until the process
  * ends): calls that overlap in time on one device, on whatever streams or contexts, race.  Calls on one

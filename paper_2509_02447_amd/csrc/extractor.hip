@@ -1050,7 +1050,7 @@ constexpr int kChunk = 4;
 
 // FIRST: the first of the two blocks is the network's first block (3 -> C on the raw u8 tile: crop and
 //        normalisation fused, weights as bf16 high part + residual, see conv_first_kernel) instead of a
-//        C -> C block; `src` replaces ws / in_off, wfragA holds that block's fragments.
+//        C -> C block; `src` replaces in, wfragA holds that block's fragments.
 // LASTB: the second block is the network's last block: no activations are written, but lines of its channel
 //        sums (see last_block_statistics).
 // WIDE : tiles of more than one column block (see above); the other instantiations keep the straight-line code
@@ -1058,9 +1058,9 @@ constexpr int kChunk = 4;
 // QUANT: row pairs per piece dealt to workgroups, with LASTB the row pairs behind a line: kChunk or 1 there, 1 otherwise.
 // PART : workgroups take runs of row pairs that begin and end inside images; otherwise every workgroup takes whole
 //        images (st.per is a multiple of an image's pieces), which costs fewer scalar instructions per step.
-// zeros: kZeroBytes of zeros (the source of the padding); in: the input activations of the launch.
+// in: the input activations of the launch.
 template <int C, bool FIRST, bool LASTB, bool WIDE, bool PART, int QUANT>
-__global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__restrict__ zeros, const uint8_t *__restrict__ in, TileSrc src,
+__global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__restrict__ in, TileSrc src,
                                                            ConvGeom g, const bf16_t *__restrict__ wfragA,
                                                            const bf16_t *__restrict__ wfragB,
                                                            const float *__restrict__ biasA,
@@ -2352,20 +2352,20 @@ WideCost conv_wide_cost(const ConvGeom &g, int num_cu)
 }
 
 template <bool FIRST, bool LASTB, bool PART, int QUANT>
-static void launch_pair_variant(bool wide, dim3 grid, hipStream_t s, const uint8_t *zeros, const uint8_t *in, const TileSrc &src,
+static void launch_pair_variant(bool wide, dim3 grid, hipStream_t s, const uint8_t *in, const TileSrc &src,
                                 const ConvGeom &g, const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a,
                                 const float *bias_b, const PairArgs &st, bf16_t *out)
 {
     if constexpr (!LASTB || QUANT == kChunk) { // (wide tiles leave chunks: fine_lines)
         if (wide) {
-            hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, true, PART, QUANT>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, true, PART, QUANT>), grid, dim3(512), 0, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
             return;
         }
     }
-    hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, false, PART, QUANT>), grid, dim3(512), 0, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+    hipLaunchKernelGGL((conv_pair_kernel<64, FIRST, LASTB, false, PART, QUANT>), grid, dim3(512), 0, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
 }
 
-hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
+hipError_t launch_conv_pair(const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
                             const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a, const float *bias_b,
                             const MeanIn &tin, const float *rsum_a, float *tout, bool last, int num_cu,
                             uint8_t *seam, bf16_t *out, hipStream_t s)
@@ -2388,9 +2388,9 @@ hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileS
         constexpr bool PART = decltype(part)::value;
         auto of = [&](auto is_first) {
             constexpr bool FIRST = decltype(is_first)::value;
-            if (fine) launch_pair_variant<FIRST, true, PART, 1>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-            else if (last) launch_pair_variant<FIRST, true, PART, kChunk>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-            else launch_pair_variant<FIRST, false, PART, 1>(wide, grid, s, zeros, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            if (fine) launch_pair_variant<FIRST, true, PART, 1>(wide, grid, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            else if (last) launch_pair_variant<FIRST, true, PART, kChunk>(wide, grid, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            else launch_pair_variant<FIRST, false, PART, 1>(wide, grid, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
         };
         if (first) of(std::true_type{});
         else of(std::false_type{});

@@ -310,7 +310,7 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
         }
     }
     L.symbols = (want_symbols && c->has_rs) ? align_up((size_t)N * c->rs.n) : 0;
-    L.total = kZeroBytes + 2 * L.act + L.tail + 2 * L.stats + L.seam + L.symbols;
+    L.total = 2 * L.act + L.tail + 2 * L.stats + L.seam + L.symbols;
     return L;
 }
 
@@ -370,10 +370,6 @@ qrm_status get_slot(qrm_ctx *c, hipStream_t s, size_t bytes, QrmSlot **out)
             e = hipMemsetAsync(slot->ws, fill ? fill : 0xFF, bytes, s);
             if (e != hipSuccess) return hip_fail(c, e, "hipMemsetAsync(workspace poison)");
         }
-        // The block of zeros the convolutions read their padding from; written once per allocation, on
-        // the stream of the kernels that read it (the stream may not synchronise with the null stream).
-        e = hipMemsetAsync(slot->ws, 0, kZeroBytes, s);
-        if (e != hipSuccess) return hip_fail(c, e, "hipMemsetAsync(workspace zero block)");
     }
     *out = slot;
     return QRM_OK;
@@ -416,13 +412,13 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
                          float *d_logits, uint8_t *d_bits, uint8_t *d_symbols, int m_sym, const WordArgs &word, float *d_act,
                          bool may_time, hipStream_t s)
 {
-    const size_t buf_off[2] = {kZeroBytes, kZeroBytes + L.act};
-    uint8_t *seam = base + kZeroBytes + 2 * L.act + L.tail + 2 * L.stats;
+    const size_t buf_off[2] = {0, L.act};
+    uint8_t *seam = base + 2 * L.act + L.tail + 2 * L.stats;
     bf16_t *buf[2] = {(bf16_t *)(base + buf_off[0]), (bf16_t *)(base + buf_off[1])};
     // what the last convolution, which reads buf[reading], leaves for the head
-    auto tail_of = [&](int reading) { return L.tail ? (float *)(base + kZeroBytes + 2 * L.act) : (float *)buf[reading ^ 1]; };
-    float *tb[2] = {(float *)(base + kZeroBytes + 2 * L.act + L.tail),
-                    (float *)(base + kZeroBytes + 2 * L.act + L.tail + L.stats)};
+    auto tail_of = [&](int reading) { return L.tail ? (float *)(base + 2 * L.act) : (float *)buf[reading ^ 1]; };
+    float *tb[2] = {(float *)(base + 2 * L.act + L.tail),
+                    (float *)(base + 2 * L.act + L.tail + L.stats)};
     const int nsym = (d_symbols && m_sym > 0) ? c->n_bits / m_sym : 0;
     auto word_at = [&](int64_t n0) {
         WordArgs a = word;
@@ -462,7 +458,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             qrm_ctx::Timed *t = time_begin(c, may_time, is_last(1) ? QRM_PROFILE_PAIR_LAST : QRM_PROFILE_PAIR_FIRST,
                                            (first_flops + block_flops) * cnt, s);
             tail = tail_of(cur); // (it reads no activations)
-            e = launch_conv_pair(base, nullptr, &src, g, c->C, c->d_w_first, c->d_w_mid[0], c->d_bias, c->d_bias + (size_t)c->C, MeanIn{},
+            e = launch_conv_pair(nullptr, &src, g, c->C, c->d_w_first, c->d_w_mid[0], c->d_bias, c->d_bias + (size_t)c->C, MeanIn{},
                                  nullptr, is_last(1) ? tail : tb[tcur], is_last(1), launch_cu(c), seam, buf[cur], s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_pair (first) launch");
             time_end(t, s);
@@ -485,7 +481,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             if (pair) {
                 qrm_ctx::Timed *t = time_begin(c, may_time, is_last(b + 1) ? QRM_PROFILE_PAIR_LAST : QRM_PROFILE_PAIR_MID,
                                                2.0 * block_flops * cnt, s);
-                e = launch_conv_pair(base, base + buf_off[cur], nullptr, g, c->C, c->d_w_mid[m], c->d_w_mid[m + 1],
+                e = launch_conv_pair(base + buf_off[cur], nullptr, g, c->C, c->d_w_mid[m], c->d_w_mid[m + 1],
                                      c->d_bias + (size_t)b * c->C, c->d_bias + (size_t)(b + 1) * c->C, means, rsum,
                                      is_last(b + 1) ? tail : tb[tcur ^ 1], is_last(b + 1), launch_cu(c), seam, buf[cur ^ 1], s);
                 if (e != hipSuccess) return hip_fail(c, e, "conv_pair launch");

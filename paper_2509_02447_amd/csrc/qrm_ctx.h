@@ -82,8 +82,8 @@ namespace qrm {
 qrm_status fail(qrm_ctx *c, qrm_status st, const std::string &msg);
 qrm_status hip_fail(qrm_ctx *c, hipError_t e, const char *what);
 
-// Where the parts of a workspace lie (byte offsets from its base are the running sums, in this order: the
-// block of zeros, two activation buffers, the sums the last convolution leaves for the head, two statistics buffers, the
+// Where the parts of a workspace lie (byte offsets from its base are the running sums, in this order: two
+// activation buffers, the sums the last convolution leaves for the head, two statistics buffers, the
 // columns a fused launch on wide tiles hands from one column block to the next, symbols).
 struct WsLayout {
     size_t act, tail, stats, seam, symbols, total;
@@ -106,6 +106,6 @@ qrm_status check_detect_args(qrm_ctx *c, const uint8_t *d_images, int64_t N, int
 // qrm_noalloc.hip: looks up the device address of the static workspace on `device` (which must be current)
 hipError_t static_scratch_init(int device);
 
-inline size_t symbols_offset(const WsLayout &L) { return kZeroBytes + 2 * L.act + L.tail + 2 * L.stats + L.seam; }
+inline size_t symbols_offset(const WsLayout &L) { return 2 * L.act + L.tail + 2 * L.stats + L.seam; }
 
 } // namespace qrm

@@ -105,10 +105,9 @@ hipError_t launch_conv_mid(const uint8_t *in, const ConvGeom &g, int C, const bf
                            const float *bias, const MeanIn &tin, const float *rsum, float *tout,
                            const Partition &part, bool last, bf16_t *out, hipStream_t s);
 
-constexpr size_t kZeroBytes = 256;
 // Two consecutive blocks in one launch, the activations between them staying in LDS (C = 64:
 // conv_pair_supported; tiles wider than 64 columns are walked through in column blocks and need `seam`,
-// conv_pair_seam_bytes() bytes of scratch).  zeros: kZeroBytes of zeros; in: the input activations.
+// conv_pair_seam_bytes() bytes of scratch).  in: the input activations.
 // first != nullptr: the first of the two is the network's first block (raw u8 tiles, wfrag_a / bias_a of that
 // block; in / tin / rsum_a unused); otherwise both are C -> C blocks and tin / rsum_a are as for
 // launch_conv_mid (first block only: the second block's weights are rounded so that it needs no correction).
@@ -131,7 +130,7 @@ bool wide_tiles_fused(const ConvGeom &g, int num_cu);
 PairSplit conv_pair_split(const ConvGeom &g, bool last, int num_cu);
 LastSums conv_pair_last_sums(const ConvGeom &g, int num_cu);
 size_t conv_pair_seam_bytes(const ConvGeom &g, int num_cu);
-hipError_t launch_conv_pair(const uint8_t *zeros, const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
+hipError_t launch_conv_pair(const uint8_t *in, const TileSrc *first, const ConvGeom &g, int C,
                             const bf16_t *wfrag_a, const bf16_t *wfrag_b, const float *bias_a, const float *bias_b,
                             const MeanIn &tin, const float *rsum_a, float *tout, bool last, int num_cu,
                             uint8_t *seam, bf16_t *out, hipStream_t s);

@@ -18,11 +18,6 @@ uint8_t *g_scratch_ptr[kMaxDevices];   // device address of `scratch` on each de
 hipError_t g_scratch_err[kMaxDevices];
 bool g_scratch_known[kMaxDevices];
 
-__global__ void clear_zero_block_kernel(u32x4 *p) // the kZeroBytes the convolutions read their padding from
-{
-    if (threadIdx.x < kZeroBytes / 16) p[threadIdx.x] = (u32x4){0u, 0u, 0u, 0u};
-}
-
 } // namespace
 
 namespace qrm {
@@ -72,12 +67,7 @@ extern "C" qrm_status qrm_detect_static(qrm_ctx *c, const uint8_t *d_images, int
                  (long long)N, tile, tile, (unsigned)(QRM_STATIC_SCRATCH_BYTES >> 20));
         return fail(c, QRM_E_UNSUPPORTED, buf);
     }
-    // The array keeps what the previous call left.  Every kernel of the path writes what it later reads,
-    // except the block of zeros at the start, which is cleared here (by a kernel: a memset node must not
-    // end up in a captured graph).
-    hipLaunchKernelGGL(clear_zero_block_kernel, dim3(1), dim3(64), 0, s, (u32x4 *)ws);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(c, e, "clear_zero_block launch");
+    // The array keeps what the previous call left: every kernel of the path writes what a later one reads.
     uint8_t *d_sym = ws + symbols_offset(L);
     TileSrc src{d_images, d_off_yx, H, W, {c->mean[0], c->mean[1], c->mean[2]},
                 {c->inv_std[0], c->inv_std[1], c->inv_std[2]}};
