@@ -259,7 +259,9 @@ __global__ __launch_bounds__(THREADS) void tile_variance_kernel(const uint8_t *_
 //
 // One workgroup per (image, strip of rows).  The column taps of the window are computed once into LDS
 // (two integer divisions per column), a lane then produces four neighbouring pixels of a row for the
-// three colours and writes one dword per plane.
+// three colours and writes one dword per plane.  Bound by the memory system.  Eight loads of eight bytes a lane and 18 KB of
+// tables (eight workgroups a compute unit) instead of 16 of four and 26 KB (six): 600 images of 480 x 640 to 256 x 256, with
+// the selection and crop behind it, 166.1 -> 164.2 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int kCoefBits = 11;
 constexpr int kMaxTile = 1024; // columns of a window
@@ -287,20 +289,20 @@ __device__ __forceinline__ void source_taps(int dst, int n_in, int n_res, int &i
 
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 
-// One colour of one window pixel from the dwords that hold its four taps (p00 p01 above p10 p11).  sel picks the
-// colour's byte out of the left tap (low half) and the right tap (high half), wx = wx0 | wx1 << 16.  The horizontal
+// One colour of one window pixel from the eight bytes of either row that hold its taps (top0 top1 above bot0 bot1).  sel picks the
+// colour's byte of the left tap (low half) and of the right tap (high half), wx = wx0 | wx1 << 16.  The horizontal
 // pass is a two-term dot product of 16-bit fields (< 2^19), the vertical pass two 24-bit products (< 2^30): all
 // full-rate instructions, and the same integers as the plain formula.
-__device__ __forceinline__ uint32_t bilinear_byte(uint32_t p00, uint32_t p01, uint32_t p10, uint32_t p11, uint32_t sel,
+__device__ __forceinline__ uint32_t bilinear_byte(uint32_t top0, uint32_t top1, uint32_t bot0, uint32_t bot1, uint32_t sel,
                                                   uint32_t wx, uint32_t wy0, uint32_t wy1)
 {
-    const uint32_t t = __builtin_amdgcn_perm(p01, p00, sel), b = __builtin_amdgcn_perm(p11, p10, sel);
+    const uint32_t t = __builtin_amdgcn_perm(top1, top0, sel), b = __builtin_amdgcn_perm(bot1, bot0, sel);
     const uint32_t top = __builtin_amdgcn_udot2(__builtin_bit_cast(ushort2_t, t), __builtin_bit_cast(ushort2_t, wx), 0u, false);
     const uint32_t bot = __builtin_amdgcn_udot2(__builtin_bit_cast(ushort2_t, b), __builtin_bit_cast(ushort2_t, wx), 0u, false);
     const uint32_t sum = __umul24(top, wy0) + (__umul24(bot, wy1) + (1u << (2 * kCoefBits - 1)));
     return sum >> (2 * kCoefBits);
 }
-constexpr uint32_t kSelect = 0x0c040c00u; // byte 0 of the second operand -> bits 0..7, byte 0 of the first -> 16..23
+constexpr uint32_t kSelect = 0x0c000c00u; // a byte to bits 0..7 (its number 0..7 is added), one to bits 16..23, zeros between
 
 // Walks the (row, pixel group) pairs of a strip, 256 at a time, without a division per step.
 struct StripWalk {
@@ -327,7 +329,7 @@ template <int VEC, bool WORDS>
 __global__ __launch_bounds__(256) void preprocess_kernel(const uint8_t *__restrict__ raw, PreArgs a,
                                                          const int32_t *__restrict__ off, uint8_t *__restrict__ out)
 {
-    __shared__ int s_x0[kMaxTile], s_x1[kMaxTile], s_y0[kMaxTile], s_y1[kMaxTile];
+    __shared__ int s_x[kMaxTile], s_y[kMaxTile];
     __shared__ uint32_t s_wx[kMaxTile], s_sel[kMaxTile];
     __shared__ uint16_t s_wy[kMaxTile];
     const int tid = threadIdx.x;
@@ -341,19 +343,18 @@ __global__ __launch_bounds__(256) void preprocess_kernel(const uint8_t *__restri
     for (int t = tid; t < a.T; t += 256) {
         int i0, i1, w1;
         source_taps(a.cx + ox + t, a.W_in, a.Wr, i0, i1, w1);
-        // A pixel's three bytes are fetched with ONE (unaligned) dword load: bytes 3i-1 .. 3i+2 for i > 0 (the colours
-        // are its upper three bytes), bytes 0 .. 3 for i = 0; both stay inside the row (rows have at least two pixels
-        // on this path; one-pixel rows are read byte by byte).  The byte selector carries the "skip one".
-        s_x0[t] = WORDS ? (i0 > 0 ? 3 * i0 - 1 : 0) : i0 * 3;
-        s_x1[t] = WORDS ? (i1 > 0 ? 3 * i1 - 1 : 0) : i1 * 3;
-        s_sel[t] = kSelect + (WORDS && i0 > 0 ? 1u : 0u) + (WORDS && i1 > 0 ? 0x10000u : 0u);
+        // The six bytes of both taps come with ONE (unaligned) load of eight, from the left tap's first byte on or, at the row's
+        // end, its last eight: always inside the row (rows have at least three pixels on this path).  The byte
+        // selector carries where the taps lie in them.
+        const int at = WORDS ? min(3 * i0, 3 * a.W_in - 8) : 3 * i0;
+        s_x[t] = at;
+        s_sel[t] = kSelect + (WORDS ? (uint32_t)(3 * i0 - at) | (uint32_t)(3 * i1 - at) << 16 : 3u << 16);
         s_wx[t] = (uint32_t)((1 << kCoefBits) - w1) | (uint32_t)w1 << 16;
     }
     for (int t = tid; t < r_end - r_begin; t += 256) {
         int y0, y1, wy1;
         source_taps(a.cy + oy + r_begin + t, a.H_in, a.Hr, y0, y1, wy1);
-        s_y0[t] = y0;
-        s_y1[t] = y1;
+        s_y[t] = y0;
         s_wy[t] = (uint16_t)wy1;
     }
     __syncthreads();
@@ -363,27 +364,27 @@ __global__ __launch_bounds__(256) void preprocess_kernel(const uint8_t *__restri
     for (StripWalk w(tid, a.T / VEC); w.row < r_end - r_begin; w.next()) {
         const int ty = r_begin + w.row, tx = w.grp * VEC;
         const uint32_t wy1 = s_wy[w.row], wy0 = (1u << kCoefBits) - wy1;
-        const uint8_t *row0 = img + (int64_t)s_y0[w.row] * a.W_in * 3, *row1 = img + (int64_t)s_y1[w.row] * a.W_in * 3;
+        const int y0 = s_y[w.row], y1 = min(y0 + 1, a.H_in - 1);
+        const uint8_t *row0 = img + (int64_t)y0 * a.W_in * 3, *row1 = img + (int64_t)y1 * a.W_in * 3;
         uint32_t pk[3] = {0u, 0u, 0u};
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
-            const int b0 = s_x0[tx + v], b1 = s_x1[tx + v];
+            const int at = s_x[tx + v];
             const uint32_t wx = s_wx[tx + v], sel = s_sel[tx + v];
-            uint32_t p00, p01, p10, p11; // the three colours of the four taps, one per byte
+            uint32_t p[2][2]; // [row]: the three colours of the left tap, then of the right one, somewhere in eight bytes
             if (WORDS) {
-                __builtin_memcpy(&p00, row0 + b0, 4);
-                __builtin_memcpy(&p01, row0 + b1, 4);
-                __builtin_memcpy(&p10, row1 + b0, 4);
-                __builtin_memcpy(&p11, row1 + b1, 4);
+                __builtin_memcpy(p[0], row0 + at, 8);
+                __builtin_memcpy(p[1], row1 + at, 8);
             } else {
-                p00 = row0[b0] | row0[b0 + 1] << 8 | row0[b0 + 2] << 16;
-                p01 = row0[b1] | row0[b1 + 1] << 8 | row0[b1 + 2] << 16;
-                p10 = row1[b0] | row1[b0 + 1] << 8 | row1[b0 + 2] << 16;
-                p11 = row1[b1] | row1[b1 + 1] << 8 | row1[b1 + 2] << 16;
+                const int b1 = min(at + 3, 3 * a.W_in - 3);
+                p[0][0] = row0[at] | row0[at + 1] << 8 | row0[at + 2] << 16 | (uint32_t)row0[b1] << 24;
+                p[0][1] = row0[b1 + 1] | row0[b1 + 2] << 8;
+                p[1][0] = row1[at] | row1[at + 1] << 8 | row1[at + 2] << 16 | (uint32_t)row1[b1] << 24;
+                p[1][1] = row1[b1 + 1] | row1[b1 + 2] << 8;
             }
 #pragma unroll
             for (int c = 0; c < 3; ++c)
-                pk[c] |= bilinear_byte(p00, p01, p10, p11, sel + c * 0x10001u, wx, wy0, wy1) << (8 * v);
+                pk[c] |= bilinear_byte(p[0][0], p[0][1], p[1][0], p[1][1], sel + c * 0x10001u, wx, wy0, wy1) << (8 * v);
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -418,7 +419,7 @@ bool preprocess_supported(int H_in, int W_in, int x, int T)
            (int64_t)2 * std::max(Hr, Wr) * 2048 < (1LL << 31);
 }
 
-// Strips a T x T window is cut into when a launch has N of them.  Enough workgroups for the chip several times over (six fit
+// Strips a T x T window is cut into when a launch has N of them.  Enough workgroups for the chip several times over (eight fit
 // a compute unit), so that no last wave of them is nearly empty: 600 images of 480 x 640 to 256 x 256 take 153 us in 3
 // strips an image (1.2 waves), 144 in 6, 139 in 13, the same from there on.  But a strip's column taps are its own, so
 // beyond one wave a strip keeps four turns of 256 pixel groups: 1024 tiles of 64 x 64 out of 512 x 512 images 12.0 us in 1
@@ -451,7 +452,7 @@ hipError_t launch_preprocess(const uint8_t *raw, int64_t N, int H_in, int W_in, 
         const int32_t *off0 = off ? off + 2 * n0 : nullptr;
         uint8_t *out0 = out + n0 * 3 * (int64_t)T * T;
         const dim3 grid((unsigned)cnt, (unsigned)strips);
-        const bool words = W_in >= 2; // a one-pixel row has no room for a dword
+        const bool words = W_in >= 3; // shorter rows have no room for eight bytes
         if (vec && words) hipLaunchKernelGGL((preprocess_kernel<4, true>), grid, dim3(256), 0, s, raw0, a, off0, out0);
         else if (vec) hipLaunchKernelGGL((preprocess_kernel<4, false>), grid, dim3(256), 0, s, raw0, a, off0, out0);
         else if (words) hipLaunchKernelGGL((preprocess_kernel<1, true>), grid, dim3(256), 0, s, raw0, a, off0, out0);

@@ -1170,6 +1170,23 @@ def test_preprocess_bit_exact(qrm, N, H_in, W_in, size, tile):
     ctx.close()
 
 
+@pytest.mark.parametrize("W_in", [2, 3, 4, 5])
+def test_preprocess_of_rows_of_about_eight_bytes(qrm, W_in):
+    """Both taps of a row come in one load of eight bytes, the row's last eight at its end: rows that are shorter, one byte longer
+    and more, enlarged, from a buffer that ends where the last row does and at every address modulo four."""
+    g = np.random.default_rng(W_in)
+    for N, H_in, size, shift in ((1, 3, 8, 0), (3, 5, 12, 1), (2, 2, 7, 2), (2, W_in, W_in, 3)):
+        raw = g.integers(0, 256, size=(N, H_in, W_in, 3), dtype=np.uint8)
+        room = empty((shift + raw.size,), torch.uint8)
+        room[shift:] = dev(raw).reshape(-1)
+        d_out = empty((N, 3, size, size), torch.uint8)
+        ctx = qrm.Context(rs=rs_dict(synth.CONFIGS["C1"]))
+        ctx.qrm_preprocess(room[shift:], N, H_in, W_in, size, None, 0, d_out)
+        torch.cuda.synchronize()
+        assert np.array_equal(d_out.cpu().numpy(), pre_oracle.preprocess(raw, size, None, 0)), (N, H_in, size, shift)
+        ctx.close()
+
+
 @pytest.mark.parametrize("shift_in,shift_out", [(5, 0), (0, 3), (13, 1)])
 def test_preprocess_buffers_at_odd_addresses(qrm, shift_in, shift_out):
     """Raw and output buffers that start at any byte: word loads and dword stores must not assume more."""
