@@ -56,6 +56,14 @@ QRM_API qrm_status qrm_diag_wide_schedule(int32_t n_img, int32_t h, int32_t w, i
                                           double *single_us, double *fused_us);
 
 /*
+ * *row_pairs = row pairs behind one line of the sums that the last fused launch (64 channels) on n_img tiles of h x w leaves for the
+ * head: 1 in launches of few tiles, 4 otherwise; *bytes = what a stream's workspace takes for a call of that many tiles
+ * through n_blocks blocks of 64 channels without a final ReLU (no code).  Host code, no device needed.
+ */
+QRM_API qrm_status qrm_diag_last_lines(int32_t n_img, int32_t h, int32_t w, int32_t n_blocks, int32_t num_cu, int32_t *row_pairs,
+                                       int64_t *bytes);
+
+/*
  * How qrm_detect_host brings its chunks in (page-locked images of H x W, a network of `channels` and n_blocks without a
  * final ReLU, `used` staging buffers in use): *first / *rest = 1 the first / the later chunks as tiles, 0 as whole images;
  * *lent = compute units the kernels leave to the gather of the next chunk.  Host code, no device needed.

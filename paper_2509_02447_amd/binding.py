@@ -42,7 +42,7 @@ EXPORTS = ["qrm_create", "qrm_destroy", "qrm_last_error", "qrm_set_micro_batch",
            "qrm_detect_host", "qrm_plan_streams", "qrm_key_threshold", "qrm_set_key", "qrm_verify_key", "qrm_detect_verify",
            "qrm_profile_enable", "qrm_profile_read", "qrm_profile_read_chunks", "qrm_release_stream", "qrm_detect_static", "qrm_version"]
 DIAG_EXPORTS = ["qrm_diag_set_flags", "qrm_diag_matrix_rate", "qrm_diag_pair_split",
-                "qrm_diag_wide_schedule", "qrm_diag_host_plan",
+                "qrm_diag_wide_schedule", "qrm_diag_last_lines", "qrm_diag_host_plan",
                 "qrm_diag_preprocess_strips", "qrm_diag_rs_lanes"]   # include/qrm_diag.h: bench and test tooling
 
 QRM_MAX_STREAMS = 8   # include/qrm.h
@@ -122,6 +122,8 @@ def load_library():
     lib.qrm_diag_pair_split.restype = C.c_int
     lib.qrm_diag_wide_schedule.argtypes = [i32] * 4 + [C.POINTER(i32), C.POINTER(C.c_double), C.POINTER(C.c_double)]
     lib.qrm_diag_wide_schedule.restype = C.c_int
+    lib.qrm_diag_last_lines.argtypes = [i32] * 5 + [C.POINTER(i32), C.POINTER(i64)]
+    lib.qrm_diag_last_lines.restype = C.c_int
     lib.qrm_diag_host_plan.argtypes = [i32] * 8 + [C.POINTER(i32)] * 3
     lib.qrm_diag_host_plan.restype = C.c_int
     lib.qrm_diag_preprocess_strips.argtypes = [i64, i32, C.POINTER(i32)]

@@ -2262,11 +2262,14 @@ hipError_t launch_conv_mid(const uint8_t *in, const ConvGeom &g, int C, const bf
 bool conv_pair_supported(int C, const ConvGeom &g) { return C == 64 && g.colblks >= 1; }
 
 // Whether the last pair leaves a line per row pair instead of one per kChunk of them: where the longest workgroup's run of row
-// pairs gets shorter for it, in launches whose chunks do not reach every compute unit.
+// pairs gets shorter for it, in launches whose chunks do not reach every compute unit, as long as an image's lines fit the place of
+// its activations (64 channels, two bytes a pixel): on tiles of up to four columns they do not, and with a block of their own for
+// them a batch of 24 tiles of 64 x 4 took a workspace half as large again as one of 25.
 static bool fine_lines(const ConvGeom &g, int num_cu)
 {
-    const int chunks = ((g.h + 1) / 2 + kChunk - 1) / kChunk;
+    const int pairs = (g.h + 1) / 2, chunks = (pairs + kChunk - 1) / kChunk;
     if (g.colblks > 1 || (int64_t)g.n_img * chunks >= num_cu) return false;
+    if ((int64_t)(4 * pairs + 8) * 4 > (int64_t)g.h * g.w * 2) return false; // (4 pairs + 8 lines: conv_pair_last_sums)
     return conv_pair_split(g, false, num_cu).cost < conv_pair_split(g, true, num_cu).cost;
 }
 

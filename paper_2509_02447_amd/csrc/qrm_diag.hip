@@ -124,6 +124,21 @@ qrm_status qrm_diag_wide_schedule(int32_t n_img, int32_t h, int32_t w, int32_t n
     return QRM_OK;
 }
 
+qrm_status qrm_diag_last_lines(int32_t n_img, int32_t h, int32_t w, int32_t n_blocks, int32_t num_cu, int32_t *row_pairs,
+                               int64_t *bytes)
+{
+    if (n_img < 1 || h < 1 || w < 1 || n_blocks < 2 || num_cu < 1 || !row_pairs || !bytes) return QRM_E_INVALID;
+    const ConvGeom g{n_img, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
+    qrm_ctx c;
+    c.num_cu = num_cu;
+    c.has_ext = c.collapse = c.pairable = true;
+    c.n_blocks = n_blocks;
+    c.C = 64;
+    *row_pairs = conv_pair_last_sums(g, num_cu).pairs ? 1 : 4;
+    *bytes = (int64_t)ws_layout(&c, n_img, h, w, false).total;
+    return QRM_OK;
+}
+
 qrm_status qrm_diag_host_plan(int32_t channels, int32_t n_blocks, int32_t H, int32_t W, int32_t tile, int32_t chunk_images,
                               int32_t used, int32_t num_cu, int32_t *first, int32_t *rest, int32_t *lent)
 {

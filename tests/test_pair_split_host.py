@@ -115,3 +115,19 @@ def test_wide_tiles_schedule_limits():
     f, s, u = C.c_int32(), C.c_double(), C.c_double()
     from paper_2509_02447_amd import binding as b
     assert b.load_library().qrm_diag_wide_schedule(10, 10, 64, 256, C.byref(f), C.byref(s), C.byref(u)) != 0
+
+
+def last_lines(n, h, w, blocks=4):
+    from paper_2509_02447_amd import binding as b
+    pairs, size = C.c_int32(), C.c_int64()
+    assert b.load_library().qrm_diag_last_lines(n, h, w, blocks, CU, C.byref(pairs), C.byref(size)) == 0
+    return pairs.value, size.value
+
+
+@pytest.mark.parametrize("w", [1, 2, 3, 4, 5, 6, 8, 16, 33, 64])
+@pytest.mark.parametrize("h", [1, 2, 7, 16, 33, 64, 75, 128])
+def test_a_smaller_batch_needs_no_larger_workspace(h, w):
+    """Launches of few tiles leave four times as many lines of sums; a stream that has served a batch serves every smaller one
+    without a new workspace."""
+    sizes = [last_lines(n, h, w)[1] for n in range(1, 300)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:])), (h, w)
