@@ -28,14 +28,19 @@ namespace qrm {
 namespace {
 
 // ---- what the table image holds behind kCodeAt for the group kernel (rs_lane.h has the rest)
-//   group kernel: syndromes: u8 [SPL][q][2 TMAX], byte j of entry (s, v): v * alpha^(G (SPL - 1 - s) (fcr + j)), 0 from 2t on;
-//                 Chien: u8 [TMAX][q][chien_bytes(SPL)], byte s of entry (j - 1, v): v * alpha^(G j s), 0 for j > t
+//   group kernel: (SPL > 1) syndromes: u8 [SPL][q][2 TMAX], byte j of entry (s, v): v * alpha^(G (SPL - 1 - s) (fcr + j)), 0 from 2t on;
+//                 (SPL > 1) Chien: u8 [TMAX][q][chien_bytes(SPL)], byte s of entry (j - 1, v): v * alpha^(G j s), 0 for j > t
 //                 what differs from lane to lane: u8 [G][kLaneBytes]: exponents of alpha, (fcr + j) last_pw for j < 2 TMAX
 //                 (last_pw: the power of the lane's symbol SPL - 1), then j first_x for j <= TMAX (first_x: minus the power of its
 //                 symbol 0)
 constexpr int kLaneBytes = 28;
-constexpr int group_tmax(int two_t) { return two_t > 8 ? 8 : 4; }
-constexpr int chien_bytes(int spl) { return spl < 4 ? 4 : spl; }
+// The t a kernel is made for: terms beyond the code's own t are looked up all the same, which shows where a lane has few symbols.  2^20 words
+// of 17 symbols and t = 1, made for two / for four: 111 / 135 us; of 24 and t = 2 125 / 151.
+constexpr int group_tmax(int two_t) { return two_t > 8 ? 8 : two_t > 4 ? 4 : 2; }
+// Bytes of a table's entry.  A lane's only symbol needs no tables: its terms are its value times the lane's own powers, and a term of
+// the locator at its first position is all there is (2^20 words of RS(15,9) 135 us, 153 by way of the tables).
+constexpr int syn_bytes(int spl, int tmax) { return spl == 1 ? 0 : 2 * tmax; }
+constexpr int chien_bytes(int spl) { return spl == 1 ? 0 : spl < 4 ? 4 : spl; }
 constexpr int64_t kDecodeBlocks = 2048; // lane kernel: eight workgroups per compute unit; each reads the tables once and takes every 2048th run of words
 // Group kernel: three workgroups of eight wavefronts to a compute unit (up to 51 KiB of tables each), every 768th run of words.
 // 20000 words of RS(255,239) 20.7 us, with two workgroups of the same size 22.
@@ -308,8 +313,8 @@ __global__ __launch_bounds__(kGroupThreads, 6) void rs_decode_group_kernel(RsPar
     if (tid < 256) s_key[tid] = (with_key && tid < k) ? key.key[tid] : 0;
     __syncthreads();
     const Gf gf{s_tab, (const uint16_t *)(s_tab + kLogAt)};
-    constexpr int SB = 2 * TMAX, CB = chien_bytes(SPL); // bytes of an entry
-    const uint8_t *syn = s_tab + kCodeAt, *chien = syn + SPL * q * SB;
+    constexpr int SB = 2 * TMAX, CB = chien_bytes(SPL);
+    const uint8_t *syn = s_tab + kCodeAt, *chien = syn + SPL * q * syn_bytes(SPL, TMAX);
 
     // this lane's fixed exponents, a byte each: (fcr + j) last_pw, j first_x (1 / X of its symbol 0)
     const int lift = (p.fcr + two_t) % ord;                // X^(-fcr-2t) = x^(fcr+2t)
@@ -363,23 +368,31 @@ __global__ __launch_bounds__(kGroupThreads, 6) void rs_decode_group_kernel(RsPar
             for (int d = 0; d < NL; ++d) first_e[d] = mine[ND + d];
         }
         uint32_t Spk[ND];
+        if constexpr (SPL > 1) {
 #pragma unroll
-        for (int s = 0; s < SPL; ++s) {
-            Packed<SB> term;
-            term.load(syn + (s * q + byte_of(r, s)) * SB);
+            for (int s = 0; s < SPL; ++s) {
+                Packed<SB> term;
+                term.load(syn + (s * q + byte_of(r, s)) * SB);
 #pragma unroll
-            for (int d = 0; d < ND; ++d) Spk[d] = s == 0 ? term.d[d] : Spk[d] ^ term.d[d];
-            if (SB == 16 && s % 4 == 3) __builtin_amdgcn_sched_barrier(0); // four look-ups of 16 bytes at a time: registers
+                for (int d = 0; d < ND; ++d) Spk[d] = s == 0 ? term.d[d] : Spk[d] ^ term.d[d];
+                if (SB == 16 && s % 4 == 3) __builtin_amdgcn_sched_barrier(0); // four look-ups of 16 bytes at a time: registers
+            }
         }
+        const int log_r = SPL == 1 ? gf.L((int)r[0]) : 0; // a lane's only symbol: the same in all of its terms
 #pragma unroll
         for (int j0 = 0; j0 < SB; j0 += 8) { // eight at a time: registers
-            int v[8];
+            constexpr int W = SB < 8 ? SB : 8;
+            int v[W];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = gf.L(byte_of(Spk, j0 + j));
+            for (int j = 0; j < W; ++j) v[j] = SPL == 1 ? log_r : gf.L(byte_of(Spk, j0 + j));
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = gf.E(v[j] + byte_of(last_e, j0 + j));
+            for (int j = 0; j < W; ++j) v[j] = gf.E(v[j] + byte_of(last_e, j0 + j));
 #pragma unroll
-            for (int j = 0; j < 8; j += 4) Spk[(j0 + j) / 4] = (uint32_t)v[j] | (uint32_t)v[j + 1] << 8 | (uint32_t)v[j + 2] << 16 | (uint32_t)v[j + 3] << 24;
+            for (int j = 0; j < W; j += 4) {
+                const int d = (j0 + j) / 4, left = two_t - 4 * d; // of these four, the code has `left`
+                Spk[d] = (uint32_t)v[j] | (uint32_t)v[j + 1] << 8 | (uint32_t)v[j + 2] << 16 | (uint32_t)v[j + 3] << 24;
+                if (SPL == 1) Spk[d] &= left >= 4 ? 0xffffffffu : left <= 0 ? 0u : (1u << (8 * left)) - 1u;
+            }
             if (SB > 8) __builtin_amdgcn_sched_barrier(0);
         }
         uint32_t any = 0;
@@ -423,21 +436,28 @@ __global__ __launch_bounds__(kGroupThreads, 6) void rs_decode_group_kernel(RsPar
             }
 #pragma unroll
             for (int j = 0; j <= TMAX; ++j) lam[j] = gf.E(llam[j] + byte_of(first_e, j));
-            uint32_t sum[CB / 4];
-#pragma unroll
-            for (int d = 0; d < CB / 4; ++d) sum[d] = (uint32_t)lam[0] * 0x01010101u;
-#pragma unroll
-            for (int j = 1; j <= TMAX; ++j) {
-                Packed<CB> term;
-                term.load(chien + ((j - 1) * q + lam[j]) * CB);
-#pragma unroll
-                for (int d = 0; d < CB / 4; ++d) sum[d] ^= term.d[d];
-            }
             uint32_t roots = 0; // bit s: symbol l + s G is in error
+            if constexpr (SPL == 1) {
+                int sum = lam[0];
 #pragma unroll
-            for (int d = 0; d < CB / 4; ++d) {
-                const uint32_t some = ((sum[d] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | sum[d]; // bit 7 of a byte: it is not zero
-                roots |= (((~some >> 7) & 0x01010101u) * 0x01020408u >> 24) << (4 * d);
+                for (int j = 1; j <= TMAX; ++j) sum ^= lam[j];
+                roots = sum == 0;
+            } else {
+                uint32_t sum[CB / 4];
+#pragma unroll
+                for (int d = 0; d < CB / 4; ++d) sum[d] = (uint32_t)lam[0] * 0x01010101u;
+#pragma unroll
+                for (int j = 1; j <= TMAX; ++j) {
+                    Packed<CB> term;
+                    term.load(chien + ((j - 1) * q + lam[j]) * CB);
+#pragma unroll
+                    for (int d = 0; d < CB / 4; ++d) sum[d] ^= term.d[d];
+                }
+#pragma unroll
+                for (int d = 0; d < CB / 4; ++d) {
+                    const uint32_t some = ((sum[d] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | sum[d]; // bit 7 of a byte: it is not zero
+                    roots |= (((~some >> 7) & 0x01010101u) * 0x01020408u >> 24) << (4 * d);
+                }
             }
             const int slots = (n - l + G - 1) / G; // symbols this lane holds
             roots &= !fail && L > 0 ? (1u << max(slots, 0)) - 1u : 0u;
@@ -460,8 +480,8 @@ __global__ __launch_bounds__(kGroupThreads, 6) void rs_decode_group_kernel(RsPar
 #pragma unroll
                 for (int j = 0; j <= TMAX; ++j) {
                     if (j < TMAX) num ^= gf.E(lom[j] + e);
-                    if (j & 1) odd ^= gf.E(llam[j] + e);
-                    e = mod_once(e + x, ord);
+                    if (j & 1) odd ^= SPL == 1 ? lam[j] : gf.E(llam[j] + e);
+                    e = SPL == 1 && j < TMAX ? byte_of(first_e, j + 1) : mod_once(e + x, ord);
                 }
                 bad = bad || (has && (odd == 0 || num == 0));
                 const int quot = gf.E(gf.L(num) + (odd ? ord - gf.L(odd) : 0));
@@ -585,7 +605,7 @@ std::vector<uint8_t> rs_table_image(RsParams &p, const std::vector<uint8_t> &exp
         const int tmax = group_tmax(p.two_t), spl = group_symbols(p.n, G);
         for (int s = 0; s < spl; ++s)
             for (int v = 0; v < q; ++v)
-                for (int j = 0; j < 2 * tmax; ++j) img.push_back(j < p.two_t ? mul_pow(v, G * (spl - 1 - s) * (p.fcr + j)) : (uint8_t)0);
+                for (int j = 0; j < syn_bytes(spl, tmax); ++j) img.push_back(j < p.two_t ? mul_pow(v, G * (spl - 1 - s) * (p.fcr + j)) : (uint8_t)0);
         for (int j = 1; j <= tmax; ++j)
             for (int v = 0; v < q; ++v)
                 for (int s = 0; s < chien_bytes(spl); ++s) img.push_back(j <= p.two_t / 2 && s < spl ? mul_pow(v, G * j * s) : (uint8_t)0);
@@ -629,15 +649,19 @@ hipError_t launch_rs_decode(const RsParams &p, const uint8_t *sym, int64_t N, ui
         RsParams second = p;
         second.tab += p.tab_bytes;
         second.tab_bytes = p.tab2_bytes;
+        if (group_tmax(p.two_t) == 2) return launch_group<32, 2, 8>(second, sym, N, msg, cw, nerr, key, s);
         return launch_group<32, 4, 8>(second, sym, N, msg, cw, nerr, key, s);
     }
-    const bool half = group_lanes(p.two_t) == 16;
-    switch (group_symbols(p.n, half ? 16 : 32)) {
-    case 1: return half ? launch_group<16, 4, 1>(p, sym, N, msg, cw, nerr, key, s) : launch_group<32, 8, 1>(p, sym, N, msg, cw, nerr, key, s);
-    case 2: return half ? launch_group<16, 4, 2>(p, sym, N, msg, cw, nerr, key, s) : launch_group<32, 8, 2>(p, sym, N, msg, cw, nerr, key, s);
-    case 4: return half ? launch_group<16, 4, 4>(p, sym, N, msg, cw, nerr, key, s) : launch_group<32, 8, 4>(p, sym, N, msg, cw, nerr, key, s);
-    case 8: return half ? launch_group<16, 4, 8>(p, sym, N, msg, cw, nerr, key, s) : launch_group<32, 8, 8>(p, sym, N, msg, cw, nerr, key, s);
-    default: return launch_group<16, 4, 16>(p, sym, N, msg, cw, nerr, key, s);
+    const int tmax = group_tmax(p.two_t);
+    switch (group_symbols(p.n, group_lanes(p.two_t))) {
+    case 1: return tmax == 8 ? launch_group<32, 8, 1>(p, sym, N, msg, cw, nerr, key, s) : launch_group<16, 4, 1>(p, sym, N, msg, cw, nerr, key, s);
+    case 2: return tmax == 8 ? launch_group<32, 8, 2>(p, sym, N, msg, cw, nerr, key, s)
+                 : tmax == 4 ? launch_group<16, 4, 2>(p, sym, N, msg, cw, nerr, key, s) : launch_group<16, 2, 2>(p, sym, N, msg, cw, nerr, key, s);
+    case 4: return tmax == 8 ? launch_group<32, 8, 4>(p, sym, N, msg, cw, nerr, key, s)
+                 : tmax == 4 ? launch_group<16, 4, 4>(p, sym, N, msg, cw, nerr, key, s) : launch_group<16, 2, 4>(p, sym, N, msg, cw, nerr, key, s);
+    case 8: return tmax == 8 ? launch_group<32, 8, 8>(p, sym, N, msg, cw, nerr, key, s)
+                 : tmax == 4 ? launch_group<16, 4, 8>(p, sym, N, msg, cw, nerr, key, s) : launch_group<16, 2, 8>(p, sym, N, msg, cw, nerr, key, s);
+    default: return tmax == 4 ? launch_group<16, 4, 16>(p, sym, N, msg, cw, nerr, key, s) : launch_group<16, 2, 16>(p, sym, N, msg, cw, nerr, key, s);
     }
 }
 

@@ -111,11 +111,14 @@ def test_rs_decode_runs_shared_out_evenly(qrm, m, n, t, per):
     ctx.close()
 
 
-@pytest.mark.parametrize("m,n,t,fcr", [(8, 255, 8, 0), (8, 255, 5, 254), (8, 255, 3, 7), (7, 127, 8, 100), (6, 63, 1, 1)])
+@pytest.mark.parametrize("m,n,t,fcr", [(8, 255, 8, 0), (8, 255, 5, 254), (8, 255, 3, 7), (7, 127, 8, 100), (6, 63, 1, 1),
+                                       # one symbol per lane; t <= 2 at every number of symbols per lane
+                                       (8, 16, 3, 1), (4, 15, 4, 2), (8, 32, 8, 254), (5, 31, 5, 0), (8, 17, 1, 0), (8, 32, 2, 3),
+                                       (8, 33, 1, 254), (8, 128, 2, 9), (8, 129, 2, 1), (8, 255, 1, 7)])
 def test_rs_decode_an_error_at_every_position(qrm, m, n, t, fcr):
     """One error at every position and t errors from every position on (every exponent of the locators and error values), in
     launches around the word count from which a workgroup takes a second run of words."""
-    code = dict(m=m, prim_poly={6: 0x43, 7: 0x89, 8: 0x11D}[m], n=n, k=n - 2 * t, fcr=fcr)
+    code = dict(m=m, prim_poly={4: 0x13, 5: 0x25, 6: 0x43, 7: 0x89, 8: 0x11D}[m], n=n, k=n - 2 * t, fcr=fcr)
     lanes = 32 if t > 4 else 16
     full = 768 * (512 // lanes)
     g = np.random.default_rng([n, t, fcr])
