@@ -327,7 +327,8 @@ struct StripWalk {
     }
 };
 
-template <int VEC, bool WORDS>
+// LOAD: bytes that a load of a row's taps takes: 8, 4 (a load for either tap) or 1 (rows of one pixel)
+template <int VEC, int LOAD>
 __global__ __launch_bounds__(256) void preprocess_kernel(const uint8_t *__restrict__ raw, PreArgs a,
                                                          const int32_t *__restrict__ off, uint8_t *__restrict__ out)
 {
@@ -347,11 +348,12 @@ __global__ __launch_bounds__(256) void preprocess_kernel(const uint8_t *__restri
         int i0, i1, w1;
         source_taps(a.cx + ox + t, a.W_in, a.Wr, i0, i1, w1);
         // The six bytes of both taps come with ONE (unaligned) load of eight, from the left tap's first byte on or, at the row's
-        // end, its last eight: always inside the row (rows have at least three pixels on this path).  The byte
-        // selector carries where the taps lie in them.
-        const int at = WORDS ? min(3 * i0, 3 * a.W_in - 8) : 3 * i0;
+        // end, its last eight: always inside the row.  The byte selector carries where the taps lie in them.  Short rows: a load
+        // of four bytes for either tap, the row's last four at its end (preprocess_load).
+        const int at = LOAD > 1 ? min(3 * i0, 3 * a.W_in - LOAD) : 3 * i0;
+        const int right = LOAD == 4 ? 4 + 3 * i1 - min(at + 3, 3 * a.W_in - 4) : LOAD == 8 ? 3 * i1 - at : 3;
         s_x[t] = at;
-        s_sel[t] = kSelect + (WORDS ? (uint32_t)(3 * i0 - at) | (uint32_t)(3 * i1 - at) << 16 : 3u << 16);
+        s_sel[t] = kSelect + ((uint32_t)(3 * i0 - at) | (uint32_t)right << 16);
         s_wx[t] = (uint32_t)((1 << kCoefBits) - w1) | (uint32_t)w1 << 16;
     }
     for (int t = tid; t < r_end - r_begin; t += 256) {
@@ -375,9 +377,15 @@ __global__ __launch_bounds__(256) void preprocess_kernel(const uint8_t *__restri
             const int at = s_x[tx + v];
             const uint32_t wx = s_wx[tx + v], sel = s_sel[tx + v];
             uint32_t p[2][2]; // [row]: the three colours of the left tap, then of the right one, somewhere in eight bytes
-            if (WORDS) {
+            if (LOAD == 8) {
                 __builtin_memcpy(p[0], row0 + at, 8);
                 __builtin_memcpy(p[1], row1 + at, 8);
+            } else if (LOAD == 4) {
+                const int b1 = min(at + 3, 3 * a.W_in - 4);
+                __builtin_memcpy(&p[0][0], row0 + at, 4);
+                __builtin_memcpy(&p[0][1], row0 + b1, 4);
+                __builtin_memcpy(&p[1][0], row1 + at, 4);
+                __builtin_memcpy(&p[1][1], row1 + b1, 4);
             } else {
                 const int b1 = min(at + 3, 3 * a.W_in - 3);
                 p[0][0] = row0[at] | row0[at + 1] << 8 | row0[at + 2] << 16 | (uint32_t)row0[b1] << 24;
@@ -436,6 +444,10 @@ int preprocess_strips(int64_t N, int T, bool vec)
     return (T + rows - 1) / rows;
 }
 
+// Bytes per load of the taps.  Rows of two pixels have no room for eight, rows of one none for four.  1000 images to 256 x 256, four /
+// eight bytes: images of 2 x 3 112 / 123 us, 3 x 4 104 / 90; of 2 x 2, one byte / four: 125 / 84.
+static int preprocess_load(int W_in) { return W_in >= 4 ? 8 : W_in >= 2 ? 4 : 1; }
+
 hipError_t launch_preprocess(const uint8_t *raw, int64_t N, int H_in, int W_in, int x, const int32_t *off, int T,
                              uint8_t *out, hipStream_t s)
 {
@@ -456,11 +468,11 @@ hipError_t launch_preprocess(const uint8_t *raw, int64_t N, int H_in, int W_in, 
         const int32_t *off0 = off ? off + 2 * n0 : nullptr;
         uint8_t *out0 = out + n0 * 3 * (int64_t)T * T;
         const dim3 grid((unsigned)(cnt * strips));
-        const bool words = W_in >= 3; // shorter rows have no room for eight bytes
-        if (vec && words) hipLaunchKernelGGL((preprocess_kernel<4, true>), grid, dim3(256), 0, s, raw0, a, off0, out0);
-        else if (vec) hipLaunchKernelGGL((preprocess_kernel<4, false>), grid, dim3(256), 0, s, raw0, a, off0, out0);
-        else if (words) hipLaunchKernelGGL((preprocess_kernel<1, true>), grid, dim3(256), 0, s, raw0, a, off0, out0);
-        else hipLaunchKernelGGL((preprocess_kernel<1, false>), grid, dim3(256), 0, s, raw0, a, off0, out0);
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, raw0, a, off0, out0); };
+        const int load = preprocess_load(W_in);
+        if (load == 8) launch(vec ? preprocess_kernel<4, 8> : preprocess_kernel<1, 8>);
+        else if (load == 4) launch(vec ? preprocess_kernel<4, 4> : preprocess_kernel<1, 4>);
+        else launch(vec ? preprocess_kernel<4, 1> : preprocess_kernel<1, 1>);
     }
     return hipGetLastError();
 }
