@@ -114,11 +114,9 @@ __global__ __launch_bounds__(kGatherThreads) void gather_host_tiles_kernel(const
 // forms the exact integers n S2 - S1^2, and the score in float64 in a fixed order with no fused
 // multiply-add; a workgroup reduction picks the first maximum.
 // A launch of fewer images than compute units waits for the round trips of its only wave of workgroups: 1024 threads an image
-// instead of 256 (one image of 224 x 224, windows of 96 at strides of 32: 10.6 -> 7.7 us a call, 256 of them 17.1 -> 11.0; 64 of
-// 384 x 384, 64 at 16: 26.4 -> 22.7; 256 of 250 x 250, byte by byte: 54.3 -> 19.4).
+// instead of 256 where that is the faster way (select_threads).
 // ------------------------------------------------------------------------------------------------
 constexpr int kMaxCells = 1024; // cells per channel a workgroup can hold
-constexpr int kFewImages = 256;  // a workgroup of 1024 threads for each at most
 
 struct SelectArgs {
     int H, W, win, stride;
@@ -484,6 +482,19 @@ bool select_tiles_supported(int H, int W, int win, int stride)
     return (int64_t)(nH - 1 + k) * (nW - 1 + k) <= kMaxCells;
 }
 
+// Threads an image.  256 / 1024 threads, us: byte by byte 256 images of 250 x 250 66 / 19, 256 of 500 x 500 242 / 41.  16 bytes at a time:
+// one image of 320 x 320 14.3 / 9.8, 32 of 512 x 512 13.2 / 10.7, 256 of 224 x 224 16.8 / 9.2, 256 of 384 x 384 31.6 / 26.0, of 416 x
+// 416 34.4 / 28.1.  Images that are larger, or wide, and more than the L2s hold fill the memory's queues with 256 threads: 200 of
+// 512 x 512 27.2 / 29.8, 64 of 480 x 640 33.8 / 38.8, 64 of 768 x 768 61.3 / 71.2, 200 of 288 x 512 18.9 / 22.4.  (Within the L2s, of
+// 28 sizes one loses by 1024 threads: 720 x 1280, 37.0 / 39.2.)
+static int select_threads(int64_t N, int H, int W, bool wide)
+{
+    if (N > 256) return 256;
+    if (!wide) return 1024;
+    const bool small = W <= 416 && (int64_t)H * W <= 416 * 416, cached = 3 * N * H * W <= 24 << 20;
+    return small || cached ? 1024 : 256;
+}
+
 hipError_t launch_select_tiles_variance(const uint8_t *img, int64_t N, int H, int W, int win, int stride,
                                         const double w[3], int32_t *off_yx, double *scores, hipStream_t s)
 {
@@ -504,10 +515,8 @@ hipError_t launch_select_tiles_variance(const uint8_t *img, int64_t N, int H, in
         const uint8_t *img0 = img + n0 * 3 * (int64_t)H * W;
         double *sc0 = scores ? scores + n0 * (int64_t)(a.nH * a.nW) : nullptr;
         auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)cnt), dim3(threads), 0, s, img0, a, off_yx + 2 * n0, sc0); };
-        if (wide && N <= kFewImages) launch(tile_variance_kernel<16, 1024>, 1024);
-        else if (wide) launch(tile_variance_kernel<16, 256>, 256);
-        else if (N <= kFewImages) launch(tile_variance_kernel<1, 1024>, 1024);
-        else launch(tile_variance_kernel<1, 256>, 256);
+        if (select_threads(N, H, W, wide) == 1024) launch(wide ? tile_variance_kernel<16, 1024> : tile_variance_kernel<1, 1024>, 1024);
+        else launch(wide ? tile_variance_kernel<16, 256> : tile_variance_kernel<1, 256>, 256);
     }
     return hipGetLastError();
 }

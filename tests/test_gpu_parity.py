@@ -1268,6 +1268,9 @@ SELECT_CASES = [  # N, H, W, tile, stride
     (3, 64, 128, 64, 64),        # stride = tile: two windows side by side
     (6, 40, 40, 40, 40),         # a single window
     (2, 256, 256, 32, 8),        # 29 x 29 windows, 32 x 32 cells
+    (257, 64, 96, 32, 16),       # more images than get a large workgroup each, 16 bytes and one byte at a time
+    (257, 50, 41, 10, 5),
+    (43, 448, 448, 64, 32),      # few images, but large ones: 256 threads each
 ]
 
 
