@@ -2265,6 +2265,7 @@ bool conv_pair_supported(int C, const ConvGeom &g) { return C == 64 && g.colblks
 // pairs gets shorter for it, in launches whose chunks do not reach every compute unit, as long as an image's lines fit the place of
 // its activations (64 channels, two bytes a pixel): on tiles of up to four columns they do not, and with a block of their own for
 // them a batch of 24 tiles of 64 x 4 took a workspace half as large again as one of 25.
+// Such a launch deals in runs: whole images cost the same in pieces of one row pair and of kChunk, and no split costs more.
 static bool fine_lines(const ConvGeom &g, int num_cu)
 {
     const int pairs = (g.h + 1) / 2, chunks = (pairs + kChunk - 1) / kChunk;
@@ -2382,6 +2383,7 @@ hipError_t launch_conv_pair(const uint8_t *in, const TileSrc *first, const ConvG
     const PairSplit split = conv_pair_split(g, last && !fine, num_cu);
     const dim3 grid((unsigned)split.workgroups);
     if ((int)grid.x > num_cu) return hipErrorInvalidValue; // the seam buffer holds num_cu workgroups
+    if (fine && !split.part) return hipErrorInvalidValue;
     const size_t half = (size_t)(2 * ((g.h + 1) / 2)) * kSeamRowBytes;
     uint8_t *seam_last = seam_column ? seam + 2 * (size_t)num_cu * half : nullptr;
     const int out_recs = last ? sums.lines : conv_pair_samples(g).recs;
@@ -2391,8 +2393,13 @@ hipError_t launch_conv_pair(const uint8_t *in, const TileSrc *first, const ConvG
         constexpr bool PART = decltype(part)::value;
         auto of = [&](auto is_first) {
             constexpr bool FIRST = decltype(is_first)::value;
-            if (fine) launch_pair_variant<FIRST, true, PART, 1>(wide, grid, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
-            else if (last) launch_pair_variant<FIRST, true, PART, kChunk>(wide, grid, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+            if constexpr (PART) { // (whole images never leave a line per row pair: fine_lines)
+                if (fine) {
+                    launch_pair_variant<FIRST, true, PART, 1>(wide, grid, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
+                    return;
+                }
+            }
+            if (last) launch_pair_variant<FIRST, true, PART, kChunk>(wide, grid, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
             else launch_pair_variant<FIRST, false, PART, 1>(wide, grid, s, in, src, g, wfrag_a, wfrag_b, bias_a, bias_b, st, out);
         };
         if (first) of(std::true_type{});

@@ -131,3 +131,14 @@ def test_a_smaller_batch_needs_no_larger_workspace(h, w):
     without a new workspace."""
     sizes = [last_lines(n, h, w)[1] for n in range(1, 300)]
     assert all(a <= b for a, b in zip(sizes, sizes[1:])), (h, w)
+
+
+def test_a_line_per_row_pair_means_runs(split):
+    """Launches that leave a line per row pair deal their row pairs in runs: there is no kernel for whole images with such lines."""
+    fine = 0
+    for h in range(1, 200):
+        for n in range(1, 256):
+            if n * -(-((h + 1) // 2) // 4) < CU and last_lines(n, h, 64)[0] == 1:
+                fine += 1
+                assert split(n, h, 64, 0)[0] == 1, (n, h)
+    assert fine > 1000
