@@ -95,11 +95,11 @@ def test_rs_decode_small_batches(qrm, N):
     ctx.close()
 
 
-@pytest.mark.parametrize("m,n,t,per", [(8, 100, 8, 8), (5, 31, 3, 16)])
+@pytest.mark.parametrize("m,n,t,per", [(8, 100, 8, 16), (5, 31, 3, 32)])
 def test_rs_decode_runs_shared_out_evenly(qrm, m, n, t, per):
     """Word counts around those at which the workgroups of a long code take one, two and three runs of `per` words each."""
     code = dict(m=m, prim_poly={5: 0x25, 8: 0x11D}[m], n=n, k=n - 2 * t, fcr=1)
-    full = 1280 * per
+    full = 768 * per
     count = 2 * full + 1
     msgs, err, _ = synth.rs_cases(90 + n, count, n, n - 2 * t, m, max_err=t + 1)
     words = oracle.rs_encode(msgs, **code) ^ err
@@ -334,17 +334,26 @@ def test_results_do_not_depend_on_the_batch_around_a_tile(qrm, C, nb, h, w, flag
         check_logits(lg[None], ref, what=f"C={C} {h}x{w} flags {flags}")
 
 
-@pytest.mark.parametrize("nb,h,w", [(4, 64, 64), (4, 37, 50), (2, 21, 33), (4, 9, 64), (4, 2, 17)])
+@pytest.mark.parametrize("nb,h,w", [(4, 64, 64), (4, 37, 50), (2, 21, 33), (4, 9, 64), (2, 33, 33)])
 def test_last_pair_lines_of_one_row_pair_and_of_four(qrm, nb, h, w):
     """Launches of few tiles leave a line of sums per row pair, others one per four: the same logits for the same tile, bit for
-    bit, on both sides of where the number of tiles changes that."""
-    border = -(-256 // -(-((h + 1) // 2) // 4))          # tiles whose groups of four row pairs reach every compute unit
+    bit, on both sides of where the number of tiles changes that, and below it in runs of one row pair and of more, across images."""
+    def row_pairs(n):
+        pairs, size = C.c_int32(), C.c_int64()
+        assert qrm.load_library().qrm_diag_last_lines(n, h, w, nb, CU, C.byref(pairs), C.byref(size)) == 0
+        return pairs.value
+
+    CU = torch.cuda.get_device_properties(0).multi_processor_count
+    last = max(n for n in range(1, CU) if row_pairs(n) == 1)
+    counts = (last + 1, last, 2 * last // 3, 5, 2, 1)
+    assert [row_pairs(n) for n in counts] == [4, 1, 1, 1, 1, 1]
+    assert last * ((h + 1) // 2) > CU                    # runs of several row pairs that begin in one image and end in the next
     wts = small_weights(64, nb, 16, nb + h)
-    tiles = np.random.default_rng(h * w).integers(0, 256, size=(border + 1, 3, h, w), dtype=np.uint8)
+    tiles = np.random.default_rng(h * w).integers(0, 256, size=(last + 1, 3, h, w), dtype=np.uint8)
     ctx = qrm.Context(weights=wts)
     ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_POISON_WORKSPACE)
     got = []
-    for N in (border + 1, border, border - 1, 5, 2, 1):
+    for N in counts:
         d_tiles, d_log = dev(tiles[:N]), empty((N, 16), torch.float32)
         ctx.qrm_extractor_forward(d_tiles, N, h, w, d_log, None)
         torch.cuda.synchronize()
