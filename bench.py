@@ -17,8 +17,10 @@ from __future__ import annotations
 
 import argparse
 import ctypes
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -31,29 +33,30 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, published
 
 # HBM bytes per launch of a configuration's dominant kernel.  These are RECORDED figures, not measured by this
 # script: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this same command, scaled by a copy kernel of known
-# size (the summaries under profiles/ give the commands), at the commit named.  A record applies only while the
-# kernel, the micro-batch and the image count it was taken on are unchanged; otherwise the line reports null.
+# size (the summary under profiles/ gives the commands), at the commit named.  A record applies only while the
+# kernel's source and the images per launch it was taken on are unchanged; otherwise the line reports null.
 RECORDED_TRAFFIC = {
-    # (configuration, launch kind): bytes per launch, where it was measured
-    ("C2", "pair_mid"): {"bytes": 1079908378, "commit": "bf5163f", "images_per_launch": 1024,
-                         "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C2", "pair_last"): {"bytes": 551404595, "commit": "bf5163f", "images_per_launch": 1024,
-                         "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C2", "pair_first"): {"bytes": 573236339, "commit": "bf5163f", "images_per_launch": 1024,
-                         "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C3", "pair_mid"): {"bytes": 4472813544, "commit": "bf5163f", "images_per_launch": 256,
-                         "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C3", "pair_last"): {"bytes": 2345266451, "commit": "bf5163f", "images_per_launch": 256,
-                         "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C3", "pair_first"): {"bytes": 2416851750, "commit": "bf5163f", "images_per_launch": 256,
-                         "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C4", "pair_mid"): {"bytes": 1108868512, "commit": "bf5163f", "images_per_launch": 256,
-                         "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C4", "pair_last"): {"bytes": 579987572, "commit": "bf5163f", "images_per_launch": 256,
-                         "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
-    ("C4", "pair_first"): {"bytes": 598561627, "commit": "bf5163f", "images_per_launch": 256,
-                         "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt"},
+    "commit": "bf5163f", "kernels": "6c7c9e135cec", "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt",
+    # (configuration, launch kind): (images per launch, bytes per launch)
+    ("C2", "pair_first"): (1024, 573236339), ("C2", "pair_mid"): (1024, 1079908378), ("C2", "pair_last"): (1024, 551404595),
+    ("C3", "pair_first"): (256, 2416851750), ("C3", "pair_mid"): (256, 4472813544), ("C3", "pair_last"): (256, 2345266451),
+    ("C4", "pair_first"): (256, 598561627), ("C4", "pair_mid"): (256, 1108868512), ("C4", "pair_last"): (256, 579987572),
 }
+
+
+def kernel_source_key(texts=None) -> str:
+    """What the convolution kernels are compiled from, comments and blanks left out, as twelve hexadecimal digits."""
+    if texts is None:
+        csrc = os.path.join(ROOT, "paper_2509_02447_amd", "csrc")
+        texts = [open(os.path.join(csrc, f)).read() for f in ("extractor.hip", "qrm_internal.h")]
+    return hashlib.sha256("".join(re.sub(r"//[^\n]*|\s+", "", t) for t in texts).encode()).hexdigest()[:12]
+
+
+def recorded_traffic(config, kind, images_per_launch, kernels):
+    """Recorded bytes per launch, or None where the record is of other kernels or of launches of another size."""
+    images, nbytes = RECORDED_TRAFFIC.get((config, kind), (None, None))
+    return nbytes if images == images_per_launch and kernels == RECORDED_TRAFFIC["kernels"] else None
+
 
 HOST_THREADS = min(16, os.cpu_count() or 1)
 
@@ -241,18 +244,17 @@ def bench_resident(env, name: str, steps: int, warmup: int, cpu_sample: int, sta
         "block_mid": "conv_mid_kernel (3x3 conv C->C, bf16 MFMA implicit GEMM)",
         "block_last": "conv_mid_kernel, last block (channel sums only)",
     }
-    rec = RECORDED_TRAFFIC.get((name, dom))
     # a record applies to launches of the size it was taken on (the FLOPs of a launch say how many images it held)
     flops_per_image_and_launch = {"pair_first": 2 * 9 * (3 + cfg.channels) * cfg.channels, "pair_mid": 2 * 2 * 9 * cfg.channels ** 2,
                                   "pair_last": 2 * 2 * 9 * cfg.channels ** 2}.get(dom, 0) * cfg.tile * cfg.tile
     images_per_launch = round(kinds[dom]["flops_per_launch"] / flops_per_image_and_launch) if flops_per_image_and_launch else 0
-    use_rec = bool(rec) and rec["images_per_launch"] == images_per_launch
+    traffic = recorded_traffic(name, dom, images_per_launch, kernel_source_key())
     roofline = {"kernel": kernel_names.get(dom, dom), "bound": "mfma",
                 "achieved": conv[dom]["tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": conv[dom]["frac_of_bf16_peak"],
-                "traffic": rec["bytes"] if use_rec else None,
+                "traffic": traffic,
                 "traffic_note": (f"recorded, not measured in this run: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE at commit "
-                                 f"{rec['commit']} ({rec['source']})") if use_rec else
+                                 f"{RECORDED_TRAFFIC['commit']} ({RECORDED_TRAFFIC['source']})") if traffic is not None else
                                 "no counter run is recorded for this kernel and launch size",
                 "launches_per_step": kinds[dom]["launches_per_step"], "avg_launch_us": kinds[dom]["avg_launch_us"],
                 "flops_per_launch": kinds[dom]["flops_per_launch"], "images_per_launch": images_per_launch,
