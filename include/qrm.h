@@ -335,6 +335,9 @@ QRM_API qrm_status qrm_detect_host(qrm_ctx *ctx, const uint8_t *const *h_chunks,
  * duration in milliseconds, the number of launches and their algorithmic FLOPs (2*9*C_in*C_out*h*w per image
  * and convolution block; 0 for the kinds that are not convolutions); it does not clear.  Any output pointer
  * may be NULL.  Errors: QRM_E_INVALID for a kind outside 0..QRM_PROFILE_KINDS-1.
+ * One launch differs from those of a call that is not timed: qrm_detect / qrm_detect_verify on up to 2048 images with a code
+ * of up to 16 symbols and n - k <= 4 otherwise decode the words in the launch filed under HEAD.  While they are timed, RS_DECODE
+ * is a launch of its own, about 4 us longer than what it adds to HEAD otherwise; the results are the same.
  */
 enum {
     QRM_PROFILE_PAIR_FIRST = 0,  /* fused launch: the network's first block + the C -> C block after it */

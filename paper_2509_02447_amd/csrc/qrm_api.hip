@@ -1029,8 +1029,8 @@ static qrm_status detect_common(qrm_ctx *c, const uint8_t *d_images, int64_t N, 
                 {c->inv_std[0], c->inv_std[1], c->inv_std[2]}};
     KeyArgs key{};
     if (verify) key = KeyArgs{(const uint8_t *)c->d_tables, c->key_tau, d_matches, d_detected};
-    // (while the two are timed apart, they are two launches)
-    const bool in_head = c->collapse && head_decodes(c->rs, N) && !c->profile;
+    // (while the two are timed apart, they are two launches; qrm_detect_host's time line is about the launches it always makes)
+    const bool in_head = c->collapse && head_decodes(c->rs, N) && (!c->profile || c->in_host_pipeline);
     const WordArgs word = in_head ? WordArgs{c->rs, d_msg, d_codeword, d_nerr, key} : WordArgs{};
     st = run_extractor(c, (uint8_t *)slot->ws, L, src, N, tile, tile, -1, d_logits, d_bits, in_head ? nullptr : d_sym, c->rs.m, word,
                        nullptr, true, s);

@@ -401,6 +401,25 @@ def test_words_decoded_by_the_head_and_by_a_launch_of_their_own(qrm, C, m, poly,
     ctx.close()
 
 
+def test_timed_small_batches_decode_in_a_launch_of_their_own(qrm):
+    """While launches are timed the words of a small batch have a launch of their own, filed under RS_DECODE: the same results."""
+    ctx = qrm.Context(weights=small_weights(32, 2, 60, 3), rs=dict(m=4, prim_poly=0x13, n=15, k=11, fcr=1))
+    d_imgs = dev(np.random.default_rng(4).integers(0, 256, size=(5, 3, 16, 16), dtype=np.uint8))
+    got = []
+    for on in (False, True, False):
+        ctx.qrm_profile_enable(on)
+        d_log, d_msg, d_ne = empty((5, 60), torch.float32), empty((5, 11), torch.uint8), empty((5,), torch.int8)
+        d_cw = empty((5, 15), torch.uint8)
+        ctx.qrm_detect(d_imgs, 5, 16, 16, None, 16, d_log, None, d_msg, d_cw, d_ne)
+        torch.cuda.synchronize()
+        launches = [ctx.qrm_profile_read(k)[1] for k in (qrm.binding.QRM_PROFILE_HEAD, qrm.binding.QRM_PROFILE_RS_DECODE)]
+        assert launches == ([1, 1] if on else [0, 0])
+        got.append([t.cpu().numpy() for t in (d_log, d_msg, d_cw, d_ne)])
+    for other in got[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(got[0], other))
+    ctx.close()
+
+
 # (channels, blocks, height, width, flags, final ReLU): the last block or the final convolution alone in its launch
 # (single-block schedule), on tiles of a strip or less, ragged in both directions, of several column blocks
 SPLIT_CASES = [(32, 2, 3, 5, 0, 0), (32, 3, 13, 64, 0, 0), (32, 4, 46, 100, 0, 0), (64, 3, 14, 33, 1, 0), (64, 4, 37, 130, 1, 0),
