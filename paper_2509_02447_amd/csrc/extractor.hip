@@ -288,8 +288,7 @@ __device__ __forceinline__ void frag_wait(bf16x8 &frag)
 // their waits are written as assembly: the compiler, not knowing which direct-to-LDS load fills which
 // bytes, would otherwise drain the whole vector-memory queue (stores included) before the first read.
 // `rowp` holds the LDS byte address of each staged row for this lane.
-// The accumulators are not read; the first matrix instruction of every output row starts from `first`.
-// `first` (zero, or the bias) starts the sums.
+// The accumulators are not read; the first matrix instruction of every output row starts from `first`: zero, or the bias.
 // rows_read() is called when the wavefront has read all it needs of the rows, with the last few matrix instructions still to
 // be issued: a step's barrier put there lets the others go on meanwhile.
 // The code begins on a boundary of 32 bytes: where its eight-byte instructions happened to straddle those of the instruction
@@ -1004,9 +1003,11 @@ __global__ __launch_bounds__(256, 2) void conv_final32_kernel(const uint8_t *__r
 //         instructions then run), then output rows 2j, 2j+1, j = s-2, from intermediate rows 2j-1 .. 2j+2
 //   end : one workgroup barrier
 // The sums start from bias (+ correction), which either group keeps in 16 registers: a third of an epilogue's vector
-// instructions and all of its LDS reads were the bias.  The groups have loops of their own: 219 registers instead of 243 and no
-// scalar ones spilled, which is where the bias found room.  A step of a middle pair takes 5200 cycles, 4608 of them matrix
-// instructions; what bounds a launch of bulk size is the clock that its power leaves (1.7 GHz of 2.4).
+// instructions and all of its LDS reads were the bias.  The groups have loops of their own: 225 .. 241 registers instead of the
+// 239 .. 256 of one loop for both, which is where the bias found room, and scalar ones (up to 24) are no longer spilled, but for six
+// where a pair is first, last, wide and dealt in runs.  A step of a middle pair of 1024 tiles of 64 x 64 takes 5190 cycles
+// (SQ_BUSY_CU_CYCLES), 4608 of them matrix instructions; what bounds a launch of bulk size is the clock that its power
+// leaves (1.6 GHz of 2.4).
 // (All loads are group A's: the vector-memory instructions of a compute unit issue in order, and loads issued
 // by group B at the end of a step would sit in front of its own stores at the start of the next.)
 // Row y of either map lives in ring slot (y + 2) mod 8.
@@ -1232,7 +1233,7 @@ __global__ __launch_bounds__(512, 1) void conv_pair_kernel(const uint8_t *__rest
     n_pos += J * (closing(0) - opening(0) + 1);
     if (n_cnt > 1) n_pos += J * (closing(n_cnt - 1) + 2);
     // The two groups have loops of their own, and each keeps the positions it needs, no others: the loops are short of scalar
-    // registers (six positions in every wavefront of one loop spilled 16 to 35 of them and cost 1 .. 5 % of a launch).
+    // registers (with six positions in every wavefront of one loop for both, up to 24 of them were spilled).
     Pos pw{0, 0, max(ja - 1, 0)}; // group A: position sg; group B: position sg - 2
     Pos p1 = pw;                  // FIRST: group A's pixel loads, position sg + 1; group B's seam loads, position sg
     if (!FIRST || grp == 0) advance(p1);
@@ -1890,7 +1891,7 @@ __device__ __forceinline__ f32x4 sum_lines(const f32x4 *p, int stride, int start
     return sum;
 }
 
-// The same over lines r that are `sums.sub` (kChunk) lines each, one per row pair (of sums.pairs): what the kernel
+// The same over lines r that are kChunk lines each, one per row pair (of `pairs`): what the kernel
 // would have added up before it wrote them, in its order.  width: lines of one row pair.
 __device__ __forceinline__ f32x4 sum_line_groups(const f32x4 *p, int stride, int start, int step, int count, int width, int pairs)
 {
@@ -2317,11 +2318,11 @@ static int pair_cost(const ConvGeom &g, int quant, int per)
 // Whole images per workgroup, or every compute unit one run of the launch's row pairs.  A run that begins and ends inside
 // images has up to two halo pairs and an opening position more than its row pairs, and its code has more scalar
 // instructions a step: runs where the longest workgroup gets shorter by more than 3 %.  Short launches are bound by the
-// steps' latency, which is why a step counts for more than the matrix work in it (fitted to 47 shapes from 40 x 5 x 64 to
-// 450 x 24 x 200, of which the rule picks the slower way by 1.5 % at most).  Eight blocks, whole images / runs, cost of a
-// middle pair: 192 tiles of 8 x 64 89 / 94 us (64 / 80), 224 of 16 x 64 132 / 141 (104 / 120), 245 of 64 x 64 425 / 439 (344 / 360), 480
-// of 64 x 64 830 / 842 (672 / 658), 240 of 128 x 128 1712 / 1741 (1312 / 1284); 40 of 5 x 64 70 / 62 (54 / 52), 160 of 16 x 64 126 / 122
-// (104 / 100), 333 of 16 x 64 209 / 190 (192 / 168), 300 of 64 x 64 651 / 535 (672 / 438), 200 of 128 x 128 1528 / 1459 (1312 / 1084).
+// steps' latency, which is why a step counts for more than the matrix work in it (of 101 shapes from 40 x 5 x 64 to
+// 1053 x 46 x 48, up to 200 columns, the rule picks the slower way by 1.7 % at most).  Eight blocks, whole images / runs, cost of a
+// middle pair: 192 tiles of 8 x 64 80 / 85 us (64 / 80), 224 of 16 x 64 123 / 129 (104 / 120), 245 of 64 x 64 411 / 424 (344 / 360), 480
+// of 64 x 64 807 / 809 (672 / 658), 240 of 128 x 128 1647 / 1655 (1312 / 1284); 40 of 5 x 64 58 / 51 (54 / 52), 160 of 16 x 64 113 / 110
+// (104 / 100), 333 of 16 x 64 191 / 177 (192 / 168), 300 of 64 x 64 634 / 502 (672 / 438), 200 of 128 x 128 1523 / 1413 (1312 / 1084).
 PairSplit conv_pair_split(const ConvGeom &g, bool last, int num_cu)
 {
     const int quant = last ? kChunk : 1;
@@ -2341,9 +2342,11 @@ PairSplit conv_pair_split(const ConvGeom &g, bool last, int num_cu)
 // evenly, its workgroups pay for each strip, for the extra rows a column of strips begins with, and for the activations of
 // every block; fused: a run's halo and opening positions (pair_cost), a launch for the last column of widths that are multiples
 // of 64, half the activations.  Fitted to 231 shapes of 128 .. 700 tiles, 4 .. 44 rows, 66 .. 256 columns with fewer than 12 row
-// pairs per compute unit (standard deviation 3.5 and 2.6 %): the faster way by the estimates is 4 % slower than the other at
-// most.  Measured, single / fused: 256 tiles of 8 x 100 191 / 144 us, 256 of 20 x 200 621 / 540, 200 of 30 x 200 741 / 681;
-// 128 of 24 x 66 203 / 216, 160 of 20 x 128 254 / 265.
+// pairs per compute unit, as the kernels were at commit eefb1c9 (standard deviation 3.5 and 2.6 %).  The present kernels take 5 %
+// (single blocks) and 7 % (fused) less than that, standard deviation 4 and 6: on 215 such shapes the way taken is the faster one or within 3 %
+// of it on 203, at worst 7.5 % slower, and then mostly single blocks, which are also the more exact (wide_tiles_fused): the line stays.
+// Measured, single / fused: 256 tiles of 8 x 100 186 / 138 us, 256 of 20 x 200 584 / 528, 200 of 30 x 200 705 / 661, 128 of 24 x 66 196 /
+// 194; 292 of 5 x 73, single blocks by the rule, 173 / 161; 181 of 27 x 152, fused by the rule, 433 / 454.
 WideCost conv_wide_cost(const ConvGeom &g, int num_cu)
 {
     const int64_t strips = (int64_t)g.n_img * g.strips * g.colblks;

@@ -274,8 +274,8 @@ namespace qrm {
 // Few images: the single-block schedule, whose runs of strips cost nothing extra (fused is 0.45 .. 0.85 times as fast below two
 // row pairs per compute unit) and which corrects the bias of every block, not of every other one (logits within 1.3 .. 4.4e-4
 // of the exact ones against 2.7 .. 5.5e-4): batches of fewer images than half the compute units keep it, at a cost of up to
-// 10 %.  From 12 row pairs per compute unit on the fused one is 0.97 .. 1.08 times as fast, from 25 on 1.06 .. 1.10 (75 x 100, 96 x
-// 96, 128 x 128, 256 x 256, 32 x 200, 200 x 66; eight blocks); in between the estimates decide.
+// 12 % (25 shapes of 8 .. 127 tiles; on seven of them it is the faster one, by up to 8 %).  From 12 row pairs per compute unit on the
+// fused one is 1.03 .. 1.18 times as fast (40 shapes of up to 500 x 200 x 256; eight blocks); in between the estimates decide.
 bool wide_tiles_fused(const ConvGeom &g, int num_cu)
 {
     if (2 * g.n_img < num_cu) return false;

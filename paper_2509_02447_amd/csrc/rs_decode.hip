@@ -57,7 +57,7 @@ int group_symbols(int n, int G) // SPL: symbols per lane, rounded up to a power 
 int group_lanes(int two_t) { return two_t > 8 ? 32 : 16; } // 3t + 1 coefficients of the systolic recursion, one per lane
 // Words of more than 128 symbols take 16 look-ups of a lane one behind the other, which shows where a launch has so few
 // of them that every workgroup takes one run: while 32 lanes a word still fit the chip that way, they have 32.  RS(255,247), 16 /
-// 32 lanes: 4096 words 8.2 / 7.4 us, 10240 10.6 / 10.2, 16000 11.3 / 13.0; RS(255,251) 7.9 / 7.7, 9.8 / 9.6, 10.5 / 12.4.
+// 32 lanes: 4096 words 8.1 / 7.9 us, 10240 10.2 / 9.8, 16000 10.7 / 12.2; RS(255,251) 7.9 / 7.9, 8.7 / 8.5, 9.1 / 10.3.
 bool second_split(int n, int two_t) { return n > 128 && two_t <= 8; }
 bool takes_second_split(const RsParams &p, int64_t N) { return second_split(p.n, p.two_t) && N <= kSecondSplitWords; }
 

@@ -429,10 +429,10 @@ bool preprocess_supported(int H_in, int W_in, int x, int T)
 }
 
 // Strips a T x T window is cut into when a launch has N of them.  Enough workgroups for the chip several times over (eight fit
-// a compute unit), so that no last wave of them is nearly empty: 600 images of 480 x 640 to 256 x 256 take 153 us in 3
-// strips an image (1.2 waves), 144 in 6, 139 in 13, the same from there on.  But a strip's column taps are its own, so
-// beyond one wave a strip keeps four turns of 256 pixel groups: 1024 tiles of 64 x 64 out of 512 x 512 images 12.0 us in 1
-// to 4 strips, 15.2 in 8; 3000 of 30 x 30 10.6 in one, 12.1 in two.
+// a compute unit), so that no last wave of them is nearly empty: 600 images of 480 x 640 to 256 x 256 take 169 us in one strip
+// an image, 151 in 3 (0.9 waves), 141 in 6, 134 in 13, 128 in 32; 300 of them 98, 72, 71, 65, 62.  But a strip's column taps are its
+// own, so beyond one wave a strip keeps four turns of 256 pixel groups: 1024 tiles of 64 x 64 out of 512 x 512 images 13.7 us in 1
+// to 4 strips, 14.8 in 8; 2048 of them 17.8 in one, 23.3 in 8; 3000 of 30 x 30 10.4 in one, 12.0 in two.
 int preprocess_strips(int64_t N, int T, bool vec)
 {
     const int64_t turns = (int64_t)T * (vec ? T / 4 : T) / 256;
@@ -537,8 +537,8 @@ HostPlan plan_host_upload(int C, int n_blocks, int final_slices, int H, int W, i
     }
     // The gather of a later chunk runs beside the kernels of the chunk before, which leave it its compute units and take 1.07 ..
     // 1.16 times as long for it: it is worth having only where the copy takes longer than that, i.e. where the link is the
-    // bound.  (24 chunks of 1024 images of 256 x 256, milliseconds a chunk, kernels alone / beside a gather / copy: tiles of
-    // 64 1.7 / 1.98 / 3.5, of 80 4.2 / 4.5 / 3.5, of 96 5.3 / 5.7 / 3.5, of 128 7.3 / 8.4 / 3.5.)  The estimate: picoseconds per block and
+    // bound.  (Six chunks, later ones copied / gathered, ms: 1024 images of 256 x 256 with tiles of 64 20.1 / 11.3, of 65 21.6 / 20.5, of 72
+    // 22.0 / 22.8, of 80 24.5 / 25.1; 512 of 512 x 512, 160 42.8 / 39.9, 176 43.6 / 45.0.)  The estimate: picoseconds per block and
     // pixel of the tiles' column blocks, 57 GB/s.
     const double columns = 64.0 * ((tile + 63) / 64);
     const double tile_s = tile * columns * 1e-12 * (n_blocks * (C == 64 ? 50.0 : 26.0) + final_slices * (C == 64 ? 50.0 : 32.0));
