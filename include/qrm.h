@@ -348,7 +348,8 @@ enum {
     QRM_PROFILE_BLOCK_LAST = 5,  /* the last block alone */
     QRM_PROFILE_HEAD = 6,        /* final convolution + pool + linear + threshold + symbol packing */
     QRM_PROFILE_RS_DECODE = 7,   /* Reed-Solomon decoding */
-    QRM_PROFILE_KINDS = 8
+    QRM_PROFILE_CHAIN = 8,       /* all blocks of a batch of few tiles in one launch */
+    QRM_PROFILE_KINDS = 9
 };
 QRM_API qrm_status qrm_profile_enable(qrm_ctx *ctx, int32_t on);
 QRM_API qrm_status qrm_profile_read(qrm_ctx *ctx, int32_t kind, double *ms_total, int64_t *launches, double *flops);

@@ -46,10 +46,10 @@ DIAG_EXPORTS = ["qrm_diag_set_flags", "qrm_diag_matrix_rate", "qrm_diag_pair_spl
                 "qrm_diag_preprocess_strips", "qrm_diag_rs_lanes"]   # include/qrm_diag.h: bench and test tooling
 
 QRM_MAX_STREAMS = 8   # include/qrm.h
-QRM_DIAG_NO_FUSED_PAIRS, QRM_DIAG_POISON_WORKSPACE, QRM_DIAG_FUSE_ALWAYS = 1, 2, 4
+QRM_DIAG_NO_FUSED_PAIRS, QRM_DIAG_POISON_WORKSPACE, QRM_DIAG_FUSE_ALWAYS, QRM_DIAG_CHAIN_ALWAYS, QRM_DIAG_NO_CHAIN = 1, 2, 4, 8, 16
 (QRM_PROFILE_PAIR_FIRST, QRM_PROFILE_PAIR_MID, QRM_PROFILE_PAIR_LAST, QRM_PROFILE_BLOCK_FIRST, QRM_PROFILE_BLOCK_MID,
- QRM_PROFILE_BLOCK_LAST, QRM_PROFILE_HEAD, QRM_PROFILE_RS_DECODE, QRM_PROFILE_KINDS) = range(9)
-PROFILE_KIND_NAMES = ["pair_first", "pair_mid", "pair_last", "block_first", "block_mid", "block_last", "head", "rs_decode"]
+ QRM_PROFILE_BLOCK_LAST, QRM_PROFILE_HEAD, QRM_PROFILE_RS_DECODE, QRM_PROFILE_CHAIN, QRM_PROFILE_KINDS) = range(10)
+PROFILE_KIND_NAMES = ["pair_first", "pair_mid", "pair_last", "block_first", "block_mid", "block_last", "head", "rs_decode", "chain"]
 
 
 def lib_path() -> str:

@@ -192,6 +192,19 @@ __device__ __forceinline__ void store16(void *buf, uint32_t bytes, uint32_t voff
     __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, voff, soff, 0);
 }
 
+// The loads of launches whose workgroups hand data to each other (conv_chain_kernel): at the scope of the device, so that they do not
+// find what the compute unit's own cache holds of earlier contents.
+constexpr int kDeviceScope = 16; // the instructions' sc1 bit
+__device__ __forceinline__ void load_lds16c(const uint8_t *buf, uint32_t bytes, uint32_t voff, uint8_t *dst)
+{
+    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(buf), 0, (int)bytes, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)dst, 16, voff, 0, 0, kDeviceScope);
+}
+__device__ __forceinline__ u32x4 load16c(const void *buf, uint32_t bytes, uint32_t voff)
+{
+    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(buf), 0, (int)bytes, 0x00020000);
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, 0, kDeviceScope);
+}
 template <int C>
 struct RowLoader {
     typedef MidCfg<C> K;
@@ -1861,6 +1874,581 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
 }
 
 // ------------------------------------------------------------------------------------------------
+// All blocks of the extractor in one launch, for batches of few tiles.
+//
+// A block of a small batch is a launch of 5 .. 14 us of which its matrix instructions take one to four: the rest is the launch
+// itself, the round trips to memory that it begins and ends with, and the weights on their way.  Here the images are dealt to the
+// XCDs, whose workgroups hand rows to each other through their L2.  A block of an image is cut into items of ROWS rows x 32
+// columns (the first block: 64 columns), and the workgroups of an XCD, one to a compute unit, draw items from one counter in the
+// order (chunk of images, block, image, strip, column block).  An item waits until all items of its image in the block before are
+// done (a counter per block and image), since the correction of its bias takes means over the image.
+//   No wait can last, whatever else runs on the device and however the workgroups are dealt to the XCDs: an item only waits for
+// items with lower numbers of the same XCD, and those have been drawn by workgroups that are running; the lowest unfinished
+// item waits for none.  Whoever draws a chunk's first number claims the next chunk of images for its XCD, so that an XCD without
+// workgroups gets none.
+//   What a later item reads has been stored in the L2 (s_waitcnt vmcnt) when the counter says so, and is loaded past the
+// compute unit's own cache (load16c, load_lds16c).  A hand-over between 8 workgroups of an XCD takes 1.0 us and 1.7 through the
+// memory behind the L2s, between 32 it takes 2.0 and 3.6; fences, which write back and invalidate a whole L2, made that 3 and 5.
+//   Products, sums, records, lines and roundings at 32 channels are those of conv_first_kernel and conv_mid_kernel, in
+// their order: the results are the same bit for bit, so that a tile's do not depend on the batch around it.  (64 channels: pairs
+// of rows as here, conv_mid_kernel has strips of four.)
+//   The state (ChainState) is all zeros when the launch begins; the launch behind it, which reads its results, clears it again.
+// ------------------------------------------------------------------------------------------------
+struct ChainArgs {
+    TileSrc src;
+    ConvGeom g;
+    int blocks;               // blocks to run
+    const bf16_t *w_first, *w_mid;
+    const float *bias, *rsum; // [blocks][C], [blocks - 1][C][C]
+    uint8_t *act[2];          // block b writes act[b & 1]
+    float *rec[2];            // its channel sums: rec[b & 1]
+    MeanIn first, mid;        // what a consumer has to know of those of the first block, of another one (rec unused)
+    float *lines;             // what the last block leaves, or null: it writes activations as the others do
+    int64_t lines_stride;     // floats from image to image
+    uint32_t *state;          // ChainState
+    int chunk, chunks;        // images that an XCD takes at a time, chunks of them
+};
+// ChainState, in words: chunks claimed; from kChainTeamAt on, for every XCD, numbers drawn and the chunks it has claimed (plus one); from
+// kChainCountAt on, for every block and image, items done.  (A line of 128 bytes for what is counted apart.)
+constexpr int kChainTeamAt = 32, kChainTeams = 8, kChainTeam = 32, kChainCountAt = kChainTeamAt + kChainTeams * kChainTeam, kChainCount = 32;
+constexpr int kChainCols = 32;
+constexpr int kChainPatience = 1 << 22; // polls, seconds: never reached (see above), but a fault elsewhere is not to hang the device
+
+// WAVES of a workgroup, RW: rows that a wavefront multiplies at a time, STEPS: times it does
+template <int C, int WAVES, int RW, int STEPS>
+struct ChainCfg {
+    typedef MidCfg<C> K;
+    static constexpr int RG = WAVES / K::NCB;           // wavefronts one above the other
+    static constexpr int ROWS = RG * RW * STEPS;
+    static_assert(RW == 2 || (C == 32 && ROWS == kRows && STEPS == 1), "a row per wavefront: where an item is a strip");
+    static constexpr int THREADS = 64 * WAVES;
+    static constexpr int HALO = kChainCols + 2;
+    static constexpr int ROWB = HALO * K::PS;           // a staged row
+    static constexpr int ROW_SLOTS = HALO * K::SPP;
+    static constexpr int SLOTS = (ROWS + 2) * ROW_SLOTS; // of 16 bytes, all rows one behind the other
+    static constexpr int LOADS = (SLOTS + THREADS - 1) / THREADS; // per thread
+    static constexpr int PIX = (ROWS + 2) * kHaloW;     // first block: staged pixels of 8 bytes
+    // Of the three horizontal taps, those whose weights come in through LDS while the block before is multiplied: as many as it has room for
+    static constexpr int AHEAD = LOADS * THREADS * 16 + 9 * K::KC * K::NCB * 1024 <= 150 * 1024 ? 3 : 2;
+    static constexpr int FRAGS = AHEAD * 3 * K::KC;     // .. and their fragments for one block of 32 output channels
+    // The wavefronts that ask for them, the second ones of their SIMDs, whose turn on the matrix pipes comes later: the loads take 0.5 us to be issued
+    static constexpr int LOADERS = WAVES == 4 ? 2 : C == 64 ? 4 : 3;
+    static_assert(K::NCB * FRAGS % LOADERS == 0, "whole fragments to a wavefront");
+};
+
+// One output row of 32 pixels x 32 channels at 32 channels, the upper or (LOWER) the lower of a pair: its products in the order of strip_mma<32, 2>.
+template <bool LOWER>
+__device__ __forceinline__ void half_pair_mma(const lrow_t (&rowp)[3], const bf16x8 (&Wr)[9][2], f32x16 &acc)
+{
+    asm volatile(".p2align 5");
+    typedef MidCfg<32> K;
+    constexpr int NF = 4, NT = 18;
+    constexpr auto row = [](int t) { return LOWER ? (t % 6 < 2 ? 1 : t % 6 % 2 * 2) : (t % 6 < 4 ? t % 6 % 2 * 2 : 1); };
+    constexpr auto chunk = [](int t) { return LOWER ? (t % 6 < 2 ? t % 6 : t % 6 / 4) : (t % 6 < 4 ? t % 6 / 2 : t % 6 - 4); };
+    bf16x8 f[NF];
+    unrolled<NF>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        frag_read<t / 6 * K::PS + chunk(t) * 32>(f[t], rowp[row(t)]);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    unrolled<NT>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        bf16x8 &fr = f[t % NF];
+        frag_wait<(t + NF <= NT ? NF - 1 : NT - 1 - t)>(fr);
+        acc = mfma32(Wr[row(t) * 3 + t / 6][chunk(t)], fr, t == 0 ? kZeroAcc : acc);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (t + NF < NT) {
+            constexpr int u = t + NF;
+            frag_read<u / 6 * K::PS + chunk(u) * 32>(fr, rowp[row(u)]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    asm volatile("" : "+v"(acc)); // (the products stay where they are)
+}
+
+template <int C, int WAVES, int RW, int STEPS>
+__global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
+{
+    typedef MidCfg<C> K;
+    typedef ChainCfg<C, WAVES, RW, STEPS> G;
+    constexpr int LDS_ROWS = G::LOADS * G::THREADS * 16;
+    static_assert(G::PIX * 8 <= LDS_ROWS, "the first block's pixels take the rows' place");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_ROWS];
+    __shared__ __attribute__((aligned(1024))) uint8_t s_weights[K::NCB * G::FRAGS * 1024];
+    __shared__ __attribute__((aligned(16))) float s_part[C == 64 ? WAVES : 1][C]; // 64 channels: sums of the records, by wavefront
+    __shared__ __attribute__((aligned(16))) float s_mean[WAVES][C];   // the image's means, for a wavefront's own use
+    __shared__ __attribute__((aligned(16))) float s_lower[RW == 1 ? 2 : 1][RW == 1 ? 1024 : 4]; // lower rows on their way to the wavefront that sums the pair up
+    __shared__ __attribute__((aligned(16))) float s_init[WAVES][32];  // bias + correction of its outputs
+    __shared__ __attribute__((aligned(16))) int s_next[2][8]; // the next item, by its parity within the workgroup: a slow wavefront may still read the one before
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cb = wave % K::NCB, rg = wave / K::NCB;
+    const int strips = (a.g.h + G::ROWS - 1) / G::ROWS, colblks = (a.g.w + kChainCols - 1) / kChainCols;
+    const int ipi0 = strips * a.g.colblks, ipi = strips * colblks;          // items of an image: first block, another one
+    const int first_items = a.chunk * ipi0, block_items = a.chunk * ipi;    // of a chunk
+    const uint32_t items = (uint32_t)(first_items + (a.blocks - 1) * block_items);
+    const uint32_t img_bytes = (uint32_t)((size_t)a.g.h * a.g.w * C * 2);
+    const int sample_phase = sampled_strip(a.g.strips);
+    const int xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) % kChainTeams; // hwreg(HW_REG_XCC_ID, 0, 4)
+    uint32_t *const team = a.state + kChainTeamAt + xcd * kChainTeam;
+
+    // One lane draws the next item's number and tells the others what it is.  Between the draw and the claim of a chunk nothing is
+    // waited for.
+    struct Item {
+        int b, n, y0, colblk; // b < 0: none, n < 0: and none will come
+    };
+    const bool draws = wave == WAVES - 1; // one lane of this wavefront
+    // (an address per lane as far as the compiler can tell: it would look at the answer at once to hand it out to several lanes)
+    auto draw = [&]() -> uint32_t {
+        uint32_t t = 0;
+        if ((tid & 63) == 0) t = __hip_atomic_fetch_add(team + pin_in_loop(0), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return t;
+    };
+    uint32_t my_chunk = 0, chunk_at = ~0u; // the chunk that numbers from chunk_at * items on are of, plus one
+    auto drawn = [&](uint32_t answer, int to) __attribute__((always_inline)) {
+        const uint32_t t = __builtin_amdgcn_readfirstlane(answer), q = t / items;
+        if (q >= (uint32_t)kChainTeams) { // there are at most kChainTeams chunks, and an XCD's first ones are those that it got
+            my_chunk = ~0u;
+        } else if (t == q * items) { // the first of a chunk
+            uint32_t c = 0;
+            if ((tid & 63) == 0) {
+                c = 1u + __hip_atomic_fetch_add(a.state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(team + 1 + q, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            my_chunk = __builtin_amdgcn_readfirstlane(c);
+        } else if (q != chunk_at) {
+            int polls = 0;
+            do my_chunk = __builtin_amdgcn_readfirstlane(__hip_atomic_load(team + 1 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            while (my_chunk == 0 && ++polls < kChainPatience); // (whoever drew the chunk's first number claims it at once)
+        }
+        chunk_at = q;
+        int i = (int)(t - q * items), b = 0, in_block = first_items, in_image = ipi0, across = a.g.colblks;
+        if (i >= first_items) {
+            i -= first_items;
+            in_block = block_items;
+            in_image = ipi;
+            across = colblks;
+            b = 1;
+        }
+        const int past = i / in_block, j = i - past * in_block, m = j / in_image, at = j - m * in_image, strip = at / across;
+        const int n = (int)(my_chunk - 1) * a.chunk + m;
+        const bool none = my_chunk - 1 >= (uint32_t)a.chunks;
+        int *s = s_next[to];
+        s[0] = !none && n < a.g.n_img ? b + past : -1;
+        s[1] = none ? -1 : n;
+        s[2] = strip * G::ROWS;
+        s[3] = at - strip * across;
+    };
+    int parity = 0;
+    // what has been drawn (and a barrier passed)
+    auto next_item = [&]() {
+        int v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_readfirstlane(s_next[parity][i]);
+        parity ^= 1;
+        return Item{v[0], v[1], v[2], v[3]};
+    };
+    auto counter = [&](int b, int n) { return a.state + kChainCountAt + ((size_t)b * a.g.n_img + n) * kChainCount; };
+    // all items of image n in block b are done
+    auto wait_for = [&](int b, int n) {
+        if (wave == 0) {
+            const uint32_t all = (uint32_t)(b == 0 ? ipi0 : ipi);
+            int polls = 0;
+            while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(counter(b, n), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < all && ++polls < kChainPatience) {}
+        }
+        lds_barrier();
+    };
+    // The item is done but for its last stores; next: the answer to the draw, which is asked for when the item's rows are there: a workgroup
+    // that drew before would hold two items of a block while others have none.
+    auto done = [&](const Item &it, uint32_t next) {
+        asm volatile("" ::: "memory");
+        if (draws) drawn(next, parity);
+        __builtin_amdgcn_s_waitcnt(kWaitVm0); // the stores are in the L2
+        lds_barrier();                        // .. those of all wavefronts, which also are done with what is in LDS
+        if (tid == 0) __hip_atomic_fetch_add(counter(it.b, it.n), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+
+    // Whether block b's rows of this strip leave sums
+    auto is_last = [&](int b) { return b == a.blocks - 1 && a.lines; };
+    auto leaves_sums = [&](int b, int strip) { return is_last(b) || (strip & 7) == sample_phase; };
+    // Bias, ReLU, bf16 and stores of the wavefront's rows, from row yw of the image on (conv_mid_kernel's epilogue)
+    auto store_rows = [&](const Item &it, int yw, const f32x16 (&acc)[RW]) __attribute__((always_inline)) {
+        const int ln = pin_in_loop(tid & 63), x = it.colblk * kChainCols + (ln & 31), half = ln >> 5;
+        const float *si = &s_init[wave][half * 16];
+        uint8_t *out = a.act[it.b & 1] + (size_t)it.n * img_bytes;
+        const uint32_t dbase = dither16(x, yw & ~1); // (pairs of rows a quarter step apart)
+#pragma unroll
+        for (int hq = 0; hq < 2; ++hq) {
+            const f32x4 b0 = *(const f32x4 *)(si + 8 * hq), b1 = *(const f32x4 *)(si + 8 * hq + 4);
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                const uint32_t dth = dbase ^ ((uint32_t)(RW == 1 ? yw & 1 : r) << 14);
+                u32x4 pk;
+                pk[0] = pack_bf16_relu(acc[r][8 * hq + 0] + b0[0], acc[r][8 * hq + 1] + b0[1], dth, true);
+                pk[1] = pack_bf16_relu(acc[r][8 * hq + 2] + b0[2], acc[r][8 * hq + 3] + b0[3], dth, true);
+                pk[2] = pack_bf16_relu(acc[r][8 * hq + 4] + b1[0], acc[r][8 * hq + 5] + b1[1], dth, true);
+                pk[3] = pack_bf16_relu(acc[r][8 * hq + 6] + b1[2], acc[r][8 * hq + 7] + b1[3], dth, true);
+                const bool inside = yw + r < a.g.h && x < a.g.w;
+                store16(out, img_bytes, inside ? (uint32_t)((((yw + r) * a.g.w + x) * C + cb * 32 + half * 16 + 8 * hq) * 2) : kOutside, 0, pk);
+            }
+        }
+    };
+    // The sums of rows yw, yw + 1 (yw even)
+    auto sum_rows = [&](const Item &it, int yw, const f32x16 (&acc)[2]) __attribute__((always_inline)) {
+        const int ln = pin_in_loop(tid & 63), px = ln & 31, half = ln >> 5;
+        const int x0 = it.colblk * kChainCols, x = x0 + px, strip = yw / kRows, rg2 = yw / 2 % 2, blk = it.colblk / 2, xb = it.colblk % 2;
+        const float *si = &s_init[wave][half * 16];
+        const int piece = rg2 * 2 + xb;
+        // a last block of 32 columns that stands alone also leaves the (empty) sums of the one beside it
+        const bool alone = xb == 0 && x0 + kChainCols >= a.g.w;
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        if (is_last(it.b)) {
+            float *lines = a.lines + it.n * a.lines_stride + cb * 32 + half * 16;
+            LinePlaces p; // those of conv_mid_last_sums() at two row groups
+            p.first_col = a.g.strips * a.g.colblks * 4;
+            p.last_col = p.first_col + a.g.strips * 2;
+            p.rows = p.last_col + a.g.strips * 2;
+            p.last_rows = p.rows + 2 * a.g.colblks;
+            p.corners = p.last_rows + 2 * a.g.colblks;
+            p.whole = (blk * a.g.strips + strip) * 4 + piece;
+            p.col = strip * 2 + rg2;
+            p.row = blk * 2 + xb;
+            last_lines<C, 2>(acc, si, lines, p, x, x0, yw, a.g.h, a.g.w, px);
+            if (alone && px < 4) {
+                *(f32x4 *)(lines + (p.whole + 1) * C + 4 * px) = zero;
+                if (yw == 0) *(f32x4 *)(lines + (p.rows + p.row + 1) * C + 4 * px) = zero;
+                if (a.g.h - 1 - yw >= 0 && a.g.h - 1 - yw < 2) *(f32x4 *)(lines + (p.last_rows + p.row + 1) * C + 4 * px) = zero;
+            }
+        } else {
+            float *rec = a.rec[it.b & 1] + ((int64_t)it.n * a.mid.recs + ((strip >> 3) * a.g.colblks + blk) * 4 + piece) * C + cb * 32 + half * 16;
+            strip_statistics<2>(acc, si, rec, x, yw, a.g.h, a.g.w, px);
+            if (alone && px < 4) *(f32x4 *)(rec + C + 4 * px) = zero;
+        }
+    };
+
+    // The weights of a block, 74 KB at 64 channels, come to the compute unit once, into LDS and while the block before is multiplied;
+    // into registers they go while the block before is waited for.  (From memory for every wavefront they are 147 or 295 KB,
+    // 1 .. 2 us, and the flags that are asked for behind them come in behind them.)
+    int lds_of = 0; // the block whose weights s_weights holds (0: none)
+    auto weights_to_lds = [&](int b) {
+        lds_of = b;
+        if (wave < WAVES - G::LOADERS) return;
+        const bf16_t *w = a.w_mid + (size_t)(b - 1) * 9 * C * C;
+        const int lane = pin_in_loop(tid & 63);
+#pragma unroll
+        for (int j = 0; j < K::NCB * G::FRAGS / G::LOADERS; ++j) {
+            const int f = j * G::LOADERS + wave - (WAVES - G::LOADERS);
+            const int block = f / G::FRAGS, r = f - block * G::FRAGS, dx = r / (3 * K::KC), kc = r / 3 % K::KC, dy = r % 3;
+            __builtin_amdgcn_global_load_lds((gptr_t)((const bf16x8 *)w + ((block * 9 + dy * 3 + dx) * K::KC + kc) * 64 + lane), (lptr_t)(s_weights + f * 1024), 16, 0, 0);
+        }
+    };
+    {
+        uint32_t first = 0;
+        if (draws) first = draw();
+        weights_to_lds(1);
+        if (draws) drawn(first, 0);
+        lds_barrier();
+    }
+    Item it = next_item();
+    // a number without an item: the next one's
+    auto skip = [&]() {
+        if (draws) drawn(draw(), parity);
+        __syncthreads();
+        it = next_item();
+    };
+
+    // ---- the first block, on the raw tile (conv_first_kernel, whose wavefronts take NCB rows each)
+    auto first_block = [&]() __attribute__((always_inline)) {
+        bf16x8 Wr[kFirstFrags];
+        {
+            const int lane = tid & 63;
+#pragma unroll
+            for (int f = 0; f < kFirstFrags; ++f) Wr[f] = ((const bf16x8 *)a.w_first)[(cb * kFirstFrags + f) * 64 + lane];
+            if (lane < 32) s_init[wave][lane] = a.bias[cb * 32 + lane];
+        }
+#pragma unroll 1
+        do {
+            const int tid = pin_in_loop(threadIdx.x); // (nothing that follows from it is kept over the items)
+            const int lane = tid & 63, px = lane & 31, half = lane >> 5, x0 = it.colblk * kTileW;
+            int oy = 0, ox = 0;
+            if (a.src.off) {
+                oy = clampi(a.src.off[2 * it.n], 0, a.src.H - a.g.h);
+                ox = clampi(a.src.off[2 * it.n + 1], 0, a.src.W - a.g.w);
+            }
+            const int plane = a.src.H * a.src.W;
+            const uint8_t *tile0 = a.src.img + (int64_t)it.n * 3 * plane + (int64_t)oy * a.src.W + ox;
+            constexpr int NB = (G::PIX * 3 + G::THREADS - 1) / G::THREADS;
+            uint32_t v[NB];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) { // all asked for before the first is used: from a pixel of the tile in any case
+                const int idx = min(tid + k * G::THREADS, G::PIX * 3 - 1);
+                const int c = idx / G::PIX, p = idx - c * G::PIX, row = p / kHaloW, col = p - row * kHaloW;
+                v[k] = tile0[(int64_t)c * plane + (int64_t)clampi(it.y0 - 1 + row, 0, a.g.h - 1) * a.src.W + clampi(x0 - 1 + col, 0, a.g.w - 1)];
+            }
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const int idx = tid + k * G::THREADS;
+                const int c = idx / G::PIX, p = idx - c * G::PIX, row = p / kHaloW, col = p - row * kHaloW;
+                const bool inside = (uint32_t)(it.y0 - 1 + row) < (uint32_t)a.g.h && (uint32_t)(x0 - 1 + col) < (uint32_t)a.g.w;
+                if (idx < G::PIX * 3) {
+                    uint16_t *q = (uint16_t *)lds + p * 4;
+                    q[c] = inside ? (uint16_t)(__builtin_bit_cast(uint32_t, (float)v[k]) >> 16) : (uint16_t)0;
+                    if (c == 0) q[3] = inside ? (uint16_t)0x3F80 : (uint16_t)0;
+                }
+            }
+            lds_barrier();
+            uint32_t next = 0;
+            if (draws) next = draw();
+            uint8_t *out = a.act[0] + (size_t)it.n * img_bytes;
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll 1
+            for (int row0 = rg * K::NCB; row0 < G::ROWS; row0 += G::RG * K::NCB) {
+                const int strip = (it.y0 + row0) / kRows;
+                if (strip >= a.g.strips) break;
+                const bool sample = (strip & 7) == sample_phase;
+                float tv[16] = {};
+                const float *si = &s_init[wave][half * 16];
+#pragma unroll 1
+                for (int i = 0; i < 2 * K::NCB; ++i) { // rows, blocks of 32 columns
+                    const int row = row0 + i / 2, y = it.y0 + row, x = x0 + i % 2 * 32 + px;
+                    if (y >= a.g.h || x0 + i % 2 * 32 >= a.g.w) continue; // the same for the whole wavefront
+                    const uint8_t *lp = lds + (row * kHaloW + i % 2 * 32 + px) * 8;
+                    bf16x8 bfrag[3];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        auto tap_at = [&](int j) { // (the halves of a wavefront may read different taps)
+                            const int tap = half ? first_tap(q, 1, j) : first_tap(q, 0, j);
+                            return *(const u32x2 *)(lp + ((tap / 3) * kHaloW + tap % 3) * 8);
+                        };
+                        const u32x2 t0 = tap_at(0), t1 = tap_at(1);
+                        bfrag[q] = __builtin_bit_cast(bf16x8, (u32x4){t0[0], t0[1], t1[0], t1[1]});
+                    }
+                    f32x16 acc = kZeroAcc;
+#pragma unroll
+                    for (int f = 0; f < kFirstFrags; ++f) acc = mfma32(Wr[f], bfrag[f % 3], acc);
+                    const uint32_t dth = dither16(x, y);
+                    const uint32_t vo = x < a.g.w ? (uint32_t)(((y * a.g.w + x) * C + cb * 32 + half * 16) * 2) : kOutside;
+#pragma unroll
+                    for (int hq = 0; hq < 2; ++hq) {
+                        u32x4 pk;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            acc[8 * hq + 2 * e] += si[8 * hq + 2 * e];
+                            acc[8 * hq + 2 * e + 1] += si[8 * hq + 2 * e + 1];
+                            pk[e] = pack_bf16_relu(acc[8 * hq + 2 * e], acc[8 * hq + 2 * e + 1], dth, true);
+                        }
+                        store16(out, img_bytes, vo + hq * 16, 0, pk); // (kOutside + 16 is outside, too)
+                    }
+                    if (sample) {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) tv[v] += x < a.g.w ? fmaxf(acc[v], 0.f) : 0.f;
+                    }
+                }
+                if (sample) {
+                    const int ri = ((strip >> 3) * a.g.colblks + it.colblk) * (kRows / K::NCB) + (it.y0 + row0) % kRows / K::NCB;
+                    float *rec = a.rec[0] + ((int64_t)it.n * a.first.recs + ri) * C + cb * 32 + half * 16;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) tv[v] = half_sum(tv[v]);
+                    if (px == kSumLane) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) *(f32x4 *)(rec + 4 * q) = (f32x4){tv[4 * q], tv[4 * q + 1], tv[4 * q + 2], tv[4 * q + 3]};
+                    }
+                }
+            }
+            done(it, next);
+            it = next_item();
+        } while (it.b == 0);
+    };
+
+    // ---- a block behind it
+    auto later_blocks = [&]() __attribute__((always_inline)) {
+        bf16x8 Wr[9][K::KC];
+        int w_of = 0; // the block whose weights the registers hold (0: none)
+        __builtin_amdgcn_s_waitcnt(kWaitVm0); // what has been asked for in the beginning (later on, done() waits for all that is under way)
+        lds_barrier();
+#pragma unroll 1
+        do {
+            const int tid = pin_in_loop(threadIdx.x);
+            const int lane = tid & 63;
+            if (w_of != it.b) {
+                if (lds_of != it.b) {
+                    weights_to_lds(it.b);
+                    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                    lds_barrier();
+                }
+#pragma unroll
+                for (int dx = 0; dx < G::AHEAD; ++dx)
+#pragma unroll
+                    for (int kc = 0; kc < K::KC; ++kc)
+#pragma unroll
+                        for (int dy = 0; dy < 3; ++dy)
+                            Wr[dy * 3 + dx][kc] = *(const bf16x8 *)(s_weights + (cb * G::FRAGS + (dx * K::KC + kc) * 3 + dy) * 1024 + lane * 16);
+                w_of = it.b;
+            }
+            uint32_t voff[G::LOADS];
+#pragma unroll
+            for (int k = 0; k < G::LOADS; ++k) {
+                const int sl = tid + k * G::THREADS, row = sl / G::ROW_SLOTS, rem = sl - row * G::ROW_SLOTS;
+                const int col = rem / K::SPP, cpos = rem - col * K::SPP;
+                const int y = it.y0 - 1 + row, x = it.colblk * kChainCols - 1 + col;
+                const bool ok = sl < G::SLOTS && cpos < C / 8 && (uint32_t)y < (uint32_t)a.g.h && (uint32_t)x < (uint32_t)a.g.w;
+                voff[k] = ok ? (uint32_t)((y * a.g.w + x) * (C * 2) + cpos * 16) : kOutside;
+            }
+            wait_for(it.b - 1, it.n);
+            // The rows, the records of the image, the other weights: in the order in which they are looked at (loads of a wavefront return
+            // in order).
+            const uint8_t *in = a.act[(it.b - 1) & 1] + (size_t)it.n * img_bytes;
+#pragma unroll
+            for (int k = 0; k < G::LOADS; ++k) load_lds16c(in, img_bytes, voff[k], lds + (k * WAVES + wave) * 1024);
+            asm volatile("" ::: "memory");
+            // (32 channels: every wavefront all of them, as ImageMeans; 64: each a share)
+            constexpr int LPR = C / 4, RPL = C == 64 ? G::THREADS / LPR : 64 / LPR, INF = C == 64 ? 2 : 4; // lanes per record, records per load, loads in flight
+            const int rec_tid = C == 64 ? tid : lane, recs = it.b == 1 ? a.first.recs : a.mid.recs;
+            const float *rec = a.rec[(it.b - 1) & 1] + (int64_t)it.n * recs * C;
+            f32x4 v[INF];
+            auto records = [&](int r0) {
+#pragma unroll
+                for (int u = 0; u < INF; ++u)
+                    v[u] = __builtin_bit_cast(f32x4, load16c(rec, (uint32_t)recs * C * 4, (uint32_t)(min(r0 + u * RPL + rec_tid / LPR, recs - 1) * LPR + rec_tid % LPR) * 16));
+            };
+            records(0);
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int dx = G::AHEAD; dx < 3; ++dx) {
+                const bf16x8 *wp = (const bf16x8 *)(a.w_mid + (size_t)(it.b - 1) * 9 * C * C) + cb * 9 * K::KC * 64 + lane;
+#pragma unroll
+                for (int kc = 0; kc < K::KC; ++kc)
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy) Wr[dy * 3 + dx][kc] = wp[((dy * 3 + dx) * K::KC + kc) * 64];
+            }
+            // what the correction of this wavefront's outputs needs: four outputs to a lane, eight lanes to an output with an eighth of the
+            // input channels each
+            constexpr int CP = C / 8;
+            const float *rsum = a.rsum + (size_t)(it.b - 1) * C * C + (lane >> 3) * CP * C + cb * 32 + 4 * (lane & 7);
+            const f32x4 bias = *(const f32x4 *)(a.bias + it.b * C + cb * 32 + 4 * (lane & 7));
+            f32x4 rs[CP];
+#pragma unroll
+            for (int k = 0; k < CP; ++k) rs[k] = *(const f32x4 *)(rsum + k * C);
+            asm volatile("" ::: "memory");
+            {
+                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int u = 0; u < INF; ++u) asm volatile("" : "+v"(v[u])); // the records are first looked at here
+                auto add = [&](int r0) {
+#pragma unroll
+                    for (int u = 0; u < INF; ++u) {
+                        const bool ok = r0 + u * RPL + rec_tid / LPR < recs;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[e] += ok ? v[u][e] : 0.f;
+                    }
+                };
+                add(0);
+#pragma unroll 1
+                for (int r0 = INF * RPL; r0 < recs; r0 += INF * RPL) {
+                    records(r0);
+                    add(r0);
+                }
+#pragma unroll
+                for (int sh = LPR; sh < 64; sh <<= 1)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[e] += __shfl_xor(sum[e], sh);
+                if (C == 64) {
+                    if (lane < LPR) *(f32x4 *)&s_part[wave % (C == 64 ? WAVES : 1)][4 * lane] = sum;
+                } else {
+                    const float inv_cnt = it.b == 1 ? a.first.inv_cnt : a.mid.inv_cnt;
+                    if (lane < LPR) *(f32x4 *)&s_mean[wave][4 * lane] = (f32x4){sum[0] * inv_cnt, sum[1] * inv_cnt, sum[2] * inv_cnt, sum[3] * inv_cnt};
+                }
+            }
+            lds_barrier(); // (the records have landed, and before them the rows)
+            uint32_t next = 0;
+            if (draws) next = draw();
+            if (lds_of == it.b && it.b + 1 < a.blocks) weights_to_lds(it.b + 1);
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                const int ln = pin_in_loop(tid & 63), px = ln & 31, half = ln >> 5;
+                const int row = (s * G::RG + rg) * RW; // the first of the wavefront's
+                lrow_t rowp[RW + 2];
+#pragma unroll
+                for (int r = 0; r < RW + 2; ++r) rowp[r] = lds_address(lds) + (uint32_t)((row + r) * G::ROWB + px * K::PS + half * 16);
+                f32x16 acc[RW];
+                if constexpr (RW == 1) {
+                    if (rg & 1) half_pair_mma<true>(rowp, Wr, acc[0]);
+                    else half_pair_mma<false>(rowp, Wr, acc[0]);
+                } else {
+                    strip_mma<C, RW>(rowp, Wr, acc, kZeroAcc, []() {});
+#pragma unroll
+                    for (int r = 0; r < RW; ++r) asm volatile("" : "+v"(acc[r])); // (the products stay where they are)
+                }
+                if (s == 0) {
+                    if constexpr (C == 64) {
+                        float m = s_part[0][ln];
+#pragma unroll
+                        for (int w = 1; w < WAVES; ++w) m += s_part[w][ln];
+                        s_mean[wave][ln] = m * (it.b == 1 ? a.first.inv_cnt : a.mid.inv_cnt);
+                    }
+                    f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int k = 0; k < CP; ++k) {
+                        const float mk = s_mean[wave][(ln >> 3) * CP + k];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) d[e] = fmaf(rs[k][e], mk, d[e]);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) d[e] += dpp_f<0x128, 0xf>(d[e]); // row_ror:8
+#pragma unroll
+                    for (int sh = 16; sh < 64; sh <<= 1)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) d[e] += __shfl_xor(d[e], sh);
+                    if (ln < 8) *(f32x4 *)&s_init[wave][4 * ln] = (f32x4){bias[0] + d[0], bias[1] + d[1], bias[2] + d[2], bias[3] + d[3]};
+                }
+                const int yw = it.y0 + row, strip = yw / kRows;
+                if (strip >= a.g.strips) continue; // (the same for the whole wavefront)
+                if (!is_last(it.b)) store_rows(it, yw, acc);
+                if (!leaves_sums(it.b, strip)) continue;
+                if constexpr (RW == 2) {
+                    sum_rows(it, yw, acc);
+                } else { // (the same for the whole workgroup, whose rows are a strip)
+                    float *lower = &s_lower[rg >> 1][ln * 4];
+                    if (rg & 1) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) *(f32x4 *)(lower + q * 256) = (f32x4){acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]};
+                    }
+                    lds_barrier();
+                    if (!(rg & 1)) {
+                        f32x16 pair[2] = {acc[0], {}};
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const f32x4 v = *(const f32x4 *)(lower + q * 256);
+                            pair[1][4 * q] = v[0]; pair[1][4 * q + 1] = v[1]; pair[1][4 * q + 2] = v[2]; pair[1][4 * q + 3] = v[3];
+                        }
+                        sum_rows(it, yw, pair);
+                    }
+                }
+            }
+            done(it, next);
+            it = next_item();
+        } while (it.b > 0);
+    };
+#pragma unroll 1
+    for (;;) {
+        if (it.b == 0) first_block();
+        else if (it.b > 0) later_blocks();
+        else if (it.n >= 0) skip();
+        else break;
+    }
+}
+
+// The state of conv_chain_kernel's launch back to zeros, by the launch behind it: image n's counters, and for n = 0 what else there is.
+__device__ __forceinline__ void clear_chain(const ChainState &c, int64_t n, int tid, int threads)
+{
+    if (!c.words) return;
+    if (n == 0)
+        for (int i = tid; i < kChainCountAt; i += threads) c.words[i] = 0u;
+    for (int b = tid; b < c.blocks; b += threads) c.words[kChainCountAt + ((size_t)b * c.n_img + n) * kChainCount] = 0u;
+}
+
+// ------------------------------------------------------------------------------------------------
 // Head for the linear tail: the nine border-aware channel sums of the last block -> final conv + global
 // average pool in closed form (fp32 weights) -> linear -> logits -> bits -> symbols.
 //   pooled[o] = 1/(h w) * sum_{c,dy,dx} Wf[o][c][dy][dx] * S[c][dy][dx],
@@ -1988,7 +2576,7 @@ __global__ __launch_bounds__(kHeadThreads, 4) void head_kernel(const float *__re
                                                                const float *__restrict__ fbias, const float *__restrict__ lin_w,
                                                                const float *__restrict__ lin_b, float *__restrict__ logits,
                                                                uint8_t *__restrict__ bits, uint8_t *__restrict__ symbols, int m,
-                                                               WordArgs word)
+                                                               WordArgs word, ChainState chain)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t s_tab[];  // tables of the code, if the words are decoded here
     __shared__ __attribute__((aligned(16))) float Q[IPB][9 * C];     // an image's sums, [q*C + c]
@@ -1999,6 +2587,7 @@ __global__ __launch_bounds__(kHeadThreads, 4) void head_kernel(const float *__re
     __shared__ uint8_t sbit[IPB][64 * NB];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int64_t img0 = (int64_t)blockIdx.x * IPB;
+    if (IPB == 1) clear_chain(chain, img0, tid, kHeadThreads);
     // final conv + pool: LPO lanes share the outputs of a k = (channel, tap), four each; a part of KLEN of them
     constexpr int nbp = 64 * NB, LPO = nbp / 4, KLEN = C * 9 * LPO / kHeadThreads, PRE = IPB > 1 ? 0 : NB == 2 ? 12 : KLEN;
     const int ol = tid % LPO, k0 = tid / LPO * KLEN;
@@ -2018,7 +2607,7 @@ __global__ __launch_bounds__(kHeadThreads, 4) void head_kernel(const float *__re
         // lane, i.e. 256 / C lines per load and four loads in flight
         constexpr int LPL = C / 4, LPW = 64 / LPL; // lanes per line, lines per wavefront-wide load
         const int l = lane % LPL, sub = lane / LPL;
-        const f32x4 *p = (const f32x4 *)recs + min(img0 + i, (int64_t)n_img - 1) * sums.lines * LPL + l;
+        const f32x4 *p = (const f32x4 *)recs + min(img0 + i, (int64_t)n_img - 1) * (sums.stride ? sums.stride : sums.lines * LPL) + l;
         auto total = [&](int first, int count, int start, int step, float *dst, int pair_lines = 0) { // pair_lines: lines per row pair, if they are
             f32x4 v;
             if (sums.pairs && pair_lines)
@@ -2141,7 +2730,7 @@ __global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *
                                                                    const float *__restrict__ lin_w,
                                                                    const float *__restrict__ lin_b, float *__restrict__ logits,
                                                                    uint8_t *__restrict__ bits, uint8_t *__restrict__ symbols,
-                                                                   int m)
+                                                                   int m, ChainState chain)
 {
     constexpr int nbp = 64 * NB, lpl = nbp / 4, groups = kHeadThreads / lpl; // lanes per line
     __shared__ __attribute__((aligned(16))) float part[kHeadThreads * 4];
@@ -2149,6 +2738,7 @@ __global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *
     __shared__ uint8_t sbit[nbp];
     const int64_t n = blockIdx.x;
     const int tid = threadIdx.x, o = tid;
+    clear_chain(chain, n, tid, kHeadThreads);
     Linear<NB> linear;
     linear.weights(lin_w, tid);
     *(f32x4 *)&part[tid * 4] = sum_lines((const f32x4 *)partial + n * lines * lpl + tid % lpl, lpl, tid / lpl, groups, lines);
@@ -2179,9 +2769,16 @@ __global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *
     }
 }
 
-__global__ __launch_bounds__(256) void nhwc_to_nchw_kernel(const bf16_t *__restrict__ in, int64_t total, int hw, int C,
-                                                           float *__restrict__ out)
+__global__ __launch_bounds__(256) void clear_chain_kernel(uint32_t *state)
 {
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < kChainStateBytes / 4; i += (size_t)gridDim.x * 256) state[i] = 0u;
+}
+
+__global__ __launch_bounds__(256) void nhwc_to_nchw_kernel(const bf16_t *__restrict__ in, int64_t total, int hw, int C,
+                                                           float *__restrict__ out, ChainState chain)
+{
+    if (blockIdx.x == 0)
+        for (int n = 0; n < chain.n_img; ++n) clear_chain(chain, n, threadIdx.x, 256);
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
         const int c = (int)(i % C);
         const int64_t p = i / C; // n*hw + pixel
@@ -2201,6 +2798,8 @@ static MeanIn sampled_strips(const ConvGeom &g, int cols, int pieces)
     const int rows = (count - 1) * kRows + std::min(kRows, g.h - last * kRows);
     return MeanIn{nullptr, count * g.colblks * pieces, 1.0f / ((float)rows * (float)cols)};
 }
+
+static int chain_most_rows(int C) { return C == 64 ? 16 : 32; }
 
 MeanIn conv_first_samples(const ConvGeom &g, int C) { return sampled_strips(g, g.w, 4 / (C / 32)); }
 
@@ -2427,13 +3026,14 @@ bool head_decodes(const RsParams &p, int64_t N) { return lane_code(p.n, p.two_t)
 
 hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n_img, int n_bits, int nbp, float inv_hw,
                        const float *wft, const float *fbias, const float *lin_w, const float *lin_b, float *logits,
-                       uint8_t *bits, uint8_t *symbols, int m, const WordArgs &word, hipStream_t s)
+                       uint8_t *bits, uint8_t *symbols, int m, const WordArgs &word, const ChainState &chain, hipStream_t s)
 {
     if (n_img <= 0) return hipSuccess;
+    if (chain.words && n_img > kHeadAlone) return hipErrorInvalidValue; // (a workgroup per image clears it)
     const unsigned tables = word.rs.tab ? (unsigned)((word.rs.tab_bytes + 1023) / 1024 * 1024) : 0u;
     auto launch = [&](auto kernel, int per) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)((n_img + per - 1) / per)), dim3(kHeadThreads), tables, s, recs, sums, (int)n_img, n_bits,
-                           inv_hw, wft, fbias, lin_w, lin_b, logits, bits, symbols, m, word);
+                           inv_hw, wft, fbias, lin_w, lin_b, logits, bits, symbols, m, word, chain);
     };
     auto of = [&](auto c) {
         constexpr int CH = decltype(c)::value;
@@ -2473,21 +3073,102 @@ hipError_t launch_conv_final(const uint8_t *in, const ConvGeom &g, int C, int nb
 
 hipError_t launch_linear_pack(const float *partial, int lines, int nbp, int64_t n_img, int n_bits, float inv_hw,
                               const float *fbias, const float *lin_w, const float *lin_b, float *logits,
-                              uint8_t *bits, uint8_t *symbols, int m, hipStream_t s)
+                              uint8_t *bits, uint8_t *symbols, int m, const ChainState &chain, hipStream_t s)
 {
     if (n_img <= 0) return hipSuccess;
     hipLaunchKernelGGL(nbp == 64 ? linear_pack_kernel<1> : linear_pack_kernel<2>, dim3((unsigned)n_img), dim3(kHeadThreads), 0, s, partial,
-                       lines, n_bits, inv_hw, fbias, lin_w, lin_b, logits, bits, symbols, m);
+                       lines, n_bits, inv_hw, fbias, lin_w, lin_b, logits, bits, symbols, m, chain);
     return hipGetLastError();
 }
 
-hipError_t launch_nhwc_to_nchw(const bf16_t *in, int64_t n_img, int h, int w, int C, float *out, hipStream_t s)
+// The rows of an item: few enough that every compute unit of an XCD gets one if there are as many.
+ChainPlan conv_chain_plan(const ConvGeom &g, int C, int blocks, int num_cu)
+{
+    ChainPlan p{};
+    const int cu = std::max(1, num_cu / kChainTeams), colblks = (g.w + kChainCols - 1) / kChainCols;
+    p.chunk = (g.n_img + kChainTeams - 1) / kChainTeams;
+    for (p.rows = kRows;; p.rows *= 2) {
+        p.items = (int64_t)p.chunk * ((g.h + p.rows - 1) / p.rows) * colblks;
+        if (p.rows == chain_most_rows(C) || p.items <= cu) break;
+    }
+    p.fits = blocks >= 2 && (int64_t)g.n_img * blocks <= kChainCounters && g.n_img <= kHeadAlone && p.items * blocks < (1 << 24) &&
+             (int64_t)conv_chain_last_sums(g, C).lines * C * 4 <= (int64_t)g.h * g.w * C * 2;
+    p.one_round = p.items <= cu;
+    return p;
+}
+
+// Images of h x w of which an XCD's compute units can still have one item each.
+int conv_chain_most_images(int h, int w, int C, int num_cu)
+{
+    const int64_t least = (int64_t)((h + chain_most_rows(C) - 1) / chain_most_rows(C)) * ((w + kChainCols - 1) / kChainCols); // items of an image
+    return (int)std::min<int64_t>(kHeadAlone, std::max(1, num_cu / kChainTeams) / least * kChainTeams);
+}
+
+// Whether all blocks in one launch are the faster way, as long as every compute unit of an XCD has one item at most: an item then takes
+// what its rows take, while a launch per block has two round trips to memory, its weights and one strip behind the other.  By
+// estimates of four (C = 32) and eight blocks in microseconds, fitted to 1033 and 210 shapes of 1 .. 512 tiles from 8 x 8 to 256 x 256,
+// standard deviation 2 .. 3 %.  Where they say so the chain is 1.11 times as fast in the mean (up to 1.5), and in the worst case 5 % slower.
+// Single blocks / chain, us: 16 tiles of 32 x 32, 32 channels 28.7 / 26.9, 256 of them 76.9 / 51.5, 16 of 128 x 128 59.2 / 51.3; 7 of 128 x
+// 128, 64 channels 118.0 / 101.6, 16 of 96 x 96 146.5 / 127.9.  Single blocks by the rule: 2 of 128 x 128, 32 channels 29.4 / 38.1; 4 of 128 x
+// 128, 64 channels 83.2 / 101.9 (an XCD has one image or none).  Narrow tiles at 64 channels have the fused pairs (one of 64 x 64 52 / 59).
+bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int num_cu)
+{
+    if (!p.one_round || (C == 64 && g.w <= kTileW)) return false;
+    const double per = (double)(((int64_t)g.n_img * g.strips * g.colblks + num_cu - 1) / num_cu), mpx = 1e-6 * g.n_img * g.h * g.w;
+    const double chunk_mpx = 1e-6 * p.chunk * g.h * g.w;
+    if (C == 32) {
+        const double item_us = p.rows == 4 ? 25.7 : p.rows == 8 ? 29.4 : p.rows == 16 ? 32.2 : 41.3;
+        return item_us + 259.0 * chunk_mpx + 0.05 * p.items < 0.97 * (24.3 + 4.7 * per + 53.9 * mpx);
+    }
+    const double item_us = p.rows == 4 ? 58.9 : p.rows == 8 ? 64.6 : 83.8;
+    return item_us + 998.0 * chunk_mpx < 0.97 * (50.5 + 18.0 * per + 260.0 * mpx);
+}
+
+// The lines are those of the single blocks at two row groups, an image's in the place of its activations.
+LastSums conv_chain_last_sums(const ConvGeom &g, int C)
+{
+    LastSums l = conv_mid_last_sums(g, 32);
+    l.stride = (int64_t)g.h * g.w * C * 2 / 16;
+    return l;
+}
+
+hipError_t launch_conv_chain(const TileSrc &src, const ConvGeom &g, int C, const ChainPlan &p, int blocks, const bf16_t *w_first,
+                             const bf16_t *w_mid, const float *bias, const float *rsum, uint8_t *act0, uint8_t *act1, float *rec0,
+                             float *rec1, float *lines, uint32_t *state, int num_cu, hipStream_t s)
+{
+    if (!p.fits) return hipErrorInvalidValue;
+    ChainArgs a{src, g, blocks, w_first, w_mid, bias, rsum, {act0, act1}, {rec0, rec1}, conv_first_samples(g, C), conv_mid_samples(g, 32),
+                lines, (int64_t)g.h * g.w * C / 2, state, p.chunk, (g.n_img + p.chunk - 1) / p.chunk};
+    const dim3 grid((unsigned)std::min<int64_t>(p.items * kChainTeams, num_cu));
+    auto launch = [&](auto kernel, int waves) { hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, s, a); };
+    if (C == 64) {
+        if (p.rows == 4) launch(conv_chain_kernel<64, 4, 2, 1>, 4);
+        else if (p.rows == 8) launch(conv_chain_kernel<64, 8, 2, 1>, 8);
+        else launch(conv_chain_kernel<64, 8, 2, 2>, 8);
+    } else {
+        if (p.rows == 4) launch(conv_chain_kernel<32, 4, 1, 1>, 4);
+        else if (p.rows == 8) launch(conv_chain_kernel<32, 4, 2, 1>, 4);
+        else if (p.rows == 16) launch(conv_chain_kernel<32, 8, 2, 1>, 8);
+        else launch(conv_chain_kernel<32, 8, 2, 2>, 8);
+    }
+    return hipGetLastError();
+}
+
+static_assert(kChainStateBytes == (size_t)(kChainCountAt + kChainCounters * kChainCount) * 4, "ChainState");
+
+hipError_t launch_clear_chain(uint32_t *state, hipStream_t s)
+{
+    hipLaunchKernelGGL(clear_chain_kernel, dim3(64), dim3(256), 0, s, state);
+    return hipGetLastError();
+}
+
+hipError_t launch_nhwc_to_nchw(const bf16_t *in, int64_t n_img, int h, int w, int C, float *out, const ChainState &chain, hipStream_t s)
 {
     const int64_t total = n_img * h * w * C;
     if (total <= 0) return hipSuccess;
     int64_t blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(nhwc_to_nchw_kernel, dim3((unsigned)blocks), dim3(256), 0, s, in, total, h * w, C, out);
+    hipLaunchKernelGGL(nhwc_to_nchw_kernel, dim3((unsigned)blocks), dim3(256), 0, s, in, total, h * w, C, out, chain);
     return hipGetLastError();
 }
 

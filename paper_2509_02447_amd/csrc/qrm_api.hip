@@ -252,6 +252,16 @@ bool use_fused(const qrm_ctx *c, int cnt, int h, int w, int blocks)
     return wide_tiles_fused(ConvGeom{cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW}, c->num_cu);
 }
 
+// Whether a launch of cnt images of h x w runs all its blocks in one launch.
+ChainPlan chain_plan(const qrm_ctx *c, int cnt, int h, int w, int blocks)
+{
+    if (c->diag_flags & (QRM_DIAG_NO_FUSED_PAIRS | QRM_DIAG_FUSE_ALWAYS | QRM_DIAG_NO_CHAIN)) return ChainPlan{};
+    const ConvGeom g{cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
+    ChainPlan p = conv_chain_plan(g, c->C, blocks, c->num_cu);
+    if (!(c->diag_flags & QRM_DIAG_CHAIN_ALWAYS)) p.fits = p.fits && conv_chain_faster(g, c->C, p, c->num_cu);
+    return p;
+}
+
 int effective_micro_batch(const qrm_ctx *c, int64_t N, int h, int w, size_t act_budget)
 {
     const size_t per_img = (size_t)h * w * c->C * 2;
@@ -308,6 +318,11 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
             L.stats = std::max(L.stats, align_up((size_t)cnt * samples * c->C * 4));
             if (fused) L.seam = std::max(L.seam, align_up(conv_pair_seam_bytes(g, launch_cu(c))));
         }
+    }
+    if (c->has_ext && L.mb > 0) { // the chain's records, of as many images as it takes: a larger batch does not need less
+        const int most = c->diag_flags & QRM_DIAG_CHAIN_ALWAYS ? L.mb : std::min(L.mb, conv_chain_most_images(h, w, c->C, c->num_cu));
+        const ConvGeom g{most, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
+        if (most > 0) L.stats = std::max(L.stats, align_up((size_t)most * conv_mid_samples(g, 32).recs * c->C * 4));
     }
     L.symbols = (want_symbols && c->has_rs) ? align_up((size_t)N * c->rs.n) : 0;
     L.total = 2 * L.act + L.tail + 2 * L.stats + L.seam + L.symbols;
@@ -408,7 +423,7 @@ void time_end(qrm_ctx::Timed *t, hipStream_t s)
 
 namespace qrm {
 
-qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc src, int64_t N, int h, int w, int n_run,
+qrm_status run_extractor(qrm_ctx *c, uint8_t *base, ChainMemory &chain_memory, const WsLayout &L, TileSrc src, int64_t N, int h, int w, int n_run,
                          float *d_logits, uint8_t *d_bits, uint8_t *d_symbols, int m_sym, const WordArgs &word, float *d_act,
                          bool may_time, hipStream_t s)
 {
@@ -454,7 +469,25 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         const bool fused = use_fused(c, cnt, h, w, blocks) && conv_pair_supported(c->C, g);
         auto is_last = [&](int b) { return n_run < 0 && c->collapse && b == c->n_blocks - 1; };
         int b = 1;
-        if (fused) {
+        const ChainPlan chain = chain_plan(c, cnt, h, w, blocks);
+        ChainState to_clear{};  // by the launch behind the chain's
+        if (chain.fits) {
+            if (chain_memory.dirty) {
+                e = launch_clear_chain(chain_memory.words, s);
+                if (e != hipSuccess) return hip_fail(c, e, "clear_chain launch");
+            }
+            chain_memory.dirty = true;
+            to_clear = ChainState{chain_memory.words, blocks, cnt};
+            const bool last = is_last(blocks - 1);
+            cur = (blocks - 1) & 1; // where the last block's activations are; without them, it reads the other one
+            if (last) tail = (float *)buf[cur], last_sums = conv_chain_last_sums(g, c->C), cur ^= 1;
+            qrm_ctx::Timed *t = time_begin(c, may_time, QRM_PROFILE_CHAIN, (first_flops + (blocks - 1) * block_flops) * cnt, s);
+            e = launch_conv_chain(src, g, c->C, chain, blocks, c->d_w_first, c->d_w_mid[0], c->d_bias, c->d_rsum, base + buf_off[0],
+                                  base + buf_off[1], tb[0], tb[1], tail, chain_memory.words, launch_cu(c), s);
+            if (e != hipSuccess) return hip_fail(c, e, "conv_chain launch");
+            time_end(t, s);
+            b = blocks;
+        } else if (fused) {
             qrm_ctx::Timed *t = time_begin(c, may_time, is_last(1) ? QRM_PROFILE_PAIR_LAST : QRM_PROFILE_PAIR_FIRST,
                                            (first_flops + block_flops) * cnt, s);
             tail = tail_of(cur); // (it reads no activations)
@@ -503,8 +536,9 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             b += pair ? 2 : 1;
         }
         if (n_run > 0) {
-            e = launch_nhwc_to_nchw(buf[cur], cnt, h, w, c->C, d_act + n0 * (int64_t)c->C * h * w, s);
+            e = launch_nhwc_to_nchw(buf[cur], cnt, h, w, c->C, d_act + n0 * (int64_t)c->C * h * w, to_clear, s);
             if (e != hipSuccess) return hip_fail(c, e, "nhwc_to_nchw launch");
+            if (to_clear.words) chain_memory.dirty = false;
             continue;
         }
         float *lg = d_logits ? d_logits + n0 * c->n_bits : nullptr;
@@ -513,7 +547,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
         qrm_ctx::Timed *t = time_begin(c, may_time, QRM_PROFILE_HEAD, 0.0, s);
         if (c->collapse) {
             e = launch_head(tail, last_sums, c->C, cnt, c->n_bits, c->nbp, inv_hw, c->d_wft, c->d_bias_final,
-                            c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, word_at(n0), s);
+                            c->d_lin_w, c->d_lin_b, lg, bt, sy, m_sym > 0 ? m_sym : 1, word_at(n0), to_clear, s);
             if (e != hipSuccess) return hip_fail(c, e, "head launch");
         } else {
             const Partition pl = conv_final_partition(cnt, tpi, launch_cu(c), c->C, c->nbp);
@@ -523,9 +557,10 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc s
             if (e != hipSuccess) return hip_fail(c, e, "conv_final launch");
             e = launch_linear_pack(tail, conv_final_lines(g), c->nbp, cnt, c->n_bits, inv_hw,
                                    c->final_relu ? nullptr : c->d_bias_final, c->d_lin_w, c->d_lin_b, lg, bt, sy,
-                                   m_sym > 0 ? m_sym : 1, s);
+                                   m_sym > 0 ? m_sym : 1, to_clear, s);
             if (e != hipSuccess) return hip_fail(c, e, "linear_pack launch");
         }
+        if (to_clear.words) chain_memory.dirty = false;
         time_end(t, s);
     }
     return QRM_OK;
@@ -660,13 +695,15 @@ qrm_status qrm_create(const qrm_extractor_desc *ext, const qrm_rs_desc *rs, int 
         }
 
         const size_t frag_bytes = align_up(frag.size() * 2);
-        const size_t total = frag_bytes + align_up(fl.size() * 4);
-        e = hipMalloc(&c->d_weights, total);
+        const size_t chain_at = frag_bytes + align_up(fl.size() * 4), chain_bytes = kChainStateBytes * (sizeof c->slots / sizeof c->slots[0]);
+        e = hipMalloc(&c->d_weights, chain_at + chain_bytes);
         if (e != hipSuccess) { delete c; return hip_fail(nullptr, e, "hipMalloc(weights)"); }
-        e = hipMemcpy(c->d_weights, frag.data(), frag.size() * 2, hipMemcpyHostToDevice);
+        e = hipMemset((uint8_t *)c->d_weights + chain_at, 0, chain_bytes); // (done before the copies behind it on the same stream are)
+        if (e == hipSuccess) e = hipMemcpy(c->d_weights, frag.data(), frag.size() * 2, hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = hipMemcpy((uint8_t *)c->d_weights + frag_bytes, fl.data(), fl.size() * 4, hipMemcpyHostToDevice);
         if (e != hipSuccess) { (void)hipFree(c->d_weights); delete c; return hip_fail(nullptr, e, "hipMemcpy(weights)"); }
+        for (QrmSlot &sl : c->slots) sl.chain.words = (uint32_t *)((uint8_t *)c->d_weights + chain_at + (&sl - c->slots) * kChainStateBytes);
         const bf16_t *fb = (const bf16_t *)c->d_weights;
         c->d_w_first = fb + frag_off[0];
         for (int b = 1; b < nb; ++b) c->d_w_mid.push_back(fb + frag_off[b]);
@@ -892,7 +929,7 @@ static qrm_status extractor_common(qrm_ctx *c, const uint8_t *d_tiles, int64_t N
     if (st != QRM_OK) return st;
     TileSrc src{d_tiles, nullptr, h, w, {c->mean[0], c->mean[1], c->mean[2]},
                 {c->inv_std[0], c->inv_std[1], c->inv_std[2]}};
-    st = run_extractor(c, (uint8_t *)slot->ws, L, src, N, h, w, n_run, d_logits, d_bits, nullptr, 0, WordArgs{}, d_act, true, s);
+    st = run_extractor(c, (uint8_t *)slot->ws, slot->chain, L, src, N, h, w, n_run, d_logits, d_bits, nullptr, 0, WordArgs{}, d_act, true, s);
     const qrm_status st2 = slot_done(c, slot, s); // also after an error: kernels may have been enqueued
     return st != QRM_OK ? st : st2;
 }
@@ -1032,7 +1069,7 @@ static qrm_status detect_common(qrm_ctx *c, const uint8_t *d_images, int64_t N, 
     // (while the two are timed apart, they are two launches; qrm_detect_host's time line is about the launches it always makes)
     const bool in_head = c->collapse && head_decodes(c->rs, N) && (!c->profile || c->in_host_pipeline);
     const WordArgs word = in_head ? WordArgs{c->rs, d_msg, d_codeword, d_nerr, key} : WordArgs{};
-    st = run_extractor(c, (uint8_t *)slot->ws, L, src, N, tile, tile, -1, d_logits, d_bits, in_head ? nullptr : d_sym, c->rs.m, word,
+    st = run_extractor(c, (uint8_t *)slot->ws, slot->chain, L, src, N, tile, tile, -1, d_logits, d_bits, in_head ? nullptr : d_sym, c->rs.m, word,
                        nullptr, true, s);
     if (st == QRM_OK && !in_head) {
         qrm_ctx::Timed *t = time_begin(c, true, QRM_PROFILE_RS_DECODE, 0.0, s);

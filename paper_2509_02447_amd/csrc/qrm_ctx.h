@@ -9,12 +9,20 @@
 
 constexpr size_t kKeyBytes = 256; // one byte per message symbol
 
+// kChainStateBytes of device memory for conv_chain_kernel's launches (ChainState); dirty: such a launch was enqueued and the one
+// that clears the memory behind it was not, as the call failed in between.
+struct ChainMemory {
+    uint32_t *words = nullptr;
+    bool dirty = false;
+};
+
 // A workspace of the context: the device memory the kernels of one caller stream work in.
 struct QrmSlot {
     bool used = false;
     hipStream_t stream = nullptr; // the stream it serves while `used`
     void *ws = nullptr;
     size_t bytes = 0;
+    ChainMemory chain;            // its own, for as long as the context lives
     hipEvent_t done = nullptr;    // recorded behind the last kernel of every call that used the workspace
     uint64_t last_use = 0;        // value of the context's call counter at that call
 };
@@ -95,7 +103,7 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
 // Runs the extractor over [N] tiles taken from `src` (whole images + origins, or raw tiles) in the workspace at
 // `base` laid out as L.  n_run < 0: full pass -> logits / bits / symbols.  n_run >= 1: stop after that many
 // blocks -> d_act.  may_time: launches may be bracketed by events when the context's profiling is on.
-qrm_status run_extractor(qrm_ctx *c, uint8_t *base, const WsLayout &L, TileSrc src, int64_t N, int h, int w, int n_run,
+qrm_status run_extractor(qrm_ctx *c, uint8_t *base, ChainMemory &chain_memory, const WsLayout &L, TileSrc src, int64_t N, int h, int w, int n_run,
                          float *d_logits, uint8_t *d_bits, uint8_t *d_symbols, int m_sym, const WordArgs &word, float *d_act,
                          bool may_time, hipStream_t s);
 

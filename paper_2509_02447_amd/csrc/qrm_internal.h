@@ -86,6 +86,7 @@ struct MeanIn {
 struct LastSums {
     int lines, first_col, last_col, rows, corners, seam;
     int pairs; // not 0: a piece is one row pair, and there are this many of them
+    int64_t stride; // 16-byte pieces from an image's lines to the next one's; 0: they follow each other
 };
 MeanIn conv_first_samples(const ConvGeom &g, int C); // (rec null)
 MeanIn conv_mid_samples(const ConvGeom &g, int C);
@@ -135,6 +136,34 @@ hipError_t launch_conv_pair(const uint8_t *in, const TileSrc *first, const ConvG
                             const MeanIn &tin, const float *rsum_a, float *tout, bool last, int num_cu,
                             uint8_t *seam, bf16_t *out, hipStream_t s);
 
+// All blocks of a batch of few tiles in one launch.
+struct ChainPlan {
+    bool fits;           // the launch takes such a batch
+    bool one_round;      // with an item per compute unit at most
+    int rows;            // of an item
+    int chunk;           // images that an XCD takes at a time
+    int64_t items;       // of a block of a chunk
+};
+constexpr int kChainCounters = 2048;                                  // images times blocks of a launch
+constexpr size_t kChainStateBytes = (size_t)(9 * 32 + kChainCounters * 32) * 4; // what a launch keeps beside the workspace
+// That memory when the launch behind conv_chain's is to clear it (words null: it is not), and what the launch was about.
+struct ChainState {
+    uint32_t *words;
+    int blocks, n_img;
+};
+ChainPlan conv_chain_plan(const ConvGeom &g, int C, int blocks, int num_cu);
+bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int num_cu);
+int conv_chain_most_images(int h, int w, int C, int num_cu);
+LastSums conv_chain_last_sums(const ConvGeom &g, int C);
+// blocks: of the network, from the first on; block b writes act[b & 1] and sampled channel sums to rec[b & 1] (conv_first_samples(),
+// then those of conv_mid_samples() at 32 channels).  lines not null: the
+// last of them leaves lines of sums there, an image's in the place of its activations (conv_chain_last_sums()).  state: all zeros;
+// the launch behind this one clears it.
+hipError_t launch_conv_chain(const TileSrc &src, const ConvGeom &g, int C, const ChainPlan &p, int blocks, const bf16_t *w_first,
+                             const bf16_t *w_mid, const float *bias, const float *rsum, uint8_t *act0, uint8_t *act1, float *rec0,
+                             float *rec1, float *lines, uint32_t *state, int num_cu, hipStream_t s);
+hipError_t launch_clear_chain(uint32_t *state, hipStream_t s);
+
 struct RsParams {
     int m, q, n, k, two_t, fcr;
     const uint8_t *tab; // device, the table image of the code (rs_table_image), 16-byte aligned
@@ -163,7 +192,7 @@ bool head_decodes(const RsParams &p, int64_t N); // whether the head of N images
 // bits, symbols, decoded words.  wft: final conv weights fp32, [C*9][nbp] (k = c*9 + tap major)
 hipError_t launch_head(const float *recs, const LastSums &sums, int C, int64_t n_img, int n_bits, int nbp, float inv_hw,
                        const float *wft, const float *fbias, const float *lin_w, const float *lin_b, float *logits,
-                       uint8_t *bits, uint8_t *symbols, int m, const WordArgs &word, hipStream_t s);
+                       uint8_t *bits, uint8_t *symbols, int m, const WordArgs &word, const ChainState &chain, hipStream_t s);
 
 // final conv3x3 C -> nbp (n_bits padded to 64s) (+bias, optional ReLU) + sum over pixels -> partial sums
 // partial: f32 [n_img][conv_final_lines()][nbp], each line over a part of the image that does not depend on `part`
@@ -177,10 +206,10 @@ hipError_t launch_conv_final(const uint8_t *in, const ConvGeom &g, int C, int nb
 // fbias: optional bias of the final convolution, added to the pooled value
 hipError_t launch_linear_pack(const float *partial, int lines, int nbp, int64_t n_img, int n_bits, float inv_hw,
                               const float *fbias, const float *lin_w, const float *lin_b, float *logits, uint8_t *bits,
-                              uint8_t *symbols, int m, hipStream_t s);
+                              uint8_t *symbols, int m, const ChainState &chain, hipStream_t s);
 
 // bf16 NHWC -> f32 NCHW (diagnostic)
-hipError_t launch_nhwc_to_nchw(const bf16_t *in, int64_t n_img, int h, int w, int C, float *out, hipStream_t s);
+hipError_t launch_nhwc_to_nchw(const bf16_t *in, int64_t n_img, int h, int w, int C, float *out, const ChainState &chain, hipStream_t s);
 
 // The tables the decoding kernels keep in LDS for this code, laid out once per context (p.tab unused; sets p.tab_bytes; codes
 // with two ways of dealing a word to lanes have an image for either, one behind the other);

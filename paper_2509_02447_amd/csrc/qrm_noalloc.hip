@@ -12,9 +12,12 @@ namespace {
 // The workspace itself.  Each device the library runs on holds its own copy, at its own address, until the
 // process ends.  In host code the array's name is only a handle for hipGetSymbolAddress.
 static __device__ __align__(256) uint8_t scratch[QRM_STATIC_SCRATCH_BYTES];
+// ChainState, zeros between calls; never a part of the workspace, which other kernels write.
+static __device__ __align__(256) uint32_t chain_state[kChainStateBytes / 4];
 
 constexpr int kMaxDevices = 64;
 uint8_t *g_scratch_ptr[kMaxDevices];   // device address of `scratch` on each device, looked up once
+ChainMemory g_chain[kMaxDevices];      // .. and `chain_state`
 hipError_t g_scratch_err[kMaxDevices];
 bool g_scratch_known[kMaxDevices];
 
@@ -30,6 +33,9 @@ hipError_t static_scratch_init(int device)
         void *p = nullptr;
         g_scratch_err[device] = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         g_scratch_ptr[device] = (uint8_t *)p;
+        p = nullptr;
+        if (g_scratch_err[device] == hipSuccess) g_scratch_err[device] = hipGetSymbolAddress(&p, HIP_SYMBOL(chain_state));
+        g_chain[device].words = (uint32_t *)p;
         g_scratch_known[device] = true;
     }
     return g_scratch_err[device];
@@ -46,7 +52,7 @@ extern "C" qrm_status qrm_detect_static(qrm_ctx *c, const uint8_t *d_images, int
     if (st != QRM_OK) return st;
     if (N == 0) return QRM_OK;
     if (c->device < 0 || c->device >= kMaxDevices || !g_scratch_known[c->device] || g_scratch_err[c->device] != hipSuccess ||
-        !g_scratch_ptr[c->device])
+        !g_scratch_ptr[c->device] || !g_chain[c->device].words)
         return fail(c, QRM_E_DEVICE, "the static workspace's address is not known on this device (hipGetSymbolAddress failed at qrm_create)");
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
@@ -73,7 +79,7 @@ extern "C" qrm_status qrm_detect_static(qrm_ctx *c, const uint8_t *d_images, int
                 {c->inv_std[0], c->inv_std[1], c->inv_std[2]}};
     const bool in_head = c->collapse && head_decodes(c->rs, N);
     const WordArgs word = in_head ? WordArgs{c->rs, d_msg, d_codeword, d_nerr, KeyArgs{}} : WordArgs{};
-    st = run_extractor(c, ws, L, src, N, tile, tile, -1, d_logits, d_bits, in_head ? nullptr : d_sym, c->rs.m, word, nullptr, false, s);
+    st = run_extractor(c, ws, g_chain[c->device], L, src, N, tile, tile, -1, d_logits, d_bits, in_head ? nullptr : d_sym, c->rs.m, word, nullptr, false, s);
     if (st != QRM_OK || in_head) return st;
     e = launch_rs_decode(c->rs, d_sym, N, d_msg, d_codeword, d_nerr, KeyArgs{}, s);
     if (e != hipSuccess) return hip_fail(c, e, "rs_decode launch");

@@ -450,6 +450,76 @@ def test_single_block_logits_do_not_depend_on_the_split(qrm, C, nb, h, w, flags,
     check_logits(logits[0][None], oracle.extractor_forward(wts, tile, final_relu=relu)[0], what=f"C={C} {h}x{w} relu {relu}")
 
 
+# (channels, blocks, images, height, width, final ReLU): items of 4, 8, 16 and 32 rows (the last ones partly or wholly below the
+# tile), widths around one and two blocks of 32 and 64 columns, images that no XCD count divides, more of them than an XCD takes at
+# a time, more items than compute units, a tile too small for its lines (single blocks all the same)
+CHAIN_CASES = [(32, 2, 1, 7, 31, 0), (32, 4, 16, 32, 32, 0), (32, 4, 5, 33, 65, 0), (32, 3, 9, 64, 63, 0), (32, 5, 17, 13, 64, 0),
+               (32, 3, 100, 30, 33, 0), (32, 4, 250, 16, 48, 0), (32, 2, 12, 130, 97, 0), (32, 3, 3, 3, 5, 0), (32, 3, 20, 40, 70, 1),
+               (64, 3, 7, 21, 70, 0), (64, 4, 2, 9, 200, 0), (64, 3, 11, 66, 129, 0), (64, 8, 8, 75, 100, 0), (64, 3, 6, 20, 128, 1)]
+
+
+@pytest.mark.parametrize("C,nb,N,h,w,relu", CHAIN_CASES)
+def test_all_blocks_in_one_launch(qrm, C, nb, N, h, w, relu):
+    """All blocks of a batch in one launch against a launch per block: the same bits at 32 channels, in every layer too; at 64 channels
+    the oracle's logits, and the single blocks' within the sum of two tolerances.  Several calls in a row, on workspaces filled with NaN:
+    each finds the state that the one before left."""
+    b = qrm.binding
+    wts = small_weights(C, nb, 24, C + nb + h)
+    tiles = np.random.default_rng(N * h + w).integers(0, 256, size=(N, 3, h, w), dtype=np.uint8)
+    d_tiles, got = dev(tiles), {}
+    for flag in (b.QRM_DIAG_CHAIN_ALWAYS, b.QRM_DIAG_NO_FUSED_PAIRS):
+        ctx = qrm.Context(weights=wts, final_relu=relu)
+        ctx.qrm_diag_set_flags(flag | b.QRM_DIAG_POISON_WORKSPACE)
+        out = []
+        for _ in range(3):
+            d_log = empty((N, 24), torch.float32)
+            ctx.qrm_extractor_forward(d_tiles, N, h, w, d_log, None)
+            out.append(d_log)
+        for n_run in range(1, nb + 1):
+            d_act = empty((N, C, h, w), torch.float32)
+            ctx.qrm_extractor_blocks(d_tiles, N, h, w, n_run, d_act)
+            out.append(d_act)
+        torch.cuda.synchronize()
+        got[flag] = [t.cpu().numpy() for t in out]
+        ctx.close()
+    chain, single = got.values()
+    assert np.array_equal(chain[0], chain[1]) and np.array_equal(chain[0], chain[2])
+    if C == 32:
+        assert all(np.array_equal(a, s) for a, s in zip(chain, single))
+    few = min(N, 3)
+    ref = oracle.extractor_forward(wts, tiles[:few], final_relu=relu)[0]
+    check_logits(chain[0][:few], ref, what=f"chain C={C} {h}x{w}")
+    assert (np.abs(chain[0] - single[0]) <= 2 * 2e-2 * np.maximum(1.0, np.abs(single[0]))).all()
+
+
+def test_all_blocks_in_one_launch_captured(qrm):
+    """The same in a captured graph, on the static workspace: every replay, with eager calls of other sizes between them, gives the
+    bits of a call outside."""
+    cfg = synth.CONFIGS["C1"]
+    ctx = qrm.Context(weights=synth.config_weights(cfg), rs=rs_dict(cfg))
+    N, side = 16, cfg.H
+    d_img, d_off = dev(synth.images(cfg, 0, N)), dev(synth.offsets(cfg, 0, N))
+    bufs = lambda n: (empty((n, cfg.n_bits), torch.float32), empty((n, cfg.n_bits), torch.uint8), empty((n, cfg.k), torch.uint8),
+                      empty((n, cfg.n), torch.uint8), empty((n,), torch.int8))
+    call = lambda n, out: ctx.qrm_detect_static(d_img, n, side, side, d_off, cfg.tile, *out)
+    want, out, other = bufs(N), bufs(N), bufs(5)
+    call(N, want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(N, out)
+    for _ in range(3):
+        for t in out:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, e) for a, e in zip(out, want))
+        call(5, other)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, e[:5]) for a, e in zip(other, want))
+    ctx.close()
+
+
 EXT_CASES = [
     ("C1 shape 32x32 c32 b4 60bit", 32, 4, 60, 32, 32, 16),
     ("C2 shape 64x64 c64 b8 48bit", 64, 8, 48, 64, 64, 6),
