@@ -1288,6 +1288,28 @@ def test_preprocess_of_rows_of_about_eight_bytes(qrm, W_in):
         ctx.close()
 
 
+@pytest.mark.parametrize("N,H_in,W_in,size,tile", [
+    (1, 4, 4, 4, 0), (3, 5, 5, 12, 0), (4, 7, 6, 8, 4), (3, 33, 35, 32, 0), (2, 63, 63, 32, 0), (2, 64, 64, 32, 0), (3, 65, 127, 64, 60),
+    (5, 37, 61, 35, 0), (2, 9, 300, 256, 0)])
+@pytest.mark.parametrize("shift", [0, 1, 2, 4])
+def test_preprocess_loads_of_whole_dwords(qrm, N, H_in, W_in, size, tile, shift):
+    """Taps out of aligned dwords (rows made less than half as long, a buffer at a multiple of four) and out of eight bytes at any
+    address, on both sides of the rule: images that begin at any byte, and a buffer that ends inside a dword, where the last
+    taps of the last row lie."""
+    g = np.random.default_rng(N + H_in * W_in + shift)
+    raw = g.integers(0, 256, size=(N, H_in, W_in, 3), dtype=np.uint8)
+    T = tile or size
+    off = np.full((N, 2), size - T, np.int32) if tile else None     # the last columns and rows
+    room = empty((shift + raw.size,), torch.uint8)
+    room[shift:] = dev(raw).reshape(-1)
+    d_out = empty((N, 3, T, T), torch.uint8)
+    ctx = qrm.Context(rs=rs_dict(synth.CONFIGS["C1"]))
+    ctx.qrm_preprocess(room[shift:], N, H_in, W_in, size, None if off is None else dev(off), tile, d_out)
+    torch.cuda.synchronize()
+    assert np.array_equal(d_out.cpu().numpy(), pre_oracle.preprocess(raw, size, off, tile))
+    ctx.close()
+
+
 @pytest.mark.parametrize("shift_in,shift_out", [(5, 0), (0, 3), (13, 1)])
 def test_preprocess_buffers_at_odd_addresses(qrm, shift_in, shift_out):
     """Raw and output buffers that start at any byte: word loads and dword stores must not assume more."""
