@@ -41,7 +41,7 @@ constexpr int group_tmax(int two_t) { return two_t > 8 ? 8 : two_t > 4 ? 4 : 2; 
 // the locator at its first position is all there is (2^20 words of RS(15,9) 135 us, 153 by way of the tables).
 constexpr int syn_bytes(int spl, int tmax) { return spl == 1 ? 0 : 2 * tmax; }
 constexpr int chien_bytes(int spl) { return spl == 1 ? 0 : spl < 4 ? 4 : spl; }
-constexpr int64_t kDecodeBlocks = 2048; // lane kernel: eight workgroups per compute unit; each reads the tables once and takes every 2048th run of words
+constexpr int64_t kDecodeThreads = 2048 * 256; // lane kernel: 32 wavefronts per compute unit; a workgroup reads the tables once and takes the runs of words a grid apart
 // Group kernel: three workgroups of eight wavefronts to a compute unit (up to 51 KiB of tables each), every 768th run of words.
 // 20000 words of RS(255,239) 20.7 us, with two workgroups of the same size 22.
 constexpr int kGroupThreads = 512;
@@ -74,22 +74,41 @@ __device__ __forceinline__ void load_tables(uint8_t *dst, const RsParams &p)
 // 32-bit look-up (all four in it), so the whole syndrome computation is n look-ups and n XORs; the errors follow in closed
 // form (lane_errors).
 // Bound by vector instructions and LDS look-ups, about 200 and 40 per word, close to what the bytes alone take.
-// 2^20 words of RS(12,8) over GF(256), 34.6 MB: 12.5 us a pass = 2.8 TB/s (a
-// recursion per lane with byte-wise loads: 44.5 us); what is left is mostly the launch and the first touch of the tables.
+// 2^20 words of RS(12,8) over GF(256), 34.6 MB: 12.5 -> 11.8 us a pass = 2.9 TB/s (a recursion per lane with byte-wise loads: 44.5 us), of
+// which 5 are the launch, the tables and the first words, which are on their way together: every further 2^20 take 6.6 (5.2 TB/s).
+// A workgroup's next words are fetched while it decodes: 2^20 of RS(15,11) 21.9 -> 20.0 us, of RS(13,9) 22.0 -> 20.8.
 // WORDS: words and messages are whole aligned dwords, read and written straight from global memory; otherwise a
-// workgroup's 256 words pass through LDS so that global memory is still accessed in dwords.
+// workgroup's words pass through LDS so that global memory is still accessed in dwords.
 // ------------------------------------------------------------------------------------------------
-template <int N4, bool WORDS>
-__global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const uint8_t *__restrict__ sym, int64_t N,
+template <int N4, bool WORDS, int TH>
+__global__ __launch_bounds__(TH) void rs_decode_lane_kernel(RsParams p, const uint8_t *__restrict__ sym, int64_t N,
                                                              uint8_t *__restrict__ msg, uint8_t *__restrict__ cw,
                                                              int8_t *__restrict__ nerr, KeyArgs key)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t s_tab[];
-    __shared__ __attribute__((aligned(16))) uint8_t s_word[WORDS ? 16 : 256 * 16 + 16];
-    __shared__ __attribute__((aligned(16))) uint8_t s_msg[WORDS ? 16 : 256 * 16];
+    __shared__ __attribute__((aligned(16))) uint8_t s_word[WORDS ? 16 : TH * 16 + 16];
+    __shared__ __attribute__((aligned(16))) uint8_t s_msg[WORDS ? 16 : TH * 16];
     const int tid = threadIdx.x;
     const int n = p.n, k = p.k, ord = p.q - 1, fcr = p.fcr;
-    load_tables<256>(s_tab, p);
+    const int64_t blocks = (N + TH - 1) / TH;
+    const bool in_dwords = WORDS || ((uintptr_t)sym & 3) == 0; // TH n is a multiple of four: every workgroup's run is aligned as the first
+    uint32_t in[N4]; // run b's words: the lane's own (WORDS) or dwords of all of them
+    auto fetch = [&](int64_t b) {
+        const int64_t w0 = b * TH;
+        if (WORDS) {
+            const uint32_t *src = (const uint32_t *)(sym + min(w0 + tid, N - 1) * n);
+#pragma unroll
+            for (int j = 0; j < N4; ++j) in[j] = src[j];
+        } else if (in_dwords) {
+            const uint32_t *src = (const uint32_t *)(sym + w0 * n);
+            const int dwords = (int)min((int64_t)TH, N - w0) * n >> 2;
+#pragma unroll
+            for (int j = 0; j < N4; ++j)
+                if (tid + TH * j < dwords) in[j] = src[tid + TH * j];
+        }
+    };
+    fetch(blockIdx.x); // (there is one for every workgroup)
+    load_tables<TH>(s_tab, p);
     const Gf gf{s_tab, (const uint16_t *)(s_tab + kLogAt)};
     const uint8_t *quad = s_tab + kQuadAt;
     const uint32_t *syn = (const uint32_t *)(s_tab + kCodeAt);
@@ -104,25 +123,25 @@ __global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const u
     }
     __syncthreads();
 
-    const int64_t blocks = (N + 255) / 256;
     for (int64_t b = blockIdx.x; b < blocks; b += gridDim.x) {
-        const int64_t w0 = b * 256;
-        const int cnt = (int)min((int64_t)256, N - w0);
+        const int64_t w0 = b * TH;
+        const int cnt = (int)min((int64_t)TH, N - w0);
         const bool mine = tid < cnt;
         const int64_t w = w0 + (mine ? tid : 0);
         uint32_t r[N4];
         if (WORDS) {
-            const uint32_t *src = (const uint32_t *)(sym + w * n);
 #pragma unroll
-            for (int j = 0; j < N4; ++j) r[j] = src[j];
+            for (int j = 0; j < N4; ++j) r[j] = in[j];
         } else {
             const uint8_t *src = sym + w0 * n;
             const int bytes = cnt * n;
-            if (((uintptr_t)sym & 3) == 0) { // 256 n is a multiple of four: every workgroup's run is aligned as the first
-                for (int i = tid; i < bytes >> 2; i += 256) ((uint32_t *)s_word)[i] = ((const uint32_t *)src)[i];
+            if (in_dwords) {
+#pragma unroll
+                for (int j = 0; j < N4; ++j)
+                    if (tid + TH * j < bytes >> 2) ((uint32_t *)s_word)[tid + TH * j] = in[j];
                 if (tid < (bytes & 3)) s_word[(bytes & ~3) + tid] = src[(bytes & ~3) + tid];
             } else {
-                for (int i = tid; i < bytes; i += 256) s_word[i] = src[i];
+                for (int i = tid; i < bytes; i += TH) s_word[i] = src[i];
             }
             __syncthreads();
             const int at = tid * n;
@@ -137,6 +156,8 @@ __global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const u
         }
 #pragma unroll
         for (int j = 0; j < N4; ++j) r[j] &= in_word[j];
+
+        if (b + gridDim.x < blocks) fetch(b + gridDim.x);
 
         // ---- syndromes, a byte each
         uint32_t S = 0;
@@ -180,10 +201,10 @@ __global__ __launch_bounds__(256) void rs_decode_lane_kernel(RsParams p, const u
             __syncthreads();
             auto copy_out = [&](uint8_t *dst, const uint8_t *from, int bytes) {
                 if (((uintptr_t)dst & 3) == 0) {
-                    for (int i = tid; i < bytes >> 2; i += 256) ((uint32_t *)dst)[i] = ((const uint32_t *)from)[i];
+                    for (int i = tid; i < bytes >> 2; i += TH) ((uint32_t *)dst)[i] = ((const uint32_t *)from)[i];
                     if (tid < (bytes & 3)) dst[(bytes & ~3) + tid] = from[(bytes & ~3) + tid];
                 } else {
-                    for (int i = tid; i < bytes; i += 256) dst[i] = from[i];
+                    for (int i = tid; i < bytes; i += TH) dst[i] = from[i];
                 }
             };
             if (cw) copy_out(cw + w0 * n, s_word, cnt * n);
@@ -565,15 +586,16 @@ template <int N4>
 hipError_t launch_lane(const RsParams &p, const uint8_t *sym, int64_t N, uint8_t *msg, uint8_t *cw, int8_t *nerr,
                        const KeyArgs &key, hipStream_t s)
 {
-    int64_t blocks = (N + 255) / 256;
-    if (blocks > kDecodeBlocks) blocks = kDecodeBlocks;
     const bool words = p.n % 4 == 0 && p.k % 4 == 0 && (((uintptr_t)sym | (uintptr_t)msg | (uintptr_t)cw) & 3) == 0;
-    if (words)
-        hipLaunchKernelGGL((rs_decode_lane_kernel<N4, true>), dim3((unsigned)blocks), dim3(256), (unsigned)p.tab_bytes, s, p, sym,
-                           N, msg, cw, nerr, key);
-    else
-        hipLaunchKernelGGL((rs_decode_lane_kernel<N4, false>), dim3((unsigned)blocks), dim3(256), (unsigned)p.tab_bytes, s, p, sym,
-                           N, msg, cw, nerr, key);
+    auto launch = [&](auto kernel, int threads) {
+        const int64_t blocks = std::min((N + threads - 1) / threads, kDecodeThreads / threads);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), (unsigned)p.tab_bytes, s, p, sym, N, msg, cw, nerr, key);
+    };
+    // Whole dwords and two full runs a workgroup: half as many copies of the tables.  2^20 words of RS(12,8), 256 / 512 / 1024 threads 12.8 / 12.2 /
+    // 12.7 us, 2^22 33.5 / 31.9 / 32.8; through LDS, 2^20 of RS(15,11) 19.6 / 22.3 / 24.1.
+    if (words && N >= 2 * kDecodeThreads) launch(rs_decode_lane_kernel<N4, true, 512>, 512);
+    else if (words) launch(rs_decode_lane_kernel<N4, true, 256>, 256);
+    else launch(rs_decode_lane_kernel<N4, false, 256>, 256);
     return hipGetLastError();
 }
 
