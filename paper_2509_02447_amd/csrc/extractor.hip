@@ -128,19 +128,6 @@ __device__ __forceinline__ uint32_t pack_bf16_relu(float a, float b, uint32_t di
     return __builtin_bit_cast(uint32_t, q);
 }
 
-// lane (px, half) holds 16 consecutive channels [half*16, half*16+16) of the 32-channel block
-__device__ __forceinline__ void store_tile_bf16(bf16_t *dst, const f32x16 &acc, uint32_t dither, bool relu)
-{
-    u32x4 lo, hi;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        lo[v] = pack_bf16_relu(acc[2 * v], acc[2 * v + 1], dither, relu);
-        hi[v] = pack_bf16_relu(acc[8 + 2 * v], acc[8 + 2 * v + 1], dither, relu);
-    }
-    *(u32x4 *)dst = lo;
-    *(u32x4 *)(dst + 8) = hi;
-}
-
 // ------------------------------------------------------------------------------------------------
 // conv3x3 C -> C on bf16 NHWC activations.  One strip = kRows x kTileW output pixels.
 // ------------------------------------------------------------------------------------------------
@@ -157,6 +144,8 @@ struct MidCfg {
 };
 
 typedef const __attribute__((address_space(1))) void *gptr_t;
+typedef const __attribute__((address_space(1))) uint32_t *global_word_t;
+typedef const __attribute__((address_space(4))) int32_t *scalar_ints_t; // what no launch writes while it runs, loaded into scalar registers
 typedef __attribute__((address_space(3))) void *lptr_t;
 typedef uint32_t lrow_t; // LDS byte address
 __device__ __forceinline__ lrow_t lds_address(const void *p)
@@ -1748,6 +1737,15 @@ __global__ __launch_bounds__(128) void conv_seam_kernel(const uint8_t *__restric
 // bf16 residual, i.e. to about 16 bits.  K = 9 taps x 4 channels = 36, padded to 48 = three 16-wide k chunks;
 // a lane's 8 k values of a chunk are two taps, i.e. two 8-byte LDS reads.  A wavefront computes one 32-channel
 // output block for one (C = 32) or two (C = 64) rows of the strip.
+//
+// Bound by the bf16 output it writes and by vector instructions.  The raw pixels of the next strip are fetched while this one is
+// multiplied, as the aligned dwords that hold a lane's four pixels of a colour, and go into the other of two windows, so that
+// a strip has one barrier, which waits for LDS only; columns of 32 that lie outside the tile are left out; the output passes
+// LDS, so that four lanes write 64 bytes of a pixel together.  Against single bytes, asked for and waited for between two barriers
+// that also wait for the strip's stores: 2000 tiles of 32 x 32, 32 channels 56 -> 36 us (3.7 TB/s written), 500 of 100 x 100
+// 109 -> 78 (4.1), 100 of 75 x 100, 64 channels 28.8 -> 22.6.  The two halves of a wavefront's pixels swapped between rows of 16
+// lanes instead, each store 64 bytes of 16 pixels from lanes 16 apart: 500 of 100 x 100 171 us where two 16-byte pieces 32 bytes
+// apart took 117.
 // ------------------------------------------------------------------------------------------------
 constexpr int kFirstPix = (kRows + 2) * kHaloW;
 
@@ -1757,7 +1755,8 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
                                                          int out_recs, int per, bf16_t *__restrict__ out)
 {
     constexpr int NCB = C / 32;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[kFirstPix * 4];
+    __shared__ __attribute__((aligned(16))) uint16_t lds[2][kFirstPix * 4]; // strips in turn
+    __shared__ u32x4 s_out[4][32 * 4]; // a wavefront's 32 pixels x 32 channels on their way out
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int px = lane & 31, half = lane >> 5;
@@ -1790,40 +1789,89 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
         }
 
     const int plane = src.H * src.W;
+    const uint32_t img_bytes = (uint32_t)((size_t)g.h * g.w * C * 2);
 
     const int tpi = g.strips * g.colblks;
     const int total = g.n_img * tpi;
     const int t_begin = blockIdx.x * per;
     const int t_end = min(total, t_begin + per);
+    if (t_begin >= t_end) return;
 
-    for (int t = t_begin; t < t_end; ++t) {
-        const int colblk = t % g.colblks;
-        const int strip = (t / g.colblks) % g.strips;
-        const int n = t / tpi;
-        const int y0 = strip * kRows, x0 = colblk * kTileW;
-        int oy = 0, ox = 0;
-        if (src.off) {
-            oy = clampi(src.off[2 * n], 0, src.H - g.h);
-            ox = clampi(src.off[2 * n + 1], 0, src.W - g.w);
-        }
-        const uint8_t *tile0 = src.img + (int64_t)n * 3 * plane + (int64_t)oy * src.W + ox;
-
-        __syncthreads(); // previous strip fully consumed
-#pragma unroll
-        for (int it = 0; it < (kFirstPix * 3 + 255) / 256; ++it) {
-            const int idx = tid + it * 256;
-            if (idx < kFirstPix * 3) {
-                const int c = idx / kFirstPix, p = idx - c * kFirstPix;
-                const int row = p / kHaloW, col = p - row * kHaloW;
-                const int ty = y0 - 1 + row, tx = x0 - 1 + col;
-                const bool inside = ty >= 0 && ty < g.h && tx >= 0 && tx < g.w;
-                float v = 0.f;
-                if (inside) v = (float)tile0[(int64_t)c * plane + (int64_t)ty * src.W + tx];
-                lds[p * 4 + c] = __builtin_bit_cast(uint16_t, (bf16_t)v);
-                if (c == 0) lds[p * 4 + 3] = inside ? (uint16_t)0x3F80 : (uint16_t)0;
+    // Four pixels of a row of the window are a lane's: 17 times 6, half of the wavefronts for one strip, the others for the next
+    constexpr int GROUPS = (kHaloW + 3) / 4;
+    static_assert(GROUPS * (kRows + 2) <= 128, "two wavefronts");
+    const int unit = tid & 127, row_of = min(unit / GROUPS, kRows + 1), group = unit % GROUPS;
+    struct Strip {
+        int n, strip, colblk;
+    };
+    auto advance = [&](Strip &q) {
+        if (++q.colblk == g.colblks) {
+            q.colblk = 0;
+            if (++q.strip == g.strips) {
+                q.strip = 0;
+                ++q.n;
             }
         }
-        __syncthreads();
+    };
+    uint32_t word[3][2];
+    uint32_t shift[3];
+    // The aligned dwords that hold the first and the last of them that lies in the tile (neither leaves the page of such a byte)
+    auto fetch = [&](const Strip &q) {
+        int oy = 0, ox = 0;
+        if (src.off) {
+            const scalar_ints_t off = (scalar_ints_t)(uintptr_t)src.off + 2 * q.n;
+            oy = clampi(off[0], 0, src.H - g.h);
+            ox = clampi(off[1], 0, src.W - g.w);
+        }
+        const uint8_t *tile0 = src.img + (int64_t)q.n * 3 * plane + (int64_t)oy * src.W + ox;
+        const int x = q.colblk * kTileW - 1 + 4 * group, first = clampi(x, 0, g.w - 1), last = clampi(x + 3, 0, g.w - 1);
+        const uint8_t *row = tile0 + (int64_t)clampi(q.strip * kRows - 1 + row_of, 0, g.h - 1) * src.W;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const uintptr_t at = (uintptr_t)(row + (int64_t)c * plane);
+            word[c][0] = *(global_word_t)((at + first) & ~(uintptr_t)3);
+            word[c][1] = *(global_word_t)((at + last) & ~(uintptr_t)3);
+            shift[c] = (uint32_t)at + (uint32_t)x;
+        }
+    };
+    // .. -> pixels in `window`
+    auto stage = [&](const Strip &q, uint16_t *window) {
+        const int x = q.colblk * kTileW - 1 + 4 * group;
+        const bool row_inside = (uint32_t)(q.strip * kRows - 1 + row_of) < (uint32_t)g.h;
+        uint32_t byte[3]; // of the four
+#pragma unroll
+        for (int c = 0; c < 3; ++c) byte[c] = __builtin_amdgcn_alignbyte(word[c][1], word[c][0], shift[c]);
+        u32x4 to[2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool inside = row_inside && (uint32_t)(x + i) < (uint32_t)g.w;
+            uint32_t f[3]; // exact in bf16, the high half
+#pragma unroll
+            for (int c = 0; c < 3; ++c) f[c] = __builtin_bit_cast(uint32_t, (float)(byte[c] >> (8 * i) & 0xffu));
+            to[i / 2][i % 2 * 2] = inside ? __builtin_amdgcn_perm(f[1], f[0], 0x07060302u) : 0u;
+            to[i / 2][i % 2 * 2 + 1] = inside ? f[2] >> 16 | 0x3F800000u : 0u;
+        }
+        if (unit < GROUPS * (kRows + 2)) {
+            u32x4 *at = (u32x4 *)(window + (row_of * kHaloW + 4 * group) * 4);
+            at[0] = to[0];
+            if (group < GROUPS - 1) at[1] = to[1]; // (a row has two columns more than whole groups)
+        }
+    };
+    static_assert(kHaloW % 4 == 2, "the last group is two pixels");
+    const int turn = wave / 2;
+    Strip q{t_begin / tpi, t_begin / g.colblks % g.strips, t_begin % g.colblks}, ahead = q;
+    if (turn == 0) fetch(q);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0); // the weights are there: a wait for them in the loop would be one for all that is under way
+
+    for (int t = t_begin; t < t_end; ++t) {
+        const int colblk = q.colblk, strip = q.strip, n = q.n;
+        const int y0 = strip * kRows, x0 = colblk * kTileW;
+        const int parity = (t - t_begin) & 1;
+        uint16_t *window = lds[parity];
+        if (turn == parity) stage(q, window);
+        if (t + 1 < t_end) advance(ahead);
+        if (turn != parity && t + 1 < t_end) fetch(ahead); // on their way while this strip is multiplied
+        lds_barrier(); // (one a strip: whoever writes the window again has passed the next strip's, behind the last reads of this one)
 
         const bool sample = tout && (strip & 7) == sampled_strip(g.strips);
         float tv[16] = {}; // sampled strip: channel sums over this wavefront's rows, this lane's columns
@@ -1834,8 +1882,9 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
             if (y >= g.h) continue; // same for the whole wavefront
 #pragma unroll
             for (int xb = 0; xb < 2; ++xb) {
+                if (x0 + xb * 32 >= g.w) continue; // (likewise)
                 const int x = x0 + xb * 32 + px;
-                const uint8_t *lp = (const uint8_t *)lds + (row * kHaloW + xb * 32 + px) * 8;
+                const uint8_t *lp = (const uint8_t *)window + (row * kHaloW + xb * 32 + px) * 8;
                 bf16x8 bfrag[3];
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
@@ -1852,8 +1901,22 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
                 f32x16 acc;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[v] = sum[v] + bias16[v];
-                if (x < g.w)
-                    store_tile_bf16(out + (((int64_t)n * g.h + y) * g.w + x) * C + cb * 32 + half * 16, acc, dither16(x, y), true);
+                const uint32_t dth = dither16(x, y);
+                u32x4 *piece = s_out[wave] + px * 4;
+#pragma unroll
+                for (int hq = 0; hq < 2; ++hq) {
+                    u32x4 pk;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) pk[e] = pack_bf16_relu(acc[8 * hq + 2 * e], acc[8 * hq + 2 * e + 1], dth, true);
+                    piece[(half * 2 + hq) ^ (px >> 2 & 3)] = pk;
+                }
+                uint8_t *img = (uint8_t *)out + (size_t)n * img_bytes;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int p = i * 16 + (lane >> 2), xs = x0 + xb * 32 + p;
+                    const u32x4 pk = s_out[wave][p * 4 + ((lane & 3) ^ (p >> 2 & 3))];
+                    store16(img, img_bytes, xs < g.w ? (uint32_t)(((y * g.w + xs) * C + cb * 32 + (lane & 3) * 8) * 2) : kOutside, 0, pk);
+                }
                 if (sample) {
 #pragma unroll
                     for (int v = 0; v < 16; ++v) tv[v] += x < g.w ? fmaxf(acc[v], 0.f) : 0.f;
@@ -1870,6 +1933,7 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
                 for (int q = 0; q < 4; ++q) *(f32x4 *)(rec + 4 * q) = (f32x4){tv[4 * q], tv[4 * q + 1], tv[4 * q + 2], tv[4 * q + 3]};
             }
         }
+        q = ahead;
     }
 }
 

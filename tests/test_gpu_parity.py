@@ -312,6 +312,53 @@ def test_extractor_blocks_match_oracle_layer_by_layer(qrm, C, nb, h, w):
     ctx.close()
 
 
+@pytest.mark.parametrize("C,h,w", [(32, 1, 1), (64, 2, 2), (32, 5, 3), (32, 6, 4), (64, 4, 5), (32, 7, 61), (32, 3, 62), (64, 9, 63), (32, 4, 64),
+                                   (64, 5, 65), (32, 8, 66), (32, 10, 67), (64, 3, 68), (32, 9, 129)])
+def test_first_block_reads_tiles_at_any_address(qrm, C, h, w):
+    """The first block alone, on tiles that begin at every place in a dword and whose rows and colours do, and with the bytes around
+    them changed: activations against the oracle, equal for all of them."""
+    wts = small_weights(C, 2, 16, C + h + w)
+    rng = np.random.default_rng(h * w + C)
+    tiles = rng.integers(0, 256, size=(5, 3, h, w), dtype=np.uint8)
+    acts = [oracle.extractor_forward(wts, tiles[i:i + 1], want_acts=True)[2][0] for i in range(5)]
+    ctx = qrm.Context(weights=wts)
+    got = []
+    for shift in range(4):
+        buf = torch.full((tiles.size + 8,), 85 * (shift % 2), dtype=torch.uint8, device="cuda")
+        view = buf[shift:shift + tiles.size].view(5, 3, h, w)
+        view.copy_(dev(tiles))
+        d_act = empty((5, C, h, w), torch.float32)
+        ctx.qrm_extractor_blocks(view, 5, h, w, 1, d_act)
+        torch.cuda.synchronize()
+        got.append(d_act.cpu().numpy())
+    ctx.close()
+    for g in got[1:]:
+        assert np.array_equal(g, got[0])
+    for i in range(5):
+        err = np.abs(got[0][i] - acts[i]) / np.maximum(1.0, np.abs(acts[i]))
+        assert err.max() <= 2.0 ** -7, (i, float(err.max()))  # one dithered rounding to bf16 (a step of 2^-8), weights to 16 bits
+
+
+@pytest.mark.parametrize("H,W,tile", [(37, 53, 21), (64, 70, 64), (33, 34, 33)])
+def test_first_block_reads_tiles_inside_images(qrm, H, W, tile):
+    """The single blocks on tiles at random origins of images: the same as on the tiles cut out."""
+    wts = small_weights(32, 3, 60, H)
+    rng = np.random.default_rng(H * W)
+    imgs = rng.integers(0, 256, size=(9, 3, H, W), dtype=np.uint8)
+    off = np.stack([rng.integers(0, H - tile + 1, 9), rng.integers(0, W - tile + 1, 9)], axis=1).astype(np.int32)
+    off[0], off[1] = (0, 0), (H - tile, W - tile)
+    tiles = np.stack([imgs[i][:, y:y + tile, x:x + tile] for i, (y, x) in enumerate(off)])
+    ctx = qrm.Context(weights=wts, rs=dict(m=4, prim_poly=0x13, n=15, k=11, fcr=1))
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_NO_CHAIN)
+    d_cut, d_in = empty((9, 60), torch.float32), empty((9, 60), torch.float32)
+    d_msg, d_cw, d_ne = empty((9, 11), torch.uint8), empty((9, 15), torch.uint8), empty((9,), torch.int8)
+    ctx.qrm_extractor_forward(dev(tiles), 9, tile, tile, d_cut, None)
+    ctx.qrm_detect(dev(imgs), 9, H, W, dev(off), tile, d_in, None, d_msg, d_cw, d_ne)
+    torch.cuda.synchronize()
+    assert torch.equal(d_cut, d_in)
+    ctx.close()
+
+
 # heights around the strips whose channel sums are sampled (strips of four rows, one in eight; row pairs in the fused
 # schedule): one strip, an odd number of row pairs in the sampled strip, a second sampled strip begun
 SAMPLE_CASES = [(64, 4, 1, 20, 0), (64, 4, 5, 64, 0), (64, 5, 13, 33, 0), (64, 4, 46, 64, 0), (64, 4, 13, 70, 0),
