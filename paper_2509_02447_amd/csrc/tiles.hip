@@ -4,6 +4,7 @@
 // dword from two aligned input dwords (funnel shift by the source misalignment), otherwise bytes.
 // Also here: variance-based tile selection (further down).
 #include <algorithm>
+#include <type_traits>
 #include "qrm_internal.h"
 
 namespace qrm {
@@ -114,7 +115,10 @@ __global__ __launch_bounds__(kGatherThreads) void gather_host_tiles_kernel(const
 // forms the exact integers n S2 - S1^2, and the score in float64 in a fixed order with no fused
 // multiply-add; a workgroup reduction picks the first maximum.
 // A launch of fewer images than compute units waits for the round trips of its only wave of workgroups: 1024 threads an image
-// instead of 256 where that is the faster way (select_threads).
+// instead of 256 where that is the faster way (select_threads).  Its length is then a chain: quotients by small products instead
+// of integer divisions, a window's six look-ups at a time and the best window by DPP moves instead of shuffles took one image of
+// 256 x 256, windows of 64 at strides of 32, from 5.9 to 4.7 us, 16 of 384 x 384 at 16 from 14.6 to 12.9, 600 of 256 x 256 from
+// 20.5 to 19.7.
 // ------------------------------------------------------------------------------------------------
 constexpr int kMaxCells = 1024; // cells per channel a workgroup can hold
 
@@ -122,8 +126,15 @@ struct SelectArgs {
     int H, W, win, stride;
     int nH, nW;     // windows
     int nCy, nCx;   // cells that lie in some window
+    int tx, rows;   // column chunks that THREADS lanes walk down at a time, rows of a run
+    float inv_tx, inv_stride, inv_nW;
     double w[3];    // channel weights
 };
+
+// a / d for 0 <= a < 2^22 from the rounded 1 / d: a + 0.5 is at least 0.5 / d away from the next whole quotient, the two roundings
+// change it by less than a 2^-23 / d.  (An integer division is some forty instructions, and this kernel has one after the other
+// before its first load.)
+__device__ __forceinline__ int small_quotient(int a, float inv_d) { return (int)(((float)a + 0.5f) * inv_d); }
 
 template <int VEC, int THREADS>
 __global__ __launch_bounds__(THREADS) void tile_variance_kernel(const uint8_t *__restrict__ img, SelectArgs a,
@@ -143,22 +154,20 @@ __global__ __launch_bounds__(THREADS) void tile_variance_kernel(const uint8_t *_
     // ---- phase 1: cell sums
     const int Hc = a.nCy * a.stride, Wc = a.nCx * a.stride; // the part of the image that windows cover
     const int ncx = Wc / VEC;                                // column chunks per row
-    const int TX = ncx < THREADS ? ncx : THREADS;
-    const int n_rg = THREADS / TX;                           // row groups
-    const int R = (Hc + n_rg - 1) / n_rg;                    // rows per group
-    const int rg = tid / TX;
+    const int TX = a.tx, R = a.rows;
+    const int rg = small_quotient(tid, a.inv_tx);            // row group
     const int64_t plane = (int64_t)a.H * a.W;
     const uint8_t *base = img + n * 3 * plane;
     // colours a lane has on their way together: all of them where few bytes are (bytes instead of 16 at a time, few images)
     constexpr int TOGETHER = VEC == 1 || THREADS > 256 ? 3 : 1;
-    if (rg < n_rg) {
+    if (rg * R < Hc && (rg + 1) * TX <= THREADS) { // (a rest of the lanes makes no group)
         const int r0 = rg * R, r1 = min(Hc, r0 + R);
         for (int c0 = 0; c0 < 3; c0 += TOGETHER)
             for (int cx = tid - rg * TX; cx < ncx; cx += TX) {
-                const int cellx = cx * VEC / a.stride;
+                const int cellx = small_quotient(cx * VEC, a.inv_stride);
                 const uint8_t *col = base + c0 * plane + cx * VEC;
                 for (int seg = r0; seg < r1;) { // the run's rows, one cell row at a time
-                    const int cy = seg / a.stride;
+                    const int cy = small_quotient(seg, a.inv_stride);
                     const int seg_end = min(r1, (cy + 1) * a.stride);
                     uint32_t s1[TOGETHER] = {}, s2[TOGETHER] = {};
 #pragma unroll 4
@@ -199,18 +208,23 @@ __global__ __launch_bounds__(THREADS) void tile_variance_kernel(const uint8_t *_
     double best = -1.0;                               // scores are >= 0
     int best_idx = 0x7fffffff;
     for (int wi = tid; wi < a.nH * a.nW; wi += THREADS) {
-        const int wy = wi / a.nW, wx = wi - wy * a.nW;
+        const int wy = small_quotient(wi, a.inv_nW), wx = wi - wy * a.nW;
+        unsigned long long S1[3] = {}, S2[3] = {};
+        for (int dy = 0; dy < k; ++dy)
+#pragma unroll 2
+            for (int dx = 0; dx < k; ++dx) {
+                const int cell = (wy + dy) * a.nCx + wx + dx;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) { // (six look-ups at a time)
+                    S1[c] += s_sum[c][cell];
+                    S2[c] += s_sq[c][cell];
+                }
+            }
         double score = 0.0;
+#pragma unroll
         for (int c = 0; c < 3; ++c) {
 #pragma clang fp contract(off) // each product and each sum is rounded on its own: no fused multiply-add
-            unsigned long long S1 = 0, S2 = 0;
-            for (int dy = 0; dy < k; ++dy)
-#pragma unroll 2
-                for (int dx = 0; dx < k; ++dx) {
-                    S1 += s_sum[c][(wy + dy) * a.nCx + wx + dx];
-                    S2 += s_sq[c][(wy + dy) * a.nCx + wx + dx];
-                }
-            const unsigned long long v = (unsigned long long)(a.win * a.win) * S2 - S1 * S1; // exact, < 2^53
+            const unsigned long long v = (unsigned long long)(a.win * a.win) * S2[c] - S1[c] * S1[c]; // exact, < 2^53
             const double term = (double)v * a.w[c];
             score = c == 0 ? term : score + term;
         }
@@ -226,21 +240,31 @@ __global__ __launch_bounds__(THREADS) void tile_variance_kernel(const uint8_t *_
             best_idx = oi;
         }
     };
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const double o = __shfl_down(best, off);
-        const int oi = __shfl_down(best_idx, off);
-        take(o, oi);
-    }
+    // The wavefront's best ends up in its last lane: a lane may meet a candidate twice
+    auto step = [&](auto ctrl, auto row_mask) {
+        constexpr int CTRL = decltype(ctrl)::value, MASK = decltype(row_mask)::value;
+        const uint64_t bits = __builtin_bit_cast(uint64_t, best);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)bits, (int)(uint32_t)bits, CTRL, MASK, 0xf, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(bits >> 32), (int)(bits >> 32), CTRL, MASK, 0xf, false);
+        const int oi = __builtin_amdgcn_update_dpp(best_idx, best_idx, CTRL, MASK, 0xf, false);
+        take(__builtin_bit_cast(double, (uint64_t)hi << 32 | lo), oi);
+    };
+    typedef std::integral_constant<int, 0xf> AllRows;
+    step(std::integral_constant<int, 0xB1>{}, AllRows{});  // quad_perm [1,0,3,2]
+    step(std::integral_constant<int, 0x4E>{}, AllRows{});  // quad_perm [2,3,0,1]
+    step(std::integral_constant<int, 0x141>{}, AllRows{}); // row_half_mirror
+    step(std::integral_constant<int, 0x140>{}, AllRows{}); // row_mirror
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{}); // row_bcast:15 into rows 1 and 3
+    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{}); // row_bcast:31 into rows 2 and 3
     const int used = min(THREADS / 64, (a.nH * a.nW + 63) / 64); // wavefronts with a window
     if (used > 1) {
-        if ((tid & 63) == 0) {
+        if ((tid & 63) == 63) {
             s_best[tid >> 6] = best;
             s_idx[tid >> 6] = best_idx;
         }
         __syncthreads();
     }
-    if (tid == 0) {
+    if (tid == 63) {
         for (int v = 1; v < used; ++v) take(s_best[v], s_idx[v]);
         off_yx[2 * n] = best_idx / a.nW * a.stride;
         off_yx[2 * n + 1] = best_idx % a.nW * a.stride;
@@ -571,6 +595,8 @@ hipError_t launch_select_tiles_variance(const uint8_t *img, int64_t N, int H, in
     const int k = win / stride;
     a.nCy = a.nH - 1 + k;
     a.nCx = a.nW - 1 + k;
+    a.inv_stride = 1.0f / (float)stride;
+    a.inv_nW = 1.0f / (float)a.nW;
     for (int c = 0; c < 3; ++c) a.w[c] = w[c];
     // 16-byte loads: chunks must not straddle cells and every row of every image must start 16-byte aligned
     const bool wide = stride % 16 == 0 && W % 16 == 0 && ((uintptr_t)img & 15u) == 0;
@@ -579,7 +605,13 @@ hipError_t launch_select_tiles_variance(const uint8_t *img, int64_t N, int H, in
         const int64_t cnt = N - n0 < kMaxGrid ? N - n0 : kMaxGrid;
         const uint8_t *img0 = img + n0 * 3 * (int64_t)H * W;
         double *sc0 = scores ? scores + n0 * (int64_t)(a.nH * a.nW) : nullptr;
-        auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3((unsigned)cnt), dim3(threads), 0, s, img0, a, off_yx + 2 * n0, sc0); };
+        auto launch = [&](auto kernel, int threads) {
+            const int chunks = a.nCx * stride / (wide ? 16 : 1), groups = threads / std::min(chunks, threads);
+            a.tx = std::min(chunks, threads);
+            a.rows = (a.nCy * stride + groups - 1) / groups;
+            a.inv_tx = 1.0f / (float)a.tx;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)cnt), dim3(threads), 0, s, img0, a, off_yx + 2 * n0, sc0);
+        };
         if (select_threads(N, H, W, wide) == 1024) launch(wide ? tile_variance_kernel<16, 1024> : tile_variance_kernel<1, 1024>, 1024);
         else launch(wide ? tile_variance_kernel<16, 256> : tile_variance_kernel<1, 256>, 256);
     }

@@ -1499,6 +1499,31 @@ def test_select_tiles_variance_bit_exact(qrm, N, H, W, tile, stride):
     rs_only.close()
 
 
+@pytest.mark.parametrize("H,W,tile,stride", [(128, 128, 16, 16), (256, 256, 32, 8), (40, 3000, 40, 20), (75, 75, 15, 5)])
+def test_select_tiles_takes_the_first_of_equal_windows(qrm, H, W, tile, stride):
+    """The same busy block at two places of a flat image, at every distance in the order of windows that a reduction over
+    lanes, rows of lanes and wavefronts can meet; flat images take window 0."""
+    nH, nW = (H - tile) // stride + 1, (W - tile) // stride + 1
+    k = tile // stride
+    rng = np.random.default_rng(tile)
+    block = rng.integers(0, 256, size=(3, tile, tile), dtype=np.uint8)
+    places = [(y, x) for y in range(0, nH, k) for x in range(0, nW, k)]   # windows that do not overlap
+    pairs = [(i, j) for i in range(min(6, len(places))) for j in range(i + 1, len(places))][:200]
+    imgs = np.full((len(pairs) + 1, 3, H, W), 128, dtype=np.uint8)
+    want = np.zeros((len(pairs) + 1, 2), dtype=np.int32)
+    for n, pair in enumerate(pairs):
+        for y, x in (places[i] for i in pair):
+            imgs[n, :, y * stride:y * stride + tile, x * stride:x * stride + tile] = block
+        want[n] = np.array(places[pair[0]]) * stride
+    ctx = qrm.Context(rs=dict(m=4, prim_poly=0x13, n=12, k=8, fcr=1))
+    for count in (1, len(imgs)):   # (both sizes of workgroup)
+        d_off = empty((count, 2), torch.int32)
+        ctx.qrm_select_tiles_variance(dev(imgs[-count:]), count, H, W, tile, stride, d_off)
+        torch.cuda.synchronize()
+        assert np.array_equal(d_off.cpu().numpy(), want[-count:])
+    ctx.close()
+
+
 def test_select_tiles_then_detect_equals_oracle_path(qrm):
     """Selection feeds detection: the origins chosen on the device, then the whole path, against the oracle's."""
     cfg = synth.CONFIGS["C2"]
