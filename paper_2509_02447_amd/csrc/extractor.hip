@@ -3161,31 +3161,42 @@ ChainPlan conv_chain_plan(const ConvGeom &g, int C, int blocks, int num_cu)
     return p;
 }
 
-// Images of h x w of which an XCD's compute units can still have one item each.
+// Items to a compute unit of an XCD, at most (conv_chain_faster).
+static int chain_rounds(int C) { return C == 32 ? 5 : 1; }
+
+// Images of h x w of which an XCD's compute units do not have more items each.
 int conv_chain_most_images(int h, int w, int C, int num_cu)
 {
     const int64_t least = (int64_t)((h + chain_most_rows(C) - 1) / chain_most_rows(C)) * ((w + kChainCols - 1) / kChainCols); // items of an image
-    return (int)std::min<int64_t>(kHeadAlone, std::max(1, num_cu / kChainTeams) / least * kChainTeams);
+    return (int)std::min<int64_t>(kHeadAlone, (int64_t)chain_rounds(C) * std::max(1, num_cu / kChainTeams) / least * kChainTeams);
 }
 
-// Whether all blocks in one launch are the faster way, as long as every compute unit of an XCD has one item at most: an item then takes
-// what its rows take, while a launch per block has two round trips to memory, its weights and one strip behind the other.  By
-// estimates of four (C = 32) and eight blocks in microseconds, fitted to 1033 and 210 shapes of 1 .. 512 tiles from 8 x 8 to 256 x 256,
-// standard deviation 2 .. 3 %.  Where they say so the chain is 1.11 times as fast in the mean (up to 1.5), and in the worst case 5 % slower.
-// Single blocks / chain, us: 16 tiles of 32 x 32, 32 channels 28.7 / 26.9, 256 of them 76.9 / 51.5, 16 of 128 x 128 59.2 / 51.3; 7 of 128 x
-// 128, 64 channels 118.0 / 101.6, 16 of 96 x 96 146.5 / 127.9.  Single blocks by the rule: 2 of 128 x 128, 32 channels 29.4 / 38.1; 4 of 128 x
-// 128, 64 channels 83.2 / 101.9 (an XCD has one image or none).  Narrow tiles at 64 channels have the fused pairs (one of 64 x 64 52 / 59).
-bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int num_cu)
+// Whether all blocks in one launch are the faster way.  As long as every compute unit of an XCD has one item at most, an item takes
+// what its rows take, while a launch per block has two round trips to memory, its weights and one strip behind the other.  With more
+// items it is the faster way at 32 channels where a tile of up to 32 columns is one item wide and half of a strip of 64.
+//   By estimates in microseconds, fitted to whole calls of two to nine blocks, 1 .. 512 tiles of 8 x 8 to 256 x 256: 724 shapes with
+// one item at most and 484 with up to five at 32 channels, 161 at 64; standard deviation 2 .. 5 % and, for more than one item, 7 %.  Of the
+// 303, 148 and 76 for which they say so the chain is 1.12, 1.21 and 1.12 times as fast in the mean (up to 1.4); 2 of these 527 are slower by
+// more than 2 %; of the others it would be faster by 1.17 at most.  The number of blocks matters: fitted to four and eight alone, the
+// rule took calls of two and three that are 1.1 and 1.0 .. 1.25 times as long this way.
+// Single blocks / chain, us: 16 tiles of 32 x 32, 32 channels, four blocks 28.7 / 26.9, 256 of them 71 / 51.5; 390 of 29 x 12 89.2 / 66.6; 7 of
+// 128 x 128, 64 channels, eight blocks 113 / 100, 16 of 96 x 96 145 / 127.9.  Single blocks by the rule: 2 of 128 x 128, 32 channels 29.4 /
+// 38.1; 4 of 128 x 128, 64 channels 83.2 / 101.9 (an XCD has one image or none).  Narrow tiles at 64 channels have the fused pairs (one of
+// 64 x 64 52 / 59).
+bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int blocks, int num_cu)
 {
-    if (!p.one_round || (C == 64 && g.w <= kTileW)) return false;
+    if ((C == 64 && g.w <= kTileW) || p.items > (int64_t)chain_rounds(C) * std::max(1, num_cu / kChainTeams)) return false;
     const double per = (double)(((int64_t)g.n_img * g.strips * g.colblks + num_cu - 1) / num_cu), mpx = 1e-6 * g.n_img * g.h * g.w;
-    const double chunk_mpx = 1e-6 * p.chunk * g.h * g.w;
-    if (C == 32) {
-        const double item_us = p.rows == 4 ? 25.7 : p.rows == 8 ? 29.4 : p.rows == 16 ? 32.2 : 41.3;
-        return item_us + 259.0 * chunk_mpx + 0.05 * p.items < 0.97 * (24.3 + 4.7 * per + 53.9 * mpx);
+    const double chunk_mpx = 1e-6 * p.chunk * g.h * g.w, later = blocks - 1, items = (double)p.items;
+    if (C == 64) {
+        const double item_us = p.rows == 4 ? 5.74 : p.rows == 8 ? 6.44 : 9.05;
+        return 15.9 + later * (item_us + 64.4 * chunk_mpx) + 736.0 * chunk_mpx < 0.97 * (9.7 + 57.5 * mpx + later * (5.24 + 2.63 * per + 30.5 * mpx));
     }
-    const double item_us = p.rows == 4 ? 58.9 : p.rows == 8 ? 64.6 : 83.8;
-    return item_us + 998.0 * chunk_mpx < 0.97 * (50.5 + 18.0 * per + 260.0 * mpx);
+    if (p.one_round) {
+        const double item_us = p.rows == 4 ? 3.44 : p.rows == 8 ? 4.59 : p.rows == 16 ? 5.6 : 8.46;
+        return 12.9 + later * item_us + 395.0 * chunk_mpx < 0.95 * (9.0 + 47.6 * mpx + later * (3.6 + 1.66 * per + 4.7 * mpx));
+    }
+    return 21.7 + 0.1 * items + later * (0.38 + 0.18 * items + 56.4 * chunk_mpx) < 0.95 * (15.6 + 16.3 * mpx + later * (4.54 + 1.36 * per + 1.0 * mpx));
 }
 
 // The lines are those of the single blocks at two row groups, an image's in the place of its activations.

@@ -258,7 +258,7 @@ ChainPlan chain_plan(const qrm_ctx *c, int cnt, int h, int w, int blocks)
     if (c->diag_flags & (QRM_DIAG_NO_FUSED_PAIRS | QRM_DIAG_FUSE_ALWAYS | QRM_DIAG_NO_CHAIN)) return ChainPlan{};
     const ConvGeom g{cnt, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
     ChainPlan p = conv_chain_plan(g, c->C, blocks, c->num_cu);
-    if (!(c->diag_flags & QRM_DIAG_CHAIN_ALWAYS)) p.fits = p.fits && conv_chain_faster(g, c->C, p, c->num_cu);
+    if (!(c->diag_flags & QRM_DIAG_CHAIN_ALWAYS)) p.fits = p.fits && conv_chain_faster(g, c->C, p, blocks, c->num_cu);
     return p;
 }
 

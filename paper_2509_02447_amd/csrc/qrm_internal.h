@@ -152,7 +152,7 @@ struct ChainState {
     int blocks, n_img;
 };
 ChainPlan conv_chain_plan(const ConvGeom &g, int C, int blocks, int num_cu);
-bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int num_cu);
+bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int blocks, int num_cu);
 int conv_chain_most_images(int h, int w, int C, int num_cu);
 LastSums conv_chain_last_sums(const ConvGeom &g, int C);
 // blocks: of the network, from the first on; block b writes act[b & 1] and sampled channel sums to rec[b & 1] (conv_first_samples(),
