@@ -378,8 +378,9 @@ __device__ __forceinline__ void load_weight_frags(bf16x8 (&Wr)[9][C / 16], const
 //      needs, per channel of the last block's output, the sums over the whole tile, its first / last
 //      row, first / last column and four corners (9 numbers): the last block writes no activations but lines
 //      of C sums, each over a part of the image that does not depend on how the rows were dealt to workgroups
-//      (LastSums), so that its results do not either: the same image gives the same bits whatever the batch around it
-//      and however many compute units the launch has.  (A record of nine sums per workgroup, wavefront and image, the
+//      (LastSums), so that its results do not either: in one schedule (a launch per block or all blocks in one, which are the same
+//      bits; two blocks a launch) the same image gives the same bits whatever the batch around it and however many compute units
+//      the launch has.  (A record of nine sums per workgroup, wavefront and image, the
 //      alternative, also was 295 KB per image for the head to read in a launch of 7 tiles of 128 x 128; the lines are 52.)
 // Accumulation order is fixed, so results do not depend on scheduling.
 __host__ __device__ constexpr int sampled_strip(int strips) { return strips < 4 ? strips - 1 : 3; }
@@ -535,16 +536,18 @@ __device__ __forceinline__ void lds_accumulate4(float *slot4, const float (&tv)[
 
 // Channel sums of the RW output rows (first row yw, column x) held in `acc`, after bias `si` (this lane's
 // 16 channels) and ReLU, written to the line of C sums at `dst` (global memory, already offset to the lane's 16
-// channels).  Four channels at a time: registers are scarce next to weights and accumulators.
+// channels).  Four channels at a time: registers are scarce next to weights and accumulators.  above: the lane's sums over the
+// rows above that belong to the line, too.
+constexpr float kNoSums[16] = {};
 template <int RW>
 __device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const float *si, float *dst, int x, int yw,
-                                                 int h, int w, int px)
+                                                 int h, int w, int px, const float (&above)[16] = kNoSums)
 {
     const bool colok = (uint32_t)x < (uint32_t)w; // (x = -1: the column left of a wide tile's first block)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const f32x4 bq = *(const f32x4 *)(si + 4 * q);
-        float tv[4] = {0.f, 0.f, 0.f, 0.f}; // sum over this wavefront's valid rows of relu(output)
+        float tv[4] = {above[4 * q], above[4 * q + 1], above[4 * q + 2], above[4 * q + 3]}; // sum over valid rows of relu(output)
 #pragma unroll
         for (int r = 0; r < RW; ++r)
             if (yw + r < h) {
@@ -565,14 +568,15 @@ __device__ __forceinline__ void strip_statistics(const f32x16 (&acc)[RW], const 
 // This lane's sums over the RW output rows (first row yw), after bias `si` and a lower bound `low`: 16 channels, zero in
 // columns beyond the tile.
 template <int RW>
-__device__ __forceinline__ void column_sums(float (&t)[16], const f32x16 (&acc)[RW], const float *si, float low, bool colok, int yw, int h)
+__device__ __forceinline__ void column_sums(float (&t)[16], const f32x16 (&acc)[RW], const float *si, float low, bool colok, int yw, int h,
+                                            const float (&above)[16] = kNoSums)
 {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const f32x4 b = *(const f32x4 *)(si + 4 * q);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            float v = 0.f;
+            float v = above[4 * q + e];
 #pragma unroll
             for (int r = 0; r < RW; ++r)
                 if (yw + r < h) v += fmaxf(acc[r][4 * q + e] + b[e], low); // (the same for the whole wavefront)
@@ -585,13 +589,14 @@ __device__ __forceinline__ void column_sums(float (&t)[16], const f32x16 (&acc)[
 // offset to the lane's 16 channels; whole / col / row: which of its lines for the whole tile, for the first / last column
 // and for the first / last row these are; the latter and the corners are written by the wavefronts that hold a border.
 // A sum over the 32 pixel lanes is one butterfly for all 16 channels (reduce16_over_half), as in the fused kernel.
+// above: as in strip_statistics; WHOLE false: more rows of the piece follow, only the tile's first and last row are written.
 struct LinePlaces {
     int first_col, last_col, rows, last_rows, corners; // as in LastSums
     int whole, col, row;
 };
-template <int C, int RW>
+template <int C, int RW, bool WHOLE = true>
 __device__ __forceinline__ void last_lines(const f32x16 (&acc)[RW], const float *si, float *lines, const LinePlaces &at, int x, int x0w,
-                                           int yw, int h, int w, int px)
+                                           int yw, int h, int w, int px, const float (&above)[16] = kNoSums)
 {
     const bool colok = x < w;
     const bool has_first = x0w == 0, has_last = x0w <= w - 1 && w - 1 < x0w + 32; // same for the whole wavefront
@@ -606,10 +611,12 @@ __device__ __forceinline__ void last_lines(const f32x16 (&acc)[RW], const float 
         }
     };
     float t[16];
-    column_sums<RW>(t, acc, si, 0.f, colok, yw, h);
-    if (has_first) single(at.first_col + at.col, t, x == 0);
-    if (has_last) single(at.last_col + at.col, t, x == w - 1);
-    summed(at.whole, t);
+    if (WHOLE) {
+        column_sums<RW>(t, acc, si, 0.f, colok, yw, h, above);
+        if (has_first) single(at.first_col + at.col, t, x == 0);
+        if (has_last) single(at.last_col + at.col, t, x == w - 1);
+        summed(at.whole, t);
+    }
     const int rl = h - 1 - yw; // image row h-1 relative to this wavefront's rows
     if (yw == 0 || (rl >= 0 && rl < RW)) {
 #pragma unroll 1
@@ -1953,9 +1960,12 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
 //   What a later item reads has been stored in the L2 (s_waitcnt vmcnt) when the counter says so, and is loaded past the
 // compute unit's own cache (load16c, load_lds16c).  A hand-over between 8 workgroups of an XCD takes 1.0 us and 1.7 through the
 // memory behind the L2s, between 32 it takes 2.0 and 3.6; fences, which write back and invalidate a whole L2, made that 3 and 5.
-//   Products, sums, records, lines and roundings at 32 channels are those of conv_first_kernel and conv_mid_kernel, in
-// their order: the results are the same bit for bit, so that a tile's do not depend on the batch around it.  (64 channels: pairs
-// of rows as here, conv_mid_kernel has strips of four.)
+//   Products, sums, records, lines and roundings are those of conv_first_kernel and conv_mid_kernel, in their order: the results
+// are the same bit for bit, so that a tile's do not depend on whether the batch around it is small enough for this launch.  A
+// wavefront therefore multiplies the rows that one of conv_mid_kernel has of a strip, or half of them in the order that they come
+// in there (half_mma); one wavefront sums the image's records up, or each for itself, never several in shares.  (64 channels: pairs of
+// rows instead of strips of four, records shared by the wavefronts and the correction behind the products are 3 % faster, 7 tiles of
+// 128 x 128, eight blocks and the head 106.7 us instead of 110.3, but then a tile's logits change with the number of tiles.)
 //   The state (ChainState) is all zeros when the launch begins; the launch behind it, which reads its results, clears it again.
 // ------------------------------------------------------------------------------------------------
 struct ChainArgs {
@@ -1984,7 +1994,10 @@ struct ChainCfg {
     typedef MidCfg<C> K;
     static constexpr int RG = WAVES / K::NCB;           // wavefronts one above the other
     static constexpr int ROWS = RG * RW * STEPS;
-    static_assert(RW == 2 || (C == 32 && ROWS == kRows && STEPS == 1), "a row per wavefront: where an item is a strip");
+    static constexpr int SR = 2 * K::NCB;               // rows that a wavefront of conv_mid_kernel has of a strip,
+    static constexpr int SG = kRows / SR;               // .. and how many such groups of rows a strip is: sums and dither are by them
+    static constexpr bool HALVES = RW < SR;             // here such a group may be two wavefronts' (an item of few rows)
+    static_assert(RW == SR || (2 * RW == SR && STEPS == 1 && (C == 64 || ROWS == kRows)), "whole groups of rows");
     static constexpr int THREADS = 64 * WAVES;
     static constexpr int HALO = kChainCols + 2;
     static constexpr int ROWB = HALO * K::PS;           // a staged row
@@ -2000,34 +2013,61 @@ struct ChainCfg {
     static_assert(K::NCB * FRAGS % LOADERS == 0, "whole fragments to a wavefront");
 };
 
-// One output row of 32 pixels x 32 channels at 32 channels, the upper or (LOWER) the lower of a pair: its products in the order of strip_mma<32, 2>.
-template <bool LOWER>
-__device__ __forceinline__ void half_pair_mma(const lrow_t (&rowp)[3], const bf16x8 (&Wr)[9][2], f32x16 &acc)
+// RW output rows of 32 pixels x 32 channels, the upper or (LOWER) the lower half of a group: their products in the order of
+// strip_mma<C, 2 * RW>, whose fragments that such a half does not need are left out.
+template <int C, bool LOWER, int RW>
+struct HalfOrder {
+    static constexpr int NT = (RW + 2) * MidCfg<C>::KC * 3; // fragments
+    int row[NT], kc[NT], dx[NT];
+    constexpr HalfOrder() : row(), kc(), dx()
+    {
+        constexpr int NP = RW + 1, KP = MidCfg<C>::KC / 2; // as there
+        int t = 0;
+        for (int s2 = 0; s2 < 3 * KP * NP; ++s2)
+            for (int j = 0; j < 4; ++j) {
+                const int r = s2 % NP + (j & 1) * NP - (LOWER ? RW : 0);
+                if (r < 0 || r >= RW + 2) continue;
+                row[t] = r;
+                kc[t] = 2 * (s2 / NP % KP) + (j >> 1);
+                dx[t++] = s2 / (NP * KP);
+            }
+    }
+};
+template <int C, bool LOWER, int RW>
+__device__ __forceinline__ void half_mma(const lrow_t (&rowp)[RW + 2], const bf16x8 (&Wr)[9][C / 16], f32x16 (&acc)[RW])
 {
     asm volatile(".p2align 5");
-    typedef MidCfg<32> K;
-    constexpr int NF = 4, NT = 18;
-    constexpr auto row = [](int t) { return LOWER ? (t % 6 < 2 ? 1 : t % 6 % 2 * 2) : (t % 6 < 4 ? t % 6 % 2 * 2 : 1); };
-    constexpr auto chunk = [](int t) { return LOWER ? (t % 6 < 2 ? t % 6 : t % 6 / 4) : (t % 6 < 4 ? t % 6 / 2 : t % 6 - 4); };
+    typedef MidCfg<C> K;
+    constexpr HalfOrder<C, LOWER, RW> at;
+    constexpr int NF = 4, NT = at.NT;
+    bool started[RW] = {};
     bf16x8 f[NF];
     unrolled<NF>([&](auto tc) {
         constexpr int t = decltype(tc)::value;
-        frag_read<t / 6 * K::PS + chunk(t) * 32>(f[t], rowp[row(t)]);
+        frag_read<at.dx[t] * K::PS + at.kc[t] * 32>(f[t], rowp[at.row[t]]);
     });
     __builtin_amdgcn_sched_barrier(0);
     unrolled<NT>([&](auto tc) {
         constexpr int t = decltype(tc)::value;
         bf16x8 &fr = f[t % NF];
         frag_wait<(t + NF <= NT ? NF - 1 : NT - 1 - t)>(fr);
-        acc = mfma32(Wr[row(t) * 3 + t / 6][chunk(t)], fr, t == 0 ? kZeroAcc : acc);
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+            const int orow = at.row[t] - dy;
+            if (orow >= 0 && orow < RW) {
+                acc[orow] = mfma32(Wr[dy * 3 + at.dx[t]][at.kc[t]], fr, started[orow] ? acc[orow] : kZeroAcc);
+                started[orow] = true;
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (t + NF < NT) {
             constexpr int u = t + NF;
-            frag_read<u / 6 * K::PS + chunk(u) * 32>(fr, rowp[row(u)]);
+            frag_read<at.dx[u] * K::PS + at.kc[u] * 32>(fr, rowp[at.row[u]]);
         }
         __builtin_amdgcn_sched_barrier(0);
     });
-    asm volatile("" : "+v"(acc)); // (the products stay where they are)
+#pragma unroll
+    for (int r = 0; r < RW; ++r) asm volatile("" : "+v"(acc[r])); // (the products stay where they are)
 }
 
 template <int C, int WAVES, int RW, int STEPS>
@@ -2039,9 +2079,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
     static_assert(G::PIX * 8 <= LDS_ROWS, "the first block's pixels take the rows' place");
     __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_ROWS];
     __shared__ __attribute__((aligned(1024))) uint8_t s_weights[K::NCB * G::FRAGS * 1024];
-    __shared__ __attribute__((aligned(16))) float s_part[C == 64 ? WAVES : 1][C]; // 64 channels: sums of the records, by wavefront
-    __shared__ __attribute__((aligned(16))) float s_mean[WAVES][C];   // the image's means, for a wavefront's own use
-    __shared__ __attribute__((aligned(16))) float s_lower[RW == 1 ? 2 : 1][RW == 1 ? 1024 : 4]; // lower rows on their way to the wavefront that sums the pair up
+    __shared__ __attribute__((aligned(16))) float s_mean[C == 32 ? WAVES : 1][C]; // the image's means, 32 channels: for a wavefront's own use
+    // what one wavefront of a group's halves hands the other, which sums it up: 32 channels the lower row, 64 the sums over the upper rows
+    __shared__ __attribute__((aligned(16))) float s_handed[G::HALVES ? WAVES / 2 : 1][G::HALVES ? 1024 : 4];
     __shared__ __attribute__((aligned(16))) float s_init[WAVES][32];  // bias + correction of its outputs
     __shared__ __attribute__((aligned(16))) int s_next[2][8]; // the next item, by its parity within the workgroup: a slow wavefront may still read the one before
 
@@ -2141,13 +2181,13 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
         const int ln = pin_in_loop(tid & 63), x = it.colblk * kChainCols + (ln & 31), half = ln >> 5;
         const float *si = &s_init[wave][half * 16];
         uint8_t *out = a.act[it.b & 1] + (size_t)it.n * img_bytes;
-        const uint32_t dbase = dither16(x, yw & ~1); // (pairs of rows a quarter step apart)
+        const uint32_t dbase = dither16(x, yw & ~(G::SR - 1)); // (its rows are quarter steps apart)
 #pragma unroll
         for (int hq = 0; hq < 2; ++hq) {
             const f32x4 b0 = *(const f32x4 *)(si + 8 * hq), b1 = *(const f32x4 *)(si + 8 * hq + 4);
 #pragma unroll
             for (int r = 0; r < RW; ++r) {
-                const uint32_t dth = dbase ^ ((uint32_t)(RW == 1 ? yw & 1 : r) << 14);
+                const uint32_t dth = dbase ^ ((uint32_t)((RW == G::SR ? 0 : yw & (G::SR - 1)) + r) << 14);
                 u32x4 pk;
                 pk[0] = pack_bf16_relu(acc[r][8 * hq + 0] + b0[0], acc[r][8 * hq + 1] + b0[1], dth, true);
                 pk[1] = pack_bf16_relu(acc[r][8 * hq + 2] + b0[2], acc[r][8 * hq + 3] + b0[3], dth, true);
@@ -2158,35 +2198,38 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
             }
         }
     };
-    // The sums of rows yw, yw + 1 (yw even)
-    auto sum_rows = [&](const Item &it, int yw, const f32x16 (&acc)[2]) __attribute__((always_inline)) {
+    // The sums of a group of SR rows, whose last ones these are (from row yw on; above: the lane's sums over the others); WHOLE false:
+    // more rows follow
+    auto sum_rows = [&](const Item &it, int yw, const auto &acc, auto whole, const float (&above)[16]) __attribute__((always_inline)) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        constexpr int N = sizeof acc / sizeof acc[0];
         const int ln = pin_in_loop(tid & 63), px = ln & 31, half = ln >> 5;
-        const int x0 = it.colblk * kChainCols, x = x0 + px, strip = yw / kRows, rg2 = yw / 2 % 2, blk = it.colblk / 2, xb = it.colblk % 2;
+        const int x0 = it.colblk * kChainCols, x = x0 + px, strip = yw / kRows, group = yw / G::SR % G::SG, blk = it.colblk / 2, xb = it.colblk % 2;
         const float *si = &s_init[wave][half * 16];
-        const int piece = rg2 * 2 + xb;
+        const int piece = group * 2 + xb;
         // a last block of 32 columns that stands alone also leaves the (empty) sums of the one beside it
         const bool alone = xb == 0 && x0 + kChainCols >= a.g.w;
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         if (is_last(it.b)) {
             float *lines = a.lines + it.n * a.lines_stride + cb * 32 + half * 16;
-            LinePlaces p; // those of conv_mid_last_sums() at two row groups
-            p.first_col = a.g.strips * a.g.colblks * 4;
-            p.last_col = p.first_col + a.g.strips * 2;
-            p.rows = p.last_col + a.g.strips * 2;
+            LinePlaces p; // those of conv_mid_last_sums()
+            p.first_col = a.g.strips * a.g.colblks * 2 * G::SG;
+            p.last_col = p.first_col + a.g.strips * G::SG;
+            p.rows = p.last_col + a.g.strips * G::SG;
             p.last_rows = p.rows + 2 * a.g.colblks;
             p.corners = p.last_rows + 2 * a.g.colblks;
-            p.whole = (blk * a.g.strips + strip) * 4 + piece;
-            p.col = strip * 2 + rg2;
+            p.whole = (blk * a.g.strips + strip) * (2 * G::SG) + piece;
+            p.col = strip * G::SG + group;
             p.row = blk * 2 + xb;
-            last_lines<C, 2>(acc, si, lines, p, x, x0, yw, a.g.h, a.g.w, px);
+            last_lines<C, N, WHOLE>(acc, si, lines, p, x, x0, yw, a.g.h, a.g.w, px, above);
             if (alone && px < 4) {
-                *(f32x4 *)(lines + (p.whole + 1) * C + 4 * px) = zero;
+                if (WHOLE) *(f32x4 *)(lines + (p.whole + 1) * C + 4 * px) = zero;
                 if (yw == 0) *(f32x4 *)(lines + (p.rows + p.row + 1) * C + 4 * px) = zero;
-                if (a.g.h - 1 - yw >= 0 && a.g.h - 1 - yw < 2) *(f32x4 *)(lines + (p.last_rows + p.row + 1) * C + 4 * px) = zero;
+                if (a.g.h - 1 - yw >= 0 && a.g.h - 1 - yw < N) *(f32x4 *)(lines + (p.last_rows + p.row + 1) * C + 4 * px) = zero;
             }
-        } else {
-            float *rec = a.rec[it.b & 1] + ((int64_t)it.n * a.mid.recs + ((strip >> 3) * a.g.colblks + blk) * 4 + piece) * C + cb * 32 + half * 16;
-            strip_statistics<2>(acc, si, rec, x, yw, a.g.h, a.g.w, px);
+        } else if (WHOLE) {
+            float *rec = a.rec[it.b & 1] + ((int64_t)it.n * a.mid.recs + ((strip >> 3) * a.g.colblks + blk) * (2 * G::SG) + piece) * C + cb * 32 + half * 16;
+            strip_statistics<N>(acc, si, rec, x, yw, a.g.h, a.g.w, px, above);
             if (alone && px < 4) *(f32x4 *)(rec + C + 4 * px) = zero;
         }
     };
@@ -2366,17 +2409,27 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
 #pragma unroll
             for (int k = 0; k < G::LOADS; ++k) load_lds16c(in, img_bytes, voff[k], lds + (k * WAVES + wave) * 1024);
             asm volatile("" ::: "memory");
-            // (32 channels: every wavefront all of them, as ImageMeans; 64: each a share)
-            constexpr int LPR = C / 4, RPL = C == 64 ? G::THREADS / LPR : 64 / LPR, INF = C == 64 ? 2 : 4; // lanes per record, records per load, loads in flight
-            const int rec_tid = C == 64 ? tid : lane, recs = it.b == 1 ? a.first.recs : a.mid.recs;
+            // (as ImageMeans; 32 channels: every wavefront all of them, 64: the first one, for all: the others see a buffer of no bytes)
+            const bool reads = C == 32 || wave == 0;
+            constexpr int LPR = C / 4, RPL = 64 / LPR, INF = 4; // lanes per record, records per load, loads in flight
+            const int recs = it.b == 1 ? a.first.recs : a.mid.recs;
             const float *rec = a.rec[(it.b - 1) & 1] + (int64_t)it.n * recs * C;
             f32x4 v[INF];
             auto records = [&](int r0) {
 #pragma unroll
                 for (int u = 0; u < INF; ++u)
-                    v[u] = __builtin_bit_cast(f32x4, load16c(rec, (uint32_t)recs * C * 4, (uint32_t)(min(r0 + u * RPL + rec_tid / LPR, recs - 1) * LPR + rec_tid % LPR) * 16));
+                    v[u] = __builtin_bit_cast(f32x4, load16c(rec, reads ? (uint32_t)recs * C * 4 : 0u, (uint32_t)(min(r0 + u * RPL + lane / LPR, recs - 1) * LPR + lane % LPR) * 16));
             };
             records(0);
+            asm volatile("" ::: "memory");
+            // What the correction of this wavefront's outputs needs: four outputs to a lane, eight lanes to an output with an eighth of the
+            // input channels each.
+            constexpr int CP = C / 8;
+            const float *rsum = a.rsum + (size_t)(it.b - 1) * C * C + (lane >> 3) * CP * C + cb * 32 + 4 * (lane & 7);
+            const f32x4 bias = *(const f32x4 *)(a.bias + it.b * C + cb * 32 + 4 * (lane & 7));
+            f32x4 rs[CP];
+#pragma unroll
+            for (int k = 0; k < CP; ++k) rs[k] = *(const f32x4 *)(rsum + k * C);
             asm volatile("" ::: "memory");
 #pragma unroll
             for (int dx = G::AHEAD; dx < 3; ++dx) {
@@ -2386,15 +2439,33 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
 #pragma unroll
                     for (int dy = 0; dy < 3; ++dy) Wr[dy * 3 + dx][kc] = wp[((dy * 3 + dx) * K::KC + kc) * 64];
             }
-            // what the correction of this wavefront's outputs needs: four outputs to a lane, eight lanes to an output with an eighth of the
-            // input channels each
-            constexpr int CP = C / 8;
-            const float *rsum = a.rsum + (size_t)(it.b - 1) * C * C + (lane >> 3) * CP * C + cb * 32 + 4 * (lane & 7);
-            const f32x4 bias = *(const f32x4 *)(a.bias + it.b * C + cb * 32 + 4 * (lane & 7));
-            f32x4 rs[CP];
-#pragma unroll
-            for (int k = 0; k < CP; ++k) rs[k] = *(const f32x4 *)(rsum + k * C);
             asm volatile("" ::: "memory");
+            auto correct = [&](int ln) __attribute__((always_inline)) {
+                f32x4 d = {0.f, 0.f, 0.f, 0.f};
+                auto part = [&]() {
+#pragma unroll
+                    for (int k = 0; k < CP; ++k) {
+                        const float mk = s_mean[C == 32 ? wave : 0][(ln >> 3) * CP + k];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) d[e] = fmaf(rs[k][e], mk, d[e]);
+                    }
+                };
+                part();
+                // FirstInit sums over parts of 64 / (C / 4): eighths at 32 channels, quarters at 64, the second half of each behind the first
+                if (C == 64) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) d[e] = dpp_f<0x118, 0xf>(d[e]); // row_shr:8
+                    part();
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) d[e] += dpp_f<0x128, 0xf>(d[e]); // row_ror:8
+                }
+#pragma unroll
+                for (int sh = 16; sh < 64; sh <<= 1)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) d[e] += __shfl_xor(d[e], sh);
+                if (ln >> 3 == (C == 64 ? 1 : 0)) *(f32x4 *)&s_init[wave][4 * (ln & 7)] = bias + d;
+            };
             {
                 f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -2402,7 +2473,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
                 auto add = [&](int r0) {
 #pragma unroll
                     for (int u = 0; u < INF; ++u) {
-                        const bool ok = r0 + u * RPL + rec_tid / LPR < recs;
+                        const bool ok = r0 + u * RPL + lane / LPR < recs;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) sum[e] += ok ? v[u][e] : 0.f;
                     }
@@ -2417,14 +2488,11 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
                 for (int sh = LPR; sh < 64; sh <<= 1)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) sum[e] += __shfl_xor(sum[e], sh);
-                if (C == 64) {
-                    if (lane < LPR) *(f32x4 *)&s_part[wave % (C == 64 ? WAVES : 1)][4 * lane] = sum;
-                } else {
-                    const float inv_cnt = it.b == 1 ? a.first.inv_cnt : a.mid.inv_cnt;
-                    if (lane < LPR) *(f32x4 *)&s_mean[wave][4 * lane] = (f32x4){sum[0] * inv_cnt, sum[1] * inv_cnt, sum[2] * inv_cnt, sum[3] * inv_cnt};
-                }
+                const float inv_cnt = it.b == 1 ? a.first.inv_cnt : a.mid.inv_cnt;
+                if (reads && lane < LPR) *(f32x4 *)&s_mean[C == 32 ? wave : 0][4 * lane] = (f32x4){sum[0] * inv_cnt, sum[1] * inv_cnt, sum[2] * inv_cnt, sum[3] * inv_cnt};
             }
             lds_barrier(); // (the records have landed, and before them the rows)
+            if (C == 64) correct(lane); // (no registers are left for what it needs while a product is formed)
             uint32_t next = 0;
             if (draws) next = draw();
             if (lds_of == it.b && it.b + 1 < a.blocks) weights_to_lds(it.b + 1);
@@ -2436,57 +2504,59 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
 #pragma unroll
                 for (int r = 0; r < RW + 2; ++r) rowp[r] = lds_address(lds) + (uint32_t)((row + r) * G::ROWB + px * K::PS + half * 16);
                 f32x16 acc[RW];
-                if constexpr (RW == 1) {
-                    if (rg & 1) half_pair_mma<true>(rowp, Wr, acc[0]);
-                    else half_pair_mma<false>(rowp, Wr, acc[0]);
-                } else {
+                if constexpr (!G::HALVES) {
                     strip_mma<C, RW>(rowp, Wr, acc, kZeroAcc, []() {});
 #pragma unroll
                     for (int r = 0; r < RW; ++r) asm volatile("" : "+v"(acc[r])); // (the products stay where they are)
+                } else if (rg & 1) {
+                    half_mma<C, true, RW>(rowp, Wr, acc);
+                } else {
+                    half_mma<C, false, RW>(rowp, Wr, acc);
                 }
-                if (s == 0) {
-                    if constexpr (C == 64) {
-                        float m = s_part[0][ln];
-#pragma unroll
-                        for (int w = 1; w < WAVES; ++w) m += s_part[w][ln];
-                        s_mean[wave][ln] = m * (it.b == 1 ? a.first.inv_cnt : a.mid.inv_cnt);
-                    }
-                    f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int k = 0; k < CP; ++k) {
-                        const float mk = s_mean[wave][(ln >> 3) * CP + k];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) d[e] = fmaf(rs[k][e], mk, d[e]);
-                    }
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) d[e] += dpp_f<0x128, 0xf>(d[e]); // row_ror:8
-#pragma unroll
-                    for (int sh = 16; sh < 64; sh <<= 1)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) d[e] += __shfl_xor(d[e], sh);
-                    if (ln < 8) *(f32x4 *)&s_init[wave][4 * ln] = (f32x4){bias[0] + d[0], bias[1] + d[1], bias[2] + d[2], bias[3] + d[3]};
-                }
+                if (C == 32 && s == 0) correct(ln);
                 const int yw = it.y0 + row, strip = yw / kRows;
-                if (strip >= a.g.strips) continue; // (the same for the whole wavefront)
-                if (!is_last(it.b)) store_rows(it, yw, acc);
-                if (!leaves_sums(it.b, strip)) continue;
-                if constexpr (RW == 2) {
-                    sum_rows(it, yw, acc);
-                } else { // (the same for the whole workgroup, whose rows are a strip)
-                    float *lower = &s_lower[rg >> 1][ln * 4];
+                const bool inside = strip < a.g.strips; // (the same for the whole wavefront)
+                if (inside && !is_last(it.b)) store_rows(it, yw, acc);
+                const bool sums = inside && leaves_sums(it.b, strip);
+                if constexpr (!G::HALVES || G::ROWS == kRows) {
+                    if (!sums) continue;
+                } else { // (a barrier follows: the same for the whole workgroup, of whose strips one at least may be inside)
+                    if (!leaves_sums(it.b, it.y0 / kRows) && !leaves_sums(it.b, it.y0 / kRows + 1)) continue;
+                }
+                float *handed = &s_handed[rg / 2 * K::NCB + cb][ln * 4];
+                if constexpr (!G::HALVES) {
+                    sum_rows(it, yw, acc, std::true_type{}, kNoSums);
+                } else if constexpr (C == 32) {
                     if (rg & 1) {
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) *(f32x4 *)(lower + q * 256) = (f32x4){acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]};
+                        for (int q = 0; q < 4; ++q) *(f32x4 *)(handed + q * 256) = (f32x4){acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]};
                     }
                     lds_barrier();
                     if (!(rg & 1)) {
                         f32x16 pair[2] = {acc[0], {}};
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            const f32x4 v = *(const f32x4 *)(lower + q * 256);
+                            const f32x4 v = *(const f32x4 *)(handed + q * 256);
                             pair[1][4 * q] = v[0]; pair[1][4 * q + 1] = v[1]; pair[1][4 * q + 2] = v[2]; pair[1][4 * q + 3] = v[3];
                         }
-                        sum_rows(it, yw, pair);
+                        sum_rows(it, yw, pair, std::true_type{}, kNoSums);
+                    }
+                } else {
+                    float above[16];
+                    if (sums && !(rg & 1)) {
+                        column_sums<RW>(above, acc, &s_init[wave][half * 16], 0.f, true, yw, a.g.h);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) *(f32x4 *)(handed + q * 256) = (f32x4){above[4 * q], above[4 * q + 1], above[4 * q + 2], above[4 * q + 3]};
+                    }
+                    lds_barrier();
+                    if (sums && !(rg & 1) && is_last(it.b)) sum_rows(it, yw, acc, std::false_type{}, kNoSums);
+                    if (sums && (rg & 1)) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const f32x4 v = *(const f32x4 *)(handed + q * 256);
+                            above[4 * q] = v[0]; above[4 * q + 1] = v[1]; above[4 * q + 2] = v[2]; above[4 * q + 3] = v[3];
+                        }
+                        sum_rows(it, yw, acc, std::true_type{}, above);
                     }
                 }
             }
@@ -3164,33 +3234,25 @@ ChainPlan conv_chain_plan(const ConvGeom &g, int C, int blocks, int num_cu)
 // Items to a compute unit of an XCD, at most (conv_chain_faster).
 static int chain_rounds(int C) { return C == 32 ? 5 : 1; }
 
-// Images of h x w of which an XCD's compute units do not have more items each.
-int conv_chain_most_images(int h, int w, int C, int num_cu)
-{
-    const int64_t least = (int64_t)((h + chain_most_rows(C) - 1) / chain_most_rows(C)) * ((w + kChainCols - 1) / kChainCols); // items of an image
-    return (int)std::min<int64_t>(kHeadAlone, (int64_t)chain_rounds(C) * std::max(1, num_cu / kChainTeams) / least * kChainTeams);
-}
-
 // Whether all blocks in one launch are the faster way.  As long as every compute unit of an XCD has one item at most, an item takes
 // what its rows take, while a launch per block has two round trips to memory, its weights and one strip behind the other.  With more
 // items it is the faster way at 32 channels where a tile of up to 32 columns is one item wide and half of a strip of 64.
 //   By estimates in microseconds, fitted to whole calls of two to nine blocks, 1 .. 512 tiles of 8 x 8 to 256 x 256: 724 shapes with
-// one item at most and 484 with up to five at 32 channels, 161 at 64; standard deviation 2 .. 5 % and, for more than one item, 7 %.  Of the
-// 303, 148 and 76 for which they say so the chain is 1.12, 1.21 and 1.12 times as fast in the mean (up to 1.4); 2 of these 527 are slower by
+// one item at most and 484 with up to five at 32 channels, 600 at 64; standard deviation 2 .. 5 % and, for more than one item, 7 %.  Of the
+// 303, 148 and 108 for which they say so the chain is 1.12, 1.21 and 1.06 times as fast in the mean (up to 1.4); 3 of these 559 are slower by
 // more than 2 %; of the others it would be faster by 1.17 at most.  The number of blocks matters: fitted to four and eight alone, the
 // rule took calls of two and three that are 1.1 and 1.0 .. 1.25 times as long this way.
-// Single blocks / chain, us: 16 tiles of 32 x 32, 32 channels, four blocks 28.7 / 26.9, 256 of them 71 / 51.5; 390 of 29 x 12 89.2 / 66.6; 7 of
-// 128 x 128, 64 channels, eight blocks 113 / 100, 16 of 96 x 96 145 / 127.9.  Single blocks by the rule: 2 of 128 x 128, 32 channels 29.4 /
-// 38.1; 4 of 128 x 128, 64 channels 83.2 / 101.9 (an XCD has one image or none).  Narrow tiles at 64 channels have the fused pairs (one of
-// 64 x 64 52 / 59).
+// Other ways / chain, us: 16 tiles of 32 x 32, 32 channels, four blocks 25.1 / 24.3, 256 of them 71.6 / 49.2; 390 of 29 x 12 90.3 / 66.7; 7 of
+// 128 x 128, 64 channels, eight blocks 110.7 / 105.7.  Not by the rule: 2 of 128 x 128, 32 channels 26.2 / 35.1; 4 of 128 x 128, 64 channels
+// 86.8 / 105.8 (an XCD has one image or none).  Narrow tiles at 64 channels have the fused pairs (one of 64 x 64 49.1 / 61.2, four 50.1 / 64.1).
 bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int blocks, int num_cu)
 {
     if ((C == 64 && g.w <= kTileW) || p.items > (int64_t)chain_rounds(C) * std::max(1, num_cu / kChainTeams)) return false;
     const double per = (double)(((int64_t)g.n_img * g.strips * g.colblks + num_cu - 1) / num_cu), mpx = 1e-6 * g.n_img * g.h * g.w;
     const double chunk_mpx = 1e-6 * p.chunk * g.h * g.w, later = blocks - 1, items = (double)p.items;
     if (C == 64) {
-        const double item_us = p.rows == 4 ? 5.74 : p.rows == 8 ? 6.44 : 9.05;
-        return 15.9 + later * (item_us + 64.4 * chunk_mpx) + 736.0 * chunk_mpx < 0.97 * (9.7 + 57.5 * mpx + later * (5.24 + 2.63 * per + 30.5 * mpx));
+        const double item_us = p.rows == 4 ? 6.25 : p.rows == 8 ? 7.25 : 10.2;
+        return 16.2 + later * (item_us + 70.0 * chunk_mpx) + 525.0 * chunk_mpx < 0.97 * (9.8 + 56.5 * mpx + later * (5.16 + 2.72 * per + 30.5 * mpx));
     }
     if (p.one_round) {
         const double item_us = p.rows == 4 ? 3.44 : p.rows == 8 ? 4.59 : p.rows == 16 ? 5.6 : 8.46;
@@ -3199,10 +3261,10 @@ bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int blocks,
     return 21.7 + 0.1 * items + later * (0.38 + 0.18 * items + 56.4 * chunk_mpx) < 0.95 * (15.6 + 16.3 * mpx + later * (4.54 + 1.36 * per + 1.0 * mpx));
 }
 
-// The lines are those of the single blocks at two row groups, an image's in the place of its activations.
+// The lines are those of the single blocks, an image's in the place of its activations.
 LastSums conv_chain_last_sums(const ConvGeom &g, int C)
 {
-    LastSums l = conv_mid_last_sums(g, 32);
+    LastSums l = conv_mid_last_sums(g, C);
     l.stride = (int64_t)g.h * g.w * C * 2 / 16;
     return l;
 }
@@ -3212,14 +3274,14 @@ hipError_t launch_conv_chain(const TileSrc &src, const ConvGeom &g, int C, const
                              float *rec1, float *lines, uint32_t *state, int num_cu, hipStream_t s)
 {
     if (!p.fits) return hipErrorInvalidValue;
-    ChainArgs a{src, g, blocks, w_first, w_mid, bias, rsum, {act0, act1}, {rec0, rec1}, conv_first_samples(g, C), conv_mid_samples(g, 32),
+    ChainArgs a{src, g, blocks, w_first, w_mid, bias, rsum, {act0, act1}, {rec0, rec1}, conv_first_samples(g, C), conv_mid_samples(g, C),
                 lines, (int64_t)g.h * g.w * C / 2, state, p.chunk, (g.n_img + p.chunk - 1) / p.chunk};
     const dim3 grid((unsigned)std::min<int64_t>(p.items * kChainTeams, num_cu));
     auto launch = [&](auto kernel, int waves) { hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, s, a); };
     if (C == 64) {
         if (p.rows == 4) launch(conv_chain_kernel<64, 4, 2, 1>, 4);
         else if (p.rows == 8) launch(conv_chain_kernel<64, 8, 2, 1>, 8);
-        else launch(conv_chain_kernel<64, 8, 2, 2>, 8);
+        else launch(conv_chain_kernel<64, 8, 4, 1>, 8);
     } else {
         if (p.rows == 4) launch(conv_chain_kernel<32, 4, 1, 1>, 4);
         else if (p.rows == 8) launch(conv_chain_kernel<32, 4, 2, 1>, 4);

@@ -319,11 +319,6 @@ WsLayout ws_layout(const qrm_ctx *c, int64_t N, int h, int w, bool want_symbols,
             if (fused) L.seam = std::max(L.seam, align_up(conv_pair_seam_bytes(g, launch_cu(c))));
         }
     }
-    if (c->has_ext && L.mb > 0) { // the chain's records, of as many images as it takes: a larger batch does not need less
-        const int most = c->diag_flags & QRM_DIAG_CHAIN_ALWAYS ? L.mb : std::min(L.mb, conv_chain_most_images(h, w, c->C, c->num_cu));
-        const ConvGeom g{most, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
-        if (most > 0) L.stats = std::max(L.stats, align_up((size_t)most * conv_mid_samples(g, 32).recs * c->C * 4));
-    }
     L.symbols = (want_symbols && c->has_rs) ? align_up((size_t)N * c->rs.n) : 0;
     L.total = 2 * L.act + L.tail + 2 * L.stats + L.seam + L.symbols;
     return L;

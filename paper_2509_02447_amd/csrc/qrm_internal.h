@@ -153,10 +153,9 @@ struct ChainState {
 };
 ChainPlan conv_chain_plan(const ConvGeom &g, int C, int blocks, int num_cu);
 bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int blocks, int num_cu);
-int conv_chain_most_images(int h, int w, int C, int num_cu);
 LastSums conv_chain_last_sums(const ConvGeom &g, int C);
 // blocks: of the network, from the first on; block b writes act[b & 1] and sampled channel sums to rec[b & 1] (conv_first_samples(),
-// then those of conv_mid_samples() at 32 channels).  lines not null: the
+// then those of conv_mid_samples()).  lines not null: the
 // last of them leaves lines of sums there, an image's in the place of its activations (conv_chain_last_sums()).  state: all zeros;
 // the launch behind this one clears it.
 hipError_t launch_conv_chain(const TileSrc &src, const ConvGeom &g, int C, const ChainPlan &p, int blocks, const bf16_t *w_first,

@@ -519,14 +519,14 @@ def test_single_block_logits_do_not_depend_on_the_split(qrm, C, nb, h, w, flags,
 # a time, more items than compute units, a tile too small for its lines (single blocks all the same)
 CHAIN_CASES = [(32, 2, 1, 7, 31, 0), (32, 4, 16, 32, 32, 0), (32, 4, 5, 33, 65, 0), (32, 3, 9, 64, 63, 0), (32, 5, 17, 13, 64, 0),
                (32, 3, 100, 30, 33, 0), (32, 4, 250, 16, 48, 0), (32, 2, 12, 130, 97, 0), (32, 3, 3, 3, 5, 0), (32, 3, 20, 40, 70, 1),
-               (64, 3, 7, 21, 70, 0), (64, 4, 2, 9, 200, 0), (64, 3, 11, 66, 129, 0), (64, 8, 8, 75, 100, 0), (64, 3, 6, 20, 128, 1)]
+               (64, 3, 7, 21, 70, 0), (64, 4, 2, 9, 200, 0), (64, 3, 11, 66, 129, 0), (64, 8, 8, 75, 100, 0), (64, 3, 6, 20, 128, 1),
+               (64, 2, 3, 4, 66, 0), (64, 4, 20, 70, 64, 0), (64, 3, 2, 3, 31, 1)]
 
 
 @pytest.mark.parametrize("C,nb,N,h,w,relu", CHAIN_CASES)
 def test_all_blocks_in_one_launch(qrm, C, nb, N, h, w, relu):
-    """All blocks of a batch in one launch against a launch per block: the same bits at 32 channels, in every layer too; at 64 channels
-    the oracle's logits, and the single blocks' within the sum of two tolerances.  Several calls in a row, on workspaces filled with NaN:
-    each finds the state that the one before left."""
+    """All blocks of a batch in one launch against a launch per block: the same bits, in every layer too.  Several calls in a row, the
+    first on a workspace filled with NaN: each finds the state that the one before left."""
     b = qrm.binding
     wts = small_weights(C, nb, 24, C + nb + h)
     tiles = np.random.default_rng(N * h + w).integers(0, 256, size=(N, 3, h, w), dtype=np.uint8)
@@ -548,12 +548,10 @@ def test_all_blocks_in_one_launch(qrm, C, nb, N, h, w, relu):
         ctx.close()
     chain, single = got.values()
     assert np.array_equal(chain[0], chain[1]) and np.array_equal(chain[0], chain[2])
-    if C == 32:
-        assert all(np.array_equal(a, s) for a, s in zip(chain, single))
+    assert all(np.array_equal(a, s) for a, s in zip(chain, single))
     few = min(N, 3)
     ref = oracle.extractor_forward(wts, tiles[:few], final_relu=relu)[0]
     check_logits(chain[0][:few], ref, what=f"chain C={C} {h}x{w}")
-    assert (np.abs(chain[0] - single[0]) <= 2 * 2e-2 * np.maximum(1.0, np.abs(single[0]))).all()
 
 
 def test_all_blocks_in_one_launch_captured(qrm):
