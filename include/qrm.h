@@ -22,6 +22,10 @@
  *     QRM_OK no kernel of that call has been launched unless stated, and
  *     qrm_last_error() describes the reason.
  *   - N == 0 is a successful no-op.
+ *   - A launch whose workgroups wait for each other gives up after seconds, which only happens where something else is wrong (calls
+ *     that overlap on the workspace of qrm_detect_static, say).  Images that it has lost have NaN logits, zero bits and, where
+ *     the words are decoded in the same launch, d_nerr -1, no matches and no detection; the next call that runs the extractor on the
+ *     context returns QRM_E_DEVICE, once, and does nothing else (qrm_detect_host: that call itself, when its chunks are done).
  *   - A context belongs to one device and one host thread at a time.  Work on
  *     up to QRM_MAX_STREAMS different streams may be in flight: each stream
  *     gets its own workspace inside the context and keeps it from call to

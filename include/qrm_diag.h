@@ -32,6 +32,22 @@ extern "C" {
 QRM_API qrm_status qrm_diag_set_flags(qrm_ctx *ctx, int32_t flags);
 
 /*
+ * For tests of what happens when the workgroups of an all-blocks launch do not hear from each other.  _patience: how often a wait
+ * looks before it gives up, 0 = once, below zero = the usual number.  _count: sets the number of items that are done of `image` in the
+ * first block to `value`, in what such launches keep beside the workspace of `stream` (or, with `shared` not 0, beside that of
+ * qrm_detect_static): with all ones the number that the launch waits for never comes up.  Synchronises the device.
+ */
+QRM_API qrm_status qrm_diag_chain_patience(qrm_ctx *ctx, int32_t looks);
+QRM_API qrm_status qrm_diag_chain_count(qrm_ctx *ctx, void *stream, int32_t shared, int32_t image, uint32_t value);
+
+/*
+ * Whether n_img tiles of h x w go through `blocks` blocks of `channels` in one launch on num_cu compute units: *fits such a launch takes
+ * them, *taken it does so by the rule.  Host code, no device needed.
+ */
+QRM_API qrm_status qrm_diag_chain_rule(int32_t channels, int32_t blocks, int32_t n_img, int32_t h, int32_t w, int32_t num_cu,
+                                       int32_t *fits, int32_t *taken);
+
+/*
  * The rate the matrix pipes sustain when nothing else runs - eight wavefronts per compute unit issuing the bf16
  * 32x32x16 matrix instruction back to back for a few milliseconds - on operands of the given kind: data = 0
  * zeros, 1 one constant, 2 random (one side small normal values like weights, the other half zeros and half

@@ -1967,6 +1967,8 @@ __global__ __launch_bounds__(256, 4) void conv_first_kernel(TileSrc src, ConvGeo
 // rows instead of strips of four, records shared by the wavefronts and the correction behind the products are 3 % faster, 7 tiles of
 // 128 x 128, eight blocks and the head 106.7 us instead of 110.3, but then a tile's logits change with the number of tiles.)
 //   The state (ChainState) is all zeros when the launch begins; the launch behind it, which reads its results, clears it again.
+//   Waits are bounded all the same.  An item whose wait has run out is not counted, nor then is any that waits for it, and the first such wait
+// cuts the others short; the launch behind finds the counts wrong, gives NaN for the image's logits and tells the host (ChainState::lost).
 // ------------------------------------------------------------------------------------------------
 struct ChainArgs {
     TileSrc src;
@@ -1980,13 +1982,17 @@ struct ChainArgs {
     float *lines;             // what the last block leaves, or null: it writes activations as the others do
     int64_t lines_stride;     // floats from image to image
     uint32_t *state;          // ChainState
+    int patience;             // looks that a wait takes
     int chunk, chunks;        // images that an XCD takes at a time, chunks of them
 };
-// ChainState, in words: chunks claimed; from kChainTeamAt on, for every XCD, numbers drawn and the chunks it has claimed (plus one); from
-// kChainCountAt on, for every block and image, items done.  (A line of 128 bytes for what is counted apart.)
+// ChainState, in words: chunks claimed; from kChainTeamAt on, for every XCD, numbers drawn, the chunks it has claimed (plus one) and, at
+// kChainGaveUp, whether a wait has run out; from kChainCountAt on, for every block and image, items done.  (A line of 128 bytes for what
+// is counted apart.)
 constexpr int kChainTeamAt = 32, kChainTeams = 8, kChainTeam = 32, kChainCountAt = kChainTeamAt + kChainTeams * kChainTeam, kChainCount = 32;
+constexpr int kChainGaveUp = 16;
 constexpr int kChainCols = 32;
-constexpr int kChainPatience = 1 << 22; // polls, seconds: never reached (see above), but a fault elsewhere is not to hang the device
+constexpr int kChainPatience = 1 << 22; // looks, seconds: never reached (see above), but a fault elsewhere is not to hang the device
+constexpr int kChainLook = 1024;        // so many looks apart, a wait sees whether another one has run out
 
 // WAVES of a workgroup, RW: rows that a wavefront multiplies at a time, STEPS: times it does
 template <int C, int WAVES, int RW, int STEPS>
@@ -2109,6 +2115,13 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
         if ((tid & 63) == 0) t = __hip_atomic_fetch_add(team + pin_in_loop(0), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return t;
     };
+    // the look number `polls` of a wait is its last one
+    auto out_of_patience = [&](int polls) {
+        return polls >= a.patience || (polls % kChainLook == 0 && __builtin_amdgcn_readfirstlane(__hip_atomic_load(team + kChainGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0);
+    };
+    auto give_up = [&]() {
+        if ((tid & 63) == 0) __hip_atomic_store(team + kChainGaveUp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     uint32_t my_chunk = 0, chunk_at = ~0u; // the chunk that numbers from chunk_at * items on are of, plus one
     auto drawn = [&](uint32_t answer, int to) __attribute__((always_inline)) {
         const uint32_t t = __builtin_amdgcn_readfirstlane(answer), q = t / items;
@@ -2124,7 +2137,8 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
         } else if (q != chunk_at) {
             int polls = 0;
             do my_chunk = __builtin_amdgcn_readfirstlane(__hip_atomic_load(team + 1 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            while (my_chunk == 0 && ++polls < kChainPatience); // (whoever drew the chunk's first number claims it at once)
+            while (my_chunk == 0 && !out_of_patience(++polls)); // (whoever drew the chunk's first number claims it at once)
+            if (my_chunk == 0) give_up(); // .. and this workgroup is done: nobody has the item
         }
         chunk_at = q;
         int i = (int)(t - q * items), b = 0, in_block = first_items, in_image = ipi0, across = a.g.colblks;
@@ -2154,23 +2168,27 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
         return Item{v[0], v[1], v[2], v[3]};
     };
     auto counter = [&](int b, int n) { return a.state + kChainCountAt + ((size_t)b * a.g.n_img + n) * kChainCount; };
-    // all items of image n in block b are done
+    // Until all items of image n in block b are done; the first wavefront knows whether they are.
     auto wait_for = [&](int b, int n) {
+        bool there = true;
         if (wave == 0) {
             const uint32_t all = (uint32_t)(b == 0 ? ipi0 : ipi);
             int polls = 0;
-            while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(counter(b, n), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < all && ++polls < kChainPatience) {}
+            do there = __builtin_amdgcn_readfirstlane(__hip_atomic_load(counter(b, n), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == all;
+            while (!there && !out_of_patience(++polls));
+            if (!there) give_up();
         }
         lds_barrier();
+        return there;
     };
     // The item is done but for its last stores; next: the answer to the draw, which is asked for when the item's rows are there: a workgroup
     // that drew before would hold two items of a block while others have none.
-    auto done = [&](const Item &it, uint32_t next) {
+    auto done = [&](const Item &it, uint32_t next, bool counts) {
         asm volatile("" ::: "memory");
         if (draws) drawn(next, parity);
         __builtin_amdgcn_s_waitcnt(kWaitVm0); // the stores are in the L2
         lds_barrier();                        // .. those of all wavefronts, which also are done with what is in LDS
-        if (tid == 0) __hip_atomic_fetch_add(counter(it.b, it.n), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (tid == 0 && counts) __hip_atomic_fetch_add(counter(it.b, it.n), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
 
     // Whether block b's rows of this strip leave sums
@@ -2363,7 +2381,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
                     }
                 }
             }
-            done(it, next);
+            done(it, next, true);
             it = next_item();
         } while (it.b == 0);
     };
@@ -2402,7 +2420,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
                 const bool ok = sl < G::SLOTS && cpos < C / 8 && (uint32_t)y < (uint32_t)a.g.h && (uint32_t)x < (uint32_t)a.g.w;
                 voff[k] = ok ? (uint32_t)((y * a.g.w + x) * (C * 2) + cpos * 16) : kOutside;
             }
-            wait_for(it.b - 1, it.n);
+            const bool there = wait_for(it.b - 1, it.n); // (if not, what follows is of no use, but within its bounds)
             // The rows, the records of the image, the other weights: in the order in which they are looked at (loads of a wavefront return
             // in order).
             const uint8_t *in = a.act[(it.b - 1) & 1] + (size_t)it.n * img_bytes;
@@ -2560,7 +2578,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
                     }
                 }
             }
-            done(it, next);
+            done(it, next, there);
             it = next_item();
         } while (it.b > 0);
     };
@@ -2573,13 +2591,22 @@ __global__ __launch_bounds__(64 * WAVES, 1) void conv_chain_kernel(ChainArgs a)
     }
 }
 
-// The state of conv_chain_kernel's launch back to zeros, by the launch behind it: image n's counters, and for n = 0 what else there is.
-__device__ __forceinline__ void clear_chain(const ChainState &c, int64_t n, int tid, int threads)
+// The state of conv_chain_kernel's launch back to zeros, by a wavefront of the launch behind it: image n's counters, and for n = 0 what
+// else there is.  Whether items of the image are missing; the host hears of it, too.
+__device__ __forceinline__ bool clear_chain(const ChainState &c, int64_t n, int lane)
 {
-    if (!c.words) return;
+    if (!c.words) return false;
+    bool missing = false;
+    if (lane < c.blocks) {
+        uint32_t *counter = c.words + kChainCountAt + ((size_t)lane * c.n_img + n) * kChainCount;
+        missing = *counter != (lane == 0 ? c.first_items : c.items);
+        *counter = 0u;
+    }
     if (n == 0)
-        for (int i = tid; i < kChainCountAt; i += threads) c.words[i] = 0u;
-    for (int b = tid; b < c.blocks; b += threads) c.words[kChainCountAt + ((size_t)b * c.n_img + n) * kChainCount] = 0u;
+        for (int i = lane; i < kChainCountAt; i += 64) c.words[i] = 0u;
+    const bool lost = __ballot(missing) != 0;
+    if (lost && lane == 0 && c.lost) __hip_atomic_store(c.lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return lost;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2635,8 +2662,8 @@ __device__ __forceinline__ f32x4 sum_line_groups(const f32x4 *p, int stride, int
 }
 
 // The image's word from its bits (sbit), by 16 lanes, one symbol each; the errors (a chain of table look-ups) are found by all of them
-// alike.
-__device__ __forceinline__ void decode_image_word(const WordArgs &word, const uint8_t *tab, const uint8_t *sbit, int64_t img, int i)
+// alike.  lost: there are no bits, and no word.
+__device__ __forceinline__ void decode_image_word(const WordArgs &word, const uint8_t *tab, const uint8_t *sbit, int64_t img, int i, bool lost)
 {
     const RsParams &p = word.rs;
     const int ord = p.q - 1;
@@ -2658,14 +2685,14 @@ __device__ __forceinline__ void decode_image_word(const WordArgs &word, const ui
     }
     if (mine && word.cw) word.cw[img * p.n + i] = (uint8_t)sym;
     if (i < p.k) word.msg[img * p.k + i] = (uint8_t)sym;
-    if (i == 0) word.nerr[img] = (int8_t)(err.ok ? err.count : -1);
+    if (i == 0) word.nerr[img] = (int8_t)(err.ok && !lost ? err.count : -1);
     if (word.key.matches) {
         int agree = i < p.k ? p.m - __popc((uint32_t)(sym ^ word.key.key[i]) & (uint32_t)ord) : 0;
 #pragma unroll
         for (int off = 8; off >= 1; off >>= 1) agree += __shfl_xor(agree, off, 16);
         if (i == 0) {
-            word.key.matches[img] = agree;
-            if (word.key.detected) word.key.detected[img] = (uint8_t)(agree >= word.key.tau);
+            word.key.matches[img] = lost ? 0 : agree;
+            if (word.key.detected) word.key.detected[img] = (uint8_t)(!lost && agree >= word.key.tau);
         }
     }
 }
@@ -2719,9 +2746,10 @@ __global__ __launch_bounds__(kHeadThreads, 4) void head_kernel(const float *__re
     __shared__ __attribute__((aligned(16))) float part[kHeadWaves][IPB][64 * NB];
     __shared__ __attribute__((aligned(16))) float pooled[IPB][64 * NB];
     __shared__ uint8_t sbit[IPB][64 * NB];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    __shared__ bool s_lost; // (IPB 1)
+    // (128 registers, no scratch: 64 outputs of 64 channels fit with the wavefront's number in a scalar, 128 of 32 channels without)
+    const int tid = threadIdx.x, wave = NB == 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6, lane = tid & 63;
     const int64_t img0 = (int64_t)blockIdx.x * IPB;
-    if (IPB == 1) clear_chain(chain, img0, tid, kHeadThreads);
     // final conv + pool: LPO lanes share the outputs of a k = (channel, tap), four each; a part of KLEN of them
     constexpr int nbp = 64 * NB, LPO = nbp / 4, KLEN = C * 9 * LPO / kHeadThreads, PRE = IPB > 1 ? 0 : NB == 2 ? 12 : KLEN;
     const int ol = tid % LPO, k0 = tid / LPO * KLEN;
@@ -2760,8 +2788,12 @@ __global__ __launch_bounds__(kHeadThreads, 4) void head_kernel(const float *__re
             const int half = (sums.corners - sums.rows) / 2;
             total(sums.rows, half, sub, LPW, &Q[i][1 * C]);
             total(sums.rows + half, half, sub, LPW, &Q[i][2 * C]);
-        } else if (sub < 4) {
-            *(f32x4 *)&Q[i][(5 + sub) * C + 4 * l] = p[(sums.corners + sub) * LPL];
+        } else {
+            if (sub < 4) *(f32x4 *)&Q[i][(5 + sub) * C + 4 * l] = p[(sums.corners + sub) * LPL];
+            if (IPB == 1) { // (this wavefront has the least to do)
+                const bool lost = clear_chain(chain, img0, lane);
+                if (lane == 0) s_lost = lost;
+            }
         }
     }
     __syncthreads();
@@ -2824,6 +2856,7 @@ __global__ __launch_bounds__(kHeadThreads, 4) void head_kernel(const float *__re
         float v = 0.f;
 #pragma unroll
         for (int kp = 0; kp < kHeadWaves; ++kp) v += part[kp][i][o];
+        if (IPB == 1 && s_lost) v = __builtin_nanf(""); // (and so is every logit)
         pooled[i][o] = o < n_bits ? v * inv_hw + (fbias ? fbias[o] : 0.f) : 0.f;
     }
     __syncthreads();
@@ -2851,7 +2884,8 @@ __global__ __launch_bounds__(kHeadThreads, 4) void head_kernel(const float *__re
             if (img0 + i < n_img) symbols[(img0 + i) * nsym + j] = (uint8_t)sym;
         }
     }
-    if (word.rs.tab && tid < 16 * IPB && img0 + tid / 16 < n_img) decode_image_word(word, s_tab, sbit[tid / 16], img0 + tid / 16, tid % 16);
+    if (word.rs.tab && tid < 16 * IPB && img0 + tid / 16 < n_img)
+        decode_image_word(word, s_tab, sbit[tid / 16], img0 + tid / 16, tid % 16, IPB == 1 && s_lost);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2870,17 +2904,22 @@ __global__ __launch_bounds__(kHeadThreads) void linear_pack_kernel(const float *
     __shared__ __attribute__((aligned(16))) float part[kHeadThreads * 4];
     __shared__ __attribute__((aligned(16))) float pooled[nbp];
     __shared__ uint8_t sbit[nbp];
+    __shared__ bool s_lost;
     const int64_t n = blockIdx.x;
     const int tid = threadIdx.x, o = tid;
-    clear_chain(chain, n, tid, kHeadThreads);
     Linear<NB> linear;
     linear.weights(lin_w, tid);
     *(f32x4 *)&part[tid * 4] = sum_lines((const f32x4 *)partial + n * lines * lpl + tid % lpl, lpl, tid / lpl, groups, lines);
+    if (tid < 64) {
+        const bool lost = clear_chain(chain, n, tid);
+        if (tid == 0) s_lost = lost;
+    }
     __syncthreads();
     if (o < nbp) {
         float s = 0.f;
 #pragma unroll
         for (int g2 = 0; g2 < groups; ++g2) s += part[g2 * nbp + o];
+        if (s_lost) s = __builtin_nanf(""); // (and so is every logit)
         pooled[o] = o < n_bits ? s * inv_hw + (fbias ? fbias[o] : 0.f) : 0.f;
     }
     __syncthreads();
@@ -2911,8 +2950,8 @@ __global__ __launch_bounds__(256) void clear_chain_kernel(uint32_t *state)
 __global__ __launch_bounds__(256) void nhwc_to_nchw_kernel(const bf16_t *__restrict__ in, int64_t total, int hw, int C,
                                                            float *__restrict__ out, ChainState chain)
 {
-    if (blockIdx.x == 0)
-        for (int n = 0; n < chain.n_img; ++n) clear_chain(chain, n, threadIdx.x, 256);
+    if (blockIdx.x == 0 && threadIdx.x < 64)
+        for (int n = 0; n < chain.n_img; ++n) clear_chain(chain, n, threadIdx.x);
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
         const int c = (int)(i % C);
         const int64_t p = i / C; // n*hw + pixel
@@ -3225,7 +3264,7 @@ ChainPlan conv_chain_plan(const ConvGeom &g, int C, int blocks, int num_cu)
         p.items = (int64_t)p.chunk * ((g.h + p.rows - 1) / p.rows) * colblks;
         if (p.rows == chain_most_rows(C) || p.items <= cu) break;
     }
-    p.fits = blocks >= 2 && (int64_t)g.n_img * blocks <= kChainCounters && g.n_img <= kHeadAlone && p.items * blocks < (1 << 24) &&
+    p.fits = blocks >= 2 && blocks <= 64 /* lanes of clear_chain */ && (int64_t)g.n_img * blocks <= kChainCounters && g.n_img <= kHeadAlone && p.items * blocks < (1 << 24) &&
              (int64_t)conv_chain_last_sums(g, C).lines * C * 4 <= (int64_t)g.h * g.w * C * 2;
     p.one_round = p.items <= cu;
     return p;
@@ -3271,11 +3310,11 @@ LastSums conv_chain_last_sums(const ConvGeom &g, int C)
 
 hipError_t launch_conv_chain(const TileSrc &src, const ConvGeom &g, int C, const ChainPlan &p, int blocks, const bf16_t *w_first,
                              const bf16_t *w_mid, const float *bias, const float *rsum, uint8_t *act0, uint8_t *act1, float *rec0,
-                             float *rec1, float *lines, uint32_t *state, int num_cu, hipStream_t s)
+                             float *rec1, float *lines, uint32_t *state, int patience, int num_cu, hipStream_t s)
 {
     if (!p.fits) return hipErrorInvalidValue;
     ChainArgs a{src, g, blocks, w_first, w_mid, bias, rsum, {act0, act1}, {rec0, rec1}, conv_first_samples(g, C), conv_mid_samples(g, C),
-                lines, (int64_t)g.h * g.w * C / 2, state, p.chunk, (g.n_img + p.chunk - 1) / p.chunk};
+                lines, (int64_t)g.h * g.w * C / 2, state, patience < 0 ? kChainPatience : patience, p.chunk, (g.n_img + p.chunk - 1) / p.chunk};
     const dim3 grid((unsigned)std::min<int64_t>(p.items * kChainTeams, num_cu));
     auto launch = [&](auto kernel, int waves) { hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, s, a); };
     if (C == 64) {
@@ -3289,6 +3328,14 @@ hipError_t launch_conv_chain(const TileSrc &src, const ConvGeom &g, int C, const
         else launch(conv_chain_kernel<32, 8, 2, 2>, 8);
     }
     return hipGetLastError();
+}
+
+uint32_t *chain_counter(uint32_t *words, int image) { return words + kChainCountAt + (size_t)image * kChainCount; }
+
+ChainState conv_chain_state(uint32_t *words, uint32_t *lost, const ConvGeom &g, const ChainPlan &p, int blocks)
+{
+    const uint32_t strips = (uint32_t)((g.h + p.rows - 1) / p.rows);
+    return ChainState{words, lost, blocks, g.n_img, strips * (uint32_t)g.colblks, strips * (uint32_t)((g.w + kChainCols - 1) / kChainCols)};
 }
 
 static_assert(kChainStateBytes == (size_t)(kChainCountAt + kChainCounters * kChainCount) * 4, "ChainState");

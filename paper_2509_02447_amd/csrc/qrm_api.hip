@@ -418,6 +418,12 @@ void time_end(qrm_ctx::Timed *t, hipStream_t s)
 
 namespace qrm {
 
+qrm_status report_lost(qrm_ctx *c)
+{
+    if (!c->h_lost || __atomic_exchange_n(c->h_lost, 0u, __ATOMIC_RELAXED) == 0) return QRM_OK;
+    return fail(c, QRM_E_DEVICE, "an earlier call's launch gave up waiting for its own workgroups: some of its logits are NaN, its bits and words there are not valid");
+}
+
 qrm_status run_extractor(qrm_ctx *c, uint8_t *base, ChainMemory &chain_memory, const WsLayout &L, TileSrc src, int64_t N, int h, int w, int n_run,
                          float *d_logits, uint8_t *d_bits, uint8_t *d_symbols, int m_sym, const WordArgs &word, float *d_act,
                          bool may_time, hipStream_t s)
@@ -472,13 +478,13 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, ChainMemory &chain_memory, c
                 if (e != hipSuccess) return hip_fail(c, e, "clear_chain launch");
             }
             chain_memory.dirty = true;
-            to_clear = ChainState{chain_memory.words, blocks, cnt};
+            to_clear = conv_chain_state(chain_memory.words, c->d_lost, g, chain, blocks);
             const bool last = is_last(blocks - 1);
             cur = (blocks - 1) & 1; // where the last block's activations are; without them, it reads the other one
             if (last) tail = (float *)buf[cur], last_sums = conv_chain_last_sums(g, c->C), cur ^= 1;
             qrm_ctx::Timed *t = time_begin(c, may_time, QRM_PROFILE_CHAIN, (first_flops + (blocks - 1) * block_flops) * cnt, s);
             e = launch_conv_chain(src, g, c->C, chain, blocks, c->d_w_first, c->d_w_mid[0], c->d_bias, c->d_rsum, base + buf_off[0],
-                                  base + buf_off[1], tb[0], tb[1], tail, chain_memory.words, launch_cu(c), s);
+                                  base + buf_off[1], tb[0], tb[1], tail, chain_memory.words, c->chain_patience, launch_cu(c), s);
             if (e != hipSuccess) return hip_fail(c, e, "conv_chain launch");
             time_end(t, s);
             b = blocks;
@@ -698,6 +704,13 @@ qrm_status qrm_create(const qrm_extractor_desc *ext, const qrm_rs_desc *rs, int 
         if (e == hipSuccess)
             e = hipMemcpy((uint8_t *)c->d_weights + frag_bytes, fl.data(), fl.size() * 4, hipMemcpyHostToDevice);
         if (e != hipSuccess) { (void)hipFree(c->d_weights); delete c; return hip_fail(nullptr, e, "hipMemcpy(weights)"); }
+        if (hipHostMalloc((void **)&c->h_lost, sizeof *c->h_lost, hipHostMallocDefault) == hipSuccess) {
+            *c->h_lost = 0;
+            if (hipHostGetDevicePointer((void **)&c->d_lost, c->h_lost, 0) != hipSuccess) c->d_lost = nullptr;
+        } else {
+            c->h_lost = nullptr;
+        }
+        (void)hipGetLastError(); // (without it, an image whose items are missing has its NaN logits all the same)
         for (QrmSlot &sl : c->slots) sl.chain.words = (uint32_t *)((uint8_t *)c->d_weights + chain_at + (&sl - c->slots) * kChainStateBytes);
         const bf16_t *fb = (const bf16_t *)c->d_weights;
         c->d_w_first = fb + frag_off[0];
@@ -718,12 +731,10 @@ qrm_status qrm_create(const qrm_extractor_desc *ext, const qrm_rs_desc *rs, int 
         c->rs = RsParams{rs->m, q, rs->n, rs->k, rs->n - rs->k, rs->fcr % (q - 1), nullptr, 0, 0};
         const std::vector<uint8_t> image = rs_table_image(c->rs, exp2, lg);
         e = hipMalloc(&c->d_tables, kKeyBytes + image.size());
-        if (e != hipSuccess) { if (c->d_weights) (void)hipFree(c->d_weights); delete c; return hip_fail(nullptr, e, "hipMalloc(tables)"); }
+        if (e != hipSuccess) { qrm_destroy(c); return hip_fail(nullptr, e, "hipMalloc(tables)"); }
         e = hipMemcpy((uint8_t *)c->d_tables + kKeyBytes, image.data(), image.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
-            (void)hipFree(c->d_tables);
-            if (c->d_weights) (void)hipFree(c->d_weights);
-            delete c;
+            qrm_destroy(c);
             return hip_fail(nullptr, e, "hipMemcpy(tables)");
         }
         c->rs.tab = (const uint8_t *)c->d_tables + kKeyBytes;
@@ -764,6 +775,7 @@ void qrm_destroy(qrm_ctx *c)
         if (s) (void)hipStreamDestroy(s);
     if (c->d_weights) (void)hipFree(c->d_weights);
     if (c->d_tables) (void)hipFree(c->d_tables);
+    if (c->h_lost) (void)hipHostFree(c->h_lost);
     delete c;
 }
 
@@ -917,10 +929,12 @@ static qrm_status extractor_common(qrm_ctx *c, const uint8_t *d_tiles, int64_t N
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
     hipStream_t s = (hipStream_t)stream;
+    qrm_status st = report_lost(c);
+    if (st != QRM_OK) return st;
     WsLayout L = ws_layout(c, N, h, w, false);
     if (L.mb < 1) return fail(c, QRM_E_UNSUPPORTED, "the activations of one tile exceed 1900 MiB");
     QrmSlot *slot = nullptr;
-    qrm_status st = get_slot(c, s, L.total, &slot);
+    st = get_slot(c, s, L.total, &slot);
     if (st != QRM_OK) return st;
     TileSrc src{d_tiles, nullptr, h, w, {c->mean[0], c->mean[1], c->mean[2]},
                 {c->inv_std[0], c->inv_std[1], c->inv_std[2]}};
@@ -1051,6 +1065,8 @@ static qrm_status detect_common(qrm_ctx *c, const uint8_t *d_images, int64_t N, 
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
     hipStream_t s = (hipStream_t)stream;
+    st = report_lost(c);
+    if (st != QRM_OK) return st;
     WsLayout L = ws_layout(c, N, tile, tile, true);
     if (L.mb < 1) return fail(c, QRM_E_UNSUPPORTED, "the activations of one tile exceed 1900 MiB");
     QrmSlot *slot = nullptr;
@@ -1278,6 +1294,7 @@ qrm_status qrm_detect_host(qrm_ctx *c, const uint8_t *const *h_chunks, int32_t n
         if (e != hipSuccess && st == QRM_OK) st = hip_fail(c, e, "hipStreamSynchronize");
     }
     c->in_host_pipeline = false;
+    if (st == QRM_OK) st = report_lost(c);
     if (timeline && st == QRM_OK) c->chunks_timed = (size_t)submitted;
     return st;
 }

@@ -46,6 +46,7 @@ struct qrm_ctx {
     const float *d_wft = nullptr;         // final conv, fp32, [C*9][nbp]
     bool collapse = false;                // final conv + pool evaluated in closed form from channel sums
     bool pairable = false;                // weights are prepared for the fused schedule (see qrm_create)
+    uint32_t *h_lost = nullptr, *d_lost = nullptr; // page-locked: a launch has given up waiting for its own workgroups (report_lost)
     // code
     qrm::RsParams rs{};
     void *d_tables = nullptr;             // key symbols [kKeyBytes], then the code's table image (rs_table_image)
@@ -56,6 +57,7 @@ struct qrm_ctx {
     QrmSlot slots[QRM_MAX_STREAMS + 1];
     uint64_t use_clock = 0;
     int diag_flags = 0;  // QRM_DIAG_* (include/qrm_diag.h); 0 in production
+    int chain_patience = -1; // looks of a wait in conv_chain_kernel, below zero the usual number (qrm_diag_chain_patience)
     // optional per-launch timing of the convolution kernels (hipEvents on the launch stream)
     bool profile = false;
     struct Timed {
@@ -107,12 +109,17 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, ChainMemory &chain_memory, c
                          float *d_logits, uint8_t *d_bits, uint8_t *d_symbols, int m_sym, const WordArgs &word, float *d_act,
                          bool may_time, hipStream_t s);
 
+// QRM_E_DEVICE, once, if an earlier call's launch has lost images.
+qrm_status report_lost(qrm_ctx *c);
+
 // Argument checks shared by the entry points that run the whole detection path.
 qrm_status check_detect_args(qrm_ctx *c, const uint8_t *d_images, int64_t N, int32_t H, int32_t W, int32_t tile,
                              uint8_t *d_msg, int8_t *d_nerr, bool verify, int32_t *d_matches);
 
 // qrm_noalloc.hip: looks up the device address of the static workspace on `device` (which must be current)
 hipError_t static_scratch_init(int device);
+// .. and what all-blocks launches keep beside it (null: static_scratch_init has failed there)
+ChainMemory *static_chain_memory(int device);
 
 inline size_t symbols_offset(const WsLayout &L) { return 2 * L.act + L.tail + 2 * L.stats + L.seam; }
 

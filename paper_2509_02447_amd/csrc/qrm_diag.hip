@@ -58,6 +58,45 @@ qrm_status qrm_diag_set_flags(qrm_ctx *c, int32_t flags)
     return QRM_OK;
 }
 
+qrm_status qrm_diag_chain_patience(qrm_ctx *c, int32_t looks)
+{
+    if (!c) return QRM_E_INVALID;
+    c->chain_patience = looks;
+    return QRM_OK;
+}
+
+// The state that launches on `stream` (or qrm_detect_static's) keep, or null.
+static ChainMemory *chain_memory(qrm_ctx *c, void *stream, int shared)
+{
+    if (shared) return static_chain_memory(c->device);
+    for (QrmSlot &sl : c->slots)
+        if (sl.used && sl.stream == (hipStream_t)stream && sl.chain.words) return &sl.chain;
+    return nullptr;
+}
+
+qrm_status qrm_diag_chain_count(qrm_ctx *c, void *stream, int32_t shared, int32_t image, uint32_t value)
+{
+    if (!c) return QRM_E_INVALID;
+    ChainMemory *m = chain_memory(c, stream, shared);
+    if (!m || image < 0 || image >= kChainCounters) return fail(c, QRM_E_INVALID, "no such workspace or image");
+    hipError_t e = hipSetDevice(c->device);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = hipMemcpy(chain_counter(m->words, image), &value, sizeof value, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(c, e, "hipMemcpy(chain state)");
+    return QRM_OK;
+}
+
+qrm_status qrm_diag_chain_rule(int32_t channels, int32_t blocks, int32_t n_img, int32_t h, int32_t w, int32_t num_cu, int32_t *fits,
+                               int32_t *taken)
+{
+    if ((channels != 32 && channels != 64) || blocks < 1 || n_img < 1 || h < 1 || w < 1 || num_cu < 1 || !fits || !taken) return QRM_E_INVALID;
+    const ConvGeom g{n_img, h, w, (h + kRows - 1) / kRows, (w + kTileW - 1) / kTileW};
+    const ChainPlan p = conv_chain_plan(g, channels, blocks, num_cu);
+    *fits = p.fits;
+    *taken = p.fits && conv_chain_faster(g, channels, p, blocks, num_cu);
+    return QRM_OK;
+}
+
 qrm_status qrm_diag_matrix_rate(qrm_ctx *c, int32_t data, double *tflops)
 {
     if (!c) return QRM_E_INVALID;

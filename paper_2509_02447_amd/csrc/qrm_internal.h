@@ -149,18 +149,22 @@ constexpr size_t kChainStateBytes = (size_t)(9 * 32 + kChainCounters * 32) * 4; 
 // That memory when the launch behind conv_chain's is to clear it (words null: it is not), and what the launch was about.
 struct ChainState {
     uint32_t *words;
+    uint32_t *lost;              // set where items are missing (null: nobody is told)
     int blocks, n_img;
+    uint32_t first_items, items; // of an image, in the first block and in another one
 };
+uint32_t *chain_counter(uint32_t *words, int image); // items that the first block has done of it
+ChainState conv_chain_state(uint32_t *words, uint32_t *lost, const ConvGeom &g, const ChainPlan &p, int blocks);
 ChainPlan conv_chain_plan(const ConvGeom &g, int C, int blocks, int num_cu);
 bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int blocks, int num_cu);
 LastSums conv_chain_last_sums(const ConvGeom &g, int C);
 // blocks: of the network, from the first on; block b writes act[b & 1] and sampled channel sums to rec[b & 1] (conv_first_samples(),
 // then those of conv_mid_samples()).  lines not null: the
 // last of them leaves lines of sums there, an image's in the place of its activations (conv_chain_last_sums()).  state: all zeros;
-// the launch behind this one clears it.
+// the launch behind this one clears it.  patience: looks that a wait takes before it gives up (below zero: the usual number).
 hipError_t launch_conv_chain(const TileSrc &src, const ConvGeom &g, int C, const ChainPlan &p, int blocks, const bf16_t *w_first,
                              const bf16_t *w_mid, const float *bias, const float *rsum, uint8_t *act0, uint8_t *act1, float *rec0,
-                             float *rec1, float *lines, uint32_t *state, int num_cu, hipStream_t s);
+                             float *rec1, float *lines, uint32_t *state, int patience, int num_cu, hipStream_t s);
 hipError_t launch_clear_chain(uint32_t *state, hipStream_t s);
 
 struct RsParams {

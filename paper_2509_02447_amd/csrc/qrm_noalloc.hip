@@ -41,6 +41,11 @@ hipError_t static_scratch_init(int device)
     return g_scratch_err[device];
 }
 
+ChainMemory *static_chain_memory(int device)
+{
+    return device >= 0 && device < kMaxDevices && g_chain[device].words ? &g_chain[device] : nullptr;
+}
+
 } // namespace qrm
 
 extern "C" qrm_status qrm_detect_static(qrm_ctx *c, const uint8_t *d_images, int64_t N, int32_t H, int32_t W,
@@ -56,6 +61,8 @@ extern "C" qrm_status qrm_detect_static(qrm_ctx *c, const uint8_t *d_images, int
         return fail(c, QRM_E_DEVICE, "the static workspace's address is not known on this device (hipGetSymbolAddress failed at qrm_create)");
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(c, e, "hipSetDevice");
+    st = report_lost(c);
+    if (st != QRM_OK) return st;
     uint8_t *ws = g_scratch_ptr[c->device]; // the device address: never the array's name
     hipStream_t s = (hipStream_t)stream;
 

@@ -554,6 +554,82 @@ def test_all_blocks_in_one_launch(qrm, C, nb, N, h, w, relu):
     check_logits(chain[0][:few], ref, what=f"chain C={C} {h}x{w}")
 
 
+def chain_buffers(cfg, n):
+    return (empty((n, cfg.n_bits), torch.float32), empty((n, cfg.n_bits), torch.uint8), empty((n, cfg.k), torch.uint8),
+            empty((n, cfg.n), torch.uint8), empty((n,), torch.int8))
+
+
+def assert_lost(cfg, out, want, lost):
+    """The images of `lost` have NaN logits, zero bits and no word, the others what they have in `want`."""
+    lost = torch.as_tensor(lost).cuda()
+    assert torch.isnan(out[0][lost]).all() and not out[1][lost].any() and (out[4][lost] == -1).all()
+    assert all(torch.equal(o[~lost], w[~lost]) for o, w in zip(out, want))
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_a_wait_that_runs_out_is_reported(qrm, static):
+    """All blocks in one launch, whose waits give up at the first look, or whose count of one image's items never comes up: every
+    kernel ends, the lost images have NaN logits and no word, the others their results, the next call says so once, and the one
+    after that is as ever."""
+    cfg = synth.CONFIGS["C1"]
+    ctx = qrm.Context(weights=synth.config_weights(cfg), rs=rs_dict(cfg))
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_CHAIN_ALWAYS)
+    N, side = 21, cfg.H
+    d_img, d_off = dev(synth.images(cfg, 0, N)), dev(synth.offsets(cfg, 0, N))
+    entry = ctx.qrm_detect_static if static else ctx.qrm_detect
+    want, out = chain_buffers(cfg, N), chain_buffers(cfg, N)
+    call = lambda to: (entry(d_img, N, side, side, d_off, cfg.tile, *to), torch.cuda.synchronize())
+    call(want)
+    assert torch.isfinite(want[0]).all()
+
+    def fails_once_then_recovers(lost):
+        assert_lost(cfg, out, want, lost)
+        with pytest.raises(qrm.QrmError, match="gave up waiting"):
+            call(out)
+        call(out)
+        assert all(torch.equal(o, w) for o, w in zip(out, want))
+
+    for image in (0, 13, N - 1):
+        ctx.qrm_diag_chain_patience(4000)
+        ctx.qrm_diag_chain_count(static, image, 0xFFFFFFFF)
+        call(out)
+        ctx.qrm_diag_chain_patience(-1)
+        lost = torch.isnan(out[0]).any(1)
+        assert bool(lost[image])               # (waits of the same XCD may have been cut short with it, and their images are lost as well)
+        fails_once_then_recovers(lost.cpu())
+    ctx.close()
+
+
+@pytest.mark.parametrize("relu", [0, 1])
+def test_a_wait_that_runs_out_without_patience(qrm, relu):
+    """The same through the extractor's entry points, behind either kind of last layer: a count that never comes up, waits of a few looks."""
+    wts = small_weights(64, 4, 24, 5)
+    tiles = dev(np.random.default_rng(3).integers(0, 256, size=(6, 3, 21, 70), dtype=np.uint8))
+    ctx = qrm.Context(weights=wts, final_relu=relu)
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_CHAIN_ALWAYS)
+    d_log, d_bits, d_act = empty((6, 24), torch.float32), empty((6, 24), torch.uint8), empty((6, 64, 21, 70), torch.float32)
+    ctx.qrm_extractor_forward(tiles, 6, 21, 70, d_log, d_bits)
+    torch.cuda.synchronize()
+    want = d_log.clone()
+    for run in (lambda: ctx.qrm_extractor_forward(tiles, 6, 21, 70, d_log, d_bits), lambda: ctx.qrm_extractor_blocks(tiles, 6, 21, 70, 3, d_act)):
+        ctx.qrm_diag_chain_patience(4000)
+        ctx.qrm_diag_chain_count(False, 4, 0xFFFFFFFF)
+        run()
+        torch.cuda.synchronize()
+        ctx.qrm_diag_chain_patience(-1)
+        with pytest.raises(qrm.QrmError, match="gave up waiting"):
+            run()
+    ctx.qrm_diag_chain_count(False, 4, 0)
+    ctx.qrm_extractor_forward(tiles, 6, 21, 70, d_log, d_bits)
+    torch.cuda.synchronize()
+    assert torch.equal(d_log, want)
+    ctx.qrm_diag_chain_patience(0)
+    ctx.qrm_extractor_forward(tiles, 6, 21, 70, d_log, d_bits)
+    torch.cuda.synchronize()
+    assert ((d_log == want) | torch.isnan(d_log)).all() and not d_bits[torch.isnan(d_log)].any()
+    ctx.close()
+
+
 def test_all_blocks_in_one_launch_captured(qrm):
     """The same in a captured graph, on the static workspace: every replay, with eager calls of other sizes between them, gives the
     bits of a call outside."""
