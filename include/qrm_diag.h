@@ -35,10 +35,12 @@ QRM_API qrm_status qrm_diag_set_flags(qrm_ctx *ctx, int32_t flags);
  * For tests of what happens when the workgroups of an all-blocks launch do not hear from each other.  _patience: how often a wait
  * looks before it gives up, 0 = once, below zero = the usual number.  _count: sets the number of items that are done of `image` in the
  * first block to `value`, in what such launches keep beside the workspace of `stream` (or, with `shared` not 0, beside that of
- * qrm_detect_static): with all ones the number that the launch waits for never comes up.  Synchronises the device.
+ * qrm_detect_static): with all ones the number that the launch waits for never comes up.  _left_over: all of that as a call leaves it
+ * whose all-blocks launch has run and whose next one has failed: every word `value`, and marked.  Both synchronise the device.
  */
 QRM_API qrm_status qrm_diag_chain_patience(qrm_ctx *ctx, int32_t looks);
 QRM_API qrm_status qrm_diag_chain_count(qrm_ctx *ctx, void *stream, int32_t shared, int32_t image, uint32_t value);
+QRM_API qrm_status qrm_diag_chain_left_over(qrm_ctx *ctx, void *stream, int32_t shared, uint32_t value);
 
 /*
  * Whether n_img tiles of h x w go through `blocks` blocks of `channels` in one launch on num_cu compute units: *fits such a launch takes

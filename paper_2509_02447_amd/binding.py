@@ -43,7 +43,8 @@ EXPORTS = ["qrm_create", "qrm_destroy", "qrm_last_error", "qrm_set_micro_batch",
            "qrm_profile_enable", "qrm_profile_read", "qrm_profile_read_chunks", "qrm_release_stream", "qrm_detect_static", "qrm_version"]
 DIAG_EXPORTS = ["qrm_diag_set_flags", "qrm_diag_matrix_rate", "qrm_diag_pair_split",
                 "qrm_diag_wide_schedule", "qrm_diag_last_lines", "qrm_diag_host_plan",
-                "qrm_diag_preprocess_strips", "qrm_diag_rs_lanes", "qrm_diag_chain_patience", "qrm_diag_chain_count", "qrm_diag_chain_rule"]   # include/qrm_diag.h: bench and test tooling
+                "qrm_diag_preprocess_strips", "qrm_diag_rs_lanes", "qrm_diag_chain_patience", "qrm_diag_chain_count",
+                "qrm_diag_chain_left_over", "qrm_diag_chain_rule"]   # include/qrm_diag.h: bench and test tooling
 
 QRM_MAX_STREAMS = 8   # include/qrm.h
 QRM_DIAG_NO_FUSED_PAIRS, QRM_DIAG_POISON_WORKSPACE, QRM_DIAG_FUSE_ALWAYS, QRM_DIAG_CHAIN_ALWAYS, QRM_DIAG_NO_CHAIN = 1, 2, 4, 8, 16
@@ -134,6 +135,8 @@ def load_library():
     lib.qrm_diag_chain_patience.restype = C.c_int
     lib.qrm_diag_chain_count.argtypes = [vp, vp, i32, i32, C.c_uint32]
     lib.qrm_diag_chain_count.restype = C.c_int
+    lib.qrm_diag_chain_left_over.argtypes = [vp, vp, i32, C.c_uint32]
+    lib.qrm_diag_chain_left_over.restype = C.c_int
     lib.qrm_diag_chain_rule.argtypes = [i32] * 6 + [C.POINTER(i32)] * 2
     lib.qrm_diag_chain_rule.restype = C.c_int
     lib.qrm_version.argtypes = []
@@ -287,6 +290,9 @@ class Context:
 
     def qrm_diag_chain_count(self, shared: bool, image: int, value: int, stream=None):
         self._check(self._lib.qrm_diag_chain_count(self._h, _stream_handle(stream), int(bool(shared)), int(image), int(value)))
+
+    def qrm_diag_chain_left_over(self, shared: bool, value: int, stream=None):
+        self._check(self._lib.qrm_diag_chain_left_over(self._h, _stream_handle(stream), int(bool(shared)), int(value)))
 
     def qrm_diag_matrix_rate(self, data: int) -> float:
         """-> TFLOP/s the matrix pipes sustain on zeros (0), a constant (1) or random operands (2)."""

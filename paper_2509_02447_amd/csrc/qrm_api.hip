@@ -472,8 +472,11 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, ChainMemory &chain_memory, c
         int b = 1;
         const ChainPlan chain = chain_plan(c, cnt, h, w, blocks);
         ChainState to_clear{};  // by the launch behind the chain's
+        bool stays_dirty = false;
         if (chain.fits) {
             if (chain_memory.dirty) {
+                hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+                stays_dirty = hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone;
                 e = launch_clear_chain(chain_memory.words, s);
                 if (e != hipSuccess) return hip_fail(c, e, "clear_chain launch");
             }
@@ -539,7 +542,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, ChainMemory &chain_memory, c
         if (n_run > 0) {
             e = launch_nhwc_to_nchw(buf[cur], cnt, h, w, c->C, d_act + n0 * (int64_t)c->C * h * w, to_clear, s);
             if (e != hipSuccess) return hip_fail(c, e, "nhwc_to_nchw launch");
-            if (to_clear.words) chain_memory.dirty = false;
+            if (to_clear.words) chain_memory.dirty = stays_dirty;
             continue;
         }
         float *lg = d_logits ? d_logits + n0 * c->n_bits : nullptr;
@@ -561,7 +564,7 @@ qrm_status run_extractor(qrm_ctx *c, uint8_t *base, ChainMemory &chain_memory, c
                                    m_sym > 0 ? m_sym : 1, to_clear, s);
             if (e != hipSuccess) return hip_fail(c, e, "linear_pack launch");
         }
-        if (to_clear.words) chain_memory.dirty = false;
+        if (to_clear.words) chain_memory.dirty = stays_dirty;
         time_end(t, s);
     }
     return QRM_OK;

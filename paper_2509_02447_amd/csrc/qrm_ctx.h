@@ -10,7 +10,8 @@
 constexpr size_t kKeyBytes = 256; // one byte per message symbol
 
 // kChainStateBytes of device memory for conv_chain_kernel's launches (ChainState); dirty: such a launch was enqueued and the one
-// that clears the memory behind it was not, as the call failed in between.
+// that clears the memory behind it was not, as the call failed in between.  Only work that is known to run takes the mark away: a
+// clearing launch that was recorded into a graph has not cleared anything yet.
 struct ChainMemory {
     uint32_t *words = nullptr;
     bool dirty = false;

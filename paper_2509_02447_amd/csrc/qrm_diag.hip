@@ -86,6 +86,20 @@ qrm_status qrm_diag_chain_count(qrm_ctx *c, void *stream, int32_t shared, int32_
     return QRM_OK;
 }
 
+qrm_status qrm_diag_chain_left_over(qrm_ctx *c, void *stream, int32_t shared, uint32_t value)
+{
+    if (!c) return QRM_E_INVALID;
+    ChainMemory *m = chain_memory(c, stream, shared);
+    if (!m) return fail(c, QRM_E_INVALID, "no such workspace");
+    const std::vector<uint32_t> words(kChainStateBytes / 4, value);
+    hipError_t e = hipSetDevice(c->device);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = hipMemcpy(m->words, words.data(), kChainStateBytes, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(c, e, "hipMemcpy(chain state)");
+    m->dirty = true;
+    return QRM_OK;
+}
+
 qrm_status qrm_diag_chain_rule(int32_t channels, int32_t blocks, int32_t n_img, int32_t h, int32_t w, int32_t num_cu, int32_t *fits,
                                int32_t *taken)
 {

@@ -600,6 +600,43 @@ def test_a_wait_that_runs_out_is_reported(qrm, static):
     ctx.close()
 
 
+@pytest.mark.parametrize("static", [False, True])
+def test_what_a_failed_call_left_is_cleared_by_work_that_runs(qrm, static):
+    """The state of an all-blocks launch whose clearing launch never came: the next call clears it, and one that is only recorded into a
+    graph leaves that to the one after it; the graph, whenever it is replayed, gives the results, too."""
+    cfg = synth.CONFIGS["C1"]
+    ctx = qrm.Context(weights=synth.config_weights(cfg), rs=rs_dict(cfg))
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_CHAIN_ALWAYS)
+    N, side = 21, cfg.H
+    d_img, d_off = dev(synth.images(cfg, 0, N)), dev(synth.offsets(cfg, 0, N))
+    entry = ctx.qrm_detect_static if static else ctx.qrm_detect
+    want, out, replayed = chain_buffers(cfg, N), chain_buffers(cfg, N), chain_buffers(cfg, N)
+    call = lambda to: entry(d_img, N, side, side, d_off, cfg.tile, *to)
+    stream = torch.cuda.Stream()
+    equal = lambda got: all(torch.equal(o, w) for o, w in zip(got, want))
+    with torch.cuda.stream(stream):
+        call(want)
+        torch.cuda.synchronize()
+        ctx.qrm_diag_chain_left_over(static, 7)
+        call(out)
+        torch.cuda.synchronize()
+        assert equal(out)
+        ctx.qrm_diag_chain_left_over(static, 7)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            call(replayed)
+        for i in range(3):
+            for t in out + replayed:
+                t.zero_()
+            call(out)
+            torch.cuda.synchronize()
+            assert equal(out), i
+            graph.replay()
+            torch.cuda.synchronize()
+            assert equal(replayed), i
+    ctx.close()
+
+
 @pytest.mark.parametrize("relu", [0, 1])
 def test_a_wait_that_runs_out_without_patience(qrm, relu):
     """The same through the extractor's entry points, behind either kind of last layer: a count that never comes up, waits of a few looks."""
