@@ -528,12 +528,14 @@ def test_all_blocks_in_one_launch(qrm, C, nb, N, h, w, relu):
     """All blocks of a batch in one launch against a launch per block: the same bits, in every layer too.  Several calls in a row, the
     first on a workspace filled with NaN: each finds the state that the one before left."""
     b = qrm.binding
+    launches = 0 if (C, h, w) == (32, 3, 5) else 3 + nb - 1   # (a single block is no chain)
     wts = small_weights(C, nb, 24, C + nb + h)
     tiles = np.random.default_rng(N * h + w).integers(0, 256, size=(N, 3, h, w), dtype=np.uint8)
     d_tiles, got = dev(tiles), {}
     for flag in (b.QRM_DIAG_CHAIN_ALWAYS, b.QRM_DIAG_NO_FUSED_PAIRS):
         ctx = qrm.Context(weights=wts, final_relu=relu)
         ctx.qrm_diag_set_flags(flag | b.QRM_DIAG_POISON_WORKSPACE)
+        ctx.qrm_profile_enable(True)
         out = []
         for _ in range(3):
             d_log = empty((N, 24), torch.float32)
@@ -545,6 +547,7 @@ def test_all_blocks_in_one_launch(qrm, C, nb, N, h, w, relu):
             out.append(d_act)
         torch.cuda.synchronize()
         got[flag] = [t.cpu().numpy() for t in out]
+        assert ctx.qrm_profile_read(b.QRM_PROFILE_CHAIN)[1] == (launches if flag == b.QRM_DIAG_CHAIN_ALWAYS else 0)
         ctx.close()
     chain, single = got.values()
     assert np.array_equal(chain[0], chain[1]) and np.array_equal(chain[0], chain[2])
@@ -667,31 +670,43 @@ def test_a_wait_that_runs_out_without_patience(qrm, relu):
     ctx.close()
 
 
-def test_all_blocks_in_one_launch_captured(qrm):
-    """The same in a captured graph, on the static workspace: every replay, with eager calls of other sizes between them, gives the
-    bits of a call outside."""
+@pytest.mark.parametrize("static", [False, True])
+def test_all_blocks_in_one_launch_captured(qrm, static):
+    """The same in a captured graph, on a context's workspace and on the static one: every replay, with eager calls of other sizes
+    between them, gives the bits of a launch per block."""
     cfg = synth.CONFIGS["C1"]
     ctx = qrm.Context(weights=synth.config_weights(cfg), rs=rs_dict(cfg))
     N, side = 16, cfg.H
     d_img, d_off = dev(synth.images(cfg, 0, N)), dev(synth.offsets(cfg, 0, N))
-    bufs = lambda n: (empty((n, cfg.n_bits), torch.float32), empty((n, cfg.n_bits), torch.uint8), empty((n, cfg.k), torch.uint8),
-                      empty((n, cfg.n), torch.uint8), empty((n,), torch.int8))
-    call = lambda n, out: ctx.qrm_detect_static(d_img, n, side, side, d_off, cfg.tile, *out)
-    want, out, other = bufs(N), bufs(N), bufs(5)
-    call(N, want)
-    torch.cuda.synchronize()
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):
+    entry = ctx.qrm_detect_static if static else ctx.qrm_detect
+    call = lambda n, out: entry(d_img, n, side, side, d_off, cfg.tile, *out)
+    want, out, other = chain_buffers(cfg, N), chain_buffers(cfg, N), chain_buffers(cfg, 5)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_NO_CHAIN)
+        call(N, want)
+        ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_CHAIN_ALWAYS)
         call(N, out)
-    for _ in range(3):
-        for t in out:
-            t.zero_()
-        graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, e) for a, e in zip(out, want))
-        call(5, other)
-        torch.cuda.synchronize()
-        assert all(torch.equal(a, e[:5]) for a, e in zip(other, want))
+        ctx.qrm_diag_chain_patience(100000)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            call(N, out)
+        for _ in range(3):
+            for t in out:
+                t.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, e) for a, e in zip(out, want))
+            call(5, other)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, e[:5]) for a, e in zip(other, want))
+    # (that these calls were chains: a count that never comes up loses an image)
+    ctx.qrm_diag_chain_count(static, 3, 0xFFFFFFFF, stream=stream)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.isnan(out[0][3]).all() and not torch.isnan(other[0]).any()
     ctx.close()
 
 
@@ -1151,15 +1166,20 @@ def test_results_are_reproducible_bit_for_bit(qrm):
                 assert np.array_equal(runs[0][key], r[key]), (name, key, mb)
 
 
-def test_more_streams_than_workspaces(qrm):
+@pytest.mark.parametrize("name,chain", [("C2", False), ("C1", True)])
+def test_more_streams_than_workspaces(qrm, name, chain):
     """Twenty short-lived streams, one after the other, on one context (which holds QRM_MAX_STREAMS = 8 workspaces):
     a stream not seen before takes over the workspace used least recently.  Half of the streams are handed back
-    with qrm_release_stream before they are destroyed, half are just dropped."""
-    cfg = synth.CONFIGS["C2"]
+    with qrm_release_stream before they are destroyed, half are just dropped.  With `chain`, all blocks in one launch, whose state goes
+    with the workspace: the results are those of a launch per block."""
+    cfg = synth.CONFIGS[name]
     N = 6
     imgs, off = synth.images(cfg, 40, N), synth.offsets(cfg, 40, N)
     ctx = qrm.Context(weights=synth.config_weights(cfg), rs=rs_dict(cfg))
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_NO_CHAIN)
     base = run_detect(ctx, cfg, imgs, off)
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_CHAIN_ALWAYS if chain else 0)
+    ctx.qrm_profile_enable(chain)
     d_img, d_off = dev(imgs), dev(off)
     torch.cuda.synchronize()
     for i in range(20):
@@ -1185,6 +1205,7 @@ def test_more_streams_than_workspaces(qrm):
     for d_logits, d_msg, d_ne in outs:
         assert np.array_equal(d_logits.cpu().numpy(), base["logits"]) and np.array_equal(d_msg.cpu().numpy(), base["msg"])
     ctx.qrm_release_stream(torch.cuda.Stream())          # a stream the context never saw: no-op
+    assert ctx.qrm_profile_read(qrm.binding.QRM_PROFILE_CHAIN)[1] == (20 + 9 if chain else 0)
     ctx.close()
 
 
@@ -1210,6 +1231,66 @@ def test_detect_on_two_streams(qrm):
         assert np.array_equal(l.cpu().numpy(), base["logits"][i * N:(i + 1) * N])
         assert np.array_equal(m_.cpu().numpy(), base["msg"][i * N:(i + 1) * N])
         assert np.array_equal(e.cpu().numpy(), base["nerr"][i * N:(i + 1) * N])
+    ctx.close()
+
+
+def test_all_blocks_in_one_launch_on_two_streams(qrm):
+    """Launches of all blocks that run beside each other, of different sizes, many in a row on either stream, with calls of the
+    static workspace on a third: all give the bits of a launch per block."""
+    cfg = synth.CONFIGS["C1"]
+    N = 250
+    imgs, off = synth.images(cfg, 7, N), synth.offsets(cfg, 7, N)
+    ctx = qrm.Context(weights=synth.config_weights(cfg), rs=rs_dict(cfg))
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_NO_CHAIN)
+    d_img, d_off = dev(imgs), dev(off)
+    want = chain_buffers(cfg, N)
+    ctx.qrm_detect(d_img, N, cfg.H, cfg.W, d_off, cfg.tile, *want)
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_CHAIN_ALWAYS)
+    torch.cuda.synchronize()
+    counts = [250, 3, 40, 129, 8, 200, 17, 1, 96, 64]
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    outs = []
+    for i, n in enumerate(counts + counts[::-1]):
+        for j, s in enumerate(streams):
+            out = chain_buffers(cfg, n)
+            entry = ctx.qrm_detect_static if j == 2 else ctx.qrm_detect
+            s.wait_stream(torch.cuda.current_stream())
+            entry(d_img, n, cfg.H, cfg.W, d_off, cfg.tile, *out, stream=s)
+            outs.append((i, j, n, out))
+    torch.cuda.synchronize()
+    for i, j, n, out in outs:
+        assert all(torch.equal(o, w[:n]) for o, w in zip(out, want)), (i, j, n)
+    ctx.close()
+
+
+def test_all_blocks_in_one_launch_in_the_host_pipeline(qrm):
+    """Chunks streamed through networks of 32 channels whose launches of all blocks leave compute units to the gather of the next
+    chunk: as a launch per block on the same images in device memory, at every depth."""
+    import ctypes
+    cfg = synth.CONFIGS["C1"]
+    chunk, n_chunks = 100, 5
+    first, rest, lent = (ctypes.c_int32() for _ in range(3))
+    fits, taken = ctypes.c_int32(), ctypes.c_int32()
+    lib = qrm.load_library()
+    assert lib.qrm_diag_host_plan(cfg.channels, cfg.n_blocks, cfg.H, cfg.W, cfg.tile, chunk, 2, 256, first, rest, lent) == 0 and lent.value > 0
+    assert lib.qrm_diag_chain_rule(cfg.channels, cfg.n_blocks, chunk, cfg.tile, cfg.tile, 256, fits, taken) == 0 and taken.value
+    n = chunk * n_chunks
+    imgs, off = synth.images(cfg, 11, n, threads=HOST_THREADS), synth.offsets(cfg, 11, n)
+    ctx = qrm.Context(weights=synth.config_weights(cfg), rs=rs_dict(cfg))
+    ctx.qrm_diag_set_flags(qrm.binding.QRM_DIAG_NO_CHAIN)
+    base = run_detect(ctx, cfg, imgs, off)
+    pinned = torch.empty((n_chunks, chunk, 3, cfg.H, cfg.W), dtype=torch.uint8, pin_memory=True)
+    pinned.copy_(torch.from_numpy(imgs.reshape(pinned.shape)))
+    offs = torch.empty((n_chunks, chunk, 2), dtype=torch.int32, pin_memory=True)
+    offs.copy_(torch.from_numpy(off.reshape(offs.shape)))
+    for flag in (0, qrm.binding.QRM_DIAG_CHAIN_ALWAYS):
+        ctx.qrm_diag_set_flags(flag)
+        for depth in (1, 2, 3):
+            h_msg, h_cw = torch.zeros((n, cfg.k), dtype=torch.uint8), torch.zeros((n, cfg.n), dtype=torch.uint8)
+            h_ne = torch.zeros((n,), dtype=torch.int8)
+            ctx.qrm_detect_host(list(pinned), chunk, cfg.H, cfg.W, list(offs), cfg.tile, depth, h_msg, h_cw, h_ne)
+            assert np.array_equal(h_msg.numpy(), base["msg"]) and np.array_equal(h_cw.numpy(), base["codeword"]), (flag, depth)
+            assert np.array_equal(h_ne.numpy(), base["nerr"])
     ctx.close()
 
 
