@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqrm.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["qrm_api.hip", "extractor.hip", "rs_decode.hip", "tiles.hip", "qrm_noalloc.hip", "qrm_diag.hip", "qrm_plan.hip"]
-HEADERS = ["qrm_internal.h", "rs_lane.h", os.path.join("..", "..", "include", "qrm.h"),
+HEADERS = ["qrm_internal.h", "qrm_ctx.h", "rs_lane.h", os.path.join("..", "..", "include", "qrm.h"),
            os.path.join("..", "..", "include", "qrm_diag.h")]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",

@@ -40,3 +40,13 @@ def test_binding_does_not_touch_the_oracle():
     assert "oracle" not in src.replace("no CPU fallback", "")
     for f in os.listdir(os.path.join(os.path.dirname(b.__file__), "csrc")):
         assert "oracle" not in open(os.path.join(os.path.dirname(b.__file__), "csrc", f)).read()
+
+
+def test_every_included_header_makes_a_build_stale():
+    from paper_2509_02447_amd import build
+    csrc = os.path.normpath(build.CSRC)
+    known = {os.path.normpath(os.path.join(csrc, h)) for h in build.HEADERS}
+    for src in [f for f in os.listdir(csrc) if f.endswith((".hip", ".h"))]:
+        for name in re.findall(r'#include "([^"]+)"', open(os.path.join(csrc, src)).read()):
+            assert os.path.normpath(os.path.join(csrc, name)) in known, (src, name)
+    assert {f for f in os.listdir(csrc) if f.endswith(".hip")} == set(build.SOURCES)
