@@ -591,9 +591,11 @@ hipError_t launch_lane(const RsParams &p, const uint8_t *sym, int64_t N, uint8_t
         const int64_t blocks = std::min((N + threads - 1) / threads, kDecodeThreads / threads);
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), (unsigned)p.tab_bytes, s, p, sym, N, msg, cw, nerr, key);
     };
-    // Whole dwords and two full runs a workgroup: half as many copies of the tables.  2^20 words of RS(12,8), 256 / 512 / 1024 threads 12.8 / 12.2 /
-    // 12.7 us, 2^22 33.5 / 31.9 / 32.8; through LDS, 2^20 of RS(15,11) 19.6 / 22.3 / 24.1.
-    if (words && N >= 2 * kDecodeThreads) launch(rs_decode_lane_kernel<N4, true, 512>, 512);
+    // Whole dwords over GF(256), whose tables are 10 KB and more, and a full run a workgroup: half as many copies of the tables.  RS(12,8), 256 /
+    // 512 threads: 2^18 + 38 k words 5.6 / 5.7 us, 2^19 8.1 / 7.6, 786 k 10.2 / 9.4, 2^20 11.7 / 11.1, 1.5 M 14.3 / 14.5, 2^21 18.5 / 17.7, 2^22
+    // 31.0 / 29.2 (28 counts of 2^19 .. 2^23: 1.025 times as fast in the mean, 0.98 .. 1.08; RS(16,12) 1.05, RS(8,4) 1.01).  Not over smaller
+    // fields: over GF(16) 0.99 in the mean, 1.5 M words 12.8 / 13.6.  Nor through LDS: 2^20 of RS(15,11), 256 / 512 / 1024 threads 19.6 / 22.3 / 24.1.
+    if (words && p.q == 256 && N >= kDecodeThreads) launch(rs_decode_lane_kernel<N4, true, 512>, 512);
     else if (words) launch(rs_decode_lane_kernel<N4, true, 256>, 256);
     else launch(rs_decode_lane_kernel<N4, false, 256>, 256);
     return hipGetLastError();

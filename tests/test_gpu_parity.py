@@ -190,7 +190,7 @@ def test_rs_decode_random_code_parameters(qrm):
 @pytest.mark.parametrize("m,n,t", [(8, 8, 2), (8, 16, 2), (4, 15, 2), (4, 7, 1)])
 def test_rs_decode_short_words_in_several_runs(qrm, m, n, t):
     """Short words whose workgroups take one run, the next one while they decode, and a last run that is not full: counts around
-    one and two runs for each of them, where the workgroups become larger."""
+    one and two runs for each of them; from one on the workgroups are larger where whole dwords are over GF(256)."""
     code = dict(m=m, prim_poly={4: 0x13, 8: 0x11D}[m], n=n, k=n - 2 * t, fcr=1)
     one = 2048 * 256
     count = 2 * one + 513
@@ -198,7 +198,7 @@ def test_rs_decode_short_words_in_several_runs(qrm, m, n, t):
     words = oracle.rs_encode(msgs, **code) ^ err
     om, oc, oe = oracle.rs_decode(words, **code)
     ctx = qrm.Context(rs=code)
-    for N in (one, one + 1, 2 * one - 1, 2 * one, count):
+    for N in (one - 1, one, one + 1, 2 * one - 1, 2 * one, count):
         gm, gc, ge = gpu_rs_decode(ctx, words[:N])
         assert np.array_equal(ge, oe[:N]) and np.array_equal(gm, om[:N]) and np.array_equal(gc, oc[:N]), N
     ctx.close()
