@@ -3277,10 +3277,11 @@ static int chain_rounds(int C) { return C == 32 ? 5 : 1; }
 // what its rows take, while a launch per block has two round trips to memory, its weights and one strip behind the other.  With more
 // items it is the faster way at 32 channels where a tile of up to 32 columns is one item wide and half of a strip of 64.
 //   By estimates in microseconds, fitted to whole calls of two to nine blocks, 1 .. 512 tiles of 8 x 8 to 256 x 256: 724 shapes with
-// one item at most and 484 with up to five at 32 channels, 600 at 64; standard deviation 2 .. 5 % and, for more than one item, 7 %.  Of the
-// 303, 148 and 108 for which they say so the chain is 1.12, 1.21 and 1.06 times as fast in the mean (up to 1.4); 3 of these 559 are slower by
-// more than 2 %; of the others it would be faster by 1.17 at most.  The number of blocks matters: fitted to four and eight alone, the
-// rule took calls of two and three that are 1.1 and 1.0 .. 1.25 times as long this way.
+// one item at most and 484 with up to five at 32 channels, 600 at 64; standard deviation 2 .. 5 % and, for more than one item, 6 .. 9 %, where the
+// single blocks have to look 9 % slower (with 5 %, five of 75 calls taken were slower so, one by 10 %).  Of 534, 166 and 300 other
+// shapes 179, 40 and 66 are taken, 1.19, 1.26 and 1.07 times as fast in the mean (up to 1.6); one is slower by more than 2 % (37 tiles of 57 x 72, three
+// blocks, 3.5 %); of the others the chain would be faster by 1.21 at most.  The number of blocks matters: fitted to four and eight alone, the rule
+// took calls of two and three that are 1.1 and 1.0 .. 1.25 times as long this way.
 // Other ways / chain, us: 16 tiles of 32 x 32, 32 channels, four blocks 25.1 / 24.3, 256 of them 71.6 / 49.2; 390 of 29 x 12 90.3 / 66.7; 7 of
 // 128 x 128, 64 channels, eight blocks 110.7 / 105.7.  Not by the rule: 2 of 128 x 128, 32 channels 26.2 / 35.1; 4 of 128 x 128, 64 channels
 // 86.8 / 105.8 (an XCD has one image or none).  Narrow tiles at 64 channels have the fused pairs (one of 64 x 64 49.1 / 61.2, four 50.1 / 64.1).
@@ -3297,7 +3298,7 @@ bool conv_chain_faster(const ConvGeom &g, int C, const ChainPlan &p, int blocks,
         const double item_us = p.rows == 4 ? 3.44 : p.rows == 8 ? 4.59 : p.rows == 16 ? 5.6 : 8.46;
         return 12.9 + later * item_us + 395.0 * chunk_mpx < 0.95 * (9.0 + 47.6 * mpx + later * (3.6 + 1.66 * per + 4.7 * mpx));
     }
-    return 21.7 + 0.1 * items + later * (0.38 + 0.18 * items + 56.4 * chunk_mpx) < 0.95 * (15.6 + 16.3 * mpx + later * (4.54 + 1.36 * per + 1.0 * mpx));
+    return 21.7 + 0.1 * items + later * (0.38 + 0.18 * items + 56.4 * chunk_mpx) < 0.91 * (15.6 + 16.3 * mpx + later * (4.54 + 1.36 * per + 1.0 * mpx));
 }
 
 // The lines are those of the single blocks, an image's in the place of its activations.

@@ -16,6 +16,7 @@ def rule(channels, blocks, n, h, w, num_cu=256):
     ((32, 4, 16, 32, 32), True), ((32, 4, 256, 32, 32), True), ((32, 4, 390, 29, 12), True), ((64, 8, 7, 128, 128), True),
     ((32, 4, 2, 128, 128), False), ((64, 8, 4, 128, 128), False),   # an XCD has one image or none, of many items
     ((64, 8, 1, 64, 64), False), ((64, 8, 300, 16, 33), False),     # narrow tiles of 64 channels: fused pairs
+    ((32, 2, 272, 29, 12), False), ((32, 2, 147, 207, 10), False), ((32, 3, 139, 43, 13), False), ((32, 3, 22, 192, 82), False),  # 1.03 .. 1.1 times as long
     ((64, 8, 2048, 64, 64), False), ((32, 4, 4096, 32, 32), False), ((32, 2, 4, 250, 250), False)])
 def test_the_rule_takes_what_is_faster_so(case, taken):
     assert rule(*case)[1] == taken
