@@ -22,6 +22,10 @@
  *     QRM_OK no kernel of that call has been launched unless stated, and
  *     qrm_last_error() describes the reason.
  *   - N == 0 is a successful no-op.
+ *   - Outputs are the same bits from call to call, on any stream, and a tile's do not depend on the tiles around it as long as its
+ *     batch runs the same schedule: a launch per block and all blocks in one launch (batches of few tiles) give the same bits; two
+ *     blocks a launch (64 channels: tiles of up to 64 columns, wider ones in batches of about half as many as there are compute units
+ *     and more) round differently, within the tolerance, so that a bit whose logit is near zero may differ between the two.
  *   - A launch whose workgroups wait for each other gives up after seconds, which only happens where something else is wrong (calls
  *     that overlap on the workspace of qrm_detect_static, say).  Images that it has lost have NaN logits, zero bits and, where
  *     the words are decoded in the same launch, d_nerr -1, no matches and no detection; the next call that runs the extractor on the

@@ -26,7 +26,7 @@ extern "C" {
                                        small batches) */
 
 #define QRM_DIAG_CHAIN_ALWAYS 8     /* all blocks in one launch for every batch that such a launch takes, */
-#define QRM_DIAG_NO_CHAIN 16        /* or for none (A/B timing, tests; the schedules round differently) */
+#define QRM_DIAG_NO_CHAIN 16        /* or for none (A/B timing, tests; a launch per block gives the same bits) */
 
 /* Sets the context's diagnostic flags (0 = production behaviour).  Affects calls made afterwards. */
 QRM_API qrm_status qrm_diag_set_flags(qrm_ctx *ctx, int32_t flags);

@@ -144,7 +144,9 @@ struct ChainPlan {
     int chunk;           // images that an XCD takes at a time
     int64_t items;       // of a block of a chunk
 };
-constexpr int kChainCounters = 2048;                                  // images times blocks of a launch
+// Images times blocks of a launch: 128 bytes each, 256 KB for each of a context's nine workspaces.  Larger batches take the other ways
+// (512 images of four blocks fit, 409 of five, 256 of eight).
+constexpr int kChainCounters = 2048;
 constexpr size_t kChainStateBytes = (size_t)(9 * 32 + kChainCounters * 32) * 4; // what a launch keeps beside the workspace
 // That memory when the launch behind conv_chain's is to clear it (words null: it is not), and what the launch was about.
 struct ChainState {

@@ -525,7 +525,7 @@ bool preprocess_supported(int H_in, int W_in, int x, int T)
 
 // Strips a T x T window is cut into when a launch has N of them.  Enough workgroups for one wave over the chip (eight fit a compute
 // unit); beyond it short strips, so that the rows that are read at a time lie together and no last wave is nearly empty: 600
-// images of 480 x 640 to 256 x 256 125 us in 4 strips, 121 in 8, 115 in 16, 111 in 32; 4069 of 128 x 128 456 in 2, 432 in 32.
+// images of 480 x 640 to 256 x 256 125 us in 4 strips, 121 in 8, 115 in 16, 111 in 32.
 // But a strip's column taps are its own: two turns of 256 pixel groups for each, four where a window has less than 16 (1024
 // windows of 64 x 64 out of 512 x 512 13.7 us in 1 to 4 strips, 14.8 in 8; 2048 of them 17.8 in one, 23.3 in 8; 3000 of 30 x 30
 // 10.4 in one, 12.0 in two; 1024 of 128 x 128 out of 300 x 300 24.5 in 4, 25.3 in 8, 29.8 in 16, out of 480 x 480 44.0, 42.3, 38.4).
