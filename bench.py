@@ -36,11 +36,11 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, published
 # size (the summary under profiles/ gives the commands), at the commit named.  A record applies only while the
 # kernel's source and the images per launch it was taken on are unchanged; otherwise the line reports null.
 RECORDED_TRAFFIC = {
-    "commit": "2d7ed5f", "kernels": "b95edbaddb6d", "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt",
+    "commit": "3dfae7d", "kernels": "cb04cd62f597", "source": "profiles/conv_pair_c2_c3_c4_hbm_traffic.txt",
     # (configuration, launch kind): (images per launch, bytes per launch)
-    ("C2", "pair_first"): (1024, 574375373), ("C2", "pair_mid"): (1024, 1079884485), ("C2", "pair_last"): (1024, 551400486),
-    ("C3", "pair_first"): (256, 2417710298), ("C3", "pair_mid"): (256, 4472742248), ("C3", "pair_last"): (256, 2345247792),
-    ("C4", "pair_first"): (256, 599851391), ("C4", "pair_mid"): (256, 1108852476), ("C4", "pair_last"): (256, 579964779),
+    ("C2", "pair_first"): (1024, 574375373), ("C2", "pair_mid"): (1024, 1079881516), ("C2", "pair_last"): (1024, 551411411),
+    ("C3", "pair_first"): (256, 2417714838), ("C3", "pair_mid"): (256, 4472741442), ("C3", "pair_last"): (256, 2345259456),
+    ("C4", "pair_first"): (256, 599851295), ("C4", "pair_mid"): (256, 1108852932), ("C4", "pair_last"): (256, 579980062),
 }
 
 

@@ -1,5 +1,8 @@
 """The benchmark's recorded traffic figures: they hold for the kernels and launch sizes that they were taken on, no others."""
 import os
+import subprocess
+
+import pytest
 
 import bench
 
@@ -21,3 +24,17 @@ def test_the_kernels_key_follows_the_code_and_not_its_comments():
     assert bench.kernel_source_key([texts[0].replace("kChunk = 4", "kChunk = 8"), texts[1]]) != key
     assert bench.kernel_source_key([texts[0], "int b;"]) != key
     assert len(bench.kernel_source_key()) == 12
+
+
+def test_the_record_names_the_commit_whose_kernels_it_was_taken_on():
+    """The key is that of the sources at the commit named, and the summary names the same commit."""
+    commit, csrc = bench.RECORDED_TRAFFIC["commit"], "paper_2509_02447_amd/csrc/"
+    path = os.path.join(bench.ROOT, bench.RECORDED_TRAFFIC["source"])
+    if os.path.exists(path):
+        assert f"sources at commit {commit}" in open(path).readline()
+    git = ["git", "-C", bench.ROOT]
+    if subprocess.run(git + ["cat-file", "-e", commit], capture_output=True).returncode:
+        pytest.skip("the history is not here")
+    texts = [subprocess.run(git + ["show", f"{commit}:{csrc}{f}"], capture_output=True, text=True, check=True).stdout
+             for f in ("extractor.hip", "qrm_internal.h")]
+    assert bench.kernel_source_key(texts) == bench.RECORDED_TRAFFIC["kernels"]
