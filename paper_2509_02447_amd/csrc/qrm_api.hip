@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -56,6 +57,49 @@ qrm_status hip_fail(qrm_ctx *c, hipError_t e, const char *what)
 } // namespace qrm
 
 namespace {
+
+// Page-locked words that kernels write and the host reads, one to a context.  Page-locking takes 130 us, a tenth of qrm_create, so the
+// contexts of a device share pages, which stay for the process: as many as its most contexts at a time have needed.
+struct HostWords {
+    uint32_t *host = nullptr, *dev = nullptr;
+    std::vector<int> free;
+};
+constexpr int kHostWords = 1024; // of a page
+std::mutex g_host_words_mutex;
+std::vector<std::vector<HostWords>> g_host_words; // [device][page]
+
+void take_host_word(int device, uint32_t **host, uint32_t **dev)
+{
+    std::lock_guard<std::mutex> lock(g_host_words_mutex);
+    *host = *dev = nullptr;
+    if (g_host_words.size() <= (size_t)device) g_host_words.resize(device + 1);
+    std::vector<HostWords> &pages = g_host_words[device];
+    auto page = std::find_if(pages.begin(), pages.end(), [](const HostWords &p) { return !p.free.empty(); });
+    if (page == pages.end()) {
+        HostWords fresh;
+        if (hipHostMalloc((void **)&fresh.host, kHostWords * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess ||
+            hipHostGetDevicePointer((void **)&fresh.dev, fresh.host, 0) != hipSuccess) {
+            if (fresh.host) (void)hipHostFree(fresh.host);
+            (void)hipGetLastError();
+            return;
+        }
+        for (int i = kHostWords - 1; i >= 0; --i) fresh.free.push_back(i);
+        page = pages.insert(pages.end(), fresh);
+    }
+    const int i = page->free.back();
+    page->free.pop_back();
+    *host = page->host + i;
+    *dev = page->dev + i;
+    **host = 0;
+}
+
+void give_host_word(int device, uint32_t *host)
+{
+    if (!host) return;
+    std::lock_guard<std::mutex> lock(g_host_words_mutex);
+    for (HostWords &p : g_host_words[device])
+        if (host >= p.host && host < p.host + kHostWords) p.free.push_back((int)(host - p.host));
+}
 
 // Non-negative integers of a few thousand bits, just enough for exact binomial tails.
 struct Big {
@@ -707,13 +751,7 @@ qrm_status qrm_create(const qrm_extractor_desc *ext, const qrm_rs_desc *rs, int 
         if (e == hipSuccess)
             e = hipMemcpy((uint8_t *)c->d_weights + frag_bytes, fl.data(), fl.size() * 4, hipMemcpyHostToDevice);
         if (e != hipSuccess) { (void)hipFree(c->d_weights); delete c; return hip_fail(nullptr, e, "hipMemcpy(weights)"); }
-        if (hipHostMalloc((void **)&c->h_lost, sizeof *c->h_lost, hipHostMallocDefault) == hipSuccess) {
-            *c->h_lost = 0;
-            if (hipHostGetDevicePointer((void **)&c->d_lost, c->h_lost, 0) != hipSuccess) c->d_lost = nullptr;
-        } else {
-            c->h_lost = nullptr;
-        }
-        (void)hipGetLastError(); // (without it, an image whose items are missing has its NaN logits all the same)
+        take_host_word(device, &c->h_lost, &c->d_lost); // (without one, an image whose items are missing has its NaN logits all the same)
         for (QrmSlot &sl : c->slots) sl.chain.words = (uint32_t *)((uint8_t *)c->d_weights + chain_at + (&sl - c->slots) * kChainStateBytes);
         const bf16_t *fb = (const bf16_t *)c->d_weights;
         c->d_w_first = fb + frag_off[0];
@@ -778,7 +816,7 @@ void qrm_destroy(qrm_ctx *c)
         if (s) (void)hipStreamDestroy(s);
     if (c->d_weights) (void)hipFree(c->d_weights);
     if (c->d_tables) (void)hipFree(c->d_tables);
-    if (c->h_lost) (void)hipHostFree(c->h_lost);
+    give_host_word(c->device, c->h_lost);
     delete c;
 }
 

@@ -47,7 +47,7 @@ struct qrm_ctx {
     const float *d_wft = nullptr;         // final conv, fp32, [C*9][nbp]
     bool collapse = false;                // final conv + pool evaluated in closed form from channel sums
     bool pairable = false;                // weights are prepared for the fused schedule (see qrm_create)
-    uint32_t *h_lost = nullptr, *d_lost = nullptr; // page-locked: a launch has given up waiting for its own workgroups (report_lost)
+    uint32_t *h_lost = nullptr, *d_lost = nullptr; // page-locked word: a launch has given up waiting for its own workgroups (report_lost)
     // code
     qrm::RsParams rs{};
     void *d_tables = nullptr;             // key symbols [kKeyBytes], then the code's table image (rs_table_image)

@@ -603,6 +603,32 @@ def test_a_wait_that_runs_out_is_reported(qrm, static):
     ctx.close()
 
 
+def test_a_wait_that_runs_out_is_reported_to_its_own_context(qrm):
+    """Contexts alive at once, and those that get a closed one's place: only the one whose launch gave up hears of it."""
+    wts = small_weights(32, 3, 24, 5)
+    tiles = dev(np.random.default_rng(3).integers(0, 256, size=(6, 3, 21, 30), dtype=np.uint8))
+    d_log = empty((6, 24), torch.float32)
+    make = lambda: qrm.Context(weights=wts)
+    run = lambda c: (c.qrm_extractor_forward(tiles, 6, 21, 30, d_log, None), torch.cuda.synchronize())
+    ctxs = [make() for _ in range(3)]
+    for c in ctxs:
+        c.qrm_diag_set_flags(qrm.binding.QRM_DIAG_CHAIN_ALWAYS)
+        run(c)
+    ctxs[1].qrm_diag_chain_patience(4000)
+    ctxs[1].qrm_diag_chain_count(False, 4, 0xFFFFFFFF)
+    run(ctxs[1])
+    assert torch.isnan(d_log[4]).all()
+    run(ctxs[0])
+    run(ctxs[2])
+    ctxs[1].close()                        # without having been told
+    fresh = [make() for _ in range(2)]
+    for c in fresh + [ctxs[0], ctxs[2]]:
+        run(c)
+    assert torch.isfinite(d_log).all()
+    for c in fresh + ctxs:
+        c.close()
+
+
 @pytest.mark.parametrize("static", [False, True])
 def test_what_a_failed_call_left_is_cleared_by_work_that_runs(qrm, static):
     """The state of an all-blocks launch whose clearing launch never came: the next call clears it, and one that is only recorded into a
