@@ -557,6 +557,26 @@ def test_all_blocks_in_one_launch(qrm, C, nb, N, h, w, relu):
     check_logits(chain[0][:few], ref, what=f"chain C={C} {h}x{w}")
 
 
+@pytest.mark.parametrize("C,nb,h,w,counts", [(64, 8, 128, 128, (1, 4, 7, 8, 9, 40)), (64, 5, 16, 74, (1, 26, 33, 100)), (32, 4, 32, 32, (1, 16, 256, 600))])
+def test_logits_do_not_depend_on_the_number_of_tiles(qrm, C, nb, h, w, counts):
+    """Batches on both sides of the rule that sends them through all blocks in one launch: the same tile gives the same bits."""
+    wts = small_weights(C, nb, 24, w)
+    tiles = dev(np.random.default_rng(h).integers(0, 256, size=(max(counts), 3, h, w), dtype=np.uint8))
+    ctx = qrm.Context(weights=wts)
+    ctx.qrm_profile_enable(True)
+    got, chains = {}, set()
+    for n in counts:
+        before = ctx.qrm_profile_read(qrm.binding.QRM_PROFILE_CHAIN)[1]
+        got[n] = empty((n, 24), torch.float32)
+        ctx.qrm_extractor_forward(tiles[:n], n, h, w, got[n], None)
+        torch.cuda.synchronize()
+        chains.add(ctx.qrm_profile_read(qrm.binding.QRM_PROFILE_CHAIN)[1] - before)
+    assert chains == {0, 1}   # some went that way, some did not
+    for n in counts:
+        assert torch.equal(got[n], got[max(counts)][:n]), n
+    ctx.close()
+
+
 def chain_buffers(cfg, n):
     return (empty((n, cfg.n_bits), torch.float32), empty((n, cfg.n_bits), torch.uint8), empty((n, cfg.k), torch.uint8),
             empty((n, cfg.n), torch.uint8), empty((n,), torch.int8))
